@@ -1,6 +1,7 @@
-"""Thin ctypes binding of libpvq (see include/pvq.h).  Argument marshalling only: every step of
+"""Thin binding of libpvq (see include/pvq.h).  Argument marshalling only: every step of
 encode / decode / decode_gemv runs in the library's kernels.  PyTorch supplies device memory and
-the stream."""
+the stream.  The calls on tensors go through _pvq_torch (csrc/pvq_torch.cpp), everything else through
+ctypes."""
 from __future__ import annotations
 
 import ctypes as C
@@ -80,6 +81,21 @@ def lib():
     return _lib
 
 
+_native_module = None
+
+
+def _native():
+    """The native half of the calls on tensors (built with the library; an error if it is missing)."""
+    global _native_module
+    if _native_module is None:
+        lib()
+        if not os.path.exists(_build.TORCH_PATH):
+            _build.build()
+        from . import _pvq_torch
+        _native_module = _pvq_torch
+    return _native_module
+
+
 def _check(status: int, where: str):
     if status != 0:
         raise PvqError(status, where)
@@ -157,14 +173,7 @@ def pvq_size_table_device(D: int, K: int, words: int, device=None):
 def pvq_hadamard(X, block: int, signs=None, inverse: bool = False, out=None, out_dtype=None):
     """Randomised Hadamard rotation of every row of the 2-D device tensor X (float32 or bfloat16) in
     blocks of `block` columns, or its inverse.  signs: uint8 device tensor [cols] (non-zero = -1) or None."""
-    import torch
-    rows, cols = X.shape
-    if out is None:
-        out = torch.empty((rows, cols), dtype=out_dtype or X.dtype, device=X.device)
-    _check(lib().pvq_hadamard(_ptr(X), _dtype_code(X), rows, cols, X.stride(0) if rows > 1 else cols, block,
-                              _ptr(signs), 1 if inverse else 0, _ptr(out), _dtype_code(out),
-                              out.stride(0) if rows > 1 else cols, _stream_ptr()), "pvq_hadamard")
-    return out
+    return _result((_native_module or _native()).hadamard(X, block, signs, inverse, out, out_dtype), "pvq_hadamard")
 
 
 # ------------------------------------------------------------------ context
@@ -233,13 +242,14 @@ def pvq_packed_sizes(ctx: PvqContext, rows: int, cols: int):
 
 
 def _stream_ptr():
-    import torch
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    return C.c_void_p((_native_module or _native()).stream())
 
 
-def _dtype_code(t):
-    import torch
-    return {torch.float32: PVQ_F32, torch.float16: PVQ_F16, torch.bfloat16: PVQ_BF16}[t.dtype]
+def _result(r, where: str):
+    """What a native call returned: its result, or (an int) the status of a call that failed."""
+    if r.__class__ is int:
+        _check(r, where)
+    return r
 
 
 def _ptr(t):
@@ -272,24 +282,24 @@ def pvq_encode(ctx: PvqContext, W, out: Packed = None, want_pulses: bool = False
     """W: 2-D float32 or bfloat16 device tensor with unit column stride."""
     rows, cols = W.shape
     assert W.stride(1) == 1 or cols <= 1
-    if out is None:
+    if out is None and want_pulses:
         out = alloc_packed(ctx, rows, cols, W.device, want_pulses)
-    ld = W.stride(0) if rows > 1 else max(cols, 1)
-    _check(lib().pvq_encode(ctx.handle, _ptr(W), _dtype_code(W), rows, cols, ld, _ptr(out.index),
-                            _ptr(out.scale), _ptr(out.rownorm), _ptr(out.pulses), _stream_ptr()),
-           "pvq_encode")
+    native = _native_module or _native()
+    if out is None:
+        return Packed(rows, cols, *_result(native.encode(ctx._h.value, W, None, None, None, None), "pvq_encode"))
+    _result(native.encode(ctx._h.value, W, out.index, out.scale, out.rownorm, out.pulses), "pvq_encode")
     return out
 
 
 def pvq_rotate_encode(ctx: PvqContext, X, block: int, signs=None, out: Packed = None) -> Packed:
     """Randomised Hadamard rotation of the rows of X (blocks of `block` columns) and encoding of the rotated
     values, in one kernel.  X: 2-D float32 or bfloat16 device tensor; signs: uint8 device tensor [cols] or None."""
-    rows, cols = X.shape
+    native = _native_module or _native()
     if out is None:
-        out = alloc_packed(ctx, rows, cols, X.device)
-    ld = X.stride(0) if rows > 1 else max(cols, 1)
-    _check(lib().pvq_rotate_encode(ctx.handle, _ptr(X), _dtype_code(X), rows, cols, ld, block, _ptr(signs),
-                                   _ptr(out.index), _ptr(out.scale), _ptr(out.rownorm), _stream_ptr()), "pvq_rotate_encode")
+        rows, cols = X.shape
+        return Packed(rows, cols, *_result(native.rotate_encode(ctx._h.value, X, block, signs, None, None, None),
+                                           "pvq_rotate_encode"))
+    _result(native.rotate_encode(ctx._h.value, X, block, signs, out.index, out.scale, out.rownorm), "pvq_rotate_encode")
     return out
 
 
@@ -349,27 +359,11 @@ def pvq_correct_static(ctx: PvqContext, W, U):
 
 def pvq_decode(ctx: PvqContext, packed: Packed, out_dtype=None, out=None):
     """Returns the decoded [rows][cols] tensor of out_dtype (torch.float32/float16/bfloat16)."""
-    import torch
-    if out is None:
-        out = torch.empty((packed.rows, packed.cols), dtype=out_dtype or torch.float32,
-                          device=packed.index.device)
-    ld = out.stride(0) if packed.rows > 1 else max(packed.cols, 1)
-    _check(lib().pvq_decode(ctx.handle, _ptr(packed.index), _ptr(packed.scale), _ptr(packed.rownorm),
-                            packed.rows, packed.cols, _ptr(out), _dtype_code(out), ld, _stream_ptr()),
-           "pvq_decode")
-    return out
+    return _result((_native_module or _native()).decode(ctx._h.value, packed.index, packed.scale, packed.rownorm,
+                                                        packed.rows, packed.cols, out_dtype, out), "pvq_decode")
 
 
 def pvq_decode_gemv(ctx: PvqContext, packed: Packed, x, out=None):
     """x: bfloat16 [batch][cols] device tensor; returns float32 [batch][rows]."""
-    import torch
-    batch = x.shape[0]
-    assert x.dtype == torch.bfloat16 and x.shape[1] == packed.cols
-    if out is None:
-        out = torch.empty((batch, packed.rows), dtype=torch.float32, device=x.device)
-    ldx = x.stride(0) if batch > 1 else max(packed.cols, 1)
-    ldy = out.stride(0) if batch > 1 else max(packed.rows, 1)
-    _check(lib().pvq_decode_gemv(ctx.handle, _ptr(packed.index), _ptr(packed.scale),
-                                 _ptr(packed.rownorm), packed.rows, packed.cols, _ptr(x), batch, ldx,
-                                 _ptr(out), ldy, _stream_ptr()), "pvq_decode_gemv")
-    return out
+    return _result((_native_module or _native()).decode_gemv(ctx._h.value, packed.index, packed.scale, packed.rownorm,
+                                                             packed.rows, packed.cols, x, out), "pvq_decode_gemv")
