@@ -321,84 +321,75 @@ extern "C" int pvq_ctx_create(pvq_ctx **out, int D, int K, int scale_bits, const
         }
     }
 
-    // tab_n[dp][k] = N(dp,k); tab_u[dp][k+1] = N(dp,0) + ... + N(dp,k), tab_u[dp][0] = 0.
-    // Every entry is below N(D,K) (the pyramid of one more dimension contains all of them), so it
-    // fits `words` words.
-    std::vector<uint32_t> hn, hu, hc, hkey;
+    // tab_u[dp][k+1] = N(dp,0) + ... + N(dp,k), tab_u[dp][0] = 0.  Every entry is below N(D,K) (the pyramid of one
+    // more dimension contains all of them), so it fits `words` words.
+    std::vector<uint32_t> hu;
+    size_t near_at = 0, key_at = 0, guess_at = 0;    // wide: where the other tables lie behind the thresholds, in words
     if (wide) {
-        // tab_n[d][k] = N(d,k), d = 0..D;  tab_u[d][k] = 2 (N(d,0) + ... + N(d,k)) mod 2^(32 words), d = 0..D-1
-        hn.resize((size_t)(D + 1) * (K + 1) * words);
-        hu.resize((size_t)D * (K + 1) * words);
-        for (int d = 0; d <= D; d++) {
-            U512 run;
-            for (int k = 0; k <= K; k++) {
-                const U512 &v = t.at(d, k);
-                run.add(v);
-                U512 twice = run;
-                twice.add(run);
-                for (int w = 0; w < words; w++) {
-                    hn[((size_t)d * (K + 1) + k) * words + w] = v.word(w);
-                    if (d < D) hu[((size_t)d * (K + 1) + k) * words + w] = twice.word(w);
+        // The thresholds T_j of every row (pvq_internal.h): T_{2C} = 2 (N(dp,0) + ... + N(dp,C-1)), T_{2C+1} = T_{2C} +
+        // N(dp,C); none is above N(dp+1,K).
+        const int row = pvq_wide_row(K), krow = pvq_wide_key_row(K), buckets = pvq_wide_buckets(words);
+        const size_t nears = (size_t)D * row + 64;    // (the decoder reads 128 at a time, and uses 64)
+        near_at = (size_t)D * row * words;
+        key_at = near_at + 2 * nears;
+        guess_at = key_at + (size_t)D * krow;
+        hu.assign(guess_at + (size_t)D * buckets / 2, 0xFFFFFFFFu);
+        double *near = reinterpret_cast<double *>(&hu[near_at]);
+        uint16_t *guess = reinterpret_cast<uint16_t *>(&hu[guess_at]);
+        std::fill(near, near + nears, (double)INFINITY);
+        for (int dp = 0; dp < D; dp++) {
+            uint32_t *key = &hu[key_at + (size_t)dp * krow];
+            U512 even;                           // T_{2C}
+            for (int C = 0; C <= K; C++) {
+                const U512 &n = t.at(dp, C);
+                U512 odd = even;
+                odd.add(n);
+                for (int h = 0; h < 2; h++) {
+                    const U512 &v = h ? odd : even;
+                    uint32_t *out = &hu[((size_t)dp * row + 2 * C + h) * words];
+                    for (int w = 0; w < words; w++) out[w] = v.word(w);
+                    key[2 * C + h] = pvq_wide_key(out, words);
+                    near[(size_t)dp * row + 2 * C + h] = pvq_wide_double(out, words);
                 }
+                even = odd;
+                even.add(n);
+            }
+            // A bucket's guess: the last threshold whose key lies below every key of the bucket (bucket 8 is the first
+            // with a key above 0).
+            for (int j = 0, from = 0; j < 2 * K + 2; j++) {
+                const int to = j + 1 == 2 * K + 2 ? buckets : std::max(8, (int)(key[j + 1] >> 22) * 8 + (int)(key[j + 1] >> 18 & 7) + 1);
+                if (to > from) std::fill(guess + (size_t)dp * buckets + from, guess + (size_t)dp * buckets + to, (uint16_t)j);
+                from = std::max(from, to);
             }
         }
-        hkey.resize((size_t)D * (K + 1));
-        for (size_t i = 0; i < hkey.size(); i++) hkey[i] = pvq_wide_key(&hu[i * words], words);
-        // The encoders' table: what a cell (d,k) of the walk adds to the index, in its four forms
-        //   N,  -E,  N - E,  2N - E   (modulo 2^(32 words); E = 0 in row D, whose cell only ever adds N),
-        // entry ((d (K+1) + k) 4 + form) of `words` words.
-        hc.resize((size_t)(D + 1) * (K + 1) * 4 * words);
-        for (int d = 0; d <= D; d++)
-            for (int k = 0; k <= K; k++) {
-                const uint32_t *n = &hn[((size_t)d * (K + 1) + k) * words];
-                const uint32_t *ev = d < D ? &hu[((size_t)d * (K + 1) + k) * words] : nullptr;
-                uint32_t *out = &hc[((size_t)d * (K + 1) + k) * 4 * words];
-                for (int form = 0; form < 4; form++) {
-                    const int times = form == 0 ? 1 : form - 1;          // how often N counts: 1, 0, 1, 2
-                    uint64_t carry = 0;
-                    int64_t borrow = 0;
-                    for (int w = 0; w < words; w++) {
-                        const uint64_t add = (uint64_t)n[w] * (uint64_t)times + carry;
-                        carry = add >> 32;
-                        const int64_t sub = (int64_t)(add & 0xFFFFFFFFu) - (form > 0 && ev ? (int64_t)ev[w] : 0) - borrow;
-                        borrow = sub < 0 ? 1 : 0;
-                        out[(size_t)form * words + w] = (uint32_t)sub;
-                    }
-                }
-            }
     } else {
-        hn.resize((size_t)D * (K + 1) * words);
         hu.resize((size_t)D * (K + 2) * words);
     }
     for (int dp = 0; dp < D && !wide; dp++) {
         U512 run;  // running sum
         for (int w = 0; w < words; w++) hu[((size_t)dp * (K + 2)) * words + w] = 0;
         for (int k = 0; k <= K; k++) {
-            const U512 &v = t.at(dp, k);
-            run.add(v);
-            for (int w = 0; w < words; w++) {
-                hn[((size_t)dp * (K + 1) + k) * words + w] = v.word(w);
-                hu[((size_t)dp * (K + 2) + k + 1) * words + w] = run.word(w);
-            }
+            run.add(t.at(dp, k));
+            for (int w = 0; w < words; w++) hu[((size_t)dp * (K + 2) + k + 1) * words + w] = run.word(w);
         }
     }
 
     pvq_ctx *c = new (std::nothrow) pvq_ctx();
     if (!c) return PVQ_E_NOMEM;
     c->D = D; c->K = K; c->index_bits = bits; c->words = words; c->scale_bits = scale_bits; c->wide = wide ? 1 : 0;
-    c->tab_n = c->tab_u = c->tab_c = c->tab_key = nullptr; c->edges = c->sqrtc = nullptr; c->fast8_blob = c->fast8g_blob = nullptr; c->enc8_offs = nullptr; c->amplitude = PVQ_AMP_NORM;
-    c->tab_n_bytes = hn.size() * 4; c->tab_u_bytes = hu.size() * 4;
+    c->tab_u = nullptr; c->tab_key = nullptr; c->tab_near = nullptr; c->tab_guess = nullptr;
+    c->edges = c->sqrtc = nullptr; c->fast8_blob = c->fast8g_blob = nullptr; c->enc8_offs = nullptr; c->amplitude = PVQ_AMP_NORM;
+    U512 last = t.at(D, K);
+    last.decrement();
+    for (int w = 0; w < 16; w++) c->last_index[w] = last.word(w);
 
     hipError_t e = hipGetDevice(&c->device);
-    if (e == hipSuccess) e = hipMalloc((void **)&c->tab_n, c->tab_n_bytes);
-    if (e == hipSuccess) e = hipMalloc((void **)&c->tab_u, c->tab_u_bytes);
-    if (e == hipSuccess) e = hipMemcpy(c->tab_n, hn.data(), c->tab_n_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->tab_u, hu.data(), c->tab_u_bytes, hipMemcpyHostToDevice);
-    if (e == hipSuccess && !hc.empty()) {
-        e = hipMalloc((void **)&c->tab_c, hc.size() * 4);
-        if (e == hipSuccess) e = hipMemcpy(c->tab_c, hc.data(), hc.size() * 4, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMalloc((void **)&c->tab_key, hkey.size() * 4);
-        if (e == hipSuccess) e = hipMemcpy(c->tab_key, hkey.data(), hkey.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMalloc((void **)&c->tab_u, hu.size() * 4);
+    if (e == hipSuccess) e = hipMemcpy(c->tab_u, hu.data(), hu.size() * 4, hipMemcpyHostToDevice);
+    if (e == hipSuccess && wide) {
+        c->tab_near = reinterpret_cast<const double *>(c->tab_u + near_at);
+        c->tab_key = c->tab_u + key_at;
+        c->tab_guess = reinterpret_cast<const uint16_t *>(c->tab_u + guess_at);
     }
     if (e == hipSuccess && scale_bits) {
         // the edge table is padded to 2^b entries with +inf so that kernels may read a full table
@@ -458,7 +449,7 @@ extern "C" int pvq_ctx_destroy(pvq_ctx *c)
 {
     if (!c) return PVQ_OK;
     hipError_t first = hipSuccess;
-    void *ptrs[10] = {c->tab_key, c->tab_n, c->tab_u, c->tab_c, c->edges, c->sqrtc, c->fast8_blob, c->fast8g_blob, c->walk_blob, c->enc8_offs};
+    void *ptrs[7] = {c->tab_u, c->edges, c->sqrtc, c->fast8_blob, c->fast8g_blob, c->walk_blob, c->enc8_offs};
     for (void *p : ptrs) {
         if (!p) continue;
         hipError_t e = hipFree(p);

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <cmath>
 #include <mutex>
 #include <stdint.h>
 
@@ -42,25 +43,49 @@ inline uint32_t pvq_wide_key(const uint32_t *w, int words)
     return ((uint32_t)(32 * t + 32 - lead) << 22) | (top >> 10);
 }
 
+// A multi-word integer as a float64 that orders like the integer wherever they differ: its highest word that is not
+// zero and the one below, rounded to nearest (the same for every integer, so equal values decide nothing).
+inline double pvq_wide_double(const uint32_t *w, int words)
+{
+    int t = words - 1;
+    while (t > 0 && w[t] == 0) t--;
+    return ldexp((double)w[t] * 4294967296.0 + (t > 0 ? (double)w[t - 1] : 0.0), 32 * t - 32);   // (the product is exact)
+}
+
+// Contexts with D = 64 or 128.  With U(d,x) = N(d,0) + ... + N(d,x) and q = N(d,k) - 1 - r for the residual r in the
+// sub-pyramid of d dimensions and k pulses, the points that leave C pulses to the d - 1 coordinates behind lie at
+//     2 U(d-1,C-1) <= q < 2 U(d-1,C),
+// the negative ones (q - 2 U(d-1,C-1) < N(d-1,C)) first; C = k, the magnitude 0, has that half only.  So row d - 1 is
+// one ascending sequence of thresholds
+//     T_{2C} = 2 U(d-1,C-1),  T_{2C+1} = T_{2C} + N(d-1,C),      C = 0 .. K,
+// a coordinate of the point is its position j in it (C = j / 2 pulses left, positive iff j is odd), the next q is
+// q - T_j, and after the last coordinate q = 0.  Hence N(D,K) - 1 - index = the sum of the thresholds of all
+// coordinates: the encoders add them up, the decoders find them one after the other.
+// Rows are at least as long as the windows of 64 that a decoder reads, with all ones behind the thresholds.
+inline int pvq_wide_row(int K) { return K < 31 ? 64 : 2 * K + 2; }
+inline int pvq_wide_key_row(int K) { return 2 * K + 2 + 6; }
+// The other decoder's first guess: keys by bit length and the three bits behind the leading one (their bits 18 to 31, less 21).
+inline int pvq_wide_buckets(int words) { return (32 * words + 1) * 8; }
+
 struct pvq_ctx {
     int D, K;
     int index_bits;
     int words;       // 32-bit words of one table entry / one index in registers: 1, 2 or 4 (wide: 4..16)
-    int wide;        // 1: D = 64 or 128; tab_n[d][k] = N(d,k) for d = 0..D, tab_u[d][k] = 2 (N(d,0)+...+N(d,k))
-                     //    mod 2^(32 words) for d = 0..D-1, both [.][K+1][words]; kernels in pvq_wide.hip
+    int wide;        // 1: D = 64 or 128; kernels in pvq_wide.hip
     int scale_bits;  // 0 = float32 amplitudes
     int device;
     // Device tables.  Entries are `words` little-endian 32-bit words.
-    //   tab_n[dp][k]  = N(dp, k),                      dp = 0..D-1, k = 0..K        (App. B.3 walks it)
-    //   tab_u[dp][k+1] = sum_{i=0..k} N(dp, i), tab_u[dp][0] = 0,  k = -1..K         (cumulative form of
+    //   tab_u[dp][k+1] = sum_{i=0..k} N(dp, i), tab_u[dp][0] = 0,  dp = 0..D-1, k = -1..K  (cumulative form of
     //                    App. C.2's V table, shifted so that the empty sum is an entry)
-    uint32_t *tab_n;
+    //   wide: tab_u[dp][j] = T_j of row dp, j = 0 .. 2K+1 (rows of pvq_wide_row entries); tab_key[dp][j] = pvq_wide_key of it
+    //         (rows of pvq_wide_key_row words); tab_guess[dp][bucket] = the last j whose key lies below the bucket
     uint32_t *tab_u;
-    uint32_t *tab_c;   // wide only: [D+1][K+1][4][words], the four forms N, -E, N-E, 2N-E of a cell (encoders)
-    uint32_t *tab_key; // wide only: [D][K+1], pvq_wide_key of tab_u's entries (the decoder's search)
+    const uint32_t *tab_key;   // (this and the next two: behind the thresholds, in tab_u's allocation)
+    const uint16_t *tab_guess;
+    const double *tab_near;    // wide: pvq_wide_double of tab_u's entries (behind a row's thresholds: infinity)
+    uint32_t last_index[16];   // N(D,K) - 1
     float *edges;   // 2^scale_bits - 1 float32 edges (or nullptr)
     float *sqrtc;   // 2^scale_bits float32 sqrt(centers) (or nullptr)
-    size_t tab_n_bytes, tab_u_bytes;
     // Table-driven decoder (D = 8, one-word indices, tables that fit LDS); fast8_blob == nullptr
     // when the configuration has none.  Two flavours of the tables: all of them in one LDS copy (the
     // decode kernel), and S0's block table kept in device memory (the fused product; nullptr if

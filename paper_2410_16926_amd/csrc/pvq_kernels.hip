@@ -24,8 +24,7 @@ template <> struct wide<2> { using type = uint64_t; };
 template <> struct wide<4> { using type = unsigned __int128; };
 
 struct tables_t {
-    const uint32_t *tab_n;  // [D][K+1] entries of W words
-    const uint32_t *tab_u;  // [D][K+2]
+    const uint32_t *tab_u;  // [D][K+2] entries of W words
     const float *edges;     // 2^scale_bits (last = +inf)
     const float *sqrtc;     // 2^scale_bits
     int K, index_bits, scale_bits;
@@ -259,7 +258,7 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(tables_t tb, pvq_encod
 tables_t make_tables(const pvq_ctx *c)
 {
     tables_t t;
-    t.tab_n = c->tab_n; t.tab_u = c->tab_u; t.edges = c->edges; t.sqrtc = c->sqrtc;
+    t.tab_u = c->tab_u; t.edges = c->edges; t.sqrtc = c->sqrtc;
     t.K = c->K; t.index_bits = c->index_bits; t.scale_bits = c->scale_bits;
     return t;
 }

@@ -4,28 +4,20 @@
 // small groups).  The size table no longer fits LDS (1.2 MB for (128,187)); it is read from device
 // memory, where the L2 keeps it.
 //
-// Tables of W-word integers (W = 4, 8, 12 or 16; arithmetic is modulo 2^(32W), every true result
-// fits):  N(d,k), and E(d,k) = 2 (N(d,0) + ... + N(d,k)).  With them the number of points of P(d,k)
-// whose first coordinate has magnitude below m >= 1 is  A(m) = N(d,k) - E(d-1,k-m)  (all points minus
-// those of magnitude m or more, two signs each), so that, in the order 0, +1, -1, +2, -2, ... of
-// App. B.2, a first coordinate +m has A(m) points before it and -m has A(m) + N(d-1,k-m).
+// One table of W-word integers (W = 4, 8, 12 or 16) serves both directions: the thresholds T_j of every row
+// (pvq_internal.h), of which a coordinate of the point is one, so that N(D,K) - 1 - index is the sum over the
+// coordinates.
 //
 // Encoding (Sec. 2.5 for the point, App. B.2 for its index): one wave per group, lane l holds coordinates
 // CP*l .. CP*l+CP-1 (CP = D/64).  The quantiser's sums run over adjacent pairs level by level (in the
 // lane, then across lanes by data-parallel-primitive moves, no LDS traffic), the repair of the pulse
-// count picks one coordinate per step by a wave-wide argmax (lowest coordinate on ties).  The index is a sum of per-coordinate terms that depend
-// on the coordinate's magnitude, sign and the pulses left before it only; a prefix sum over the
-// magnitudes gives the latter.  Because the pulses left after coordinate j-1 are those before
-// coordinate j, the terms regroup by the cells (d_j, k_j) that the walk visits: cell j adds
-// N(d_j,k_j) ([m_j > 0] + [coordinate j-1 negative]) - E(d_j,k_j) [m_{j-1} > 0].  A third table holds, per
-// cell, the four forms this can take (N, -E, N-E, 2N-E), so a coordinate costs one table entry and one
-// multi-word addition; six levels of multi-word additions across the lanes give the total.
+// count picks one coordinate per step by a wave-wide argmax (lowest coordinate on ties).  The index is a sum of
+// per-coordinate thresholds that depend on the coordinate's magnitude, sign and the pulses left before it only; a
+// prefix sum over the magnitudes gives the latter; six levels of multi-word additions across the lanes give the total.
 //
-// Decoding (App. B.3): one lane per group, coordinate by coordinate.  The lane keeps q = N(d,k) - 1 - r
-// for the residual r; the coordinate's magnitude is the smallest m with E(d-1,k-1-m) <= q (E(.,-1) = 0),
-// one table entry and one multi-word subtraction per step, and the difference of the last failed step
-// gives the next q.  Points go to LDS as int16, and the waves then write whole groups with consecutive
-// lanes on consecutive addresses.
+// Decoding (App. B.3): coordinate by coordinate, q = N(D,K) - 1 - index first; a coordinate is the last
+// threshold of its row that is not above q, and q loses it.  Few groups: a wave per group
+// (decode_wide_wave_kernel); many: a lane per group (decode_wide_kernel).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -46,10 +38,10 @@ struct wint {
 };
 
 template <int W>
-__device__ inline wint<W> load_entry(const uint32_t *tab, int64_t entry)
+__device__ inline wint<W> load_entry(const uint32_t *tab, int entry)
 {
     wint<W> r;
-    const uint4 *p = reinterpret_cast<const uint4 *>(tab + entry * W);
+    const uint4 *p = reinterpret_cast<const uint4 *>(tab + (uint32_t)entry * (uint32_t)W);
 #pragma unroll
     for (int i = 0; i < W / 4; i++) {
         const uint4 v = p[i];
@@ -65,28 +57,6 @@ __device__ inline void add_to(wint<W> &a, const wint<W> &b)
     uint32_t carry = 0;
 #pragma unroll
     for (int i = 0; i < W; i++) a.w[i] = __builtin_addc(a.w[i], b.w[i], carry, &carry);
-}
-
-// a - b (modulo 2^(32W)); *borrow = 1 when b > a
-template <int W>
-__device__ inline wint<W> subtract(const wint<W> &a, const wint<W> &b, uint32_t *borrow)
-{
-    wint<W> r;
-    uint32_t br = 0;
-#pragma unroll
-    for (int i = 0; i < W; i++) r.w[i] = __builtin_subc(a.w[i], b.w[i], br, &br);
-    *borrow = br;
-    return r;
-}
-
-// a -= b (modulo 2^(32W)); *borrow = 1 when b > a
-template <int W>
-__device__ inline void subtract_from(wint<W> &a, const wint<W> &b, uint32_t *borrow)
-{
-    uint32_t br = 0;
-#pragma unroll
-    for (int i = 0; i < W; i++) a.w[i] = __builtin_subc(a.w[i], b.w[i], br, &br);
-    *borrow = br;
 }
 
 // A lane's value moved by one data-parallel-primitive pattern; lanes whose row is not in ROWS, or whose
@@ -123,7 +93,9 @@ struct encode_wide_params {
     const void *X;
     int64_t ldx, groups, index_row_words;
     int K, bits, tile_groups, tiles_per_row, ls;
-    const uint32_t *tab_c;   // per cell (d,k) the four forms N, -E, N-E, 2N-E
+    const uint32_t *tab_t;   // thresholds [D][row_len][W]
+    int row_len;
+    uint32_t last_index[16]; // N(D,K) - 1
     uint32_t *index_out;
     float *scale_out;
     int8_t *pulses_out;
@@ -259,40 +231,16 @@ __global__ __launch_bounds__(512) void encode_wide_kernel(encode_wide_params p)
         incl += (int)dpp_move<0x142, 0xA>((uint32_t)incl);   // lane 15 of rows 0, 2 into rows 1, 3
         incl += (int)dpp_move<0x143, 0xC>((uint32_t)incl);   // lane 31 into rows 2, 3
         int k = K - (incl - mine);   // pulses left before this lane's first coordinate
-        // The walk visits the cells (d_j, k_j), j = 0..D, d_j = D - j, k_j = pulses left before coordinate
-        // j.  Cell j adds  N(d_j,k_j) ([m_j > 0] + [coordinate j-1 negative]) - E(d_j,k_j) [m_{j-1} > 0]
-        // (the -E(d-1,k-m) of coordinate j-1 and the N(d-1,k-m) of a negative one are values of the next
-        // cell): one table entry, in the form that the two coordinates around the cell call for.
-        int prev_state;              // of the coordinate before: bit 0 = magnitude > 0, bit 1 = negative
-        {
-            const int last = (m[CP - 1] > 0 ? 1 : 0) | ((m[CP - 1] > 0 && w[CP - 1] < 0.0f) ? 2 : 0);
-            const int up = __shfl_up(last, 1, 64);
-            prev_state = lane > 0 ? up : 0;
-        }
         wint<W> acc;
 #pragma unroll
         for (int i = 0; i < W; i++) acc.w[i] = 0;
 #pragma unroll
         for (int j = 0; j < CP; j++) {
-            const int d = D - (CP * lane + j);
+            const int row_t = D - 1 - (CP * lane + j);
             const int kk = min(max(k, 0), K), mm = min(max(m[j], 0), kk);   // in range whatever the input
-            const int times = (mm > 0 ? 1 : 0) + (prev_state >> 1);         // how often N(d,k) counts
-            const bool prev_pos = prev_state & 1;
-            if (prev_pos || times) {
-                const int form = prev_pos ? 1 + times : 0;
-                add_to(acc, load_entry<W>(p.tab_c, ((int64_t)d * (K + 1) + kk) * 4 + form));
-            }
-            prev_state = (mm > 0 ? 1 : 0) | ((mm > 0 && w[j] < 0.0f) ? 2 : 0);
             k = kk - mm;
-        }
-        if (lane == 63) {
-            // the last cell is (0, 0): N = 1, E = 2
-            const int32_t last_cell = (prev_state >> 1) - 2 * (prev_state & 1);
-            wint<W> small;
-#pragma unroll
-            for (int i = 0; i < W; i++) small.w[i] = last_cell < 0 ? 0xFFFFFFFFu : 0u;
-            small.w[0] = (uint32_t)last_cell;
-            add_to(acc, small);
+            const int at = 2 * k + (mm > 0 && !(w[j] < 0.0f) ? 1 : 0);
+            if (at) add_to(acc, load_entry<W>(p.tab_t, row_t * p.row_len + at));     // (T_0 = 0)
         }
 #define PVQ_STEP(CTRL, ROWS)                                                           \
     {                                                                                  \
@@ -305,10 +253,10 @@ __global__ __launch_bounds__(512) void encode_wide_kernel(encode_wide_params p)
 
         // ---- into the tile's bit stream: lane i takes word i of the index (lane 63 has it), shifted to
         // its place
-        uint32_t word = 0;
+        uint32_t word = 0, borrow = 0;
 #pragma unroll
         for (int i = 0; i < W; i++) {
-            const uint32_t wi = (uint32_t)__builtin_amdgcn_readlane((int)acc.w[i], 63);
+            const uint32_t wi = __builtin_subc(p.last_index[i], (uint32_t)__builtin_amdgcn_readlane((int)acc.w[i], 63), borrow, &borrow);
             word = lane == i ? wi : word;
         }
         const int off = gi * p.bits, sh = off & 31, w0 = off >> 5;
@@ -452,34 +400,18 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
     incl += (int)dpp_move<0x114>((uint32_t)incl);        // row_shr:4
     incl += (int)dpp_move<0x118>((uint32_t)incl);        // row_shr:8
     int k = K - (incl - mine);
-    // cell by cell as in the wave-per-group form: one table entry per cell, in the form that the two
-    // coordinates around it call for
-    const uint32_t last_state = (m[CP - 1] > 0 ? 1u : 0u) | ((m[CP - 1] > 0 && w[CP - 1] < 0.0f) ? 2u : 0u);
-    int prev_state = (int)dpp_move<0x111>(last_state);   // the lane before in the row; none for sub = 0
     wint<W> acc;
 #pragma unroll
     for (int i = 0; i < W; i++) acc.w[i] = 0;
 #pragma unroll
     for (int j = 0; j < CP; j++) {
-        const int d = D - (CP * sub + j);
+        const int row_t = D - 1 - (CP * sub + j);
         const int kk = min(max(k, 0), K), mm = min(max(m[j], 0), kk);   // in range whatever the input
-        const int times = (mm > 0 ? 1 : 0) + (prev_state >> 1);
-        const bool prev_pos = prev_state & 1;
-        if (prev_pos || times) {
-            const int form = prev_pos ? 1 + times : 0;
-            add_to(acc, load_entry<W>(p.tab_c, ((int64_t)d * (K + 1) + kk) * 4 + form));
-        }
-        prev_state = (mm > 0 ? 1 : 0) | ((mm > 0 && w[j] < 0.0f) ? 2 : 0);
         k = kk - mm;
-    }
-    if (sub == 15) {
-        // the last cell is (0, 0): N = 1, E = 2
-        const int32_t last_cell = (prev_state >> 1) - 2 * (prev_state & 1);
-        wint<W> small;
-#pragma unroll
-        for (int i = 0; i < W; i++) small.w[i] = last_cell < 0 ? 0xFFFFFFFFu : 0u;
-        small.w[0] = (uint32_t)last_cell;
-        add_to(acc, small);
+        const int at = 2 * k + (mm > 0 && !(w[j] < 0.0f) ? 1 : 0);
+        // (T_0 = 0.  The condition keeps the entries from being read all at once: fewer registers, more waves, which is
+        // what hides the trips to the L2: without it 155 instead of 94 us for 2048 x 8192 values rotated and encoded)
+        if (at) add_to(acc, load_entry<W>(p.tab_t, row_t * p.row_len + at));
     }
 #define PVQ_STEP(CTRL)                                                                  \
 {                                                                                   \
@@ -491,9 +423,12 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
 #undef PVQ_STEP
 
     // ---- into the tile's bit stream: lane sub = i of the group takes word i of the index
-    uint32_t word = 0;
+    uint32_t word = 0, borrow = 0;
 #pragma unroll
-    for (int i = 0; i < W; i++) word = sub == i ? acc.w[i] : word;
+    for (int i = 0; i < W; i++) {
+        const uint32_t wi = __builtin_subc(p.last_index[i], acc.w[i], borrow, &borrow);
+        word = sub == i ? wi : word;
+    }
     const int off = gl * p.bits, sh = off & 31, w0 = off >> 5;
     const uint32_t prev = dpp_move<0x111>(word);         // word sub-1, zero for sub = 0
     const uint32_t out = sh ? (word << sh) | (prev >> (32 - sh)) : word;
@@ -622,12 +557,48 @@ struct decode_wide_params {
     const uint32_t *index;
     const float *scale;
     int64_t groups, total_groups, index_row_words, ldw;
-    int K, bits;
-    const uint32_t *tab_n, *tab_e, *tab_key;
+    int K, bits, row_len, key_len, buckets, out_dtype;
+    const uint32_t *tab_t, *tab_key;
+    const uint16_t *tab_guess;
+    const double *tab_near;
+    uint32_t last_index[16];
     void *W_out;
 };
 
-constexpr int kDecodeLanes = 128;
+// word i of the W-word index of group g of a row (zero beyond the index)
+__device__ inline uint32_t index_word(const uint32_t *row, const decode_wide_params &p, int64_t g, int i)
+{
+    const int left = p.bits - 32 * i;
+    const int64_t at = g * p.bits + 32 * i, wi = at >> 5;
+    const int sh = (int)(at & 31);
+    // (both words are read whatever the field needs, inside the row: no read waits for another)
+    const uint32_t lo = row[std::min(wi, p.index_row_words - 1)], hi = row[std::min(wi + 1, p.index_row_words - 1)];
+    const uint32_t v = __builtin_amdgcn_alignbit(hi, lo, sh);
+    return left >= 32 ? v : left <= 0 ? 0u : v & ((1u << left) - 1u);
+}
+
+// CP neighbouring values of a decoded group
+template <int CP>
+__device__ inline void store_values(const decode_wide_params &p, int64_t at, const float (&v)[CP])
+{
+    if (p.out_dtype == PVQ_F32) {
+        float *o = reinterpret_cast<float *>(p.W_out) + at;
+        if constexpr (CP == 2) *reinterpret_cast<float2 *>(o) = make_float2(v[0], v[1]);
+        else o[0] = v[0];
+    } else if (p.out_dtype == PVQ_F16) {
+        __half *o = reinterpret_cast<__half *>(p.W_out) + at;
+        if constexpr (CP == 2) *reinterpret_cast<__half2 *>(o) = __halves2half2(__float2half_rn(v[0]), __float2half_rn(v[1]));
+        else o[0] = __float2half_rn(v[0]);
+    } else {
+        uint16_t *o = reinterpret_cast<uint16_t *>(p.W_out) + at;
+        const f32x2_t pair = {v[0], CP == 2 ? v[CP - 1] : 0.0f};
+        const uint32_t bits = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
+        if constexpr (CP == 2) *reinterpret_cast<uint32_t *>(o) = bits;
+        else o[0] = (uint16_t)bits;
+    }
+}
+
+// ---- many groups: a lane per group -------------------------------------------------------------------
 
 // Bytes of LDS per lane for the decoded point of a group of D: magnitudes and signs.  With K <= 255 a magnitude is a
 // byte and the signs are a bit each (D + D/8 bytes); else int16 values.  Rounded up to an odd number of words, so
@@ -638,179 +609,356 @@ __host__ __device__ inline int decode_point_bytes(int D, int K)
     return 4 * (words | 1);
 }
 
-// OUT: pvq_dtype of the result.  LDS: kDecodeLanes points (decode_point_bytes each), kDecodeLanes float32 gains;
-// little per lane, so that many waves share a unit: a wave's walk is a chain of dependent steps, and what a unit
-// gets done is the number of chains it holds.
-// A coordinate's magnitude is the smallest m with E(d-1,k-1-m) <= q.  Tried one m after the other with the
-// multi-word entries, that is a dependent trip to the tables and a multi-word subtraction per unit of magnitude,
-// and a wave takes as many as its largest magnitude.  Here the search runs on 32-bit keys of the entries
-// (pvq_wide_key), four at a time, against the key of q: keys that differ order the integers, and equal keys (about
-// one comparison in a million) send the lane through the multi-word search.  The entries themselves are then read
-// once per coordinate, together: E at the magnitude found, and N for the sign.
-template <int OUT, int CP, int W>
-__global__ __launch_bounds__(kDecodeLanes, 4) void decode_wide_kernel(decode_wide_params p)
+// The walk of one lane.  A coordinate takes three dependent trips to the tables, of which the L1 and L2 hold the few lines
+// of a row that are in use: the guess of q's bucket, the four keys behind it, and the threshold found.  Equal keys
+// (about one comparison in a million, and the all-zero groups) show as a borrow of the subtraction, after which the
+// threshold before is taken.
+// Bound by its chain of about 150 instructions a coordinate: D = 128, K = 187, 8192-wide rows, 512 / 2048 / 4096 of them:
+// 97 / 157 / 162 us, where the same search with one multi-word comparison per magnitude and the subtractions of the
+// enumeration's own recursion took 208 / 261 / 355.  (With the thresholds around the wave's pulses in LDS, loaded a pair of
+// rows ahead, 112 / 128 / 252: half as many waves fit a unit then.)
+template <int CP, int W>
+struct lane_walk {
+    static constexpr int D = 64 * CP;
+    const decode_wide_params &p;
+    unsigned char *mine;
+    uint32_t q[W];
+    int k, n2, i;
+    uint32_t sign_byte;
+
+    // pvq_wide_key of q, which lies below 2^(32 WP): its leading word and the one below are nearly always among the upper four
+    template <int WP>
+    __device__ inline uint32_t key_of_q() const
+    {
+        constexpr int w1 = WP > 1 ? WP - 2 : 0, w2 = WP > 2 ? WP - 3 : 0, w3 = WP > 3 ? WP - 4 : 0;
+        uint32_t a = q[WP - 1], b = WP > 1 ? q[w1] : 0u;
+        int length = 32 * WP;
+        if (WP > 2) {
+            const bool none = a == 0 && b == 0;                    // both upper words
+            const uint32_t c = none ? (WP > 4 ? q[WP > 4 ? WP - 5 : 0] : 0u) : q[w2];
+            a = none ? q[w2] : a; b = none ? (WP > 3 ? q[w3] : 0u) : b; length = none ? 32 * (WP - 2) : length;
+            const bool lower = a == 0;
+            a = lower ? b : a; b = lower ? c : b; length -= lower ? 32 : 0;
+        } else if (WP > 1) {
+            const bool lower = a == 0;
+            a = lower ? b : a; b = lower ? 0u : b; length -= lower ? 32 : 0;
+        }
+        const int lead = __builtin_clz(a | 1u);
+        const uint32_t two = __builtin_amdgcn_alignbit(a, b, (32 - lead) & 31);          // the 32 bits from the leading one on
+        uint32_t key = ((uint32_t)(length - lead) << 22) | ((lead ? two : a) >> 10);
+        if (WP > 4) { if (__any(a == 0)) key = a == 0 ? pvq_wide_key(q, WP) : key; }
+        else key = a == 0 ? 0u : key;
+        return key;
+    }
+
+    // one coordinate; every q of the wave lies below 2^(32 WP)
+    template <int WP>
+    __device__ inline void step()
+    {
+        const uint32_t row = (uint32_t)(D - 1 - i);
+        const uint32_t kq = key_of_q<WP>();
+        const uint32_t *keys = p.tab_key + row * (uint32_t)p.key_len;
+        uint32_t j = p.tab_guess[row * (uint32_t)p.buckets + (kq >> 19 & ~7u) + (kq >> 18 & 7u)];
+        uint32_t more;
+        do {
+            uint32_t ke[4];
+            __builtin_memcpy(ke, keys + j + 1, 16);
+            more = (ke[0] <= kq ? 1u : 0u) + (ke[1] <= kq ? 1u : 0u) + (ke[2] <= kq ? 1u : 0u) + (ke[3] <= kq ? 1u : 0u);
+            j += more;
+        } while (__any(more == 4));                                // (ends: the keys behind a row are all ones)
+        j = min(j, (uint32_t)(2 * k + 1));
+        const uint32_t *trow = p.tab_t + row * (uint32_t)(p.row_len * W);
+        uint32_t t[(WP + 3) / 4 * 4];
+        auto read = [&] {
+#pragma unroll
+            for (int x = 0; x < (WP + 3) / 4; x++) {
+                const uint4 v = *reinterpret_cast<const uint4 *>(trow + (j * W + 4 * x));
+                t[4 * x] = v.x; t[4 * x + 1] = v.y; t[4 * x + 2] = v.z; t[4 * x + 3] = v.w;
+            }
+        };
+        read();
+        uint32_t br = 0;
+#pragma unroll
+        for (int x = 0; x < WP; x++) q[x] = __builtin_subc(q[x], t[x], br, &br);
+        if (__any(br)) {
+            while (br) {                                           // (ends: T_0 = 0)
+                uint32_t c = 0;
+#pragma unroll
+                for (int x = 0; x < WP; x++) q[x] = __builtin_addc(q[x], t[x], c, &c);
+                j--;
+                read();
+                br = 0;
+#pragma unroll
+                for (int x = 0; x < WP; x++) q[x] = __builtin_subc(q[x], t[x], br, &br);
+            }
+        }
+        const int C = (int)(j >> 1), m = k - C;
+        const uint32_t negative = ~j & 1u;
+        k = C;
+        n2 += __mul24(m, m);
+        if (p.K <= 255) {
+            mine[i] = (unsigned char)m;
+            sign_byte = ((i & 7) ? sign_byte : 0u) | (negative << (i & 7));
+            if ((i & 7) == 7) mine[D + (i >> 3)] = (unsigned char)sign_byte;
+        } else {
+            reinterpret_cast<int16_t *>(mine)[i] = (int16_t)(negative ? -m : m);
+        }
+        i++;
+    }
+
+    // q shrinks as it goes: the walk runs in as many words as the wave's largest q needs
+    template <int WP>
+    __device__ inline void walk()
+    {
+        while (i < D && (WP == 1 || __any(q[WP - 1] != 0))) step<WP>();
+        if constexpr (WP > 1) walk<WP - 1>();
+    }
+};
+
+// A wave is a workgroup, with decode_point_bytes of LDS per lane.
+template <int CP, int W>
+__global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     constexpr int D = 64 * CP;
-    const int K = p.K;
-    const bool bytes = K <= 255;
-    const int LB = decode_point_bytes(D, K);
-    float *gains = reinterpret_cast<float *>(lds_raw + (size_t)kDecodeLanes * LB);
-    const int64_t gid = (int64_t)blockIdx.x * kDecodeLanes + threadIdx.x;
-    unsigned char *mine = lds_raw + (size_t)threadIdx.x * LB;      // magnitudes [D], sign bytes [D/8]; or int16 [D]
+    const bool bytes = p.K <= 255;
+    const int LB = decode_point_bytes(D, p.K);
+    const int lane = threadIdx.x;
+    const int64_t g0 = (int64_t)blockIdx.x * 64;
+    const int count = (int)std::min<int64_t>(64, p.total_groups - g0);
+    int64_t out_row = g0 / p.groups, out_g = g0 - out_row * p.groups;
 
-    if (gid < p.total_groups) {
-        const int64_t row = gid / p.groups, g = gid - row * p.groups;
-        const uint32_t *src = p.index + row * p.index_row_words;
-        // the group's index: bits [g*bits, (g+1)*bits) of the row's stream
-        wint<W> r;
+    // the lane's group (lanes behind the last group take that one, unused)
+    const uint32_t ahead = (uint32_t)out_g + (uint32_t)std::min(lane, count - 1);
+    const int64_t mine = g0 + std::min(lane, count - 1);
+    const int64_t row = out_row + ahead / (uint32_t)p.groups, g = ahead % (uint32_t)p.groups;
+    lane_walk<CP, W> walk{p, lds_raw + (size_t)lane * LB, {}, p.K, 0, 0, 0u};
+    // q = N(D,K) - 1 - index; an index that is no codeword decodes to zeros
+    uint32_t br = 0;
 #pragma unroll
-        for (int i = 0; i < W; i++) {
-            const int left = p.bits - 32 * i;
-            uint32_t v = 0;
-            if (left > 0) {
-                const int64_t at = g * p.bits + 32 * i;
-                const int64_t wi = at >> 5;
-                const int sh = (int)(at & 31);
-                v = src[wi] >> sh;
-                if (sh && wi + 1 < p.index_row_words) v |= src[wi + 1] << (32 - sh);
-                if (left < 32) v &= (1u << left) - 1u;
-            }
-            r.w[i] = v;
-        }
-        // q = N(D,K) - 1 - r; an index that is no codeword decodes to zeros
-        uint32_t br;
-        wint<W> q = subtract(load_entry<W>(p.tab_n, (int64_t)D * (K + 1) + K), r, &br);
-        bool valid = !br;
-        {
-            wint<W> one;
+    for (int i = 0; i < W; i++) walk.q[i] = __builtin_subc(p.last_index[i], index_word(p.index + row * p.index_row_words, p, g, i), br, &br);
+    const bool valid = !br;
+    if (!valid) {
 #pragma unroll
-            for (int i = 0; i < W; i++) one.w[i] = 0;
-            one.w[0] = 1;
-            q = subtract(q, one, &br);
-            valid = valid && !br;
-        }
-        int k = valid ? K : 0;
-        int n2 = 0;
-        uint32_t sign_byte = 0;
-        for (int i = 0; i < D; i++) {
-            const int d = D - i;
-            int y = 0;
-            if (k > 0) {
-                if (d == 1) {
-                    // the two points +k, -k of P(1,k): q = 1, 0
-                    bool zero = true;
-#pragma unroll
-                    for (int x = 0; x < W; x++) zero = zero && q.w[x] == 0;
-                    y = zero ? -k : k;
-                    k = 0;
-                } else {
-                    const int rw = d - 1;                                   // the tables' row
-                    const uint32_t *erow = p.tab_e + (int64_t)rw * (K + 1) * W;
-                    const uint32_t *krow = p.tab_key + (int64_t)rw * (K + 1);
-                    // the search on keys: m = the magnitude, or `unsure` at a pair of equal keys
-                    const uint32_t kq = pvq_wide_key(q.w, W);
-                    int m = k;
-                    bool unsure = false;
-                    for (int m0 = 0; m0 < k; m0 += 4) {
-                        uint32_t ke[4];
-#pragma unroll
-                        for (int u = 0; u < 4; u++) ke[u] = krow[max(k - 1 - m0 - u, 0)];
-                        bool done = false;
-#pragma unroll
-                        for (int u = 0; u < 4; u++) {
-                            if (!done && m0 + u < k && ke[u] <= kq) {
-                                done = true;
-                                m = m0 + u;
-                                unsure = ke[u] == kq;
-                            }
-                        }
-                        if (done) break;
-                    }
-                    // q - E(d-1, k-1) for m = 0 (the next q); for m > 0, q - E(d-1, k-m), the entry of the last
-                    // magnitude that failed.  In place: the walk's integers are not copied.
-                    // (requested together with E; for m = 0 it is not used.  After the rare search below m is another,
-                    // and it is read again)
-                    wint<W> n = load_entry<W>(p.tab_n, (int64_t)rw * (K + 1) + (k - m));
-                    if (unsure) {
-                        // the multi-word search from the start
-                        const wint<W> q0 = q;
-                        for (m = 0; m < k; m++) {
-                            uint32_t b;
-                            const wint<W> t = subtract(q0, load_entry<W>(erow, k - 1 - m), &b);
-                            if (!b) { if (m == 0) q = t; break; }   // E <= q: magnitude m
-                            q = t;
-                        }
-                        n = load_entry<W>(p.tab_n, (int64_t)rw * (K + 1) + (k - m));
-                    } else {
-                        uint32_t b;
-                        subtract_from(q, load_entry<W>(erow, m == 0 ? k - 1 : k - m), &b);
-                    }
-                    if (m > 0) {
-                        // inside the block of magnitude m: v = q - E(d-1,k-m) + N(d-1,k-m); negative means
-                        // the second half of the block (the coordinate is -m), whose q is v + N(d-1,k-m)
-                        add_to(q, n);
-                        const bool negative = q.w[W - 1] >> 31;
-                        if (negative) add_to(q, n);
-                        y = negative ? -m : m;
-                        k -= m;
-                    }
-                }
-            }
-            if (bytes) {
-                mine[i] = (unsigned char)(y < 0 ? -y : y);
-                sign_byte = ((i & 7) ? sign_byte : 0u) | ((y < 0 ? 1u : 0u) << (i & 7));
-                if ((i & 7) == 7) mine[D + (i >> 3)] = (unsigned char)sign_byte;
-            } else {
-                reinterpret_cast<int16_t *>(mine)[i] = (int16_t)y;
-            }
-            n2 += y * y;
-        }
-        gains[threadIdx.x] = valid ? p.scale[gid] / sqrtf((float)n2) : 0.0f;
+        for (int i = 0; i < W; i++) walk.q[i] = 0;
     }
-    __syncthreads();
+    walk.template walk<W>();
+    const float gain = valid ? p.scale[mine] / sqrtf((float)walk.n2) : 0.0f;
 
-    // whole groups out, a wave per group in turn
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int s = wave; s < kDecodeLanes; s += kDecodeLanes / 64) {
-        const int64_t og = (int64_t)blockIdx.x * kDecodeLanes + s;
-        if (og >= p.total_groups) break;
-        const int64_t row = og / p.groups, g = og - row * p.groups;
-        const float gain = gains[s];
-        const unsigned char *pt = lds_raw + (size_t)s * LB;
+    // the groups out, one after the other: consecutive lanes, consecutive values
+    int64_t at = out_row * p.ldw + out_g * D + CP * lane;
+    const unsigned char *pt = lds_raw;
+    for (int s = 0; s < count; s++) {
+        const float gs = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(gain), s));
+        int y[CP];
+        if (bytes) {
+            uint32_t mags;
+            if constexpr (CP == 2) mags = *reinterpret_cast<const uint16_t *>(pt + 2 * lane);
+            else mags = pt[lane];
+            const uint32_t signs = pt[D + (CP * lane >> 3)] >> (CP * lane & 7);
+#pragma unroll
+            for (int j = 0; j < CP; j++) {
+                const int mag = (int)(mags >> (8 * j) & 0xFFu);
+                y[j] = (signs >> j & 1u) ? -mag : mag;
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < CP; j++) y[j] = reinterpret_cast<const int16_t *>(pt)[CP * lane + j];
+        }
         float v[CP];
 #pragma unroll
-        for (int j = 0; j < CP; j++) {
-            const int c = CP * lane + j;
-            int y;
-            if (bytes) {
-                const int mag = pt[c];
-                y = (pt[D + (c >> 3)] >> (c & 7)) & 1 ? -mag : mag;
-            } else {
-                y = reinterpret_cast<const int16_t *>(pt)[c];
+        for (int j = 0; j < CP; j++) v[j] = gs * (float)y[j];
+        store_values<CP>(p, at, v);
+        pt += LB;
+        at += D;
+        if (++out_g == p.groups) { out_g = 0; at += p.ldw - p.groups * D; }
+    }
+}
+
+// ---- few groups: a wave per group --------------------------------------------------------------------
+
+// The walk of one wave.  q lies across the lanes, a word each; float64 approximations of 64 neighbouring thresholds of
+// the row (32 possible values of the pulses left) lie across them too, the highest in lane 0, and the thresholds
+// themselves in LDS.  A coordinate is one comparison of approximations, the first lane that passes it, one read of that
+// threshold by words, and a subtraction whose borrows run through a scalar addition.  Rows are fetched four coordinates
+// in advance, straight into LDS, at the place that k has then: k only falls, by one or two a coordinate, so the window
+// nearly always still holds the coordinate.
+// A walk is one chain of dependent instructions (8 clocks each, 52 for a read of LDS), so the chain of one coordinate on
+// the next is all that counts: about twenty instructions and one read of LDS, hence the few instructions written out;
+// everything else about a coordinate is done while the next one's read is on its way.  D = 128, K = 187, one row of 8192
+// values / 16 of them: 23 / 30 us, where a lane per group takes 95 (and took 208 when each magnitude was one trip).
+constexpr int kWavesFew = 2;          // of a workgroup
+
+template <int CP, int W>
+struct wave_walk {
+    static constexpr int D = 64 * CP, kAhead = 4;
+    static constexpr int kLoads = W / 4 + 1;                       // of a window, 1 KiB each: its thresholds, its approximations
+    static constexpr int kWindow = 1024 * kLoads;
+    const decode_wide_params &p;
+    const int lane;
+    unsigned char *ring;              // LDS: kAhead windows
+    uint32_t q;                       // lane x: word x
+    int k, n2, i;
+    int y[CP];                        // the lane's coordinates: CP * lane + j
+    int j, base[kAhead];              // place of the coordinate before in its row; first threshold of a window
+    // LDS addresses: the lane's approximation in window 0; its word of the threshold that lane l of a window stands for
+    // is from - 4 W l (lanes without a word read a zero)
+    uint32_t near_from, from[kAhead];
+    int entry;
+
+    // thresholds b .. b + 63 of a row (a row has 64 at least)
+    template <int u>
+    __device__ __forceinline__ void fetch(int row, int b)
+    {
+        base[u] = b;
+        const uint32_t at = (uint32_t)(row * p.row_len + b);
+        const unsigned char *t = reinterpret_cast<const unsigned char *>(p.tab_t) + (at * (uint32_t)(4 * W) + 16u * (uint32_t)lane);
+        const unsigned char *n = reinterpret_cast<const unsigned char *>(p.tab_near) + (at * 8u + 16u * (uint32_t)lane);
+        auto *to = (__attribute__((address_space(3))) void *)(ring + u * kWindow);
+        // (the instruction's offset counts on both sides)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 0, 0);
+        if constexpr (W > 4) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 1024, 0);
+        if constexpr (W > 8) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 2048, 0);
+        if constexpr (W > 12) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 3072, 0);
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)n,
+                                         (__attribute__((address_space(3))) void *)(ring + u * kWindow + 1024 * (W / 4)), 16, 0, 0);
+    }
+
+    // The coordinate's place in its row, all words compared, window by window from the one for the present k down (ends:
+    // T_0 = 0): for windows that lie too high.
+    __device__ __forceinline__ static int search(const uint32_t *trow, uint32_t q, int lane, int k)
+    {
+        for (int b = max(2 * k + 1 - 63, 0);; b = max(b - 64, 0)) {
+            bool less = false, equal = true;                       // threshold against q, from the highest word down
+#pragma unroll 1
+            for (int x = W - 1; x >= 0; x--) {
+                const uint32_t qx = (uint32_t)__builtin_amdgcn_readlane((int)q, x), tx = trow[(uint32_t)((b + lane) * W + x)];
+                less = less || (equal && tx < qx);
+                equal = equal && tx == qx;
             }
-            v[j] = gain * (float)y;
-        }
-        const int64_t at = row * p.ldw + g * D + CP * lane;
-        if constexpr (OUT == PVQ_F32) {
-            float *o = reinterpret_cast<float *>(p.W_out) + at;
-            if constexpr (CP == 2) *reinterpret_cast<float2 *>(o) = make_float2(v[0], v[1]);
-            else o[0] = v[0];
-        } else if constexpr (OUT == PVQ_F16) {
-            __half *o = reinterpret_cast<__half *>(p.W_out) + at;
-            if constexpr (CP == 2) *reinterpret_cast<__half2 *>(o) = __halves2half2(__float2half_rn(v[0]), __float2half_rn(v[1]));
-            else o[0] = __float2half_rn(v[0]);
-        } else {
-            uint16_t *o = reinterpret_cast<uint16_t *>(p.W_out) + at;
-            if constexpr (CP == 2) {
-                const f32x2_t pair = {v[0], v[1]};
-                *reinterpret_cast<uint32_t *>(o) = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
-            } else {
-                const f32x2_t pair = {v[0], 0.0f};
-                o[0] = (uint16_t)__builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
-            }
+            const uint64_t found = __ballot(less || equal);
+            if (found) return b + 63 - __builtin_clzll(found);
+            if (b == 0) return 0;                                  // (cannot be: T_0 = 0)
         }
     }
+
+    // q -= t over the lanes.  A word borrows from the next where it is smaller (generate), or equal and borrowed from
+    // (propagate): the borrows are what the carries of propagate + 2 generate change.  Returns them.
+    __device__ __forceinline__ static uint32_t subtract(uint32_t &q, uint32_t t)
+    {
+        const uint32_t generate = (uint32_t)__builtin_amdgcn_uicmp(q, t, 36), propagate = (uint32_t)__builtin_amdgcn_uicmp(q, t, 32);
+        const uint32_t borrows = (propagate + 2u * generate) ^ propagate;
+        asm("v_subb_co_u32_e64 %0, vcc, %1, %2, %3" : "=v"(q) : "v"(q), "v"(t), "s"((uint64_t)borrows) : "vcc");
+        return borrows;
+    }
+
+    // what the coordinate before, at place j of its row, leaves to be done; u is its window, which takes the row four on
+    template <int u>
+    __device__ __forceinline__ void finish()
+    {
+        const int C = j >> 1, m = k - C;
+        k = C;
+        n2 += m * m;
+        y[u % CP] = lane == (i - 1) / CP ? ((j & 1) ? m : -m) : y[u % CP];   // (i - 1 = u modulo 4; none for i = 0, whose m is 0)
+        fetch<u>(max(D - kAhead - i, 0), max(2 * k - 62, 0));      // (past the last row: row 0, not used)
+    }
+
+    template <int u>
+    __device__ __forceinline__ void step()
+    {
+        // this window has arrived once only the loads of the two fetched behind it are on their way (in order)
+        double near;
+        asm volatile("s_waitcnt vmcnt(%2)\n\tds_read_b64 %0, %1" : "=v"(near) : "v"(near_from + u * kWindow), "n"((kAhead - 2) * kLoads) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        // q's approximation (pvq_wide_double), from its highest word that is not zero and the one below it (lane 63 holds
+        // 0; for q = 0 the highest word is "lane 32", which holds 0)
+        int lead, first;
+        asm("s_flbit_i32_b32 %0, %1" : "=s"(lead) : "s"((uint32_t)__builtin_amdgcn_uicmp(q, 0u, 33)));
+        const int at = 31 - lead;
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)q, at), lo = (uint32_t)__builtin_amdgcn_readlane((int)q, at - 1);
+        const double nq = __builtin_amdgcn_ldexp(__builtin_fma((double)hi, 4294967296.0, (double)lo), 32 * at - 32);
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(near));
+        uint64_t found = __ballot(near <= nq);
+        asm("s_ff1_i32_b64 %0, %1" : "=s"(first) : "s"(found));    // (-1 for none: what is read then is not used)
+        uint32_t t;
+        asm volatile("v_mad_i32_i24 %0, %1, %2, %3\n\tds_read_b32 %0, %0" : "=&v"(t) : "s"(first), "v"(entry), "v"(from[u]) : "memory");
+        finish<(u + kAhead - 1) % kAhead>();
+        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(t));
+        const uint32_t q0 = q;
+        uint32_t borrows = subtract(q, t);
+        if (__builtin_expect(((borrows & (1u << W)) | ((uint32_t)first & 0x80000000u)) != 0, 0)) {
+            // a threshold above q of the same approximation: the one behind it in the window
+            while (found != 0 && (borrows >> W & 1u)) {
+                found &= found - 1;
+                first = found ? __builtin_ctzll(found) : 0;
+                asm volatile("v_mad_i32_i24 %0, %1, %2, %3\n\tds_read_b32 %0, %0\n\ts_waitcnt lgkmcnt(0)"
+                             : "=&v"(t) : "s"(first), "v"(entry), "v"(from[u]) : "memory");
+                q = q0;
+                borrows = subtract(q, t);
+            }
+            if (found == 0) {
+                const uint32_t *trow = p.tab_t + (uint32_t)((D - 1 - i) * p.row_len * W);
+                q = q0;
+                j = __builtin_amdgcn_readfirstlane(search(trow, q, lane, k));
+                t = lane < W ? trow[(uint32_t)(j * W + lane)] : 0u;
+                __builtin_amdgcn_s_waitcnt(0x0F70);                // (before the paths meet: no wait behind them covers it)
+                subtract(q, t);
+                first = base[u] + 63 - j;
+            }
+        }
+        j = base[u] + 63 - first;
+        i++;
+    }
+};
+
+template <int CP, int W>
+__global__ __launch_bounds__(64 * kWavesFew) void decode_wide_wave_kernel(decode_wide_params p)
+{
+    using walk_t = wave_walk<CP, W>;
+    constexpr int D = 64 * CP, kRing = walk_t::kAhead * walk_t::kWindow;
+    extern __shared__ __align__(16) unsigned char lds_raw[];       // the waves' windows, and a zero
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t gid = (int64_t)blockIdx.x * kWavesFew + wave;
+    if (gid >= p.total_groups) return;
+    const int64_t row = gid / p.groups, g = gid - row * p.groups;
+    walk_t walk{p, lane, lds_raw + wave * kRing};
+    walk.k = p.K; walk.n2 = 0; walk.i = 0; walk.j = 2 * p.K;       // (before the first coordinate: one of magnitude 0)
+#pragma unroll
+    for (int j = 0; j < CP; j++) walk.y[j] = 0;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
+    walk.near_from = lds0 + wave * kRing + 1024 * (W / 4) + 8 * (63 - lane);
+    walk.entry = lane < W ? -4 * W : 0;
+#pragma unroll
+    for (int u = 0; u < walk_t::kAhead; u++)
+        walk.from[u] = lds0 + (lane < W ? wave * kRing + u * walk_t::kWindow + 4 * lane + 63 * 4 * W : kWavesFew * kRing);
+    asm volatile("ds_write_b32 %0, %1" : : "v"(lds0 + kWavesFew * kRing), "v"(0u) : "memory");
+    const int b0 = max(2 * p.K - 62, 0);
+    walk.template fetch<0>(D - 1, b0);
+    walk.template fetch<1>(D - 2, b0);
+    walk.template fetch<2>(D - 3, b0);
+    // q = N(D,K) - 1 - index; an index that is no codeword decodes to zeros
+    walk.q = 0;
+#pragma unroll
+    for (int x = 0; x < W; x++) walk.q = lane == x ? p.last_index[x] : walk.q;
+    const uint32_t borrows = walk_t::subtract(walk.q, lane < W ? index_word(p.index + row * p.index_row_words, p, g, lane) : 0u);
+    const bool valid = !((borrows >> W) & 1u);
+    if (valid) {
+#pragma unroll 1
+        while (walk.i < D) {
+            walk.template step<0>();
+            walk.template step<1>();
+            walk.template step<2>();
+            walk.template step<3>();
+        }
+        walk.template finish<3>();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");             // (the workgroup's LDS is not given back before the last loads into it)
+    const float gain = valid ? p.scale[gid] / sqrtf((float)walk.n2) : 0.0f;
+    float v[CP];
+#pragma unroll
+    for (int j = 0; j < CP; j++) v[j] = gain * (float)walk.y[j];
+    store_values<CP>(p, row * p.ldw + g * D + CP * lane, v);
 }
 
 int gcd_int(int a, int b) { return b ? gcd_int(b, a % b) : a; }
@@ -822,7 +970,8 @@ hipError_t pvq_wide_launch_encode(const pvq_ctx *c, const pvq_encode_args &a, in
     encode_wide_params p;
     p.X = a.W; p.ldx = a.ldw; p.groups = a.groups; p.index_row_words = a.index_row_words;
     p.K = c->K; p.bits = c->index_bits; p.ls = a.ls_amplitude;
-    p.tab_c = c->tab_c;
+    p.tab_t = c->tab_u; p.row_len = pvq_wide_row(c->K);
+    for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
     p.index_out = a.index_out; p.scale_out = reinterpret_cast<float *>(a.scale_out); p.pulses_out = a.pulses_out;
     p.cols = a.cols;
     // 16 lanes per group, four groups per wave, when the index and the word it may spill into fit 16 lanes
@@ -870,7 +1019,9 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
     p.e.X = nullptr; p.e.ldx = 0; p.e.groups = a.groups; p.e.index_row_words = a.index_row_words;
     p.e.K = c->K; p.e.bits = c->index_bits; p.e.ls = a.ls_amplitude;
     p.e.tile_groups = L / 16; p.e.tiles_per_row = p.chunks_per_row;
-    p.e.tab_c = c->tab_c; p.e.index_out = a.index_out; p.e.scale_out = reinterpret_cast<float *>(a.scale_out);
+    p.e.tab_t = c->tab_u; p.e.row_len = pvq_wide_row(c->K);
+    for (int i = 0; i < 16; i++) p.e.last_index[i] = c->last_index[i];
+    p.e.index_out = a.index_out; p.e.scale_out = reinterpret_cast<float *>(a.scale_out);
     p.e.pulses_out = nullptr; p.e.cols = a.cols;
     if (a.rows * p.chunks_per_row > 0x7FFFFFFF) return hipErrorInvalidValue;
     size_t lds = (size_t)(L / 16) * c->index_bits / 8 + 16;
@@ -898,28 +1049,40 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
     return hipGetLastError();
 }
 
+// Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full
+// (8192-wide rows of D = 128, K = 187: 23 us for 64 groups, 30 for 1024, 75 for 4096, 142 for 8192); a lane per group
+// takes the one walk of a wave whatever their number, until there are several waves per SIMD (95 us from 64 groups to
+// 32768, 157 for 131072, 162 for 262144).  D = 64, K = 96: 13, 17 (2048), 62 (8192) against 53, the same line.
+constexpr int64_t kFewGroups = 5120;
+
 hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
     decode_wide_params p;
     p.index = a.index; p.scale = reinterpret_cast<const float *>(a.scale);
     p.groups = a.groups; p.total_groups = a.rows * a.groups; p.index_row_words = a.index_row_words; p.ldw = a.ldw;
-    p.K = c->K; p.bits = c->index_bits; p.tab_n = c->tab_n; p.tab_e = c->tab_u; p.tab_key = c->tab_key; p.W_out = a.W_out;
-    if ((p.total_groups + kDecodeLanes - 1) / kDecodeLanes > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const size_t lds = (size_t)kDecodeLanes * decode_point_bytes(c->D, c->K) + (size_t)kDecodeLanes * 4;
-    const dim3 grid((unsigned)((p.total_groups + kDecodeLanes - 1) / kDecodeLanes)), blk(kDecodeLanes);
-#define PVQ_WIDE_DEC(O, CP, W) hipLaunchKernelGGL((decode_wide_kernel<O, CP, W>), grid, blk, lds, s, p)
-#define PVQ_WIDE_DEC_W(O, CP)                                  \
-    switch (c->words) {                                        \
-    case 4: PVQ_WIDE_DEC(O, CP, 4); break;                     \
-    case 8: PVQ_WIDE_DEC(O, CP, 8); break;                     \
-    case 12: PVQ_WIDE_DEC(O, CP, 12); break;                   \
-    default: PVQ_WIDE_DEC(O, CP, 16); break;                   \
+    p.K = c->K; p.bits = c->index_bits; p.out_dtype = out_dtype;
+    p.row_len = pvq_wide_row(c->K); p.key_len = pvq_wide_key_row(c->K); p.buckets = pvq_wide_buckets(c->words);
+    p.tab_t = c->tab_u; p.tab_key = c->tab_key; p.tab_near = c->tab_near; p.tab_guess = c->tab_guess;
+    p.W_out = a.W_out;
+    for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
+    if ((p.total_groups + 63) / 64 > 0x7FFFFFFF) return hipErrorInvalidValue;
+    const bool few = p.total_groups <= kFewGroups;
+    const size_t lds = few ? (size_t)kWavesFew * 4 * 1024 * (c->words / 4 + 1) + 16 : (size_t)64 * decode_point_bytes(c->D, c->K);
+    const int per_block = few ? kWavesFew : 64;
+    const dim3 grid((unsigned)((p.total_groups + per_block - 1) / per_block)), blk(few ? 64 * kWavesFew : 64);
+#define PVQ_WIDE_DEC(CP, W)                                                                                              \
+    do {                                                                                                                 \
+        if (few) hipLaunchKernelGGL((decode_wide_wave_kernel<CP, W>), grid, blk, lds, s, p);                             \
+        else hipLaunchKernelGGL((decode_wide_kernel<CP, W>), grid, blk, lds, s, p);                                      \
+    } while (0)
+#define PVQ_WIDE_DEC_W(CP)                                  \
+    switch (c->words) {                                     \
+    case 4: PVQ_WIDE_DEC(CP, 4); break;                     \
+    case 8: PVQ_WIDE_DEC(CP, 8); break;                     \
+    case 12: PVQ_WIDE_DEC(CP, 12); break;                   \
+    default: PVQ_WIDE_DEC(CP, 16); break;                   \
     }
-#define PVQ_WIDE_DEC_D(O) if (c->D == 128) { PVQ_WIDE_DEC_W(O, 2) } else { PVQ_WIDE_DEC_W(O, 1) }
-    if (out_dtype == PVQ_F32) { PVQ_WIDE_DEC_D(PVQ_F32) }
-    else if (out_dtype == PVQ_F16) { PVQ_WIDE_DEC_D(PVQ_F16) }
-    else { PVQ_WIDE_DEC_D(PVQ_BF16) }
-#undef PVQ_WIDE_DEC_D
+    if (c->D == 128) { PVQ_WIDE_DEC_W(2) } else { PVQ_WIDE_DEC_W(1) }
 #undef PVQ_WIDE_DEC_W
 #undef PVQ_WIDE_DEC
     return hipGetLastError();

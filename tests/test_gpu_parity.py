@@ -247,6 +247,15 @@ def test_long_groups_adversarial(D, K):
         run_long_groups(X, D, K, amplitude="ls")
 
 
+@pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
+@pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
+def test_long_groups_both_decoders(D, K, rows, groups):
+    # a wave per group up to 5120 groups, a lane per group beyond (5121: a last wave with one group); rows of
+    # thresholds just shorter and just longer than a window, points kept as bytes and as int16
+    X = si.adversarial_groups(1 << 13, D, seed=K)[:rows * groups].reshape(rows, groups * D)
+    run_long_groups(np.ascontiguousarray(X), D, K)
+
+
 @pytest.mark.parametrize("tokens,hidden,block,bits_per_value,bf16", [(5, 8192, 8192, 3, True), (3, 16384, 8192, 3, False),
                                                                      (9, 4096, 4096, 3, True), (4, 12288, 4096, 2, False),
                                                                      (7, 2048, 512, 3, True), (6, 6144, 2048, 3, True),
