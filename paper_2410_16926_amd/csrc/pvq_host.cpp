@@ -203,80 +203,91 @@ extern "C" int pvq_beta_tables(int D, int64_t G, int scale_bits, double *edges, 
 
 namespace {
 
-U512 shifted_left(const U512 &v, int n)   // n < 512; bits shifted out are lost
-{
-    U512 r;
-    const int limbs = n / 64, bits = n % 64;
-    for (int i = 7; i >= limbs; i--) {
-        uint64_t x = v.limb[i - limbs] << bits;
-        if (bits && i - limbs - 1 >= 0) x |= v.limb[i - limbs - 1] >> (64 - bits);
-        r.limb[i] = x;
-    }
-    return r;
-}
+typedef unsigned __int128 u128;
 
-bool less_or_equal(const U512 &a, const U512 &b)
-{
-    for (int i = 7; i >= 0; i--)
-        if (a.limb[i] != b.limb[i]) return a.limb[i] < b.limb[i];
-    return true;
-}
+u128 low128(const U512 &v) { return ((u128)v.limb[1] << 64) | v.limb[0]; }
 
-// Lays the blob out (pvq_walk.h has the layout's formulas) and fills it: rows d' = 1 .. D-1 of U(d',x),
-// x = -1 .. K+1; guess rows for d' >= 2: entry 0 for q/2 = 0, entry 1 + (e << mb) + f for q/2 in
-// [2^e (1 + f / 2^mb), 2^e (1 + (f+1) / 2^mb)) = the number of x in [0, K] with U(d',x) <= that bucket's lower edge.
-bool build_walk_tables(const SizeTable &t, int D, int K, int words, std::vector<unsigned char> &blob, pvq_walk_params &p)
+// Lays the blob out (pvq_walk.h has the layout's formulas) and fills it.  Bucket (e, f) of a guess row with mb fraction
+// bits holds the q whose float, as the decoder forms it from q | 1, lies in [2^e (1 + f / 2^mb), 2^e (1 + (f+1) / 2^mb));
+// its guess is the last threshold that is not above any of them.
+template <int D, int W, int DX, int DA, int DB>
+bool fill_walk_tables(const SizeTable &t, std::vector<unsigned char> &blob, pvq_walk_params &p)
 {
     using namespace pvq_walk;
-    if (D > 32 || K > 253) return false;
-    memset(&p, 0, sizeof p);
-    int fit_half = 0, fit_quarter = 0;
-    for (int d = 1; d < D; d++) {
-        if (words >= 2 && t.at(d, K).bit_length() <= 16 * words) fit_half = d;
-        if (words >= 4 && t.at(d, K).bit_length() <= 8 * words) fit_quarter = d;
-    }
-    pvq_walk_schedule(D, words, fit_half, fit_quarter, &p.dA, &p.dB);
-    if (p.dA > fit_half || p.dB > fit_quarter || p.dB > p.dA) return false;
-    p.K = K;
-    for (int cls = 0; cls < 3; cls++) p.row_bytes[cls] = (uint32_t)(((size_t)(K + 3) * ((4 * words) >> cls) + 15) / 16 * 16);
-    blob.clear();
-    // cumulative rows
-    std::vector<std::vector<U512>> U(D);
-    for (int dp = 1; dp < D; dp++) {
-        const int es = pvq_walk_entry_bits(dp, words, p.dA, p.dB) / 8;
-        U512 run;
-        for (int x = 0; x <= K; x++) { run.add(t.at(dp, x)); U[dp].push_back(run); }
-        if (run.bit_length() > 8 * es) return false;
-        const size_t first = blob.size();
-        blob.resize(first + p.row_bytes[pvq_walk_class(dp, p.dA, p.dB)], 0);
-        for (int x = 0; x <= K; x++)
-            for (int w = 0; w < es / 4; w++) {
-                const uint32_t v = U[dp][x].word(w);
-                memcpy(&blob[first + (size_t)(x + 1) * es + 4 * w], &v, 4);
+    const int K = p.K, entries = 2 * K + 3;
+    for (int i = 0; i < 3; i++) p.part_bytes[i] = (uint32_t)((entries * (4 << i) + 15) / 16 * 16);
+    uint32_t at = threshold_base(D, W, DX, DA, DB);
+    blob.assign(at, 0);
+    p.more = 0;
+    std::vector<u128> T(entries);
+    for (int dp = D - 1; dp >= 2; dp--) {
+        const int words = words_of_row(dp, W, DX, DA, DB), mb = guess_bits(dp, D);
+        const u128 limit = low128(t.at(dp + 1, K));                // of q
+        if (t.at(dp + 1, K).bit_length() > 32 * words) return false;
+        u128 even = 0;
+        for (int C = 0; C <= K; C++) {
+            const u128 n = low128(t.at(dp, C));
+            T[2 * C] = even;
+            T[2 * C + 1] = even + n;
+            even += 2 * n;
+        }
+        T[2 * K + 2] = ~(u128)0;
+        blob.resize(at + row_bytes(p, words), 0);
+        for (int j = 0; j < entries; j++)
+            for (int w = 0; w < words; w++) {
+                const uint32_t v = (uint32_t)(T[j] >> (32 * w));
+                memcpy(&blob[words == 3 ? (w < 2 ? at + 8 * j + 4 * w : at + p.part_bytes[1] + 4 * j) : at + 4 * (words * j + w)], &v, 4);
             }
-        memset(&blob[first + (size_t)(K + 2) * es], 0xFF, es);        // never <= q/2
-    }
-    // guess rows
-    p.guess_base = (uint32_t)blob.size();
-    for (int dp = 2; dp < D; dp++) {
-        const int mb = pvq_walk_mb(dp);
-        const int n = (int)pvq_walk_guess_entries(dp, pvq_walk_entry_bits(dp, words, p.dA, p.dB));
-        if (blob.size() != p.guess_base + pvq_walk_guess_offset(dp, words, p.dA, p.dB)) return false;
-        for (int idx = 0; idx < n; idx++) {
-            int count = 0;
-            if (idx >= 1) {
-                const int e = (idx - 1) >> mb, f = (idx - 1) & ((1 << mb) - 1);
-                // U <= (2^mb + f) 2^(e - mb)   <=>   U 2^mb <= (2^mb + f) 2^e
-                const U512 edge = shifted_left(U512::of((uint64_t)((1 << mb) + f)), e);
-                for (int x = 0; x <= K; x++)
-                    if (less_or_equal(shifted_left(U[dp][x], mb), edge)) count = x + 1;
-            }
-            blob.push_back((unsigned char)count);
+        at = (uint32_t)blob.size();
+        // the buckets
+        unsigned char *guess = &blob[guess_row(dp, D, W, DX, DA, DB)];
+        const uint32_t n = guess_entries(dp, D, words);
+        const u128 one = 1;
+        auto edge = [&](uint32_t b) -> u128 {                      // the bucket's lower edge, rounded up
+            const int e = (int)(b >> mb);
+            const u128 f = (one << mb) + (b & ((1u << mb) - 1u));
+            if (e >= 128) return ~(u128)0;
+            return e >= mb ? f << (e - mb) : (f + (one << (mb - e)) - 1) >> (mb - e);
+        };
+        int j = 0, above = 0;                                      // thresholds: the last <= from, the last <= to
+        for (uint32_t b = 0; b < n; b++) {
+            // q from .. to: exact below 2^23, with what the roundings may move beyond it
+            u128 from = edge(b), to = edge(b + 1);
+            if (from >> 23) from -= from >> 21;
+            if (to >> 23) to += std::min(to >> 21, ~(u128)0 - to);
+            from -= from & 1;                                      // (q | 1)
+            to = std::min(to, limit);                              // (exclusive)
+            if (from >= to) { guess[b] = (unsigned char)j; continue; }
+            while (T[j + 1] <= from) j++;
+            above = std::max(above, j);
+            while (T[above + 1] < to) above++;
+            guess[b] = (unsigned char)j;
+            if (above > j + 1) p.more = 1;
         }
     }
-    blob.resize((blob.size() + 15) / 16 * 16);
     p.bytes = (uint32_t)blob.size();
-    return true;
+    return searches(D, W, DX, DA) || !p.more;
+}
+
+bool build_walk_tables(const SizeTable &t, int D, int K, int words, std::vector<unsigned char> &blob, pvq_walk_params &p)
+{
+    if (D > 32 || K > 127) return false;
+    memset(&p, 0, sizeof p);
+    int fit_3q = 0, fit_half = 0, fit_quarter = 0;
+    for (int d = 1; d < D; d++) {
+        const int bits = t.at(d, K).bit_length();
+        if (words >= 4 && bits <= 24 * words) fit_3q = d;
+        if (words >= 2 && bits <= 16 * words) fit_half = d;
+        if (words >= 4 && bits <= 8 * words) fit_quarter = d;
+    }
+    pvq_walk_schedule(D, words, fit_3q, fit_half, fit_quarter, &p.dX, &p.dA, &p.dB);
+    p.K = K;
+    U512 last = t.at(D, K);
+    last.decrement();
+    for (int w = 0; w < 4; w++) p.last_index[w] = last.word(w);
+#define PVQ_WALK_FILL(D_, W_, DX_, DA_, DB_) fill_walk_tables<D_, W_, DX_, DA_, DB_>(t, blob, p)
+    PVQ_WALK_DISPATCH(PVQ_WALK_FILL, D, words, p.dX, p.dA, p.dB);
+#undef PVQ_WALK_FILL
 }
 
 }  // namespace
@@ -778,10 +789,6 @@ extern "C" int pvq_decode_gemv_plan(const pvq_ctx *c, int64_t rows, int64_t cols
 
 namespace {
 
-typedef unsigned __int128 u128;
-
-u128 low128(const U512 &v) { return ((u128)v.limb[1] << 64) | v.limb[0]; }
-
 // App. B.3 as printed (with the corrections of the boundary's decode contract), in 128-bit integers
 void plain_unrank(const SizeTable &t, int D, int K, u128 c, int *y)
 {
@@ -801,7 +808,7 @@ void plain_unrank(const SizeTable &t, int D, int K, u128 c, int *y)
     y[D - 1] = r == 0 ? k : -k;
 }
 
-template <int D, int W, int DA, int DB>
+template <int D, int W, int DX, int DA, int DB>
 uint64_t replay_walk(const SizeTable &t, int K, const std::vector<unsigned char> &blob, const pvq_walk_params &p,
                      uint64_t seed, uint64_t count)
 {
@@ -826,8 +833,8 @@ uint64_t replay_walk(const SizeTable &t, int K, const std::vector<unsigned char>
         plain_unrank(t, D, K, c, want);
         int n2w = 0;
         for (int i = 0; i < D; i++) n2w += want[i] * want[i];
-        const int n2 = pvq_walk::unrank_walk<D, W, DA, DB>((T)c, blob.data(), p, [&](int i, uint32_t m, bool negative) { got[i] = negative ? -(int)m : (int)m; });
-        bool same = n2 == n2w;
+        const float n2 = pvq_walk::unrank_walk<D, W, DX, DA, DB>((T)c, blob.data(), p, [&](int i, float minus_y) { got[i] = -(int)minus_y; });
+        bool same = n2 == (float)n2w;
         for (int i = 0; i < D; i++) same = same && got[i] == want[i];
         bad += !same;
     }
@@ -852,7 +859,7 @@ extern "C" int pvq_walk_tables_selftest(int D, int K, uint64_t seed, uint64_t co
     if (!build_walk_tables(t, D, K, words, blob, p)) return PVQ_E_UNSUPPORTED;
     if (schedule) { schedule[0] = p.dA; schedule[1] = p.dB; }
     if (table_bytes) *table_bytes = p.bytes;
-#define PVQ_WALK_REPLAY(D_, W_, DA_, DB_) (*mismatches = replay_walk<D_, W_, DA_, DB_>(t, K, blob, p, seed, count), PVQ_OK)
-    PVQ_WALK_DISPATCH(PVQ_WALK_REPLAY, D, words, p.dA, p.dB);
+#define PVQ_WALK_REPLAY(D_, W_, DX_, DA_, DB_) (*mismatches = replay_walk<D_, W_, DX_, DA_, DB_>(t, K, blob, p, seed, count), PVQ_OK)
+    PVQ_WALK_DISPATCH(PVQ_WALK_REPLAY, D, words, p.dX, p.dA, p.dB);
 #undef PVQ_WALK_REPLAY
 }

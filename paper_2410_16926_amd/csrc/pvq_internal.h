@@ -11,18 +11,18 @@
 #include "pvq.h"
 #include "pvq_fast8.h"
 
-// Tables of the coordinate-by-coordinate decoder (pvq_walk.hip), one blob copied to LDS by every workgroup:
-// rows of the cumulative size table U(d', x) = N(d',0) + ... + N(d',x) for d' = 1 .. D-1 in this order, entries
-// x = -1 .. K+1 (U(d',-1) = 0; the entry behind the row is all ones), each row in the width of its dimension's
-// arithmetic and padded to a multiple of 16 bytes; behind them a guess row of bytes per d' >= 2.  Where a row
-// lies follows from the schedule (known when the kernels are compiled) and three row sizes, so that the
-// kernels carry a handful of scalars rather than an offset per row (pvq_walk.h: pvq_walk_row, pvq_walk_guess).
+// Tables of the coordinate-by-coordinate decoder (pvq_walk.hip), one blob copied to LDS by every workgroup behind the
+// amplitude table: a guess row of bytes per d' = D-1 .. 2, then the rows of thresholds T_j (below) for d' = D-1 .. 2, each
+// in the width of its dimension's arithmetic, with an entry of all ones behind T_{2K+1}, padded to a multiple of 16
+// bytes.  Where a row lies follows from the schedule (known when the kernels are compiled) and three sizes
+// (pvq_walk.h: guess_row, row_bytes).
 struct pvq_walk_params {
-    uint32_t bytes;         // of the blob (a multiple of 16)
+    uint32_t bytes;         // of the blob, the amplitude table in front included (a multiple of 16)
     int K;
-    int dA, dB;             // the width schedule: dimensions above dA in `words` words, above dB in half, the rest in a quarter
-    uint32_t row_bytes[3];  // bytes of a cumulative row in full, half and quarter width
-    uint32_t guess_base;    // byte offset of the first guess row (d' = 2)
+    int dX, dA, dB;         // the width schedule: dimensions above dX in `words` words, above dA in three quarters of them, above dB in half, the rest in a quarter
+    int more;               // 1: some bucket holds more than one threshold besides its guess
+    uint32_t part_bytes[3]; // bytes of a row with entries of 4, 8 and 16 bytes (a row of 12-byte entries: the first two)
+    uint32_t last_index[4]; // N(D,K) - 1
 };
 
 // A multi-word integer (w[0] the lowest word) as 32 bits that order like the integer wherever they differ: its
@@ -52,7 +52,7 @@ inline double pvq_wide_double(const uint32_t *w, int words)
     return ldexp((double)w[t] * 4294967296.0 + (t > 0 ? (double)w[t - 1] : 0.0), 32 * t - 32);   // (the product is exact)
 }
 
-// Contexts with D = 64 or 128.  With U(d,x) = N(d,0) + ... + N(d,x) and q = N(d,k) - 1 - r for the residual r in the
+// Thresholds.  With U(d,x) = N(d,0) + ... + N(d,x) and q = N(d,k) - 1 - r for the residual r in the
 // sub-pyramid of d dimensions and k pulses, the points that leave C pulses to the d - 1 coordinates behind lie at
 //     2 U(d-1,C-1) <= q < 2 U(d-1,C),
 // the negative ones (q - 2 U(d-1,C-1) < N(d-1,C)) first; C = k, the magnitude 0, has that half only.  So row d - 1 is
@@ -60,8 +60,8 @@ inline double pvq_wide_double(const uint32_t *w, int words)
 //     T_{2C} = 2 U(d-1,C-1),  T_{2C+1} = T_{2C} + N(d-1,C),      C = 0 .. K,
 // a coordinate of the point is its position j in it (C = j / 2 pulses left, positive iff j is odd), the next q is
 // q - T_j, and after the last coordinate q = 0.  Hence N(D,K) - 1 - index = the sum of the thresholds of all
-// coordinates: the encoders add them up, the decoders find them one after the other.
-// Rows are at least as long as the windows of 64 that a decoder reads, with all ones behind the thresholds.
+// coordinates: an encoder adds them up, a decoder finds them one after the other.
+// Contexts with D = 64 or 128: rows are at least as long as the windows of 64 that a decoder reads, with all ones behind the thresholds.
 inline int pvq_wide_row(int K) { return K < 31 ? 64 : 2 * K + 2; }
 inline int pvq_wide_key_row(int K) { return 2 * K + 2 + 6; }
 // The other decoder's first guess: keys by bit length and the three bits behind the leading one (their bits 18 to 31, less 21).

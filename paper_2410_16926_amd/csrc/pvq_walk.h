@@ -14,7 +14,7 @@
 
 namespace pvq_walk {
 
-PVQ_HD uint32_t pvq_float_bits(float f)
+PVQ_HD uint32_t float_bits(float f)
 {
 #if defined(__HIP_DEVICE_COMPILE__)
     return __float_as_uint(f);
@@ -25,214 +25,237 @@ PVQ_HD uint32_t pvq_float_bits(float f)
 #endif
 }
 
+PVQ_HD float bits_float(uint32_t u)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return __uint_as_float(u);
+#else
+    float f;
+    memcpy(&f, &u, 4);
+    return f;
+#endif
+}
+
 template <int W> struct wide;
 template <> struct wide<1> { using type = uint32_t; };
 template <> struct wide<2> { using type = uint64_t; };
 template <> struct wide<4> { using type = unsigned __int128; };
 
-// Keeps a 32-bit word of a wider integer a 32-bit value in the compiler's eyes: otherwise the conversion of a
-// word known to be a shifted-down 64-bit value is widened back into a 64-bit-to-float conversion (five
-// instructions instead of one).
-#if defined(__HIP_DEVICE_COMPILE__)
-#define PVQ_WALK_OPAQUE(x) asm volatile("" : "+v"(x))
-#else
-#define PVQ_WALK_OPAQUE(x) ((void)0)
-#endif
-
 // ---- layout of the blob (shared with the host builder) ---------------------------------------------------
-// entry width class of row DP under the schedule (DA, DB): 0 full, 1 half, 2 quarter
-constexpr int pvq_walk_class(int dp, int DA, int DB) { return dp >= DA ? 0 : dp >= DB ? 1 : 2; }
-// fraction bits of guess row DP: the rows of the lowest dimensions grow slowly and get finer buckets
-constexpr int pvq_walk_mb(int dp) { return dp == 2 ? 5 : dp == 3 ? 4 : 3; }
-// entries of guess row DP: every value of the row's integer type (entry_bits wide) lands inside
-constexpr uint32_t pvq_walk_guess_entries(int dp, int entry_bits) { return ((uint32_t)(entry_bits + 3) << pvq_walk_mb(dp)) + 1u; }
-constexpr int pvq_walk_entry_bits(int dp, int W, int DA, int DB) { return (32 * W) >> pvq_walk_class(dp, DA, DB); }
-// byte offset of guess row DP behind guess_base
-constexpr uint32_t pvq_walk_guess_offset(int dp, int W, int DA, int DB)
+// Words of row DP's integers under the schedule (D, W, DX, DA, DB): dimensions (DP + 1 are left) above DX in W words,
+// above DA in three quarters, above DB in half of them, the rest in a quarter.
+constexpr int words_of_row(int dp, int W, int DX, int DA, int DB) { return dp >= DX ? W : dp >= DA ? 3 * W / 4 : dp >= DB ? W / 2 : W / 4; }
+// Fraction bits of guess row DP, chosen so that a bucket of q holds one threshold besides the one its guess stands for
+// (the rows of few dimensions grow slowly and get finer buckets).  Enough for every K of the schedules
+// that have no search behind the guess (searches); with the others pvq_walk_params::more says whether they are.
+constexpr int guess_bits(int dp, int D)
 {
-    uint32_t off = 0;
-    for (int j = 2; j < dp; j++) off += pvq_walk_guess_entries(j, pvq_walk_entry_bits(j, W, DA, DB));
-    return off;
+    return D == 32 ? (dp == 2 ? 6 : dp <= 5 ? 5 : dp <= 13 ? 4 : 3) : dp == 2 ? 5 : dp <= 10 ? 4 : 3;
 }
-// rows 1 .. dp-1 lie in front of row dp: how many of each width class
-constexpr int pvq_walk_rows_before(int dp, int cls, int DA, int DB)
+constexpr bool searches(int D, int W, int DX, int DA) { return DA == 0 ? W == 4 || (W == 2 && D <= 16) : W == 4 && DX == DA; }
+// entries of guess row DP: every value of the row's integer type lands inside (up to 2^(32 words), where the largest round to)
+constexpr uint32_t guess_entries(int dp, int D, int words) { return ((uint32_t)(32 * words) << guess_bits(dp, D)) + 1u; }
+// The guess of bucket b of row DP lies at byte guess_offset(DP) + b.  Buckets are floats shifted down, of which 1 is the
+// smallest, so b starts at 127 << guess_bits, and the rows follow one another from the highest dimension, the coarsest,
+// on (the lower ones start far enough behind the amplitude table in front for the offset to be a plain
+// immediate: a row never starts below its 127 << guess_bits).
+constexpr uint32_t kWalkHead = 1024;               // the amplitude table, 256 floats
+constexpr uint32_t guess_row(int dp, int D, int W, int DX, int DA, int DB)
 {
-    int n = 0;
-    for (int j = 1; j < dp; j++) n += pvq_walk_class(j, DA, DB) == cls;
-    return n;
-}
-// byte offset of U(DP, 0) (the row starts one entry earlier, with U(DP,-1) = 0)
-template <int DP, int W, int DA, int DB>
-PVQ_HD uint32_t pvq_walk_row(const pvq_walk_params &p)
-{
-    return p.row_bytes[0] * (uint32_t)pvq_walk_rows_before(DP, 0, DA, DB) + p.row_bytes[1] * (uint32_t)pvq_walk_rows_before(DP, 1, DA, DB) +
-           p.row_bytes[2] * (uint32_t)pvq_walk_rows_before(DP, 2, DA, DB) + (uint32_t)(pvq_walk_entry_bits(DP, W, DA, DB) / 8);
-}
-
-// Place of h among the buckets of a guess row with MB fraction bits: 0 for h = 0, else 1 + (e << MB) + f for
-// h in [2^e (1 + f / 2^MB), 2^e (1 + (f+1) / 2^MB)), or the bucket below when h lies within 2^-20 (relative)
-// of the bucket's lower edge: conversions and sums round to nearest, the last factor takes back more than
-// they can add, so the float is not above h.
-template <int MB>
-PVQ_HD uint32_t bucket_of_float(float f, uint32_t cap)
-{
-    f *= 1.0f - 0x1p-21f;
-    constexpr uint32_t base = (127u << MB) - 1u;
-    const uint32_t idx = std::max(pvq_float_bits(f) >> (23u - MB), base) - base;
-    return std::min(idx, cap);
-}
-
-// Half of q as the integer h, and its bucket.  For two-word integers h is put together from the two words that
-// the conversion to float uses, so that the shift is made once.
-template <typename T, int MB>
-PVQ_HD uint32_t half_and_bucket(T q, T &h)
-{
-    if constexpr (sizeof(T) == 4) {
-        h = q >> 1;
-        return bucket_of_float<MB>((float)h, 0xFFFFFFFFu);
-    } else if constexpr (sizeof(T) == 8) {
-        uint32_t hi = (uint32_t)(q >> 33);
-        const uint32_t lo = (uint32_t)(q >> 1);
-        PVQ_WALK_OPAQUE(hi);
-        h = ((T)hi << 32) | lo;
-        return bucket_of_float<MB>(fmaf((float)hi, 4294967296.0f, (float)lo), 0xFFFFFFFFu);
-    } else {
-        h = q >> 1;
-        uint32_t w3 = (uint32_t)(h >> 96), w2 = (uint32_t)(h >> 64), w1 = (uint32_t)(h >> 32);
-        PVQ_WALK_OPAQUE(w3); PVQ_WALK_OPAQUE(w2); PVQ_WALK_OPAQUE(w1);
-        float f = fmaf((float)w3, 4294967296.0f, (float)w2);
-        f = fmaf(f, 4294967296.0f, (float)w1);
-        f = fmaf(f, 4294967296.0f, (float)(uint32_t)h);
-        return bucket_of_float<MB>(f, 130u << MB);                            // 2^128 - 1 rounds to infinity
+    uint32_t at = kWalkHead;
+    for (int j = D - 1; j >= dp; j--) {
+        const uint32_t least = 127u << guess_bits(j, D);
+        at = at < least ? least : at;
+        if (j > dp) at += guess_entries(j, D, words_of_row(j, W, DX, DA, DB));
     }
+    return at;
+}
+// end of the guess rows, where the thresholds start
+constexpr uint32_t threshold_base(int D, int W, int DX, int DA, int DB)
+{
+    return (guess_row(2, D, W, DX, DA, DB) + guess_entries(2, D, words_of_row(2, W, DX, DA, DB)) + 15u) / 16u * 16u;
+}
+// Rows of thresholds follow in the order DP = D-1 .. 2, each of 2K + 3 entries, padded to 16 bytes; rows of three words
+// in two parts, the lower two words of all entries in front of the third ones.
+// bytes of a row
+PVQ_HD uint32_t row_bytes(const pvq_walk_params &p, int words)
+{
+    return words == 1 ? p.part_bytes[0] : words == 2 ? p.part_bytes[1] : words == 3 ? p.part_bytes[0] + p.part_bytes[1] : p.part_bytes[2];
 }
 
-// One coordinate with d = DP + 1 dimensions left (row DP of the cumulative table) under the schedule
-// <W, DA, DB>.  q, k in and out; returns the coordinate's magnitude, sets `negative` and adds the square to n2.
-template <typename T, int DP, int W, int DA, int DB>
-PVQ_HD uint32_t walk_step(const unsigned char *lds, const pvq_walk_params &p, T &q, int &k, int &n2, bool &negative)
+// q (its lowest bit set, so that it is not zero) as a float: each operation rounds to nearest, which the builder of the
+// guess rows allows for.
+template <int WP>
+PVQ_HD float float_of(const uint32_t *q)
 {
-    T h;
-    uint32_t C;
-    T um, ux;
-    if constexpr (DP == 1) {
-        // U(1,x) = 2x + 1
-        h = q >> 1;
-        C = (uint32_t)std::min<T>((h + 1) >> 1, (T)(uint32_t)k);
-        ux = (T)(2u * C + 1u);
-        um = C ? (T)(2u * C - 1u) : (T)0;
-    } else {
-        const uint32_t idx = half_and_bucket<T, pvq_walk_mb(DP)>(q, h);
-        C = lds[p.guess_base + pvq_walk_guess_offset(DP, W, DA, DB) + idx];
-        const T *u = reinterpret_cast<const T *>(lds + pvq_walk_row<DP, W, DA, DB>(p));   // u[x] = U(DP, x), x = -1 .. K+1
-        um = u[(int)C - 1];
-        ux = u[C];
-        const T up = u[C + 1];
-        if (ux <= h) { C++; um = ux; ux = up; }
-        while (ux <= h) { C++; um = ux; ux = u[C]; }                          // ends: u[K+1] is all ones
-        C = std::min(C, (uint32_t)k);                                          // (a stored index >= N(D,K) only)
-    }
-    const uint32_t m = (uint32_t)k - C;
-    const T t = q - um;
-    negative = t < ux;
-    q = negative ? t - um : t - ux;
-    k = (int)C;
+    float f = (float)(WP == 1 ? q[0] | 1u : q[WP - 1]);
 #if defined(__HIP_DEVICE_COMPILE__)
-    n2 += __mul24((int)m, (int)m);                  // m <= K < 2^12
-#else
-    n2 += (int)(m * m);
+#pragma unroll
 #endif
-    return m;
+    for (int x = WP - 2; x >= 0; x--) f = fmaf(f, 4294967296.0f, (float)(x == 0 ? q[0] | 1u : q[x]));
+    return f;
 }
 
-// The state of a walk: the residual in the three widths (one of them is live at a time), pulses left, sum of
-// squares.  coordinate<I>() decodes coordinate I (dimensions left: D - I) in the width of its schedule.
-template <int D, int W, int DA, int DB>
+// d = a - b over WP words; returns the borrow
+template <int WP>
+PVQ_HD uint32_t subtract(uint32_t *d, const uint32_t *a, const uint32_t *b)
+{
+    uint32_t borrow = 0;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+    for (int x = 0; x < WP; x++) d[x] = __builtin_subc(a[x], b[x], borrow, &borrow);
+    return borrow;
+}
+
+// One of a row's entries, or a guess, at a byte of the tables: LDS address in a kernel, where they start at 0 (an address
+// formed from the array's name would be an addition more).
+template <typename T>
+PVQ_HD T table_at(const unsigned char *tables, uint32_t byte)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return *reinterpret_cast<const __attribute__((address_space(3))) T *>(byte);
+#else
+    T v;
+    memcpy(&v, __builtin_assume_aligned(tables + byte, sizeof(T)), sizeof(T));
+    return v;
+#endif
+}
+typedef uint32_t word4 __attribute__((vector_size(16)));
+
+// entry j of the row of thresholds at byte `at`
+template <int WP>
+PVQ_HD void threshold(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t j, uint32_t *t)
+{
+    if constexpr (WP == 1) t[0] = table_at<uint32_t>(tables, at + 4u * j);
+    if constexpr (WP == 2 || WP == 3) {
+        const uint64_t v = table_at<uint64_t>(tables, at + 8u * j);
+        t[0] = (uint32_t)v; t[1] = (uint32_t)(v >> 32);
+    }
+    if constexpr (WP == 3) t[2] = table_at<uint32_t>(tables, at + p.part_bytes[1] + 4u * j);
+    if constexpr (WP == 4) {
+        const word4 v = table_at<word4>(tables, at + 16u * j);
+        t[0] = v[0]; t[1] = v[1]; t[2] = v[2]; t[3] = v[3];
+    }
+}
+
+// The coordinate of row DP (DP + 1 dimensions left), whose thresholds start at byte `at`: its place j in them
+// (pvq_internal.h).  q loses T_j.
+template <int DP, int D, int W, int DX, int DA, int DB>
+PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t *q)
+{
+    constexpr int WP = words_of_row(DP, W, DX, DA, DB);
+    if constexpr (DP == 1) {
+        // T = 0, 1, 2, 4, 6, ...
+        const uint32_t j = std::min(q[0], (q[0] >> 1) + 1u);
+        q[0] = q[0] < 2u ? 0u : q[0] & 1u;
+        return j;
+    } else {
+        constexpr int MB = guess_bits(DP, D);
+        constexpr uint32_t guesses = guess_row(DP, D, W, DX, DA, DB) - (127u << MB);
+        uint32_t j = table_at<uint8_t>(tables, guesses + (float_bits(float_of<WP>(q)) >> (23 - MB)));
+        uint32_t t0[WP], t1[WP], d0[WP], d1[WP];
+        if constexpr (searches(D, W, DX, DA)) {
+            if (p.more) {                                          // (the same for all lanes)
+                for (;; j++) {                                     // (ends: the entry behind the row's thresholds is all ones)
+                    threshold<WP>(tables, p, at, j + 1, t1);
+                    if (subtract<WP>(d1, q, t1)) break;
+                }
+            }
+        }
+        threshold<WP>(tables, p, at, j, t0);
+        threshold<WP>(tables, p, at, j + 1, t1);
+        subtract<WP>(d0, q, t0);
+        uint32_t borrow = subtract<WP>(d1, q, t1), unused;
+        const bool up = !borrow;
+        j = __builtin_subc(j, 0xFFFFFFFFu, borrow, &unused);       // j + 1 - borrow
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+        for (int x = 0; x < WP; x++) q[x] = up ? d1[x] : d0[x];
+        return j;
+    }
+}
+
+// The state of a walk: the residual, pulses left, sum of squares.
+template <int D, int W, int DX, int DA, int DB>
 struct walk_state {
-    using T0 = typename wide<W>::type;
-    using T1 = typename wide<(W >= 2 ? W / 2 : 1)>::type;
-    using T2 = typename wide<(W >= 4 ? W / 4 : 1)>::type;
-    T0 q0;
-    T1 q1;
-    T2 q2;
-    int k, n2;
+    uint32_t q[W];
+    uint32_t k, at;
+    float n2;
 
     template <int I, typename Emit>
-    PVQ_HD void coordinate(const unsigned char *lds, const pvq_walk_params &p, Emit &emit)
+    PVQ_HD void coordinate(const unsigned char *tables, const pvq_walk_params &p, Emit &emit)
     {
-        constexpr int d = D - I;                 // dimensions left, this coordinate included
-        uint32_t v;
-        bool negative;
-        if constexpr (d > DA) {
-            v = walk_step<T0, d - 1, W, DA, DB>(lds, p, q0, k, n2, negative);
-            if constexpr (d - 1 == DA) q1 = (T1)q0;          // the next coordinate runs in the narrower type
-            if constexpr (d - 1 == DA && DA == DB) q2 = (T2)q0;
-        } else if constexpr (d > DB) {
-            v = walk_step<T1, d - 1, W, DA, DB>(lds, p, q1, k, n2, negative);
-            if constexpr (d - 1 == DB) q2 = (T2)q1;
-        } else {
-            v = walk_step<T2, d - 1, W, DA, DB>(lds, p, q2, k, n2, negative);
-        }
-        emit(I, v, negative);
+        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, q);
+        at += row_bytes(p, words_of_row(D - 1 - I, W, DX, DA, DB));
+        const uint32_t C = j >> 1;
+        const float m = (float)(k - C);
+        k = C;
+        n2 = fmaf(m, m, n2);                                       // (exact: at most K^2 < 2^14)
+        emit(I, bits_float(j << 31 | float_bits(m)));
     }
     template <typename Emit, int... Is>
-    PVQ_HD void all(const unsigned char *lds, const pvq_walk_params &p, Emit &emit, std::integer_sequence<int, Is...>)
+    PVQ_HD void all(const unsigned char *tables, const pvq_walk_params &p, Emit &emit, std::integer_sequence<int, Is...>)
     {
-        (coordinate<Is>(lds, p, emit), ...);
+        (coordinate<Is>(tables, p, emit), ...);
     }
 };
 
-// The whole point from its index c.  emit(i, |y_i|, y_i < 0) for i = 0 .. D-1 in order (a coordinate that is 0
-// may come with either sign); returns sum y_i^2.
-template <int D, int W, int DA, int DB, typename Emit>
-PVQ_HD int unrank_walk(typename wide<W>::type c, const unsigned char *lds, const pvq_walk_params &p,
-                                  Emit &&emit)
+// The whole point from its index c, negated (the place of a positive coordinate is odd, which becomes a sign bit):
+// emit(i, -y_i) for i = 0 .. D-1 in order, +0 where y_i is 0; returns sum y_i^2.  An index that is no codeword decodes as
+// the last one.
+template <int D, int W, int DX, int DA, int DB, typename Emit>
+PVQ_HD float unrank_walk(typename wide<W>::type c, const unsigned char *tables, const pvq_walk_params &p, Emit &&emit)
 {
-    using T0 = typename wide<W>::type;
-    static_assert(DA < D && DB <= DA, "width schedule");
-    const int K = p.K;
-    const T0 *u0 = reinterpret_cast<const T0 *>(lds + pvq_walk_row<D - 1, W, DA, DB>(p));
-    walk_state<D, W, DA, DB> st;
-    st.q0 = u0[K] + u0[K - 1] - 1 - c;          // N(D,K) - 1 - c
-    st.q1 = 0; st.q2 = 0; st.k = K; st.n2 = 0;
-    st.all(lds, p, emit, std::make_integer_sequence<int, D - 1>{});
+    static_assert(DX <= D && DA <= DX && DB <= DA, "width schedule");
+    walk_state<D, W, DX, DA, DB> st;
+    uint32_t index[W];
+    for (int x = 0; x < W; x++) index[x] = (uint32_t)(c >> (32 * x));
+    const bool none = subtract<W>(st.q, p.last_index, index);
+    for (int x = 0; x < W; x++) st.q[x] = none ? 0u : st.q[x];
+    st.k = (uint32_t)p.K; st.n2 = 0.0f;
+    st.at = threshold_base(D, W, DX, DA, DB);
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(st.at));                                // (else a kernel's loop keeps a register per row)
+#endif
+    st.all(tables, p, emit, std::make_integer_sequence<int, D - 1>{});
     // the two points +k, -k of P(1,k): q = 1, 0
-    bool zero;
-    if constexpr (DB >= 1) zero = st.q2 == 0;
-    else if constexpr (DA >= 1) zero = st.q1 == 0;
-    else zero = st.q0 == 0;
-    emit(D - 1, (uint32_t)st.k, zero);
-    return st.n2 + st.k * st.k;
+    const float m = (float)st.k;
+    emit(D - 1, bits_float(st.q[0] << 31 | float_bits(m)));
+    return fmaf(m, m, st.n2);
 }
-
 
 }  // namespace pvq_walk
 
-// Which width schedule a context gets: fit_half / fit_quarter = the largest number of dimensions d whose
-// N(d,K) fits half / a quarter of the index's words.  Names only schedules listed in PVQ_WALK_DISPATCH.
-inline void pvq_walk_schedule(int D, int words, int fit_half, int fit_quarter, int *dA, int *dB)
+// Which width schedule a context gets: fit_3q / fit_half / fit_quarter = the largest number of dimensions d whose
+// N(d,K) fits three quarters / half / a quarter of the index's words.  Names only schedules listed in PVQ_WALK_DISPATCH.
+inline void pvq_walk_schedule(int D, int words, int fit_3q, int fit_half, int fit_quarter, int *dX, int *dA, int *dB)
 {
     *dA = 0; *dB = 0;
     if (D == 16 && words == 2 && fit_half >= 8) *dA = 8;
     if (D == 32 && words == 2 && fit_half >= 12) *dA = 12;
     if (D == 32 && words == 4 && fit_half >= 15 && fit_quarter >= 6) { *dA = 15; *dB = 6; }
+    *dX = *dA;
+    if (D == 32 && words == 4 && *dA == 15 && fit_3q >= 28) *dX = 28;
 }
 
-// The instantiated width schedules <D, W, DA, DB>: CALL(D, W, DA, DB) for the schedule (dA, dB) chosen for a
+// The instantiated width schedules <D, W, DX, DA, DB>: CALL(D, W, DX, DA, DB) for the schedule (dX, dA, dB) chosen for a
 // context of group size D with `words`-word indices.
-#define PVQ_WALK_DISPATCH(CALL, D_, W_, dA_, dB_)                                                       \
-    do {                                                                                                \
-        if ((D_) == 8) {                                                                                \
-            if ((W_) == 1) return CALL(8, 1, 0, 0);                                                     \
-            return CALL(8, 2, 0, 0);                                                                    \
-        }                                                                                               \
-        if ((D_) == 16) {                                                                               \
-            if ((W_) == 1) return CALL(16, 1, 0, 0);                                                    \
-            if ((W_) == 2) { if ((dA_) == 8) return CALL(16, 2, 8, 0); return CALL(16, 2, 0, 0); }      \
-            return CALL(16, 4, 0, 0);                                                                   \
-        }                                                                                               \
-        if ((W_) == 1) return CALL(32, 1, 0, 0);                                                        \
-        if ((W_) == 2) { if ((dA_) == 12) return CALL(32, 2, 12, 0); return CALL(32, 2, 0, 0); }        \
-        if ((dA_) == 15 && (dB_) == 6) return CALL(32, 4, 15, 6);                                       \
-        return CALL(32, 4, 0, 0);                                                                       \
+#define PVQ_WALK_DISPATCH(CALL, D_, W_, dX_, dA_, dB_)                                                       \
+    do {                                                                                                     \
+        if ((D_) == 8) {                                                                                     \
+            if ((W_) == 1) return CALL(8, 1, 0, 0, 0);                                                       \
+            return CALL(8, 2, 0, 0, 0);                                                                      \
+        }                                                                                                    \
+        if ((D_) == 16) {                                                                                    \
+            if ((W_) == 1) return CALL(16, 1, 0, 0, 0);                                                      \
+            if ((W_) == 2) { if ((dA_) == 8) return CALL(16, 2, 8, 8, 0); return CALL(16, 2, 0, 0, 0); }     \
+            return CALL(16, 4, 0, 0, 0);                                                                     \
+        }                                                                                                    \
+        if ((W_) == 1) return CALL(32, 1, 0, 0, 0);                                                          \
+        if ((W_) == 2) { if ((dA_) == 12) return CALL(32, 2, 12, 12, 0); return CALL(32, 2, 0, 0, 0); }      \
+        if ((dX_) == 28) return CALL(32, 4, 28, 15, 6);                                                      \
+        if ((dA_) == 15 && (dB_) == 6) return CALL(32, 4, 15, 15, 6);                                        \
+        return CALL(32, 4, 0, 0, 0);                                                                         \
     } while (0)

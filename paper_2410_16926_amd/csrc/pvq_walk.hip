@@ -2,23 +2,17 @@
 // that has no table-driven block decoder: groups of 16 and 32 (the paper's 3.25 bits/weight row is D = 16,
 // K = 33, 52-bit indices), and groups of 8 with multi-word indices.  One lane owns one group.
 //
-// With U(d,x) = N(d,0) + ... + N(d,x) (U(d,-1) = 0) and q = N(d,k) - 1 - r for the residual r in the
-// sub-pyramid still open, the coordinate's magnitude is m = k - C with C = #{x >= 0 : U(d-1,x) <= q/2}
-// (the points with magnitude below m number N(d,k) - 2 U(d-1,k-m); C <= k because q/2 < U(d-1,k)).
-// U(d-1, .) grows geometrically, so the position of q/2 among its values follows from the magnitude of
-// q/2: a guess table per row, indexed by the exponent and the leading fraction bits of q/2 as a float
-// (rounded down), gives g = #{x : U(d-1,x) <= lower edge of that bucket} <= C, and nearly always C is g or
-// g+1.  One read of the three entries U(d-1,g-1), U(d-1,g), U(d-1,g+1) settles it (a loop moves on in the
-// rare bucket that holds two thresholds) and holds everything the step needs:
-//     um = U(d-1,C-1), ux = U(d-1,C);  t = q - um;  the sign is negative iff t < ux;
-//     next q = negative ? t - um : t - ux;  next k = C
-// (for m = 0 the "negative" case applies and leaves q - 2 U(d-1,k-1), as it must).  App. B.3's search over
-// magnitudes, and a binary search over the row (six dependent probes at K = 33), become two LDS reads.
+// With q = N(D,K) - 1 - index first, a coordinate is the last threshold T_j of its row that is not above q, and q loses it
+// (pvq_internal.h).  The thresholds of a row grow geometrically, so q's place among them follows from its magnitude: a
+// guess row, indexed by the exponent and the leading fraction bits of q as a float, gives the last threshold below q's
+// whole bucket, and only the one behind it is left to compare.  A coordinate is one byte and two neighbouring thresholds
+// read from LDS, two subtractions, and the borrow of the second decides between them; App. B.3's search over magnitudes,
+// and a binary search over the row (six dependent probes at K = 33), become two LDS reads.
 //
 // Widths: the integers of a step with d dimensions left are below N(d,K), so the later coordinates run in
-// narrower arithmetic: dimensions above DA in W words, above DB in W/2 words, the rest in W/4 (for D = 16,
+// narrower arithmetic: dimensions above DX in W words, above DA in 3W/4, above DB in W/2, the rest in W/4 (for D = 16,
 // K = 33: 64 bits down to nine dimensions, 32 bits from eight on, N(8,33) < 2^32).  The last two coordinates
-// need no table: U(1,x) = 2x + 1, and P(1,k) = {+k, -k}.
+// need no table: the thresholds of row 1 are 0, 1, 2, 4, 6, ..., and P(1,k) = {+k, -k}.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -42,29 +36,59 @@ struct walk_launch {
 
 using namespace pvq_walk;
 
+typedef __attribute__((ext_vector_type(4))) short bf16x4;
+typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(16))) float f32x16;
+
+// the value of lane L of the lane's quad
+template <int L>
+__device__ inline float quad_lane(float v)
+{
+    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), L * 0x55, 0xF, 0xF, false));
+}
+
+// the sum over the lanes of the same place in their quads, in every lane: rotations by 4 and 8 inside the rows of 16, then
+// across the rows
+__device__ inline float sum_over_quads(float v)
+{
+    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x124, 0xF, 0xF, false));
+    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x128, 0xF, 0xF, false));
+    v += __shfl_xor(v, 16, kWave);
+    return v + __shfl_xor(v, 32, kWave);
+}
+
 // What a group needs from memory, as it comes: the W + 1 words its index may touch, its amplitude (the float, or the
-// word that holds its code) and, with codes, the row's normaliser.  Fetching does no arithmetic on loaded data and has
-// no load under a condition, so the loads stay in flight until the item is taken apart, one item later: a wait placed
+// word that holds its code).  Fetching does no arithmetic on loaded data and
+// has no load under a condition, so the loads stay in flight until the item is taken apart, one item later: a wait placed
 // right behind a load also waits for every store issued before it (memory operations complete in order).
 template <int W>
 struct raw_group {
     uint32_t w[W + 1];
     uint32_t amp;
-    float rownorm;
 };
 
-// row: the row's index words, last_word: index of the row's last word (words past the field's own are read
-// inside the row and dropped); srow: the row of the scale plane
+// A part of the index plane that a wave reads from, as a buffer: words behind the plane's end read as 0 (and are not part
+// of any field), so that a field's words need no bounds of their own.
+struct index_plane {
+    __amdgpu_buffer_rsrc_t words;
+    __device__ inline index_plane(const pvq_decode_args &a, int64_t row)
+    {
+        const int64_t bytes = (a.rows - row) * a.index_row_words * 4;
+        words = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(a.index) + row * a.index_row_words, 0,
+                                                  (int)(uint32_t)std::min<int64_t>(bytes, 0xFFFFFFFC), 0x00027000);
+    }
+};
+
+// from: byte of the row in the plane; srow: the row of the scale plane
 template <int W>
-__device__ inline void fetch_group(const uint32_t *__restrict__ row, uint32_t last_word, const void *__restrict__ srow,
-                                   const float *__restrict__ rownorm, int g, int index_bits, int scale_bits, raw_group<W> &r)
+__device__ inline void fetch_group(const index_plane &plane, uint32_t from, const void *__restrict__ scales, uint32_t scale_from,
+                                   int g, int index_bits, int scale_bits, raw_group<W> &r)
 {
-    const uint32_t w0 = __umul24((uint32_t)g, (uint32_t)index_bits) >> 5;     // (rows have at most 2^21 groups)
+    const uint32_t at = from + 4u * (__umul24((uint32_t)g, (uint32_t)index_bits) >> 5);     // (rows have at most 2^21 groups)
 #pragma unroll
-    for (int i = 0; i <= W; i++) r.w[i] = row[std::min(w0 + (uint32_t)i, last_word)];
+    for (int i = 0; i <= W; i++) r.w[i] = (uint32_t)__builtin_amdgcn_raw_buffer_load_b32(plane.words, (int)(at + 4u * i), 0, 0);
     const uint32_t aw = scale_bits == 0 ? (uint32_t)g : __umul24((uint32_t)g, (uint32_t)scale_bits) >> 5;
-    r.amp = reinterpret_cast<const uint32_t *>(srow)[aw];
-    r.rownorm = scale_bits == 0 ? 0.0f : *rownorm;
+    r.amp = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const unsigned char *>(scales) + (scale_from + 4u * aw));
 }
 
 template <int W>
@@ -72,26 +96,34 @@ __device__ inline typename wide<W>::type group_index(const raw_group<W> &r, int 
 {
     using T = typename wide<W>::type;
     const uint32_t sh = __umul24((uint32_t)g, (uint32_t)bits) & 31;
-    const int span = (int)sh + bits;
-    T v = (T)(r.w[0] >> sh);
+    uint32_t v[W];
 #pragma unroll
-    for (int i = 1; i <= W; i++) {
-        const int off = 32 * i - (int)sh;
-        if (32 * i < span && off < 32 * W) v |= (T)r.w[i] << off;
+    for (int i = 0; i < W; i++) {
+        const int left = bits - 32 * i;                            // (the same for all lanes)
+        const uint32_t mask = left >= 32 ? 0xFFFFFFFFu : left <= 0 ? 0u : (1u << left) - 1u;
+        v[i] = __builtin_amdgcn_alignbit(r.w[i + 1], r.w[i], sh) & mask;
     }
-    if (bits < 32 * W) v &= (((T)1) << bits) - 1;
-    return v;
+    T c = 0;
+#pragma unroll
+    for (int i = 0; i < W; i++) c |= (T)v[i] << (32 * i);
+    return c;
 }
 
+// the group's amplitude; with codes, relative to the square root of the row's normaliser
 template <int W>
 __device__ inline float group_amp(const raw_group<W> &r, int g, int scale_bits, const float *sqrtc)
 {
     if (scale_bits == 0) return __uint_as_float(r.amp);
-    const uint32_t pos = __umul24((uint32_t)g, (uint32_t)scale_bits);
-    const uint32_t code = (r.amp >> (pos & 31)) & ((1u << scale_bits) - 1u);
-    return sqrtc[code] * sqrtf(r.rownorm);
+    return sqrtc[__builtin_amdgcn_ubfe(r.amp, __umul24((uint32_t)g, (uint32_t)scale_bits) & 31u, (uint32_t)scale_bits)];
 }
 
+// 1 / sqrt(n2) within an ulp and a half of rounding (n2 >= 1): the hardware's approximation and one step of Newton's
+// iteration, six instructions, against twenty for a square root and a quotient.
+__device__ inline float reciprocal_norm(float n2)
+{
+    const float r = __builtin_amdgcn_rsqf(n2);
+    return fmaf(0.5f * r, fmaf(-(n2 * r), r, 1.0f), r);
+}
 
 __device__ inline uint32_t f32_to_bf16_rne(float f)
 {
@@ -103,12 +135,20 @@ __device__ inline uint32_t f32_to_bf16_rne(float f)
 
 __device__ inline uint16_t f32_to_f16_rne(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
 
-__device__ inline void tables_to_lds(unsigned char *lds, const walk_launch &wl, float *sqrtc)
+// The tables into LDS, behind the amplitude table: straight from memory, 1 KiB a wave and instruction, all of them on
+// their way at once (through registers, a thread that copies 16 bytes at a time waits for each of them: 60 KiB for groups
+// of 32 took 4 us of a small launch).
+__device__ inline void tables_to_lds(unsigned char *lds, const walk_launch &wl)
 {
-    for (uint32_t i = threadIdx.x * 16u; i < wl.p.bytes; i += blockDim.x * 16u)
-        *reinterpret_cast<uint4 *>(lds + i) = *reinterpret_cast<const uint4 *>(wl.blob + i);
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), lane = threadIdx.x % kWave;
+    for (uint32_t at = kWalkHead + 1024u * wave; at < wl.p.bytes; at += 1024u * (blockDim.x / kWave))
+        if (at + 16u * lane < wl.p.bytes)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(wl.blob + at + 16u * lane),
+                                             (__attribute__((address_space(3))) void *)(lds + at), 16, 0, 0);
+    float *sqrtc = reinterpret_cast<float *>(lds);
     if (wl.scale_bits > 0)
         for (int i = threadIdx.x; i < (1 << wl.scale_bits); i += blockDim.x) sqrtc[i] = wl.sqrtc[i];
+    __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
     __syncthreads();
 }
 
@@ -116,7 +156,7 @@ __device__ inline void tables_to_lds(unsigned char *lds, const walk_launch &wl, 
 // every wave works alone and takes (row, 64 consecutive groups) items in turn.  A lane's group is D consecutive
 // outputs, so the lanes of a wave would each store 16 bytes out of every D * size; with STAGE the wave lays
 // its 64 groups out in LDS instead and every store instruction writes 1 KiB of consecutive addresses.
-template <int D, int W, int DA, int DB, int OUT, bool STAGE>
+template <int D, int W, int DX, int DA, int DB, int OUT, bool STAGE>
 __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl, pvq_decode_args a, int tiles)
 {
     using T = typename wide<W>::type;
@@ -124,11 +164,11 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
     constexpr int NC = D * OSZ / 16;                 // 16-byte chunks of one group
     const int kWaves = (int)blockDim.x / kWave;
     extern __shared__ __align__(16) unsigned char lds[];
-    float *sqrtc = reinterpret_cast<float *>(lds + wl.p.bytes);
+    const float *sqrtc = reinterpret_cast<const float *>(lds);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    uint4 *stage = reinterpret_cast<uint4 *>(lds + wl.p.bytes + 256 * sizeof(float)) + wave * (kWave * NC);
-    tables_to_lds(lds, wl, sqrtc);
+    uint4 *stage = reinterpret_cast<uint4 *>(lds + wl.p.bytes) + wave * (kWave * NC);
+    tables_to_lds(lds, wl);
     const int G = (int)a.groups;
     const int64_t items = a.rows * tiles, stride = (int64_t)gridDim.x * kWaves;
     // What an item needs from memory is requested one item ahead, in front of the current item's stores: a
@@ -137,18 +177,17 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
     // past a row's last group, fetch a valid place again and drop it.
     raw_group<W> nx;
     int g_nx = 0;
-    const uint32_t last_word = (uint32_t)a.index_row_words - 1u;
     const int64_t srow_bytes = wl.scale_bits == 0 ? a.groups * 4 : a.scale_row_words * 4;
+    float norm_nx = 0.0f;
     // (row, tile) of an item without a division per item: a wave moves on by `stride` items at a time
     const int64_t step_rows = stride / tiles;
     const int step_tiles = (int)(stride - step_rows * tiles);
     auto fetch = [&](int64_t row, int tile) {
         const int g = tile * kWave + lane;
         g_nx = g < G ? g : 0;
-        fetch_group<W>(a.index + row * a.index_row_words, last_word,
-                       reinterpret_cast<const unsigned char *>(a.scale) + row * srow_bytes,
-                       wl.scale_bits == 0 ? nullptr : a.rownorm + row, g_nx,
-                       wl.index_bits, wl.scale_bits, nx);
+        fetch_group<W>(index_plane(a, row), 0u, reinterpret_cast<const unsigned char *>(a.scale) + row * srow_bytes, 0u,
+                       g_nx, wl.index_bits, wl.scale_bits, nx);
+        norm_nx = wl.scale_bits == 0 ? 1.0f : a.rownorm[row];
     };
     const int64_t first = (int64_t)blockIdx.x * kWaves + wave;
     int64_t row_n = first / tiles;                              // the item that is being fetched
@@ -163,18 +202,16 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
         const int g0 = tile_n * kWave;                          // the wave's first group
         const int g_mine = g_nx;                                // the lane's group: g0 + lane, or 0 past the row's end
         const T c = group_index<W>(nx, g_mine, wl.index_bits);
-        const float amp = group_amp<W>(nx, g_mine, wl.scale_bits, sqrtc);
+        const float amp = group_amp<W>(nx, g_mine, wl.scale_bits, sqrtc) * sqrtf(norm_nx);
         row_n += step_rows;
         tile_n += step_tiles;
         if (tile_n >= tiles) { tile_n -= tiles; row_n++; }
         if (row_n >= a.rows) { row_n = a.rows - 1; tile_n = tiles - 1; }   // past the last item: its place again, dropped
         fetch(row_n, tile_n);
         float y[D];
-        const int n2 = unrank_walk<D, W, DA, DB>(c, lds, wl.p, [&](int i, uint32_t m, bool negative) {
-            y[i] = negative ? -(float)m : (float)m;            // (a zero coordinate comes as -0)
-        });
+        const float n2 = unrank_walk<D, W, DX, DA, DB>(c, lds, wl.p, [&](int i, float minus_y) { y[i] = minus_y; });
         // direction on the unit sphere times the amplitude (Sec. 2.4): w = amp * y / ||y||_2
-        const float gain = amp / sqrtf((float)n2);
+        const float gain = -amp * reciprocal_norm(n2);
         // gain * y + 0: the product as it is, and +0 for a zero coordinate
         auto value = [&](int i) { return fmaf(gain, y[i], 0.0f); };
         const int valid = std::min(kWave, G - g0);             // groups of this item inside the row
@@ -218,76 +255,136 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
     }
 }
 
-// Decode fused into y = W_hat x for NB vectors.  A wave takes whole rows (lanes stride the groups; the next
-// group's index, amplitude and activations are requested before the current group is decoded) and adds its
-// 64 partial sums with a fixed xor butterfly.
-template <int D, int W, int DA, int DB, int NB>
-__global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0)
+// Decode fused into y = W_hat x for up to 16 vectors in one pass.  A wave's 64 groups are R rows x 64/R neighbouring group
+// columns (lane = row + R column), so that a lane's own pulses, exact in bfloat16, are its part of the A operand of a
+// matrix instruction that computes 64/R blocks at once, each block a group column of R rows with activations of its own:
+// 16 x 16 x 4 with four blocks (R = 16, 16 vectors) or 4 x 4 x 4 with sixteen (R = 4, four vectors, NV of them for 4 NV).
+// D/4 of these in a row give the dot products of whole groups, whose gains (one per row and block) are multiplied
+// afterwards: products exact in float32, as on the vector ALUs.  A workgroup takes R rows at a time, its waves take the
+// columns in turn, and their sums meet in LDS, so that a few rows fill the chip as well.
+// Bound by the instructions of the walk (about 13 to 27 a coordinate, by its width).  14336 x 4096, D = 16, K = 33, 4-bit
+// codes, 1 / 4 / 5 / 16 vectors: 36 / 36 / 39 / 43 us, where passes of 4, 2 and 1 vectors on the vector ALUs, a wave per
+// row, took 51 / 72 / 123 / 287; D = 32, K = 60, 1 / 16 vectors: 51 / 52 us; 84 x 11776, D = 32, 11 vectors: 19 us (412
+// before); 139 x 864, one vector: 8 us (17).
+template <int D, int W, int DX, int DA, int DB, int R, int NV>
+__global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles)
 {
+    static_assert(R == 16 ? NV == 4 : R == 4, "tiles");
     using T = typename wide<W>::type;
+    constexpr int CG = kWave / R;                  // group columns of a wave
+    constexpr int XV = R == 16 ? 1 : NV;           // vectors whose activations a lane holds
+    constexpr int XW = D / 8;                      // 16-byte words of one group's activations
+    constexpr int kSums = 4 * R * NV;              // of a tile: rows x vectors
     extern __shared__ __align__(16) unsigned char lds[];
-    float *sqrtc = reinterpret_cast<float *>(lds + wl.p.bytes);
-    tables_to_lds(lds, wl, sqrtc);
+    const float *sqrtc = reinterpret_cast<const float *>(lds);
+    const int lane = threadIdx.x % kWave;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), waves = (int)blockDim.x / kWave;
+    float *gains = reinterpret_cast<float *>(lds + wl.p.bytes) + wave * kWave;
+    float *sums = reinterpret_cast<float *>(lds + wl.p.bytes) + (R == 16 ? waves * kWave : 0);
     const int G = (int)a.groups;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-    const uint16_t *xb = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)b0 * a.ldx;
-    constexpr int XW = D / 8;                       // 16-byte words of one group's activations
-    const int kWaves = (int)blockDim.x / kWave;
-    for (int64_t row = (int64_t)blockIdx.x * kWaves + wave; row < a.rows; row += (int64_t)gridDim.x * kWaves) {
-        const uint32_t *irow = a.index + row * a.index_row_words;
-        const uint32_t last_word = (uint32_t)a.index_row_words - 1u;
-        const unsigned char *srow = reinterpret_cast<const unsigned char *>(a.scale) +
-                                    row * (wl.scale_bits == 0 ? a.groups * 4 : a.scale_row_words * 4);
-        float acc[NB];
+    const int chunks = (G + CG - 1) / CG;
+    const int row_l = lane % R, col_l = lane / R;
+    const uint32_t scale_row_words = (uint32_t)(wl.scale_bits == 0 ? a.groups : a.scale_row_words);
+    raw_group<W> nx;
+    int g_nx = 0;
+    // (rows and columns past the end fetch the last ones again; their gains are 0, their rows not written)
+    auto fetch = [&](int tile, int chunk) {
+        const int64_t row0 = (int64_t)tile * R;
+        const uint32_t row = (uint32_t)std::min<int64_t>(row_l, a.rows - 1 - row0);
+        g_nx = std::min(chunk * CG + col_l, G - 1);
+        fetch_group<W>(index_plane(a, row0), 4u * __umul24(row, (uint32_t)a.index_row_words), reinterpret_cast<const uint32_t *>(a.scale) + row0 * scale_row_words,
+                       4u * __umul24(row, scale_row_words), g_nx, wl.index_bits, wl.scale_bits, nx);
+    };
+    const uint16_t *x0[XV];
 #pragma unroll
-        for (int b = 0; b < NB; b++) acc[b] = 0.0f;
-        // what a group needs from memory; lanes past the row's end fetch group 0 again and drop it
-        raw_group<W> nx;
-        int g_nx = 0;
-        uint4 x_n[NB][XW];
-        auto fetch = [&](int g) {
-            const int gg = g < G ? g : 0;
-            g_nx = gg;
-            fetch_group<W>(irow, last_word, srow, wl.scale_bits == 0 ? nullptr : a.rownorm + row, gg, wl.index_bits, wl.scale_bits, nx);
+    for (int v = 0; v < XV; v++)
+        x0[v] = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)(b0 + std::min(4 * v + lane % (R == 16 ? 16 : 4), vectors - 1)) * a.ldx;
+    fetch((int)blockIdx.x, wave);                  // (there are no more waves than chunks)
+    tables_to_lds(lds, wl);
+    int turn = 0;
+    for (int tile = (int)blockIdx.x; tile < row_tiles; tile += (int)gridDim.x, turn++) {
+        f32x4 acc[XV];                             // R = 16: rows 4 (lane / 16) + r, vector lane % 16; else row r, vector 4 v + lane % 4, own block
 #pragma unroll
-            for (int b = 0; b < NB; b++)
-#pragma unroll
-                for (int w = 0; w < XW; w++)
-                    x_n[b][w] = *reinterpret_cast<const uint4 *>(xb + (int64_t)b * a.ldx + (int64_t)gg * D + 8 * w);
-        };
-        fetch(lane);
-        for (int g = lane; g < G; g += kWave) {
+        for (int v = 0; v < XV; v++) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int chunk = wave; chunk < chunks; chunk += waves) {
             const T c = group_index<W>(nx, g_nx, wl.index_bits);
-            const float amp = group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc);
-            uint4 x[NB][XW];
+            const float amp = chunk * CG + col_l < G ? group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc) : 0.0f;
+            uint4 x[XV][XW];
 #pragma unroll
-            for (int b = 0; b < NB; b++)
+            for (int v = 0; v < XV; v++)
 #pragma unroll
-                for (int w = 0; w < XW; w++) x[b][w] = x_n[b][w];
-            fetch(g + kWave);
-            float s[NB];
+                for (int w = 0; w < XW; w++) x[v][w] = *reinterpret_cast<const uint4 *>(x0[v] + ((int64_t)g_nx * D + 8 * w));
+            // the wave's next groups: of this tile, or of its next one
+            const bool here = chunk + waves < chunks;
+            fetch(here ? tile : std::min(tile + (int)gridDim.x, row_tiles - 1), here ? chunk + waves : wave);
+            f32x16 out16;
+            f32x4 out4[XV];
+            if constexpr (R == 16) {
 #pragma unroll
-            for (int b = 0; b < NB; b++) s[b] = 0.0f;
-            const int n2 = unrank_walk<D, W, DA, DB>(c, lds, wl.p, [&](int i, uint32_t m, bool negative) {
-                const float yv = negative ? -(float)m : (float)m;
+                for (int i = 0; i < 16; i++) out16[i] = 0.0f;
+            } else {
 #pragma unroll
-                for (int b = 0; b < NB; b++) {
-                    const uint4 q = x[b][i / 8];
-                    const uint32_t word = (i % 8) / 2 == 0 ? q.x : (i % 8) / 2 == 1 ? q.y : (i % 8) / 2 == 2 ? q.z : q.w;
-                    const float xv = (i & 1) ? __uint_as_float(word & 0xFFFF0000u) : __uint_as_float(word << 16);
-                    s[b] = fmaf(yv, xv, s[b]);
+                for (int v = 0; v < XV; v++) out4[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+            }
+            uint32_t pair[2];
+            float even = 0.0f;
+            const float n2 = unrank_walk<D, W, DX, DA, DB>(c, lds, wl.p, [&](int i, float minus_y) {
+                if ((i & 1) == 0) { even = minus_y; return; }
+                pair[(i >> 1) & 1] = __builtin_amdgcn_perm(__float_as_uint(minus_y), __float_as_uint(even), 0x07060302u);
+                if ((i & 3) != 3) return;
+                const bf16x4 y4 = __builtin_bit_cast(bf16x4, make_uint2(pair[0], pair[1]));
+#pragma unroll
+                for (int v = 0; v < XV; v++) {
+                    const uint4 q = x[v][i / 8];
+                    const bf16x4 x4 = __builtin_bit_cast(bf16x4, (i & 4) ? make_uint2(q.z, q.w) : make_uint2(q.x, q.y));
+                    if constexpr (R == 16) out16 = __builtin_amdgcn_mfma_f32_16x16x4bf16_1k(y4, x4, out16, 0, 0, 0);
+                    else out4[v] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(y4, x4, out4[v], 0, 0, 0);
                 }
             });
-            const float gain = amp / sqrtf((float)n2);
+            const float gain = -amp * reciprocal_norm(n2);         // (0 past the last column)
+            if constexpr (R == 16) {
+                gains[lane] = gain;                // (read by this wave only)
 #pragma unroll
-            for (int b = 0; b < NB; b++) acc[b] = fmaf(gain, s[b], acc[b]);
+                for (int blk = 0; blk < 4; blk++) {
+                    const f32x4 g4 = *reinterpret_cast<const f32x4 *>(gains + 16 * blk + 4 * (lane / 16));
+#pragma unroll
+                    for (int r = 0; r < 4; r++) acc[0][r] = fmaf(g4[r], out16[4 * blk + r], acc[0][r]);
+                }
+            } else {
+                const float g4[4] = {quad_lane<0>(gain), quad_lane<1>(gain), quad_lane<2>(gain), quad_lane<3>(gain)};
+#pragma unroll
+                for (int v = 0; v < XV; v++)
+#pragma unroll
+                    for (int r = 0; r < 4; r++) acc[v][r] = fmaf(g4[r], out4[v][r], acc[v][r]);
+            }
         }
+        const int64_t row0 = (int64_t)tile * R;
+        auto write = [&](const float *from, int t) {               // sum t of the tile, over the waves
+            const int vec = R == 16 ? (t >> 2) & 15 : t >> 2;
+            const int64_t row = row0 + (R == 16 ? 4 * (t >> 6) : 0) + (t & 3);
+            if (vec >= vectors || row >= a.rows) return;
+            const float norm = wl.scale_bits == 0 ? 1.0f : sqrtf(a.rownorm[row]);
+            float v = from[t];
+            for (int w = 1; w < waves; w++) v += from[w * kSums + t];
+            a.y[(int64_t)(b0 + vec) * a.ldy + row] = v * norm;
+        };
+        if constexpr (R == 4) {
+            // The sixteen blocks' sums, then the waves': two places in turn, so that the wave that writes this tile is done
+            // with its place when the others come to use it again, one barrier later.
+            float *to = sums + (turn & 1) * (waves * kSums);
 #pragma unroll
-        for (int b = 0; b < NB; b++) {
-            float v = acc[b];
+            for (int v = 0; v < XV; v++) {
 #pragma unroll
-            for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, kWave);
-            if (lane == 0) a.y[(int64_t)(b0 + b) * a.ldy + row] = v;
+                for (int r = 0; r < 4; r++) acc[v][r] = sum_over_quads(acc[v][r]);
+                if (lane < 4) *reinterpret_cast<f32x4 *>(to + wave * kSums + 16 * v + 4 * lane) = acc[v];
+            }
+            __syncthreads();
+            if (wave == turn % waves && lane < kSums) write(to, lane);
+        } else {
+            __syncthreads();                       // (the tile before has been read)
+            *reinterpret_cast<f32x4 *>(sums + wave * kSums + 4 * lane) = acc[0];
+            __syncthreads();
+            for (int t = (int)threadIdx.x; t < kSums; t += (int)blockDim.x) write(sums, t);
         }
     }
 }
@@ -314,14 +411,14 @@ walk_launch make_launch(const pvq_ctx *c)
     return wl;
 }
 
-// lanes of a workgroup for a context: small tables are copied by many small workgroups, large ones once per
-// sixteen waves
-int block_threads(const pvq_ctx *c) { return c->walk.bytes <= 16 * 1024 ? 256 : kMaxThreads; }
+// lanes of a workgroup for a context: small tables are copied by many small workgroups (eight to a unit's 160 KiB), large
+// ones once per sixteen waves
+int block_threads(const pvq_ctx *c) { return c->walk.bytes <= 20 * 1024 ? 256 : kMaxThreads; }
 
-// tables, amplitude table, and (decode with staging) 64 groups of outputs per wave
+// tables, and (decode with staging) 64 groups of outputs per wave
 size_t lds_bytes(const pvq_ctx *c, size_t group_out_bytes = 0)
 {
-    return (size_t)c->walk.bytes + 256 * sizeof(float) + (block_threads(c) / kWave) * kWave * group_out_bytes;
+    return (size_t)c->walk.bytes + (block_threads(c) / kWave) * kWave * group_out_bytes;
 }
 
 // kernels that need more LDS than a kernel gets without asking (64 KiB) say so once
@@ -339,59 +436,103 @@ unsigned persistent_grid(const pvq_ctx *c, int64_t items)
     return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + per_block - 1) / per_block, (int64_t)units() * 32 / per_block));
 }
 
-template <int D, int W, int DA, int DB, int OUT, bool STAGE>
+template <int D, int W, int DX, int DA, int DB, int OUT, bool STAGE>
 hipError_t launch_decode_staged(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
     const int tiles = (int)((a.groups + kWave - 1) / kWave);
     const size_t lds = lds_bytes(c, STAGE ? (size_t)D * (OUT == PVQ_F32 ? 4 : 2) : 0);
-    const hipError_t e = allow_lds(decode_walk_kernel<D, W, DA, DB, OUT, STAGE>, lds);
+    const hipError_t e = allow_lds(decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>, lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((decode_walk_kernel<D, W, DA, DB, OUT, STAGE>), dim3(persistent_grid(c, a.rows * tiles)), dim3(block_threads(c)), lds, s,
+    hipLaunchKernelGGL((decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>), dim3(persistent_grid(c, a.rows * tiles)), dim3(block_threads(c)), lds, s,
                        make_launch(c), a, tiles);
     return hipGetLastError();
 }
 
-template <int D, int W, int DA, int DB, int OUT>
+template <int D, int W, int DX, int DA, int DB, int OUT>
 hipError_t launch_decode_out(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
     // the staging buffer is used where the unit's 160 KiB still hold 32 waves with it
-    if (lds_bytes(c, (size_t)D * (OUT == PVQ_F32 ? 4 : 2)) * (2048 / block_threads(c)) <= 160 * 1024) return launch_decode_staged<D, W, DA, DB, OUT, true>(c, a, s);
-    return launch_decode_staged<D, W, DA, DB, OUT, false>(c, a, s);
+    if (lds_bytes(c, (size_t)D * (OUT == PVQ_F32 ? 4 : 2)) * (2048 / block_threads(c)) <= 160 * 1024) return launch_decode_staged<D, W, DX, DA, DB, OUT, true>(c, a, s);
+    return launch_decode_staged<D, W, DX, DA, DB, OUT, false>(c, a, s);
 }
 
-template <int D, int W, int DA, int DB>
+template <int D, int W, int DX, int DA, int DB>
 hipError_t launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
     switch (out_dtype) {
-    case PVQ_F32: return launch_decode_out<D, W, DA, DB, PVQ_F32>(c, a, s);
-    case PVQ_F16: return launch_decode_out<D, W, DA, DB, PVQ_F16>(c, a, s);
-    default: return launch_decode_out<D, W, DA, DB, PVQ_BF16>(c, a, s);
+    case PVQ_F32: return launch_decode_out<D, W, DX, DA, DB, PVQ_F32>(c, a, s);
+    case PVQ_F16: return launch_decode_out<D, W, DX, DA, DB, PVQ_F16>(c, a, s);
+    default: return launch_decode_out<D, W, DX, DA, DB, PVQ_BF16>(c, a, s);
     }
 }
 
-template <int D, int W, int DA, int DB>
+// How a pass is split: tiles of `rows` rows, `waves` waves per workgroup
+struct gemv_split {
+    int rows, waves;
+    unsigned grid;
+};
+
+// LDS of a pass: tables, a gain per lane, the waves' sums (rows x vectors; two places for tiles of four rows)
+size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
+{
+    return (size_t)c->walk.bytes + (size_t)waves * (R == 16 ? kWave + sums : 2 * sums) * sizeof(float);
+}
+
+// The split that should take least, from what a wave's 64 groups take (clocks, measured): alone, as a chain of table reads; of
+// a SIMD's issue slots, when several waves share it; of the unit's loads of activations, which a tile of four rows
+// repeats four times as often (11 bytes a clock); and what a tile takes besides.  It picks tiles of 16 rows for more than
+// four vectors on large matrices (D = 32, 14336 x 4096, 16 vectors: 52 us, with four rows 79), four rows while those would
+// leave units idle (1289 x 16384, 11 vectors: 38 us, with sixteen 50).
+gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors)
+{
+    gemv_split best = {0, 0, 0};
+    double least = 0;
+    const double chain = 280.0 * c->D, issue = 4.0 * (80.0 + c->D * (c->words == 1 ? 14.0 : c->words == 2 ? 17.0 : 25.0));
+    for (int R = 4; R <= 16; R += 12) {
+        if (R == 16 && vectors <= 4) continue;
+        const int nv = vectors <= 4 ? 1 : vectors <= 8 ? 2 : 4, sums = R == 16 ? 256 : 16 * nv;
+        const double loads = c->D * 128.0 / 11.0 * (R == 16 ? 1 : nv);
+        const int64_t tiles = (rows + R - 1) / R, chunks = (groups + kWave / R - 1) / (kWave / R);
+        const int64_t tiles_unit = (tiles + units() - 1) / units();
+        for (int waves = 16; waves >= 1; waves -= waves > 8 ? 4 : waves > 4 ? 2 : 1) {
+            const size_t lds = gemv_lds(c, waves, R, sums);
+            if (waves > chunks || lds > 160 * 1024) continue;
+            const int resident = R == 16 || nv < 4 ? (c->D < 32 ? 32 : nv == 2 && R == 4 ? 16 : 20) : c->D == 8 ? 24 : 16;   // waves of a unit
+            const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)(160 * 1024 / lds)), tiles_unit));
+            const double turns = (double)((tiles_unit + blocks - 1) / blocks), steps = (double)((chunks + waves - 1) / waves);
+            const double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
+                                         (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
+            if (best.rows == 0 || cost < least) {
+                least = cost;
+                best = {R, waves, (unsigned)std::min<int64_t>(tiles, (int64_t)units() * blocks)};
+            }
+        }
+    }
+    return best;
+}
+
+template <int D, int W, int DX, int DA, int DB, int R, int NV>
+hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, int vectors, const gemv_split &split, hipStream_t s)
+{
+    const size_t lds = gemv_lds(c, split.waves, R, 4 * R * NV);
+    const hipError_t e = allow_lds(gemv_walk_kernel<D, W, DX, DA, DB, R, NV>, lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((gemv_walk_kernel<D, W, DX, DA, DB, R, NV>), dim3(split.grid), dim3((unsigned)(split.waves * kWave)), lds, s,
+                       make_launch(c), a, b0, vectors, (int)((a.rows + R - 1) / R));
+    return hipGetLastError();
+}
+
+template <int D, int W, int DX, int DA, int DB>
 hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
-    const unsigned grid = persistent_grid(c, a.rows);
-    const dim3 block((unsigned)block_threads(c));
-    const walk_launch wl = make_launch(c);
-    const size_t lds = lds_bytes(c);
-    // the batch is cut into passes of 4, 2 and 1 activation vectors over the codes
-    int b0 = 0;
-    while (b0 < a.batch) {
-        const int left = a.batch - b0;
+    for (int b0 = 0; b0 < a.batch; b0 += 16) {
+        const int vectors = std::min(a.batch - b0, 16);
+        const gemv_split split = split_gemv(c, a.rows, a.groups, vectors);
         hipError_t e;
-        if (left >= 4) {
-            if ((e = allow_lds(gemv_walk_kernel<D, W, DA, DB, 4>, lds)) != hipSuccess) return e;
-            hipLaunchKernelGGL((gemv_walk_kernel<D, W, DA, DB, 4>), dim3(grid), block, lds, s, wl, a, b0); b0 += 4;
-        } else if (left >= 2) {
-            if ((e = allow_lds(gemv_walk_kernel<D, W, DA, DB, 2>, lds)) != hipSuccess) return e;
-            hipLaunchKernelGGL((gemv_walk_kernel<D, W, DA, DB, 2>), dim3(grid), block, lds, s, wl, a, b0); b0 += 2;
-        } else {
-            if ((e = allow_lds(gemv_walk_kernel<D, W, DA, DB, 1>, lds)) != hipSuccess) return e;
-            hipLaunchKernelGGL((gemv_walk_kernel<D, W, DA, DB, 1>), dim3(grid), block, lds, s, wl, a, b0); b0 += 1;
-        }
-        e = hipGetLastError();
+        if (split.rows == 16) e = launch_gemv_pass<D, W, DX, DA, DB, 16, 4>(c, a, b0, vectors, split, s);
+        else if (vectors <= 4) e = launch_gemv_pass<D, W, DX, DA, DB, 4, 1>(c, a, b0, vectors, split, s);
+        else if (vectors <= 8) e = launch_gemv_pass<D, W, DX, DA, DB, 4, 2>(c, a, b0, vectors, split, s);
+        else e = launch_gemv_pass<D, W, DX, DA, DB, 4, 4>(c, a, b0, vectors, split, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
@@ -407,14 +548,14 @@ bool pvq_walk_usable(const pvq_ctx *c)
 
 hipError_t pvq_walk_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
-#define PVQ_WALK_DECODE(D, W, DA, DB) launch_decode<D, W, DA, DB>(c, a, out_dtype, s)
-    PVQ_WALK_DISPATCH(PVQ_WALK_DECODE, c->D, c->words, c->walk.dA, c->walk.dB);
+#define PVQ_WALK_DECODE(D, W, DX, DA, DB) launch_decode<D, W, DX, DA, DB>(c, a, out_dtype, s)
+    PVQ_WALK_DISPATCH(PVQ_WALK_DECODE, c->D, c->words, c->walk.dX, c->walk.dA, c->walk.dB);
 #undef PVQ_WALK_DECODE
 }
 
 hipError_t pvq_walk_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
-#define PVQ_WALK_GEMV(D, W, DA, DB) launch_gemv<D, W, DA, DB>(c, a, s)
-    PVQ_WALK_DISPATCH(PVQ_WALK_GEMV, c->D, c->words, c->walk.dA, c->walk.dB);
+#define PVQ_WALK_GEMV(D, W, DX, DA, DB) launch_gemv<D, W, DX, DA, DB>(c, a, s)
+    PVQ_WALK_DISPATCH(PVQ_WALK_GEMV, c->D, c->words, c->walk.dX, c->walk.dA, c->walk.dB);
 #undef PVQ_WALK_GEMV
 }

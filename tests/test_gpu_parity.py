@@ -247,6 +247,15 @@ def test_long_groups_adversarial(D, K):
         run_long_groups(X, D, K, amplitude="ls")
 
 
+@pytest.mark.parametrize("D,K,bits", [(16, 33, 4), (32, 60, 0), (32, 50, 1), (8, 16, 2), (16, 58, 0), (32, 9, 8), (32, 68, 0)])
+@pytest.mark.parametrize("rows,groups", [(1, 2), (3, 15), (17, 65), (70, 17), (1030, 5)])
+def test_products_on_the_walk_at_the_edges_of_tiles(D, K, bits, rows, groups):
+    # tiles of 4 and 16 rows, 16 and 4 group columns, with remainders; 1 .. 4, 5 .. 8 and 9 .. 16 vectors; every width of
+    # the integers, with and without the search behind the guess
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=K + rows, rotate=False)
+    run_case(W, D, K, bits, batches=(1, 4, 5, 9, 16), out_dtypes=("f32",))
+
+
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
