@@ -558,160 +558,6 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
     }
 }
 
-// Sums of 16 per-lane values over the 64 lanes, all 16 at once: at each of the first four steps a lane
-// hands half of its values to the partner lane (lane ^ 1, 2, 4, 8) and adds the partner's other half
-// to the ones it keeps, so the work halves every step (8 + 4 + 2 + 1 additions instead of 16 per
-// step); two more steps add the four rows of 16 lanes.  Returns, in every lane, the total of vector
-// number  8*(lane&1) + 4*((lane>>1)&1) + 2*((lane>>2)&1) + ((lane>>3)&1).  Fixed order.
-__device__ inline float wave_sum16(const float (&a)[16], int lane)
-{
-    const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-    float n8[8], n4[4], n2[2];
-#pragma unroll
-    for (int c = 0; c < 8; c++) {
-        const float keep = b0 ? a[c + 8] : a[c], send = b0 ? a[c] : a[c + 8];
-        n8[c] = keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0xB1, 0xF, 0xF, false));
-    }
-#pragma unroll
-    for (int c = 0; c < 4; c++) {
-        const float keep = b1 ? n8[c + 4] : n8[c], send = b1 ? n8[c] : n8[c + 4];
-        n4[c] = keep + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, send), 0x4E, 0xF, 0xF, false));
-    }
-#pragma unroll
-    for (int c = 0; c < 2; c++) {
-        const float keep = b2 ? n4[c + 2] : n4[c], send = b2 ? n4[c] : n4[c + 2];
-        n2[c] = keep + __shfl_xor(send, 4, kWave);
-    }
-    const float keep = b3 ? n2[1] : n2[0], send = b3 ? n2[0] : n2[1];
-    float v = keep + __shfl_xor(send, 8, kWave);
-    v += __shfl_xor(v, 16, kWave);
-    v += __shfl_xor(v, 32, kWave);
-    return v;
-}
-
-// Sixteen activation vectors in one pass over the codes.  With four neighbouring groups per lane the
-// activations of 16 vectors would need 256 registers, so here a lane owns ONE group column (a wave
-// covers 64 consecutive groups of a row, 64 registers of activations) and keeps three ROWS in flight
-// instead (a fourth spills registers and measured slower): the table walks overlap as in the other kernels, and every decoded group is used for
-// 16 dot products.  Waves: nsl slices of 64 groups x rl row lanes.  Per row and vector the wave's
-// sum goes to LDS, where the slices' partial sums meet in slice order (deterministic).
-// AMP: 0 = float32 amplitudes, 1 = amplitude codes.
-constexpr int kWide = 16;            // vectors per pass
-constexpr int kWideRows = 3;         // rows a wave keeps in flight
-constexpr size_t kWidePartBytes = 64 * kWide * sizeof(float);   // (row, slice) pairs of a batch x vectors
-
-template <int AMP, bool B24>
-__global__ __launch_bounds__(kGemvThreads) void gemv8_wide_kernel(fast8_launch f, pvq_decode_args a, int b0,
-                                                                  int nvec, int nsl, int rl, int rows_per_block)
-{
-    constexpr bool CODES = AMP != 0;
-    constexpr int RI = kWideRows, NB = kWide;
-    __shared__ __align__(16) unsigned char lds[kLdsBytes];
-    float *sqrtc_l = reinterpret_cast<float *>(lds + f.p.tab_bytes);
-    float *part = sqrtc_l + 256;
-
-    const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
-    const int64_t r_end = std::min<int64_t>(a.rows, r_begin + rows_per_block);
-    const int64_t r_last = r_end - 1;
-    const int G = (int)a.groups;
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int slice = wave % nsl, rowlane = wave / nsl;
-    const int g = slice * kWave + lane;
-    const bool in_row = g < G;
-    const uint32_t gc = in_row ? (uint32_t)g : 0u;     // lanes beyond the row decode its first group against zeros
-    const int RB = RI * rl;
-    // the vector whose wave total wave_sum16 leaves in this lane
-    const int my_vector = 8 * (lane & 1) + 4 * ((lane >> 1) & 1) + 2 * ((lane >> 2) & 1) + ((lane >> 3) & 1);
-
-    // what a lane fetches per row: the dword that holds its index, and its amplitude (code word or float)
-    struct item { uint32_t w, s; };
-    auto fetch = [&](int64_t row, item &it) {
-        row = std::min<int64_t>(row, r_last);
-        const unsigned char *irow = reinterpret_cast<const unsigned char *>(a.index + row * a.index_row_words);
-        if constexpr (B24) {
-            // the 3 bytes of group g start at byte 3g; one dword load from byte 3g-1 (3g for g = 0)
-            // holds them and stays inside the row
-            uint32_t v;
-            __builtin_memcpy(&v, irow + 3u * gc - (gc > 0 ? 1u : 0u), 4);
-            it.w = v;
-        } else {
-            const uint32_t b = (uint32_t)f.index_bits;
-            const uint32_t pos = gc * b, w0 = pos >> 5, sh = pos & 31;
-            uint64_t v = reinterpret_cast<const uint32_t *>(irow)[w0];
-            if (sh + b > 32) v |= (uint64_t)reinterpret_cast<const uint32_t *>(irow)[w0 + 1] << 32;
-            it.w = (uint32_t)(v >> sh) & (uint32_t)((1ull << b) - 1ull);
-        }
-        if constexpr (CODES)
-            it.s = (reinterpret_cast<const uint32_t *>(a.scale) + row * a.scale_row_words)[(gc * (uint32_t)f.scale_bits) >> 5];
-        else
-            it.s = __float_as_uint(reinterpret_cast<const float *>(a.scale)[row * a.groups + gc]);
-    };
-
-    item cur[RI];
-    if (r_begin < r_end) {
-#pragma unroll
-        for (int i = 0; i < RI; i++) fetch(r_begin + i * rl + rowlane, cur[i]);
-    }
-    load_tables<false>(lds, f, sqrtc_l);
-    if (r_begin >= r_end) return;
-
-    uint32_t xr[NB][4];
-#pragma unroll
-    for (int b = 0; b < NB; b++) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (in_row && b < nvec)     // fewer than 16 vectors: the missing ones are zeros and are not written
-            v = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(a.x) + (int64_t)(b0 + b) * a.ldx + (int64_t)g * 8);
-        xr[b][0] = v.x; xr[b][1] = v.y; xr[b][2] = v.z; xr[b][3] = v.w;
-    }
-
-    for (int64_t batch = r_begin; batch < r_end; batch += RB) {
-        uint32_t c[RI], pr[RI][4], n2x4[RI];
-        float amp[RI];
-#pragma unroll
-        for (int i = 0; i < RI; i++) {
-            if constexpr (B24) c[i] = gc > 0 ? cur[i].w >> 8 : cur[i].w & 0xFFFFFFu;
-            else c[i] = cur[i].w;
-            if constexpr (CODES) {
-                const uint32_t code = (cur[i].s >> ((gc * (uint32_t)f.scale_bits) & 31u)) & ((1u << f.scale_bits) - 1u);
-                amp[i] = sqrtc_l[code];
-            } else {
-                amp[i] = __uint_as_float(cur[i].s);
-            }
-            // the registers of the consumed row take this wave's row of the next batch
-            fetch(batch + RB + i * rl + rowlane, cur[i]);
-        }
-        pvq_fast8_decode<RI, false>(lds, f.blob, f.p, c, pr, n2x4);
-#pragma unroll
-        for (int i = 0; i < RI; i++) {
-            const float gain = amp[i] * *reinterpret_cast<const float *>(lds + f.p.invs + n2x4[i]);
-            float acc[NB];
-#pragma unroll
-            for (int b = 0; b < NB; b++) {
-                float s = dot2_bf16(pr[i][0], xr[b][0], 0.0f);
-                s = dot2_bf16(pr[i][1], xr[b][1], s);
-                s = dot2_bf16(pr[i][2], xr[b][2], s);
-                s = dot2_bf16(pr[i][3], xr[b][3], s);
-                acc[b] = gain * s;
-            }
-            const float v = wave_sum16(acc, lane);
-            if (lane < NB) part[((i * rl + rowlane) * nsl + slice) * NB + my_vector] = v;
-        }
-        __syncthreads();
-        if ((int)threadIdx.x < RB * NB) {
-            const int rloc = threadIdx.x / NB, b = threadIdx.x % NB;
-            const int64_t row = batch + rloc;
-            if (row < r_end && b < nvec) {
-                float v = 0.0f;
-                for (int s = 0; s < nsl; s++) v += part[(rloc * nsl + s) * NB + b];
-                if constexpr (CODES) v *= sqrtf(a.rownorm[row]);
-                a.y[(int64_t)(b0 + b) * a.ldy + row] = v;
-            }
-        }
-        __syncthreads();   // `part` is rewritten by the next batch
-    }
-}
-
 // ---------------------------------------------------------------------------------------------
 // Many activation vectors: the dot products on the matrix cores
 // ---------------------------------------------------------------------------------------------
@@ -1109,14 +955,6 @@ bool pvq_fast8_decode_usable(const pvq_ctx *c, const pvq_decode_args &a)
     return c->fast8_blob != nullptr;
 }
 
-bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
-{
-    // a row must fit the waves of one workgroup: at most 16 slices of 256 groups
-    // lanes take whole quads of groups
-    return c->fast8_blob != nullptr && a.groups % kGroupsPerLane == 0 &&
-           (a.groups + kTileGroups - 1) / kTileGroups <= kGemvThreads / kWave;
-}
-
 hipError_t pvq_fast8_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
     const fast8_launch f = make_launch(c, false);
@@ -1187,26 +1025,6 @@ hipError_t launch_gemv_row(const pvq_ctx *c, const pvq_decode_args &a, int b0, h
 
 namespace {
 
-// one launch of the 16-vector kernel for vectors [b0, b0 + nvec), nvec <= 16
-hipError_t launch_gemv_wide(const pvq_ctx *c, const pvq_decode_args &a, int b0, int nvec, hipStream_t s)
-{
-    const fast8_launch f = make_launch(c, false);
-    const int nsl = (int)((a.groups + kWave - 1) / kWave);
-    const int rl = std::max(1, (kGemvThreads / kWave) / nsl);
-    const int RB = kWideRows * rl;
-    const int64_t batches = (a.rows + RB - 1) / RB;
-    const int64_t nblocks = std::max<int64_t>(1, std::min<int64_t>(g_num_cus > 0 ? g_num_cus : 256, batches));
-    const int rows_per_block = (int)(((batches + nblocks - 1) / nblocks) * RB);
-    const dim3 grid((unsigned)((a.rows + rows_per_block - 1) / rows_per_block)), block((unsigned)(kWave * nsl * rl));
-    const bool b24 = f.index_bits == 24, codes = f.scale_bits > 0;
-#define PVQ_WIDE_CASE(AMP, B24) \
-    hipLaunchKernelGGL((gemv8_wide_kernel<AMP, B24>), grid, block, 0, s, f, a, b0, nvec, nsl, rl, rows_per_block)
-    if (codes) { if (b24) PVQ_WIDE_CASE(1, true); else PVQ_WIDE_CASE(1, false); }
-    else { if (b24) PVQ_WIDE_CASE(0, true); else PVQ_WIDE_CASE(0, false); }
-#undef PVQ_WIDE_CASE
-    return hipGetLastError();
-}
-
 // one launch of the matrix-core kernel for vectors [b0, b0 + nvec), nvec <= 16
 hipError_t launch_gemv_mfma(const pvq_ctx *c, const pvq_decode_args &a, int b0, int nvec, hipStream_t s)
 {
@@ -1237,14 +1055,6 @@ bool mfma_usable(const pvq_ctx *c, const pvq_decode_args &a)
            (size_t)c->fast8.tab_bytes + 256 * sizeof(float) + kMfmaPartBytes <= (size_t)kLdsBytes;
 }
 
-// the 16-vector kernel takes rows of at most 16 slices of 64 groups whose tables, amplitude table and
-// partial sums fit LDS together
-bool wide_usable(const pvq_ctx *c, const pvq_decode_args &a)
-{
-    return (a.groups + kWave - 1) / kWave <= kGemvThreads / kWave &&
-           (size_t)c->fast8.tab_bytes + 256 * sizeof(float) + kWidePartBytes <= (size_t)kLdsBytes;
-}
-
 // the barrier-free kernel takes rows of whole slices of 256 groups, and pays off when every wave of every
 // unit gets a few rows
 bool row_usable(const pvq_ctx *c, const pvq_decode_args &a)
@@ -1255,6 +1065,24 @@ bool row_usable(const pvq_ctx *c, const pvq_decode_args &a)
 }
 
 }  // namespace
+
+// Which products the table decoder takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
+// vectors) has the others.
+//  - Rows must fit the waves of one workgroup, at most 16 slices of 256 groups, in whole quads.
+//  - The tables take 8 us of a launch (155 KB for every unit), the walk about 1.7 times as long per group.  Measured, table / walk:
+//    one vector 512 x 4096 10.3 / 6.2 us, 1024 x 8192 10.6 / 8.5, 2048 x 8192 11.1 / 14.9; 5 vectors 1024 x 8192
+//    17.5 / 9.1, 2048 x 8192 17.7 / 16.0; 16 vectors 1024 x 8192 20.5 / 14.1, 2048 x 8192 20.6 / 23.7.
+//  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (20128 x 10720, 3 / 5 / 16
+//    vectors: 179 / 204 / 469 against 114 / 120 / 120 us), or one of four, which takes as long as the walk.
+// Matrices of fewer than 4096 groups, less than a wave per SIMD has to do, keep the plan that they had.
+bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
+{
+    if (c->fast8_blob == nullptr || a.groups % kGroupsPerLane != 0 || (a.groups + kTileGroups - 1) / kTileGroups > kGemvThreads / kWave) return false;
+    const int64_t groups = a.rows * a.groups;
+    if (groups < 4096 && a.batch < 8) return true;
+    if (a.batch >= 3 && !mfma_usable(c, a)) return false;
+    return groups >= (a.batch == 1 ? 1 << 20 : 3 << 19);
+}
 
 // The passes that a product of a.batch vectors is made of, in order: which kernel takes how many vectors.
 int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pass *out)
@@ -1268,11 +1096,9 @@ int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pas
         // measured on the benchmark shape: 1 vector 78 us on the barrier-free kernel (84 us with row batches and
         // partial sums through LDS, which remains for short matrices and rows that are not whole slices),
         // 2 vectors 91 us and 4 vectors 111..125 us on the vector-ALU kernels; the matrix-core pass takes
-        // 105..117 us whatever the count, so it takes three vectors and more.  Where it cannot run, one
-        // 16-vector pass (about 215 us) beats two or more 4-vector passes from eight vectors on.
+        // 105..117 us whatever the count, so it takes three vectors and more.
         pvq_gemv_pass p;
         if (left >= 3 && mfma_usable(c, a)) p = {PVQ_PASS_MFMA, std::min(left, 16)};
-        else if (left >= 8 && wide_usable(c, a)) p = {PVQ_PASS_VALU16, std::min(left, kWide)};
         else if (left >= 4) p = {PVQ_PASS_VALU, 4};
         else if (left >= 2) p = {PVQ_PASS_VALU, 2};
         else if (ahead && row_usable(c, a)) p = {PVQ_PASS_VALU_ROWS, 1};
@@ -1294,7 +1120,6 @@ hipError_t pvq_fast8_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hip
         hipError_t e;
         switch (plan[i].kind) {
         case PVQ_PASS_MFMA: e = launch_gemv_mfma(c, a, b0, nvec, s); break;
-        case PVQ_PASS_VALU16: e = launch_gemv_wide(c, a, b0, nvec, s); break;
         case PVQ_PASS_VALU_ROWS: e = launch_gemv_row(c, a, b0, s); break;
         default:
             e = nvec == 4 ? launch_gemv_pass<4, false>(c, a, b0, s)
