@@ -796,7 +796,7 @@ struct wave_walk {
     static constexpr int kWindow = 1024 * kLoads;
     const decode_wide_params &p;
     const int lane;
-    unsigned char *ring;              // LDS: kAhead windows
+    const uint32_t ring;              // LDS address of kAhead windows
     uint32_t q;                       // lane x: word x
     int k, n2, i;
     int y[CP];                        // the lane's coordinates: CP * lane + j
@@ -806,23 +806,35 @@ struct wave_walk {
     uint32_t near_from, from[kAhead];
     int entry;
 
-    // thresholds b .. b + 63 of a row (a row has 64 at least)
+    // Thresholds b .. b + 63 of a row (a row has 64 at least) and their approximations, 16 bytes a lane and load.  The
+    // loads have no result in registers, and the compiler does not see that they write LDS: step waits for them by their
+    // number, where the compiler, which knows no windows, would wait for the ones just issued as well.  What is read from
+    // a window afterwards are ordinary loads, so that every register has the compiler's own wait before its first use.
     template <int u>
     __device__ __forceinline__ void fetch(int row, int b)
     {
         base[u] = b;
         const uint32_t at = (uint32_t)(row * p.row_len + b);
-        const unsigned char *t = reinterpret_cast<const unsigned char *>(p.tab_t) + (at * (uint32_t)(4 * W) + 16u * (uint32_t)lane);
-        const unsigned char *n = reinterpret_cast<const unsigned char *>(p.tab_near) + (at * 8u + 16u * (uint32_t)lane);
-        auto *to = (__attribute__((address_space(3))) void *)(ring + u * kWindow);
+        const uint32_t t = at * (uint32_t)(4 * W) + 16u * (uint32_t)lane, n = at * 8u + 16u * (uint32_t)lane;
+        const uint32_t to = ring + u * kWindow;
         // (the instruction's offset counts on both sides)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 0, 0);
-        if constexpr (W > 4) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 1024, 0);
-        if constexpr (W > 8) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 2048, 0);
-        if constexpr (W > 12) __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)t, to, 16, 3072, 0);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)n,
-                                         (__attribute__((address_space(3))) void *)(ring + u * kWindow + 1024 * (W / 4)), 16, 0, 0);
+#define PVQ_TO_LDS "s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+        if constexpr (W == 4)
+            asm volatile(PVQ_TO_LDS : : "s"(to), "v"(t), "s"(p.tab_t) : "memory", "m0");
+        else if constexpr (W == 8)
+            asm volatile(PVQ_TO_LDS "\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024" : : "s"(to), "v"(t), "s"(p.tab_t) : "memory", "m0");
+        else if constexpr (W == 12)
+            asm volatile(PVQ_TO_LDS "\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\tglobal_load_lds_dwordx4 %1, %2 offset:2048"
+                         : : "s"(to), "v"(t), "s"(p.tab_t) : "memory", "m0");
+        else
+            asm volatile(PVQ_TO_LDS "\n\tglobal_load_lds_dwordx4 %1, %2 offset:1024\n\tglobal_load_lds_dwordx4 %1, %2 offset:2048"
+                         "\n\tglobal_load_lds_dwordx4 %1, %2 offset:3072" : : "s"(to), "v"(t), "s"(p.tab_t) : "memory", "m0");
+        asm volatile(PVQ_TO_LDS : : "s"(to + 1024 * (W / 4)), "v"(n), "s"(p.tab_near) : "memory", "m0");
+#undef PVQ_TO_LDS
     }
+
+    template <typename T>
+    __device__ __forceinline__ static T from_lds(uint32_t at) { return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at); }
 
     // The coordinate's place in its row, all words compared, window by window from the one for the present k down (ends:
     // T_0 = 0): for windows that lie too high.
@@ -867,8 +879,8 @@ struct wave_walk {
     __device__ __forceinline__ void step()
     {
         // this window has arrived once only the loads of the two fetched behind it are on their way (in order)
-        double near;
-        asm volatile("s_waitcnt vmcnt(%2)\n\tds_read_b64 %0, %1" : "=v"(near) : "v"(near_from + u * kWindow), "n"((kAhead - 2) * kLoads) : "memory");
+        asm volatile("s_waitcnt vmcnt(%0)" : : "n"((kAhead - 2) * kLoads) : "memory");
+        const double near = from_lds<double>(near_from + u * kWindow);
         __builtin_amdgcn_sched_barrier(0);
         // q's approximation (pvq_wide_double), from its highest word that is not zero and the one below it (lane 63 holds
         // 0; for q = 0 the highest word is "lane 32", which holds 0)
@@ -877,13 +889,12 @@ struct wave_walk {
         const int at = 31 - lead;
         const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)q, at), lo = (uint32_t)__builtin_amdgcn_readlane((int)q, at - 1);
         const double nq = __builtin_amdgcn_ldexp(__builtin_fma((double)hi, 4294967296.0, (double)lo), 32 * at - 32);
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(near));
         uint64_t found = __ballot(near <= nq);
         asm("s_ff1_i32_b64 %0, %1" : "=s"(first) : "s"(found));    // (-1 for none: what is read then is not used)
-        uint32_t t;
-        asm volatile("v_mad_i32_i24 %0, %1, %2, %3\n\tds_read_b32 %0, %0" : "=&v"(t) : "s"(first), "v"(entry), "v"(from[u]) : "memory");
+        uint32_t t = from_lds<uint32_t>(from[u] + (uint32_t)__mul24(first, entry));
+        __builtin_amdgcn_sched_barrier(0);
         finish<(u + kAhead - 1) % kAhead>();
-        asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(t));
+        __builtin_amdgcn_sched_barrier(0);
         const uint32_t q0 = q;
         uint32_t borrows = subtract(q, t);
         if (__builtin_expect(((borrows & (1u << W)) | ((uint32_t)first & 0x80000000u)) != 0, 0)) {
@@ -891,8 +902,7 @@ struct wave_walk {
             while (found != 0 && (borrows >> W & 1u)) {
                 found &= found - 1;
                 first = found ? __builtin_ctzll(found) : 0;
-                asm volatile("v_mad_i32_i24 %0, %1, %2, %3\n\tds_read_b32 %0, %0\n\ts_waitcnt lgkmcnt(0)"
-                             : "=&v"(t) : "s"(first), "v"(entry), "v"(from[u]) : "memory");
+                t = from_lds<uint32_t>(from[u] + (uint32_t)__mul24(first, entry));
                 q = q0;
                 borrows = subtract(q, t);
             }
@@ -901,7 +911,6 @@ struct wave_walk {
                 q = q0;
                 j = __builtin_amdgcn_readfirstlane(search(trow, q, lane, k));
                 t = lane < W ? trow[(uint32_t)(j * W + lane)] : 0u;
-                __builtin_amdgcn_s_waitcnt(0x0F70);                // (before the paths meet: no wait behind them covers it)
                 subtract(q, t);
                 first = base[u] + 63 - j;
             }
@@ -922,11 +931,11 @@ __global__ __launch_bounds__(64 * kWavesFew) void decode_wide_wave_kernel(decode
     const int64_t gid = (int64_t)blockIdx.x * kWavesFew + wave;
     if (gid >= p.total_groups) return;
     const int64_t row = gid / p.groups, g = gid - row * p.groups;
-    walk_t walk{p, lane, lds_raw + wave * kRing};
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
+    walk_t walk{p, lane, lds0 + wave * kRing};
     walk.k = p.K; walk.n2 = 0; walk.i = 0; walk.j = 2 * p.K;       // (before the first coordinate: one of magnitude 0)
 #pragma unroll
     for (int j = 0; j < CP; j++) walk.y[j] = 0;
-    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_raw;
     walk.near_from = lds0 + wave * kRing + 1024 * (W / 4) + 8 * (63 - lane);
     walk.entry = lane < W ? -4 * W : 0;
 #pragma unroll

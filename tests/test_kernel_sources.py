@@ -1,0 +1,56 @@
+"""What the kernels' sources must hold to and no run shows: properties that hold or fail when the compiler allocates
+registers and LDS."""
+import glob
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_16926_amd", "csrc")
+SOURCES = sorted(os.path.basename(p) for pattern in ("*.hip", "*.h") for p in glob.glob(os.path.join(CSRC, pattern)))
+
+# a load whose result comes into registers (loads into LDS have none)
+LOAD = re.compile(r"\b(ds_(read|load|bpermute|permute|swizzle)\w*|(global|buffer|flat|scratch)_load_(?!lds)\w+|s_(buffer_)?load_\w+)")
+
+
+def asm_statements(text):
+    """The argument lists of the inline assembly statements of a source."""
+    for m in re.finditer(r"\basm\s*(?:volatile\s*)?\(", text):
+        depth, at, quoted = 1, m.end(), False
+        while depth:
+            c = text[at]
+            if c == "\\":
+                at += 1
+            elif c == '"':
+                quoted = not quoted
+            elif not quoted:
+                depth += (c == "(") - (c == ")")
+            at += 1
+        yield text[m.end():at - 1]
+
+
+def loads_without_a_wait(text):
+    """Statements in which a load into registers is not followed by a wait: their outputs would count as written while the
+    load is still under way, and the compiler may copy or spill them then."""
+    out = []
+    for statement in asm_statements(text):
+        statement = re.sub(r"\\[nt]", " ", statement)
+        last = None
+        for m in LOAD.finditer(statement):
+            last = m
+        if last and "s_waitcnt" not in statement[last.end():]:
+            out.append(statement)
+    return out
+
+
+@pytest.mark.parametrize("name", SOURCES)
+def test_inline_assembly_waits_for_what_it_loads(name):
+    with open(os.path.join(CSRC, name)) as f:
+        assert loads_without_a_wait(f.read()) == []
+
+
+def test_the_check_finds_a_load_that_is_not_waited_for():
+    late = 'asm volatile("s_waitcnt vmcnt(2)\\n\\tds_read_b64 %0, %1" : "=v"(near) : "v"(at)); asm("s_waitcnt lgkmcnt(0)" : "+v"(near));'
+    good = 'asm volatile("ds_read_b32 %0, %1\\n\\ts_waitcnt lgkmcnt(0)" : "=v"(t) : "v"(at)); asm("global_load_lds_dwordx4 %0, %1" : : "v"(a), "s"(b));'
+    assert len(loads_without_a_wait(late)) == 1
+    assert loads_without_a_wait(good) == []
