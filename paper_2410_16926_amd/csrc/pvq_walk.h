@@ -108,8 +108,8 @@ PVQ_HD uint32_t subtract(uint32_t *d, const uint32_t *a, const uint32_t *b)
     return borrow;
 }
 
-// One of a row's entries, or a guess, at a byte of the tables: LDS address in a kernel, where they start at 0 (an address
-// formed from the array's name would be an addition more).
+// One of a row's entries, or a guess, at a byte of the tables: LDS address in a kernel, where they start at 0 (the launch
+// checks it; an address formed from the array's name would be an addition more).
 template <typename T>
 PVQ_HD T table_at(const unsigned char *tables, uint32_t byte)
 {

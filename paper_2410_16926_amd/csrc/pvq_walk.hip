@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <utility>
 
 #include "pvq_internal.h"
@@ -421,12 +422,22 @@ size_t lds_bytes(const pvq_ctx *c, size_t group_out_bytes = 0)
     return (size_t)c->walk.bytes + (block_threads(c) / kWave) * kWave * group_out_bytes;
 }
 
-// kernels that need more LDS than a kernel gets without asking (64 KiB) say so once
-template <typename Kernel>
-hipError_t allow_lds(Kernel kernel, size_t bytes)
+// What a launch of a kernel with `bytes` of dynamic LDS needs first.  table_at counts on dynamic LDS starting at byte 0: a
+// kernel that has come to have static LDS as well (the compiler may move private arrays there) is refused; that is asked
+// once per kernel.  Kernels that need more LDS than a kernel gets without asking (64 KiB) say so.
+template <auto Kernel>
+hipError_t allow_lds(size_t bytes)
 {
+    static std::atomic<bool> checked{false};
+    if (!checked.load(std::memory_order_relaxed)) {
+        hipFuncAttributes attributes;
+        const hipError_t e = hipFuncGetAttributes(&attributes, reinterpret_cast<const void *>(Kernel));
+        if (e != hipSuccess) return e;
+        if (attributes.sharedSizeBytes != 0) return hipErrorInvalidDeviceFunction;
+        checked.store(true, std::memory_order_relaxed);
+    }
     if (bytes <= 64 * 1024) return hipSuccess;
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
 // workgroups of a launch over `items` wave items: 32 waves per unit, fewer if the work is small
@@ -441,7 +452,7 @@ hipError_t launch_decode_staged(const pvq_ctx *c, const pvq_decode_args &a, hipS
 {
     const int tiles = (int)((a.groups + kWave - 1) / kWave);
     const size_t lds = lds_bytes(c, STAGE ? (size_t)D * (OUT == PVQ_F32 ? 4 : 2) : 0);
-    const hipError_t e = allow_lds(decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>, lds);
+    const hipError_t e = allow_lds<decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>), dim3(persistent_grid(c, a.rows * tiles)), dim3(block_threads(c)), lds, s,
                        make_launch(c), a, tiles);
@@ -515,7 +526,7 @@ template <int D, int W, int DX, int DA, int DB, int R, int NV>
 hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, int vectors, const gemv_split &split, hipStream_t s)
 {
     const size_t lds = gemv_lds(c, split.waves, R, 4 * R * NV);
-    const hipError_t e = allow_lds(gemv_walk_kernel<D, W, DX, DA, DB, R, NV>, lds);
+    const hipError_t e = allow_lds<gemv_walk_kernel<D, W, DX, DA, DB, R, NV>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((gemv_walk_kernel<D, W, DX, DA, DB, R, NV>), dim3(split.grid), dim3((unsigned)(split.waves * kWave)), lds, s,
                        make_launch(c), a, b0, vectors, (int)((a.rows + R - 1) / R));

@@ -3,8 +3,11 @@ registers and LDS."""
 import glob
 import os
 import re
+import subprocess
 
 import pytest
+
+from paper_2410_16926_amd import build
 
 CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2410_16926_amd", "csrc")
 SOURCES = sorted(os.path.basename(p) for pattern in ("*.hip", "*.h") for p in glob.glob(os.path.join(CSRC, pattern)))
@@ -54,3 +57,19 @@ def test_the_check_finds_a_load_that_is_not_waited_for():
     good = 'asm volatile("ds_read_b32 %0, %1\\n\\ts_waitcnt lgkmcnt(0)" : "=v"(t) : "v"(at)); asm("global_load_lds_dwordx4 %0, %1" : : "v"(a), "s"(b));'
     assert len(loads_without_a_wait(late)) == 1
     assert loads_without_a_wait(good) == []
+
+
+def test_kernels_that_address_lds_from_zero_have_no_static_lds(tmp_path):
+    """The walk's tables are addressed from byte 0 of LDS on, where dynamic LDS starts in a kernel without static LDS."""
+    obj = os.path.join(os.path.dirname(CSRC), "_build", "pvq_walk.hip.o")
+    if not os.path.exists(obj):
+        build.build()
+    llvm = "/opt/rocm/llvm/bin"
+    bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
+    subprocess.run([f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", obj, str(tmp_path / "copy.o")], check=True)
+    subprocess.run([f"{llvm}/clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={bundle}",
+                    f"--output={code}", "--unbundle"], check=True)
+    notes = subprocess.run([f"{llvm}/llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    kernels = re.findall(r"\.group_segment_fixed_size:\s*(\d+).*?\.name:\s*(\S*(?:decode|gemv)_walk_kernel\S*)", notes, re.S)
+    assert len(kernels) > 50
+    assert [name for size, name in kernels if size != "0"] == []
