@@ -273,9 +273,10 @@ int pvq_rotate_encode(const pvq_ctx *ctx, const void *X, int dtype, int64_t rows
  *               ldw >= cols and ldw*sizeof(element) a multiple of 16.  Float32 arithmetic, one
  *               round-to-nearest-even conversion to the output type.  For D = 8 with 24-bit indices small
  *               matrices (fewer than about 1.5 M groups) and large ones run on different decoders, whose
- *               float32 gains amplitude / ||p||_2 can differ in the last place (a division by the square
- *               root, or a multiplication by its tabulated reciprocal): values are deterministic for a
- *               given shape and within the stated 1e-6 of the exact ones on either.
+ *               float32 gains amplitude / ||p||_2 can differ in the last place (the quotient, off by at most
+ *               1.5 * 2^-24 of itself, or a product with the tabulated reciprocal of the norm, off by at most
+ *               2 * 2^-24): values are deterministic for a given shape and within the stated 1e-6 of the
+ *               exact ones on either.
  * A stored index >= N(D,K) (corrupt data) decodes to unspecified values without any out-of-bounds
  * access.
  */

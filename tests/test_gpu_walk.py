@@ -34,3 +34,24 @@ def test_a_kernels_first_call_may_be_captured():
         assert gu.ulp_f16(oracle.to_f16(ref).view(np.uint16), out.cpu().numpy().view(np.uint16)) <= 1
         gu.assert_gemv_close(y.cpu().numpy(), xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref))
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K", [(8, 16), (8, 127), (16, 33), (32, 60)])
+def test_the_gain_is_no_further_off_than_a_rounded_root_and_quotient(D, K):
+    # gain = amplitude / ||y||, seen where the pulse is a power of two and the product with it exact.  It is rounded once
+    # (2^-24 of itself at most), and its correction carries half of the rounding of n2 * r (2^-24): 1.5 * 2^-24
+    W = si.gaussian_weights(256, 4096, 0.02, seed=si.BASE_SEED + 610 + K, rotate=False)
+    ctx = pvq.pvq_ctx_create(D, K)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W), want_pulses=True)
+    got = pvq.pvq_decode(ctx, packed, torch.float32).cpu().numpy().reshape(-1, D).astype(np.float64)
+    y = packed.pulses.cpu().numpy().reshape(-1, D).astype(np.float64)
+    gain = packed.scale.cpu().numpy().reshape(-1, 1).astype(np.float64) / np.sqrt((y * y).sum(axis=1, keepdims=True))
+    power = (y != 0) & (np.exp2(np.round(np.log2(np.maximum(np.abs(y), 1)))) == np.abs(y))
+    assert power.mean() > 0.02
+    err = np.abs(got / np.where(y == 0, 1, y) - gain)[power] / np.broadcast_to(gain, y.shape)[power]
+    assert err.max() <= 1.5 * 2.0 ** -24, err.max() * 2.0 ** 24
+    # an infinite amplitude: infinities, of the pulses' signs
+    packed.scale.fill_(float("inf"))
+    got = pvq.pvq_decode(ctx, packed, torch.float32).cpu().numpy().reshape(-1, D)
+    assert np.array_equal(got[y != 0], np.copysign(np.inf, y[y != 0]))
+    ctx.close()
