@@ -292,7 +292,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
     const uint32_t scale_row_words = (uint32_t)(wl.scale_bits == 0 ? a.groups : a.scale_row_words);
     raw_group<W> nx;
     int g_nx = 0;
-    // (rows and columns past the end fetch the last ones again; their gains are 0, their rows not written)
+    // (rows and columns past the end fetch the last ones again; such rows are not written, such columns' dot products left out)
     auto fetch = [&](int tile, int chunk) {
         const int64_t row0 = (int64_t)tile * R;
         const uint32_t row = (uint32_t)std::min<int64_t>(row_l, a.rows - 1 - row0);
@@ -313,7 +313,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
         for (int v = 0; v < XV; v++) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int chunk = wave; chunk < chunks; chunk += waves) {
             const T c = group_index<W>(nx, g_nx, wl.index_bits);
-            const float amp = chunk * CG + col_l < G ? group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc) : 0.0f;
+            const float amp = group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc);
             uint4 x[XV][XW];
 #pragma unroll
             for (int v = 0; v < XV; v++)
@@ -346,16 +346,24 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
                     else out4[v] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(y4, x4, out4[v], 0, 0, 0);
                 }
             });
-            const float gain = norm_gain(-amp, n2);         // (0 past the last column)
+            float gain = norm_gain(-amp, n2);
             if constexpr (R == 16) {
                 gains[lane] = gain;                // (read by this wave only)
 #pragma unroll
                 for (int blk = 0; blk < 4; blk++) {
+                    if (chunk * CG + blk >= G) break;
                     const f32x4 g4 = *reinterpret_cast<const f32x4 *>(gains + 16 * blk + 4 * (lane / 16));
 #pragma unroll
                     for (int r = 0; r < 4; r++) acc[0][r] = fmaf(g4[r], out16[4 * blk + r], acc[0][r]);
                 }
             } else {
+                if ((chunk + 1) * CG > G) {        // (both 0: the gain and the dot products of the last group may be infinite)
+                    gain = chunk * CG + col_l < G ? gain : 0.0f;
+#pragma unroll
+                    for (int v = 0; v < XV; v++)
+#pragma unroll
+                        for (int r = 0; r < 4; r++) out4[v][r] = chunk * CG + col_l < G ? out4[v][r] : 0.0f;
+                }
                 const float g4[4] = {quad_lane<0>(gain), quad_lane<1>(gain), quad_lane<2>(gain), quad_lane<3>(gain)};
 #pragma unroll
                 for (int v = 0; v < XV; v++)

@@ -55,3 +55,33 @@ def test_the_gain_is_no_further_off_than_a_rounded_root_and_quotient(D, K):
     got = pvq.pvq_decode(ctx, packed, torch.float32).cpu().numpy().reshape(-1, D)
     assert np.array_equal(got[y != 0], np.copysign(np.inf, y[y != 0]))
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K,bits", [(8, 16, 2), (16, 33, 0), (32, 60, 4)])
+@pytest.mark.parametrize("rows,groups,batch", [(5, 17, 1), (33, 19, 7), (21, 5, 16), (1030, 5, 5), (1030, 6, 16)])
+def test_infinities_in_a_rows_last_group(D, K, bits, rows, groups, batch):
+    # group counts that fill neither 16 nor 4 columns, so that the columns past the row's end hold the last group again: an
+    # infinite activation there gives what float64 gives, infinities where the pulse is not 0 and no number where it is; and
+    # large ones, whose dot products overflow (the group's pulses have one sign), give infinities
+    cols = D * groups
+    W = si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 620 + rows, rotate=False)
+    W[:, -D:] = np.abs(W[:, -D:])
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, D, K, bits, oe), oc)
+    xf, _ = si.activations(batch, cols, seed=rows + batch)
+    for value in (np.inf, -np.inf):
+        xf[:, -3] = value
+        y = pvq.pvq_decode_gemv(ctx, packed, gu.to_dev_bf16(si.f32_to_bf16_bits(xf.astype(np.float32)))).cpu().numpy()
+        with np.errstate(invalid="ignore"):
+            want = np.where(ref[:, -3] == 0, np.nan, value * ref[:, -3])
+        assert np.array_equal(y, np.broadcast_to(want.astype(np.float32), y.shape), equal_nan=True)
+    xf[:, -D:] = 3e38
+    y = pvq.pvq_decode_gemv(ctx, packed, gu.to_dev_bf16(si.f32_to_bf16_bits(xf.astype(np.float32)))).cpu().numpy()
+    assert np.all(y == np.inf)
+    if bits == 0:
+        xf[:, -D:] = 1.0
+        packed.scale[:, -1] = np.inf
+        y = pvq.pvq_decode_gemv(ctx, packed, gu.to_dev_bf16(si.f32_to_bf16_bits(xf.astype(np.float32)))).cpu().numpy()
+        assert np.all(y == np.inf)
+    ctx.close()
