@@ -45,7 +45,7 @@ def lib():
     if _lib is None:
         path = _build.LIB_PATH
         if not os.path.exists(path):
-            _build.build()
+            _build.build(binding=False)
         # PyTorch ships its own HIP runtime; load it first so that the process holds one runtime
         # and the library's streams and pointers are the ones torch hands out.
         import torch  # noqa: F401
@@ -85,12 +85,13 @@ _native_module = None
 
 
 def _native():
-    """The native half of the calls on tensors (built with the library; an error if it is missing)."""
+    """The native half of the calls on tensors.  Built only if there is none for this Python and the installed torch; a
+    broken one is an error."""
     global _native_module
     if _native_module is None:
         lib()
-        if not os.path.exists(_build.TORCH_PATH):
-            _build.build()
+        if not _build.binding_fits():
+            _build.build(library=False, binding=True)
         from . import _pvq_torch
         _native_module = _pvq_torch
     return _native_module

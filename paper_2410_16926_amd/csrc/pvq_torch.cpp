@@ -260,4 +260,7 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_pvq_torch", "libpvq's calls on to
 
 }  // namespace
 
+// What the module was built for, for build.py, which looks for this text in the file before the module is loaded.
+extern "C" __attribute__((used, visibility("default"))) const char pvq_torch_built_for[] = PVQ_BUILT_FOR;
+
 PyMODINIT_FUNC PyInit__pvq_torch(void) { return PyModule_Create(&module); }
