@@ -23,7 +23,7 @@ EXPORTS = [
 
 # host-only diagnostics declared in csrc/pvq_diagnostics.h, exported for the tests
 DIAGNOSTICS = ["pvq_fast_tables_selftest", "pvq_walk_tables_selftest", "pvq_decode_gemv_plan", "pvq_correct_set_front_tiles",
-               "pvq_decode_set_table_decoder_min_groups"]
+               "pvq_decode_set_table_decoder_min_groups", "pvq_decode_gemv_on"]
 
 
 class PvqError(RuntimeError):
@@ -77,6 +77,7 @@ def lib():
         L.pvq_correct_static.argtypes = [vp, vp, i64, i64, i64, vp, i64, vp]
         L.pvq_decode.argtypes = [vp, vp, vp, vp, i64, i64, vp, i32, i64, vp]
         L.pvq_decode_gemv.argtypes = [vp, vp, vp, vp, i64, i64, vp, i32, i64, vp, i64, vp]
+        L.pvq_decode_gemv_on.argtypes = [vp, vp, vp, vp, i64, i64, vp, i32, i64, vp, i64, vp, i32, i32]
         _lib = L
     return _lib
 
@@ -368,3 +369,19 @@ def pvq_decode_gemv(ctx: PvqContext, packed: Packed, x, out=None):
     """x: bfloat16 [batch][cols] device tensor; returns float32 [batch][rows]."""
     return _result((_native_module or _native()).decode_gemv(ctx._h.value, packed.index, packed.scale, packed.rownorm,
                                                              packed.rows, packed.cols, x, out), "pvq_decode_gemv")
+
+
+def pvq_decode_gemv_on(ctx: PvqContext, packed: Packed, x, decoder: str, tile_rows: int = 0, out=None):
+    """Diagnostics: pvq_decode_gemv on the decoder named ("table" or "walk", the latter with tiles of 4 or 16 rows, 0 = as
+    its rule has it) instead of the one that the rule picks."""
+    import torch
+    batch = x.shape[0]
+    assert x.dtype == torch.bfloat16 and x.shape[1] == packed.cols
+    if out is None:
+        out = torch.empty((batch, packed.rows), dtype=torch.float32, device=x.device)
+    ldx = x.stride(0) if batch > 1 else max(packed.cols, 1)
+    ldy = out.stride(0) if batch > 1 else max(packed.rows, 1)
+    _check(lib().pvq_decode_gemv_on(ctx.handle, _ptr(packed.index), _ptr(packed.scale), _ptr(packed.rownorm), packed.rows,
+                                    packed.cols, _ptr(x), batch, ldx, _ptr(out), ldy, _stream_ptr(),
+                                    {"table": 1, "walk": 2}[decoder], tile_rows), "pvq_decode_gemv_on")
+    return out

@@ -1066,18 +1066,24 @@ bool row_usable(const pvq_ctx *c, const pvq_decode_args &a)
 
 }  // namespace
 
-// Which products the table decoder takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
+// Which products the table decoder can take: rows must fit the waves of one workgroup, at most 16 slices of 256 groups, in
+// whole quads.
+bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
+{
+    return c->fast8_blob != nullptr && a.groups % kGroupsPerLane == 0 && (a.groups + kTileGroups - 1) / kTileGroups <= kGemvThreads / kWave;
+}
+
+// Which of them it takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
 // vectors) has the others.
-//  - Rows must fit the waves of one workgroup, at most 16 slices of 256 groups, in whole quads.
 //  - The tables take 8 us of a launch (155 KB for every unit), the walk about 1.7 times as long per group.  Measured, table / walk:
 //    one vector 512 x 4096 10.3 / 6.2 us, 1024 x 8192 10.6 / 8.5, 2048 x 8192 11.1 / 14.9; 5 vectors 1024 x 8192
 //    17.5 / 9.1, 2048 x 8192 17.7 / 16.0; 16 vectors 1024 x 8192 20.5 / 14.1, 2048 x 8192 20.6 / 23.7.
 //  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (20128 x 10720, 3 / 5 / 16
 //    vectors: 179 / 204 / 469 against 114 / 120 / 120 us), or one of four, which takes as long as the walk.
 // Matrices of fewer than 4096 groups, less than a wave per SIMD has to do, keep the plan that they had.
-bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
+bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
 {
-    if (c->fast8_blob == nullptr || a.groups % kGroupsPerLane != 0 || (a.groups + kTileGroups - 1) / kTileGroups > kGemvThreads / kWave) return false;
+    if (!pvq_fast8_gemv_usable(c, a)) return false;
     const int64_t groups = a.rows * a.groups;
     if (groups < 4096 && a.batch < 8) return true;
     if (a.batch >= 3 && !mfma_usable(c, a)) return false;

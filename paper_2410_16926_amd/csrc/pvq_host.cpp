@@ -734,9 +734,9 @@ extern "C" int pvq_decode(const pvq_ctx *c, const uint32_t *index, const void *s
     return e == hipSuccess ? PVQ_OK : hip_fail(e);
 }
 
-extern "C" int pvq_decode_gemv(const pvq_ctx *c, const uint32_t *index, const void *scale,
-                               const float *rownorm, int64_t rows, int64_t cols, const void *x,
-                               int batch, int64_t ldx, float *y, int64_t ldy, void *stream)
+static int decode_gemv(const pvq_ctx *c, const uint32_t *index, const void *scale, const float *rownorm, int64_t rows,
+                       int64_t cols, const void *x, int batch, int64_t ldx, float *y, int64_t ldy, void *stream, int decoder,
+                       int tile_rows)
 {
     int rc = check_shape(c, rows, cols);
     if (rc) return rc;
@@ -758,9 +758,27 @@ extern "C" int pvq_decode_gemv(const pvq_ctx *c, const uint32_t *index, const vo
     if ((rc = fill_decode_args(c, a, index, scale, rownorm, rows, cols))) return rc;
     if ((rc = check_device(c))) return rc;
     a.x = x; a.batch = batch; a.ldx = ldx; a.y = y; a.ldy = ldy;
-    hipError_t e = pvq_fast8_gemv_usable(c, a) ? pvq_fast8_launch_gemv(c, a, (hipStream_t)stream)
-                                               : pvq_walk_launch_gemv(c, a, (hipStream_t)stream);
+    if (decoder == PVQ_PRODUCT_TABLE && !pvq_fast8_gemv_usable(c, a)) return PVQ_E_UNSUPPORTED;
+    const bool table = decoder == PVQ_PRODUCT_TABLE || (decoder == PVQ_PRODUCT_BY_RULE && pvq_fast8_gemv_pays(c, a));
+    hipError_t e = table ? pvq_fast8_launch_gemv(c, a, (hipStream_t)stream)
+                         : pvq_walk_launch_gemv(c, a, tile_rows, (hipStream_t)stream);
     return e == hipSuccess ? PVQ_OK : hip_fail(e);
+}
+
+extern "C" int pvq_decode_gemv(const pvq_ctx *c, const uint32_t *index, const void *scale,
+                               const float *rownorm, int64_t rows, int64_t cols, const void *x,
+                               int batch, int64_t ldx, float *y, int64_t ldy, void *stream)
+{
+    return decode_gemv(c, index, scale, rownorm, rows, cols, x, batch, ldx, y, ldy, stream, PVQ_PRODUCT_BY_RULE, 0);
+}
+
+extern "C" int pvq_decode_gemv_on(const pvq_ctx *c, const uint32_t *index, const void *scale, const float *rownorm, int64_t rows,
+                                  int64_t cols, const void *x, int batch, int64_t ldx, float *y, int64_t ldy, void *stream,
+                                  int decoder, int tile_rows)
+{
+    if (decoder != PVQ_PRODUCT_TABLE && decoder != PVQ_PRODUCT_WALK) return PVQ_E_INVALID_ARG;
+    if (tile_rows != 0 && (decoder != PVQ_PRODUCT_WALK || (tile_rows != 4 && tile_rows != 16))) return PVQ_E_INVALID_ARG;
+    return decode_gemv(c, index, scale, rownorm, rows, cols, x, batch, ldx, y, ldy, stream, decoder, tile_rows);
 }
 
 extern "C" int pvq_decode_gemv_plan(const pvq_ctx *c, int64_t rows, int64_t cols, int batch, int *kinds, int *nvecs,
@@ -776,7 +794,7 @@ extern "C" int pvq_decode_gemv_plan(const pvq_ctx *c, int64_t rows, int64_t cols
     pvq_gemv_pass plan[16];
     int n = 1;
     plan[0] = {PVQ_PASS_GENERIC, batch};
-    if (pvq_fast8_gemv_usable(c, a)) n = pvq_fast8_plan_gemv(c, a, plan);
+    if (pvq_fast8_gemv_pays(c, a)) n = pvq_fast8_plan_gemv(c, a, plan);
     if (n > max_passes) return PVQ_E_INVALID_ARG;
     for (int i = 0; i < n; i++) { kinds[i] = plan[i].kind; nvecs[i] = plan[i].nvec; }
     *passes = n;

@@ -182,7 +182,8 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *ctx, const pvq_encode_ar
 // coordinate-by-coordinate decoder with one table probe per coordinate (pvq_walk.hip)
 bool pvq_walk_usable(const pvq_ctx *ctx);
 hipError_t pvq_walk_launch_decode(const pvq_ctx *ctx, const pvq_decode_args &a, int out_dtype, hipStream_t s);
-hipError_t pvq_walk_launch_gemv(const pvq_ctx *ctx, const pvq_decode_args &a, hipStream_t s);
+// tile_rows: 4 or 16 rows a tile, or 0 for the split that should take least
+hipError_t pvq_walk_launch_gemv(const pvq_ctx *ctx, const pvq_decode_args &a, int tile_rows, hipStream_t s);
 
 // D = 8 / 24-bit encoder (pvq_encode8.hip)
 bool pvq_encode8_usable(const pvq_ctx *ctx, const pvq_encode_args &a);
@@ -192,9 +193,10 @@ bool pvq_rotate_encode8_usable(const pvq_ctx *ctx, const pvq_encode_args &a, int
 hipError_t pvq_rotate_encode8_launch(const pvq_ctx *ctx, const pvq_encode_args &a, int dtype, int block,
                                      const uint8_t *signs, hipStream_t s);
 
-// D = 8 table-driven kernels (pvq_fast8.hip).  `*_usable` says whether the shape qualifies.
+// D = 8 table-driven kernels (pvq_fast8.hip).  `*_usable` says whether the shape qualifies, `*_pays` whether it is theirs.
 bool pvq_fast8_decode_usable(const pvq_ctx *ctx, const pvq_decode_args &a);
 bool pvq_fast8_gemv_usable(const pvq_ctx *ctx, const pvq_decode_args &a);
+bool pvq_fast8_gemv_pays(const pvq_ctx *ctx, const pvq_decode_args &a);
 hipError_t pvq_fast8_launch_decode(const pvq_ctx *ctx, const pvq_decode_args &a, int out_dtype, hipStream_t s);
 hipError_t pvq_fast8_launch_gemv(const pvq_ctx *ctx, const pvq_decode_args &a, hipStream_t s);
 // The passes of a fused product: which kind of kernel takes how many vectors (a batch of up to 16 vectors

@@ -506,13 +506,14 @@ size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
 // repeats four times as often (11 bytes a clock); and what a tile takes besides.  It picks tiles of 16 rows for more than
 // four vectors on large matrices (D = 32, 14336 x 4096, 16 vectors: 52 us, with four rows 79), four rows while those would
 // leave units idle (1289 x 16384, 11 vectors: 38 us, with sixteen 50).
-gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors)
+// tile_rows: only tiles of so many rows are looked at (0: both).
+gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows)
 {
     gemv_split best = {0, 0, 0};
     double least = 0;
     const double chain = 280.0 * c->D, issue = 4.0 * (80.0 + c->D * (c->words == 1 ? 14.0 : c->words == 2 ? 17.0 : 25.0));
     for (int R = 4; R <= 16; R += 12) {
-        if (R == 16 && vectors <= 4) continue;
+        if (tile_rows ? R != tile_rows : R == 16 && vectors <= 4) continue;
         const int nv = vectors <= 4 ? 1 : vectors <= 8 ? 2 : 4, sums = R == 16 ? 256 : 16 * nv;
         const double loads = c->D * 128.0 / 11.0 * (R == 16 ? 1 : nv);
         const int64_t tiles = (rows + R - 1) / R, chunks = (groups + kWave / R - 1) / (kWave / R);
@@ -546,11 +547,12 @@ hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, 
 }
 
 template <int D, int W, int DX, int DA, int DB>
-hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
+hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, int tile_rows, hipStream_t s)
 {
     for (int b0 = 0; b0 < a.batch; b0 += 16) {
         const int vectors = std::min(a.batch - b0, 16);
-        const gemv_split split = split_gemv(c, a.rows, a.groups, vectors);
+        const gemv_split split = split_gemv(c, a.rows, a.groups, vectors, tile_rows);
+        if (split.rows == 0) return hipErrorInvalidValue;          // (no LDS left beside the tables: only where tile_rows asks for 16)
         hipError_t e;
         if (split.rows == 16) e = launch_gemv_pass<D, W, DX, DA, DB, 16, 4>(c, a, b0, vectors, split, s);
         else if (vectors <= 4) e = launch_gemv_pass<D, W, DX, DA, DB, 4, 1>(c, a, b0, vectors, split, s);
@@ -576,9 +578,9 @@ hipError_t pvq_walk_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
 #undef PVQ_WALK_DECODE
 }
 
-hipError_t pvq_walk_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
+hipError_t pvq_walk_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, int tile_rows, hipStream_t s)
 {
-#define PVQ_WALK_GEMV(D, W, DX, DA, DB) launch_gemv<D, W, DX, DA, DB>(c, a, s)
+#define PVQ_WALK_GEMV(D, W, DX, DA, DB) launch_gemv<D, W, DX, DA, DB>(c, a, tile_rows, s)
     PVQ_WALK_DISPATCH(PVQ_WALK_GEMV, c->D, c->words, c->walk.dX, c->walk.dA, c->walk.dB);
 #undef PVQ_WALK_GEMV
 }

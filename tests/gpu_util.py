@@ -86,6 +86,19 @@ def decoder_setting(min_groups):
         pvq.pvq_decode_set_table_decoder_min_groups(old)
 
 
+def products(ctx, packed, x):
+    """(name, result) of the product by the library's own choice of kernel and on every kernel that can take it: the table
+    decoder (groups of 8), the walk with tiles of 4 and of 16 rows."""
+    yield "by rule", pvq.pvq_decode_gemv(ctx, packed, x).cpu().numpy()
+    if ctx.D == 8:
+        try:
+            yield "table", pvq.pvq_decode_gemv_on(ctx, packed, x, "table").cpu().numpy()
+        except pvq.PvqError as e:
+            assert e.status == -2
+    for tile_rows in (4, 16):
+        yield f"walk {tile_rows}", pvq.pvq_decode_gemv_on(ctx, packed, x, "walk", tile_rows).cpu().numpy()
+
+
 def assert_decode_close(got_f32: np.ndarray, ref64: np.ndarray, rel=1e-6):
     """float32 output against the float64 oracle: relative 1e-6, zeros exactly zero."""
     got = got_f32.astype(np.float64)

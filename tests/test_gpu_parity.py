@@ -15,7 +15,9 @@ torch = pytest.importorskip("torch")
 
 
 def run_case(W32, D, K, scale_bits, src_bits=None, batches=(1, 4), out_dtypes=("f32", "f16", "bf16"), seed=1,
-             amplitude="l2"):
+             amplitude="l2", matrix_cores=False):
+    """matrix_cores: the products' table decoder must be there and run 3..16 vectors on the matrix cores (which passes it
+    takes depends on the vectors, the context and the row's length, not on the number of rows)."""
     rows, cols = W32.shape
     G = cols // D
     ctx, oe, oc = gu.make_ctx(D, K, scale_bits, G)
@@ -41,9 +43,13 @@ def run_case(W32, D, K, scale_bits, src_bits=None, batches=(1, 4), out_dtypes=("
                 assert gu.ulp_f16(oracle.to_bf16_bits(ref), got) <= 1
     for B in batches:
         xf, xb = si.activations(B, cols, seed=seed + B)
-        y = pvq.pvq_decode_gemv(ctx, packed, gu.to_dev_bf16(xb)).cpu().numpy()
-        want = xf.astype(np.float64) @ ref.T
-        gu.assert_gemv_close(y, want, gu.product_scale(xf, ref))
+        want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+        names = []
+        for name, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
+            gu.assert_gemv_close(y, want, scale)
+            names.append(name)
+        if matrix_cores:
+            assert "table" in names and pvq.pvq_decode_gemv_plan(ctx, 1 << 20, cols, B) == [("mfma_bf16", B)]
     ctx.close()
     return packed, enc
 
@@ -133,8 +139,8 @@ def test_ragged_shapes(rows, cols, D):
 @pytest.mark.parametrize("rows,cols,bits", [(1, 8 * 4, 0), (5, 8 * 296, 2), (37, 8 * 1000, 8), (3, 8 * 3584, 2),
                                             (130, 8 * 64, 0)])
 def test_many_vectors_on_ragged_shapes(rows, cols, bits):
-    # the 16-vector pass (one group column per lane) with partial slices, few rows, rows that do not
-    # fill a batch; and a batch size that the narrower passes share (4 + 2 + 1)
+    # the walk's one pass for up to 16 vectors and the table decoder's passes of 4, 2 and 1 of them, with partial slices, few
+    # rows, rows that do not fill a batch
     wf, wb = si.gaussian_weights(rows, cols, 0.015, seed=si.BASE_SEED + 80 + rows, rotate=False, bf16=True)
     run_case(wf, 8, 16, bits, src_bits=wb, batches=(16, 11, 8, 7), out_dtypes=("bf16",))
 
@@ -145,9 +151,9 @@ def test_many_vectors_on_ragged_shapes(rows, cols, bits):
 def test_many_vectors_on_the_matrix_cores(rows, cols, bits):
     # 3..16 vectors with rows of 4, 5, 7, 8, 12, 13, 16 slabs of 64 groups: the pass whose dot products
     # run as 4x4x4 matrix instructions, one to four per half group; row counts that leave partial tiles of 16 rows and rounds of
-    # four, two and one tile, every amplitude format
+    # four, two and one tile, every amplitude format (matrices so small go to the walk by rule: the pass is asked for)
     wf, wb = si.gaussian_weights(rows, cols, 0.015, seed=si.BASE_SEED + 90 + rows, rotate=False, bf16=True)
-    run_case(wf, 8, 16, bits, src_bits=wb, batches=(16, 5, 9, 13, 3), out_dtypes=())
+    run_case(wf, 8, 16, bits, src_bits=wb, batches=(16, 5, 9, 13, 3), out_dtypes=(), matrix_cores=True)
 
 
 @pytest.mark.parametrize("rows,cols,bits", [(21, 8 * 1088, 2), (40, 8 * 1792, 2), (17, 8 * 3584, 0), (3, 8 * 2048, 8),
@@ -156,7 +162,7 @@ def test_many_vectors_on_the_matrix_cores_long_rows(rows, cols, bits):
     # rows of more than 16 slabs (17, 28, 56, 32, 31): the sixteen waves of a row tile take several slabs
     # each, some one more than others
     wf, wb = si.gaussian_weights(rows, cols, 0.015, seed=si.BASE_SEED + 95 + rows, rotate=False, bf16=True)
-    run_case(wf, 8, 16, bits, src_bits=wb, batches=(16, 5, 3), out_dtypes=())
+    run_case(wf, 8, 16, bits, src_bits=wb, batches=(16, 5, 10, 3), out_dtypes=(), matrix_cores=True)
 
 
 @pytest.mark.parametrize("rows,cols,bits,batch", [(4111, 8 * 320, 2, 5), (9001, 8 * 512, 0, 16), (20481, 8 * 256, 8, 3)])
@@ -164,7 +170,7 @@ def test_many_vectors_with_several_row_tiles_per_workgroup(rows, cols, bits, bat
     # more than 256 tiles of 16 rows: workgroups own two to six tiles (the last one partial) and take them in
     # rounds of four, two and one
     wf, wb = si.gaussian_weights(rows, cols, 0.015, seed=si.BASE_SEED + 96 + rows, rotate=False, bf16=True)
-    run_case(wf, 8, 16, bits, src_bits=wb, batches=(batch,), out_dtypes=())
+    run_case(wf, 8, 16, bits, src_bits=wb, batches=(batch,), out_dtypes=(), matrix_cores=True)
 
 
 @pytest.mark.parametrize("D,K", [(8, 16), (16, 33), (32, 60), (8, 1), (8, 127)])
@@ -514,8 +520,8 @@ def test_leading_dimensions_and_views():
 
 
 def test_leading_dimensions_in_the_many_vector_pass():
-    # rows of 256 groups with 24-bit indices go to the matrix-core pass for 3..16 vectors: activations
-    # and results as views with larger leading dimensions, results beyond the rows untouched
+    # rows of 256 groups with 24-bit indices, 3..16 vectors, on the matrix-core pass of the table decoder and on the walk:
+    # activations and results as views with larger leading dimensions, results beyond the rows untouched
     D, K, rows, cols, ld = 8, 16, 21, 2048, 2048 + 64
     wf, wb = si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 51, bf16=True)
     ctx = pvq.pvq_ctx_create(D, K)
@@ -524,11 +530,12 @@ def test_leading_dimensions_in_the_many_vector_pass():
     for batch in (5, 16):
         xf, xb = si.activations(batch, ld, seed=7 + batch)
         xv = gu.to_dev_bf16(xb)[:, :cols]
-        y_big = torch.full((batch, rows + 11), -3.0, dtype=torch.float32, device="cuda")
-        pvq.pvq_decode_gemv(ctx, packed, xv, out=y_big[:, :rows])
-        gu.assert_gemv_close(y_big[:, :rows].cpu().numpy(), xf[:, :cols].astype(np.float64) @ ref.T,
-                             gu.product_scale(xf[:, :cols], ref))
-        assert torch.all(y_big[:, rows:] == -3.0)
+        for decoder, tile_rows in (("table", 0), ("walk", 4), ("walk", 16)):
+            y_big = torch.full((batch, rows + 11), -3.0, dtype=torch.float32, device="cuda")
+            pvq.pvq_decode_gemv_on(ctx, packed, xv, decoder, tile_rows, out=y_big[:, :rows])
+            gu.assert_gemv_close(y_big[:, :rows].cpu().numpy(), xf[:, :cols].astype(np.float64) @ ref.T,
+                                 gu.product_scale(xf[:, :cols], ref))
+            assert torch.all(y_big[:, rows:] == -3.0)
     ctx.close()
 
 
@@ -614,9 +621,9 @@ def test_corrupt_indices_do_not_fault():
             torch.cuda.synchronize()
             assert out.shape == (16, 8192) and bool(torch.isfinite(out).all())
     x = torch.ones((16, 8192), dtype=torch.bfloat16, device="cuda")
-    for b in (1, 4, 16):                     # the single-vector, four-vector and matrix-core passes
-        y = pvq.pvq_decode_gemv(ctx, p, x[:b])
-        assert bool(torch.isfinite(y).all())
+    for b in (1, 2, 4, 16):                  # the table decoder's vector-ALU and matrix-core passes, the walk's
+        for _, y in gu.products(ctx, p, x[:b]):
+            assert np.isfinite(y).all()
     torch.cuda.synchronize()
     assert out.shape == (16, 8192) and bool(torch.isfinite(out).all())
     ctx.close()

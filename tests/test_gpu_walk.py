@@ -85,3 +85,20 @@ def test_infinities_in_a_rows_last_group(D, K, bits, rows, groups, batch):
         y = pvq.pvq_decode_gemv(ctx, packed, gu.to_dev_bf16(si.f32_to_bf16_bits(xf.astype(np.float32)))).cpu().numpy()
         assert np.all(y == np.inf)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K,bits,groups", [(8, 16, 2, 259), (16, 33, 4, 67), (32, 60, 0, 65), (32, 63, 2, 66)])
+def test_products_with_many_tiles_for_a_workgroup(D, K, bits, groups):
+    # more tiles of 4 and of 16 rows than workgroups at once, so that each takes several (the last one partial); group counts
+    # that fill neither 16 nor 4 columns; the schedules of 32, 64 / 32, 128 / 96 / 64 / 32 and 128 / 64 / 32 bits
+    rows = 9001
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=si.BASE_SEED + 640 + D, rotate=False)
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, D, K, bits, oe, nthreads=8), oc, nthreads=8)
+    for batch in (2, 7, 16):
+        xf, xb = si.activations(batch, D * groups, seed=D + batch)
+        want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+        for _, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
+            gu.assert_gemv_close(y, want, scale)
+    ctx.close()
