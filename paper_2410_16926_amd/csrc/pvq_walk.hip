@@ -25,7 +25,8 @@
 namespace {
 
 constexpr int kMaxThreads = 1024;   // lanes of a workgroup: 256 while the tables are small, 1024 (one copy of the
-                                    // tables for sixteen waves, two workgroups to a unit) when they are not
+                                    // tables for sixteen waves) when they are not: two workgroups to a unit, or one where
+                                    // the tables take more than half of its LDS (D = 32 from K = 68, D = 16 from 123)
 constexpr int kWave = 64;
 
 struct walk_launch {
@@ -266,13 +267,19 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
 // 16 x 16 x 4 with four blocks (R = 16, 16 vectors) or 4 x 4 x 4 with sixteen (R = 4, four vectors, NV of them for 4 NV).
 // D/4 of these in a row give the dot products of whole groups, whose gains (one per row and block) are multiplied
 // afterwards: products exact in float32, as on the vector ALUs.  A workgroup takes R rows at a time, its waves take the
-// columns in turn, and their sums meet in LDS, so that a few rows fill the chip as well.
+// columns in turn, and their sums meet in LDS, so that a few rows fill the chip as well.  Where the tables leave room for one
+// workgroup to a unit, its waves are several teams, each with a tile of its own.
 // Bound by the instructions of the walk (about 13 to 27 a coordinate, by its width).  14336 x 4096, D = 16, K = 33, 4-bit
 // codes, 1 / 4 / 5 / 16 vectors: 36 / 36 / 39 / 43 us, where passes of 4, 2 and 1 vectors on the vector ALUs, a wave per
 // row, took 51 / 72 / 123 / 287; D = 32, K = 60, 1 / 16 vectors: 51 / 52 us; 84 x 11776, D = 32, 11 vectors: 19 us (412
 // before); 139 x 864, one vector: 8 us (17).
+struct gemv_teams {
+    int waves, teams;
+    int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves
+};
+
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
-__global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles)
+__global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)
 {
     static_assert(R == 16 ? NV == 4 : R == 4, "tiles");
     using T = typename wide<W>::type;
@@ -283,9 +290,11 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
     extern __shared__ __align__(16) unsigned char lds[];
     const float *sqrtc = reinterpret_cast<const float *>(lds);
     const int lane = threadIdx.x % kWave;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), waves = (int)blockDim.x / kWave;
-    float *gains = reinterpret_cast<float *>(lds + wl.p.bytes) + wave * kWave;
-    float *sums = reinterpret_cast<float *>(lds + wl.p.bytes) + (R == 16 ? waves * kWave : 0);
+    const int wave_all = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
+    const int waves = split.waves, teams = split.teams, waves_all = waves * teams;
+    const int team = wave_all * split.inverse >> 8, wave = wave_all - team * waves;
+    float *gains = reinterpret_cast<float *>(lds + wl.p.bytes) + wave_all * kWave;
+    float *sums = reinterpret_cast<float *>(lds + wl.p.bytes) + (R == 16 ? waves_all * kWave : 0) + team * waves * kSums;
     const int G = (int)a.groups;
     const int chunks = (G + CG - 1) / CG;
     const int row_l = lane % R, col_l = lane / R;
@@ -304,14 +313,18 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
 #pragma unroll
     for (int v = 0; v < XV; v++)
         x0[v] = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)(b0 + std::min(4 * v + lane % (R == 16 ? 16 : 4), vectors - 1)) * a.ldx;
-    fetch((int)blockIdx.x, wave);                  // (there are no more waves than chunks)
+    const int stride = (int)gridDim.x * teams;
+    // (a team without a tile of its own, in a workgroup's last turn, fetches the last one and leaves it)
+    fetch(std::min((int)blockIdx.x * teams + team, row_tiles - 1), wave);   // (there are no more waves than chunks)
     tables_to_lds(lds, wl);
     int turn = 0;
-    for (int tile = (int)blockIdx.x; tile < row_tiles; tile += (int)gridDim.x, turn++) {
+    for (int first = (int)blockIdx.x * teams; first < row_tiles; first += stride, turn++) {
+        const int tile = first + team;
+        const bool live = tile < row_tiles;
         f32x4 acc[XV];                             // R = 16: rows 4 (lane / 16) + r, vector lane % 16; else row r, vector 4 v + lane % 4, own block
 #pragma unroll
         for (int v = 0; v < XV; v++) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-        for (int chunk = wave; chunk < chunks; chunk += waves) {
+        for (int chunk = live ? wave : chunks; chunk < chunks; chunk += waves) {
             const T c = group_index<W>(nx, g_nx, wl.index_bits);
             const float amp = group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc);
             uint4 x[XV][XW];
@@ -321,7 +334,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
                 for (int w = 0; w < XW; w++) x[v][w] = *reinterpret_cast<const uint4 *>(x0[v] + ((int64_t)g_nx * D + 8 * w));
             // the wave's next groups: of this tile, or of its next one
             const bool here = chunk + waves < chunks;
-            fetch(here ? tile : std::min(tile + (int)gridDim.x, row_tiles - 1), here ? chunk + waves : wave);
+            fetch(here ? tile : std::min(tile + stride, row_tiles - 1), here ? chunk + waves : wave);
             f32x16 out16;
             f32x4 out4[XV];
             if constexpr (R == 16) {
@@ -375,7 +388,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
         auto write = [&](const float *from, int t) {               // sum t of the tile, over the waves
             const int vec = R == 16 ? (t >> 2) & 15 : t >> 2;
             const int64_t row = row0 + (R == 16 ? 4 * (t >> 6) : 0) + (t & 3);
-            if (vec >= vectors || row >= a.rows) return;
+            if (vec >= vectors || row >= a.rows) return;           // (no row of a team without a tile)
             const float norm = wl.scale_bits == 0 ? 1.0f : sqrtf(a.rownorm[row]);
             float v = from[t];
             for (int w = 1; w < waves; w++) v += from[w * kSums + t];
@@ -384,7 +397,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
         if constexpr (R == 4) {
             // The sixteen blocks' sums, then the waves': two places in turn, so that the wave that writes this tile is done
             // with its place when the others come to use it again, one barrier later.
-            float *to = sums + (turn & 1) * (waves * kSums);
+            float *to = sums + (turn & 1) * (waves_all * kSums);
 #pragma unroll
             for (int v = 0; v < XV; v++) {
 #pragma unroll
@@ -397,7 +410,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
             __syncthreads();                       // (the tile before has been read)
             *reinterpret_cast<f32x4 *>(sums + wave * kSums + 4 * lane) = acc[0];
             __syncthreads();
-            for (int t = (int)threadIdx.x; t < kSums; t += (int)blockDim.x) write(sums, t);
+            for (int t = wave * kWave + lane; t < kSums; t += waves * kWave) write(sums, t);
         }
     }
 }
@@ -489,9 +502,9 @@ hipError_t launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dty
     }
 }
 
-// How a pass is split: tiles of `rows` rows, `waves` waves per workgroup
+// How a pass is split: tiles of `rows` rows, `waves` waves for each, `teams` of so many waves per workgroup
 struct gemv_split {
-    int rows, waves;
+    int rows, waves, teams;
     unsigned grid;
 };
 
@@ -509,7 +522,7 @@ size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
 // tile_rows: only tiles of so many rows are looked at (0: both).
 gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows)
 {
-    gemv_split best = {0, 0, 0};
+    gemv_split best = {0, 0, 0, 0};
     double least = 0;
     const double chain = 280.0 * c->D, issue = 4.0 * (80.0 + c->D * (c->words == 1 ? 14.0 : c->words == 2 ? 17.0 : 25.0));
     for (int R = 4; R <= 16; R += 12) {
@@ -518,17 +531,26 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
         const double loads = c->D * 128.0 / 11.0 * (R == 16 ? 1 : nv);
         const int64_t tiles = (rows + R - 1) / R, chunks = (groups + kWave / R - 1) / (kWave / R);
         const int64_t tiles_unit = (tiles + units() - 1) / units();
+        bool most = true;                          // the most waves that have a chunk each
         for (int waves = 16; waves >= 1; waves -= waves > 8 ? 4 : waves > 4 ? 2 : 1) {
+            if (waves > chunks) continue;
+            const bool all = most;
+            most = false;
             const size_t lds = gemv_lds(c, waves, R, sums);
-            if (waves > chunks || lds > 160 * 1024) continue;
+            if (lds > 160 * 1024) continue;
             const int resident = R == 16 || nv < 4 ? (c->D < 32 ? 32 : nv == 2 && R == 4 ? 16 : 20) : c->D == 8 ? 24 : 16;   // waves of a unit
-            const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)(160 * 1024 / lds)), tiles_unit));
-            const double turns = (double)((tiles_unit + blocks - 1) / blocks), steps = (double)((chunks + waves - 1) / waves);
+            int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)(160 * 1024 / lds)), tiles_unit));
+            // One workgroup to a unit, and a row too short for its waves: more teams.  D = 32, one vector on 14336 x 4096,
+            // K = 68 / 69 / 105: eight waves 145 / 169 / 171 us, two teams of eight 91 / 107 / 108.
+            int teams = 1;
+            if (all && c->walk.bytes > 80 * 1024)
+                while (teams < tiles_unit && (teams + 1) * waves <= std::min(resident, 16) && gemv_lds(c, (teams + 1) * waves, R, sums) <= 160 * 1024) teams++;
+            const double turns = (double)((tiles_unit + blocks * teams - 1) / (blocks * teams)), steps = (double)((chunks + waves - 1) / waves);
             const double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
                                          (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
             if (best.rows == 0 || cost < least) {
                 least = cost;
-                best = {R, waves, (unsigned)std::min<int64_t>(tiles, (int64_t)units() * blocks)};
+                best = {R, waves, teams, (unsigned)std::min<int64_t>((tiles + teams - 1) / teams, (int64_t)units() * blocks)};
             }
         }
     }
@@ -538,11 +560,11 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
 hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, int vectors, const gemv_split &split, hipStream_t s)
 {
-    const size_t lds = gemv_lds(c, split.waves, R, 4 * R * NV);
+    const size_t lds = gemv_lds(c, split.waves * split.teams, R, 4 * R * NV);
     const hipError_t e = allow_lds<gemv_walk_kernel<D, W, DX, DA, DB, R, NV>>(lds);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((gemv_walk_kernel<D, W, DX, DA, DB, R, NV>), dim3(split.grid), dim3((unsigned)(split.waves * kWave)), lds, s,
-                       make_launch(c), a, b0, vectors, (int)((a.rows + R - 1) / R));
+    hipLaunchKernelGGL((gemv_walk_kernel<D, W, DX, DA, DB, R, NV>), dim3(split.grid), dim3((unsigned)(split.waves * split.teams * kWave)), lds, s,
+                       make_launch(c), a, b0, vectors, (int)((a.rows + R - 1) / R), gemv_teams{split.waves, split.teams, (256 + split.waves - 1) / split.waves});
     return hipGetLastError();
 }
 

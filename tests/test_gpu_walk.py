@@ -102,3 +102,22 @@ def test_products_with_many_tiles_for_a_workgroup(D, K, bits, groups):
         for _, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
             gu.assert_gemv_close(y, want, scale)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K,bits", [(32, 69, 4), (32, 105, 0), (16, 127, 2)])
+@pytest.mark.parametrize("rows,groups", [(2049, 3), (5003, 20), (3100, 65)])
+def test_products_with_several_teams_of_waves(D, K, bits, rows, groups):
+    # tables that leave room for one workgroup to a unit, several tiles of rows for each: teams of 1, 4 and 16 waves, the
+    # last turn with teams that have no tile
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=si.BASE_SEED + 630 + rows, rotate=False)
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, D, K, bits, oe, nthreads=8), oc, nthreads=8)
+    for batch in (1, 5, 16):
+        xf, xb = si.activations(batch, D * groups, seed=rows + batch)
+        want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+        x = gu.to_dev_bf16(xb)
+        gu.assert_gemv_close(pvq.pvq_decode_gemv(ctx, packed, x).cpu().numpy(), want, scale)
+        for tile_rows in (4, 16):
+            gu.assert_gemv_close(pvq.pvq_decode_gemv_on(ctx, packed, x, "walk", tile_rows).cpu().numpy(), want, scale)
+    ctx.close()
