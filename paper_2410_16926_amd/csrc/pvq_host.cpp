@@ -262,7 +262,7 @@ bool fill_walk_tables(const SizeTable &t, std::vector<unsigned char> &blob, pvq_
             above = std::max(above, j);
             while (T[above + 1] < to) above++;
             guess[b] = (unsigned char)j;
-            if (above > j + 1) p.more = 1;
+            if (above > j + 1) p.more |= 1u << dp;
         }
     }
     p.bytes = (uint32_t)blob.size();

@@ -47,7 +47,7 @@ template <> struct wide<4> { using type = unsigned __int128; };
 constexpr int words_of_row(int dp, int W, int DX, int DA, int DB) { return dp >= DX ? W : dp >= DA ? 3 * W / 4 : dp >= DB ? W / 2 : W / 4; }
 // Fraction bits of guess row DP, chosen so that a bucket of q holds one threshold besides the one its guess stands for
 // (the rows of few dimensions grow slowly and get finer buckets).  Enough for every K of the schedules
-// that have no search behind the guess (searches); with the others pvq_walk_params::more says whether they are.
+// that have no search behind the guess (searches); with the others pvq_walk_params::more says for which rows they are not.
 constexpr int guess_bits(int dp, int D)
 {
     return D == 32 ? (dp == 2 ? 6 : dp <= 5 ? 5 : dp <= 13 ? 4 : 3) : dp == 2 ? 5 : dp <= 10 ? 4 : 3;
@@ -142,7 +142,7 @@ PVQ_HD void threshold(const unsigned char *tables, const pvq_walk_params &p, uin
 // The coordinate of row DP (DP + 1 dimensions left), whose thresholds start at byte `at`: its place j in them
 // (pvq_internal.h).  q loses T_j.
 template <int DP, int D, int W, int DX, int DA, int DB>
-PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t *q)
+PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t more, uint32_t *q)
 {
     constexpr int WP = words_of_row(DP, W, DX, DA, DB);
     if constexpr (DP == 1) {
@@ -155,14 +155,6 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
         constexpr uint32_t guesses = guess_row(DP, D, W, DX, DA, DB) - (127u << MB);
         uint32_t j = table_at<uint8_t>(tables, guesses + (float_bits(float_of<WP>(q)) >> (23 - MB)));
         uint32_t t0[WP], t1[WP], d0[WP], d1[WP];
-        if constexpr (searches(D, W, DX, DA)) {
-            if (p.more) {                                          // (the same for all lanes)
-                for (;; j++) {                                     // (ends: the entry behind the row's thresholds is all ones)
-                    threshold<WP>(tables, p, at, j + 1, t1);
-                    if (subtract<WP>(d1, q, t1)) break;
-                }
-            }
-        }
         threshold<WP>(tables, p, at, j, t0);
         threshold<WP>(tables, p, at, j + 1, t1);
         subtract<WP>(d0, q, t0);
@@ -172,7 +164,28 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
 #endif
-        for (int x = 0; x < WP; x++) q[x] = up ? d1[x] : d0[x];
+        for (int x = 0; x < WP; x++) d0[x] = up ? d1[x] : d0[x];
+        if constexpr (searches(D, W, DX, DA)) {
+            // A bucket with more thresholds: one read more in nearly every wave, in the rows that have such (in all rows of a
+            // context that has one, and in front of the pair, it cost D = 32, K = 80 114 instead of 71 us for 14336 x 4096 to
+            // bf16, D = 16, K = 45 71 instead of 50).
+            if (more >> DP & 1u) {                                 // (the same for all lanes)
+                bool on = up;
+                while (on) {                                       // (ends: q lies below the entry behind the thresholds)
+                    threshold<WP>(tables, p, at, j + 1, t1);
+                    on = !subtract<WP>(d1, q, t1);
+                    j += on ? 1u : 0u;
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+                    for (int x = 0; x < WP; x++) d0[x] = on ? d1[x] : d0[x];
+                }
+            }
+        }
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+#endif
+        for (int x = 0; x < WP; x++) q[x] = d0[x];
         return j;
     }
 }
@@ -181,13 +194,13 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
 template <int D, int W, int DX, int DA, int DB>
 struct walk_state {
     uint32_t q[W];
-    uint32_t k, at;
+    uint32_t k, at, more;
     float n2;
 
     template <int I, typename Emit>
     PVQ_HD void coordinate(const unsigned char *tables, const pvq_walk_params &p, Emit &emit)
     {
-        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, q);
+        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, more, q);
         at += row_bytes(p, words_of_row(D - 1 - I, W, DX, DA, DB));
         const uint32_t C = j >> 1;
         const float m = (float)(k - C);
@@ -216,8 +229,9 @@ PVQ_HD float unrank_walk(typename wide<W>::type c, const unsigned char *tables, 
     for (int x = 0; x < W; x++) st.q[x] = none ? 0u : st.q[x];
     st.k = (uint32_t)p.K; st.n2 = 0.0f;
     st.at = threshold_base(D, W, DX, DA, DB);
+    st.more = p.more;
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+s"(st.at));                                // (else a kernel's loop keeps a register per row)
+    asm volatile("" : "+s"(st.at), "+s"(st.more));                 // (else a kernel's loop keeps registers per row: 106 scalar ones, seven waves)
 #endif
     st.all(tables, p, emit, std::make_integer_sequence<int, D - 1>{});
     // the two points +k, -k of P(1,k): q = 1, 0

@@ -541,7 +541,8 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
             const int resident = R == 16 || nv < 4 ? (c->D < 32 ? 32 : nv == 2 && R == 4 ? 16 : 20) : c->D == 8 ? 24 : 16;   // waves of a unit
             int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)(160 * 1024 / lds)), tiles_unit));
             // One workgroup to a unit, and a row too short for its waves: more teams.  D = 32, one vector on 14336 x 4096,
-            // K = 68 / 69 / 105: eight waves 145 / 169 / 171 us, two teams of eight 91 / 107 / 108.
+            // K = 68 / 80 / 105: two teams of eight 57 / 63 / 71 us (before the walk's search became shorter eight waves took
+            // 145 / 170 / 171, two teams 91 / 108 / 108).
             int teams = 1;
             if (all && c->walk.bytes > 80 * 1024)
                 while (teams < tiles_unit && (teams + 1) * waves <= std::min(resident, 16) && gemv_lds(c, (teams + 1) * waves, R, sums) <= 160 * 1024) teams++;

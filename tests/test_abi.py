@@ -142,11 +142,14 @@ def test_pvq_correct_work_bytes():
 
 @pytest.mark.parametrize("D,K,schedule", [(16, 33, (8, 0)), (32, 60, (15, 6)), (16, 16, (8, 0)), (8, 40, (0, 0)),
                                           (32, 9, (12, 0)), (32, 25, (15, 6)), (16, 60, (0, 0)), (8, 127, (0, 0)),
-                                          (16, 1, (0, 0)), (32, 2, (0, 0)), (8, 3, (0, 0))])
+                                          (16, 1, (0, 0)), (32, 2, (0, 0)), (8, 3, (0, 0)), (8, 64, (0, 0)),
+                                          (16, 45, (0, 0)), (16, 127, (0, 0)), (32, 64, (15, 6)), (32, 69, (0, 0)),
+                                          (32, 105, (0, 0))])
 def test_one_probe_per_coordinate_decoder_replays_sampled_indices(D, K, schedule):
-    # host logic: the cumulative rows and guess tables the D = 16 / 32 kernels walk, replayed on the CPU over the
+    # host logic: the thresholds and guess tables the D = 16 / 32 kernels walk, replayed on the CPU over the
     # ends of the index range and seeded random indices against the magnitude-by-magnitude decoding; the width
-    # schedule (64-bit integers down to 9 dimensions and 32-bit ones from 8 on, for the 52-bit setting)
+    # schedule (64-bit integers down to 9 dimensions and 32-bit ones from 8 on, for the 52-bit setting); settings whose
+    # buckets hold up to two thresholds in a few rows, in most rows, or five
     bad, sched, nbytes = pvq.pvq_walk_tables_selftest(D, K, seed=D * 1000 + K, count=60000)
     assert bad == 0
     assert sched == schedule
