@@ -465,6 +465,24 @@ hipError_t allow_lds(size_t bytes)
     return hipFuncSetAttribute(reinterpret_cast<const void *>(Kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
 }
 
+// Waves of a kernel that a SIMD holds by the kernel's registers, asked once per kernel (a workgroup of four waves has one on
+// each SIMD).
+template <auto Kernel>
+int waves_per_simd()
+{
+    static std::atomic<int> known{0};
+    int n = known.load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void *>(Kernel), 4 * kWave, 0) != hipSuccess) {
+            (void)hipGetLastError();
+            n = 0;
+        }
+        n = std::min(std::max(n, 4), 8);           // (a workgroup of 1024 lanes has four)
+        known.store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
+
 // workgroups of a launch over `items` wave items: 32 waves per unit, fewer if the work is small
 unsigned persistent_grid(const pvq_ctx *c, int64_t items)
 {
@@ -502,6 +520,9 @@ hipError_t launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dty
     }
 }
 
+// workgroups with so much LDS that a unit's 160 KiB hold (given out in steps of 1280 bytes)
+int unit_copies(size_t lds) { return (int)(160 * 1024 / ((lds + 1279) / 1280 * 1280)); }
+
 // How a pass is split: tiles of `rows` rows, `waves` waves for each, `teams` of so many waves per workgroup
 struct gemv_split {
     int rows, waves, teams;
@@ -514,13 +535,18 @@ size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
     return (size_t)c->walk.bytes + (size_t)waves * (R == 16 ? kWave + sums : 2 * sums) * sizeof(float);
 }
 
-// The split that should take least, from what a wave's 64 groups take (clocks, measured): alone, as a chain of table reads; of
+// The split that should take least, from what a wave's 64 groups take in clocks: alone, as a chain of table reads; of
 // a SIMD's issue slots, when several waves share it; of the unit's loads of activations, which a tile of four rows
-// repeats four times as often (11 bytes a clock); and what a tile takes besides.  It picks tiles of 16 rows for more than
-// four vectors on large matrices (D = 32, 14336 x 4096, 16 vectors: 52 us, with four rows 79), four rows while those would
-// leave units idle (1289 x 16384, 11 vectors: 38 us, with sixteen 50).
+// repeats four times as often (11 bytes a clock); and what a tile takes besides.  These are estimates (a line each through
+// products of D = 8, 16 and 32), not a bound: of 234 products (six contexts, 64 x 4096 to 8192 x 28672, 1 to 16 vectors)
+// the split picked is 6 % slower than the best one in the median, 18 % at the ninth decile, 47 % at the worst.  It picks
+// tiles of 16 rows for more than four vectors on large matrices (D = 32, 14336 x 4096, 16 vectors: 50 us, with four rows
+// 79), four rows while those would leave units idle (1289 x 16384, 11 vectors: 37 us, with sixteen 50).
+// How many workgroups a unit holds follows from their LDS and from the kernel's registers (simd4, simd16: waves of a
+// SIMD, for tiles of 4 and 16 rows); a workgroup more than that waits for a whole one (D = 16, K = 59, one vector on
+// 14336 x 4096: 114 us where three copies of the tables were thought to fit, with two 63).
 // tile_rows: only tiles of so many rows are looked at (0: both).
-gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows)
+gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows, int simd4, int simd16)
 {
     gemv_split best = {0, 0, 0, 0};
     double least = 0;
@@ -538,13 +564,13 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
             most = false;
             const size_t lds = gemv_lds(c, waves, R, sums);
             if (lds > 160 * 1024) continue;
-            const int resident = R == 16 || nv < 4 ? (c->D < 32 ? 32 : nv == 2 && R == 4 ? 16 : 20) : c->D == 8 ? 24 : 16;   // waves of a unit
-            int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)(160 * 1024 / lds)), tiles_unit));
+            const int resident = 4 * (R == 16 ? simd16 : simd4);                       // waves of a unit
+            int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)unit_copies(lds)), tiles_unit));
             // One workgroup to a unit, and a row too short for its waves: more teams.  D = 32, one vector on 14336 x 4096,
             // K = 68 / 80 / 105: two teams of eight 57 / 63 / 71 us (before the walk's search became shorter eight waves took
             // 145 / 170 / 171, two teams 91 / 108 / 108).
             int teams = 1;
-            if (all && c->walk.bytes > 80 * 1024)
+            if (all && unit_copies(c->walk.bytes) == 1)
                 while (teams < tiles_unit && (teams + 1) * waves <= std::min(resident, 16) && gemv_lds(c, (teams + 1) * waves, R, sums) <= 160 * 1024) teams++;
             const double turns = (double)((tiles_unit + blocks * teams - 1) / (blocks * teams)), steps = (double)((chunks + waves - 1) / waves);
             const double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
@@ -574,7 +600,11 @@ hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, int tile_rows
 {
     for (int b0 = 0; b0 < a.batch; b0 += 16) {
         const int vectors = std::min(a.batch - b0, 16);
-        const gemv_split split = split_gemv(c, a.rows, a.groups, vectors, tile_rows);
+        const gemv_split split = split_gemv(c, a.rows, a.groups, vectors, tile_rows,
+                                            vectors <= 4 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 1>>()
+                                            : vectors <= 8 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 2>>()
+                                                           : waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 4>>(),
+                                            waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 16, 4>>());
         if (split.rows == 0) return hipErrorInvalidValue;          // (no LDS left beside the tables: only where tile_rows asks for 16)
         hipError_t e;
         if (split.rows == 16) e = launch_gemv_pass<D, W, DX, DA, DB, 16, 4>(c, a, b0, vectors, split, s);

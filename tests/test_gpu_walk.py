@@ -87,10 +87,11 @@ def test_infinities_in_a_rows_last_group(D, K, bits, rows, groups, batch):
     ctx.close()
 
 
-@pytest.mark.parametrize("D,K,bits,groups", [(8, 16, 2, 259), (16, 33, 4, 67), (32, 60, 0, 65), (32, 63, 2, 66)])
+@pytest.mark.parametrize("D,K,bits,groups", [(8, 16, 2, 259), (16, 33, 4, 67), (32, 60, 0, 65), (32, 63, 2, 66), (16, 59, 0, 65)])
 def test_products_with_many_tiles_for_a_workgroup(D, K, bits, groups):
     # more tiles of 4 and of 16 rows than workgroups at once, so that each takes several (the last one partial); group counts
-    # that fill neither 16 nor 4 columns; the schedules of 32, 64 / 32, 128 / 96 / 64 / 32 and 128 / 64 / 32 bits
+    # that fill neither 16 nor 4 columns; the schedules of 32, 64 / 32, 128 / 96 / 64 / 32 and 128 / 64 / 32 bits; tables of
+    # which a unit would hold three copies but for the steps LDS is given out in
     rows = 9001
     W = si.gaussian_weights(rows, D * groups, 0.02, seed=si.BASE_SEED + 640 + D, rotate=False)
     ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
