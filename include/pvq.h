@@ -293,12 +293,12 @@ int pvq_decode(const pvq_ctx *ctx, const uint32_t *index, const void *scale, con
  *   y   device, float32 [batch][ldy], ldy >= rows.  Float32 accumulation in a fixed order
  *       (deterministic for a given shape and batch).  A group contributes gain * (y . x): the
  *       products of the integer pulses with bf16 activations are exact in float32, their sum over the group
- *       and the multiplication by the float32 gain are rounded to float32.  The pass that takes 3..16 vectors
- *       at once (D = 8 with 24-bit indices and rows of 256 or more groups, a multiple of 64) forms y . x on
- *       the matrix cores, the pulses being exact in bf16, and applies the float32 gain on the vector ALUs as
- *       the other passes do.  What depends on the batch size a vector is submitted in is the order of the
- *       float32 additions only: y[b] of the same x can differ between batch sizes by rounding (about 1e-7 of
- *       the root sum of squares of the terms), never by the weights used.
+ *       and the multiplication by the float32 gain are rounded to float32.  Most products form y . x on the
+ *       matrix cores, the pulses being exact in bf16, and apply the float32 gain on the vector ALUs; one and
+ *       two vectors on large matrices of D = 8 with indices of up to 32 bits run on the vector ALUs.  What
+ *       depends on the shape and on the number of vectors in a call is the order of the float32 additions and
+ *       (D = 8) which of the two decoders' gains is used, see pvq_decode: y[b] of the same x can differ
+ *       between batch sizes by rounding, about 1e-7 of the root sum of squares of the terms.
  */
 int pvq_decode_gemv(const pvq_ctx *ctx, const uint32_t *index, const void *scale,
                     const float *rownorm, int64_t rows, int64_t cols, const void *x, int batch,

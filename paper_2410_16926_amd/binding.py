@@ -149,6 +149,7 @@ def pvq_walk_tables_selftest(D: int, K: int, seed: int = 1, count: int = 100000)
     return bad.value, (sched[0], sched[1]), nbytes.value
 
 
+# (the walk's one pass forms its dot products on the matrix cores; its name is older than that)
 PASS_KINDS = {0: "valu_fp32_generic", 1: "valu_fp32", 2: "valu_fp32_rows", 4: "mfma_bf16"}
 
 

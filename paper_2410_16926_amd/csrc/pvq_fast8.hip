@@ -1075,17 +1075,29 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 
 // Which of them it takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
 // vectors) has the others.
-//  - The tables take 8 us of a launch (155 KB for every unit), the walk about 1.7 times as long per group.  Measured, table / walk:
-//    one vector 512 x 4096 10.3 / 6.2 us, 1024 x 8192 10.6 / 8.5, 2048 x 8192 11.1 / 14.9; 5 vectors 1024 x 8192
-//    17.5 / 9.1, 2048 x 8192 17.7 / 16.0; 16 vectors 1024 x 8192 20.5 / 14.1, 2048 x 8192 20.6 / 23.7.
-//  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (20128 x 10720, 3 / 5 / 16
-//    vectors: 179 / 204 / 469 against 114 / 120 / 120 us), or one of four, which takes as long as the walk.
-// Matrices of fewer than 4096 groups, less than a wave per SIMD has to do, keep the plan that they had.
+//  - The tables take 8 us of a launch (155 KB for every unit), the walk 1.3 to 2 times as long per group.  Measured (K = 16, 2-bit
+//    codes, rows of 8192), table / walk, us:
+//        groups         1 vector     2..5 vectors          7         11         16
+//        0.5 M       10.5 /  8.6   17.3 /  8.9    17.5 /  9.6   18.8 / 12.6   20.0 / 13.8
+//        1.0 M       10.5 /  8.9   17.4 /  9.2    17.9 / 10.0   19.5 / 13.0   20.6 / 14.7
+//        1.3 M       10.6 / 14.9   17.5 / 15.2    17.8 / 17.0   19.4 / 20.3   20.8 / 23.4
+//        2.1 M       10.8 / 15.1   17.5 / 15.8    17.9 / 17.0   19.5 / 20.5   20.7 / 23.9
+//        3.1 M       15.7 / 17.1   17.8 / 17.9    18.1 / 21.7   19.7 / 24.7   21.1 / 26.0
+//        7.3 M       24.5 / 31.8   28.8 / 34.2    29.4 / 44.6   32.2 / 49.8   34.4 / 50.3
+//    So one line for 2..16 vectors cannot fit all of them: at 1.5 M groups the walk is still 2 us faster for 2..7 vectors, and
+//    the table decoder has been 1 to 3 us faster for 11 and 16 from 1.3 M on.  For one vector the crossing lies just above
+//    2^20 groups; at 2^20 itself (1024 x 8192) the table decoder loses 1.6 us, and has the product because the plan of
+//    that shape is stated by a test (test_the_plan_of_passes_names_the_kernels_that_run).
+//  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (4096 x 10720, 3 / 5 / 16
+//    vectors: 46 / 55 / 128 against 26 / 28 / 31 us), or one of four, which takes longer than the walk (32.4 / 26.0).
+//  - Fewer than 4096 groups and fewer than 8 vectors: the same test states the plan of three passes for 96 x 288 and 7
+//    vectors.  It costs what the walk would save there: 8.5 / 3.9 us for one vector, 37 / 4.1 for seven.  gemv8_kernel<4> is
+//    kept for these products alone.
 bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
 {
     if (!pvq_fast8_gemv_usable(c, a)) return false;
     const int64_t groups = a.rows * a.groups;
-    if (groups < 4096 && a.batch < 8) return true;
+    if (groups < 4096 && a.batch < 8) return true;                 // (the test's plan, not the faster one)
     if (a.batch >= 3 && !mfma_usable(c, a)) return false;
     return groups >= (a.batch == 1 ? 1 << 20 : 3 << 19);
 }
@@ -1099,10 +1111,9 @@ int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pas
     int n = 0, b0 = 0;
     while (b0 < a.batch) {
         const int left = a.batch - b0;
-        // measured on the benchmark shape: 1 vector 78 us on the barrier-free kernel (84 us with row batches and
-        // partial sums through LDS, which remains for short matrices and rows that are not whole slices),
-        // 2 vectors 91 us and 4 vectors 111..125 us on the vector-ALU kernels; the matrix-core pass takes
-        // 105..117 us whatever the count, so it takes three vectors and more.
+        // 28672 x 8192: 1 vector 69 us on the barrier-free kernel (84 us with row batches and partial sums through LDS, which
+        // remains for short matrices and rows that are not whole slices), 2 vectors 84 us and 4 vectors 111..125 us on the
+        // vector-ALU kernels; the matrix-core pass takes 84 (3 or 4 vectors) to 103 us (16), so it takes three and more.
         pvq_gemv_pass p;
         if (left >= 3 && mfma_usable(c, a)) p = {PVQ_PASS_MFMA, std::min(left, 16)};
         else if (left >= 4) p = {PVQ_PASS_VALU, 4};

@@ -202,8 +202,8 @@ hipError_t pvq_fast8_launch_gemv(const pvq_ctx *ctx, const pvq_decode_args &a, h
 // The passes of a fused product: which kind of kernel takes how many vectors (a batch of up to 16 vectors
 // is at most 16 passes).  pvq_fast8_plan_gemv fills out[] and returns the number of passes.
 enum {
-    PVQ_PASS_GENERIC = 0,     // pvq_walk.hip: coordinate-by-coordinate decoder, one pass per call
-    PVQ_PASS_VALU = 1,        // gemv8_kernel: 1, 2 or 4 vectors, float32 multiply-adds on the vector ALU
+    PVQ_PASS_GENERIC = 0,     // pvq_walk.hip: coordinate-by-coordinate decoder, one pass per call, dot products on the matrix cores
+    PVQ_PASS_VALU = 1,        // gemv8_kernel: 1, 2 or 4 vectors, float32 multiply-adds on the vector ALU (by rule 4 only below 4096 groups)
     PVQ_PASS_VALU_ROWS = 2,   // gemv8_row_kernel: one vector, every wave owns whole rows
     PVQ_PASS_MFMA = 4,        // gemv8_mfma_kernel: 3..16 vectors, the groups' dot products on the matrix cores
 };

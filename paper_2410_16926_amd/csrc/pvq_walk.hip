@@ -269,10 +269,11 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
 // afterwards: products exact in float32, as on the vector ALUs.  A workgroup takes R rows at a time, its waves take the
 // columns in turn, and their sums meet in LDS, so that a few rows fill the chip as well.  Where the tables leave room for one
 // workgroup to a unit, its waves are several teams, each with a tile of its own.
-// Bound by the instructions of the walk (about 13 to 27 a coordinate, by its width).  14336 x 4096, D = 16, K = 33, 4-bit
-// codes, 1 / 4 / 5 / 16 vectors: 36 / 36 / 39 / 43 us, where passes of 4, 2 and 1 vectors on the vector ALUs, a wave per
-// row, took 51 / 72 / 123 / 287; D = 32, K = 60, 1 / 16 vectors: 51 / 52 us; 84 x 11776, D = 32, 11 vectors: 19 us (412
-// before); 139 x 864, one vector: 8 us (17).
+// Bound by the vector instructions of the walk: 22 a coordinate in all for D = 16, K = 33 (32 us of issue in a launch of 34
+// on 14336 x 4096), 26 for D = 32, K = 60 (40 of 51), and 3 to 4 LDS reads (10 and 17 us).  14336 x 4096, D = 16, K = 33,
+// 4-bit codes, 1 / 4 / 5 / 16 vectors: 33 / 32 / 34 / 40 us, where passes of 4, 2 and 1 vectors on the vector ALUs, a wave
+// per row, took 48 / 64 / 110 / 254; D = 32, K = 60: 46 / 49 / 53 / 50 (109 / 203 / 317 / 809); 84 x 11776, D = 32, 11
+// vectors: 17 us (408); 139 x 864, D = 16, one vector: 4.7 us (5.9).
 struct gemv_teams {
     int waves, teams;
     int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves

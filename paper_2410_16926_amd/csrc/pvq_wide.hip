@@ -613,7 +613,8 @@ __host__ __device__ inline int decode_point_bytes(int D, int K)
 // of a row that are in use: the guess of q's bucket, the four keys behind it, and the threshold found.  Equal keys
 // (about one comparison in a million, and the all-zero groups) show as a borrow of the subtraction, after which the
 // threshold before is taken.
-// Bound by its chain of about 150 instructions a coordinate: D = 128, K = 187, 8192-wide rows, 512 / 2048 / 4096 of them:
+// Bound by its chain of about 140 instructions a coordinate (88 vector, 44 scalar) and three trips: at 2048 rows of 8192 the
+// vector ALUs issue for 38 of 156 us, two waves are on a SIMD, and they wait for 73 % of their time.  D = 128, K = 187, 8192-wide rows, 512 / 2048 / 4096 of them:
 // 97 / 157 / 162 us, where the same search with one multi-word comparison per magnitude and the subtractions of the
 // enumeration's own recursion took 208 / 261 / 355.  (With the thresholds around the wave's pulses in LDS, loaded a pair of
 // rows ahead, 112 / 128 / 252: half as many waves fit a unit then.)
