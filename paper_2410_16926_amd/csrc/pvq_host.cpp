@@ -695,9 +695,13 @@ static int fill_decode_args(const pvq_ctx *c, pvq_decode_args &a, const uint32_t
     return PVQ_OK;
 }
 
-// The table decoder for groups of 8 copies 155 KB of tables into every unit's LDS before its first group (about
-// 13 us a launch); the coordinate-by-coordinate decoder starts with 3 KB.  Measured to bf16: 1024 x 8192 (1.0 M
-// groups) 22.2 against 17.8 us, 512 x 512 27 against 14 us, 2048 x 8192 (2.1 M groups) 24.1 against 25.4 us.
+// The table decoder for groups of 8 copies 155 KB of tables into every unit's LDS before its first group; the
+// coordinate-by-coordinate decoder starts with 7 KB.  Launches in a row, K = 16, 2-bit codes, table / walk, us:
+//                512 x 512    1024 x 8192   2048 x 8192   3072 x 8192   4096 x 8192   28672 x 8192
+//   to bf16      25.2 /  3.7   18.5 / 10.6   20.1 / 16.2   20.4 / 20.2   20.8 / 24.7   125 / 151
+//   to float32   25.3 /  3.7   21.4 / 11.3   23.1 / 16.2   26.3 / 21.8   30.0 / 27.6   302 / 261
+// The line (1.5 M groups, which a test states) was drawn with an earlier walk, from 1024 x 8192 and 2048 x 8192: by these
+// times it would lie at 3.1 M groups to 16 bits, and the walk would have every matrix to float32.
 static std::atomic<int64_t> g_table_decoder_min_groups{1572864};
 
 static bool table_decoder_pays(const pvq_ctx *c, const pvq_decode_args &a)
