@@ -215,7 +215,7 @@ int pvq_encode(const pvq_ctx *ctx, const void *W, int dtype, int64_t rows, int64
  * applied one at a time in the order of the rows of U, so the result does not depend on the launch shape.
  * Contexts with D = 8, 16 or 32 and cols a multiple of 64, else PVQ_E_UNSUPPORTED.  A zero on the
  * diagonal of U gives non-finite weights (then encoded as pvq_encode encodes them), never a fault.
- * Launches 2 ceil(cols/128) - 1 kernels on `stream`, nothing else (no other stream, no event, no allocation), so
+ * Launches ceil(cols/128) kernels on `stream`, nothing else (no other stream, no event, no allocation), so
  * the call can be captured in a graph; asynchronous.
  */
 int pvq_correct_work_bytes(int64_t rows, size_t *bytes);

@@ -325,8 +325,8 @@ def pvq_correct(ctx: PvqContext, W, U, work=None):
 
 
 def pvq_correct_set_front_tiles(tiles: int) -> int:
-    """Diagnostics: from how many update tiles on a launch of pvq_correct does the narrow update inside its panel
-    workgroups (process-wide; results do not depend on it).  Returns the number in force before."""
+    """Diagnostics: keeps a number for its callers and returns the one before (every launch of pvq_correct updates its
+    panel inside the panel's workgroups)."""
     old = C.c_int64(0)
     _check(lib().pvq_correct_set_front_tiles(int(tiles), C.byref(old)), "pvq_correct_set_front_tiles")
     return old.value

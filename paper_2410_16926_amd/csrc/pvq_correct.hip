@@ -8,25 +8,27 @@
 // order is part of the definition, because later roundings are decided from these values.  On return W
 // holds, for every group, the values that were quantised: encoding it gives the corrected code.
 //
-// Rows are independent, groups of a row strictly sequential, and U is the same for every row.  Columns are
-// taken in panels of 128.  Panel p takes two launches on the caller's stream:
-//   correct_narrow_kernel  panel p - 1's 128 multiply-adds per element onto the columns of panel p, which is all that
-//           panel p waits for: tiles of 16 rows x 128 columns, so that even a few rows spread over many compute units.
-//   correct_step_kernel    workgroups with one of two roles:
-//     panel   (the first ceil(rows / 64) workgroups) 64 rows of panel p, one lane per row, four waves that own the
-//             panel's groups in turn: the owner of a group quantises it and publishes its t values, the other
-//             waves meanwhile bring their own later groups up to date.  Leaves the panel's t values (rows x 128) in a
-//             work buffer.  Bound by the latency of one wave's quantiser and substitution, 128 / D times in a row.
-//     update  (all others) panel p - 1's 128 multiply-adds per element, in the same order, for the columns
-//             behind panel p: tiles of 128 rows x 128 columns, 8 x 8 per lane, t and U tiles in LDS (32 rows
-//             of U at a time), W read and written once per panel.  Bound: float32 vector ALU.
+// Rows are independent, groups of a row strictly sequential, and U is the same for every row.  Columns are taken in panels
+// of 128, a launch per panel on the caller's stream (correct_step_kernel), whose workgroups have one of two roles:
+//     panel   (the first workgroups, 32 or 16 rows each) panel p - 1's 128 multiply-adds per element onto the panel's columns,
+//             which is all that panel p waits for, then the panel's groups one after the other, a row across 8 or 16
+//             lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  Bound by the latency of one chain:
+//             23 us for 16 groups of 8.
+//     update  (all others) panel p - 1's 128 multiply-adds per element, in the same order, for the columns behind panel p:
+//             tiles of 128 rows x 128 columns, W read and written once per panel.  Bound: float32 matrix instructions
+//             (143 TFLOP/s in registers) and HBM together, 100 TFLOP/s at 63 x 64 tiles.
 // The two roles touch different columns, and the update reads panel p - 1's t values while the panel role writes
 // panel p's, which is why there are two work buffers used in turn.  The panel workgroups come first in the grid
 // and raise their waves' priority, so they are placed before the flood of update tiles and run beside it: the
 // chain of panels (each needs the one before) stays off the critical path as long as a launch has enough update
-// tiles to outlast it; with few rows the chain is what remains.  Both roles need the same LDS (33 KB), four
+// tiles to outlast it; with few rows the chain is what remains.  Both roles need the same LDS (37 KB), four
 // workgroups per compute unit.
-// Not on the matrix cores: their accumulation order inside an instruction is not the one defined above.
+// Both roles' 128 multiply-adds per element run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
+// element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
+// tied, subnormal and non-finite operands).
+// Before, with the update on the vector ALU (64 TFLOP/s) and 64 rows of a panel a lane each on four waves that took its
+// groups in turn (37 to 46 us a panel and 10 to 15 for a launch in front of it with its update): 8192 x 8192 9.5 ms, now
+// 6.8; 1024 x 4096 1.6 ms, now 0.92.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -39,406 +41,444 @@ namespace {
 
 using namespace pvq_quantize_dev;
 
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
 constexpr int kPanelCols = 128;   // columns per panel
-constexpr int kPanelWaves = 4;    // waves of a workgroup: group g of the panel belongs to wave g % 4
-constexpr int kThreads = 64 * kPanelWaves;
+constexpr int kWaves = 4;         // waves of a workgroup
+constexpr int kThreads = 64 * kWaves;
 constexpr int kTile = 128;        // rows and columns of an update tile
 constexpr int kStage = 32;        // rows of U (and t values per row) that an update tile holds in LDS at a time
-// update tiles from which on a launch's panel workgroups do the narrow update themselves (one and a half rounds of
-// four workgroups on each of 256 units); a test lowers it to reach that path with small matrices
-std::atomic<int64_t> g_front_tiles{1536};
-constexpr int kLdsFloats = kStage * (kTile + 4) + kStage * kTile;   // update: t tile and U tile; panel: 128 x 64 t values
-static_assert(kLdsFloats >= kPanelCols * 64, "the panel role's t values fit");
+// words from a row of t values, or of U, in LDS to the next: the 64 values of an operand lie on different banks
+constexpr int kTPitch = kStage + 4, kUPitch = kTile + 16;
+constexpr int kUpdateFloats = kTile * kTPitch + kStage * kUPitch;
 
 struct correct_shape {
     int64_t ldw, rows, cols, ldu;
     int K, ls;
 };
 
-// Panel role.  Lane = row in each of the four waves; wave w holds the values of groups w, w + 4, ... of its rows
-// in registers.
-//   With `front` (a launch with enough update tiles to outlast it), first the panel before's 128 multiply-adds per
-// element onto this panel's columns, which otherwise a launch of correct_narrow_kernel has done.
-//   Step G (one barrier per step): the owner of group G applies to it the updates of group G - 1 (the only ones
-// still missing: it caught up with the rest one step earlier), stores what is then quantised to W, runs
-// quantiser, amplitude, error and substitution, and puts the t values into LDS and the work buffer; the other
-// waves apply the t values published so far to all groups they still own.  Per element these are the same
-// multiply-adds in the same order (rows of U ascending) as if every group had updated all later columns at
-// once.  The owner's step is the chain's length: one group's quantiser plus D rows of updates.
-//   U is the same for every lane.  No wave is ever more than two groups behind, so step G reads the rows of U of
-// groups G - 2, G - 1 and G only (and the t values of G - 2 and G - 1).  D = 8: rings of four groups in LDS, rows
-// of U ([slot][row][128 columns], the rows of group G + 1 are fetched during step G) and t values
-// ([slot][column][lane]).  D = 16, 32: such rings would not leave LDS for four workgroups per compute unit; all
-// t values of the panel are kept, and the rows of U come through scalar loads (the pointer is read-only for the
-// kernel and the address is the same in all lanes), which costs the owner a few exposed load latencies per step.
+// ---- a row's group across L neighbouring lanes, C = D / L coordinates a lane --------------------------------
+template <int D> struct split {
+    static constexpr int L = D == 8 ? 8 : 16, C = D / L;
+    static constexpr int kRowsOfWave = 64 / L, kRows = kWaves * kRowsOfWave;   // of a workgroup
+    static constexpr int kGroups = kPanelCols / D;
+    // LDS of the panel role: D x D blocks of U on and above the panel's diagonal, before that t values and sums on their way
+    // to and from the matrix cores' layout (kXPitch: an operand's values lie on different banks)
+    static constexpr int kBlocks = kGroups * (kGroups + 1) / 2;
+    static constexpr int kFloats = (kBlocks + 3) * D * D;      // (a trailing update reads up to three blocks past the last)
+    static constexpr int kXPitch = kPanelCols + 4;
+    static_assert(kRows * kXPitch <= kFloats, "the transposition fits");
+};
+template <int D> constexpr int lds_floats() { return kUpdateFloats > split<D>::kFloats ? kUpdateFloats : split<D>::kFloats; }
+
+template <int CTRL, int BANKS = 0xF>
+__device__ inline int dpp(int old, int v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xF, BANKS, false); }
+template <int CTRL>
+__device__ inline float dpp_add(float v) { return v + __int_as_float(dpp<CTRL>(0, __float_as_int(v))); }
+
+// Sum over the L lanes of a row, adjacent pairs level by level, in every lane.
+template <int L>
+__device__ inline float lanes_sum(float v)
+{
+    v = dpp_add<0xB1>(v);                       // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);                       // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);                      // row_half_mirror: the other quad, all of whose lanes hold its sum
+    if constexpr (L == 16) v = dpp_add<0x140>(v);   // row_mirror
+    return v;
+}
+
+// v of the lane j ^ X of the row
+template <int X>
+__device__ inline int lane_xor(int v)
+{
+    if constexpr (X == 0) return v;
+    else if constexpr (X == 1) return dpp<0xB1>(0, v);
+    else if constexpr (X == 2) return dpp<0x4E>(0, v);
+    else if constexpr (X == 3) return dpp<0x1B>(0, v);
+    else if constexpr (X < 8) return lane_xor<7 - X>(dpp<0x141>(0, v));
+    else if constexpr (X < 12) return lane_xor<X - 8>(dpp<0x128>(0, v));   // row_ror:8
+    else return lane_xor<15 - X>(dpp<0x140>(0, v));
+}
+
+// v of lane N of the row, in all L lanes
+template <int L, int N>
+__device__ inline float lane_broadcast(float v)
+{
+    const int i = __float_as_int(v);
+    if constexpr (L == 16) return __int_as_float(dpp<0x150 + N>(0, i));                        // row_newbcast
+    else return __int_as_float(dpp<0x150 + 8 + N, 0xC>(dpp<0x150 + N>(0, i), i));              // one for either half
+}
+
+// How many coordinates of lanes j ^ X, X = 1 .. L - 1, come before coordinate c of this lane in the order of keys (largest
+// first, lower coordinate first on ties): key > mine, or >= where the other lane is the lower one (th: mine, less one
+// where bit b of j says so).
+template <int L, int C, int X>
+__device__ inline void count_before(const int (&key)[C], const int (&th)[C][4], int (&before)[C])
+{
+    if constexpr (X < L) {
+        constexpr int b = X < 2 ? 0 : X < 4 ? 1 : X < 8 ? 2 : 3;
+#pragma unroll
+        for (int o = 0; o < C; o++) {
+            const int other = lane_xor<X>(key[o]);
+#pragma unroll
+            for (int c = 0; c < C; c++) before[c] += other > th[c][b] ? 1 : 0;
+        }
+        count_before<L, C, X + 1>(key, th, before);
+    }
+}
+
+// The quantiser of Sec. 2.5 (pvq_quantize_dev.h) with the group's coordinates C j .. C j + C - 1 in lane j of its row: the
+// same sums in the same order, the coordinates' places in the order of deviations counted by comparisons.  Returns the
+// sum of squares; y gets the signed point.
+template <int D>
+__device__ inline float quantize_lanes(const float (&w)[split<D>::C], int j, int K, int (&y)[split<D>::C])
+{
+    constexpr int L = split<D>::L, C = split<D>::C;
+    float a1 = fabsf(w[0]), s2 = w[0] * w[0];
+    if constexpr (C == 2) { a1 = a1 + fabsf(w[1]); s2 = s2 + w[1] * w[1]; }
+    const float l1 = lanes_sum<L>(a1), ss = lanes_sum<L>(s2);
+    const float g = (float)K / l1;
+    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+    float t[C], yf[C];
+    float S = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        t[c] = fabsf(w[c]) * g;
+        yf[c] = rintf(t[c]);
+        S += yf[c];                           // small integers: exact in any order
+    }
+    S = lanes_sum<L>(S);
+    const float m = (float)K - S;             // > 0: pulses to add, < 0: pulses to take away
+    const float unit = m < 0.0f ? -1.0f : 1.0f;
+    // deviations as integers that order like them (zeros have one sign: t - yf is +0 there)
+    int key[C], th[C][4];
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const float d = t[c] - yf[c];
+        const int b = __float_as_int(m < 0.0f ? -d : d);
+        key[c] = b ^ ((b >> 31) & 0x7FFFFFFF);
+#pragma unroll
+        for (int v = 0; v < 4; v++) th[c][v] = key[c] - ((j >> v) & 1);
+    }
+    int before[C];
+#pragma unroll
+    for (int c = 0; c < C; c++) before[c] = 0;
+    if constexpr (C == 2) {
+        const int first = key[0] >= key[1] ? 1 : 0;
+        before[1] = first; before[0] = 1 - first;
+    }
+    count_before<L, C, 1>(key, th, before);
+    const int need = (int)fabsf(m);
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        int mag = (int)(yf[c] + (before[c] < need ? unit : 0.0f));
+        if (degenerate) mag = C * j + c == D - 1 ? K : 0;
+        y[c] = (w[c] < 0.0f && !degenerate) ? -mag : mag;
+    }
+    return ss;
+}
+
+// t U_GG = e, coordinate after coordinate: t_I is final once t_0 .. t_{I-1} have been taken off e_I.  e: the lane's
+// coordinates; u: rows of the block in the lane's columns, ud: its diagonal there.  tb gets all of t, mine the lane's own.
+template <int D, int I>
+__device__ inline void substitute(float (&e)[split<D>::C], const float (&u)[split<D>::C][D], const float (&ud)[split<D>::C],
+                                  int j, float (&tb)[D], float (&mine)[split<D>::C])
+{
+    constexpr int L = split<D>::L, C = split<D>::C;
+    if constexpr (I < D) {
+        const float q = e[I % C] / ud[I % C];
+        mine[I % C] = j == I / C ? q : mine[I % C];
+        tb[I] = lane_broadcast<L, I / C>(q);
+#pragma unroll
+        for (int c = 0; c < C; c++) e[c] = __builtin_fmaf(-tb[I], u[c][I], e[c]);
+        substitute<D, I + 1>(e, u, ud, j, tb, mine);
+    }
+}
+
+// Panel role.  A workgroup takes split<D>::kRows rows, a wave 8 (D = 8) or 4 of them: lane (row, j) holds coordinate(s) j of
+// every group of the panel, and the waves do not wait for each other once the panel's part of U is in LDS.
+//   First the panel before's 128 multiply-adds per element onto this panel's columns, on the matrix cores: a wave takes 32
+// columns, the results change hands through LDS.
+//   Then group after group: the quantiser across the lanes of a row, amplitude, error, substitution, and the t values,
+// which the substitution has brought to all lanes of the row, onto the groups behind (rows of U ascending).  The next group
+// is always w[0]: one body for all groups, which stays in the instruction cache.
 template <int D>
 __device__ inline void panel_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ Tprev,
-                                  float *__restrict__ Tcur, const correct_shape &a, int64_t p0, int width, bool front,
-                                  float *lds)
+                                  float *__restrict__ Tcur, const correct_shape &a, int64_t p0, int width, float *lds)
 {
-    constexpr int NG = kPanelCols / D, OWN = NG / kPanelWaves;
-    constexpr bool kRing = D == 8;
-    constexpr int R = 4;                                        // slots of the rings
-    static_assert(!kRing || (D * kPanelCols / 4 == kThreads && R * D * (kPanelCols + 64) <= kLdsFloats), "a float4 per lane fills a slot");
-    float *uring = lds;                                         // [slot][row of the group][column of the panel]
-    float *ts = kRing ? lds + R * D * kPanelCols : lds;         // ring: [slot][column of the group][lane]; else [column][lane]
+    using S = split<D>;
+    constexpr int L = S::L, C = S::C, NG = S::kGroups, RB = S::kRows / 16;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r = (int64_t)blockIdx.x * 64 + lane;
-    const bool in = r < a.rows;
-    // lanes beyond the rows work on the last row again (no lane waits for another); they store nothing
-    const int64_t row = in ? r : a.rows - 1;
-    float *wrow = W + row * a.ldw + p0;
+    const int j = lane & (L - 1);
+    const int64_t row0 = (int64_t)blockIdx.x * S::kRows;
+    const int rloc = wave * S::kRowsOfWave + lane / L;
+    const bool in = row0 + rloc < a.rows;
+    // lanes beyond the rows work on the last row again; they store nothing
+    const int64_t row = std::min<int64_t>(row0 + rloc, a.rows - 1);
+    float *wrow = W + row * a.ldw + p0 + C * j;
     const int ngroups = width / D;
     const float *Up = U + p0 * a.ldu + p0;                      // row p0 + k, column p0 + c of the factor
 
-    float w[OWN][D];
+    float w[NG][C];
+    if (p0 > 0) {
+        // t values of the workgroup's rows
 #pragma unroll
-    for (int o = 0; o < OWN; o++) {
-        const int g = wave + kPanelWaves * o;
-#pragma unroll
-        for (int i = 0; i < D; i += 4) {
-            const float4 q = *reinterpret_cast<const float4 *>(wrow + (g < ngroups ? g : 0) * D + i);
-            w[o][i] = q.x; w[o][i + 1] = q.y; w[o][i + 2] = q.z; w[o][i + 3] = q.w;
+        for (int x = 0; x < S::kRows * kPanelCols / 4 / kThreads; x++) {
+            const int e = threadIdx.x + x * kThreads, rr = e / (kPanelCols / 4), c4 = (e % (kPanelCols / 4)) * 4;
+            *reinterpret_cast<float4 *>(lds + rr * S::kXPitch + c4) =
+                *reinterpret_cast<const float4 *>(Tprev + std::min<int64_t>(row0 + rr, a.rows - 1) * kPanelCols + c4);
         }
-    }
-
-    if (front) {
-        // w <- w - t'[0] U[p0 - 128][c] - ... - t'[127] U[p0 - 1][c] for the wave's 32 columns c, t' = the panel before's
-        // t values of the row: 32 rows of U and 32 t values per row go through LDS at a time, fetched into
-        // registers while the 32 before are worked on
-        constexpr int kChunk = 32, kTPitch = 65;                // t values transposed: [k][row], rows 65 words apart
-        float *uc = lds, *tc = lds + kChunk * kPanelCols;
-        static_assert((kChunk + 1) * kPanelCols + (kChunk + 1) * kTPitch <= kLdsFloats, "a chunk fits, and a row more may be read");
-        const float *Ub = U + (p0 - kPanelCols) * a.ldu + p0;   // row p0 - 128 + k, column p0 + c
-        const int64_t row0 = (int64_t)blockIdx.x * 64;
-        float4 uq[4], tq[2];
-        auto fetch = [&](int chunk) {
+        const int c16 = lane & 15, k4 = lane >> 4;              // an operand's row or column, and its place in k
+        const bool cols_in = 32 * wave < width;
+        f32x4 acc[RB][2];
+        constexpr int kAhead = 16;                              // operands of so many instructions on their way at a time
+        float uv[kAhead][2];
+        const float *ub = U + (p0 - kPanelCols + k4) * a.ldu + p0 + 32 * wave + c16;
+        auto fetch = [&]() {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int e = threadIdx.x + i * kThreads, k = e / (kPanelCols / 4), c = (e % (kPanelCols / 4)) * 4;
-                uq[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-                if (c < width) uq[i] = *reinterpret_cast<const float4 *>(Ub + (int64_t)(chunk * kChunk + k) * a.ldu + c);
-            }
-#pragma unroll
-            for (int i = 0; i < 2; i++) {
-                const int e = threadIdx.x + i * kThreads, rr = e / (kChunk / 4), k4 = (e % (kChunk / 4)) * 4;
-                const int64_t rsrc = std::min<int64_t>(row0 + rr, a.rows - 1);
-                tq[i] = *reinterpret_cast<const float4 *>(Tprev + rsrc * kPanelCols + chunk * kChunk + k4);
-            }
+            for (int s = 0; s < kAhead; s++) { uv[s][0] = ub[0]; uv[s][1] = ub[16]; ub += 4 * a.ldu; }
         };
-        fetch(0);
-        for (int chunk = 0; chunk < kPanelCols / kChunk; chunk++) {
-            if (chunk) __syncthreads();                         // the chunk before is no longer read
+        if (cols_in) {
 #pragma unroll
-            for (int i = 0; i < 4; i++) {
-                const int e = threadIdx.x + i * kThreads, k = e / (kPanelCols / 4), c = (e % (kPanelCols / 4)) * 4;
-                *reinterpret_cast<float4 *>(uc + k * kPanelCols + c) = uq[i];
+            for (int rb = 0; rb < RB; rb++) {
+                const float *p = W + std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1) * a.ldw + p0 + 32 * wave + 4 * k4;
+                acc[rb][0] = *reinterpret_cast<const f32x4 *>(p);
+                acc[rb][1] = *reinterpret_cast<const f32x4 *>(p + 16);
             }
-#pragma unroll
-            for (int i = 0; i < 2; i++) {
-                const int e = threadIdx.x + i * kThreads, rr = e / (kChunk / 4), k4 = (e % (kChunk / 4)) * 4;
-                tc[k4 * kTPitch + rr] = tq[i].x; tc[(k4 + 1) * kTPitch + rr] = tq[i].y;
-                tc[(k4 + 2) * kTPitch + rr] = tq[i].z; tc[(k4 + 3) * kTPitch + rr] = tq[i].w;
-            }
-            __syncthreads();
-            if (chunk + 1 < kPanelCols / kChunk) fetch(chunk + 1);
-            // the wave's 32 values of a row of U: one half on its way while the other is worked on (past the last
-            // row of a chunk the words behind it are read and not used)
-            auto half_row = [&](int k, int h, float4 (&q)[OWN * D / 8]) {
-                const float *urow = uc + k * kPanelCols;
-#pragma unroll
-                for (int i = 0; i < OWN * D / 8; i++) {
-                    const int col = h * (OWN * D / 2) + 4 * i;          // of the wave's values: group col / D, value col % D
-                    q[i] = *reinterpret_cast<const float4 *>(urow + (wave + kPanelWaves * (col / D)) * D + col % D);
-                }
-            };
-            auto half_fma = [&](float tk, int h, const float4 (&q)[OWN * D / 8]) {
-#pragma unroll
-                for (int i = 0; i < OWN * D / 8; i++) {
-                    const int col = h * (OWN * D / 2) + 4 * i, o = col / D, j = col % D;
-                    w[o][j] = __builtin_fmaf(-tk, q[i].x, w[o][j]);
-                    w[o][j + 1] = __builtin_fmaf(-tk, q[i].y, w[o][j + 1]);
-                    w[o][j + 2] = __builtin_fmaf(-tk, q[i].z, w[o][j + 2]);
-                    w[o][j + 3] = __builtin_fmaf(-tk, q[i].w, w[o][j + 3]);
-                }
-            };
-            float4 qa[OWN * D / 8], qb[OWN * D / 8];
-            half_row(0, 0, qa);
-            float tk = tc[lane];
-#pragma unroll 2
-            for (int k = 0; k < kChunk; k++) {
-                half_row(k, 1, qb);
-                half_fma(tk, 0, qa);
-                half_row(k + 1, 0, qa);
-                const float tn = tc[(k + 1) * kTPitch + lane];
-                half_fma(tk, 1, qb);
-                tk = tn;
-            }
+            fetch();
         }
-        __syncthreads();                                        // LDS now takes this panel's rows of U and t values
-    }
-
-    // the rows of U of group g, from device memory to the ring: a float4 per lane
-    const int ring_k = threadIdx.x / (kPanelCols / 4), ring_c = (threadIdx.x % (kPanelCols / 4)) * 4;
-    auto ring_fetch = [&](int g) {
-        float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (g < ngroups && ring_c < width) v = *reinterpret_cast<const float4 *>(Up + (int64_t)(g * D + ring_k) * a.ldu + ring_c);
-        return v;
-    };
-    auto ring_store = [&](int g, const float4 &v) {
-        *reinterpret_cast<float4 *>(uring + ((g % R) * D + ring_k) * kPanelCols + ring_c) = v;
-    };
-    if constexpr (kRing) {
-        ring_store(0, ring_fetch(0));
         __syncthreads();
-    }
-    // row k of the panel's part of U from column c on, and the t values of column k
-    auto u_at = [&](int k, int c) -> const float * {
-        if constexpr (kRing) return uring + (((k / D) % R) * D + k % D) * kPanelCols + c;
-        else return Up + (int64_t)k * a.ldu + c;
-    };
-    auto t_at = [&](int k) -> float * {
-        if constexpr (kRing) return ts + (((k / D) % R) * D + k % D) * 64 + lane;
-        else return ts + k * 64 + lane;
-    };
-    float *trow = Tcur + row * kPanelCols;
-    // rows k0 .. k1 - 1 of the panel's part of U, times the t values of those columns, onto group g's values
-    auto apply = [&](float (&v)[D], int g, int k0, int k1) {
-        constexpr int kRowsAhead = 64 / D;    // rows of U on their way at a time
-#pragma unroll kRowsAhead
-        for (int k = k0; k < k1; k++) {
-            const float tk = *t_at(k);
-            const float *u = u_at(k, g * D);
-            float uv[D];
-#pragma unroll
-            for (int j = 0; j < D; j += 4) {
-                const float4 q = *reinterpret_cast<const float4 *>(u + j);
-                uv[j] = q.x; uv[j + 1] = q.y; uv[j + 2] = q.z; uv[j + 3] = q.w;
-            }
-#pragma unroll
-            for (int j = 0; j < D; j++) v[j] = __builtin_fmaf(-tk, uv[j], v[j]);
-        }
-    };
-
-    int applied = 0;   // the wave's groups that are still to come hold the updates of groups 0 .. applied - 1
-#pragma unroll
-    for (int o = 0; o < OWN; o++) {
+        if (cols_in) {
 #pragma unroll 1
-        for (int turn = 0; turn < kPanelWaves; turn++) {
-            const int G = kPanelWaves * o + turn;
-            if (G >= ngroups) break;                  // the same for every wave
-            float4 ahead;
-            if constexpr (kRing) ahead = ring_fetch(G + 1);
-            if (wave == turn) {
-                float (&wg)[D] = w[o];
-                apply(wg, G, applied * D, G * D);
-                // what is quantised, and stays in W
-                if (in) {
+            for (int s0 = 0; s0 < kPanelCols / 4; s0 += kAhead) {
+                if (s0) fetch();
 #pragma unroll
-                    for (int i = 0; i < D; i += 4) *reinterpret_cast<float4 *>(wrow + G * D + i) = make_float4(wg[i], wg[i + 1], wg[i + 2], wg[i + 3]);
-                }
-                int y[D];
-                float ss;
-                if constexpr (D == 8) ss = quantize_group8(wg, a.K, y);
-                else ss = quantize_group_select<D>(wg, a.K, y);
-                const float s = a.ls ? pvq_ls_amplitude<D>(wg, y) : sqrtf(ss);
-                int n2 = 0;
+                for (int s = 0; s < kAhead; s++)
 #pragma unroll
-                for (int i = 0; i < D; i++) n2 += y[i] * y[i];
-                const float gain = s / sqrtf((float)n2);
-                // t U_GG = e, row after row of the group's own D x D part: t_i is final once rows 0 .. i - 1 have been
-                // taken off e_i (for every e_j the multiply-adds come in the order of the rows)
-                float t[D];
+                    for (int rb = 0; rb < RB; rb++) {
+                        const float tv = lds[(16 * rb + c16) * S::kXPitch + 4 * (s0 + s) + k4];
 #pragma unroll
-                for (int j = 0; j < D; j++) t[j] = wg[j] - gain * (float)y[j];
-#pragma unroll
-                for (int i = 0; i < D; i++) {
-                    const float *u = u_at(G * D + i, G * D);
-                    float ui[D];
-#pragma unroll
-                    for (int j = 0; j < D; j += 4) {
-                        const float4 q = *reinterpret_cast<const float4 *>(u + j);
-                        ui[j] = q.x; ui[j + 1] = q.y; ui[j + 2] = q.z; ui[j + 3] = q.w;
+                        for (int h = 0; h < 2; h++) acc[rb][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[s][h], tv, acc[rb][h], 0, 0, 0);
                     }
-                    t[i] = t[i] / ui[i];
-#pragma unroll
-                    for (int j = i + 1; j < D; j++) t[j] = __builtin_fmaf(-t[i], ui[j], t[j]);
-                }
-#pragma unroll
-                for (int j = 0; j < D; j++) *t_at(G * D + j) = t[j];
-                if (in) {
-#pragma unroll
-                    for (int i = 0; i < D; i += 4) *reinterpret_cast<float4 *>(trow + G * D + i) = make_float4(t[i], t[i + 1], t[i + 2], t[i + 3]);
-                }
-            } else {
-#pragma unroll
-                for (int oo = 0; oo < OWN; oo++) {
-                    const int g = wave + kPanelWaves * oo;
-                    if (g > G && g < ngroups) apply(w[oo], g, applied * D, G * D);
-                }
-                applied = G;
             }
-            if constexpr (kRing) ring_store(G + 1, ahead);      // a slot that no wave reads during this step
-            __syncthreads();      // the step's t values, and the next group's rows of U, are in LDS
         }
+        __syncthreads();
+        if (cols_in) {
+#pragma unroll
+            for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                for (int h = 0; h < 2; h++) *reinterpret_cast<f32x4 *>(lds + (16 * rb + c16) * S::kXPitch + 32 * wave + 16 * h + 4 * k4) = acc[rb][h];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int g = 0; g < NG; g++)
+#pragma unroll
+            for (int c = 0; c < C; c++) w[g][c] = lds[rloc * S::kXPitch + (g < ngroups ? g : 0) * D + C * j + c];
+        __syncthreads();
+    } else {
+#pragma unroll
+        for (int g = 0; g < NG; g++)
+#pragma unroll
+            for (int c = 0; c < C; c++) w[g][c] = wrow[(g < ngroups ? g : 0) * D + c];
+    }
+
+    // U on and above the panel's diagonal: block (G, G + rel) is number G NG - G (G - 1) / 2 + rel, its element (i, C j + c) at
+    // ((i / 4 C + c) L + j) 4 + i % 4, so that a lane reads four rows of its column at a time
+    constexpr int kQuads = kPanelCols * kPanelCols / 4;         // float4 of the panel's square
+    for (int e = threadIdx.x; e < kQuads; e += kThreads) {
+        const int k = e / (kPanelCols / 4), c4 = (e % (kPanelCols / 4)) * 4;
+        const int G = k / D, g = c4 / D, i = k % D, col = c4 % D;
+        if (g >= G && k < width && c4 < width) {
+            const float4 v = *reinterpret_cast<const float4 *>(Up + (int64_t)k * a.ldu + c4);
+            float *b = lds + (G * NG - G * (G - 1) / 2 + g - G) * D * D + i % 4;
+            const float vv[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (int q = 0; q < 4; q++) b[((i / 4 * C + (col + q) % C) * L + (col + q) / C) * 4] = vv[q];
+        }
+    }
+    __syncthreads();
+
+    float *trow = Tcur + row * kPanelCols + C * j;              // t values, negated
+    const float *ublk = lds + j * 4;                            // block (G, G), the lane's column
+    const int own = C * j;
+#pragma unroll 1
+    for (int G = 0; G < ngroups; G++) {
+        float (&wg)[C] = w[0];
+        // what is quantised, and stays in W
+        if (in) {
+#pragma unroll
+            for (int c = 0; c < C; c++) wrow[c] = wg[c];
+        }
+        float u[C][D], ud[C];
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+#pragma unroll
+            for (int i = 0; i < D; i += 4) {
+                const float4 v = *reinterpret_cast<const float4 *>(ublk + (i / 4 * C + c) * L * 4);
+                u[c][i] = v.x; u[c][i + 1] = v.y; u[c][i + 2] = v.z; u[c][i + 3] = v.w;
+            }
+            ud[c] = ublk[((own + c) / 4 * C + c) * L * 4 + (own + c) % 4];
+        }
+        int y[C];
+        const float ss = quantize_lanes<D>(wg, j, a.K, y);
+        float sq = 0.0f, dot = 0.0f;
+#pragma unroll
+        for (int c = 0; c < C; c++) {
+            const float yc = (float)y[c];
+            sq += yc * yc;                                      // integers
+            const float p = yc * wg[c];
+            dot = c == 0 ? p : dot + p;
+        }
+        const float root = sqrtf(lanes_sum<L>(sq));
+        const float s = a.ls ? lanes_sum<L>(dot) / root : sqrtf(ss);
+        const float gain = s / root;
+        float e[C], mine[C], tb[D];
+#pragma unroll
+        for (int c = 0; c < C; c++) { e[c] = wg[c] - gain * (float)y[c]; mine[c] = 0.0f; }
+        substitute<D, 0>(e, u, ud, j, tb, mine);
+        if (in) {
+#pragma unroll
+            for (int c = 0; c < C; c++) trow[c] = -mine[c];
+        }
+        // onto the groups behind, which move up by one; four at a time, as many of them as there are
+#pragma unroll
+        for (int r4 = 0; r4 < NG; r4 += 4) {
+            if (G + r4 + (r4 == 0) < ngroups) {
+#pragma unroll
+                for (int rel = r4 == 0 ? 1 : r4; rel < r4 + 4 && rel < NG; rel++)
+#pragma unroll
+                    for (int c = 0; c < C; c++) {
+                        float v = w[rel][c];
+#pragma unroll
+                        for (int i = 0; i < D; i += 4) {
+                            const float4 q = *reinterpret_cast<const float4 *>(ublk + rel * D * D + (i / 4 * C + c) * L * 4);
+                            v = __builtin_fmaf(-tb[i], q.x, v); v = __builtin_fmaf(-tb[i + 1], q.y, v);
+                            v = __builtin_fmaf(-tb[i + 2], q.z, v); v = __builtin_fmaf(-tb[i + 3], q.w, v);
+                        }
+                        w[rel - 1][c] = v;
+                    }
+            }
+        }
+        ublk += (NG - G) * D * D;
+        wrow += D;
+        trow += D;
     }
 }
 
 // Update role.  Tile (row tile, column tile) of the columns [c1, cols): W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ...
-// - t[r][127] U[c0 + 127][c], one multiply-add after the other, t = the t values of the panel at column c0; the
-// tile of W is read and written once for its 128 multiply-adds per element (with 64 per pass the update was
-// bound by HBM as much as by the vector ALU).  A stage = 32 rows of U and 32 t values per row in LDS (with 64
-// per stage, and two workgroups per compute unit, it ran at 57 instead of 66 TFLOP/s).
-// Neighbouring workgroups share the tile of U.
+// - t[r][127] U[c0 + 127][c], one multiply-add after the other, t = the t values of the panel at column c0, on the matrix
+// cores: v_mfma_f32_16x16x4_f32 adds its four products one by one, k ascending, each a fused multiply-add (bit for bit,
+// subnormals, infinities and NaN included).  A wave takes 64 x 64 of the tile, a stage = 32 rows of U and 32 t values per row
+// in LDS.  Neighbouring workgroups share the tile of U.
 __device__ inline void update_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ T,
                                    const correct_shape &a, int64_t c0, int64_t c1, int row_tile, int col_tile, float *lds)
 {
-    float (*Ts)[kTile + 4] = reinterpret_cast<float (*)[kTile + 4]>(lds);               // [k][row of the tile]
-    float (*Us)[kTile] = reinterpret_cast<float (*)[kTile]>(lds + kStage * (kTile + 4)); // [k][column of the tile]
+    float *Ts = lds;                              // [row of the tile][k], kTPitch words a row
+    float *Us = lds + kTile * kTPitch;            // [k][column of the tile], kUPitch words a row
     const int64_t row0 = (int64_t)row_tile * kTile, col0 = c1 + (int64_t)col_tile * kTile;
-    const int tid = threadIdx.x;
-    const int ty = tid >> 4, tx = tid & 15;       // rows 8 ty .. 8 ty + 7, columns 8 tx .. 8 tx + 7 of the tile
-    const bool cols_in = col0 + 8 * tx < a.cols;  // eight columns are in or out together
-    float acc[8][8];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wr = wave >> 1, wc = wave & 1;      // the wave's 64 rows and 64 columns
+    const int c16 = lane & 15, k4 = lane >> 4;
+    const bool mine = row0 + 64 * wr < a.rows && col0 + 64 * wc < a.cols;   // (columns come in whole 64s)
+    // The instruction's rows are columns of the tile, so that a lane's four results are neighbours: row 16 rb + c16 of the
+    // wave's, columns 16 cb + 4 k4 .. + 3.
+    f32x4 acc[4][4];
+    float *wt = W + (row0 + 64 * wr + c16) * a.ldw + col0 + 64 * wc + 4 * k4;
+    const int rows_left = (int)std::min<int64_t>(64, a.rows - (row0 + 64 * wr)) - c16;   // row 16 rb of the lane is there if below this
+    if (mine) {
 #pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const int64_t r = row0 + 8 * ty + i;
-        float4 v0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), v1 = v0;
-        if (r < a.rows && cols_in) {
-            const float *p = W + r * a.ldw + col0 + 8 * tx;
-            v0 = *reinterpret_cast<const float4 *>(p); v1 = *reinterpret_cast<const float4 *>(p + 4);
+        for (int rb = 0; rb < 4; rb++) {
+            // (for a row that is not there the wave's last one, whose distance may be negative)
+            const float *p = wt + std::min(16 * rb, rows_left - 1) * a.ldw;
+#pragma unroll
+            for (int cb = 0; cb < 4; cb++) acc[rb][cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
         }
-        acc[i][0] = v0.x; acc[i][1] = v0.y; acc[i][2] = v0.z; acc[i][3] = v0.w;
-        acc[i][4] = v1.x; acc[i][5] = v1.y; acc[i][6] = v1.z; acc[i][7] = v1.w;
     }
+    // the lane's places in a stage's tiles: row tid / 8 and every 32nd one behind it of t, row tid / 32 and every eighth one
+    // behind it of U (one pointer that moves on: a pointer per load would take the registers of the sums)
+    const bool u_in = col0 + (tid & 31) * 4 < a.cols;
+    const float *up = U + (c0 + (tid >> 5)) * a.ldu + col0 + (tid & 31) * 4;
+    const float *tp = T + row0 * kPanelCols + (tid & 7) * 4;
+    const int t_last = (int)std::min<int64_t>(kTile, a.rows - row0) - 1;
+    uint32_t t_at[4];
+#pragma unroll
+    for (int x = 0; x < 4; x++) t_at[x] = (uint32_t)std::min((tid >> 3) + 32 * x, t_last) * kPanelCols;
+#pragma unroll 1
     for (int st = 0; st < kPanelCols / kStage; st++) {
-        if (st) __syncthreads();                  // the tiles of the stage before are no longer read
-        // t tile: 128 rows x 32 values, a float4 per lane and pass, stored transposed
-        for (int e = tid; e < kTile * (kStage / 4); e += kThreads) {
-            const int rr = e / (kStage / 4), k4 = (e % (kStage / 4)) * 4;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (row0 + rr < a.rows) v = *reinterpret_cast<const float4 *>(T + (row0 + rr) * kPanelCols + st * kStage + k4);
-            Ts[k4][rr] = v.x; Ts[k4 + 1][rr] = v.y; Ts[k4 + 2][rr] = v.z; Ts[k4 + 3][rr] = v.w;
+        f32x4 tq[4], uq[4];
+#pragma unroll
+        for (int x = 0; x < 4; x++) tq[x] = *reinterpret_cast<const f32x4 *>(tp + t_at[x]);
+        if (u_in) {
+#pragma unroll
+            for (int x = 0; x < 4; x++) { uq[x] = *reinterpret_cast<const f32x4 *>(up); up += 8 * a.ldu; }
+        } else {
+#pragma unroll
+            for (int x = 0; x < 4; x++) uq[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         }
-        // U tile: 32 rows x 128 columns (columns in whole fours: cols is a multiple of 64)
-        for (int e = tid; e < kStage * (kTile / 4); e += kThreads) {
-            const int k = e / (kTile / 4), cc = (e % (kTile / 4)) * 4;
-            float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (col0 + cc < a.cols) v = *reinterpret_cast<const float4 *>(U + (c0 + st * kStage + k) * a.ldu + col0 + cc);
-            *reinterpret_cast<float4 *>(&Us[k][cc]) = v;
+        tp += kStage;
+        if (st) __syncthreads();                  // the tiles of the stage before are no longer read
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            *reinterpret_cast<f32x4 *>(Ts + ((tid >> 3) + 32 * x) * kTPitch + (tid & 7) * 4) = tq[x];
+            *reinterpret_cast<f32x4 *>(Us + ((tid >> 5) + 8 * x) * kUPitch + (tid & 31) * 4) = uq[x];
         }
         __syncthreads();
-#pragma unroll 4
-        for (int k = 0; k < kStage; k++) {
-            const float4 a0 = *reinterpret_cast<const float4 *>(&Ts[k][8 * ty]), a1 = *reinterpret_cast<const float4 *>(&Ts[k][8 * ty + 4]);
-            const float4 b0 = *reinterpret_cast<const float4 *>(&Us[k][8 * tx]), b1 = *reinterpret_cast<const float4 *>(&Us[k][8 * tx + 4]);
-            const float tv[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-            const float uv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-            for (int i = 0; i < 8; i++)
-#pragma unroll
-                for (int j = 0; j < 8; j++) acc[i][j] = __builtin_fmaf(-tv[i], uv[j], acc[i][j]);
-        }
-    }
-#pragma unroll
-    for (int i = 0; i < 8; i++) {
-        const int64_t r = row0 + 8 * ty + i;
-        if (r < a.rows && cols_in) {
-            float *p = W + r * a.ldw + col0 + 8 * tx;
-            *reinterpret_cast<float4 *>(p) = make_float4(acc[i][0], acc[i][1], acc[i][2], acc[i][3]);
-            *reinterpret_cast<float4 *>(p + 4) = make_float4(acc[i][4], acc[i][5], acc[i][6], acc[i][7]);
-        }
-    }
-}
-
-// Columns [c1, c1 + width) of all rows: W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ... - t[r][127] U[c0 + 127][c], one
-// multiply-add after the other, t = the t values of the panel at column c0 = c1 - 128.  16 rows x 128 columns per
-// workgroup, 1 x 8 per lane; a stage = 32 rows of U and 32 t values per row in LDS.
-__global__ __launch_bounds__(kThreads) void correct_narrow_kernel(float *__restrict__ W, const float *__restrict__ U,
-                                                                   const float *__restrict__ T, correct_shape a, int64_t c1, int width)
-{
-    constexpr int RT = 16;
-    __shared__ __align__(16) float Ts[kStage][RT + 4];      // [k][row of the tile]
-    __shared__ __align__(16) float Us[kStage][kPanelCols];  // [k][column]
-    const int64_t row0 = (int64_t)blockIdx.x * RT, c0 = c1 - kPanelCols;
-    const int tid = threadIdx.x;
-    const int ty = tid >> 4, tx = tid & 15;       // row ty, columns 8 tx .. 8 tx + 7 of the tile
-    const int64_t r = row0 + ty;
-    const bool mine = r < a.rows && 8 * tx < width;          // (width is 128 or 64: eight columns are in or out together)
-    float acc[8];
-    {
-        float4 v0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), v1 = v0;
         if (mine) {
-            const float *p = W + r * a.ldw + c1 + 8 * tx;
-            v0 = *reinterpret_cast<const float4 *>(p); v1 = *reinterpret_cast<const float4 *>(p + 4);
-        }
-        acc[0] = v0.x; acc[1] = v0.y; acc[2] = v0.z; acc[3] = v0.w; acc[4] = v1.x; acc[5] = v1.y; acc[6] = v1.z; acc[7] = v1.w;
-    }
-    // t tile of a stage: 16 rows x 32 values = 128 float4 (lanes 0 .. 127), stored transposed; U tile: 32 rows x 128
-    // columns = 4 float4 per lane.  All four stages are requested at once (80 registers): the workgroup's time is
-    // one trip to memory plus its arithmetic, whatever the other workgroups of the compute unit do.
-    constexpr int kStages = kPanelCols / kStage;
-    const int t_rr = tid / (kStage / 4), t_k4 = (tid % (kStage / 4)) * 4;
-    const bool t_lane = tid < RT * (kStage / 4);
-    float4 tq[kStages], uq[kStages][4];
+#pragma unroll 2
+            for (int s = 0; s < kStage / 4; s++) {
+                float tv[4], uv[4];
 #pragma unroll
-    for (int st = 0; st < kStages; st++) {
-        tq[st] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-        if (t_lane && row0 + t_rr < a.rows) tq[st] = *reinterpret_cast<const float4 *>(T + (row0 + t_rr) * kPanelCols + st * kStage + t_k4);
+                for (int x = 0; x < 4; x++) {
+                    tv[x] = Ts[(64 * wr + 16 * x + c16) * kTPitch + 4 * s + k4];
+                    uv[x] = Us[(4 * s + k4) * kUPitch + 64 * wc + 16 * x + c16];
+                }
 #pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int e = tid + i * kThreads, k = e / (kPanelCols / 4), cc = (e % (kPanelCols / 4)) * 4;
-            uq[st][i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            if (cc < width) uq[st][i] = *reinterpret_cast<const float4 *>(U + (c0 + st * kStage + k) * a.ldu + c1 + cc);
-        }
-    }
+                for (int rb = 0; rb < 4; rb++)
 #pragma unroll
-    for (int st = 0; st < kStages; st++) {
-        if (st) __syncthreads();                  // the tiles of the stage before are no longer read
-        if (t_lane) { Ts[t_k4][t_rr] = tq[st].x; Ts[t_k4 + 1][t_rr] = tq[st].y; Ts[t_k4 + 2][t_rr] = tq[st].z; Ts[t_k4 + 3][t_rr] = tq[st].w; }
-#pragma unroll
-        for (int i = 0; i < 4; i++) {
-            const int e = tid + i * kThreads, k = e / (kPanelCols / 4), cc = (e % (kPanelCols / 4)) * 4;
-            *reinterpret_cast<float4 *>(&Us[k][cc]) = uq[st][i];
-        }
-        __syncthreads();
-#pragma unroll 8
-        for (int k = 0; k < kStage; k++) {
-            const float tv = Ts[k][ty];
-            const float4 b0 = *reinterpret_cast<const float4 *>(&Us[k][8 * tx]), b1 = *reinterpret_cast<const float4 *>(&Us[k][8 * tx + 4]);
-            const float uv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-            for (int j = 0; j < 8; j++) acc[j] = __builtin_fmaf(-tv, uv[j], acc[j]);
+                    for (int cb = 0; cb < 4; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[cb], tv[rb], acc[rb][cb], 0, 0, 0);
+            }
         }
     }
     if (mine) {
-        float *p = W + r * a.ldw + c1 + 8 * tx;
-        *reinterpret_cast<float4 *>(p) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-        *reinterpret_cast<float4 *>(p + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+        for (int rb = 0; rb < 4; rb++)
+            if (16 * rb < rows_left) {
+#pragma unroll
+                for (int cb = 0; cb < 4; cb++) *reinterpret_cast<f32x4 *>(wt + 16 * rb * a.ldw + 16 * cb) = acc[rb][cb];
+            }
     }
 }
 
-// The panel at column p0 (its own 128 or 64 columns, which have taken the panel before's update), and the
+// The panel at column p0 (its own 128 or 64 columns, and in front of them the panel before's update of those), and the
 // panel before's update of the columns from p0 + 128 on.  Tprev: the t values of the panel before (unused for
-// p0 = 0), Tcur: where this panel's go.  panel_wgs = ceil(rows / 64), row_tiles = ceil(rows / 128); the grid is
-// panel_wgs + row_tiles * (column tiles behind the panel) workgroups, the latter none for p0 = 0.
-// (at most 128 registers per lane, four workgroups per compute unit; 170 and three for groups of 32)
+// p0 = 0), Tcur: where this panel's go.  The grid is panel_wgs + row_tiles * (column tiles behind the panel) workgroups,
+// the latter none for p0 = 0.
+// (at most 128 registers per lane, four workgroups per compute unit; three for groups of 32, whose blocks take more LDS)
 template <int D>
 __global__ __launch_bounds__(kThreads, D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
                                                                  const float *__restrict__ Tprev, float *__restrict__ Tcur,
-                                                                 correct_shape a, int64_t p0, int width, int panel_wgs, int row_tiles,
-                                                                 int front)
+                                                                 correct_shape a, int64_t p0, int width, int panel_wgs, int row_tiles)
 {
-    __shared__ __align__(16) float lds[kLdsFloats];
+    __shared__ __align__(16) float lds[lds_floats<D>()];
     if ((int)blockIdx.x < panel_wgs) {
         // the chain's waves go first where they share a SIMD with update waves, which have plenty of others to fill in
         __builtin_amdgcn_s_setprio(2);
-        panel_role<D>(W, U, Tprev, Tcur, a, p0, width, front != 0, lds);
+        panel_role<D>(W, U, Tprev, Tcur, a, p0, width, lds);
     } else {
         const int tile = (int)blockIdx.x - panel_wgs;
         update_role(W, U, Tprev, a, p0 - kPanelCols, p0 + kPanelCols, tile % row_tiles, tile / row_tiles, lds);
     }
+}
+
+template <int D>
+void launch_step(float *W, const float *U, const float *Tprev, float *Tcur, const correct_shape &a, int64_t p0, int width,
+                 int row_tiles, int col_tiles, hipStream_t s)
+{
+    const int panel_wgs = (int)((a.rows + split<D>::kRows - 1) / split<D>::kRows);
+    hipLaunchKernelGGL((correct_step_kernel<D>), dim3((unsigned)(panel_wgs + row_tiles * col_tiles)), dim3(kThreads), 0, s,
+                       W, U, Tprev, Tcur, a, p0, width, panel_wgs, row_tiles);
 }
 
 // W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: two buffers of rows x 128 floats.
@@ -447,23 +487,17 @@ hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols
 {
     correct_shape a;
     a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
-    const int panel_wgs = (int)((rows + 63) / 64), row_tiles = (int)((rows + kTile - 1) / kTile);
+    const int row_tiles = (int)((rows + kTile - 1) / kTile);
     int p = 0;
     for (int64_t p0 = 0; p0 < cols; p0 += kPanelCols, p++) {
         const int width = (int)std::min<int64_t>(kPanelCols, cols - p0);   // 128, or 64 at the end
         const int64_t behind = cols - (p0 + kPanelCols);
         const int col_tiles = p0 > 0 && behind > 0 ? (int)((behind + kTile - 1) / kTile) : 0;
         float *Tcur = work + (int64_t)(p & 1) * rows * kPanelCols, *Tprev = work + (int64_t)((p & 1) ^ 1) * rows * kPanelCols;
-        // the panel before's update of this panel's columns: by the panel workgroups themselves (64 rows x 128 columns
-        // x 128 terms on four waves: 25 us) where the launch's update tiles outlast that, else by a launch of its own
-        // that spreads over the machine
-        const int front = p0 > 0 && (int64_t)row_tiles * col_tiles >= g_front_tiles.load(std::memory_order_relaxed) ? 1 : 0;
-        if (p0 > 0 && !front) hipLaunchKernelGGL(correct_narrow_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(kThreads), 0, s, W, U, Tprev, a, p0, width);
-        const dim3 grid((unsigned)(panel_wgs + row_tiles * col_tiles));
         switch (c->D) {
-        case 8: hipLaunchKernelGGL((correct_step_kernel<8>), grid, dim3(kThreads), 0, s, W, U, Tprev, Tcur, a, p0, width, panel_wgs, row_tiles, front); break;
-        case 16: hipLaunchKernelGGL((correct_step_kernel<16>), grid, dim3(kThreads), 0, s, W, U, Tprev, Tcur, a, p0, width, panel_wgs, row_tiles, front); break;
-        default: hipLaunchKernelGGL((correct_step_kernel<32>), grid, dim3(kThreads), 0, s, W, U, Tprev, Tcur, a, p0, width, panel_wgs, row_tiles, front); break;
+        case 8: launch_step<8>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
+        case 16: launch_step<16>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
+        default: launch_step<32>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
@@ -510,7 +544,12 @@ hipError_t pvq_launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t 
 
 int64_t pvq_correct_static_max_rows(void) { return kStaticRows; }
 
-int64_t pvq_correct_front_tiles(int64_t tiles) { return g_front_tiles.exchange(tiles); }
+// (no launch asks for it any more: the panel workgroups always take the panel before's update of their columns)
+int64_t pvq_correct_front_tiles(int64_t tiles)
+{
+    static std::atomic<int64_t> value{1536};
+    return value.exchange(tiles);
+}
 
 // The same launches with the library's own work buffers.
 hipError_t pvq_launch_correct_static(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw,

@@ -53,10 +53,9 @@ int pvq_decode_gemv_on(const struct pvq_ctx *ctx, const uint32_t *index, const v
                        void *stream, int decoder, int tile_rows);
 
 /*
- * pvq_correct chooses per launch who applies the panel before's update to the panel's own columns: a launch of
- * its own, or, from *tiles* update tiles in the launch on, the panel's workgroups themselves (default 1536, which
- * small test matrices never reach).  Sets that number for the process and returns the one in force before in
- * *previous (may be NULL); results do not depend on it.  PVQ_E_INVALID_ARG for tiles < 0.
+ * The panel before's update of a panel's own columns: pvq_correct once chose per launch, by the number of its update
+ * tiles, between a launch of its own and the panel's workgroups, which now always apply it.  Keeps the number for its
+ * callers and returns the one before in *previous (may be NULL).  PVQ_E_INVALID_ARG for tiles < 0.
  */
 int pvq_correct_set_front_tiles(int64_t tiles, int64_t *previous);
 

@@ -88,6 +88,29 @@ def test_narrow_update_inside_the_panel_workgroups(D, K, rows, cols, amplitude):
         assert pvq.pvq_correct_set_front_tiles(old) == 1
 
 
+@pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 15, 384), (8, 16, 33, 448), (8, 16, 257, 512), (16, 33, 17, 384), (16, 33, 143, 448),
+                                           (32, 60, 16, 448), (32, 60, 129, 320)])
+def test_ragged_tiles_of_the_matrix_instructions(D, K, rows, cols):
+    # rows around the 16 of an instruction, the 16 or 32 of a panel workgroup and the 64 and 128 of an update tile; columns
+    # that end in half a panel and half a tile
+    run_correct(D, K, rows, cols, seed=si.BASE_SEED + 630 + rows + cols, ld_extra=4)
+
+
+def test_updates_of_tiny_weights_round_like_fused_multiply_adds():
+    # weights around the smallest normal float: products and sums of the updates are subnormal or round there, and the
+    # matrix instructions must keep every bit, as fmaf does
+    D, K, rows, cols = 8, 16, 140, 512
+    W0 = np.asarray(si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 641, rotate=False, bf16=False), dtype=np.float32)
+    W0 *= np.exp2(-np.linspace(100, 124, rows)).astype(np.float32)[:, None]
+    _, U = si.calibration_hessian(cols, 2 * cols, si.BASE_SEED + 642)
+    ref, _ = oracle.correct(W0, U, D, K, nthreads=8)
+    ctx = pvq.pvq_ctx_create(D, K)
+    Wd = gu.to_dev_f32(W0)
+    pvq.pvq_correct(ctx, Wd, gu.to_dev_f32(U))
+    assert np.array_equal(Wd.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+    ctx.close()
+
+
 @pytest.mark.parametrize("rows,cols", [(200, 256), (1100, 640)])
 def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols):
     # kernels only, all on the capturing stream; every replay must reproduce the eager result for the weights
