@@ -1,21 +1,26 @@
 // Encoder specialised for D = 8 with 24-bit indices (the 3 bits/weight setting).
 //
 // Same arithmetic, in the same order, as the generic encoder (pvq_kernels.hip) — results are bit for
-// bit the same — but organised for throughput:
-//   * one lane per group, workgroups of 256 lanes that take whole rows, 256 groups at a time (several
-//     workgroups share a compute unit, so one's loads and barriers hide behind the others' arithmetic;
-//     1024-lane workgroups measured twice as slow);
+// bit the same — but organised for throughput, which vector instructions bound:
+//   * one lane per group, workgroups of 256 lanes that take whole rows, 256 groups at a time, as many workgroups as
+//     the machine holds at once; the next tile's weights are on their way while one is worked on;
 //   * the pulse-count repair (Sec. 2.5) adjusts the coordinates that hold the |sum - K| first places in the
-//     order of deviations, found in one short round per place (first_places8).  This equals the
+//     order of deviations, found in one short round per place (adjust_first_places8).  This equals the
 //     one-at-a-time repair because no coordinate is ever adjusted twice (for finite input the
 //     |sum - K| largest deviations are all positive, an adjusted coordinate drops below -1/2);
-//   * the index (App. B.2) is a sum of seven table entries, one per coordinate, from a table of
-//     per-coordinate offsets indexed by (coordinate, pulses left, magnitude, sign);
+//   * the index (App. B.2) is a sum of seven table entries, one per coordinate, from a table of per-coordinate offsets
+//     indexed by (coordinate, pulses left, signed value), whose addresses come out of one multiply-add each
+//     (index_address);
 //   * four neighbouring lanes assemble their 24-bit indices into three dwords with DPP moves and write
 //     them straight to global memory; amplitude codes are OR-reduced across lanes the same way;
 //   * the row normaliser's pairwise sum is a wave butterfly followed by a small tree over wave sums
 //     (adding +0.0 for absent groups is exact, so padding a row to a power of two does not change
-//     the pair-level sum).
+//     the pair-level sum);
+//   * an amplitude code takes one 16-byte read for two of its bits (pvq_quantize_dev::count_edges).
+// Of the vector instructions float32 additions and multiplications issue in 2.4 cycles a wave, the others in 4 (v_rcp and
+// v_permlane*_swap 8): where there is a choice the forms are of the first kind.  28672 x 8192 bf16 weights, 2-bit codes: 248
+// vector instructions a group, 185 us; with integer addresses, a multiplication by the number of pulses for each, marks of
+// all rounds as masks and a bisection for the code 284 and 211.  14336 x 4096, 8-bit codes: 57 us, before 81.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,8 +36,14 @@ namespace {
 constexpr int kWave = 64;
 constexpr int D = 8;
 
+// The offset table in LDS: [7][kMaxK + 1][2 kMaxK + 1] words (coordinate, pulses left, value + kMaxK), whatever K is
+// (15 or 16 with 24-bit indices), so that the rows' distances are known here.
+constexpr int kMaxK = PVQ_ENC8_MAX_K;
+constexpr int kStepValue = 4, kStepPulse = 4 * (2 * kMaxK + 1), kStepCoordinate = kStepPulse * (kMaxK + 1);   // bytes
+constexpr int kTableWords = (PVQ_ENC8_WORDS + 3) & ~3;
+
 struct enc8_launch {
-    const uint32_t *offs;   // [7][K+1][K+1][2]
+    const uint32_t *offs;
     const float *edges;     // 2^scale_bits entries, last = +inf (or nullptr)
     int K, scale_bits;
 };
@@ -59,21 +70,22 @@ __device__ inline float wave_pair_sum(float v)
     return v;
 }
 
-// OR of v over aligned runs of n lanes (n = 1, 2, 4, ... 32), in every lane of the run: the first four levels
-// by lane patterns inside a row of 16 lanes (within a quad; then, the quads being uniform, the mirror images
-// inside 8 and 16 lanes bring the other half), the fifth across rows.
+// OR of v over aligned runs of N lanes (N = 4, 8, 16, 32), in every lane of the run: the first four levels by lane
+// patterns inside a row of 16 lanes (within a quad; then, the quads being uniform, the mirror images inside 8 and 16
+// lanes bring the other half), the fifth across rows.
 template <int CTRL>
 __device__ inline uint32_t dpp_or(uint32_t v)
 {
     return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
 }
-__device__ inline uint32_t or_over_lanes(uint32_t v, int n)
+template <int N>
+__device__ inline uint32_t or_over_lanes(uint32_t v)
 {
-    if (n > 1) v = dpp_or<0xB1>(v);            // quad_perm [1,0,3,2]
-    if (n > 2) v = dpp_or<0x4E>(v);            // quad_perm [2,3,0,1]
-    if (n > 4) v = dpp_or<0x141>(v);           // row_half_mirror
-    if (n > 8) v = dpp_or<0x140>(v);           // row_mirror
-    if (n > 16) v |= __shfl_xor(v, 16, kWave);
+    v = dpp_or<0xB1>(v);                              // quad_perm [1,0,3,2]
+    v = dpp_or<0x4E>(v);                              // quad_perm [2,3,0,1]
+    if constexpr (N > 4) v = dpp_or<0x141>(v);        // row_half_mirror
+    if constexpr (N > 8) v = dpp_or<0x140>(v);        // row_mirror
+    if constexpr (N > 16) v |= __shfl_xor(v, 16, kWave);
     return v;
 }
 
@@ -87,14 +99,35 @@ __device__ inline float tree8(float (&v)[D])
     return v[0];
 }
 
-template <typename TIn>
-__device__ inline void load8(const TIn *__restrict__ p, float (&w)[D])
-{
-    if constexpr (sizeof(TIn) == 4) {
-        const float4 q0 = *reinterpret_cast<const float4 *>(p), q1 = *reinterpret_cast<const float4 *>(p + 4);
+// A group as it comes from memory: 8 float32 or bf16 values.
+template <typename TIn> struct raw8;
+template <> struct raw8<float> {
+    float4 q0, q1;
+    __device__ void load(const float *__restrict__ p)
+    {
+        q0 = *reinterpret_cast<const float4 *>(p); q1 = *reinterpret_cast<const float4 *>(p + 4);
+    }
+    __device__ void flip(uint2 bits)
+    {
+        float *v[D] = {&q0.x, &q0.y, &q0.z, &q0.w, &q1.x, &q1.y, &q1.z, &q1.w};
+#pragma unroll
+        for (int j = 0; j < D; j++) *v[j] = pvq_hadamard_dev::with_sign(*v[j], bits, j);
+    }
+    __device__ void get(float (&w)[D]) const
+    {
         w[0] = q0.x; w[1] = q0.y; w[2] = q0.z; w[3] = q0.w; w[4] = q1.x; w[5] = q1.y; w[6] = q1.z; w[7] = q1.w;
-    } else {
-        const uint4 q = *reinterpret_cast<const uint4 *>(p);
+    }
+};
+template <> struct raw8<uint16_t> {
+    uint4 q;
+    __device__ void load(const uint16_t *__restrict__ p) { q = *reinterpret_cast<const uint4 *>(p); }
+    __device__ void flip(uint2 bits)
+    {
+        q.x = pvq_hadamard_dev::with_signs(q.x, bits, 0); q.y = pvq_hadamard_dev::with_signs(q.y, bits, 1);
+        q.z = pvq_hadamard_dev::with_signs(q.z, bits, 2); q.w = pvq_hadamard_dev::with_signs(q.w, bits, 3);
+    }
+    __device__ void get(float (&w)[D]) const
+    {
         const uint32_t u[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
         for (int j = 0; j < 4; j++) {
@@ -102,164 +135,221 @@ __device__ inline void load8(const TIn *__restrict__ p, float (&w)[D])
             w[2 * j + 1] = __uint_as_float(u[j] & 0xFFFF0000u);
         }
     }
-}
+};
 
-// One group: returns its 24-bit index, the sum of squares, and the signed point in y.
-__device__ inline uint32_t encode_group8(const float (&w)[D], int K, const uint32_t *offs, float &ss_out,
-                                         int (&y)[D])
+// A float whose bits are the integer n (subnormal for the n used here): small integers times bytes(1) add and multiply
+// exactly, so one fused multiply-add steps a byte address, and its result's bits are the address.
+__device__ constexpr float bytes(uint32_t n) { return __builtin_bit_cast(float, n); }
+
+// One group: returns its 24-bit index, the sum of squares, and the signed point in y (float, zeros of either sign).
+// table: LDS address of offs[0][0][0].  POINT: y of a group without a direction is set too (else its y is unspecified).
+template <bool POINT>
+__device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t table, float &ss_out, bool &degenerate, float (&y)[D])
 {
-    float a[D], tmp[D];
+    float tmp[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) { a[i] = fabsf(w[i]); tmp[i] = a[i]; }
+    for (int i = 0; i < D; i++) tmp[i] = fabsf(w[i]);
     const float l1 = tree8(tmp);
 #pragma unroll
     for (int i = 0; i < D; i++) tmp[i] = w[i] * w[i];
     ss_out = tree8(tmp);
 
-    const float g = (float)K / l1;
-    // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite
-    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
-    // from here on every t is finite and within [0, K(1+eps)] unless `degenerate`
-    float t[D], yf[D];
-    float S = 0.0f;
+    float g = K / l1, pulses = K;
+    // from here on t is finite and within [-K(1+eps), K(1+eps)]
+    float t[D], mag[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-        t[i] = a[i] * g;
-        yf[i] = rintf(t[i]);
-        S += yf[i];                       // small integers: exact in any order
-    }
-    const float m = (float)K - S;         // > 0: pulses to add, < 0: pulses to take away
-    float key[D];
+    for (int i = 0; i < D; i++) t[i] = w[i] * g;
+    // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite.  Zeros then, whose index comes out as
+    // that of (0, ..., 0, K): 0.  (Looked at closely only in waves with a norm that is not well inside the normal floats.)
+    degenerate = false;
+    if (__any(__float_as_uint(l1) - 0x01000000u >= 0x7E000000u)) {
+        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+        pulses = degenerate ? 0.0f : K;
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-        const float d = t[i] - yf[i];     // how far below its projected value
-        key[i] = m < 0.0f ? -d : d;
+        for (int i = 0; i < D; i++) t[i] = degenerate ? 0.0f : t[i];
     }
-    const int need = degenerate ? 0 : (int)fminf(fabsf(m), (float)D);   // coordinates to adjust; they hold the places 0 .. need-1
-    bool adj[D];
-    pvq_quantize_dev::first_places8(key, need, adj);
+    float S[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) { mag[i] = rintf(fabsf(t[i])); S[i] = mag[i]; }
+    // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
+    const float m = pulses - tree8(S);
     const float unit = m < 0.0f ? -1.0f : 1.0f;
-    uint32_t c = 0;
-    int k = K;
+    // deviations, how far below its projected value (negated where pulses have to go), as integers: those that are looked for
+    // are positive, and positive floats order like their bits
+    int key[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-        int mag = (int)(yf[i] + (adj[i] ? unit : 0.0f));
-        // sign bit of the weight; a degenerate group takes +K.  (-0.0 never carries a pulse: a
-        // coordinate whose projection is zero is not among the ones raised.)
-        const uint32_t neg = __float_as_uint(w[i]) >> 31;
-        if (degenerate) mag = (i == D - 1) ? K : 0;
-        // the magnitudes of the adjusted point lie in [0, k] and sum to K (a degenerate group was
-        // given its point just above); the last coordinate takes what is left
-        if (i == D - 1) mag = k;
-        y[i] = (neg && !degenerate) ? -mag : mag;
-        if (i < D - 1) {
-            // offs[i][k][mag][neg]: what coordinate i adds to the index with k pulses left (App. B.2);
-            // with mag = 0 both signs hold 0
-            // (24-bit multiplies: everything here is far below 2^24)
-            c += offs[(__mul24(i * (K + 1) + k, K + 1) + mag) * 2 + neg];
-            k -= mag;
-        } else {
-            c += (neg && !degenerate && k > 0) ? 1u : 0u;
-        }
+    for (int i = 0; i < D; i++) key[i] = __float_as_int((fabsf(t[i]) - mag[i]) * unit);
+    pvq_quantize_dev::adjust_first_places8(key, fabsf(m), unit, mag);
+    // (-0.0 never carries a pulse: a coordinate whose projection is zero is not among the ones raised)
+#pragma unroll
+    for (int i = 0; i < D; i++) y[i] = copysignf(mag[i], w[i]);
+    // offs[i][k][y]: what coordinate i adds to the index with k pulses left (App. B.2); 0 for y = 0
+    uint32_t part[D - 1];
+    float at = __uint_as_float(table) + K * bytes(kStepPulse) + bytes(kMaxK * kStepValue);   // offs[0][K][0]
+#pragma unroll
+    for (int i = 0; i < D - 1; i++) {
+        const uint32_t address = __float_as_uint(__builtin_fmaf(y[i], bytes(kStepValue), at));
+        part[i] = *reinterpret_cast<const __attribute__((address_space(3))) uint32_t *>(address + i * kStepCoordinate);
+        at = __builtin_fmaf(mag[i], -bytes(kStepPulse), at);
+    }
+    // the last coordinate takes what is left: +k is first, -k second
+    uint32_t c = y[D - 1] < 0.0f ? 1u : 0u;
+#pragma unroll
+    for (int i = 0; i < D - 1; i++) c += part[i];
+    if constexpr (POINT) {
+        if (degenerate) y[D - 1] = K;
     }
     return c;
 }
 
+// Least-squares amplitude (pvq_ls_amplitude) for the point in y.
+__device__ inline float ls_amplitude8(const float (&w)[D], const float (&y)[D], bool degenerate)
+{
+    float p[D], n[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+        p[i] = y[i] * w[i];
+        n[i] = y[i] * y[i];                   // small integers
+    }
+    if (__any(degenerate)) {
+        // zeros of the point are positive (the sign of a sum of zeros is theirs)
+#pragma unroll
+        for (int i = 0; i < D - 1; i++) p[i] = degenerate ? 0.0f * w[i] : p[i];
+    }
+    return tree8(p) / sqrtf(tree8(n));
+}
+
+// four neighbouring 24-bit indices -> three dwords: lane j of a quad (j < 3) builds dword j from its own index and the
+// next lane's
+__device__ inline uint32_t index_word(uint32_t c, int quad_pos)
+{
+    const uint32_t cn = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xF9, 0xF, 0xF, false);
+    const uint32_t lo = c | (cn << 24), hi = cn >> 8;
+    return __builtin_amdgcn_alignbit(hi, lo, 8 * quad_pos);
+}
+
+// The row's sum of squares from its wave sums (at most 64, zero padded; the pairwise tree goes on), in a scalar register.
+__device__ inline float row_sum(const float *wsum, int lane)
+{
+    return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_pair_sum(wsum[lane])), kWave - 1));
+}
+
+// The row's amplitude codes (Sec. 3.3 Step 5): code = number of quantile edges <= u, u = ss_g / rowss, packed 32/SB lanes to
+// a dword by an OR butterfly.  step: lanes of the workgroup.
+template <int SB>
+__device__ inline void write_codes(const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int step, int lane)
+{
+    for (int g = threadIdx.x; g - lane < G; g += step) {
+        const float ss = g < G ? ss_row[g] : 0.0f;
+        const uint32_t code = pvq_quantize_dev::count_edges<SB>(tree, ss / rowss);
+        const uint32_t word = or_over_lanes<32 / SB>(code << ((lane * SB) & 31));
+        if ((lane & (32 / SB - 1)) == 0 && g < G) srow[((uint32_t)g * SB) >> 5] = word;
+    }
+}
+// (the width of a code is the same for all lanes; a branch per row, so that no loop keeps its conditions in registers)
+__device__ inline void write_codes(int sb, const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int step, int lane)
+{
+    switch (sb) {
+    case 1: write_codes<1>(ss_row, rowss, tree, srow, G, step, lane); break;
+    case 2: write_codes<2>(ss_row, rowss, tree, srow, G, step, lane); break;
+    case 4: write_codes<4>(ss_row, rowss, tree, srow, G, step, lane); break;
+    default: write_codes<8>(ss_row, rowss, tree, srow, G, step, lane); break;
+    }
+}
+
+// LDS of both kernels, from byte 0: the offset table, the edges' tree, two rows' wave sums (used in turn, so that one
+// barrier a row is enough), the row's sums of squares (CODES; every lane reads its own).
+struct enc8_lds {
+    float4 *tree;
+    float *wsum, *ss_row;
+    uint32_t table;
+};
+template <bool CODES>
+__device__ inline enc8_lds fill_lds(uint32_t *smem, const enc8_launch &f, int lanes)
+{
+    enc8_lds l;
+    l.tree = reinterpret_cast<float4 *>(smem + kTableWords);
+    l.wsum = reinterpret_cast<float *>(l.tree + pvq_quantize_dev::kEdgeNodes);
+    l.ss_row = l.wsum + 2 * 64;
+    l.table = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)smem);
+    for (int i = threadIdx.x; i < kTableWords / 4; i += lanes) reinterpret_cast<uint4 *>(smem)[i] = reinterpret_cast<const uint4 *>(f.offs)[i];
+    if constexpr (CODES) pvq_quantize_dev::fill_edge_tree(l.tree, f.edges, f.scale_bits, threadIdx.x, lanes);
+    for (int i = threadIdx.x; i < 2 * 64; i += lanes) l.wsum[i] = 0.0f;
+    return l;
+}
+// its words in front of the row's sums of squares
+constexpr int kHeadWords = kTableWords + 4 * pvq_quantize_dev::kEdgeNodes + 2 * 64;
+
 // TIn: float or uint16_t (bf16 bits).  A block of kBlock lanes takes whole rows, kBlock groups at a
-// time; several blocks share a compute unit, so one block's loads and barriers hide behind the
-// others' arithmetic.
+// time; several blocks share a compute unit, so one block's barriers hide behind the others' arithmetic.
 constexpr int kBlock = 256;
 constexpr int kMaxGroups = 4096;   // groups per row this kernel takes (their sums of squares sit in LDS)
 
 // LS: least-squares amplitudes (Sec. 3.3 Step 4) instead of norms.
 template <typename TIn, bool CODES, bool LS>
-__global__ __launch_bounds__(kBlock) void encode8_kernel(enc8_launch f, pvq_encode_args a)
+__global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_encode_args a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
-    const int K = f.K, sb = f.scale_bits;
-    const int ntab = 7 * (K + 1) * (K + 1) * 2;
-    uint32_t *offs = smem;
-    float *edges = reinterpret_cast<float *>(smem + ntab);       // 256 floats
-    float *wsum = edges + 256;                                    // 64 wave sums of the row (zero padded)
-    float *ss_row = wsum + 64;                                    // the row's sums of squares (CODES)
-    for (int i = threadIdx.x; i < ntab; i += kBlock) offs[i] = f.offs[i];
-    if constexpr (CODES)
-        for (int i = threadIdx.x; i < (1 << sb); i += kBlock) edges[i] = f.edges[i];
-    if (threadIdx.x < 64) wsum[threadIdx.x] = 0.0f;
-    __syncthreads();
+    const int sb = f.scale_bits;
+    const float K = (float)f.K;
+    const enc8_lds l = fill_lds<CODES>(smem, f, kBlock);
 
     const int G = (int)a.groups;
-    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int quad_pos = lane & 3;
-    const int tiles = (G + kBlock - 1) / kBlock;
+    // tiles of a row in which the wave has groups
+    const int tiles = (G - wave * kWave + kBlock - 1) / kBlock;
+    const TIn *W = reinterpret_cast<const TIn *>(a.W);
+    // (a lane past the row's end takes the last group again, and writes nothing)
+    auto source = [&](int64_t row, int tix) { return W + row * a.ldw + (int64_t)min(tix * kBlock + (int)threadIdx.x, G - 1) * D; };
 
+    raw8<TIn> next;
+    if (tiles > 0) next.load(source(blockIdx.x, 0));
+    __syncthreads();
+    float *wsum = l.wsum;
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
-        const TIn *wrow = reinterpret_cast<const TIn *>(a.W) + row * a.ldw;
         uint32_t *irow = a.index_out + row * a.index_row_words;
         for (int tix = 0; tix < tiles; tix++) {
             const int g = tix * kBlock + (int)threadIdx.x;
-            uint32_t c = 0;
-            float ss = 0.0f;
-            if (g < G) {
-                float w[D];
-                int y[D];
-                load8<TIn>(wrow + (int64_t)g * D, w);
-                c = encode_group8(w, K, offs, ss, y);
-                float amp;
-                if constexpr (LS) { amp = pvq_ls_amplitude<D>(w, y); ss = amp * amp; }
-                else amp = sqrtf(ss);
-                if (a.pulses_out) {
-                    uint32_t lo = 0, hi = 0;
+            const bool in = g < G;
+            float w[D], y[D], ss;
+            next.get(w);
+            // the tile behind, or the next row's first (of the last row once more)
+            const bool more = tix + 1 < tiles;
+            next.load(source(more ? row : min(row + (int64_t)gridDim.x, a.rows - 1), more ? tix + 1 : 0));
+            bool degenerate;
+            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, degenerate, y);
+            float amp;
+            if constexpr (LS) { amp = ls_amplitude8(w, y, degenerate); ss = amp * amp; }
+            else amp = sqrtf(ss);
+            if (a.pulses_out && in) {
+                if (degenerate) y[D - 1] = K;
+                uint32_t lo = 0, hi = 0;
 #pragma unroll
-                    for (int j = 0; j < 4; j++) {
-                        lo |= ((uint32_t)y[j] & 0xFFu) << (8 * j);
-                        hi |= ((uint32_t)y[4 + j] & 0xFFu) << (8 * j);
-                    }
-                    *reinterpret_cast<uint2 *>(a.pulses_out + row * a.cols + (int64_t)g * D) = make_uint2(lo, hi);
+                for (int j = 0; j < 4; j++) {
+                    lo |= ((uint32_t)(int)y[j] & 0xFFu) << (8 * j);
+                    hi |= ((uint32_t)(int)y[4 + j] & 0xFFu) << (8 * j);
                 }
-                if constexpr (CODES) ss_row[g] = ss;
+                *reinterpret_cast<uint2 *>(a.pulses_out + row * a.cols + (int64_t)g * D) = make_uint2(lo, hi);
+            }
+            if (in) {
+                if constexpr (CODES) l.ss_row[g] = ss;
                 else reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
             }
-            // four neighbouring 24-bit indices -> three dwords: lane j of a quad (j < 3) builds dword j
-            // from its own index and the next lane's
-            const uint32_t cn = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xF9, 0xF, 0xF, false);
-            const uint32_t lo = c | (cn << 24), hi = cn >> 8;
-            const uint32_t word = __builtin_amdgcn_alignbit(hi, lo, 8 * quad_pos);
-            if (quad_pos < 3 && g < G) irow[3 * (g >> 2) + quad_pos] = word;
+            const uint32_t word = index_word(c, quad_pos);
+            if (quad_pos < 3 && in) irow[3 * (g >> 2) + quad_pos] = word;
             if constexpr (CODES) {
                 // pairwise sum over the wave's 64 groups (absent groups add +0.0, which is exact)
-                const float v = wave_pair_sum(ss);
+                const float v = wave_pair_sum(in ? ss : 0.0f);
                 if (lane == kWave - 1) wsum[tix * (kBlock / kWave) + wave] = v;
             }
         }
         if constexpr (CODES) {
             __syncthreads();
-            // the pairwise tree continues over the (at most 64, zero padded) wave sums
-            float rowss = wsum[lane];
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) rowss += __shfl_xor(rowss, off, kWave);
+            const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            // Sec. 3.3 Step 5: code = number of quantile edges <= u, u = ss_g / rowss (bisection over
-            // the ascending edges), packed 32/sb lanes to a dword by an OR butterfly
-            uint32_t *srow = reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words;
-            const int nedges = (1 << sb) - 1;
-            const int lanes_per_word = 32 / sb;
-            for (int tix = 0; tix < tiles; tix++) {
-                const int g = tix * kBlock + (int)threadIdx.x;
-                uint32_t v = 0;
-                if (g < G) {
-                    const float u = ss_row[g] / rowss;
-                    int lo = 0, hi = nedges;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (edges[mid] <= u) lo = mid + 1; else hi = mid;
-                    }
-                    v = (uint32_t)lo << ((lane * sb) & 31);
-                }
-                v = or_over_lanes(v, lanes_per_word);
-                if ((lane & (lanes_per_word - 1)) == 0 && g < G) srow[((uint32_t)g * (uint32_t)sb) >> 5] = v;
-            }
-            __syncthreads();   // ss_row and wsum are rewritten by the next row
+            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, kBlock, lane);
+            wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
 }
@@ -278,63 +368,52 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
 {
     using namespace pvq_hadamard_dev;
     extern __shared__ __align__(16) uint32_t smem[];
-    const int K = f.K, sb = f.scale_bits;
+    const int sb = f.scale_bits;
+    const float K = (float)f.K;
     const int L = blockDim.x;
-    const int ntab = 7 * (K + 1) * (K + 1) * 2;
     const int G = (int)a.groups;
-    uint32_t *offs = smem;
-    float *edges = reinterpret_cast<float *>(smem + ntab);       // 256 floats
-    float *wsum = edges + 256;                                    // 64 wave sums of the row (zero padded)
-    float *ss_row = wsum + 64;                                    // the row's sums of squares (CODES)
-    float *hbuf = ss_row + (CODES ? ((G + 3) & ~3) : 0);          // the rotation's exchange buffers
-    for (int i = threadIdx.x; i < ntab; i += L) offs[i] = f.offs[i];
-    if constexpr (CODES)
-        for (int i = threadIdx.x; i < (1 << sb); i += L) edges[i] = f.edges[i];
-    if (threadIdx.x < 64) wsum[threadIdx.x] = 0.0f;
+    const enc8_lds l = fill_lds<CODES>(smem, f, L);
+    float *hbuf = l.ss_row + (CODES ? ((G + 3) & ~3) : 0);       // the rotation's exchange buffer
     __syncthreads();
 
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
     const int quad_pos = lane & 3;
     const int chunks = G / L;                                    // whole chunks: every lane has a group
+    const int from = load_lane<LOG2N>(tid);                      // the 8 values of a chunk that the lane loads
     const int waves = L / kWave;
 
+    float *wsum = l.wsum;
     for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
         const TIn *xrow = reinterpret_cast<const TIn *>(a.W) + row * a.ldw;
         uint32_t *irow = a.index_out + row * a.index_row_words;
         for (int ch = 0; ch < chunks; ch++) {
             const int g = ch * L + tid;
             float v[D];
-            load8<TIn>(xrow + (int64_t)g * D, v);
-            if (signs) {
-                const uint2 s8 = *reinterpret_cast<const uint2 *>(signs + (int64_t)g * D);
-#pragma unroll
-                for (int j = 0; j < D; j++) {
-                    const uint32_t byte = ((j < 4 ? s8.x : s8.y) >> (8 * (j & 3))) & 0xFFu;
-                    if (byte) v[j] = -v[j];
-                }
-            }
+            raw8<TIn> raw;
+            raw.load(xrow + (int64_t)(ch * L + from) * D);
+            if (signs) raw.flip(sign_bits(*reinterpret_cast<const uint2 *>(signs + (int64_t)(ch * L + from) * D)));
+            raw.get(v);
             // one exchange buffer (a barrier in front of every exchange, which also keeps a chunk's writes
             // behind the reads of the chunk before): two workgroups of 1024 lanes then fit a unit's LDS
             // (which cross-lane stages go through the LDS permute unit: all of them for blocks of up to 512 values,
             // where the encoder's arithmetic is what the kernel waits for and that unit is idle; only the one over
             // 4 lanes for 1024 and 2048; none from 4096 on, where the exchanges through LDS need it: measured)
             constexpr int kPermuted = LOG2N <= 9 ? 4 + 8 + 16 + 32 : LOG2N <= 11 ? 4 : 0;
-            hadamard_stages<LOG2N, false, true, kPermuted>(v, tid, log2n, hbuf, L);
-            float w[D];
+            int stages = log2n;
+            if constexpr (LOG2N <= 9) asm volatile("" : "+s"(stages));   // (else the comparisons below stay in scalar registers over the loop)
+            hadamard_stages<LOG2N, false, true, kPermuted>(v, tid, stages, hbuf, L);
+            float w[D], y[D], ss;
 #pragma unroll
             for (int j = 0; j < D; j++) w[j] = v[j] * scale;
-            int y[D];
-            float ss;
-            const uint32_t c = encode_group8(w, K, offs, ss, y);
+            bool degenerate;
+            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, degenerate, y);
             float amp;
-            if constexpr (LS) { amp = pvq_ls_amplitude<D>(w, y); ss = amp * amp; }
+            if constexpr (LS) { amp = ls_amplitude8(w, y, degenerate); ss = amp * amp; }
             else amp = sqrtf(ss);
-            if constexpr (CODES) ss_row[g] = ss;
+            if constexpr (CODES) l.ss_row[g] = ss;
             else reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
-            const uint32_t cn = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)c, 0xF9, 0xF, 0xF, false);
-            const uint32_t lo = c | (cn << 24), hi = cn >> 8;
-            const uint32_t word = __builtin_amdgcn_alignbit(hi, lo, 8 * quad_pos);
+            const uint32_t word = index_word(c, quad_pos);
             if (quad_pos < 3) irow[3 * (g >> 2) + quad_pos] = word;
             if constexpr (CODES) {
                 const float s64 = wave_pair_sum(ss);
@@ -343,26 +422,10 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
         }
         if constexpr (CODES) {
             __syncthreads();
-            float rowss = wsum[lane];
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) rowss += __shfl_xor(rowss, off, kWave);
+            const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            uint32_t *srow = reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words;
-            const int nedges = (1 << sb) - 1;
-            const int lanes_per_word = 32 / sb;
-            for (int ch = 0; ch < chunks; ch++) {
-                const int g = ch * L + tid;
-                const float u = ss_row[g] / rowss;
-                int lo = 0, hi = nedges;
-                while (lo < hi) {
-                    const int mid = (lo + hi) >> 1;
-                    if (edges[mid] <= u) lo = mid + 1; else hi = mid;
-                }
-                uint32_t code = (uint32_t)lo << ((lane * sb) & 31);
-                code = or_over_lanes(code, lanes_per_word);
-                if ((lane & (lanes_per_word - 1)) == 0) srow[((uint32_t)g * (uint32_t)sb) >> 5] = code;
-            }
-            __syncthreads();   // ss_row and wsum are rewritten by the next row
+            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, L, lane);
+            wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
 }
@@ -371,7 +434,7 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
 // lane (the body needs 68: a few values go to scratch), which measured 0.60 against 0.73 ms on 28672 x 8192.
 // The smaller workgroups of the other block sizes keep all their registers.
 template <typename TIn, bool CODES, bool LS, int LOG2N>
-__global__ __launch_bounds__(512) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
+__global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)
 {
     rotate_encode8_body<TIn, CODES, LS, LOG2N>(f, a, log2n, signs, scale);
@@ -385,6 +448,14 @@ __global__ __launch_bounds__(1024, 8) void rotate_encode8_kernel_8192(enc8_launc
 }
 
 }  // namespace
+
+// Workgroups of `lanes` lanes and `lds` bytes that the machine holds at once, up to 8 waves on a SIMD: they take the rows in
+// turn, so that the tables are copied to LDS once per place and not once per row.
+static unsigned resident_grid(int64_t rows, int lanes, size_t lds)
+{
+    const int64_t by_waves = 32 / (lanes / kWave), by_lds = (int64_t)(160 * 1024 / ((lds + 1279) / 1280 * 1280));
+    return (unsigned)std::min<int64_t>(rows, 256 * std::max<int64_t>(1, std::min(by_waves, by_lds)));
+}
 
 // lanes of the fused kernel's workgroup for a rotation block: whole blocks, at least 256 lanes
 static int rotate8_lanes(int block) { return std::min(1024, std::max(256, block / 8)); }
@@ -407,8 +478,8 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     const bool codes = c->scale_bits > 0, ls = a.ls_amplitude != 0;
     const float scale = (float)(1.0 / std::sqrt((double)block));
     const size_t hbuf = log2n > 9 ? (size_t)(8 * L + 8 * L / 32 + 1) : 0;
-    const size_t lds = ((size_t)7 * (c->K + 1) * (c->K + 1) * 2 + 256 + 64 + (codes ? (size_t)((a.groups + 3) & ~3) : 0) + hbuf) * 4;
-    const unsigned grid = (unsigned)std::min<int64_t>(a.rows, 8192);
+    const size_t lds = (kHeadWords + (codes ? (size_t)((a.groups + 3) & ~3) : 0) + hbuf) * 4;
+    const unsigned grid = resident_grid(a.rows, L, lds);
 #define PVQ_RE8_LAUNCH(KERNEL)                                                                                   \
     do {                                                                                                        \
         if (lds > 64 * 1024) {                                                                                  \
@@ -449,11 +520,9 @@ hipError_t pvq_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a, int dt
     enc8_launch f;
     f.offs = c->enc8_offs; f.edges = c->edges; f.K = c->K; f.scale_bits = c->scale_bits;
     const dim3 block(kBlock);
-    const bool with_codes = c->scale_bits > 0;
-    const size_t lds = ((size_t)7 * (c->K + 1) * (c->K + 1) * 2 + 256 + 64 + (with_codes ? (size_t)a.groups : 0)) * 4;
-    // rows are strided over the blocks; enough blocks to fill every unit several times over
-    const unsigned grid = (unsigned)std::min<int64_t>(a.rows, 8192);
     const bool codes = c->scale_bits > 0;
+    const size_t lds = (kHeadWords + (codes ? (size_t)a.groups : 0)) * 4;
+    const unsigned grid = resident_grid(a.rows, kBlock, lds);
 #define PVQ_ENC8_CASE(T, C, L) hipLaunchKernelGGL((encode8_kernel<T, C, L>), dim3(grid), dim3(block), lds, s, f, a)
     const bool ls = a.ls_amplitude != 0;
     if (dtype == PVQ_F32) {

@@ -39,18 +39,19 @@ __global__ __launch_bounds__(1024) void hadamard_kernel(const void *X, int64_t l
     const int64_t row = blockIdx.x / chunks_per_row;
     const int chunk = blockIdx.x - (int)(row * chunks_per_row);
     const int64_t col0 = (int64_t)chunk * 8 * L + 8 * lane;   // first of this lane's 8 columns
-    const bool live = col0 < cols;                             // whole blocks: a lane is in or out
+    const int64_t from = (int64_t)chunk * 8 * L + 8 * load_lane<LOG2N>(lane);   // ... that it loads
+    const bool live = col0 < cols;                             // whole blocks: a lane, and a block's quads, are in or out
 
     float v[8];
 #pragma unroll
     for (int j = 0; j < 8; j++) v[j] = 0.0f;
     if (live) {
         if constexpr (IN == PVQ_F32) {
-            const float *p = reinterpret_cast<const float *>(X) + row * ldx + col0;
+            const float *p = reinterpret_cast<const float *>(X) + row * ldx + from;
             const float4 a = *reinterpret_cast<const float4 *>(p), b = *reinterpret_cast<const float4 *>(p + 4);
             v[0] = a.x; v[1] = a.y; v[2] = a.z; v[3] = a.w; v[4] = b.x; v[5] = b.y; v[6] = b.z; v[7] = b.w;
         } else {
-            const uint4 q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(X) + row * ldx + col0);
+            const uint4 q = *reinterpret_cast<const uint4 *>(reinterpret_cast<const uint16_t *>(X) + row * ldx + from);
             const uint32_t u[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
             for (int j = 0; j < 4; j++) {
@@ -59,20 +60,11 @@ __global__ __launch_bounds__(1024) void hadamard_kernel(const void *X, int64_t l
             }
         }
     }
-    uint32_t flip[8];   // sign bit where the column's sign is -1
-#pragma unroll
-    for (int j = 0; j < 8; j++) flip[j] = 0;
-    if (signs && live) {
-        const uint2 s8 = *reinterpret_cast<const uint2 *>(signs + col0);
-#pragma unroll
-        for (int j = 0; j < 8; j++) {
-            const uint32_t byte = ((j < 4 ? s8.x : s8.y) >> (8 * (j & 3))) & 0xFFu;
-            flip[j] = byte ? 0x80000000u : 0u;
-        }
-    }
+    uint2 flip = make_uint2(0, 0);
+    if (signs && live) flip = sign_bits(*reinterpret_cast<const uint2 *>(signs + (signs_after ? col0 : from)));
     if (!signs_after) {
 #pragma unroll
-        for (int j = 0; j < 8; j++) v[j] = __uint_as_float(__float_as_uint(v[j]) ^ flip[j]);
+        for (int j = 0; j < 8; j++) v[j] = with_sign(v[j], flip, j);
     }
 
     // Blocks of 1024 and 8192 values end with a single stage (index bit 9, or 12): its ownership (P, 1)
@@ -112,7 +104,7 @@ __global__ __launch_bounds__(1024) void hadamard_kernel(const void *X, int64_t l
 #pragma unroll
     for (int j = 0; j < 8; j++) {
         v[j] = v[j] * scale;
-        if (signs_after) v[j] = __uint_as_float(__float_as_uint(v[j]) ^ flip[j]);
+        if (signs_after) v[j] = with_sign(v[j], flip, j);
     }
     if (!live) return;
     if constexpr (OUT == PVQ_F32) {

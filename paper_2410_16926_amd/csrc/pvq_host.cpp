@@ -430,20 +430,20 @@ extern "C" int pvq_ctx_create(pvq_ctx **out, int D, int K, int scale_bits, const
         if (e == hipSuccess) e = hipMemcpy(c->walk_blob, blob.data(), blob.size(), hipMemcpyHostToDevice);
         if (e == hipSuccess && !pvq_walk_usable(c)) { pvq_ctx_destroy(c); return PVQ_E_UNSUPPORTED; }
     }
-    if (e == hipSuccess && D == 8 && bits == 24) {
+    if (e == hipSuccess && D == 8 && bits == 24 && K <= PVQ_ENC8_MAX_K) {
         // What coordinate i (7-i dimensions after it) adds to the index when k pulses are left and it
-        // takes magnitude m with the given sign (App. B.2):
-        //   N(7-i,k) [m>0] + 2 sum_{j=1}^{m-1} N(7-i,k-j) + [negative] N(7-i,k-m)
-        const int K1 = K + 1;
-        std::vector<uint32_t> offs((size_t)7 * K1 * K1 * 2, 0u);
+        // takes the value y of magnitude m (App. B.2):
+        //   N(7-i,k) [m>0] + 2 sum_{j=1}^{m-1} N(7-i,k-j) + [y<0] N(7-i,k-m)
+        constexpr int M = PVQ_ENC8_MAX_K;
+        std::vector<uint32_t> offs((size_t)(PVQ_ENC8_WORDS + 3) / 4 * 4, 0u);
         for (int i = 0; i < 7; i++)
             for (int k = 0; k <= K; k++)
                 for (int m = 1; m <= k; m++) {
                     uint64_t v = t.at(7 - i, k).limb[0];
                     for (int j = 1; j < m; j++) v += 2 * t.at(7 - i, k - j).limb[0];
-                    const size_t at = (((size_t)i * K1 + k) * K1 + m) * 2;
-                    offs[at] = (uint32_t)v;
-                    offs[at + 1] = (uint32_t)(v + t.at(7 - i, k - m).limb[0]);
+                    uint32_t *zero = &offs[((size_t)i * (M + 1) + k) * (2 * M + 1) + M];
+                    zero[m] = (uint32_t)v;
+                    zero[-m] = (uint32_t)(v + t.at(7 - i, k - m).limb[0]);
                 }
         e = hipMalloc((void **)&c->enc8_offs, offs.size() * 4);
         if (e == hipSuccess) e = hipMemcpy(c->enc8_offs, offs.data(), offs.size() * 4, hipMemcpyHostToDevice);

@@ -67,6 +67,11 @@ inline int pvq_wide_key_row(int K) { return 2 * K + 2 + 6; }
 // The other decoder's first guess: keys by bit length and the three bits behind the leading one (their bits 18 to 31, less 21).
 inline int pvq_wide_buckets(int words) { return (32 * words + 1) * 8; }
 
+// The D = 8 / 24-bit encoder's offsets: [7][PVQ_ENC8_MAX_K + 1][2 PVQ_ENC8_MAX_K + 1] words: coordinate, pulses left, value +
+// PVQ_ENC8_MAX_K.  K is 15 or 16 with 24-bit indices.
+constexpr int PVQ_ENC8_MAX_K = 16;
+constexpr int PVQ_ENC8_WORDS = 7 * (PVQ_ENC8_MAX_K + 1) * (2 * PVQ_ENC8_MAX_K + 1);
+
 struct pvq_ctx {
     int D, K;
     int index_bits;
@@ -96,8 +101,8 @@ struct pvq_ctx {
     unsigned char *walk_blob = nullptr;
     pvq_walk_params walk;
     int amplitude;   // PVQ_AMP_NORM or PVQ_AMP_LS
-    // Per-coordinate index offsets for the D = 8 / 24-bit encoder: [7][K+1][K+1][2] words
-    // (coordinate, pulses left, magnitude, sign); nullptr when the configuration has none.
+    // Per-coordinate index offsets for the D = 8 / 24-bit encoder (PVQ_ENC8_WORDS words, padded to a multiple of 16 bytes);
+    // nullptr when the configuration has none.
     uint32_t *enc8_offs;
 };
 

@@ -3,7 +3,7 @@
 // format.  The point: project onto the l1 ball of radius K, round to nearest even, then move single pulses on
 // the coordinates of largest deviation (lowest coordinate on ties) until the count is K.  quantize_group8 finds
 // it without branches for D = 8 (count_wins); the D = 8 encoder and quantize_group_select<D>, for any D, take one
-// round per pulse to move (first_places8 for D = 8).
+// round per pulse to move (adjust_first_places8 for D = 8).
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -42,26 +42,43 @@ __device__ inline void count_wins(const float (&key)[8], int (&wins)[8])
     for (int j = 0; j < D; j++) wins[j] += j - lose[j];   // j beat every earlier coordinate it did not lose to
 }
 
-// adj[i] = coordinate i holds one of the `need` first places in the order of keys (largest first, lower coordinate
-// first on ties).  A round takes the largest key left (three-operand maxima), marks the first coordinate that has
-// it and takes its key out; a wave runs as many rounds as its lane with the largest `need`, two or three for
-// groups of 8, at 20 instructions each, against a hundred for count_wins: the form for kernels that are short of
-// vector instructions (the encoders).  Changes key.
-__device__ inline void first_places8(float (&key)[8], int need, bool (&adj)[8])
+// The repair of Sec. 2.5 for groups of 8: mag[i] += unit for the coordinates that hold the `need` first places in the order
+// of keys (largest first, lower coordinate first on ties; the bits of floats, of which the first `need` are positive).  A
+// round takes the largest key left (three-operand maxima), marks the first coordinate that has it and takes its key out; a
+// wave runs as many rounds as its lane with the largest `need`, two or three for groups of 8, against a hundred
+// instructions for count_wins: the form for kernels that are short of vector instructions (the encoders).  The first two
+// rounds keep their marks as masks (scalar registers; those of more rounds do not fit there).  Changes key.
+__device__ inline void adjust_first_places8(int (&key)[8], float need, float unit, float (&mag)[8])
 {
+    bool adj[8];
 #pragma unroll
     for (int i = 0; i < 8; i++) adj[i] = false;
-    for (int round = 0; round < 8; round++) {
-        if (!__any(round < need)) break;
-        const float best = fmaxf(fmaxf(fmaxf(key[0], key[1]), fmaxf(key[2], key[3])),
-                                 fmaxf(fmaxf(key[4], key[5]), fmaxf(key[6], key[7])));
-        bool taken = !(round < need);             // a lane that needs no more takes nothing
+    auto mark = [&](bool open) {                  // (a lane that needs no more takes nothing)
+        const int best = max(max(max(max(key[0], key[1]), key[2]), max(max(key[3], key[4]), key[5])), max(key[6], key[7]));
+        bool taken = !open;
 #pragma unroll
         for (int i = 0; i < 8; i++) {
-            const bool hit = !taken && key[i] == best;
-            adj[i] = adj[i] || hit;
-            taken = taken || hit;
-            key[i] = hit ? -INFINITY : key[i];
+            const bool equal = key[i] == best;
+            adj[i] = adj[i] || (equal && !taken);
+            taken = taken || equal;
+        }
+    };
+    mark(need > 0.0f);
+    if (__any(need > 1.0f)) {
+#pragma unroll
+        for (int i = 0; i < 8; i++) key[i] = adj[i] ? INT32_MIN : key[i];
+        mark(need > 1.0f);
+    }
+#pragma unroll
+    for (int i = 0; i < 8; i++) mag[i] += adj[i] ? unit : 0.0f;
+    if (__any(need > 2.0f)) {
+#pragma unroll 1
+        for (float round = 2.0f; round < 8.0f && __any(need > round); round += 1.0f) {
+#pragma unroll
+            for (int i = 0; i < 8; i++) { key[i] = adj[i] ? INT32_MIN : key[i]; adj[i] = false; }
+            mark(need > round);
+#pragma unroll
+            for (int i = 0; i < 8; i++) mag[i] += adj[i] ? unit : 0.0f;
         }
     }
 }
@@ -179,6 +196,36 @@ __device__ inline float quantize_group_select(const float (&w)[D], int K, int (&
         k -= mag;
     }
     return ss;
+}
+
+// ---- amplitude codes (Sec. 3.3 Step 5): how many of the 2^bits - 1 ascending edges are <= u ----------------------
+// A tree of nodes of three edges, one 16-byte read and three comparisons for two bits of the code (a bisection takes a
+// dependent read per bit): node v of level l holds every 4^(L-l-1)-th edge of the 4^(L-l) - 1 under it, L = (bits + 1) / 2
+// levels.  Absent edges (the fourth word, and two of three with one bit) are NaN, which no u reaches.
+constexpr int kEdgeNodes = 85;
+__device__ constexpr int edge_level_base(int l) { return ((1 << 2 * l) - 1) / 3; }
+
+__device__ inline void fill_edge_tree(float4 *tree, const float *__restrict__ edges, int bits, int tid, int lanes)
+{
+    const int L = (bits + 1) / 2;
+    for (int e = tid; e < 4 * edge_level_base(L); e += lanes) {
+        const int n = e >> 2, j = e & 3;
+        const int l = n < 1 ? 0 : n < 5 ? 1 : n < 21 ? 2 : 3;
+        const int at = ((n - edge_level_base(l)) * 4 + j + 1) * (1 << 2 * (L - l - 1)) - 1;
+        reinterpret_cast<float *>(tree)[e] = j < 3 && at < (1 << bits) - 1 ? edges[at] : __builtin_nanf("");
+    }
+}
+
+template <int BITS>
+__device__ inline uint32_t count_edges(const float4 *tree, float u)
+{
+    uint32_t v = 0;
+#pragma unroll
+    for (int l = 0; 2 * l < BITS; l++) {
+        const float4 n = tree[edge_level_base(l) + v];
+        v = 4 * v + (n.x <= u ? 1u : 0u) + (n.y <= u ? 1u : 0u) + (n.z <= u ? 1u : 0u);
+    }
+    return v;
 }
 
 }  // namespace pvq_quantize_dev

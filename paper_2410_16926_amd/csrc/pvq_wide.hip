@@ -503,7 +503,7 @@ __global__ __launch_bounds__(1024) void rotate_encode16_kernel(rotate_encode_par
     const int lane = threadIdx.x;
     const int64_t row = blockIdx.x / p.chunks_per_row;
     const int chunk = blockIdx.x - (int)(row * p.chunks_per_row);
-    const int64_t col0 = (int64_t)chunk * 8 * L + 8 * lane;   // first of this lane's 8 columns
+    const int64_t col0 = (int64_t)chunk * 8 * L + 8 * pvq_hadamard_dev::load_lane<LOG2N>(lane);   // first of the 8 columns that the lane loads
     const bool live = col0 < p.cols;                           // whole blocks and groups: a lane is in or out
 
     float v[8];
@@ -524,12 +524,9 @@ __global__ __launch_bounds__(1024) void rotate_encode16_kernel(rotate_encode_par
             }
         }
         if (p.signs) {
-            const uint2 s8 = *reinterpret_cast<const uint2 *>(p.signs + col0);
+            const uint2 bits = pvq_hadamard_dev::sign_bits(*reinterpret_cast<const uint2 *>(p.signs + col0));
 #pragma unroll
-            for (int j = 0; j < 8; j++) {
-                const uint32_t byte = ((j < 4 ? s8.x : s8.y) >> (8 * (j & 3))) & 0xFFu;
-                if (byte) v[j] = -v[j];
-            }
+            for (int j = 0; j < 8; j++) v[j] = pvq_hadamard_dev::with_sign(v[j], bits, j);
         }
     }
     pvq_hadamard_dev::hadamard_stages<LOG2N, false>(v, lane, p.log2n, smem, L);

@@ -347,6 +347,50 @@ def test_rotation_and_encoding_in_one_kernel_for_groups_of_8(rows, cols, block, 
     ctx.close()
 
 
+@pytest.mark.parametrize("rows,cols,K,bits,amplitude", [(5003, 96, 16, 1, "l2"), (4099, 160, 15, 2, "ls"), (2049, 32, 16, 4, "l2"),
+                                                        (6145, 96, 15, 8, "ls"), (4500, 224, 16, 0, "ls")])
+def test_rows_that_workgroups_take_in_turn(rows, cols, K, bits, amplitude):
+    # more rows than the machine holds workgroups (2048), waves without groups, both K with 24-bit indices, every code width
+    wf, wb = si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 710 + rows, rotate=False, bf16=True)
+    ctx, oe, oc = gu.make_ctx(8, K, bits, cols // 8)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    packed = pvq.pvq_encode(ctx, gu.to_dev_bf16(wb), want_pulses=True)
+    gu.assert_encode_equal(packed, oracle.encode(wf, 8, K, bits, oe, nthreads=8, amplitude=amplitude))
+    ctx.close()
+
+
+@pytest.mark.parametrize("K,raise_", [(16, True), (16, False), (15, True), (15, False)])
+def test_many_pulses_to_move_in_groups_of_8(K, raise_):
+    # projections whose fractions lie on one side, so that three or more pulses have to move, ties among them (a power of two
+    # times small integers: the projections of rows with equal magnitudes tie exactly)
+    rng = np.random.default_rng(7 + K)
+    rows, groups = 64, 32
+    base = rng.integers(0, 4, size=(rows, groups, 8)).astype(np.float64)
+    t = base + (rng.uniform(0.28, 0.48, size=base.shape) if raise_ else rng.uniform(0.52, 0.72, size=base.shape))
+    t[:, ::3, 1::2] = t[:, ::3, 0::2]
+    W = (t * rng.choice([-1.0, 1.0], size=t.shape) * 2.0 ** -6).astype(np.float32).reshape(rows, groups * 8)
+    for bits in (0, 2):
+        ctx, oe, oc = gu.make_ctx(8, K, bits, groups)
+        packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W), want_pulses=True)
+        gu.assert_encode_equal(packed, oracle.encode(W, 8, K, bits, oe))
+        ctx.close()
+
+
+@pytest.mark.parametrize("rows,cols,block", [(600, 8192, 8192), (1100, 4096, 4096), (2100, 2048, 64), (1030, 8192, 1024)])
+def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
+    # more rows than resident workgroups; any byte that is not zero is a sign
+    _, wb = si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 730 + block, rotate=False, bf16=True)
+    Xd = gu.to_dev_bf16(wb)
+    sgd = torch.from_numpy(np.random.default_rng(block).choice([0, 1, 2, 128, 255], size=cols).astype(np.uint8)).cuda()
+    ones = (sgd != 0).to(torch.uint8)
+    rotated = pvq.pvq_hadamard(Xd, block, ones, out_dtype=torch.float32)
+    assert torch.equal(rotated, pvq.pvq_hadamard(Xd, block, sgd, out_dtype=torch.float32))
+    ctx, oe, oc = gu.make_ctx(8, 16, 4, cols // 8)
+    packed, two = pvq.pvq_rotate_encode(ctx, Xd, block, sgd), pvq.pvq_encode(ctx, rotated)
+    assert torch.equal(two.index, packed.index) and torch.equal(two.scale, packed.scale) and torch.equal(two.rownorm, packed.rownorm)
+    ctx.close()
+
+
 def test_rotation_and_encoding_for_groups_of_8_limits():
     X = torch.zeros((2, 1024), dtype=torch.float32, device="cuda")
     ctx = pvq.pvq_ctx_create(8, 16)
