@@ -17,7 +17,8 @@
 //
 // Decoding (App. B.3): coordinate by coordinate, q = N(D,K) - 1 - index first; a coordinate is the last
 // threshold of its row that is not above q, and q loses it.  Few groups: a wave per group
-// (decode_wide_wave_kernel); many: a lane per group (decode_wide_kernel).
+// (decode_wide_wave_kernel); many: a lane per group, the rows in LDS (decode_wide_rows_kernel) or, for K > 255, in device
+// memory (decode_wide_kernel).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -31,6 +32,7 @@ namespace {
 
 typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
 template <int W>
 struct wint {
@@ -597,32 +599,10 @@ __device__ inline void store_values(const decode_wide_params &p, int64_t at, con
 
 // ---- many groups: a lane per group -------------------------------------------------------------------
 
-// Bytes of LDS per lane for the decoded point of a group of D: magnitudes and signs.  With K <= 255 a magnitude is a
-// byte and the signs are a bit each (D + D/8 bytes); else int16 values.  Rounded up to an odd number of words, so
-// that the lanes' rows spread over the banks.
-__host__ __device__ inline int decode_point_bytes(int D, int K)
-{
-    const int words = K <= 255 ? D / 4 + D / 32 : D / 2;
-    return 4 * (words | 1);
-}
-
-// The walk of one lane.  A coordinate takes three dependent trips to the tables, of which the L1 and L2 hold the few lines
-// of a row that are in use: the guess of q's bucket, the four keys behind it, and the threshold found.  Equal keys
-// (about one comparison in a million, and the all-zero groups) show as a borrow of the subtraction, after which the
-// threshold before is taken.
-// Bound by its chain of about 140 instructions a coordinate (88 vector, 44 scalar) and three trips: at 2048 rows of 8192 the
-// vector ALUs issue for 38 of 156 us, two waves are on a SIMD, and they wait for 73 % of their time.  D = 128, K = 187, 8192-wide rows, 512 / 2048 / 4096 of them:
-// 97 / 157 / 162 us, where the same search with one multi-word comparison per magnitude and the subtractions of the
-// enumeration's own recursion took 208 / 261 / 355.  (With the thresholds around the wave's pulses in LDS, loaded a pair of
-// rows ahead, 112 / 128 / 252: half as many waves fit a unit then.)
-template <int CP, int W>
-struct lane_walk {
-    static constexpr int D = 64 * CP;
-    const decode_wide_params &p;
-    unsigned char *mine;
+// q of one lane's group.
+template <int W>
+struct lane_q {
     uint32_t q[W];
-    int k, n2, i;
-    uint32_t sign_byte;
 
     // pvq_wide_key of q, which lies below 2^(32 WP): its leading word and the one below are nearly always among the upper four
     template <int WP>
@@ -642,19 +622,17 @@ struct lane_walk {
             a = lower ? b : a; b = lower ? 0u : b; length -= lower ? 32 : 0;
         }
         const int lead = __builtin_clz(a | 1u);
-        const uint32_t two = __builtin_amdgcn_alignbit(a, b, (32 - lead) & 31);          // the 32 bits from the leading one on
-        uint32_t key = ((uint32_t)(length - lead) << 22) | ((lead ? two : a) >> 10);
-        if (WP > 4) { if (__any(a == 0)) key = a == 0 ? pvq_wide_key(q, WP) : key; }
+        const uint32_t from_one = (uint32_t)((((uint64_t)a << 32 | b) << lead) >> 32);   // the 32 bits from the leading one on
+        uint32_t key = __builtin_amdgcn_alignbit((uint32_t)(length - lead), from_one, 10);
+        if (WP > 4) { if (a == 0) key = pvq_wide_key(q, WP); }
         else key = a == 0 ? 0u : key;
         return key;
     }
 
-    // one coordinate; every q of the wave lies below 2^(32 WP)
-    template <int WP>
-    __device__ inline void step()
+    // The coordinate's place in a row by the tables in device memory, two dependent trips: the guess of q's bucket, the four
+    // keys behind it.  (Equal keys: one too high, which the subtraction shows by its borrow.)
+    __device__ inline static uint32_t place_by_guess(const decode_wide_params &p, uint32_t row, uint32_t kq, int k)
     {
-        const uint32_t row = (uint32_t)(D - 1 - i);
-        const uint32_t kq = key_of_q<WP>();
         const uint32_t *keys = p.tab_key + row * (uint32_t)p.key_len;
         uint32_t j = p.tab_guess[row * (uint32_t)p.buckets + (kq >> 19 & ~7u) + (kq >> 18 & 7u)];
         uint32_t more;
@@ -664,43 +642,337 @@ struct lane_walk {
             more = (ke[0] <= kq ? 1u : 0u) + (ke[1] <= kq ? 1u : 0u) + (ke[2] <= kq ? 1u : 0u) + (ke[3] <= kq ? 1u : 0u);
             j += more;
         } while (__any(more == 4));                                // (ends: the keys behind a row are all ones)
-        j = min(j, (uint32_t)(2 * k + 1));
+        return min(j, (uint32_t)(2 * k + 1));
+    }
+
+    // the first WP words (in whole fours) of threshold j of a row in device memory
+    template <int WP>
+    __device__ inline static void read_threshold(const decode_wide_params &p, uint32_t row, uint32_t j, uint32_t (&t)[(WP + 3) / 4 * 4])
+    {
         const uint32_t *trow = p.tab_t + row * (uint32_t)(p.row_len * W);
-        uint32_t t[(WP + 3) / 4 * 4];
-        auto read = [&] {
 #pragma unroll
-            for (int x = 0; x < (WP + 3) / 4; x++) {
-                const uint4 v = *reinterpret_cast<const uint4 *>(trow + (j * W + 4 * x));
-                t[4 * x] = v.x; t[4 * x + 1] = v.y; t[4 * x + 2] = v.z; t[4 * x + 3] = v.w;
-            }
-        };
-        read();
+        for (int x = 0; x < (WP + 3) / 4; x++) {
+            const uint4 v = *reinterpret_cast<const uint4 *>(trow + (j * W + 4 * x));
+            t[4 * x] = v.x; t[4 * x + 1] = v.y; t[4 * x + 2] = v.z; t[4 * x + 3] = v.w;
+        }
+    }
+
+    // q -= t, the threshold of place j of the row, or of the place below where that one is above q
+    template <int WP>
+    __device__ inline void subtract(const decode_wide_params &p, uint32_t row, uint32_t &j, uint32_t (&t)[(WP + 3) / 4 * 4])
+    {
         uint32_t br = 0;
 #pragma unroll
         for (int x = 0; x < WP; x++) q[x] = __builtin_subc(q[x], t[x], br, &br);
-        if (__any(br)) {
-            while (br) {                                           // (ends: T_0 = 0)
-                uint32_t c = 0;
+        while (br) {                                               // (ends: T_0 = 0)
+            uint32_t c = 0;
 #pragma unroll
-                for (int x = 0; x < WP; x++) q[x] = __builtin_addc(q[x], t[x], c, &c);
-                j--;
-                read();
-                br = 0;
+            for (int x = 0; x < WP; x++) q[x] = __builtin_addc(q[x], t[x], c, &c);
+            j--;
+            read_threshold<WP>(p, row, j, t);
+            br = 0;
 #pragma unroll
-                for (int x = 0; x < WP; x++) q[x] = __builtin_subc(q[x], t[x], br, &br);
+            for (int x = 0; x < WP; x++) q[x] = __builtin_subc(q[x], t[x], br, &br);
+        }
+    }
+};
+
+// ---- many groups: a lane per group, the rows of the tables in LDS ------------------------------------------
+// All lanes of a workgroup are at the same coordinate, so they need the same row, of it the places from their largest 2 k + 1
+// down (k pulses left; a coordinate of magnitude m is 2 m places below 2 k), and rows of fewer dimensions in fewer words.  The
+// rows go through LDS in turn, requested three coordinates ahead; the window is a matter of the workgroup's
+// largest and smallest k, looked at every eighth coordinate (k only falls, the margin below covers the rest).
+// A coordinate takes three keys (places 3, 7 and 11 below 2 k), the four keys of the block of places they point to, and the
+// threshold: three dependent reads of LDS.  A lane whose place is further down, or lies below the window (points that have
+// nearly all their pulses in a few coordinates), looks it up in device memory.
+// Bound by the walk's chain, about 150 instructions and the three reads a coordinate, 0.55 us of a wave alone; from two
+// waves a SIMD on by their issue (90 vector and 45 scalar instructions).  D = 128, K = 187, 8192-wide rows, 512 / 1024 / 2048 /
+// 4096 of them: 72 / 75 / 84 / 108 us; with guess, keys and thresholds in device memory 95 / 100 / 155 / 161.  D = 64, K = 96:
+// 37 / 41 / 53 / 97, before 55 / 57 / 86 / 104.  Four coordinates share a turn of the loop, so that slots and shifts are known
+// when it is compiled (one at a time: 104 / 104 / 117 us for the first three).
+constexpr int kRowWindow = 256;       // places of a row in LDS
+constexpr int kRowPad = 16;           // keys in front of them: zeros
+
+// A row in LDS: kT pieces of 16 bytes a lane for the thresholds, kK words a lane for the keys behind their padding.
+constexpr int rows_pieces(int W, int lanes) { return (kRowWindow * W / 4 + lanes - 1) / lanes; }
+constexpr int rows_keys(int lanes) { return (kRowWindow + lanes - 1) / lanes; }
+constexpr int kPointWords = 19;       // 64 coordinates on their way out: 16 words of magnitudes, 2 of signs, and one for the banks' sake
+constexpr int kRowSlots = 4;          // rows in LDS: the present coordinate's, the next two, and the one on its way
+constexpr size_t decode_rows_lds(int W, int lanes)
+{
+    const size_t rows = (size_t)kRowSlots * (16 * rows_pieces(W, lanes) * lanes + 4 * (kRowPad + rows_keys(lanes) * lanes)) + (lanes / 64) * 8;
+    return std::max(rows, (size_t)4 * kPointWords * lanes);
+}
+
+template <int CP, int W, int LANES>
+struct rows_walk : lane_q<W> {
+    using lane_q<W>::q;
+    static constexpr int D = 64 * CP;
+    static constexpr int kT = rows_pieces(W, LANES), kK = rows_keys(LANES);
+    static constexpr uint32_t kTBytes = 16 * kT * LANES, kKBytes = 4 * (kRowPad + kK * LANES);   // of a slot
+    const decode_wide_params &p;
+    const uint32_t ts, ks;            // LDS addresses of the slots' thresholds, keys
+    int *const stat;                  // LDS: every wave's largest and smallest 2 k
+    const int tid, wave;
+    const bool walks;                 // the wave has a group to walk for
+    int k2, n2, i;                    // 2 k, 4 sum m^2
+    uint32_t sign, mag;               // the last coordinates' places' lowest bits, the latest on top; their magnitudes, a byte each
+    int lo[kRowSlots];                // first place of a slot's window
+    int latest_lo, latest_count;      // the window of the rows requested from now on
+
+    template <typename T>
+    __device__ __forceinline__ static T from_lds(uint32_t at) { return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at); }
+
+    __device__ inline void set_window(int most2, int least2)
+    {
+        latest_lo = __builtin_amdgcn_readfirstlane(max(max(least2 - 64, most2 + 2 - kRowWindow), 0));
+        latest_count = __builtin_amdgcn_readfirstlane(most2 + 2) - latest_lo;
+    }
+    // The window's places of coordinate c's row (past the last: row 0, not used) straight into slot S.  The compiler does not
+    // see that these loads write LDS; a wave has kT + kK of them on their way for a row (lanes past the window load its end
+    // once more, or what lies behind it in the tables, into the slot's rest) and step waits for them by that number, in order.
+    template <int S>
+    __device__ inline void request(int c)
+    {
+        // (the same for the workgroup)
+        latest_lo = __builtin_amdgcn_readfirstlane(latest_lo); latest_count = __builtin_amdgcn_readfirstlane(latest_count);
+        lo[S] = latest_lo;
+        const uint32_t row = (uint32_t)max(D - 1 - c, 0);
+        const unsigned char *t = reinterpret_cast<const unsigned char *>(p.tab_t) + (row * (uint32_t)p.row_len + (uint32_t)latest_lo) * (4u * W);
+        const unsigned char *key = reinterpret_cast<const unsigned char *>(p.tab_key) + (row * (uint32_t)p.key_len + (uint32_t)latest_lo) * 4u;
+        const int last = latest_count * (4 * W) - 16;
+#pragma unroll
+        for (int x = 0; x < kT; x++) {
+            const uint32_t from = (uint32_t)min(16 * tid, max(last - x * LANES * 16, 0));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         : : "s"(ts + (S * kTBytes + (uint32_t)(x * LANES * 16)) + (uint32_t)(wave * 1024)), "v"(from), "s"(t + x * LANES * 16) : "memory", "m0");
+        }
+#pragma unroll
+        for (int x = 0; x < kK; x++) {
+            const uint32_t from = (uint32_t)min(4 * tid, max(4 * latest_count - 4 - x * LANES * 4, 0));
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
+                         : : "s"(ks + (S * kKBytes + (uint32_t)(4 * kRowPad + x * LANES * 4)) + (uint32_t)(wave * 256)), "v"(from), "s"(key + x * LANES * 4) : "memory", "m0");
+        }
+    }
+    // before the first coordinate: all of a lane's pulses are left
+    __device__ inline void start()
+    {
+        set_window(2 * p.K, 2 * p.K);
+        request<0>(0);
+        request<1>(1);
+        request<2>(2);
+    }
+
+    // coordinate i + S, i a multiple of four; every q of the wave lies below 2^(32 WP)
+    template <int WP, int S>
+    __device__ inline void step()
+    {
+        // the row is in LDS once only the next two rows' loads are on their way, and the row before it has been used
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * (kT + kK)) : "memory");
+        if (S == 0 && (i & 4) == 0 && i > 0) {
+            int most2 = 0, least2 = 2 * p.K;
+#pragma unroll
+            for (int w = 0; w < LANES / 64; w++) { most2 = max(most2, stat[2 * w]); least2 = min(least2, stat[2 * w + 1]); }
+            set_window(most2, min(least2, most2));
+        }
+        request<(S + 3) % kRowSlots>(i + S + 3);
+        if (!walks) return;
+        const uint32_t row = (uint32_t)(D - 1 - S - i);
+        const uint32_t kq = this->template key_of_q<WP>();
+        // places below 2 k whose threshold is above q: three keys, then the four of the block of places they point to
+        const int first = __builtin_amdgcn_readfirstlane(lo[S]);
+        const int top = max(k2 - first, -1);
+        uint32_t keys = ks + (S * kKBytes + 4 * (kRowPad - 11));
+        asm volatile("" : "+s"(keys));                             // (one address for the reads' small offsets)
+        const uint32_t at = keys + 4u * (uint32_t)top;
+        int down = (from_lds<uint32_t>(at + 32) > kq ? -4 : 0) + (from_lds<uint32_t>(at + 16) > kq ? -4 : 0) + (from_lds<uint32_t>(at) > kq ? -4 : 0);
+        const uint32_t block = keys + 4u * (uint32_t)(top + down);
+        down -= from_lds<uint32_t>(block + 44) > kq ? 1 : 0; down -= from_lds<uint32_t>(block + 40) > kq ? 1 : 0;
+        down -= from_lds<uint32_t>(block + 36) > kq ? 1 : 0; down -= from_lds<uint32_t>(block + 32) > kq ? 1 : 0;
+        const int in_window = top + down;
+        uint32_t j = (uint32_t)(first + in_window);
+        const uint32_t entry = ts + (uint32_t)__mul24(max(in_window, 0), 4 * W);
+        uint32_t t[(WP + 3) / 4 * 4];
+#pragma unroll
+        for (int x = 0; x < (WP + 3) / 4; x++) {
+            const u32x4 v = from_lds<u32x4>(entry + (S * kTBytes + 16 * x));
+            t[4 * x] = v[0]; t[4 * x + 1] = v[1]; t[4 * x + 2] = v[2]; t[4 * x + 3] = v[3];
+        }
+        // below the window, or further down than the keys that were looked at
+        const bool elsewhere = in_window < 0 || down == -16;
+        if (elsewhere) {
+            j = lane_q<W>::place_by_guess(p, row, kq, k2 >> 1);
+            lane_q<W>::template read_threshold<WP>(p, row, j, t);
+            // used here, so that the compiler's wait for it stands here: behind the branch it would be one for the rows just
+            // requested as well
+#pragma unroll
+            for (int x = 0; x < (WP + 3) / 4 * 4; x++) asm volatile("" : "+v"(t[x]));
+        }
+        this->template subtract<WP>(p, row, j, t);
+        const int left2 = (int)(j & ~1u), d = k2 - left2;
+        k2 = left2;
+        n2 = (int)__umul24((uint32_t)d, (uint32_t)d) + n2;
+        mag = S == 0 ? (uint32_t)d >> 1 : (uint32_t)d << (8 * S - 1) | mag;
+        sign = __builtin_amdgcn_alignbit(j, sign, 1);
+    }
+
+    // mags, signs: the point
+    template <int WP>
+    __device__ __forceinline__ void four_steps(uint32_t (&mags)[D / 4], uint32_t (&signs)[D / 32])
+    {
+        step<WP, 0>(); step<WP, 1>(); step<WP, 2>(); step<WP, 3>();
+        const int at = __builtin_amdgcn_readfirstlane(i) >> 2;
+        mags[at] = mag;
+#pragma unroll
+        for (int x = 0; x < D / 32; x++) signs[x] = at == 8 * x + 7 ? ~sign : signs[x];
+        if (i & 4) {
+            uint32_t most2 = walks ? (uint32_t)k2 : 0u, least2 = walks ? (uint32_t)k2 : ~0u;
+#define PVQ_STEP(CTRL, ROWS) most2 = max(most2, dpp_move<CTRL, ROWS>(most2, 0u)); least2 = min(least2, dpp_move<CTRL, ROWS>(least2, ~0u));
+            PVQ_WAVE_STEPS(PVQ_STEP)
+#undef PVQ_STEP
+            if ((tid & 63) == 63) { stat[2 * wave] = (int)most2; stat[2 * wave + 1] = (int)min(least2, 0x7FFFFFFFu); }
+        }
+        i += 4;
+    }
+
+    // q shrinks as it goes: the walk runs in as many words as the wave's largest q needs, or one more
+    template <int WP>
+    __device__ __forceinline__ void walk(uint32_t (&mags)[D / 4], uint32_t (&signs)[D / 32])
+    {
+        while (i < D && (WP <= 2 || __builtin_amdgcn_ballot_w64((q[WP - 1] | q[WP - 2]) != 0))) four_steps<WP>(mags, signs);
+        if constexpr (WP > 2) walk<WP - 2>(mags, signs);
+    }
+};
+
+template <int CP, int W, int LANES>
+__global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_kernel(decode_wide_params p)
+{
+    extern __shared__ __align__(16) uint32_t lds_words[];
+    constexpr int D = 64 * CP;
+    using walk_t = rows_walk<CP, W, LANES>;
+    uint32_t *keys = lds_words + kRowSlots * walk_t::kTBytes / 4;
+    int *stat = reinterpret_cast<int *>(keys + kRowSlots * walk_t::kKBytes / 4);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t g0 = (int64_t)blockIdx.x * LANES;
+    // the lane's group (lanes behind the last group take that one, and write nothing)
+    const int64_t gid = std::min<int64_t>(g0 + tid, p.total_groups - 1);
+    const int64_t row = gid / p.groups, g = gid - row * p.groups;
+
+    // q = N(D,K) - 1 - index; an index that is no codeword decodes to zeros
+    uint32_t q[W], br = 0, any = 0;
+#pragma unroll
+    for (int i = 0; i < W; i++) {
+        const uint32_t w = index_word(p.index + row * p.index_row_words, p, g, i);
+        any |= w;
+        q[i] = __builtin_subc(p.last_index[i], w, br, &br);
+    }
+    const bool valid = !br, one_hot = any == 0;
+    // Groups that are no codeword, and those with index 0, (0, ..., 0, K), zeros among them, whose k does not fall until the end,
+    // would widen the workgroup's windows: they walk another group of the wave once more, and get their points afterwards.
+    const uint64_t walkers = __ballot(valid && !one_hot);
+    const int source = valid && !one_hot ? lane : walkers ? __builtin_ctzll(walkers) : 0;
+#pragma unroll
+    for (int i = 0; i < W; i++) q[i] = walkers ? (uint32_t)__shfl((int)q[i], source, 64) : 0u;
+
+    if (tid < kRowSlots * kRowPad) keys[tid / kRowPad * (walk_t::kKBytes / 4) + tid % kRowPad] = 0;
+    auto lds_address = [](void *at) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)at; };
+    walk_t walk{{}, p, lds_address(lds_words), lds_address(keys), stat, tid, wave, walkers != 0};
+#pragma unroll
+    for (int i = 0; i < W; i++) walk.q[i] = q[i];
+    walk.k2 = 2 * p.K; walk.n2 = 0; walk.i = 0; walk.sign = walk.mag = 0;
+    uint32_t mags[D / 4], signs[D / 32] = {};   // (registers, indexed by what is the same for all lanes)
+    walk.start();
+    walk.template walk<W>(mags, signs);
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");             // (the workgroup's LDS is not given back before the last loads into it)
+
+    int n2 = walk.n2 >> 2;
+    if (valid && one_hot) {
+#pragma unroll
+        for (int x = 0; x < D / 4; x++) mags[x] = x == D / 4 - 1 ? (uint32_t)p.K << 24 : 0u;
+#pragma unroll
+        for (int x = 0; x < D / 32; x++) signs[x] = 0;
+        n2 = p.K * p.K;
+    }
+    const float gain = valid ? p.scale[gid] / sqrtf((float)n2) : 0.0f;
+
+    // The wave's groups out, 64 values of each at a time: through LDS (where the rows were, once all waves are done with
+    // them), from which 8 lanes take a group's 64 values.
+    __syncthreads();
+    uint32_t *points = lds_words + wave * 64 * kPointWords;
+    const int64_t at = row * p.ldw + g * D;
+    const int part = lane % 8;
+#pragma unroll 1
+    for (int half = 0; half < D / 64; half++) {
+#pragma unroll
+        for (int x = 0; x < 16; x++) points[lane * kPointWords + x] = D == 128 && half ? mags[D / 4 - 16 + x] : mags[x];
+#pragma unroll
+        for (int x = 0; x < 2; x++) points[lane * kPointWords + 16 + x] = D == 128 && half ? signs[D / 32 - 2 + x] : signs[x];
+#pragma unroll 2
+        for (int s0 = 0; s0 < 64; s0 += 8) {
+            const int s = s0 + lane / 8;
+            const float gs = __shfl(gain, s, 64);
+            const int64_t to = ((int64_t)__shfl((int)(at >> 32), s, 64) << 32 | (uint32_t)__shfl((int)at, s, 64)) + half * 64 + 8 * part;
+            const uint32_t *point = points + s * kPointWords;
+            const uint32_t m[2] = {point[2 * part], point[2 * part + 1]}, negative = point[16 + part / 4] >> (8 * (part & 3));
+            float v[8];
+#pragma unroll
+            for (int x = 0; x < 8; x++) {
+                const int mag = (int)(m[x / 4] >> (8 * (x & 3)) & 0xFFu);
+                v[x] = gs * (float)((negative >> x & 1u) ? -mag : mag);
+            }
+            if (g0 + wave * 64 + s >= p.total_groups) continue;
+            if (p.out_dtype == PVQ_F32) {
+                float *o = reinterpret_cast<float *>(p.W_out) + to;
+                *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
+                *reinterpret_cast<float4 *>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+            } else {
+                uint32_t u[4];
+#pragma unroll
+                for (int x = 0; x < 4; x++) {
+                    if (p.out_dtype == PVQ_F16) {
+                        u[x] = __builtin_bit_cast(uint32_t, __halves2half2(__float2half_rn(v[2 * x]), __float2half_rn(v[2 * x + 1])));
+                    } else {
+                        const f32x2_t pair = {v[2 * x], v[2 * x + 1]};
+                        u[x] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
+                    }
+                }
+                *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(p.W_out) + to) = make_uint4(u[0], u[1], u[2], u[3]);
             }
         }
+    }
+}
+
+// ---- K > 255: a lane per group, the tables in device memory -------------------------------------------------
+// (points no longer fit a byte per magnitude, rows of thresholds take up to 128 KB)
+// Bytes of LDS per lane for the decoded point: int16 values, rounded up to an odd number of words.
+__host__ __device__ constexpr int decode_point_bytes16(int D) { return 4 * (D / 2 | 1); }
+
+// The walk of one lane.  A coordinate takes three dependent trips to the tables, of which the L1 and L2 hold the few lines
+// of a row that are in use: the guess of q's bucket, the four keys behind it, and the threshold found.  Equal keys
+// (about one comparison in a million, and the all-zero groups) show as a borrow of the subtraction, after which the
+// threshold before is taken.  Bound by its chain of about 140 instructions a coordinate and three trips.
+template <int CP, int W>
+struct lane_walk : lane_q<W> {
+    using lane_q<W>::q;
+    static constexpr int D = 64 * CP;
+    const decode_wide_params &p;
+    int16_t *mine;
+    int k, n2, i;
+
+    // one coordinate; every q of the wave lies below 2^(32 WP)
+    template <int WP>
+    __device__ inline void step()
+    {
+        const uint32_t row = (uint32_t)(D - 1 - i);
+        uint32_t j = lane_q<W>::place_by_guess(p, row, this->template key_of_q<WP>(), k);
+        uint32_t t[(WP + 3) / 4 * 4];
+        lane_q<W>::template read_threshold<WP>(p, row, j, t);
+        this->template subtract<WP>(p, row, j, t);
         const int C = (int)(j >> 1), m = k - C;
-        const uint32_t negative = ~j & 1u;
         k = C;
         n2 += __mul24(m, m);
-        if (p.K <= 255) {
-            mine[i] = (unsigned char)m;
-            sign_byte = ((i & 7) ? sign_byte : 0u) | (negative << (i & 7));
-            if ((i & 7) == 7) mine[D + (i >> 3)] = (unsigned char)sign_byte;
-        } else {
-            reinterpret_cast<int16_t *>(mine)[i] = (int16_t)(negative ? -m : m);
-        }
+        mine[i] = (int16_t)(j & 1u ? m : -m);
         i++;
     }
 
@@ -713,14 +985,12 @@ struct lane_walk {
     }
 };
 
-// A wave is a workgroup, with decode_point_bytes of LDS per lane.
+// A wave is a workgroup, with decode_point_bytes16 of LDS per lane.
 template <int CP, int W>
 __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    constexpr int D = 64 * CP;
-    const bool bytes = p.K <= 255;
-    const int LB = decode_point_bytes(D, p.K);
+    constexpr int D = 64 * CP, LB = decode_point_bytes16(D);
     const int lane = threadIdx.x;
     const int64_t g0 = (int64_t)blockIdx.x * 64;
     const int count = (int)std::min<int64_t>(64, p.total_groups - g0);
@@ -730,7 +1000,7 @@ __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
     const uint32_t ahead = (uint32_t)out_g + (uint32_t)std::min(lane, count - 1);
     const int64_t mine = g0 + std::min(lane, count - 1);
     const int64_t row = out_row + ahead / (uint32_t)p.groups, g = ahead % (uint32_t)p.groups;
-    lane_walk<CP, W> walk{p, lds_raw + (size_t)lane * LB, {}, p.K, 0, 0, 0u};
+    lane_walk<CP, W> walk{{}, p, reinterpret_cast<int16_t *>(lds_raw + (size_t)lane * LB), p.K, 0, 0};
     // q = N(D,K) - 1 - index; an index that is no codeword decodes to zeros
     uint32_t br = 0;
 #pragma unroll
@@ -748,24 +1018,9 @@ __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
     const unsigned char *pt = lds_raw;
     for (int s = 0; s < count; s++) {
         const float gs = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(gain), s));
-        int y[CP];
-        if (bytes) {
-            uint32_t mags;
-            if constexpr (CP == 2) mags = *reinterpret_cast<const uint16_t *>(pt + 2 * lane);
-            else mags = pt[lane];
-            const uint32_t signs = pt[D + (CP * lane >> 3)] >> (CP * lane & 7);
-#pragma unroll
-            for (int j = 0; j < CP; j++) {
-                const int mag = (int)(mags >> (8 * j) & 0xFFu);
-                y[j] = (signs >> j & 1u) ? -mag : mag;
-            }
-        } else {
-#pragma unroll
-            for (int j = 0; j < CP; j++) y[j] = reinterpret_cast<const int16_t *>(pt)[CP * lane + j];
-        }
         float v[CP];
 #pragma unroll
-        for (int j = 0; j < CP; j++) v[j] = gs * (float)y[j];
+        for (int j = 0; j < CP; j++) v[j] = gs * (float)reinterpret_cast<const int16_t *>(pt)[CP * lane + j];
         store_values<CP>(p, at, v);
         pt += LB;
         at += D;
@@ -1056,11 +1311,42 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
     return hipGetLastError();
 }
 
-// Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full
-// (8192-wide rows of D = 128, K = 187: 23 us for 64 groups, 30 for 1024, 75 for 4096, 142 for 8192); a lane per group
-// takes the one walk of a wave whatever their number, until there are several waves per SIMD (95 us from 64 groups to
-// 32768, 157 for 131072, 162 for 262144).  D = 64, K = 96: 13, 17 (2048), 62 (8192) against 53, the same line.
-constexpr int64_t kFewGroups = 5120;
+// Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full; a
+// lane per group takes the one walk of a wave whatever their number, until there are several waves per SIMD.  8192-wide
+// rows, us, wave / lane: D = 128, K = 187: 23 (64 groups), 35 (2048), 67 / 70 (3072), 73 / 70 (3584), 77 / 70 (4096);
+// K = 84: 48 / 66 (3072), 59 / 66, 71 / 67; D = 64, K = 96: 25 / 33 (3072), 37 / 33 (4096).
+constexpr int64_t kFewGroups = 3584;
+
+// Lanes of a workgroup whose rows of the tables go through LDS: the fewest, from 128 on, with which the groups take one place
+// on each of the 256 units, up to 512.  (64 lanes, a wave that loads its rows alone: 8192 groups of 128 in 80 us, with 128
+// lanes 70; 256 at most: 262144 groups in 151 us, with 512 lanes, two workgroups to a unit, 109.)
+static int rows_lanes(int64_t groups)
+{
+    int lanes = 128;
+    while (lanes < 512 && groups > (int64_t)256 * lanes) lanes *= 2;
+    return lanes;
+}
+
+template <int CP, int W, int LANES>
+static hipError_t launch_rows(const decode_wide_params &p, size_t lds, hipStream_t s)
+{
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(decode_wide_rows_kernel<CP, W, LANES>),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES), lds, s, p);
+    return hipSuccess;
+}
+
+#define PVQ_WIDE_DEC_W(CP)                                  \
+    switch (c->words) {                                     \
+    case 4: PVQ_WIDE_DEC(CP, 4); break;                     \
+    case 8: PVQ_WIDE_DEC(CP, 8); break;                     \
+    case 12: PVQ_WIDE_DEC(CP, 12); break;                   \
+    default: PVQ_WIDE_DEC(CP, 16); break;                   \
+    }
+#define PVQ_WIDE_DEC_DW if (c->D == 128) { PVQ_WIDE_DEC_W(2) } else { PVQ_WIDE_DEC_W(1) }
 
 hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
@@ -1073,24 +1359,31 @@ hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
     p.W_out = a.W_out;
     for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
     if ((p.total_groups + 63) / 64 > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const bool few = p.total_groups <= kFewGroups;
-    const size_t lds = few ? (size_t)kWavesFew * 4 * 1024 * (c->words / 4 + 1) + 16 : (size_t)64 * decode_point_bytes(c->D, c->K);
-    const int per_block = few ? kWavesFew : 64;
-    const dim3 grid((unsigned)((p.total_groups + per_block - 1) / per_block)), blk(few ? 64 * kWavesFew : 64);
-#define PVQ_WIDE_DEC(CP, W)                                                                                              \
-    do {                                                                                                                 \
-        if (few) hipLaunchKernelGGL((decode_wide_wave_kernel<CP, W>), grid, blk, lds, s, p);                             \
-        else hipLaunchKernelGGL((decode_wide_kernel<CP, W>), grid, blk, lds, s, p);                                      \
-    } while (0)
-#define PVQ_WIDE_DEC_W(CP)                                  \
-    switch (c->words) {                                     \
-    case 4: PVQ_WIDE_DEC(CP, 4); break;                     \
-    case 8: PVQ_WIDE_DEC(CP, 8); break;                     \
-    case 12: PVQ_WIDE_DEC(CP, 12); break;                   \
-    default: PVQ_WIDE_DEC(CP, 16); break;                   \
-    }
-    if (c->D == 128) { PVQ_WIDE_DEC_W(2) } else { PVQ_WIDE_DEC_W(1) }
-#undef PVQ_WIDE_DEC_W
+    const int64_t total = p.total_groups;
+    if (total <= kFewGroups) {
+        const size_t lds = (size_t)kWavesFew * 4 * 1024 * (c->words / 4 + 1) + 16;
+#define PVQ_WIDE_DEC(CP, W) \
+    hipLaunchKernelGGL((decode_wide_wave_kernel<CP, W>), dim3((unsigned)((total + kWavesFew - 1) / kWavesFew)), dim3(64 * kWavesFew), lds, s, p)
+        PVQ_WIDE_DEC_DW
 #undef PVQ_WIDE_DEC
+    } else if (c->K > 255) {
+        const size_t lds = (size_t)64 * decode_point_bytes16(c->D);
+#define PVQ_WIDE_DEC(CP, W) hipLaunchKernelGGL((decode_wide_kernel<CP, W>), dim3((unsigned)((total + 63) / 64)), dim3(64), lds, s, p)
+        PVQ_WIDE_DEC_DW
+#undef PVQ_WIDE_DEC
+    } else {
+        const int lanes = rows_lanes(total);
+        const size_t lds = decode_rows_lds(c->words, lanes);
+        hipError_t e = hipSuccess;
+#define PVQ_WIDE_DEC(CP, W)                                                        \
+    switch (lanes) {                                                               \
+    case 128: e = launch_rows<CP, W, 128>(p, lds, s); break;                       \
+    case 256: e = launch_rows<CP, W, 256>(p, lds, s); break;                       \
+    default: e = launch_rows<CP, W, 512>(p, lds, s); break;                        \
+    }
+        PVQ_WIDE_DEC_DW
+#undef PVQ_WIDE_DEC
+        if (e != hipSuccess) return e;
+    }
     return hipGetLastError();
 }

@@ -265,10 +265,30 @@ def test_products_on_the_walk_at_the_edges_of_tiles(D, K, bits, rows, groups):
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
-    # a wave per group up to 5120 groups, a lane per group beyond (5121: a last wave with one group); rows of
+    # a wave per group up to 3584 groups, a lane per group beyond (5121: a last wave with one group); rows of
     # thresholds just shorter and just longer than a window, points kept as bytes and as int16
     X = si.adversarial_groups(1 << 13, D, seed=K)[:rows * groups].reshape(rows, groups * D)
     run_long_groups(np.ascontiguousarray(X), D, K)
+
+
+@pytest.mark.parametrize("D,K,rows,groups", [(64, 40, 3001, 22), (128, 84, 1029, 33), (128, 187, 523, 64), (64, 255, 419, 9), (128, 255, 131, 29)])
+def test_long_groups_with_the_rows_of_the_tables_in_lds(D, K, rows, groups):
+    # workgroups of 128, 256 and 512 lanes with a ragged last one; integers of 4 to 16 words; groups of one workgroup whose
+    # pulses run out early, late and not before the end side by side (places below the window), zeros, rows that are no codewords
+    X = si.activation_matrix(rows, D * groups, seed=D + K, rotate=False, bf16=False)
+    odd = si.adversarial_groups(1 << 12, D, seed=K)
+    X.reshape(rows * groups, D)[5::41] = odd[np.arange(rows * groups)[5::41] % len(odd)]
+    X[rows // 2] = 0.0
+    run_long_groups(X, D, K)
+    ctx = pvq.pvq_ctx_create(D, K)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(X))
+    before = pvq.pvq_decode(ctx, packed, torch.float32)
+    packed.index[rows // 3] = -1
+    after = pvq.pvq_decode(ctx, packed, torch.float32)
+    assert torch.all(after[rows // 3] == 0)
+    keep = torch.arange(rows, device="cuda") != rows // 3
+    assert torch.equal(after[keep], before[keep])
+    ctx.close()
 
 
 @pytest.mark.parametrize("tokens,hidden,block,bits_per_value,bf16", [(5, 8192, 8192, 3, True), (3, 16384, 8192, 3, False),
