@@ -35,11 +35,8 @@
 #include <atomic>
 
 #include "pvq_internal.h"
-#include "pvq_quantize_dev.h"
 
 namespace {
-
-using namespace pvq_quantize_dev;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -127,7 +124,7 @@ __device__ inline void count_before(const int (&key)[C], const int (&th)[C][4], 
     }
 }
 
-// The quantiser of Sec. 2.5 (pvq_quantize_dev.h) with the group's coordinates C j .. C j + C - 1 in lane j of its row: the
+// The quantiser of Sec. 2.5 (as in pvq_quantize_dev.h) with the group's coordinates C j .. C j + C - 1 in lane j of its row: the
 // same sums in the same order, the coordinates' places in the order of deviations counted by comparisons.  Returns the
 // sum of squares; y gets the signed point.
 template <int D>

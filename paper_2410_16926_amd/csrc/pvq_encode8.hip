@@ -32,8 +32,8 @@
 
 namespace {
 
+using namespace pvq_quantize_dev;
 
-constexpr int kWave = 64;
 constexpr int D = 8;
 
 // The offset table in LDS: [7][kMaxK + 1][2 kMaxK + 1] words (coordinate, pulses left, value + kMaxK), whatever K is
@@ -47,47 +47,6 @@ struct enc8_launch {
     const float *edges;     // 2^scale_bits entries, last = +inf (or nullptr)
     int K, scale_bits;
 };
-
-// v + (v moved across lanes by one data-parallel-primitive pattern); lanes outside ROWS add zero
-template <int CTRL, int ROWS = 0xF>
-__device__ inline float dpp_add(float v)
-{
-    const int moved = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, false);
-    return v + __builtin_bit_cast(float, moved);
-}
-
-// Sum of the 64 lanes' values over adjacent pairs, level by level (lanes 2i and 2i+1, then pairs of
-// pairs, ...), valid in lane 63.  Each level adds the two halves' sums, in whichever operand order
-// the lane pattern gives (addition commutes exactly), so the result is the pair-level sum bit for bit.
-__device__ inline float wave_pair_sum(float v)
-{
-    v = dpp_add<0xB1>(v);          // quad_perm [1,0,3,2]
-    v = dpp_add<0x4E>(v);          // quad_perm [2,3,0,1]
-    v = dpp_add<0x141>(v);         // row_half_mirror
-    v = dpp_add<0x140>(v);         // row_mirror
-    v = dpp_add<0x142, 0xA>(v);    // row_bcast15 into rows 1 and 3
-    v = dpp_add<0x143, 0xC>(v);    // row_bcast31 into rows 2 and 3
-    return v;
-}
-
-// OR of v over aligned runs of N lanes (N = 4, 8, 16, 32), in every lane of the run: the first four levels by lane
-// patterns inside a row of 16 lanes (within a quad; then, the quads being uniform, the mirror images inside 8 and 16
-// lanes bring the other half), the fifth across rows.
-template <int CTRL>
-__device__ inline uint32_t dpp_or(uint32_t v)
-{
-    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
-}
-template <int N>
-__device__ inline uint32_t or_over_lanes(uint32_t v)
-{
-    v = dpp_or<0xB1>(v);                              // quad_perm [1,0,3,2]
-    v = dpp_or<0x4E>(v);                              // quad_perm [2,3,0,1]
-    if constexpr (N > 4) v = dpp_or<0x141>(v);        // row_half_mirror
-    if constexpr (N > 8) v = dpp_or<0x140>(v);        // row_mirror
-    if constexpr (N > 16) v |= __shfl_xor(v, 16, kWave);
-    return v;
-}
 
 // Sum over adjacent pairs, level by level (fixed order, float32).
 __device__ inline float tree8(float (&v)[D])
@@ -137,10 +96,6 @@ template <> struct raw8<uint16_t> {
     }
 };
 
-// A float whose bits are the integer n (subnormal for the n used here): small integers times bytes(1) add and multiply
-// exactly, so one fused multiply-add steps a byte address, and its result's bits are the address.
-__device__ constexpr float bytes(uint32_t n) { return __builtin_bit_cast(float, n); }
-
 // One group: returns its 24-bit index, the sum of squares, and the signed point in y (float, zeros of either sign).
 // table: LDS address of offs[0][0][0].  POINT: y of a group without a direction is set too (else its y is unspecified).
 template <bool POINT>
@@ -179,7 +134,7 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
     int key[D];
 #pragma unroll
     for (int i = 0; i < D; i++) key[i] = __float_as_int((fabsf(t[i]) - mag[i]) * unit);
-    pvq_quantize_dev::adjust_first_places8(key, fabsf(m), unit, mag);
+    adjust_first_places8(key, fabsf(m), unit, mag);
     // (-0.0 never carries a pulse: a coordinate whose projection is zero is not among the ones raised)
 #pragma unroll
     for (int i = 0; i < D; i++) y[i] = copysignf(mag[i], w[i]);
@@ -202,7 +157,8 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
     return c;
 }
 
-// Least-squares amplitude (pvq_ls_amplitude) for the point in y.
+// Least-squares amplitude (Sec. 3.3 Step 4) for the point in y: (y . w) / ||y||_2, products rounded one by one and summed over
+// adjacent pairs, level by level.
 __device__ inline float ls_amplitude8(const float (&w)[D], const float (&y)[D], bool degenerate)
 {
     float p[D], n[D];
@@ -234,29 +190,6 @@ __device__ inline float row_sum(const float *wsum, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_pair_sum(wsum[lane])), kWave - 1));
 }
 
-// The row's amplitude codes (Sec. 3.3 Step 5): code = number of quantile edges <= u, u = ss_g / rowss, packed 32/SB lanes to
-// a dword by an OR butterfly.  step: lanes of the workgroup.
-template <int SB>
-__device__ inline void write_codes(const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int step, int lane)
-{
-    for (int g = threadIdx.x; g - lane < G; g += step) {
-        const float ss = g < G ? ss_row[g] : 0.0f;
-        const uint32_t code = pvq_quantize_dev::count_edges<SB>(tree, ss / rowss);
-        const uint32_t word = or_over_lanes<32 / SB>(code << ((lane * SB) & 31));
-        if ((lane & (32 / SB - 1)) == 0 && g < G) srow[((uint32_t)g * SB) >> 5] = word;
-    }
-}
-// (the width of a code is the same for all lanes; a branch per row, so that no loop keeps its conditions in registers)
-__device__ inline void write_codes(int sb, const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int step, int lane)
-{
-    switch (sb) {
-    case 1: write_codes<1>(ss_row, rowss, tree, srow, G, step, lane); break;
-    case 2: write_codes<2>(ss_row, rowss, tree, srow, G, step, lane); break;
-    case 4: write_codes<4>(ss_row, rowss, tree, srow, G, step, lane); break;
-    default: write_codes<8>(ss_row, rowss, tree, srow, G, step, lane); break;
-    }
-}
-
 // LDS of both kernels, from byte 0: the offset table, the edges' tree, two rows' wave sums (used in turn, so that one
 // barrier a row is enough), the row's sums of squares (CODES; every lane reads its own).
 struct enc8_lds {
@@ -269,16 +202,16 @@ __device__ inline enc8_lds fill_lds(uint32_t *smem, const enc8_launch &f, int la
 {
     enc8_lds l;
     l.tree = reinterpret_cast<float4 *>(smem + kTableWords);
-    l.wsum = reinterpret_cast<float *>(l.tree + pvq_quantize_dev::kEdgeNodes);
+    l.wsum = reinterpret_cast<float *>(l.tree + kEdgeNodes);
     l.ss_row = l.wsum + 2 * 64;
     l.table = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint32_t *)smem);
     for (int i = threadIdx.x; i < kTableWords / 4; i += lanes) reinterpret_cast<uint4 *>(smem)[i] = reinterpret_cast<const uint4 *>(f.offs)[i];
-    if constexpr (CODES) pvq_quantize_dev::fill_edge_tree(l.tree, f.edges, f.scale_bits, threadIdx.x, lanes);
+    if constexpr (CODES) fill_edge_tree(l.tree, f.edges, f.scale_bits, threadIdx.x, lanes);
     for (int i = threadIdx.x; i < 2 * 64; i += lanes) l.wsum[i] = 0.0f;
     return l;
 }
 // its words in front of the row's sums of squares
-constexpr int kHeadWords = kTableWords + 4 * pvq_quantize_dev::kEdgeNodes + 2 * 64;
+constexpr int kHeadWords = kTableWords + 4 * kEdgeNodes + 2 * 64;
 
 // TIn: float or uint16_t (bf16 bits).  A block of kBlock lanes takes whole rows, kBlock groups at a
 // time; several blocks share a compute unit, so one block's barriers hide behind the others' arithmetic.
@@ -348,7 +281,7 @@ __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_e
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, kBlock, lane);
+            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, threadIdx.x, kBlock, lane);
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
@@ -424,7 +357,7 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, L, lane);
+            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, tid, L, lane);
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }

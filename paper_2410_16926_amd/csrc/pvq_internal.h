@@ -132,25 +132,6 @@ struct pvq_decode_args {
     int64_t ldy;
 };
 
-// Least-squares amplitude of a group for its point y (Sec. 3.3 Step 4): (y . w) / ||y||_2 in float32,
-// products rounded one by one and summed over adjacent pairs, level by level.
-template <int D>
-__device__ inline float pvq_ls_amplitude(const float (&w)[D], const int (&y)[D])
-{
-    float p[D];
-    int n2 = 0;
-#pragma unroll
-    for (int i = 0; i < D; i++) {
-        p[i] = (float)y[i] * w[i];
-        n2 += y[i] * y[i];
-    }
-#pragma unroll
-    for (int s = 1; s < D; s *= 2)
-#pragma unroll
-        for (int i = 0; i < D; i += 2 * s) p[i] = p[i] + p[i + s];
-    return p[0] / sqrtf((float)n2);
-}
-
 // Each returns a hipError_t from the launch (hipSuccess if enqueued).
 // false: a row's share of LDS (size table, and with amplitude codes the row's amplitudes) exceeds 64 KB
 bool pvq_encode_fits(const pvq_ctx *ctx, const pvq_encode_args &a);

@@ -1,10 +1,21 @@
 // gfx950 kernels of libpvq: the generic encoder (every group size and index width that has no kernel of its
 // own); the matching decoders are in pvq_walk.hip.
 //
-// Work mapping (wave64): one lane owns one group of D weights from load to store, so the group's
-// float32 sums are plain register trees with a fixed order, and the index arithmetic is a carry
-// chain in that lane's registers.  The size tables live in LDS.  Bit-packed planes are assembled
-// in LDS with ds_or and written out as whole words.
+// Work mapping (wave64): one lane owns one group of D weights from load to store, so the group's float32 sums are plain
+// register trees with a fixed order.  A team of up to four waves takes whole rows, 64 groups a wave at a time; a workgroup
+// has one team or several, which share its tables, and as many workgroups run as the machine holds at once.
+//   * The index (App. B.2) is N(D,K) - 1 less one number per coordinate: with U(d,k) = N(d,0) + ... + N(d,k) and C pulses
+//     left behind a coordinate that has d coordinates after it, 2 U(d,C-1), and N(d,C) more if it is positive (what is left
+//     at the last coordinate: 1 if positive).  These are the thresholds that the decoders compare with.  A workgroup makes
+//     their table in LDS from the size table, coordinates next to one another, so that a read's address is one
+//     multiply-add from the coordinate before and the coordinate an offset in the instruction.
+//   * A wave assembles its 64 indices, 2 b whole words, in words of its own in LDS with ds_or and writes them out.
+//   * The row's sum and the amplitude codes are the ones of the encoder for groups of 8 (pvq_quantize_dev.h).
+// Bound by vector instructions, 550 a group of 16 (16-bit weights, 2-bit codes).  8192 x 8192 of these, 48-bit indices: 67 us;
+// groups of 32, 96 bits: 88 us; 3001 x 11008 float32 weights, least-squares amplitudes in 4-bit codes, groups of 16, 52 bits:
+// 44 us; 7001 x 1000 in groups of 8: 13 us.  Before, with a workgroup per row that copied the size table, four reads of it
+// per coordinate, a bisection for the code and words assembled by a whole workgroup between barriers: 101, 148, 65, 26.
+// (A workgroup per set of rows instead of resident ones: 74, 140 and 49 us for the first three.)
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -16,237 +27,290 @@ namespace {
 
 using namespace pvq_quantize_dev;
 
-constexpr int kThreads = 256;
-
 template <int W> struct wide;
 template <> struct wide<1> { using type = uint32_t; };
 template <> struct wide<2> { using type = uint64_t; };
 template <> struct wide<4> { using type = unsigned __int128; };
 
-struct tables_t {
+constexpr int kMaxLanes = 1024;      // of a workgroup
+
+struct encode_launch {
     const uint32_t *tab_u;  // [D][K+2] entries of W words
     const float *edges;     // 2^scale_bits (last = +inf)
-    const float *sqrtc;     // 2^scale_bits
     int K, index_bits, scale_bits;
+    int team;               // lanes that take a row: 64, 128 or 256
 };
 
-// ---------------------------------------------------------------------------------------------
-// bit streams
-// ---------------------------------------------------------------------------------------------
-
-// The `bits`-wide field at bit `pos` of a little-endian stream of 32-bit words.  Only words that
-// hold part of the field are read.
-template <int W>
-__device__ inline typename wide<W>::type load_field(const uint32_t *__restrict__ row, uint32_t pos, int bits)
+// LDS, from byte 0: thresholds [2K+2][D-1] of W words, the edges' tree, each wave's words of an index tile, and per team
+// two rows' wave sums (used in turn, so that one barrier a row is enough) and the row's sums of squares (every lane reads its own)
+struct encode_lds {
+    uint32_t tree, stage, stage_words, sums, sum_words, rows, row_words, total;      // starts and total in bytes
+};
+__host__ __device__ inline encode_lds lds_of(int D, int W, const encode_launch &f, int G, int lanes)
 {
-    using T = typename wide<W>::type;
-    const uint32_t w0 = pos >> 5, sh = pos & 31;
-    const int span = (int)sh + bits;  // bits from the start of word w0 to the end of the field
-    T v = (T)(row[w0] >> sh);
-#pragma unroll
-    for (int i = 1; i <= W; i++) {
-        if (32 * i < span) {
-            const int off = 32 * i - (int)sh;  // 1 .. 32*W
-            if (off < 32 * W) v |= (T)row[w0 + i] << off;
-        }
-    }
-    if (bits < 32 * W) v &= (((T)1) << bits) - 1;
-    return v;
+    encode_lds l;
+    const bool codes = f.scale_bits > 0;
+    const uint32_t teams = (uint32_t)(lanes / f.team);
+    l.tree = ((uint32_t)(2 * f.K + 2) * (D - 1) * W * 4 + 15) / 16 * 16;
+    l.stage = l.tree + (codes ? kEdgeNodes * 16 : 0);
+    l.stage_words = 2 * f.index_bits + W;
+    l.sums = l.stage + (uint32_t)(lanes / kWave) * l.stage_words * 4;
+    l.sum_words = codes ? (uint32_t)(G + kWave * kWave - 1) / (kWave * kWave) * kWave : 0;
+    l.rows = l.sums + 2 * teams * l.sum_words * 4;
+    l.row_words = codes ? (uint32_t)G : 0;
+    l.total = l.rows + teams * l.row_words * 4;
+    return l;
 }
-
-// OR a `bits`-wide value into an LDS word stream at bit `pos` (the stream was zeroed before).
-template <int W>
-__device__ inline void stage_field(uint32_t *stage, uint32_t pos, int bits, typename wide<W>::type v)
-{
-    const uint32_t w0 = pos >> 5, sh = pos & 31;
-    const int span = (int)sh + bits;
-    atomicOr(&stage[w0], (uint32_t)v << sh);
-#pragma unroll
-    for (int i = 1; i <= W; i++) {
-        if (32 * i < span) {
-            const int off = 32 * i - (int)sh;
-            const uint32_t part = off < 32 * W ? (uint32_t)(v >> off) : 0u;
-            atomicOr(&stage[w0 + i], part);
-        }
-    }
-}
-
-template <typename T>
-__device__ inline void copy_to_lds(T *dst, const T *__restrict__ src, int n)
-{
-    for (int i = threadIdx.x; i < n; i += kThreads) dst[i] = src[i];
-}
-
-__device__ inline float bf16_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
 
 // ---------------------------------------------------------------------------------------------
 // encode
 // ---------------------------------------------------------------------------------------------
 
-template <int D, typename TIn>
-__device__ inline void load_group(const TIn *__restrict__ p, float (&w)[D])
-{
-    if constexpr (sizeof(TIn) == 4) {
+// Waves that a SIMD's registers are divided among (groups of 16, 3001 x 11008: 44 us, with 4 46, with 6, which spill, 52;
+// groups of 32, 8192 x 8192: 104 us, with 3 141)
+constexpr int waves_per_simd(int D) { return D == 8 ? 7 : D == 16 ? 5 : 4; }
+
+// A group as it comes from memory
+template <int D, typename TIn> struct raw_group {
+    static constexpr int N = D * (int)sizeof(TIn) / 16;
+    uint32_t q[4 * N];
+    __device__ void load(const TIn *__restrict__ p)
+    {
 #pragma unroll
-        for (int i = 0; i < D; i += 4) {
-            float4 q = *reinterpret_cast<const float4 *>(p + i);
-            w[i] = q.x; w[i + 1] = q.y; w[i + 2] = q.z; w[i + 3] = q.w;
+        for (int i = 0; i < N; i++) {
+            const uint4 v = reinterpret_cast<const uint4 *>(p)[i];
+            q[4 * i] = v.x; q[4 * i + 1] = v.y; q[4 * i + 2] = v.z; q[4 * i + 3] = v.w;
         }
-    } else {
+    }
+    __device__ void get(float (&w)[D]) const
+    {
+        if constexpr (sizeof(TIn) == 4) {
 #pragma unroll
-        for (int i = 0; i < D; i += 8) {
-            uint4 q = *reinterpret_cast<const uint4 *>(p + i);
-            uint32_t u[4] = {q.x, q.y, q.z, q.w};
+            for (int i = 0; i < D; i++) w[i] = __uint_as_float(q[i]);
+        } else {
 #pragma unroll
-            for (int j = 0; j < 4; j++) {
-                w[i + 2 * j] = bf16_to_f32(u[j] & 0xFFFFu);
-                w[i + 2 * j + 1] = __uint_as_float(u[j] & 0xFFFF0000u);
+            for (int i = 0; i < D; i += 2) {
+                w[i] = __uint_as_float(q[i / 2] << 16);
+                w[i + 1] = __uint_as_float(q[i / 2] & 0xFFFF0000u);
             }
         }
     }
+};
+
+// The point of Sec. 2.5: |w| K / ||w||_1, rounded, and pulses moved at the largest deviations.  Signed point in y (zeros of
+// either sign); a group without a direction gets zeros (its point is (0, ..., 0, K)).
+template <int D>
+__device__ inline void project_group(const float (&w)[D], float K, float &ss_out, bool &degenerate, float (&y)[D])
+{
+    float tmp[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) tmp[i] = fabsf(w[i]);
+    const float l1 = tree_sum<D>(tmp);
+#pragma unroll
+    for (int i = 0; i < D; i++) tmp[i] = w[i] * w[i];
+    ss_out = tree_sum<D>(tmp);
+
+    const float g = K / l1;
+    float t[D], pulses = K;
+#pragma unroll
+    for (int i = 0; i < D; i++) t[i] = w[i] * g;
+    // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite  (looked at closely only in waves
+    // with a norm that is not well inside the normal floats)
+    degenerate = false;
+    if (__any(__float_as_uint(l1) - 0x04000000u >= 0x78000000u)) {
+        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+        pulses = degenerate ? 0.0f : K;
+#pragma unroll
+        for (int i = 0; i < D; i++) t[i] = degenerate ? 0.0f : t[i];
+    }
+#pragma unroll
+    for (int i = 0; i < D; i++) { y[i] = rintf(t[i]); tmp[i] = fabsf(y[i]); }
+    // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
+    const float m = pulses - tree_sum<D>(tmp);
+    const float unit = m < 0.0f ? -1.0f : 1.0f;
+    // deviations (negated where pulses have to go), as integers: those that are looked for are positive, and positive
+    // floats order like their bits
+    int key[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) key[i] = __float_as_int((fabsf(t[i]) - fabsf(y[i])) * unit);
+    adjust_first_places<D>(key, fabsf(m), unit, y);
 }
 
-// App. B.2 with the inner sum taken from the cumulative table (App. C.2): with
-// U(d,k) = N(d,0)+...+N(d,k) and U(d,-1) = 0, a coordinate of magnitude m >= 1 adds
-//   N(d,k) + 2 (U(d,k-1) - U(d,k-m)) + [x<0] N(d,k-m)  =  U(k) + U(k-1) - U(k-m) - U(k-m-[x<0]).
-// tab_u rows are shifted by one entry so that U(-1) is stored.  With k' = k - m that is
-// [U(k) + U(k-1)] - [U(k') + U(k'-[x<0])], and the form of a negative coordinate is also right for a zero (k' = k:
-// nothing is added), so the coordinate's value need not be branched on: with four-word entries the straight form
-// is the faster one (D = 32, K = 60: 0.47 against 0.51 ms on 28672 x 8192), with one- and two-word entries the
-// branch (D = 16, K = 33: 0.31 against 0.33 ms; a second table of U(k) + U(k-1), two reads per coordinate: 0.34 ms).
+// The index of the point.  table: LDS address of the thresholds, last: N(D,K) - 1.
 template <int D, int W>
-__device__ inline typename wide<W>::type rank_point(const int (&y)[D], int K,
-                                                    const typename wide<W>::type *tab_u)
+__device__ inline typename wide<W>::type rank_point(const float (&y)[D], bool degenerate, float K,
+                                                    uint32_t table, typename wide<W>::type last)
 {
     using T = typename wide<W>::type;
-    T c = 0;
-    int k = K;
+    constexpr int kStep = (D - 1) * W * 4;       // bytes between a coordinate's thresholds
+    T c = last;
+    float at = __builtin_fmaf(K, bytes(2 * kStep), __uint_as_float(table));
 #pragma unroll
     for (int i = 0; i < D - 1; i++) {
-        const T *u = tab_u + (D - 1 - i) * (K + 2) + 1;  // u[j] = U(D-1-i, j), j >= -1
-        const int m = y[i] < 0 ? -y[i] : y[i];
-        if constexpr (W == 4) {
-            const int kp = k - m;
-            c += (u[k] + u[k - 1]) - (u[kp] + u[kp - (y[i] > 0 ? 0 : 1)]);
-            k = kp;
-        } else if (m > 0) {
-            const int neg = y[i] < 0;
-            c += u[k] + u[k - 1] - u[k - m] - u[k - m - neg];
-            k -= m;
-        }
+        at = __builtin_fmaf(fabsf(y[i]), -bytes(2 * kStep), at);
+        const float positive = __builtin_amdgcn_fmed3f(y[i], 0.0f, 1.0f);
+        const uint32_t address = __float_as_uint(__builtin_fmaf(positive, bytes(kStep), at));
+        c -= *reinterpret_cast<const __attribute__((address_space(3))) T *>(address + i * W * 4);
     }
-    // last coordinate: +k is first, -k second (k > 0); nothing to add when k == 0
-    c += (y[D - 1] < 0) ? 1 : 0;
+    c -= y[D - 1] > 0.0f || degenerate ? 1 : 0;
     return c;
 }
 
-template <int D, int W, typename TIn>
-__global__ __launch_bounds__(kThreads) void encode_kernel(tables_t tb, pvq_encode_args a)
+// Least-squares amplitude (Sec. 3.3 Step 4) for the point y: (y . w) / ||y||_2, products rounded one by one and summed over
+// adjacent pairs, level by level.
+template <int D>
+__device__ inline float ls_amplitude(const float (&w)[D], const float (&y)[D], bool degenerate, float K)
+{
+    float p[D], n[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+        p[i] = y[i] * w[i];
+        n[i] = y[i] * y[i];                   // small integers
+    }
+    if (__any(degenerate)) {
+        // zeros of the point are positive (the sign of a sum of zeros is theirs)
+#pragma unroll
+        for (int i = 0; i < D; i++) p[i] = degenerate ? (i < D - 1 ? 0.0f : K) * w[i] : p[i];
+        n[D - 1] = degenerate ? K * K : n[D - 1];
+    }
+    return tree_sum<D>(p) / sqrtf(tree_sum<D>(n));
+}
+
+// OR a `bits`-wide value into a wave's words at bit 32 * (word of `at`) + sh (one word behind it too, with nothing)
+template <int W>
+__device__ inline void stage_field(uint32_t *at, uint32_t sh, typename wide<W>::type v)
+{
+    atomicOr(at, (uint32_t)v << sh);
+#pragma unroll
+    for (int i = 1; i <= W; i++) {
+        const uint64_t two = (uint64_t)(uint32_t)(v >> (32 * (i - 1))) | (i < W ? (uint64_t)(uint32_t)(v >> (32 * (i % W))) << 32 : 0);
+        atomicOr(at + i, (uint32_t)(two >> (32 - sh)));
+    }
+}
+
+// LS: least-squares amplitudes (Sec. 3.3 Step 4) instead of norms.
+template <int D, int W, typename TIn, bool LS>
+__global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(encode_launch f, pvq_encode_args a)
 {
     using T = typename wide<W>::type;
     extern __shared__ __align__(16) unsigned char smem[];
-    const int K = tb.K, b = tb.index_bits, sb = tb.scale_bits;
+    const int lanes = blockDim.x, b = f.index_bits, sb = f.scale_bits;
     const int G = (int)a.groups;
-    const int tab_entries = D * (K + 2);
-    T *tab_u = reinterpret_cast<T *>(smem);
-    uint32_t *stage = reinterpret_cast<uint32_t *>(tab_u + tab_entries);  // 8*b words
-    uint32_t *sstage = stage + 8 * b;                                      // 8*sb words
-    float *edges = reinterpret_cast<float *>(sstage + 8 * 8);              // 256 floats
-    float *ss_row = edges + 256;                                           // G floats   (sb > 0)
-    float *red0 = ss_row + G;                                              // (G+1)/2
-    float *red1 = red0 + (G + 1) / 2;                                      // (G+3)/4
+    const float K = (float)f.K;
+    const encode_lds l = lds_of(D, W, f, G, lanes);
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = f.team / kWave, team = wave / waves, first = wave % waves;     // waves of a team, and the wave's place there
+    const int teams = lanes / f.team;
 
-    copy_to_lds(tab_u, reinterpret_cast<const T *>(tb.tab_u), tab_entries);
-    if (sb > 0) copy_to_lds(edges, tb.edges, 1 << sb);
+    float4 *tree = reinterpret_cast<float4 *>(smem + l.tree);
+    uint32_t *stage = reinterpret_cast<uint32_t *>(smem + l.stage) + wave * l.stage_words;
+    float *sums = reinterpret_cast<float *>(smem + l.sums) + team * 2 * l.sum_words;
+    float *ss_row = reinterpret_cast<float *>(smem + l.rows) + team * l.row_words;
+    const uint32_t table = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) unsigned char *)smem);
 
-    const int tid = threadIdx.x;
-    const int ntiles = (G + kThreads - 1) / kThreads;
-    const int tile_words = 8 * b;  // 256 groups * b bits / 32
+    const int tiles = (G + kWave - 1) / kWave;
+    const TIn *source = reinterpret_cast<const TIn *>(a.W);
+    // (a lane past the row's end takes the last group again, and writes nothing)
+    auto group_at = [&](int64_t row, int t) { return source + row * a.ldw + (int64_t)min(t * kWave + lane, G - 1) * D; };
+    const int64_t step = (int64_t)gridDim.x * teams;
+    int64_t row = (int64_t)blockIdx.x * teams + team;
 
-    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
-        const TIn *wrow = reinterpret_cast<const TIn *>(a.W) + row * a.ldw;
-        uint32_t *irow = a.index_out + row * a.index_row_words;
-        for (int tile = 0; tile < ntiles; tile++) {
-            for (int i = tid; i < tile_words; i += kThreads) stage[i] = 0;
-            __syncthreads();
-            const int g = tile * kThreads + tid;
-            if (g < G) {
-                float w[D];
-                int y[D];
-                load_group<D, TIn>(wrow + (int64_t)g * D, w);
-                float ss;
-                if constexpr (D == 8) ss = quantize_group8(w, K, y);
-                else ss = quantize_group_select<D>(w, K, y);
-                const T c = rank_point<D, W>(y, K, tab_u);
-                stage_field<W>(stage, (uint32_t)tid * (uint32_t)b, b, c);
-                // the amplitude: the norm, or the least-squares one, whose square then stands for
-                // the sum of squares in the codes (Sec. 3.3 Steps 4 and 5)
-                float amp;
-                if (a.ls_amplitude) { amp = pvq_ls_amplitude<D>(w, y); ss = amp * amp; }
-                else amp = sqrtf(ss);
+    // groups of 32 are loaded where they are used: there are no registers for a second one (16-bit weights, 96-bit indices,
+    // 8192 x 8192: 105 us with one, 88)
+    constexpr bool kAhead = D < 32;
+    raw_group<D, TIn> next;
+    if (kAhead && first < tiles) next.load(group_at(min(row, a.rows - 1), first));
+
+    // thresholds from the size table, whose rows are shifted by one entry so that U(-1) is stored
+    const T *tab_u = reinterpret_cast<const T *>(f.tab_u);
+    for (int e = tid; e < (2 * f.K + 2) * (D - 1); e += lanes) {
+        const int j = e / (D - 1), i = e % (D - 1);
+        const T *u = tab_u + (D - 1 - i) * (f.K + 2) + (j >> 1);           // u[0] = U(D-1-i, C-1)
+        reinterpret_cast<T *>(smem)[e] = u[0] + ((j & 1) ? u[1] : u[0]);
+    }
+    if (sb > 0) fill_edge_tree(tree, f.edges, sb, tid, lanes);
+    for (int i = tid; i < (int)(lanes / kWave * l.stage_words); i += lanes) reinterpret_cast<uint32_t *>(smem + l.stage)[i] = 0;
+    for (int i = tid; i < (int)(2 * teams * l.sum_words); i += lanes) reinterpret_cast<float *>(smem + l.sums)[i] = 0.0f;
+    __syncthreads();
+    // U(D-1,K) + U(D-1,K-1) = N(D,K)
+    const T last = reinterpret_cast<const T *>(smem)[(2 * f.K + 1) * (D - 1)] - 1;
+
+    const uint32_t sh = (uint32_t)(lane * b) & 31;
+    uint32_t *const at = stage + ((uint32_t)(lane * b) >> 5);
+    uint32_t turn = 0;
+    for (int64_t base = (int64_t)blockIdx.x * teams; base < a.rows; base += step, row += step) {
+        const bool live = row < a.rows;          // (a team without a row waits at the barrier)
+        for (int t = first; live && t < tiles; t += waves) {
+            const int g = t * kWave + lane;
+            const bool in = g < G;
+            float w[D], y[D], ss;
+            if constexpr (!kAhead) next.load(group_at(row, t));
+            next.get(w);
+            if constexpr (kAhead) {
+                // the tile behind, or the next row's first (of the last row once more)
+                const bool more = t + waves < tiles;
+                next.load(group_at(more ? row : min(row + step, a.rows - 1), more ? t + waves : first));
+            }
+            bool degenerate;
+            project_group<D>(w, K, ss, degenerate, y);
+            const T c = rank_point<D, W>(y, degenerate, K, table, last);
+            stage_field<W>(at, sh, in ? c : 0);
+            // the amplitude: the norm, or the least-squares one, whose square then stands for
+            // the sum of squares in the codes (Sec. 3.3 Steps 4 and 5)
+            float amp;
+            if constexpr (LS) { amp = ls_amplitude<D>(w, y, degenerate, K); ss = amp * amp; }
+            else amp = sqrtf(ss);
+            if (in) {
                 if (sb > 0) ss_row[g] = ss;
                 else reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
-                if (a.pulses_out) {
-                    int8_t *p = a.pulses_out + row * a.cols + (int64_t)g * D;
+            }
+            if (a.pulses_out && in) {
+                int8_t *p = a.pulses_out + row * a.cols + (int64_t)g * D;
+                if (degenerate) y[D - 1] = K;
 #pragma unroll
-                    for (int i = 0; i < D; i += 8) {
-                        uint32_t lo = 0, hi = 0;
+                for (int i = 0; i < D; i += 8) {
+                    uint32_t lo = 0, hi = 0;
 #pragma unroll
-                        for (int j = 0; j < 4; j++) {
-                            lo |= ((uint32_t)y[i + j] & 0xFFu) << (8 * j);
-                            hi |= ((uint32_t)y[i + 4 + j] & 0xFFu) << (8 * j);
-                        }
-                        *reinterpret_cast<uint2 *>(p + i) = make_uint2(lo, hi);
+                    for (int j = 0; j < 4; j++) {
+                        lo |= ((uint32_t)(int)y[i + j] & 0xFFu) << (8 * j);
+                        hi |= ((uint32_t)(int)y[i + 4 + j] & 0xFFu) << (8 * j);
                     }
+                    *reinterpret_cast<uint2 *>(p + i) = make_uint2(lo, hi);
                 }
             }
-            __syncthreads();
-            const int64_t w0 = (int64_t)tile * tile_words;
-            const int nw = (int)min((int64_t)tile_words, a.index_row_words - w0);
-            for (int i = tid; i < nw; i += kThreads) irow[w0 + i] = stage[i];
-            __syncthreads();
+            if (sb > 0) {
+                // pairwise sum over the wave's 64 groups (absent groups add +0.0, which is exact)
+                const float v = wave_pair_sum(in ? ss : 0.0f);
+                if (lane == kWave - 1) sums[turn + t] = v;
+            }
+            // the tile's words, cleared for the next (a wave's LDS instructions are carried out in order)
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            uint32_t *irow = a.index_out + row * a.index_row_words + (int64_t)t * 2 * b;
+            const int nw = (int)min((int64_t)2 * b, a.index_row_words - (int64_t)t * 2 * b);
+            for (int i = lane; i < nw; i += kWave) {
+                irow[i] = stage[i];
+                stage[i] = 0;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         }
         // Row normaliser (code mode only): sum of the groups' sums of squares, adjacent pairs
-        // level by level, an odd last element moving up unchanged.
+        // level by level, an odd last element moving up unchanged (as if zeros followed).
         if (sb > 0) {
-            int n = G;
-            const float *src = ss_row;
-            float *dst = red0;
-            while (n > 1) {
-                const int h = n >> 1, odd = n & 1;
-                for (int i = tid; i < h + odd; i += kThreads)
-                    dst[i] = i < h ? src[2 * i] + src[2 * i + 1] : src[n - 1];
-                __syncthreads();
-                n = h + odd;
-                src = dst;
-                dst = (dst == red0) ? red1 : red0;
-            }
-            const float rowss = src[0];
-            if (tid == 0) a.rownorm_out[row] = rowss;
-            // Sec. 3.3 Step 5: code = floor(CDF(u) 2^b) = number of quantile edges <= u,
-            // u = ss_g / rowss.  The edges ascend, so the count is found by bisection.
-            uint32_t *srow = reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words;
-            const int stile_words = 8 * sb;
-            const int nedges = (1 << sb) - 1;
-            for (int tile = 0; tile < ntiles; tile++) {
-                for (int i = tid; i < stile_words; i += kThreads) sstage[i] = 0;
-                __syncthreads();
-                const int g = tile * kThreads + tid;
-                if (g < G) {
-                    const float u = ss_row[g] / rowss;
-                    int lo = 0, hi = nedges;
-                    while (lo < hi) {
-                        const int mid = (lo + hi) >> 1;
-                        if (edges[mid] <= u) lo = mid + 1; else hi = mid;
-                    }
-                    atomicOr(&sstage[(tid * sb) >> 5], (uint32_t)lo << ((tid * sb) & 31));
+            __syncthreads();
+            if (live) {
+                float part[4];                       // of 4096 groups each (rows of more than 16384 do not fit)
+#pragma unroll
+                for (int i = 0; i < 4; i++) {
+                    part[i] = 0.0f;
+                    if (i * kWave < tiles)
+                        part[i] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_pair_sum(sums[turn + i * kWave + lane])), kWave - 1));
                 }
-                __syncthreads();
-                const int64_t w0 = (int64_t)tile * stile_words;
-                const int nw = (int)min((int64_t)stile_words, a.scale_row_words - w0);
-                for (int i = tid; i < nw; i += kThreads) srow[w0 + i] = sstage[i];
-                __syncthreads();
+                const float rowss = (part[0] + part[1]) + (part[2] + part[3]);
+                if (first == 0 && lane == 0) a.rownorm_out[row] = rowss;
+                write_codes(sb, ss_row, rowss, tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G,
+                            first * kWave + lane, f.team, lane);
             }
+            turn = l.sum_words - turn;
         }
     }
 }
@@ -255,41 +319,57 @@ __global__ __launch_bounds__(kThreads) void encode_kernel(tables_t tb, pvq_encod
 // launchers
 // ---------------------------------------------------------------------------------------------
 
-tables_t make_tables(const pvq_ctx *c)
-{
-    tables_t t;
-    t.tab_u = c->tab_u; t.edges = c->edges; t.sqrtc = c->sqrtc;
-    t.K = c->K; t.index_bits = c->index_bits; t.scale_bits = c->scale_bits;
-    return t;
-}
-
 constexpr size_t kMaxLds = 64 * 1024;
 
-// LDS of encode_kernel for a row of G groups: the size table's rows, the row's index words being assembled,
-// and with amplitude codes the row's amplitudes
-size_t encode_lds_bytes(const pvq_ctx *c, size_t G)
+// What a row may take: a size table, index words of 256 groups, and with amplitude codes the row's sums of squares and what
+// their sum takes level by level.  (A row within it has at most 9362 groups, and encode_kernel's LDS is less than
+// 136 KB with one team of 256 lanes: twice the size table, the rest below the 8 KB of the two largest index widths.)
+size_t encode_row_bytes(const pvq_ctx *c, size_t G)
 {
     size_t lds = (size_t)c->D * (c->K + 2) * c->words * 4 + (size_t)8 * c->index_bits * 4 + 64 * 4 + 256 * 4;
     if (c->scale_bits > 0) lds += (G + (G + 1) / 2 + (G + 3) / 4 + 4) * 4;
     return lds;
 }
 
+template <int D, int W, typename TIn, bool LS>
+hipError_t launch_encode_kernel(const pvq_ctx *c, const pvq_encode_args &a, hipStream_t s)
+{
+    encode_launch f;
+    f.tab_u = c->tab_u; f.edges = c->edges;
+    f.K = c->K; f.index_bits = c->index_bits; f.scale_bits = c->scale_bits;
+    f.team = a.groups <= kWave ? kWave : a.groups <= 2 * kWave ? 2 * kWave : 4 * kWave;
+    // Lanes of a workgroup: the fewest with which the most waves fit a unit's LDS beside one another.
+    constexpr int kWavesMost = 4 * waves_per_simd(D);
+    int lanes = 0, waves = 0;
+    for (int n = 256; n <= kMaxLanes; n *= 2) {
+        const uint32_t lds = (lds_of(D, W, f, (int)a.groups, n).total + 1279) / 1280 * 1280;
+        const int fit = std::min<int>(160 * 1024 / lds * (n / kWave), kWavesMost / (n / kWave) * (n / kWave));
+        if (fit > waves) { waves = fit; lanes = n; }
+    }
+    if (lanes == 0) return hipErrorInvalidValue;      // (the caller has asked pvq_encode_fits)
+    const uint32_t lds = lds_of(D, W, f, (int)a.groups, lanes).total;
+    const auto kernel = &encode_kernel<D, W, TIn, LS>;
+    if (lds > kMaxLds) {
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const int64_t teams = lanes / f.team;
+    const unsigned grid = (unsigned)std::min<int64_t>((a.rows + teams - 1) / teams, 256 * (waves / (lanes / kWave)));
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(lanes), lds, s, f, a);
+    return hipGetLastError();
+}
+
 template <int D, int W>
 hipError_t launch_encode_dw(const pvq_ctx *c, const pvq_encode_args &a, int dtype, hipStream_t s)
 {
-    const size_t lds = encode_lds_bytes(c, (size_t)a.groups);
-    if (lds > kMaxLds) return hipErrorInvalidValue;      // (the caller has asked pvq_encode_fits)
-    const unsigned grid = (unsigned)std::min<int64_t>(a.rows, 1 << 20);
-    if (dtype == PVQ_F32)
-        hipLaunchKernelGGL((encode_kernel<D, W, float>), dim3(grid), dim3(kThreads), lds, s, make_tables(c), a);
-    else
-        hipLaunchKernelGGL((encode_kernel<D, W, uint16_t>), dim3(grid), dim3(kThreads), lds, s, make_tables(c), a);
-    return hipGetLastError();
+    if (a.ls_amplitude)
+        return dtype == PVQ_F32 ? launch_encode_kernel<D, W, float, true>(c, a, s) : launch_encode_kernel<D, W, uint16_t, true>(c, a, s);
+    return dtype == PVQ_F32 ? launch_encode_kernel<D, W, float, false>(c, a, s) : launch_encode_kernel<D, W, uint16_t, false>(c, a, s);
 }
 
 }  // namespace
 
-bool pvq_encode_fits(const pvq_ctx *c, const pvq_encode_args &a) { return encode_lds_bytes(c, (size_t)a.groups) <= kMaxLds; }
+bool pvq_encode_fits(const pvq_ctx *c, const pvq_encode_args &a) { return encode_row_bytes(c, (size_t)a.groups) <= kMaxLds; }
 
 hipError_t pvq_launch_encode(const pvq_ctx *c, const pvq_encode_args &a, int dtype, hipStream_t s)
 {

@@ -1,9 +1,8 @@
-// Device code shared by the kernels that quantise a group onto the pyramid (Sec. 2.5): the encoders and
-// the error correction of Sec. 3.3 Step 6.  float32, fixed evaluation order: the results are part of the
-// format.  The point: project onto the l1 ball of radius K, round to nearest even, then move single pulses on
-// the coordinates of largest deviation (lowest coordinate on ties) until the count is K.  quantize_group8 finds
-// it without branches for D = 8 (count_wins); the D = 8 encoder and quantize_group_select<D>, for any D, take one
-// round per pulse to move (adjust_first_places8 for D = 8).
+// Device code shared by the encoders of groups of up to 32 (Sec. 2.5, Sec. 3.3 Steps 3 to 5).  float32, fixed evaluation
+// order: the results are part of the format.  The point: project onto the l1 ball of radius K, round to nearest even, then
+// move single pulses on the coordinates of largest deviation (lowest coordinate on ties) until the count is K.  No coordinate
+// is ever adjusted twice: for finite input the |sum - K| largest deviations are all positive, and an adjusted coordinate
+// drops below -1/2.  So the repair takes one round per pulse, with the deviations formed once.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -21,33 +20,12 @@ __device__ inline float tree_sum(float (&v)[D])
     return v[0];
 }
 
-// Position of every coordinate in the order of keys (largest first, lower coordinate first on
-// ties): wins[i] = number of coordinates that i comes before.  One comparison per pair feeds two
-// counters through its carry: i's wins over later coordinates and j's losses against earlier ones.
-__device__ inline void count_wins(const float (&key)[8], int (&wins)[8])
-{
-    constexpr int D = 8;
-    int lose[D];
-#pragma unroll
-    for (int i = 0; i < D; i++) { wins[i] = 0; lose[i] = 0; }
-#pragma unroll
-    for (int i = 0; i < D; i++)
-#pragma unroll
-        for (int j = i + 1; j < D; j++) {
-            const int first = key[i] >= key[j] ? 1 : 0;
-            wins[i] += first;
-            lose[j] += first;
-        }
-#pragma unroll
-    for (int j = 0; j < D; j++) wins[j] += j - lose[j];   // j beat every earlier coordinate it did not lose to
-}
-
 // The repair of Sec. 2.5 for groups of 8: mag[i] += unit for the coordinates that hold the `need` first places in the order
 // of keys (largest first, lower coordinate first on ties; the bits of floats, of which the first `need` are positive).  A
 // round takes the largest key left (three-operand maxima), marks the first coordinate that has it and takes its key out; a
-// wave runs as many rounds as its lane with the largest `need`, two or three for groups of 8, against a hundred
-// instructions for count_wins: the form for kernels that are short of vector instructions (the encoders).  The first two
-// rounds keep their marks as masks (scalar registers; those of more rounds do not fit there).  Changes key.
+// wave runs as many rounds as its lane with the largest `need`, two or three for groups of 8 (counting every coordinate's
+// place with 28 comparisons takes a hundred instructions).  The first two rounds keep their marks as masks (scalar registers;
+// those of more rounds do not fit there).  Changes key.
 __device__ inline void adjust_first_places8(int (&key)[8], float need, float unit, float (&mag)[8])
 {
     bool adj[8];
@@ -83,119 +61,71 @@ __device__ inline void adjust_first_places8(int (&key)[8], float need, float uni
     }
 }
 
-// Groups of 8 without branches (for the error correction, whose waves wait for one group after the other: rounds
-// with a wave-wide vote measured 2 % slower there): the coordinates' places in the order of deviations are counted
-// with 28 comparisons and the |sum - K| first places are adjusted, which equals the one-at-a-time repair because no
-// coordinate is ever adjusted twice (for finite input the |sum - K| largest deviations are all positive, and an
-// adjusted coordinate drops below -1/2).  Returns the sum of squares; y gets the signed point.  Weights that are
-// not finite give (0, ..., 0, K).
-__device__ inline float quantize_group8(const float (&w)[8], int K, int (&y)[8])
+// The same repair for any D and signed points (whose zeros have their sign too), in one loop for all rounds: a place that is taken gets the key -1 (below every positive float,
+// and the bits of no deviation), which shows at the end where a pulse moved.  A wave runs as many rounds as its lane with the
+// largest `need`, about three for D = 16 and five for D = 32.
+template <int D>
+__device__ inline void adjust_first_places(int (&key)[D], float need, float unit, float (&y)[D])
 {
-    constexpr int D = 8;
-    float a[D], tmp[D];
+#pragma unroll 1
+    for (float round = 0.0f; round < (float)D && __any(need > round); round += 1.0f) {
+        int best = max(key[0], key[1]);
 #pragma unroll
-    for (int i = 0; i < D; i++) { a[i] = fabsf(w[i]); tmp[i] = a[i]; }
-    const float l1 = tree_sum<D>(tmp);
+        for (int i = 2; i < D; i += 2) best = max(max(best, key[i]), key[i + 1]);
+        bool taken = !(need > round);             // (a lane that needs no more takes nothing)
 #pragma unroll
-    for (int i = 0; i < D; i++) tmp[i] = w[i] * w[i];
-    const float ss = tree_sum<D>(tmp);
-    const float g = (float)K / l1;
-    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
-    float t[D], yf[D];
-    float S = 0.0f;
-#pragma unroll
-    for (int i = 0; i < D; i++) {
-        t[i] = a[i] * g;
-        yf[i] = rintf(t[i]);
-        S += yf[i];                       // small integers: exact in any order
+        for (int i = 0; i < D; i++) {
+            const bool equal = key[i] == best;
+            key[i] = equal && !taken ? -1 : key[i];
+            taken = taken || equal;
+        }
     }
-    const float m = (float)K - S;         // > 0: pulses to add, < 0: pulses to take away
-    float key[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) {
-        const float d = t[i] - yf[i];
-        key[i] = m < 0.0f ? -d : d;
-    }
-    int wins[D];
-    count_wins(key, wins);
-    const int need = (int)fabsf(m);
-    const float unit = m < 0.0f ? -1.0f : 1.0f;
-    int k = K;
-#pragma unroll
-    for (int i = 0; i < D; i++) {
-        const bool adjust = wins[i] + need >= D;      // place = D-1-wins < need
-        int mag = (int)(yf[i] + (adjust ? unit : 0.0f));
-        if (degenerate) mag = 0;
-        if (i == D - 1) mag = k;                      // the last coordinate takes what is left
-        y[i] = (w[i] < 0.0f && !degenerate) ? -mag : mag;
-        k -= mag;
-    }
-    return ss;
+    for (int i = 0; i < D; i++) y[i] = copysignf(fabsf(y[i]) + (key[i] == -1 ? unit : 0.0f), y[i]);
 }
 
-// The same point for any D, without the two repair loops' re-evaluation of every deviation: the deviations are
-// formed once (as keys, negated when pulses have to be taken away), and each of the |sum - K| rounds picks the
-// largest key, lowest coordinate on ties, adjusts that coordinate and takes its key out.  This is the one-at-a-time
-// repair itself, since an adjusted coordinate never comes up again (see quantize_group8); a wave runs as many rounds
-// as its lane with the largest |sum - K| needs, two to five for D = 16 and 32 (re-evaluating all deviations in every
-// round, in one loop for pulses to take away and one for pulses to add, took 2.5 times the instructions).
-// Weights that are not finite give (0, ..., 0, K).
-template <int D>
-__device__ inline float quantize_group_select(const float (&w)[D], int K, int (&y)[D])
+// ---- sums and fields over the lanes of a wave ----------------------------------------------------------------------
+constexpr int kWave = 64;
+
+// v + (v moved across lanes by one data-parallel-primitive pattern); lanes outside ROWS add zero
+template <int CTRL, int ROWS = 0xF>
+__device__ inline float dpp_add(float v)
 {
-    float a[D], tmp[D];
-#pragma unroll
-    for (int i = 0; i < D; i++) { a[i] = fabsf(w[i]); tmp[i] = a[i]; }
-    const float l1 = tree_sum<D>(tmp);
-#pragma unroll
-    for (int i = 0; i < D; i++) tmp[i] = w[i] * w[i];
-    const float ss = tree_sum<D>(tmp);
-    const float g = (float)K / l1;
-    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
-    float key[D], yf[D];
-    float S = 0.0f;
-#pragma unroll
-    for (int i = 0; i < D; i++) {
-        const float t = a[i] * g;
-        yf[i] = rintf(t);
-        S += yf[i];                       // small integers: exact in any order
-        key[i] = t - yf[i];
-    }
-    const float m = (float)K - S;         // > 0: pulses to add, < 0: pulses to take away
-    const float unit = m < 0.0f ? -1.0f : 1.0f;
-    if (m < 0.0f) {
-#pragma unroll
-        for (int i = 0; i < D; i++) key[i] = -key[i];
-    }
-    const int need = degenerate ? 0 : (int)fminf(fabsf(m), (float)D);
-    for (int round = 0; round < D; round++) {
-        if (!__any(round < need)) break;
-        float best = key[0];
-        int at = 0;
-#pragma unroll
-        for (int i = 1; i < D; i++) {
-            const bool take = key[i] > best;
-            best = take ? key[i] : best;
-            at = take ? i : at;
-        }
-        if (round < need) {
-#pragma unroll
-            for (int i = 0; i < D; i++) {
-                const bool hit = i == at;
-                yf[i] += hit ? unit : 0.0f;
-                key[i] = hit ? -INFINITY : key[i];
-            }
-        }
-    }
-    int k = K;
-#pragma unroll
-    for (int i = 0; i < D; i++) {
-        int mag = degenerate ? 0 : (int)yf[i];
-        if (i == D - 1) mag = k;                      // the last coordinate takes what is left
-        y[i] = (w[i] < 0.0f && !degenerate) ? -mag : mag;
-        k -= mag;
-    }
-    return ss;
+    const int moved = __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, ROWS, 0xF, false);
+    return v + __builtin_bit_cast(float, moved);
+}
+
+// Sum of the 64 lanes' values over adjacent pairs, level by level (lanes 2i and 2i+1, then pairs of
+// pairs, ...), valid in lane 63.  Each level adds the two halves' sums, in whichever operand order
+// the lane pattern gives (addition commutes exactly), so the result is the pair-level sum bit for bit.
+__device__ inline float wave_pair_sum(float v)
+{
+    v = dpp_add<0xB1>(v);          // quad_perm [1,0,3,2]
+    v = dpp_add<0x4E>(v);          // quad_perm [2,3,0,1]
+    v = dpp_add<0x141>(v);         // row_half_mirror
+    v = dpp_add<0x140>(v);         // row_mirror
+    v = dpp_add<0x142, 0xA>(v);    // row_bcast15 into rows 1 and 3
+    v = dpp_add<0x143, 0xC>(v);    // row_bcast31 into rows 2 and 3
+    return v;
+}
+
+// OR of v over aligned runs of N lanes (N = 4, 8, 16, 32), in every lane of the run: the first four levels by lane
+// patterns inside a row of 16 lanes (within a quad; then, the quads being uniform, the mirror images inside 8 and 16
+// lanes bring the other half), the fifth across rows.
+template <int CTRL>
+__device__ inline uint32_t dpp_or(uint32_t v)
+{
+    return v | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xF, 0xF, false);
+}
+template <int N>
+__device__ inline uint32_t or_over_lanes(uint32_t v)
+{
+    v = dpp_or<0xB1>(v);                              // quad_perm [1,0,3,2]
+    v = dpp_or<0x4E>(v);                              // quad_perm [2,3,0,1]
+    if constexpr (N > 4) v = dpp_or<0x141>(v);        // row_half_mirror
+    if constexpr (N > 8) v = dpp_or<0x140>(v);        // row_mirror
+    if constexpr (N > 16) v |= __shfl_xor(v, 16, kWave);
+    return v;
 }
 
 // ---- amplitude codes (Sec. 3.3 Step 5): how many of the 2^bits - 1 ascending edges are <= u ----------------------
@@ -227,5 +157,32 @@ __device__ inline uint32_t count_edges(const float4 *tree, float u)
     }
     return v;
 }
+
+// The row's amplitude codes (Sec. 3.3 Step 5): code = number of quantile edges <= u, u = ss_g / rowss, packed 32/SB lanes to
+// a dword by an OR butterfly.  first, step: the lane's first group and the distance to its next.
+template <int SB>
+__device__ inline void write_codes(const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int step, int lane)
+{
+    for (int g = first; g - lane < G; g += step) {
+        const float ss = g < G ? ss_row[g] : __builtin_nanf("");          // (no edge is reached: absent groups leave zeros)
+        const uint32_t code = count_edges<SB>(tree, ss / rowss);
+        const uint32_t word = or_over_lanes<32 / SB>(code << ((lane * SB) & 31));
+        if ((lane & (32 / SB - 1)) == 0 && g < G) srow[((uint32_t)g * SB) >> 5] = word;
+    }
+}
+// (the width of a code is the same for all lanes; a branch per row, so that no loop keeps its conditions in registers)
+__device__ inline void write_codes(int sb, const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int step, int lane)
+{
+    switch (sb) {
+    case 1: write_codes<1>(ss_row, rowss, tree, srow, G, first, step, lane); break;
+    case 2: write_codes<2>(ss_row, rowss, tree, srow, G, first, step, lane); break;
+    case 4: write_codes<4>(ss_row, rowss, tree, srow, G, first, step, lane); break;
+    default: write_codes<8>(ss_row, rowss, tree, srow, G, first, step, lane); break;
+    }
+}
+
+// A float whose bits are the integer n (subnormal for the n used here): small integers times bytes(1) add and multiply
+// exactly, so one fused multiply-add steps a byte address, and its result's bits are the address.
+__device__ constexpr float bytes(uint32_t n) { return __builtin_bit_cast(float, n); }
 
 }  // namespace pvq_quantize_dev

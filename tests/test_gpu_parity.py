@@ -379,6 +379,26 @@ def test_rows_that_workgroups_take_in_turn(rows, cols, K, bits, amplitude):
     ctx.close()
 
 
+@pytest.mark.parametrize("D,budget,bits,rows,groups,amplitude", [
+    (8, 24, 2, 3, 4099, "l2"), (8, 24, 1, 2, 8901, "ls"), (8, 40, 0, 6001, 3, "l2"), (8, 64, 8, 70, 63, "ls"),   # sums of 4096 groups, one wave a row
+    (16, 20, 4, 5003, 65, "l2"), (16, 52, 8, 130, 129, "ls"), (16, 64, 2, 2600, 64, "l2"), (16, 104, 4, 600, 256, "ls"),
+    (32, 30, 1, 9000, 5, "ls"), (32, 64, 4, 1030, 128, "l2"), (32, 96, 0, 1100, 67, "ls"), (32, 128, 2, 530, 257, "l2")])
+def test_generic_encoder_teams_and_index_widths(D, budget, bits, rows, groups, amplitude):
+    # rows for one, two and four waves, one group more or less; more rows than teams at once; thresholds of up to 100 KB, one
+    # to four words wide; groups with ties, zeros, one-hot and wide ranges among them
+    K = min(127, pvq.pvq_max_k(D, budget))
+    rng = np.random.default_rng(D + groups)
+    W = si.gaussian_weights(rows, groups * D, 0.02, seed=si.BASE_SEED + 750 + groups, rotate=False, bf16=True)[0].reshape(-1, D)
+    n = min(len(W), 4096)
+    W[rng.choice(len(W), n, replace=False)] = si.adversarial_groups(n, D, seed=groups)
+    W = W.reshape(rows, groups * D)
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W), want_pulses=True)
+    gu.assert_encode_equal(packed, oracle.encode(W, D, K, bits, oe, nthreads=8, amplitude=amplitude))
+    ctx.close()
+
+
 @pytest.mark.parametrize("K,raise_", [(16, True), (16, False), (15, True), (15, False)])
 def test_many_pulses_to_move_in_groups_of_8(K, raise_):
     # projections whose fractions lie on one side, so that three or more pulses have to move, ties among them (a power of two
