@@ -8,12 +8,12 @@
 // (pvq_internal.h), of which a coordinate of the point is one, so that N(D,K) - 1 - index is the sum over the
 // coordinates.
 //
-// Encoding (Sec. 2.5 for the point, App. B.2 for its index): one wave per group, lane l holds coordinates
-// CP*l .. CP*l+CP-1 (CP = D/64).  The quantiser's sums run over adjacent pairs level by level (in the
+// Encoding (Sec. 2.5 for the point, App. B.2 for its index): 16 lanes per group, lane l holds coordinates
+// CP*l .. CP*l+CP-1 (CP = D/16).  The quantiser's sums run over adjacent pairs level by level (in the
 // lane, then across lanes by data-parallel-primitive moves, no LDS traffic), the repair of the pulse
-// count picks one coordinate per step by a wave-wide argmax (lowest coordinate on ties).  The index is a sum of
+// count takes the largest deviation of the group per step (lowest coordinate on ties).  The index is a sum of
 // per-coordinate thresholds that depend on the coordinate's magnitude, sign and the pulses left before it only; a
-// prefix sum over the magnitudes gives the latter; six levels of multi-word additions across the lanes give the total.
+// prefix sum over the magnitudes gives the latter.
 //
 // Decoding (App. B.3): coordinate by coordinate, q = N(D,K) - 1 - index first; a coordinate is the last
 // threshold of its row that is not above q, and q loses it.  Few groups: a wave per group
@@ -34,33 +34,6 @@ typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
 typedef __attribute__((ext_vector_type(2))) float f32x2_t;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 
-template <int W>
-struct wint {
-    uint32_t w[W];
-};
-
-template <int W>
-__device__ inline wint<W> load_entry(const uint32_t *tab, int entry)
-{
-    wint<W> r;
-    const uint4 *p = reinterpret_cast<const uint4 *>(tab + (uint32_t)entry * (uint32_t)W);
-#pragma unroll
-    for (int i = 0; i < W / 4; i++) {
-        const uint4 v = p[i];
-        r.w[4 * i] = v.x; r.w[4 * i + 1] = v.y; r.w[4 * i + 2] = v.z; r.w[4 * i + 3] = v.w;
-    }
-    return r;
-}
-
-// a += b (modulo 2^(32W))
-template <int W>
-__device__ inline void add_to(wint<W> &a, const wint<W> &b)
-{
-    uint32_t carry = 0;
-#pragma unroll
-    for (int i = 0; i < W; i++) a.w[i] = __builtin_addc(a.w[i], b.w[i], carry, &carry);
-}
-
 // A lane's value moved by one data-parallel-primitive pattern; lanes whose row is not in ROWS, or whose
 // source lies outside their row, get `idle`.
 template <int CTRL, int ROWS = 0xF>
@@ -72,24 +45,9 @@ __device__ inline uint32_t dpp_move(uint32_t v, uint32_t idle = 0)
 // The six steps that bring a combination of all 64 lanes' values to lane 63: lane^1, lane^2 (quad
 // permutations), the other quad of the half row and the other half of the row (mirror patterns: the
 // partner holds the same value as every lane of its group by then), row 0 into 1 and 2 into 3, rows 0..1
-// into 2..3.  For sums this is the adjacent-pair order, level by level.  No LDS traffic.
+// into 2..3.  No LDS traffic.
 #define PVQ_WAVE_STEPS(STEP)                                       \
     STEP(0xB1, 0xF) STEP(0x4E, 0xF) STEP(0x141, 0xF) STEP(0x140, 0xF) STEP(0x142, 0xA) STEP(0x143, 0xC)
-
-__device__ inline float wave_sum_pairs(float v)
-{
-#define PVQ_STEP(CTRL, ROWS) v = v + __uint_as_float(dpp_move<CTRL, ROWS>(__float_as_uint(v)));
-    PVQ_WAVE_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-    return __uint_as_float(__builtin_amdgcn_readlane((int)__float_as_uint(v), 63));
-}
-__device__ inline int wave_sum_int(int v)
-{
-#define PVQ_STEP(CTRL, ROWS) v += (int)dpp_move<CTRL, ROWS>((uint32_t)v);
-    PVQ_WAVE_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-    return __builtin_amdgcn_readlane(v, 63);
-}
 
 struct encode_wide_params {
     const void *X;
@@ -104,180 +62,14 @@ struct encode_wide_params {
     int64_t cols;
 };
 
-// TIN: 0 = float32, 2 = bf16.  A workgroup takes tile_groups consecutive groups of one row, chosen so
-// that their indices fill whole words; the words are put together in LDS and stored once.
-template <int TIN, int CP, int W>
-__global__ __launch_bounds__(512) void encode_wide_kernel(encode_wide_params p)
-{
-    extern __shared__ __align__(16) uint32_t stream[];
-    constexpr int D = 64 * CP;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), nwaves = blockDim.x >> 6;
-    const int64_t row = blockIdx.x / p.tiles_per_row;
-    const int tile = blockIdx.x - (int)(row * p.tiles_per_row);
-    const int64_t g0 = (int64_t)tile * p.tile_groups;
-    const int ng = (int)min((int64_t)p.tile_groups, p.groups - g0);
-    const int tile_words = (int)(((int64_t)ng * p.bits + 31) / 32);
-    const int64_t first_word = g0 * p.bits / 32;   // exact: tile_groups * bits is a multiple of 32
-    const int K = p.K;
-
-    for (int i = threadIdx.x; i < tile_words; i += blockDim.x) stream[i] = 0;
-    __syncthreads();
-
-    for (int gi = wave; gi < ng; gi += nwaves) {
-        const int64_t g = g0 + gi;
-        float w[CP];
-        if constexpr (TIN == PVQ_F32) {
-            const float *src = reinterpret_cast<const float *>(p.X) + row * p.ldx + g * D + CP * lane;
-            if constexpr (CP == 2) {
-                const float2 v = *reinterpret_cast<const float2 *>(src);
-                w[0] = v.x; w[1] = v.y;
-            } else {
-                w[0] = src[0];
-            }
-        } else {
-            const uint16_t *src = reinterpret_cast<const uint16_t *>(p.X) + row * p.ldx + g * D + CP * lane;
-            if constexpr (CP == 2) {
-                const uint32_t v = *reinterpret_cast<const uint32_t *>(src);
-                w[0] = __uint_as_float(v << 16); w[1] = __uint_as_float(v & 0xFFFF0000u);
-            } else {
-                w[0] = __uint_as_float((uint32_t)src[0] << 16);
-            }
-        }
-
-        // ---- the point (Sec. 2.5): project onto sum |t| = K, round, repair the pulse count
-        float a[CP], l1p, ssp;
-#pragma unroll
-        for (int j = 0; j < CP; j++) a[j] = fabsf(w[j]);
-        if constexpr (CP == 2) { l1p = a[0] + a[1]; ssp = w[0] * w[0] + w[1] * w[1]; }
-        else { l1p = a[0]; ssp = w[0] * w[0]; }
-        const float l1 = wave_sum_pairs(l1p), ss = wave_sum_pairs(ssp);
-        const float gain = (float)K / l1;
-        const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(gain < INFINITY);
-        float t[CP];
-        int m[CP];
-        int S = 0;
-#pragma unroll
-        for (int j = 0; j < CP; j++) {
-            t[j] = a[j] * gain;
-            m[j] = degenerate ? 0 : (int)rintf(t[j]);
-            S += m[j];
-        }
-        S = wave_sum_int(S);
-        if (degenerate) {
-            if (lane == 63) m[CP - 1] = K;   // the point (0, ..., 0, +K): index 0
-            S = K;
-        }
-        // one pulse per step: off the coordinate that lies furthest above its projected value (among
-        // those that have one), or onto the one furthest below; ties go to the lowest coordinate.  A
-        // valid group needs at most D/2 steps.
-        for (int step = 0; step < D && S != K; step++) {
-            const bool down = S > K;
-            float be = -INFINITY;
-            int bi = 0x7FFFFFFF;
-#pragma unroll
-            for (int j = 0; j < CP; j++) {
-                const float e = down ? (float)m[j] - t[j] : t[j] - (float)m[j];
-                const bool can = !down || m[j] > 0;
-                if (can && (bi == 0x7FFFFFFF || e > be)) { be = e; bi = CP * lane + j; }
-            }
-#define PVQ_STEP(CTRL, ROWS)                                                                             \
-    {                                                                                                    \
-        const float oe = __uint_as_float(dpp_move<CTRL, ROWS>(__float_as_uint(be), 0xFF800000u));        \
-        const int oi = (int)dpp_move<CTRL, ROWS>((uint32_t)bi, 0x7FFFFFFFu);                             \
-        const bool take = oi != 0x7FFFFFFF && (bi == 0x7FFFFFFF || oe > be || (oe == be && oi < bi));    \
-        if (take) { be = oe; bi = oi; }                                                                  \
-    }
-            PVQ_WAVE_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-            bi = __builtin_amdgcn_readlane(bi, 63);
-#pragma unroll
-            for (int j = 0; j < CP; j++)
-                if (bi == CP * lane + j) m[j] += down ? -1 : 1;
-            S += down ? -1 : 1;
-        }
-
-        // ---- amplitude (Sec. 2.3, or Sec. 3.3 Step 4)
-        float amp;
-        if (p.ls) {
-            float dp;
-            int n2 = 0;
-            float pr[CP];
-#pragma unroll
-            for (int j = 0; j < CP; j++) {
-                const int ys = w[j] < 0.0f ? -m[j] : m[j];
-                pr[j] = (float)ys * w[j];
-                n2 += m[j] * m[j];
-            }
-            if constexpr (CP == 2) dp = pr[0] + pr[1]; else dp = pr[0];
-            amp = wave_sum_pairs(dp) / sqrtf((float)wave_sum_int(n2));
-        } else {
-            amp = sqrtf(ss);
-        }
-        if (lane == 0) p.scale_out[row * p.groups + g] = amp;
-        if (p.pulses_out) {
-#pragma unroll
-            for (int j = 0; j < CP; j++)
-                p.pulses_out[row * p.cols + g * D + CP * lane + j] = (int8_t)(w[j] < 0.0f ? -m[j] : m[j]);
-        }
-
-        // ---- the index (App. B.2): pulses left before each coordinate, then the terms
-        int mine = 0;
-#pragma unroll
-        for (int j = 0; j < CP; j++) mine += m[j];
-        int incl = mine;   // inclusive prefix sum over the lanes: inside the rows of 16, then across them
-        incl += (int)dpp_move<0x111>((uint32_t)incl);        // row_shr:1
-        incl += (int)dpp_move<0x112>((uint32_t)incl);        // row_shr:2
-        incl += (int)dpp_move<0x114>((uint32_t)incl);        // row_shr:4
-        incl += (int)dpp_move<0x118>((uint32_t)incl);        // row_shr:8
-        incl += (int)dpp_move<0x142, 0xA>((uint32_t)incl);   // lane 15 of rows 0, 2 into rows 1, 3
-        incl += (int)dpp_move<0x143, 0xC>((uint32_t)incl);   // lane 31 into rows 2, 3
-        int k = K - (incl - mine);   // pulses left before this lane's first coordinate
-        wint<W> acc;
-#pragma unroll
-        for (int i = 0; i < W; i++) acc.w[i] = 0;
-#pragma unroll
-        for (int j = 0; j < CP; j++) {
-            const int row_t = D - 1 - (CP * lane + j);
-            const int kk = min(max(k, 0), K), mm = min(max(m[j], 0), kk);   // in range whatever the input
-            k = kk - mm;
-            const int at = 2 * k + (mm > 0 && !(w[j] < 0.0f) ? 1 : 0);
-            if (at) add_to(acc, load_entry<W>(p.tab_t, row_t * p.row_len + at));     // (T_0 = 0)
-        }
-#define PVQ_STEP(CTRL, ROWS)                                                           \
-    {                                                                                  \
-        wint<W> other;                                                                 \
-        _Pragma("unroll") for (int i = 0; i < W; i++) other.w[i] = dpp_move<CTRL, ROWS>(acc.w[i]); \
-        add_to(acc, other);                                                            \
-    }
-        PVQ_WAVE_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-
-        // ---- into the tile's bit stream: lane i takes word i of the index (lane 63 has it), shifted to
-        // its place
-        uint32_t word = 0, borrow = 0;
-#pragma unroll
-        for (int i = 0; i < W; i++) {
-            const uint32_t wi = __builtin_subc(p.last_index[i], (uint32_t)__builtin_amdgcn_readlane((int)acc.w[i], 63), borrow, &borrow);
-            word = lane == i ? wi : word;
-        }
-        const int off = gi * p.bits, sh = off & 31, w0 = off >> 5;
-        const uint32_t below = __shfl_up(word, 1, 64);
-        const uint32_t prev = lane > 0 ? below : 0u;
-        const uint32_t out = sh ? (word << sh) | (prev >> (32 - sh)) : word;
-        if (lane <= W && w0 + lane < tile_words && out) atomicOr(&stream[w0 + lane], out);
-    }
-    __syncthreads();
-    uint32_t *dst = p.index_out + row * p.index_row_words + first_word;
-    for (int i = threadIdx.x; i < tile_words; i += blockDim.x) dst[i] = stream[i];
-}
-
-// The same encoder with 16 lanes per group and four groups per wave (lane = 16 * group + sub, sub holds
-// coordinates CP*sub .. CP*sub+CP-1, CP = D/16): the sums, the argmax, the prefix sum and the multi-word
-// total then need four cross-lane levels instead of six, all of them permutations inside a row of 16
-// lanes after which every lane of the row holds the result, and a lane's own coordinates (four or eight)
-// are independent work in between.  That form remains for indices of more than 12 words, whose 17
-// stream words do not fit 16 lanes.
+// Encoding, 16 lanes per group and four groups per wave (lane = 16 * group + sub, sub holds coordinates CP*sub ..
+// CP*sub+CP-1, CP = D/16): the sums, the largest deviation, the prefix sum and the multi-word total need four cross-lane
+// levels, all of them permutations inside a row of 16 lanes after which every lane of the row holds the result, and a lane's
+// own coordinates (four or eight) are independent work in between.
+// Bound by vector instructions (1020 a wave at D = 128, K = 187, with the rotation in front) and the gathers of thresholds.
+// 2048 rows of 8192 rotated and encoded: 88 us, K = 84: 60 us; 2048 x 8192 encoded, D = 64, K = 96: 43 us.  With 90
+// instructions and not 30 per pulse that has to move, and a lane reading all of an entry's pieces: 101, 100, 64 us.  A wave
+// per group, the form of small batches before: 7.7 and 11 us for 32 and 4096 groups (D = 128, K = 187), this one 6.9 and 7.7.
 #define PVQ_ROW_STEPS(STEP) STEP(0xB1) STEP(0x4E) STEP(0x141) STEP(0x140)
 
 __device__ inline float row_sum_pairs(float v)
@@ -287,14 +79,6 @@ __device__ inline float row_sum_pairs(float v)
 #undef PVQ_STEP
     return v;
 }
-__device__ inline int row_sum_int(int v)
-{
-#define PVQ_STEP(CTRL) v += (int)dpp_move<CTRL>((uint32_t)v);
-    PVQ_ROW_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-    return v;
-}
-
 // sum of CP values over adjacent pairs, level by level
 template <int CP>
 __device__ inline float tree_sum(const float (&x)[CP])
@@ -318,123 +102,188 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
                                       const encode_wide_params &p, uint32_t *stream, int tile_words)
 {
     constexpr int D = 16 * CP;
-    const int K = p.K;
-    // ---- the point (Sec. 2.5)
-    float a[CP], sq[CP], t[CP];
+    // ---- the point (Sec. 2.5): the magnitudes as floats, which add and multiply at twice the rate of integers
+    const float K = (float)p.K;
+    float tmp[CP], t[CP];
 #pragma unroll
-    for (int j = 0; j < CP; j++) { a[j] = fabsf(w[j]); sq[j] = w[j] * w[j]; }
-    const float l1 = row_sum_pairs(tree_sum<CP>(a)), ss = row_sum_pairs(tree_sum<CP>(sq));
-    const float gain = (float)K / l1;
+    for (int j = 0; j < CP; j++) tmp[j] = fabsf(w[j]);
+    const float l1 = row_sum_pairs(tree_sum<CP>(tmp));
+#pragma unroll
+    for (int j = 0; j < CP; j++) tmp[j] = w[j] * w[j];
+    const float ss = row_sum_pairs(tree_sum<CP>(tmp));
+    const float gain = K / l1;
+    // no direction: the point is (0, ..., 0, +K), zeros here until the pulses have been moved
     const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(gain < INFINITY);
-    int m[CP];
-    int S = 0;
+    const bool any_degenerate = __any(degenerate);
 #pragma unroll
-    for (int j = 0; j < CP; j++) {
-        t[j] = a[j] * gain;
-        m[j] = degenerate ? 0 : (int)rintf(t[j]);
-        S += m[j];
-    }
-    S = row_sum_int(S);
-    if (degenerate) {
-        if (sub == 15) m[CP - 1] = K;   // the point (0, ..., 0, +K): index 0
-        S = K;
-    }
-    // one pulse per step and group, as in the wave-per-group form; the wave goes on while any of its
-    // four groups is off the pyramid (a valid group needs at most D/2 steps)
-    for (int step = 0; step < D; step++) {
-        const bool need = S != K;           // the same in the 16 lanes of a group
-        if (!__any(need)) break;
-        const bool down = S > K;
-        float be = -INFINITY;
-        int bi = 0x7FFFFFFF;
+    for (int j = 0; j < CP; j++) t[j] = fabsf(w[j]) * gain;
+    if (any_degenerate) {
 #pragma unroll
-        for (int j = 0; j < CP; j++) {
-            const float e = down ? (float)m[j] - t[j] : t[j] - (float)m[j];
-            const bool can = !down || m[j] > 0;
-            if (can && (bi == 0x7FFFFFFF || e > be)) { be = e; bi = CP * sub + j; }
-        }
-#define PVQ_STEP(CTRL)                                                                                   \
-{                                                                                                    \
-    const float oe = __uint_as_float(dpp_move<CTRL>(__float_as_uint(be), 0xFF800000u));              \
-    const int oi = (int)dpp_move<CTRL>((uint32_t)bi, 0x7FFFFFFFu);                                   \
-    const bool take = oi != 0x7FFFFFFF && (bi == 0x7FFFFFFF || oe > be || (oe == be && oi < bi));    \
-    if (take) { be = oe; bi = oi; }                                                                  \
-}
+        for (int j = 0; j < CP; j++) t[j] = degenerate ? 0.0f : t[j];
+    }
+    float m[CP];
+#pragma unroll
+    for (int j = 0; j < CP; j++) { m[j] = rintf(t[j]); tmp[j] = m[j]; }
+    // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
+    const float miss = (degenerate ? 0.0f : K) - row_sum_pairs(tree_sum<CP>(tmp));
+    const float unit = miss < 0.0f ? -1.0f : 1.0f, need = fabsf(miss);
+    // one pulse per step and group on the largest deviation (negated where pulses have to go), lowest coordinate on ties, as
+    // bits of floats: those that are looked for are positive, and none comes up twice (a place taken gets the key -1, the
+    // bits of no deviation).  The wave goes on while any of its four groups is off the pyramid, about five steps at D = 128.
+    int key[CP];
+#pragma unroll
+    for (int j = 0; j < CP; j++) key[j] = (int)__float_as_uint((t[j] - m[j]) * unit);
+#pragma unroll 1
+    for (float step = 0.0f; step < (float)D && __any(need > step); step += 1.0f) {
+        const bool open = need > step;      // the same in the 16 lanes of a group
+        int largest = max(key[0], key[1]);
+#pragma unroll
+        for (int j = 2; j < CP; j += 2) largest = max(max(largest, key[j]), key[j + 1]);
+        int best = largest;
+#define PVQ_STEP(CTRL) best = max(best, (int)dpp_move<CTRL>((uint32_t)best, 0x80000000u));
         PVQ_ROW_STEPS(PVQ_STEP)
 #undef PVQ_STEP
-        if (need) {
-#pragma unroll
-            for (int j = 0; j < CP; j++)
-                if (bi == CP * sub + j) m[j] += down ? -1 : 1;
-            S += down ? -1 : 1;
+        bool taken = !(open && largest == best);
+        if (16 * __popcll(__ballot(!taken)) != __popcll(__ballot(open))) {      // a tie between lanes of a group
+            int first = taken ? 16 : sub;
+#define PVQ_STEP(CTRL) first = min(first, (int)dpp_move<CTRL>((uint32_t)first, 0x7FFFFFFFu));
+            PVQ_ROW_STEPS(PVQ_STEP)
+#undef PVQ_STEP
+            taken = taken || first != sub;
         }
+#pragma unroll
+        for (int j = 0; j < CP; j++) {
+            const bool equal = key[j] == best;
+            key[j] = equal && !taken ? -1 : key[j];
+            taken = taken || equal;
+        }
+    }
+    float y[CP];
+#pragma unroll
+    for (int j = 0; j < CP; j++) {
+        m[j] += key[j] == -1 ? unit : 0.0f;
+        y[j] = copysignf(m[j], w[j]);
+    }
+    if (any_degenerate && degenerate && sub == 15) {
+        m[CP - 1] = K;
+        y[CP - 1] = w[CP - 1] < 0.0f ? -K : K;
     }
 
     // ---- amplitude (Sec. 2.3, or Sec. 3.3 Step 4)
     float amp;
     if (p.ls) {
         float pr[CP];
-        int n2 = 0;
 #pragma unroll
         for (int j = 0; j < CP; j++) {
-            const int ys = w[j] < 0.0f ? -m[j] : m[j];
-            pr[j] = (float)ys * w[j];
-            n2 += m[j] * m[j];
+            pr[j] = y[j] * w[j];
+            tmp[j] = m[j] * m[j];
         }
-        amp = row_sum_pairs(tree_sum<CP>(pr)) / sqrtf((float)row_sum_int(n2));
+        if (any_degenerate) {
+            // zeros of the point are positive (the sign of a sum of zeros is theirs)
+#pragma unroll
+            for (int j = 0; j < CP; j++) pr[j] = m[j] == 0.0f ? 0.0f * w[j] : pr[j];
+        }
+        amp = row_sum_pairs(tree_sum<CP>(pr)) / sqrtf(row_sum_pairs(tree_sum<CP>(tmp)));
     } else {
         amp = sqrtf(ss);
     }
     if (on && sub == 0) p.scale_out[row * p.groups + g] = amp;
     if (on && p.pulses_out) {
 #pragma unroll
-        for (int j = 0; j < CP; j++)
-            p.pulses_out[row * p.cols + g * D + CP * sub + j] = (int8_t)(w[j] < 0.0f ? -m[j] : m[j]);
+        for (int j = 0; j < CP; j++) p.pulses_out[row * p.cols + g * D + CP * sub + j] = (int8_t)(int)y[j];
     }
 
-    // ---- the index (App. B.2)
-    int mine = 0;
-#pragma unroll
-    for (int j = 0; j < CP; j++) mine += m[j];
-    int incl = mine;   // inclusive prefix sum over the 16 lanes of the group
-    incl += (int)dpp_move<0x111>((uint32_t)incl);        // row_shr:1
-    incl += (int)dpp_move<0x112>((uint32_t)incl);        // row_shr:2
-    incl += (int)dpp_move<0x114>((uint32_t)incl);        // row_shr:4
-    incl += (int)dpp_move<0x118>((uint32_t)incl);        // row_shr:8
-    int k = K - (incl - mine);
-    wint<W> acc;
-#pragma unroll
-    for (int i = 0; i < W; i++) acc.w[i] = 0;
+    // ---- the index (App. B.2): the bytes of the coordinates' thresholds in the table, as floats whose bits are the integers
+    // (below 2^24, to which they add and multiply exactly)
+    constexpr uint32_t kEntry = 4 * W;
+    const uint32_t row_bytes = (uint32_t)p.row_len * kEntry;
+    float mine = tree_sum<CP>(m), incl = mine;   // inclusive prefix sum over the 16 lanes of the group
+    incl += __uint_as_float(dpp_move<0x111>(__float_as_uint(incl)));        // row_shr:1
+    incl += __uint_as_float(dpp_move<0x112>(__float_as_uint(incl)));        // row_shr:2
+    incl += __uint_as_float(dpp_move<0x114>(__float_as_uint(incl)));        // row_shr:4
+    incl += __uint_as_float(dpp_move<0x118>(__float_as_uint(incl)));        // row_shr:8
+    float left = K - (incl - mine);              // pulses left in front of the lane's first coordinate
+    float trow = __uint_as_float((uint32_t)(D - 1 - CP * sub) * row_bytes);
+    uint32_t from[CP];
 #pragma unroll
     for (int j = 0; j < CP; j++) {
-        const int row_t = D - 1 - (CP * sub + j);
-        const int kk = min(max(k, 0), K), mm = min(max(m[j], 0), kk);   // in range whatever the input
-        k = kk - mm;
-        const int at = 2 * k + (mm > 0 && !(w[j] < 0.0f) ? 1 : 0);
-        // (T_0 = 0.  The condition keeps the entries from being read all at once: fewer registers, more waves, which is
-        // what hides the trips to the L2: without it 155 instead of 94 us for 2048 x 8192 values rotated and encoded)
-        if (at) add_to(acc, load_entry<W>(p.tab_t, row_t * p.row_len + at));
+        left -= m[j];
+        const float k = __builtin_amdgcn_fmed3f(left, 0.0f, K);              // (in range whatever the input)
+        const float positive = __builtin_amdgcn_fmed3f(y[j], 0.0f, 1.0f);
+        from[j] = __float_as_uint(fmaf(positive, __uint_as_float(kEntry), fmaf(k, __uint_as_float(2 * kEntry), trow)));
+        trow -= __uint_as_float(row_bytes);
     }
-#define PVQ_STEP(CTRL)                                                                  \
-{                                                                                   \
-    wint<W> other;                                                                  \
-    _Pragma("unroll") for (int i = 0; i < W; i++) other.w[i] = dpp_move<CTRL>(acc.w[i]); \
-    add_to(acc, other);                                                             \
-}
-    PVQ_ROW_STEPS(PVQ_STEP)
+    // An entry is read by neighbouring lanes, 16 bytes each: a gather of 16 bytes a lane costs the vector memory path a cycle
+    // per lane, three of them for an entry of 12 words, and the lanes of a quad beside one another little more than one for
+    // all.  So lane i of a quad adds up piece i (of two pieces: i mod 2) of its quad's entries, with a word for what overflows.
+    constexpr int NP = W / 4, kLanes = NP == 3 ? 4 : NP;
+    const int i4 = sub & 3, piece = kLanes == 4 ? min(i4, NP - 1) : i4 & (kLanes - 1);
+    uint32_t acc[5] = {};
+    const unsigned char *base = reinterpret_cast<const unsigned char *>(p.tab_t);
+    u32x4 e[2][kLanes];
+    auto request = [&](u32x4 (&e)[kLanes], uint32_t at) {
+        uint32_t a[kLanes];
+        if constexpr (kLanes == 4) {
+            a[0] = dpp_move<0x00>(at); a[1] = dpp_move<0x55>(at); a[2] = dpp_move<0xAA>(at); a[3] = dpp_move<0xFF>(at);
+        } else if constexpr (kLanes == 2) {
+            a[0] = dpp_move<0x50>(at); a[1] = dpp_move<0xFA>(at);             // lanes 0 0 1 1, 2 2 3 3
+        } else {
+            a[0] = at;
+        }
+#pragma unroll
+        for (int l = 0; l < kLanes; l++) e[l] = *reinterpret_cast<const u32x4 *>(base + (a[l] + 16u * piece));
+    };
+    auto add5 = [&](uint32_t w0, uint32_t w1, uint32_t w2, uint32_t w3, uint32_t w4) {
+        uint32_t c;
+        acc[0] = __builtin_addc(acc[0], w0, 0u, &c);
+        acc[1] = __builtin_addc(acc[1], w1, c, &c);
+        acc[2] = __builtin_addc(acc[2], w2, c, &c);
+        acc[3] = __builtin_addc(acc[3], w3, c, &c);
+        acc[4] = __builtin_addc(acc[4], w4, c, &c);
+    };
+    request(e[0], from[0]);
+#pragma unroll
+    for (int j = 0; j < CP; j++) {
+        if (j + 1 < CP) request(e[(j + 1) & 1], from[j + 1]);
+#pragma unroll
+        for (int l = 0; l < kLanes; l++) add5(e[j & 1][l].x, e[j & 1][l].y, e[j & 1][l].z, e[j & 1][l].w, 0u);
+    }
+#define PVQ_STEP(CTRL) add5(dpp_move<CTRL>(acc[0]), dpp_move<CTRL>(acc[1]), dpp_move<CTRL>(acc[2]), dpp_move<CTRL>(acc[3]), dpp_move<CTRL>(acc[4]));
+    if constexpr (kLanes < 2) { PVQ_STEP(0xB1) }
+    if constexpr (kLanes < 4) { PVQ_STEP(0x4E) }
+    PVQ_STEP(0x124) PVQ_STEP(0x128)              // the quads of the group: rotations by 4 and 8
 #undef PVQ_STEP
 
-    // ---- into the tile's bit stream: lane sub = i of the group takes word i of the index
-    uint32_t word = 0, borrow = 0;
+    // N(D,K) - 1 less the sum: every piece by itself, then what it owes the next
+    uint32_t d[4], owed = 0;
 #pragma unroll
-    for (int i = 0; i < W; i++) {
-        const uint32_t wi = __builtin_subc(p.last_index[i], acc.w[i], borrow, &borrow);
-        word = sub == i ? wi : word;
+    for (int x = 0; x < 4; x++) {
+        uint32_t last = p.last_index[x];
+#pragma unroll
+        for (int n = 1; n < NP; n++) last = i4 == n ? p.last_index[4 * n + x] : last;
+        d[x] = __builtin_subc(last, acc[x], owed, &owed);
     }
-    const int off = gl * p.bits, sh = off & 31, w0 = off >> 5;
-    const uint32_t prev = dpp_move<0x111>(word);         // word sub-1, zero for sub = 0
+    owed += acc[4];
+#pragma unroll
+    for (int n = 1; n < NP; n++) {
+        uint32_t c, in = dpp_move<0x90>(owed);                               // of the lane before in the quad (all lanes move)
+        in = i4 == 0 ? 0u : in;
+        d[0] = __builtin_subc(d[0], in, 0u, &c);
+        d[1] = __builtin_subc(d[1], 0u, c, &c);
+        d[2] = __builtin_subc(d[2], 0u, c, &c);
+        d[3] = __builtin_subc(d[3], 0u, c, &owed);
+    }
+    // ---- into the tile's bit stream: of quad x, lane i takes word 4 i + x of the index, the last of them what it shifts out
+    const int quad = sub >> 2;
+    uint32_t before = dpp_move<0x90>(d[3]);
+    before = i4 == 0 ? 0u : before;
+    const uint32_t word = quad == 0 ? d[0] : quad == 1 ? d[1] : quad == 2 ? d[2] : d[3];
+    const uint32_t prev = quad == 0 ? before : quad == 1 ? d[0] : quad == 2 ? d[1] : d[2];
+    const int off = gl * p.bits, sh = off & 31, w0 = off >> 5, at = 4 * i4 + quad;
     const uint32_t out = sh ? (word << sh) | (prev >> (32 - sh)) : word;
-    if (on && sub <= W && w0 + sub < tile_words && out) atomicOr(&stream[w0 + sub], out);
+    if (on && at < W && w0 + at < tile_words && out) atomicOr(&stream[w0 + at], out);
+    const uint32_t over = sh ? word >> (32 - sh) : 0u;
+    if (on && at == W - 1 && w0 + W < tile_words && over) atomicOr(&stream[w0 + W], over);
 }
 
 template <int TIN, int CP, int W>
@@ -498,7 +347,7 @@ struct rotate_encode_params {
 };
 
 template <int TIN, int W, int LOG2N>
-__global__ __launch_bounds__(1024) void rotate_encode16_kernel(rotate_encode_params p)
+__global__ __launch_bounds__(1024, 8) void rotate_encode16_kernel(rotate_encode_params p)
 {
     extern __shared__ __align__(16) float smem[];
     const int L = blockDim.x;
@@ -1236,33 +1085,24 @@ hipError_t pvq_wide_launch_encode(const pvq_ctx *c, const pvq_encode_args &a, in
     for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
     p.index_out = a.index_out; p.scale_out = reinterpret_cast<float *>(a.scale_out); p.pulses_out = a.pulses_out;
     p.cols = a.cols;
-    // 16 lanes per group, four groups per wave, when the index and the word it may spill into fit 16 lanes
-    // and there are enough groups to fill the waves; else a wave per group (shorter chain per group)
-    const bool rows16 = c->words <= 12 && a.rows * a.groups >= 16384;
-    p.tile_groups = 32 / gcd_int(c->index_bits, 32);
-    if (rows16 && p.tile_groups < 4) p.tile_groups = 4;
+    // tiles of whole words and whole waves, four groups each
+    p.tile_groups = std::max(4, 32 / gcd_int(c->index_bits, 32));
     p.tiles_per_row = (int)((a.groups + p.tile_groups - 1) / p.tile_groups);
     if (a.rows * p.tiles_per_row > 0x7FFFFFFF) return hipErrorInvalidValue;
-    const int per_wave = rows16 ? 4 : 1;
-    const int waves = std::min(p.tile_groups / per_wave, 8);
+    const int waves = std::min(p.tile_groups / 4, 8);
     const size_t lds = (size_t)(p.tile_groups * c->index_bits / 32) * 4;
     const dim3 grid((unsigned)(a.rows * p.tiles_per_row)), blk(64u * waves);
-#define PVQ_WIDE_ENC(T, CP, W) hipLaunchKernelGGL((encode_wide_kernel<T, CP, W>), grid, blk, lds, s, p)
-#define PVQ_WIDE_ENC16(T, CP, W) hipLaunchKernelGGL((encode_wide16_kernel<T, CP, W>), grid, blk, lds, s, p)
+#define PVQ_WIDE_ENC(T, CP, W) hipLaunchKernelGGL((encode_wide16_kernel<T, CP, W>), grid, blk, lds, s, p)
 #define PVQ_WIDE_ENC_W(T, D64)                                                                                  \
     switch (c->words) {                                                                                         \
-    case 4: if (rows16) { if (D64) PVQ_WIDE_ENC16(T, 4, 4); else PVQ_WIDE_ENC16(T, 8, 4); }                     \
-            else { if (D64) PVQ_WIDE_ENC(T, 1, 4); else PVQ_WIDE_ENC(T, 2, 4); } break;                         \
-    case 8: if (rows16) { if (D64) PVQ_WIDE_ENC16(T, 4, 8); else PVQ_WIDE_ENC16(T, 8, 8); }                     \
-            else { if (D64) PVQ_WIDE_ENC(T, 1, 8); else PVQ_WIDE_ENC(T, 2, 8); } break;                         \
-    case 12: if (rows16) { if (D64) PVQ_WIDE_ENC16(T, 4, 12); else PVQ_WIDE_ENC16(T, 8, 12); }                  \
-             else { if (D64) PVQ_WIDE_ENC(T, 1, 12); else PVQ_WIDE_ENC(T, 2, 12); } break;                      \
-    default: if (D64) PVQ_WIDE_ENC(T, 1, 16); else PVQ_WIDE_ENC(T, 2, 16); break;                               \
+    case 4: if (D64) PVQ_WIDE_ENC(T, 4, 4); else PVQ_WIDE_ENC(T, 8, 4); break;                                  \
+    case 8: if (D64) PVQ_WIDE_ENC(T, 4, 8); else PVQ_WIDE_ENC(T, 8, 8); break;                                  \
+    case 12: if (D64) PVQ_WIDE_ENC(T, 4, 12); else PVQ_WIDE_ENC(T, 8, 12); break;                               \
+    default: if (D64) PVQ_WIDE_ENC(T, 4, 16); else PVQ_WIDE_ENC(T, 8, 16); break;                               \
     }
     const bool d64 = c->D == 64;
     if (dtype == PVQ_F32) { PVQ_WIDE_ENC_W(PVQ_F32, d64) } else { PVQ_WIDE_ENC_W(PVQ_BF16, d64) }
 #undef PVQ_WIDE_ENC_W
-#undef PVQ_WIDE_ENC16
 #undef PVQ_WIDE_ENC
     return hipGetLastError();
 }
