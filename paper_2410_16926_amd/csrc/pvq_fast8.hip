@@ -802,8 +802,17 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_mfma_kernel(fast8_launch f
 // decode to a matrix
 // ---------------------------------------------------------------------------------------------
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
+// Where of a wave's 64 groups a lane's is: a store instruction is to write one contiguous KiB.  A group is 16 bytes of 16-bit
+// values; of float32 it is 32, which lanes 2i and 2i + 1, with groups i and 32 + i, store together, 16 bytes each
+// (28672 x 8192 247 us, 8192 x 8192 71; 16 bytes out of every 32 a lane, in two stores: 301 and 90).
 template <int OUT>
-__device__ inline void store_group(void *W_out, int64_t elem, const uint32_t (&pr)[4], float gain)
+__device__ inline int group_place(int lane) { return OUT == PVQ_F32 ? (lane >> 1) + 32 * (lane & 1) : lane; }
+
+// Stores the lanes' groups; g: the lane's group, of G in the row at `out`.
+template <int OUT>
+__device__ inline void store_group(void *out, int g, int G, int lane, const uint32_t (&pr)[4], float gain)
 {
     float v[8];
 #pragma unroll
@@ -812,11 +821,21 @@ __device__ inline void store_group(void *W_out, int64_t elem, const uint32_t (&p
         v[2 * j + 1] = gain * __uint_as_float(pr[j] & 0xFFFF0000u);
     }
     if constexpr (OUT == PVQ_F32) {
-        float *o = reinterpret_cast<float *>(W_out) + elem;
-        *reinterpret_cast<float4 *>(o) = make_float4(v[0], v[1], v[2], v[3]);
-        *reinterpret_cast<float4 *>(o + 4) = make_float4(v[4], v[5], v[6], v[7]);
+        const bool odd = lane & 1;
+        u32x4 first, second;                     // a half of group i, a half of group 32 + i
+#pragma unroll
+        for (int j = 0; j < 4; j++) {
+            const uint32_t lo = __float_as_uint(v[j]), hi = __float_as_uint(v[4 + j]);
+            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(odd ? lo : hi), 0xB1, 0xF, 0xF, false);
+            first[j] = odd ? other : lo;
+            second[j] = odd ? hi : other;
+        }
+        const int g0 = odd ? g - 32 : g;
+        float *o = reinterpret_cast<float *>(out) + (int64_t)g0 * 8 + 4 * (lane & 1);
+        if (g0 < G) *reinterpret_cast<u32x4 *>(o) = first;
+        if (g0 + 32 < G) *reinterpret_cast<u32x4 *>(o + 32 * 8) = second;
     } else {
-        uint32_t q[4];
+        u32x4 q;
 #pragma unroll
         for (int j = 0; j < 4; j++) {
             if constexpr (OUT == PVQ_F16) {
@@ -828,7 +847,7 @@ __device__ inline void store_group(void *W_out, int64_t elem, const uint32_t (&p
                 q[j] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
             }
         }
-        *reinterpret_cast<uint4 *>(reinterpret_cast<uint16_t *>(W_out) + elem) = make_uint4(q[0], q[1], q[2], q[3]);
+        if (g < G) *reinterpret_cast<u32x4 *>(reinterpret_cast<uint16_t *>(out) + (int64_t)g * 8) = q;
     }
 }
 
@@ -844,7 +863,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
     load_tables<false>(lds, f, sqrtc_l);
 
     const int G = (int)a.groups;
-    const int lane = threadIdx.x & (kWave - 1);
+    const int lane = threadIdx.x & (kWave - 1), place = group_place<OUT>(lane);
     // the wave's number as a scalar, so that rows, tiles and row addresses are computed once per wave
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int nwaves = blockDim.x / kWave;
@@ -864,7 +883,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
     float cur_rn = 1.0f, nxt_rn = 1.0f;
     bool live = item < i_end;     // uniform in the wave
     if (!live) return;            // (after the table copy's barrier; no barrier follows)
-    fetch_item<CODES, B24>(f, a, row, (int)tile * kTileGroups + lane, cur);
+    fetch_item<CODES, B24>(f, a, row, (int)tile * kTileGroups + place, cur);
     if constexpr (CODES) cur_rn = a.rownorm[row];
     while (live) {
         int64_t nrow = row + step_rows;
@@ -872,24 +891,21 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
         if (ntile >= T) { ntile -= T; nrow += 1; }
         const bool nlive = item + stride < i_end;
         if (!nlive) { nrow = row; ntile = tile; }     // nothing follows: fetch this item again, unused
-        fetch_item<CODES, B24>(f, a, nrow, (int)ntile * kTileGroups + lane, nxt);
+        fetch_item<CODES, B24>(f, a, nrow, (int)ntile * kTileGroups + place, nxt);
         if constexpr (CODES) nxt_rn = a.rownorm[nrow];
 
-        const int gbase = (int)tile * kTileGroups + lane;
+        const int gbase = (int)tile * kTileGroups + place;
         const float srn = CODES ? sqrtf(cur_rn) : 1.0f;
         uint32_t c[kGroupsPerLane], prs[kGroupsPerLane][4], n2x4s[kGroupsPerLane];
         item_indices<B24>(cur, gbase, c);
         pvq_fast8_decode<kGroupsPerLane, false>(lds, f.blob, f.p, c, prs, n2x4s);
 #pragma unroll
         for (int j = 0; j < kGroupsPerLane; j++) {
-            const int g = gbase + kWave * j;
-            if (g < G) {
-                // amp / sqrt(n2): the amplitude first (sqrt(center) * sqrt(row normaliser), or the stored
-                // float), then the tabulated 1/sqrt(n2)
-                const float amp = CODES ? sqrtc_l[item_code(f, cur, gbase, j)] * srn : __uint_as_float(cur.a[j]);
-                const float gain = amp * *reinterpret_cast<const float *>(lds + f.p.invs + n2x4s[j]);
-                store_group<OUT>(a.W_out, row * a.ldw + (int64_t)g * 8, prs[j], gain);
-            }
+            // amp / sqrt(n2): the amplitude first (sqrt(center) * sqrt(row normaliser), or the stored
+            // float), then the tabulated 1/sqrt(n2)
+            const float amp = CODES ? sqrtc_l[item_code(f, cur, gbase, j)] * srn : __uint_as_float(cur.a[j]);
+            const float gain = amp * *reinterpret_cast<const float *>(lds + f.p.invs + n2x4s[j]);
+            store_group<OUT>(reinterpret_cast<unsigned char *>(a.W_out) + row * a.ldw * (OUT == PVQ_F32 ? 4 : 2), gbase + kWave * j, G, lane, prs[j], gain);
         }
         cur = nxt; cur_rn = nxt_rn; row = nrow; tile = ntile; live = nlive; item += stride;
     }
