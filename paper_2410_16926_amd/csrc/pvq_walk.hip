@@ -40,6 +40,7 @@ using namespace pvq_walk;
 
 typedef __attribute__((ext_vector_type(4))) short bf16x4;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
 // the value of lane L of the lane's quad
@@ -131,12 +132,37 @@ __device__ inline float norm_gain(float amp, float n2)
     return fmaf(amp, r, amp * rest);
 }
 
-__device__ inline uint32_t f32_to_bf16_rne(float f)
+// The lanes of a pair (T = 2) or quad: chunk[j] of lane i goes to chunk[i] of lane j.  i: the lane's place.
+template <int CTRL>
+__device__ inline void exchange_chunks(u32x4 &a, u32x4 &b, bool upper)
+{
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const uint32_t from_a = (uint32_t)__builtin_amdgcn_mov_dpp((int)a[e], CTRL, 0xF, 0xF, true);
+        const uint32_t from_b = (uint32_t)__builtin_amdgcn_mov_dpp((int)b[e], CTRL, 0xF, 0xF, true);
+        a[e] = upper ? from_b : a[e];
+        b[e] = upper ? b[e] : from_a;
+    }
+}
+template <int T>
+__device__ inline void transpose_chunks(u32x4 (&c)[T], int i)
+{
+    if constexpr (T == 2) exchange_chunks<0xB1>(c[0], c[1], i & 1);          // the pair's other lane
+    if constexpr (T == 4) {
+        exchange_chunks<0xB1>(c[0], c[1], i & 1);
+        exchange_chunks<0xB1>(c[2], c[3], i & 1);
+        exchange_chunks<0x4E>(c[0], c[2], i & 2);                            // two lanes on in the quad
+        exchange_chunks<0x4E>(c[1], c[3], i & 2);
+    }
+}
+
+// two values in bfloat16, rounded to nearest even
+__device__ inline uint32_t bf16_pair(float lo, float hi)
 {
     typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2_t;
     typedef __attribute__((ext_vector_type(2))) float f32x2_t;
-    const f32x2_t pair = {f, 0.0f};
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t)) & 0xFFFFu;
+    const f32x2_t pair = {lo, hi};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, bf16x2_t));
 }
 
 __device__ inline uint16_t f32_to_f16_rne(float f) { return __builtin_bit_cast(uint16_t, (_Float16)f); }
@@ -160,22 +186,32 @@ __device__ inline void tables_to_lds(unsigned char *lds, const walk_launch &wl)
 
 // Decode to a matrix.  Workgroups stay for the whole launch (the tables are copied once each); after the copy
 // every wave works alone and takes (row, 64 consecutive groups) items in turn.  A lane's group is D consecutive
-// outputs, so the lanes of a wave would each store 16 bytes out of every D * size; with STAGE the wave lays
-// its 64 groups out in LDS instead and every store instruction writes 1 KiB of consecutive addresses.
+// outputs, NC chunks of 16 bytes, and lanes that stored their own would write 16 bytes out of every D * size.  The N lanes of
+// a pair or quad exchange chunks instead (an N x N transposition in registers, by data-parallel-primitive moves), so that a
+// store of a lane is one chunk of a group that all N store; and the lanes of a block of 4 N hold its groups in the order
+// in which the four pairs or quads then store consecutive groups: runs of 128 (N = 2) or 256 bytes (NC = 4; 64 bytes out of
+// every 128 for NC = 8).  28672 x 8192 in groups of 16 to float32 252 us, to bfloat16 144, 14336 x 4096 in groups of 32 to
+// bfloat16 51, to float32 96; laid out in LDS, or with larger tables stored as they are: 378, 174, 60 and 114.
+// Groups of 8 to float32 (STAGE, where LDS has room for it beside the tables) are laid out in LDS: the walk of so few
+// coordinates leaves no instructions to hide the exchange's behind (2500 x 5000 14.9 us, exchanged 15.6).
 template <int D, int W, int DX, int DA, int DB, int OUT, bool STAGE>
 __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl, pvq_decode_args a, int tiles)
 {
     using T = typename wide<W>::type;
     constexpr int OSZ = OUT == PVQ_F32 ? 4 : 2;
     constexpr int NC = D * OSZ / 16;                 // 16-byte chunks of one group
+    constexpr int N = STAGE ? 1 : NC < 4 ? NC : 4;
     const int kWaves = (int)blockDim.x / kWave;
     extern __shared__ __align__(16) unsigned char lds[];
     const float *sqrtc = reinterpret_cast<const float *>(lds);
     const int lane = threadIdx.x % kWave;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
-    uint4 *stage = reinterpret_cast<uint4 *>(lds + wl.p.bytes) + wave * (kWave * NC);
+    u32x4 *stage = reinterpret_cast<u32x4 *>(lds + wl.p.bytes) + wave * (kWave * NC);
     tables_to_lds(lds, wl);
     const int G = (int)a.groups;
+    // lane 4 N x + N y + i holds the wave's group 4 N x + 4 i + y, and stores chunk i (mod N) of the groups 4 N x + 4 j + y
+    const int i_t = lane % N, y_t = lane / N % 4, block = lane - lane % (4 * N);
+    const int place = block + 4 * i_t + y_t;
     const int64_t items = a.rows * tiles, stride = (int64_t)gridDim.x * kWaves;
     // What an item needs from memory is requested one item ahead, in front of the current item's stores: a
     // wait for a load also waits for every memory operation issued before it, so loads that follow stores
@@ -189,7 +225,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
     const int64_t step_rows = stride / tiles;
     const int step_tiles = (int)(stride - step_rows * tiles);
     auto fetch = [&](int64_t row, int tile) {
-        const int g = tile * kWave + lane;
+        const int g = tile * kWave + place;
         g_nx = g < G ? g : 0;
         fetch_group<W>(index_plane(a, row), 0u, reinterpret_cast<const unsigned char *>(a.scale) + row * srow_bytes, 0u,
                        g_nx, wl.index_bits, wl.scale_bits, nx);
@@ -206,7 +242,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
     for (int64_t item = first; item < items; item += stride) {
         const int64_t row = row_n;
         const int g0 = tile_n * kWave;                          // the wave's first group
-        const int g_mine = g_nx;                                // the lane's group: g0 + lane, or 0 past the row's end
+        const int g_mine = g_nx;                                // the lane's group: g0 + place, or 0 past the row's end
         const T c = group_index<W>(nx, g_mine, wl.index_bits);
         const float amp = group_amp<W>(nx, g_mine, wl.scale_bits, sqrtc) * sqrtf(norm_nx);
         row_n += step_rows;
@@ -220,42 +256,48 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
         const float gain = norm_gain(-amp, n2);
         // gain * y + 0: the product as it is, and +0 for a zero coordinate
         auto value = [&](int i) { return fmaf(gain, y[i], 0.0f); };
-        const int valid = std::min(kWave, G - g0);             // groups of this item inside the row
         unsigned char *orow = reinterpret_cast<unsigned char *>(a.W_out) + row * a.ldw * OSZ;
-        unsigned char *o = orow + (int64_t)g0 * D * OSZ;
 #pragma unroll
-        for (int j = 0; j < NC; j++) {
-            uint4 chunk;
-            if constexpr (OUT == PVQ_F32) {
-                chunk = make_uint4(__float_as_uint(value(4 * j)), __float_as_uint(value(4 * j + 1)),
-                                   __float_as_uint(value(4 * j + 2)), __float_as_uint(value(4 * j + 3)));
-            } else {
-                uint32_t pk[4];
+        for (int h = 0; h < NC; h += N) {
+            u32x4 chunk[N];
 #pragma unroll
-                for (int e = 0; e < 4; e++) {
-                    const float f0 = value(8 * j + 2 * e), f1 = value(8 * j + 2 * e + 1);
-                    if constexpr (OUT == PVQ_F16) pk[e] = (uint32_t)f32_to_f16_rne(f0) | ((uint32_t)f32_to_f16_rne(f1) << 16);
-                    else pk[e] = f32_to_bf16_rne(f0) | (f32_to_bf16_rne(f1) << 16);
+            for (int j = 0; j < N; j++) {
+                if constexpr (OUT == PVQ_F32) {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) chunk[j][e] = __float_as_uint(value(4 * (h + j) + e));
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; e++) {
+                        const float f0 = value(8 * (h + j) + 2 * e), f1 = value(8 * (h + j) + 2 * e + 1);
+                        if constexpr (OUT == PVQ_F16) chunk[j][e] = (uint32_t)f32_to_f16_rne(f0) | ((uint32_t)f32_to_f16_rne(f1) << 16);
+                        else chunk[j][e] = bf16_pair(f0, f1);
+                    }
                 }
-                chunk = make_uint4(pk[0], pk[1], pk[2], pk[3]);
             }
-            // without staging every lane stores its own group; lanes past the row's end have decoded the row's first
-            // group once more and store it where it belongs (the same bytes as its owner writes): no store is
-            // under a condition, see below
-            if constexpr (STAGE) stage[lane * NC + j] = chunk;
-            else *reinterpret_cast<uint4 *>(orow + ((size_t)g_mine * NC + j) * 16) = chunk;
+            if constexpr (STAGE) {
+                stage[lane * NC + h] = chunk[0];
+                continue;
+            }
+            transpose_chunks<N>(chunk, i_t);
+            // a place past the row's end holds the row's first group, decoded once more, which is stored where it belongs (the
+            // same bytes as its owner writes): no store is under a condition, so that the number of stores in flight is
+            // known where the next item's words are waited for, and that wait does not have to cover them
+#pragma unroll
+            for (int j = 0; j < N; j++) {
+                const int g = g0 + block + 4 * j + y_t;
+                const uint32_t at = (uint32_t)(g < G ? g : 0) * (NC * 16u) + (uint32_t)(h + i_t) * 16u;      // (rows have at most 2^21 groups)
+                *reinterpret_cast<u32x4 *>(orow + at) = chunk[j];
+            }
         }
         if constexpr (STAGE) {
-            // the item's groups are NC * valid consecutive chunks of the output.  Every lane stores in every pass:
-            // lanes past the item's end store its last chunk once more (the same bytes to the same place), so that
-            // the number of stores in flight is known where the next item's words are waited for, and that wait
-            // does not have to cover them
-            const int last = valid * NC - 1;
+            // the item's groups are consecutive chunks of the output; lanes past the item's end store its last chunk once
+            // more (no store under a condition here either)
+            const int last = std::min(kWave, G - g0) * NC - 1;
 #pragma unroll
             for (int j = 0; j < NC; j++) {
                 const int ch = std::min(j * kWave + lane, last);
-                const uint4 v = stage[ch];                     // written by this wave only: no barrier
-                *reinterpret_cast<uint4 *>(o + (size_t)ch * 16) = v;
+                const u32x4 v = stage[ch];                     // written by this wave only: no barrier
+                *reinterpret_cast<u32x4 *>(orow + (uint32_t)(g0 * NC + ch) * 16u) = v;
             }
         }
     }
@@ -442,11 +484,7 @@ walk_launch make_launch(const pvq_ctx *c)
 // ones once per sixteen waves
 int block_threads(const pvq_ctx *c) { return c->walk.bytes <= 20 * 1024 ? 256 : kMaxThreads; }
 
-// tables, and (decode with staging) 64 groups of outputs per wave
-size_t lds_bytes(const pvq_ctx *c, size_t group_out_bytes = 0)
-{
-    return (size_t)c->walk.bytes + (block_threads(c) / kWave) * kWave * group_out_bytes;
-}
+size_t lds_bytes(const pvq_ctx *c) { return (size_t)c->walk.bytes; }      // the tables
 
 // What a launch of a kernel with `bytes` of dynamic LDS needs first.  table_at counts on dynamic LDS starting at byte 0: a
 // kernel that has come to have static LDS as well (the compiler may move private arrays there) is refused; that is asked
@@ -492,10 +530,9 @@ unsigned persistent_grid(const pvq_ctx *c, int64_t items)
 }
 
 template <int D, int W, int DX, int DA, int DB, int OUT, bool STAGE>
-hipError_t launch_decode_staged(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
+hipError_t launch_decode_staged(const pvq_ctx *c, const pvq_decode_args &a, size_t lds, hipStream_t s)
 {
     const int tiles = (int)((a.groups + kWave - 1) / kWave);
-    const size_t lds = lds_bytes(c, STAGE ? (size_t)D * (OUT == PVQ_F32 ? 4 : 2) : 0);
     const hipError_t e = allow_lds<decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>>(lds);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((decode_walk_kernel<D, W, DX, DA, DB, OUT, STAGE>), dim3(persistent_grid(c, a.rows * tiles)), dim3(block_threads(c)), lds, s,
@@ -506,9 +543,12 @@ hipError_t launch_decode_staged(const pvq_ctx *c, const pvq_decode_args &a, hipS
 template <int D, int W, int DX, int DA, int DB, int OUT>
 hipError_t launch_decode_out(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
-    // the staging buffer is used where the unit's 160 KiB still hold 32 waves with it
-    if (lds_bytes(c, (size_t)D * (OUT == PVQ_F32 ? 4 : 2)) * (2048 / block_threads(c)) <= 160 * 1024) return launch_decode_staged<D, W, DX, DA, DB, OUT, true>(c, a, s);
-    return launch_decode_staged<D, W, DX, DA, DB, OUT, false>(c, a, s);
+    if constexpr (D == 8 && OUT == PVQ_F32) {
+        // where the unit's 160 KiB still hold 32 waves with 64 groups each
+        const size_t staged = lds_bytes(c) + (size_t)block_threads(c) * D * 4;
+        if (staged * (2048 / block_threads(c)) <= 160 * 1024) return launch_decode_staged<D, W, DX, DA, DB, OUT, true>(c, a, staged, s);
+    }
+    return launch_decode_staged<D, W, DX, DA, DB, OUT, false>(c, a, lds_bytes(c), s);
 }
 
 template <int D, int W, int DX, int DA, int DB>

@@ -262,6 +262,14 @@ def test_products_on_the_walk_at_the_edges_of_tiles(D, K, bits, rows, groups):
     run_case(W, D, K, bits, batches=(1, 4, 5, 9, 16), out_dtypes=("f32",))
 
 
+@pytest.mark.parametrize("D,K", [(8, 16), (8, 127), (16, 5), (16, 33), (16, 127), (32, 9), (32, 60), (32, 105)])
+@pytest.mark.parametrize("rows,groups", [(2, 1), (3, 9), (5, 63), (2, 129)])
+def test_decode_to_every_type_at_the_edges_of_a_wave(D, K, rows, groups):
+    # lanes exchange 16-byte pieces of 1, 2, 4 and 8 per group and store one another's; lanes without a group among them
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=K + groups, rotate=False)
+    run_case(W, D, K, 0, batches=(), out_dtypes=("f32", "f16", "bf16"))
+
+
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
