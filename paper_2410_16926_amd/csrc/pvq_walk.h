@@ -123,18 +123,19 @@ PVQ_HD T table_at(const unsigned char *tables, uint32_t byte)
 }
 typedef uint32_t word4 __attribute__((vector_size(16)));
 
-// entry j of the row of thresholds at byte `at`
-template <int WP>
+// entry j + NEXT of the row of thresholds at byte `at`  (NEXT is part of the instruction: entry j and the one behind it are
+// two offsets from one address)
+template <int WP, uint32_t NEXT = 0>
 PVQ_HD void threshold(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t j, uint32_t *t)
 {
-    if constexpr (WP == 1) t[0] = table_at<uint32_t>(tables, at + 4u * j);
+    if constexpr (WP == 1) t[0] = table_at<uint32_t>(tables, (at + 4u * j) + 4u * NEXT);
     if constexpr (WP == 2 || WP == 3) {
-        const uint64_t v = table_at<uint64_t>(tables, at + 8u * j);
+        const uint64_t v = table_at<uint64_t>(tables, (at + 8u * j) + 8u * NEXT);
         t[0] = (uint32_t)v; t[1] = (uint32_t)(v >> 32);
     }
-    if constexpr (WP == 3) t[2] = table_at<uint32_t>(tables, at + p.part_bytes[1] + 4u * j);
+    if constexpr (WP == 3) t[2] = table_at<uint32_t>(tables, (at + p.part_bytes[1] + 4u * j) + 4u * NEXT);
     if constexpr (WP == 4) {
-        const word4 v = table_at<word4>(tables, at + 16u * j);
+        const word4 v = table_at<word4>(tables, (at + 16u * j) + 16u * NEXT);
         t[0] = v[0]; t[1] = v[1]; t[2] = v[2]; t[3] = v[3];
     }
 }
@@ -142,7 +143,7 @@ PVQ_HD void threshold(const unsigned char *tables, const pvq_walk_params &p, uin
 // The coordinate of row DP (DP + 1 dimensions left), whose thresholds start at byte `at`: its place j in them
 // (pvq_internal.h).  q loses T_j.
 template <int DP, int D, int W, int DX, int DA, int DB>
-PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t more, uint32_t *q)
+PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t more, uint32_t ones, uint32_t *q)
 {
     constexpr int WP = words_of_row(DP, W, DX, DA, DB);
     if constexpr (DP == 1) {
@@ -156,11 +157,15 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
         uint32_t j = table_at<uint8_t>(tables, guesses + (float_bits(float_of<WP>(q)) >> (23 - MB)));
         uint32_t t0[WP], t1[WP], d0[WP], d1[WP];
         threshold<WP>(tables, p, at, j, t0);
-        threshold<WP>(tables, p, at, j + 1, t1);
+        // Entry j + 1 from entry j's address saves two vector instructions a coordinate (groups of 16: 14336 x 4096, 52 bits,
+        // times five vectors 33.6 -> 33.2 us, 8192 x 8192, 48 bits, times two 37.7 -> 36.2), but makes one read of the two, which
+        // comes back later: with four words (groups of 32, 104 bits, to bfloat16) 47.6 us, from two addresses 45.9.
+        constexpr uint32_t kNext = W <= 2 ? 1 : 0;
+        threshold<WP, kNext>(tables, p, at, j + 1 - kNext, t1);
         subtract<WP>(d0, q, t0);
         uint32_t borrow = subtract<WP>(d1, q, t1), unused;
         const bool up = !borrow;
-        j = __builtin_subc(j, 0xFFFFFFFFu, borrow, &unused);       // j + 1 - borrow
+        j = __builtin_subc(j, W <= 2 ? ones : 0xFFFFFFFFu, borrow, &unused);       // j + 1 - borrow
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
 #endif
@@ -172,7 +177,7 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
             if (more >> DP & 1u) {                                 // (the same for all lanes)
                 bool on = up;
                 while (on) {                                       // (ends: q lies below the entry behind the thresholds)
-                    threshold<WP>(tables, p, at, j + 1, t1);
+                    threshold<WP, kNext>(tables, p, at, j + 1 - kNext, t1);
                     on = !subtract<WP>(d1, q, t1);
                     j += on ? 1u : 0u;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -194,13 +199,13 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
 template <int D, int W, int DX, int DA, int DB>
 struct walk_state {
     uint32_t q[W];
-    uint32_t k, at, more;
+    uint32_t k, at, more, ones;
     float n2;
 
     template <int I, typename Emit>
     PVQ_HD void coordinate(const unsigned char *tables, const pvq_walk_params &p, Emit &emit)
     {
-        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, more, q);
+        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, more, ones, q);
         at += row_bytes(p, words_of_row(D - 1 - I, W, DX, DA, DB));
         const uint32_t C = j >> 1;
         const float m = (float)(k - C);
@@ -230,7 +235,9 @@ PVQ_HD float unrank_walk(typename wide<W>::type c, const unsigned char *tables, 
     st.k = (uint32_t)p.K; st.n2 = 0.0f;
     st.at = threshold_base(D, W, DX, DA, DB);
     st.more = p.more;
+    st.ones = ~0u;
 #if defined(__HIP_DEVICE_COMPILE__)
+    asm("" : "+v"(st.ones));                                       // (a constant would be added by itself, after the borrow)
     asm volatile("" : "+s"(st.at), "+s"(st.more));                 // (else a kernel's loop keeps registers per row: 106 scalar ones, seven waves)
 #endif
     st.all(tables, p, emit, std::make_integer_sequence<int, D - 1>{});
