@@ -302,7 +302,7 @@ extern "C" int pvq_ctx_create(pvq_ctx **out, int D, int K, int scale_bits, const
     if (!out) return PVQ_E_INVALID_ARG;
     *out = nullptr;
     // groups of 64 and 128 values (the on-the-fly activation setting) go to the kernels of pvq_wide.hip:
-    // a wave per group, tables of up to 16-word integers streamed from device memory
+    // tables of up to 16-word integers in device memory
     const bool wide = D == 64 || D == 128;
     if (!wide && D != 8 && D != 16 && D != 32) return PVQ_E_UNSUPPORTED;
     if (K < 1 || K > (wide ? 1023 : 127)) return PVQ_E_UNSUPPORTED;
