@@ -110,19 +110,19 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
     ss_out = tree8(tmp);
 
     float g = K / l1, pulses = K;
-    // from here on t is finite and within [-K(1+eps), K(1+eps)]
     float t[D], mag[D];
 #pragma unroll
     for (int i = 0; i < D; i++) t[i] = w[i] * g;
     // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite.  Zeros then, whose index comes out as
-    // that of (0, ..., 0, K): 0.  (Looked at closely only in waves with a norm that is not well inside the normal floats.)
+    // that of (0, ..., 0, K): 0.  (Looked at closely only in waves with a norm that is not an ordinary one.)
     degenerate = false;
-    if (__any(__float_as_uint(l1) - 0x01000000u >= 0x7E000000u)) {
+    if (__any(!ordinary_norm<kMaxK>(l1))) {
         degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
         pulses = degenerate ? 0.0f : K;
 #pragma unroll
         for (int i = 0; i < D; i++) t[i] = degenerate ? 0.0f : t[i];
     }
+    // from here on t is finite and within [-K(1+eps), K(1+eps)], so that the addresses below lie inside the table
     float S[D];
 #pragma unroll
     for (int i = 0; i < D; i++) { mag[i] = rintf(fabsf(t[i])); S[i] = mag[i]; }

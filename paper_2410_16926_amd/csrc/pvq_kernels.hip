@@ -33,6 +33,7 @@ template <> struct wide<2> { using type = uint64_t; };
 template <> struct wide<4> { using type = unsigned __int128; };
 
 constexpr int kMaxLanes = 1024;      // of a workgroup
+constexpr int kMaxK = 127;           // of a context with groups of up to 32 (pulses are int8)
 
 struct encode_launch {
     const uint32_t *tab_u;  // [D][K+2] entries of W words
@@ -115,9 +116,9 @@ __device__ inline void project_group(const float (&w)[D], float K, float &ss_out
 #pragma unroll
     for (int i = 0; i < D; i++) t[i] = w[i] * g;
     // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite  (looked at closely only in waves
-    // with a norm that is not well inside the normal floats)
+    // with a norm that is not an ordinary one)
     degenerate = false;
-    if (__any(__float_as_uint(l1) - 0x04000000u >= 0x78000000u)) {
+    if (__any(!ordinary_norm<kMaxK>(l1))) {
         degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
         pulses = degenerate ? 0.0f : K;
 #pragma unroll

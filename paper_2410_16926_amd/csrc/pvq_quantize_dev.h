@@ -9,6 +9,25 @@
 
 namespace pvq_quantize_dev {
 
+// Whether a group's norm l1 is one that all groups but tiny and huge ones have: finite, not zero, and with K / l1 finite for
+// every K up to MAX_K.  What is not has to be looked at closely, and what is has a direction.  From a power of two 2^(f - 127)
+// on, f the exponent's field, K / l1 <= MAX_K 2^(127 - f), which is finite if MAX_K < 2^(f + 1).  (K / l1 overflows up to
+// l1 = K 2^-128, which is 2^-124 for K = 16: above the smallest normal float.)  Up to 2^127, so that infinities and NaN,
+// whose bits lie above, are not among them.
+__device__ constexpr uint32_t ordinary_norm_from(int max_k)
+{
+    uint32_t f = 1;
+    while (max_k >> (f + 1)) f++;
+    return f << 23;
+}
+template <int MAX_K>
+__device__ inline bool ordinary_norm(float l1)
+{
+    constexpr uint32_t from = ordinary_norm_from(MAX_K), to = 0x7F000000u;
+    static_assert(MAX_K / __builtin_bit_cast(float, from) <= __FLT_MAX__, "K over the smallest ordinary norm is finite");
+    return __float_as_uint(l1) - from < to - from;
+}
+
 // Sum over adjacent pairs, level by level: ((v0+v1)+(v2+v3))+...  (fixed order, float32).
 template <int D>
 __device__ inline float tree_sum(float (&v)[D])

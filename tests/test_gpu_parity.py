@@ -424,6 +424,81 @@ def test_many_pulses_to_move_in_groups_of_8(K, raise_):
         ctx.close()
 
 
+def groups_around_the_overflow(rows, groups, D, K, seed, bf16=False, huge=False):
+    """float32 [rows][groups * D] with groups whose l1 norm lies between 2^-128 and 2^-118, about K 2^-128, below which
+    K / l1 overflows: rows of such groups alone, rows in which one of them stands among ordinary ones, rows of both in equal
+    parts.  Exactly K 2^-128 and the floats beside it, one-hot groups, a negative last value and zeros among them.
+    huge: norms up to the largest float too (whose sums of squares are infinite)."""
+    rng = np.random.default_rng(seed)
+    W = rng.standard_normal((rows, groups, D)) * 0.02
+    pick = rng.random((rows, groups)) < np.array([1.0, 0.0, 0.5])[np.arange(rows) % 3][:, None]
+    pick[1::3] = np.arange(groups) == rng.integers(0, groups, size=len(pick[1::3]))[:, None]
+    at = np.argwhere(pick)
+    for i, (r, g) in enumerate(at):
+        kind = 1 if r % 3 == 1 else i % 7
+        l1 = 2.0 ** rng.uniform(-128, -118)
+        if kind == 0:
+            l1 = K * 2.0 ** -128 * (1 + rng.integers(-2, 3) * 2.0 ** -22)
+        elif kind == 1:
+            l1 = K * 2.0 ** (rng.uniform(-1, 0.5) - 128)
+        elif kind == 2:
+            l1 = 2.0 ** rng.integers(-127, -120)
+        v = np.abs(rng.standard_normal(D)) if kind < 5 else np.zeros(D)
+        if kind == 0:
+            v[:] = 1.0
+        elif kind == 5:
+            v[rng.integers(0, D)] = 1.0
+        elif kind == 6:
+            v[D - 1] = rng.choice([0.0, 1.0])
+        v = v * (l1 / max(v.sum(), 1.0)) * rng.choice([-1.0, 1.0], size=D)
+        if i % 2:
+            v[D - 1] = -abs(v[D - 1])
+        W[r, g] = v
+    if huge:
+        W[2::3, 0] = 1.2 * 2.0 ** rng.uniform(119, 127.5, size=(len(W[2::3]), 1)) / D
+    W = W.reshape(rows, groups * D).astype(np.float32)
+    return si.bf16_bits_to_f32(si.f32_to_bf16_bits(W)) if bf16 else W
+
+
+@pytest.mark.parametrize("D,K", [(8, 15), (8, 16), (8, 1), (8, 127), (16, 33), (32, 127)])
+@pytest.mark.parametrize("bits,amplitude", [(0, "l2"), (2, "l2"), (0, "ls"), (2, "ls")])
+def test_groups_whose_norm_is_about_the_overflow_of_the_gain(D, K, bits, amplitude):
+    # K / l1 is infinite below K 2^-128 and finite from there on: (0, ..., 0, K) below, a point with a direction above
+    if (D, K) == (32, 127):
+        K = min(127, pvq.pvq_max_k(32, 128))
+    for rows, groups, bf16 in ((24, 256, False), (9, 68, True)):
+        W = groups_around_the_overflow(rows, groups, D, K, 17 * D + K + bits, bf16, huge=bits == 0 and amplitude == "l2")
+        ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+        ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+        Wd = gu.to_dev_bf16(si.f32_to_bf16_bits(W)) if bf16 else gu.to_dev_f32(W)
+        enc = oracle.encode(W, D, K, bits, oe, nthreads=8, amplitude=amplitude)
+        p = enc.pulses.reshape(rows, groups, D)
+        none = (p[..., :-1] == 0).all(axis=2) & (p[..., -1] == K)
+        assert 0.1 < none[::3].mean() < 0.9          # both sides of the line
+        gu.assert_encode_equal(pvq.pvq_encode(ctx, Wd, want_pulses=True), enc)
+        ctx.close()
+
+
+@pytest.mark.parametrize("K", [15, 16])
+@pytest.mark.parametrize("bits,amplitude", [(0, "l2"), (2, "l2"), (0, "ls"), (2, "ls")])
+@pytest.mark.parametrize("cols,block", [(2048, 8), (2048, 512), (4096, 1024), (8192, 8192)])
+def test_rotated_groups_whose_norm_is_about_the_overflow_of_the_gain(K, bits, amplitude, cols, block):
+    # the same behind the rotation: rows of such groups (a rotated block of them is one), and for blocks of 8 rows of both kinds
+    rows, groups = 12, cols // 8
+    W = groups_around_the_overflow(rows, groups, 8, K, K + cols + block + bits)
+    if block > 8:
+        rng = np.random.default_rng(block + K)
+        tiny = rng.standard_normal((rows, cols // block, block)) * 2.0 ** rng.uniform(-130, -125, size=(rows, cols // block, 1))
+        W[::2] = tiny.reshape(rows, cols)[::2].astype(np.float32)
+    sg = np.random.default_rng(block).integers(0, 2, size=cols).astype(np.uint8)
+    ctx, oe, oc = gu.make_ctx(8, K, bits, groups)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    packed = pvq.pvq_rotate_encode(ctx, gu.to_dev_f32(W), block, torch.from_numpy(sg).cuda())
+    gu.assert_encode_equal(packed, oracle.encode(oracle.hadamard_rows(W, block, sg), 8, K, bits, oe, nthreads=8, amplitude=amplitude),
+                           check_pulses=False)
+    ctx.close()
+
+
 @pytest.mark.parametrize("rows,cols,block", [(600, 8192, 8192), (1100, 4096, 4096), (2100, 2048, 64), (1030, 8192, 1024)])
 def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
     # more rows than resident workgroups; any byte that is not zero is a sign
