@@ -166,7 +166,7 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
     }
     if (any_degenerate && degenerate && sub == 15) {
         m[CP - 1] = K;
-        y[CP - 1] = w[CP - 1] < 0.0f ? -K : K;
+        y[CP - 1] = K;                       // (positive whatever the value's sign)
     }
 
     // ---- amplitude (Sec. 2.3, or Sec. 3.3 Step 4)

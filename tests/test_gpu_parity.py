@@ -499,6 +499,22 @@ def test_rotated_groups_whose_norm_is_about_the_overflow_of_the_gain(K, bits, am
     ctx.close()
 
 
+@pytest.mark.parametrize("D,K", [(128, 187), (64, 40), (64, 127), (128, 382), (64, 1)])
+@pytest.mark.parametrize("amplitude", ["l2", "ls"])
+def test_long_groups_whose_norm_is_about_the_overflow_of_the_gain(D, K, amplitude):
+    # (0, ..., 0, K) below the line, also where the last value is negative; behind the rotation (indices of up to 12 words) too
+    X = groups_around_the_overflow(42, 24, D, K, D + K)
+    ctx = pvq.pvq_ctx_create(D, K)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    Xd = gu.to_dev_f32(X)
+    packed = pvq.pvq_encode(ctx, Xd, want_pulses=K <= 127)
+    gu.assert_encode_equal(packed, oracle.encode(X, D, K, 0, None, nthreads=8, amplitude=amplitude))
+    if (D, K) == (128, 187):
+        packed = pvq.pvq_rotate_encode(ctx, Xd, 1024)
+        gu.assert_encode_equal(packed, oracle.encode(oracle.hadamard_rows(X, 1024), D, K, 0, None, nthreads=8, amplitude=amplitude))
+    ctx.close()
+
+
 @pytest.mark.parametrize("rows,cols,block", [(600, 8192, 8192), (1100, 4096, 4096), (2100, 2048, 64), (1030, 8192, 1024)])
 def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
     # more rows than resident workgroups; any byte that is not zero is a sign
