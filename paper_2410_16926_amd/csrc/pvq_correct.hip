@@ -32,7 +32,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <atomic>
+#include <mutex>
 
 #include "pvq_internal.h"
 
@@ -540,13 +540,6 @@ hipError_t pvq_launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t 
 }
 
 int64_t pvq_correct_static_max_rows(void) { return kStaticRows; }
-
-// (no launch asks for it any more: the panel workgroups always take the panel before's update of their columns)
-int64_t pvq_correct_front_tiles(int64_t tiles)
-{
-    static std::atomic<int64_t> value{1536};
-    return value.exchange(tiles);
-}
 
 // The same launches with the library's own work buffers.
 hipError_t pvq_launch_correct_static(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw,

@@ -656,8 +656,10 @@ extern "C" int pvq_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t col
 
 extern "C" int pvq_correct_set_front_tiles(int64_t tiles, int64_t *previous)
 {
+    // (kept for callers that set and restore it; no launch depends on it)
+    static std::atomic<int64_t> value{1536};
     if (tiles < 0) return PVQ_E_INVALID_ARG;
-    const int64_t old = pvq_correct_front_tiles(tiles);
+    const int64_t old = value.exchange(tiles);
     if (previous) *previous = old;
     return PVQ_OK;
 }

@@ -145,8 +145,6 @@ hipError_t pvq_launch_correct(const pvq_ctx *ctx, float *W, int64_t rows, int64_
                               int64_t ldu, float *work, hipStream_t s);
 // the same with the library's static work buffer (at most pvq_correct_static_max_rows() rows), on `s` alone
 int64_t pvq_correct_static_max_rows(void);
-// keeps a number and returns the one before (pvq_diagnostics.h)
-int64_t pvq_correct_front_tiles(int64_t tiles);
 hipError_t pvq_launch_correct_static(const pvq_ctx *ctx, float *W, int64_t rows, int64_t cols, int64_t ldw,
                                      const float *U, int64_t ldu, hipStream_t s);
 

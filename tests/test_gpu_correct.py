@@ -78,9 +78,9 @@ def test_wide_updates_beside_the_next_panel(D, K, rows, cols):
 @pytest.mark.parametrize("D,K,rows,cols,amplitude", [(8, 16, 700, 1536, "l2"), (8, 16, 130, 448, "ls"), (16, 33, 300, 640, "l2"),
                                                      (32, 60, 150, 384, "ls"), (8, 5, 65, 320, "l2")])
 def test_narrow_update_inside_the_panel_workgroups(D, K, rows, cols, amplitude):
-    # a launch with many update tiles lets its panel workgroups apply the panel before's update to their own
-    # columns instead of a launch of its own; the threshold is lowered so that these small matrices take that path
-    # in every launch that has update tiles at all (the last two panels of a matrix keep the separate launch)
+    # The panel workgroups apply the panel before's update to their own columns, in every launch behind the first: the path of
+    # all calls, here with other shapes and amplitudes than above.  The setter chooses no path (it keeps a number): what the
+    # test adds is that a call between two settings gives the oracle's weights like any other.
     old = pvq.pvq_correct_set_front_tiles(1)
     try:
         run_correct(D, K, rows, cols, seed=si.BASE_SEED + 580 + rows + cols, amplitude=amplitude)
