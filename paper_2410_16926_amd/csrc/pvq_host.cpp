@@ -857,9 +857,15 @@ uint64_t replay_walk(const SizeTable &t, int K, const std::vector<unsigned char>
         plain_unrank(t, D, K, c, want);
         int n2w = 0;
         for (int i = 0; i < D; i++) n2w += want[i] * want[i];
-        const float n2 = pvq_walk::unrank_walk<D, W, DX, DA, DB>((T)c, blob.data(), p, [&](int i, float minus_y) { got[i] = -(int)minus_y; });
-        bool same = n2 == (float)n2w;
-        for (int i = 0; i < D; i++) same = same && got[i] == want[i];
+        auto emit = [&](int i, float minus_y) { got[i] = -(int)minus_y; };
+        auto equal = [&](float n2) {
+            bool same = n2 == (float)n2w;
+            for (int i = 0; i < D; i++) same = same && got[i] == want[i];
+            return same;
+        };
+        // both ways to the second threshold (the kernels differ in which they take)
+        bool same = equal(pvq_walk::unrank_walk<D, W, DX, DA, DB, 0>((T)c, blob.data(), p, emit));
+        same = equal(pvq_walk::unrank_walk<D, W, DX, DA, DB, 1>((T)c, blob.data(), p, emit)) && same;
         bad += !same;
     }
     return bad;

@@ -53,6 +53,23 @@ constexpr int guess_bits(int dp, int D)
     return D == 32 ? (dp == 2 ? 6 : dp <= 5 ? 5 : dp <= 13 ? 4 : 3) : dp == 2 ? 5 : dp <= 10 ? 4 : 3;
 }
 constexpr bool searches(int D, int W, int DX, int DA) { return DA == 0 ? W == 4 || (W == 2 && D <= 16) : W == 4 && DX == DA; }
+// Whether a coordinate reads entry j + 1 from entry j's address (walk_step's NEXT): two vector instructions a coordinate less,
+// a few registers more, since both reads are one.  Decoding, with integers of up to two words, it takes less time or the same.
+// In the products the registers decide how many workgroups a unit holds, and with them the split (us, two addresses / one):
+//  - groups of 8 and 16 without the search behind the guess: as many waves either way, and 0 to 7 % faster (D = 16, K = 33:
+//    28672 x 8192 times five vectors 121 / 114, 14336 x 4096 times one 29.9 / 29.0);
+//  - not with the search: tiles of 16 rows take more than 64 registers then (28672 x 8192 times five vectors, D = 16, K = 45:
+//    141 / 174, K = 58: 148 / 195);
+//  - groups of 32: tiles of 16 rows, which are held to 64 registers (gemv_waves; 8192 x 14336 times five, K = 4: 61 / 49; without
+//    the bound seven waves or five, 54, and 28672 x 8192, K = 14, 105 / 123), and with two words those of four (8192 x 14336
+//    times one, K = 8: 56.0 / 50.7); with one word the kernel for 5 to 8 vectors in tiles of four would lose a wave
+//    (3001 x 11008, K = 4: 20.8 / 27.8);
+//  - with four words one read of both comes back later than two (groups of 32, 104 bits, to bfloat16: 45.9 / 47.6).
+constexpr uint32_t next_from_decode(int W) { return W <= 2 ? 1 : 0; }
+constexpr uint32_t next_from_product(int D, int W, int DX, int DA, int R)
+{
+    return W <= 2 && !searches(D, W, DX, DA) && (D <= 16 || W == 2 || R == 16) ? 1 : 0;
+}
 // entries of guess row DP: every value of the row's integer type lands inside (up to 2^(32 words), where the largest round to)
 constexpr uint32_t guess_entries(int dp, int D, int words) { return ((uint32_t)(32 * words) << guess_bits(dp, D)) + 1u; }
 // The guess of bucket b of row DP lies at byte guess_offset(DP) + b.  Buckets are floats shifted down, of which 1 is the
@@ -141,8 +158,8 @@ PVQ_HD void threshold(const unsigned char *tables, const pvq_walk_params &p, uin
 }
 
 // The coordinate of row DP (DP + 1 dimensions left), whose thresholds start at byte `at`: its place j in them
-// (pvq_internal.h).  q loses T_j.
-template <int DP, int D, int W, int DX, int DA, int DB>
+// (pvq_internal.h).  q loses T_j.  NEXT: 1 if the second threshold is read from the first one's address.
+template <int DP, int D, int W, int DX, int DA, int DB, uint32_t NEXT>
 PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p, uint32_t at, uint32_t more, uint32_t ones, uint32_t *q)
 {
     constexpr int WP = words_of_row(DP, W, DX, DA, DB);
@@ -157,15 +174,11 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
         uint32_t j = table_at<uint8_t>(tables, guesses + (float_bits(float_of<WP>(q)) >> (23 - MB)));
         uint32_t t0[WP], t1[WP], d0[WP], d1[WP];
         threshold<WP>(tables, p, at, j, t0);
-        // Entry j + 1 from entry j's address saves two vector instructions a coordinate (groups of 16: 14336 x 4096, 52 bits,
-        // times five vectors 33.6 -> 33.2 us, 8192 x 8192, 48 bits, times two 37.7 -> 36.2), but makes one read of the two, which
-        // comes back later: with four words (groups of 32, 104 bits, to bfloat16) 47.6 us, from two addresses 45.9.
-        constexpr uint32_t kNext = W <= 2 ? 1 : 0;
-        threshold<WP, kNext>(tables, p, at, j + 1 - kNext, t1);
+        threshold<WP, NEXT>(tables, p, at, j + 1 - NEXT, t1);
         subtract<WP>(d0, q, t0);
         uint32_t borrow = subtract<WP>(d1, q, t1), unused;
         const bool up = !borrow;
-        j = __builtin_subc(j, W <= 2 ? ones : 0xFFFFFFFFu, borrow, &unused);       // j + 1 - borrow
+        j = __builtin_subc(j, NEXT ? ones : 0xFFFFFFFFu, borrow, &unused);       // j + 1 - borrow
 #if defined(__HIP_DEVICE_COMPILE__)
 #pragma unroll
 #endif
@@ -177,7 +190,7 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
             if (more >> DP & 1u) {                                 // (the same for all lanes)
                 bool on = up;
                 while (on) {                                       // (ends: q lies below the entry behind the thresholds)
-                    threshold<WP, kNext>(tables, p, at, j + 1 - kNext, t1);
+                    threshold<WP, NEXT>(tables, p, at, j + 1 - NEXT, t1);
                     on = !subtract<WP>(d1, q, t1);
                     j += on ? 1u : 0u;
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -196,7 +209,7 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
 }
 
 // The state of a walk: the residual, pulses left, sum of squares.
-template <int D, int W, int DX, int DA, int DB>
+template <int D, int W, int DX, int DA, int DB, uint32_t NEXT>
 struct walk_state {
     uint32_t q[W];
     uint32_t k, at, more, ones;
@@ -205,7 +218,7 @@ struct walk_state {
     template <int I, typename Emit>
     PVQ_HD void coordinate(const unsigned char *tables, const pvq_walk_params &p, Emit &emit)
     {
-        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB>(tables, p, at, more, ones, q);
+        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB, NEXT>(tables, p, at, more, ones, q);
         at += row_bytes(p, words_of_row(D - 1 - I, W, DX, DA, DB));
         const uint32_t C = j >> 1;
         const float m = (float)(k - C);
@@ -223,11 +236,11 @@ struct walk_state {
 // The whole point from its index c, negated (the place of a positive coordinate is odd, which becomes a sign bit):
 // emit(i, -y_i) for i = 0 .. D-1 in order, +0 where y_i is 0; returns sum y_i^2.  An index that is no codeword decodes as
 // the last one.
-template <int D, int W, int DX, int DA, int DB, typename Emit>
+template <int D, int W, int DX, int DA, int DB, uint32_t NEXT, typename Emit>
 PVQ_HD float unrank_walk(typename wide<W>::type c, const unsigned char *tables, const pvq_walk_params &p, Emit &&emit)
 {
     static_assert(DX <= D && DA <= DX && DB <= DA, "width schedule");
-    walk_state<D, W, DX, DA, DB> st;
+    walk_state<D, W, DX, DA, DB, NEXT> st;
     uint32_t index[W];
     for (int x = 0; x < W; x++) index[x] = (uint32_t)(c >> (32 * x));
     const bool none = subtract<W>(st.q, p.last_index, index);

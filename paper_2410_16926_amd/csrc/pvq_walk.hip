@@ -251,7 +251,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
         if (row_n >= a.rows) { row_n = a.rows - 1; tile_n = tiles - 1; }   // past the last item: its place again, dropped
         fetch(row_n, tile_n);
         float y[D];
-        const float n2 = unrank_walk<D, W, DX, DA, DB>(c, lds, wl.p, [&](int i, float minus_y) { y[i] = minus_y; });
+        const float n2 = unrank_walk<D, W, DX, DA, DB, next_from_decode(W)>(c, lds, wl.p, [&](int i, float minus_y) { y[i] = minus_y; });
         // direction on the unit sphere times the amplitude (Sec. 2.4): w = amp * y / ||y||_2
         const float gain = norm_gain(-amp, n2);
         // gain * y + 0: the product as it is, and +0 for a zero coordinate
@@ -321,8 +321,12 @@ struct gemv_teams {
     int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves
 };
 
+// Waves of a SIMD that a kernel's registers are to leave room for: eight in tiles of 16 rows of groups of 32 with up to two words,
+// which the schedule of the reads would pass by a few registers (next_from_product); else those of a workgroup of 1024 lanes.
+constexpr int gemv_waves(int D, int W, int R) { return D == 32 && W <= 2 && R == 16 ? 8 : 4; }
+
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
-__global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)
+__global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)
 {
     static_assert(R == 16 ? NV == 4 : R == 4, "tiles");
     using T = typename wide<W>::type;
@@ -389,7 +393,7 @@ __global__ __launch_bounds__(kMaxThreads) void gemv_walk_kernel(walk_launch wl, 
             }
             uint32_t pair[2];
             float even = 0.0f;
-            const float n2 = unrank_walk<D, W, DX, DA, DB>(c, lds, wl.p, [&](int i, float minus_y) {
+            const float n2 = unrank_walk<D, W, DX, DA, DB, next_from_product(D, W, DX, DA, R)>(c, lds, wl.p, [&](int i, float minus_y) {
                 if ((i & 1) == 0) { even = minus_y; return; }
                 pair[(i >> 1) & 1] = __builtin_amdgcn_perm(__float_as_uint(minus_y), __float_as_uint(even), 0x07060302u);
                 if ((i & 3) != 3) return;

@@ -73,3 +73,33 @@ def test_kernels_that_address_lds_from_zero_have_no_static_lds(tmp_path):
     kernels = re.findall(r"\.group_segment_fixed_size:\s*(\d+).*?\.name:\s*(\S*(?:decode|gemv)_walk_kernel\S*)", notes, re.S)
     assert len(kernels) > 50
     assert [name for size, name in kernels if size != "0"] == []
+
+
+def walk_notes(tmp_path):
+    """What the compiler notes about the kernels of pvq_walk.hip."""
+    obj = os.path.join(os.path.dirname(CSRC), "_build", "pvq_walk.hip.o")
+    if not os.path.exists(obj):
+        build.build()
+    llvm = "/opt/rocm/llvm/bin"
+    bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
+    subprocess.run([f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", obj, str(tmp_path / "copy.o")], check=True)
+    subprocess.run([f"{llvm}/clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={bundle}",
+                    f"--output={code}", "--unbundle"], check=True)
+    return subprocess.run([f"{llvm}/llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+
+
+def test_products_on_the_walk_keep_their_waves(tmp_path):
+    """Registers decide how many workgroups of a product a unit holds (64 for eight waves a SIMD, 80 for six): with integers of
+    up to two words the kernels with tiles of 16 rows have eight waves, those of 5 to 8 vectors in groups of up to 16 seven
+    or eight, in groups of 32 with one word six.  (28672 x 8192 times five vectors, D = 16, K = 58: 148 us, with seven waves
+    in tiles of 16 rows 195; 3001 x 11008, D = 32, K = 4: 20.8 us, with five waves 27.8.)"""
+    kernels = re.findall(r"\.name:\s*\S*gemv_walk_kernelI((?:Li\d+E)+)E.*?\.vgpr_count:\s*(\d+)", walk_notes(tmp_path), re.S)
+    found = {tuple(int(v) for v in re.findall(r"Li(\d+)E", name)): int(registers) for name, registers in kernels}
+    most = {}
+    for (D, W, DX, DA, DB, R, NV) in found:
+        if W <= 2 and R == 16:
+            most[D, W, DX, DA, DB, R, NV] = 64
+        elif W <= 2 and NV == 2 and (D <= 16 or W == 1):
+            most[D, W, DX, DA, DB, R, NV] = 72 if D <= 16 else 80
+    assert len(most) > 10
+    assert {k: found[k] for k in most if found[k] > most[k]} == {}
