@@ -17,8 +17,8 @@
 //
 // Decoding (App. B.3): coordinate by coordinate, q = N(D,K) - 1 - index first; a coordinate is the last
 // threshold of its row that is not above q, and q loses it.  Few groups: a wave per group
-// (decode_wide_wave_kernel); many: a lane per group, the rows in LDS (decode_wide_rows_kernel) or, for K > 255, in device
-// memory (decode_wide_kernel).
+// (decode_wide_wave_kernel); many: a lane per group, the rows in LDS (decode_wide_rows_kernel) or, for many pulses (rows_in_lds), in
+// device memory (decode_wide_kernel).
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
@@ -792,8 +792,8 @@ __global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_
     }
 }
 
-// ---- K > 255: a lane per group, the tables in device memory -------------------------------------------------
-// (points no longer fit a byte per magnitude, rows of thresholds take up to 128 KB)
+// ---- many pulses: a lane per group, the tables in device memory ----------------------------------------------
+// (beyond 255 points no longer fit a byte per magnitude, rows of thresholds take up to 128 KB)
 // Bytes of LDS per lane for the decoded point: int16 values, rounded up to an odd number of words.
 __host__ __device__ constexpr int decode_point_bytes16(int D) { return 4 * (D / 2 | 1); }
 
@@ -1151,11 +1151,28 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
     return hipGetLastError();
 }
 
-// Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full; a
-// lane per group takes the one walk of a wave whatever their number, until there are several waves per SIMD.  8192-wide
-// rows, us, wave / lane: D = 128, K = 187: 23 (64 groups), 35 (2048), 67 / 70 (3072), 73 / 70 (3584), 77 / 70 (4096);
-// K = 84: 48 / 66 (3072), 59 / 66, 71 / 67; D = 64, K = 96: 25 / 33 (3072), 37 / 33 (4096).
-constexpr int64_t kFewGroups = 3584;
+// Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full, in
+// steps, by the width of the integers (and for many pulses by the windows a coordinate is looked for in); a lane per group
+// takes the one walk of a wave whatever their number, until there are several waves per SIMD.  us, wave / lane, to bfloat16:
+//                        128 groups   2048        3520        4096        4608        4736
+//   D = 128, K = 28      23 / 57      30 / 58     44 / 58     44 / 58     52 / 58     61 / 58     (integers of 4 words)
+//            K = 84      23 / 65      30 / 66     58 / 66     71 / 66     78 / 66     79 / 66     (8)
+//            K = 187     24 / 70      34 / 72     73 / 72     76 / 72     87 / 72     92 / 72     (12)
+//   D = 64,  K = 40      13 / 30      16 / 30     23 / 30     24 / 30     27 / 30     32 / 30     (4)
+//            K = 96      13 / 33      17 / 34     31 / 34     38 / 34     41 / 34     41 / 34     (8)
+//            K = 127     13 / 39      17 / 39     31 / 39     38 / 39     41 / 39     41 / 39     (8)
+//            K = 220     17 / 47      24 / 48     40 / 48     43 / 48     50 / 47     51 / 48     (12)
+//            K = 255     21 / 48      30 / 48     45 / 48     50 / 48     57 / 48     57 / 48     (12)
+static int64_t few_groups(const pvq_ctx *c)
+{
+    return c->words == 4 || (c->D == 64 && c->K > 112 && c->K <= 230) ? 4608 : 3584;
+}
+
+// Beyond that, whether the rows of the tables go through LDS.  They do while a magnitude fits a byte; but with more than about
+// twice as many pulses as coordinates many places lie outside a window of 256, and then all of them are as well read from device
+// memory.  us, LDS / device memory, 8192 groups: D = 64, K = 96 34 / 44, 127 39 / 45, 140 43 / 46, 160 49 / 46, 200 58 / 47,
+// 255 59 / 48; D = 128, K = 187 71 / 95, 255 90 / 97.
+static bool rows_in_lds(const pvq_ctx *c) { return c->K <= (c->D == 64 ? 150 : 255); }
 
 // Lanes of a workgroup whose rows of the tables go through LDS: the fewest, from 128 on, with which the groups take one place
 // on each of the 256 units, up to 512.  (64 lanes, a wave that loads its rows alone: 8192 groups of 128 in 80 us, with 128
@@ -1170,13 +1187,29 @@ static int rows_lanes(int64_t groups)
 template <int CP, int W, int LANES>
 static hipError_t launch_rows(const decode_wide_params &p, size_t lds, hipStream_t s)
 {
-    if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(decode_wide_rows_kernel<CP, W, LANES>),
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
+    if constexpr (CP == 2 || W <= 8) {              // (as wide as the integers of rows_in_lds are)
+        if (lds > 64 * 1024) {
+            const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(decode_wide_rows_kernel<CP, W, LANES>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES), lds, s, p);
+        return hipSuccess;
+    } else {
+        return hipErrorInvalidValue;
     }
-    hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES), lds, s, p);
-    return hipSuccess;
+}
+
+template <int CP, int W>
+static hipError_t launch_lanes(const decode_wide_params &p, hipStream_t s)
+{
+    if constexpr (CP == 2 ? W == 16 : W >= 8) {
+        const size_t lds = (size_t)64 * decode_point_bytes16(64 * CP);
+        hipLaunchKernelGGL((decode_wide_kernel<CP, W>), dim3((unsigned)((p.total_groups + 63) / 64)), dim3(64), lds, s, p);
+        return hipSuccess;
+    } else {
+        return hipErrorInvalidValue;
+    }
 }
 
 #define PVQ_WIDE_DEC_W(CP)                                  \
@@ -1200,17 +1233,18 @@ hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
     for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
     if ((p.total_groups + 63) / 64 > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int64_t total = p.total_groups;
-    if (total <= kFewGroups) {
+    if (total <= few_groups(c)) {
         const size_t lds = (size_t)kWavesFew * 4 * 1024 * (c->words / 4 + 1) + 16;
 #define PVQ_WIDE_DEC(CP, W) \
     hipLaunchKernelGGL((decode_wide_wave_kernel<CP, W>), dim3((unsigned)((total + kWavesFew - 1) / kWavesFew)), dim3(64 * kWavesFew), lds, s, p)
         PVQ_WIDE_DEC_DW
 #undef PVQ_WIDE_DEC
-    } else if (c->K > 255) {
-        const size_t lds = (size_t)64 * decode_point_bytes16(c->D);
-#define PVQ_WIDE_DEC(CP, W) hipLaunchKernelGGL((decode_wide_kernel<CP, W>), dim3((unsigned)((total + 63) / 64)), dim3(64), lds, s, p)
+    } else if (!rows_in_lds(c)) {
+        hipError_t e = hipSuccess;
+#define PVQ_WIDE_DEC(CP, W) e = launch_lanes<CP, W>(p, s)
         PVQ_WIDE_DEC_DW
 #undef PVQ_WIDE_DEC
+        if (e != hipSuccess) return e;
     } else {
         const int lanes = rows_lanes(total);
         const size_t lds = decode_rows_lds(c->words, lanes);

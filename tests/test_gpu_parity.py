@@ -273,16 +273,27 @@ def test_decode_to_every_type_at_the_edges_of_a_wave(D, K, rows, groups):
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
-    # a wave per group up to 3584 groups, a lane per group beyond (5121: a last wave with one group); rows of
+    # a wave per group up to 3584 or 4608 groups, a lane per group beyond (5121: a last wave with one group); rows of
     # thresholds just shorter and just longer than a window, points kept as bytes and as int16
     X = si.adversarial_groups(1 << 13, D, seed=K)[:rows * groups].reshape(rows, groups * D)
     run_long_groups(np.ascontiguousarray(X), D, K)
 
 
+@pytest.mark.parametrize("D,K,rows,groups", [(64, 40, 2304, 2), (64, 40, 419, 11), (128, 28, 4609, 1), (64, 96, 512, 7), (64, 96, 717, 5), (64, 127, 144, 32),
+                                             (64, 127, 419, 11), (64, 150, 4609, 1), (64, 151, 4609, 1), (64, 196, 23, 201), (64, 230, 4608, 1), (64, 231, 717, 5)])
+def test_long_groups_at_the_lines_between_the_decoders(D, K, rows, groups):
+    # the last number of groups that a wave each decodes and the first that lanes do, by the integers' width and by the pulses;
+    # the last pulses whose rows go through LDS and the first that are read from device memory, with integers of 8 and 12 words
+    X = si.activation_matrix(rows, D * groups, seed=D + K + rows, rotate=False, bf16=False)
+    odd = si.adversarial_groups(1 << 10, D, seed=K)
+    X.reshape(rows * groups, D)[3::29] = odd[np.arange(rows * groups)[3::29] % len(odd)]
+    run_long_groups(X, D, K)
+
+
 @pytest.mark.parametrize("D,K,rows,groups", [(64, 40, 3001, 22), (128, 84, 1029, 33), (128, 187, 523, 64), (64, 255, 419, 9), (128, 255, 131, 29)])
 def test_long_groups_with_the_rows_of_the_tables_in_lds(D, K, rows, groups):
-    # workgroups of 128, 256 and 512 lanes with a ragged last one; integers of 4 to 16 words; groups of one workgroup whose
-    # pulses run out early, late and not before the end side by side (places below the window), zeros, rows that are no codewords
+    # workgroups of 128, 256 and 512 lanes with a ragged last one; integers of 4 to 16 words (D = 64, K = 255: the same with the
+    # rows read from device memory); groups of one workgroup whose pulses run out early, late and not before the end side by side (places below the window), zeros, rows that are no codewords
     X = si.activation_matrix(rows, D * groups, seed=D + K, rotate=False, bf16=False)
     odd = si.adversarial_groups(1 << 12, D, seed=K)
     X.reshape(rows * groups, D)[5::41] = odd[np.arange(rows * groups)[5::41] % len(odd)]
