@@ -40,6 +40,7 @@ struct encode_launch {
     const float *edges;     // 2^scale_bits (last = +inf)
     int K, index_bits, scale_bits;
     int team;               // lanes that take a row: 64, 128 or 256
+    int working;            // teams of a workgroup that take rows; the others help with the table only
 };
 
 // LDS, from byte 0: thresholds [2K+2][D-1] of W words, the edges' tree, each wave's words of an index tile, and per team
@@ -213,8 +214,8 @@ __global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(en
     const TIn *source = reinterpret_cast<const TIn *>(a.W);
     // (a lane past the row's end takes the last group again, and writes nothing)
     auto group_at = [&](int64_t row, int t) { return source + row * a.ldw + (int64_t)min(t * kWave + lane, G - 1) * D; };
-    const int64_t step = (int64_t)gridDim.x * teams;
-    int64_t row = (int64_t)blockIdx.x * teams + team;
+    const int64_t step = (int64_t)gridDim.x * f.working;
+    int64_t row = team < f.working ? (int64_t)blockIdx.x * f.working + team : (int64_t)1 << 40;      // (no row has that number)
 
     // groups of 32 are loaded where they are used: there are no registers for a second one (16-bit weights, 96-bit indices,
     // 8192 x 8192: 105 us with one, 88)
@@ -222,12 +223,18 @@ __global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(en
     raw_group<D, TIn> next;
     if (kAhead && first < tiles) next.load(group_at(min(row, a.rows - 1), first));
 
-    // thresholds from the size table, whose rows are shifted by one entry so that U(-1) is stored
+    // thresholds from the size table, whose rows are shifted by one entry so that U(-1) is stored; neighbouring lanes read
+    // neighbouring entries of a row, several reads on their way at a time
     const T *tab_u = reinterpret_cast<const T *>(f.tab_u);
-    for (int e = tid; e < (2 * f.K + 2) * (D - 1); e += lanes) {
-        const int j = e / (D - 1), i = e % (D - 1);
-        const T *u = tab_u + (D - 1 - i) * (f.K + 2) + (j >> 1);           // u[0] = U(D-1-i, C-1)
-        reinterpret_cast<T *>(smem)[e] = u[0] + ((j & 1) ? u[1] : u[0]);
+    const uint32_t per = (uint32_t)f.K + 1;
+#pragma unroll 4
+    for (uint32_t e = (uint32_t)tid; e < per * (D - 1); e += (uint32_t)lanes) {
+        const uint32_t i = e / per, C = e % per;
+        const T *u = tab_u + (D - 1 - i) * (per + 1) + C;                  // u[0] = U(D-1-i, C-1)
+        const T u0 = u[0], u1 = u[1];
+        T *t = reinterpret_cast<T *>(smem) + 2 * C * (D - 1) + i;
+        t[0] = u0 + u0;
+        t[D - 1] = u0 + u1;
     }
     if (sb > 0) fill_edge_tree(tree, f.edges, sb, tid, lanes);
     for (int i = tid; i < (int)(lanes / kWave * l.stage_words); i += lanes) reinterpret_cast<uint32_t *>(smem + l.stage)[i] = 0;
@@ -239,7 +246,7 @@ __global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(en
     const uint32_t sh = (uint32_t)(lane * b) & 31;
     uint32_t *const at = stage + ((uint32_t)(lane * b) >> 5);
     uint32_t turn = 0;
-    for (int64_t base = (int64_t)blockIdx.x * teams; base < a.rows; base += step, row += step) {
+    for (int64_t base = (int64_t)blockIdx.x * f.working; base < a.rows; base += step, row += step) {
         const bool live = row < a.rows;          // (a team without a row waits at the barrier)
         for (int t = first; live && t < tiles; t += waves) {
             const int g = t * kWave + lane;
@@ -354,8 +361,10 @@ hipError_t launch_encode_kernel(const pvq_ctx *c, const pvq_encode_args &a, hipS
         const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    const int64_t teams = lanes / f.team;
-    const unsigned grid = (unsigned)std::min<int64_t>((a.rows + teams - 1) / teams, 256 * (waves / (lanes / kWave)));
+    // Neighbouring rows go to the teams of a workgroup (28672 x 512, D = 16, K = 5: 35 us, rows a grid apart 38), but few rows
+    // go to as many units as there are (256 x 4096, D = 32, K = 105: 11.4 us, to the teams of as few as hold them 15.5).
+    f.working = (int)std::min<int64_t>(lanes / f.team, (a.rows + 255) / 256);
+    const unsigned grid = (unsigned)std::min<int64_t>((a.rows + f.working - 1) / f.working, 256 * (waves / (lanes / kWave)));
     hipLaunchKernelGGL(kernel, dim3(grid), dim3(lanes), lds, s, f, a);
     return hipGetLastError();
 }

@@ -418,6 +418,17 @@ def test_generic_encoder_teams_and_index_widths(D, budget, bits, rows, groups, a
     ctx.close()
 
 
+@pytest.mark.parametrize("D,K,bits,rows,groups", [(32, 105, 0, 1, 1), (32, 105, 4, 255, 3), (32, 105, 4, 257, 65), (32, 80, 0, 513, 128), (16, 127, 8, 300, 66),
+                                                  (8, 127, 2, 256, 64), (8, 127, 0, 769, 9), (8, 5, 1, 64, 257)])
+def test_generic_encoder_spreads_few_rows(D, K, bits, rows, groups):
+    # up to 256 rows one of a workgroup's teams takes rows, then two, and so on up to all of them
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=si.BASE_SEED + 770 + rows, rotate=False)
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W), want_pulses=True)
+    gu.assert_encode_equal(packed, oracle.encode(W, D, K, bits, oe, nthreads=8))
+    ctx.close()
+
+
 @pytest.mark.parametrize("K,raise_", [(16, True), (16, False), (15, True), (15, False)])
 def test_many_pulses_to_move_in_groups_of_8(K, raise_):
     # projections whose fractions lie on one side, so that three or more pulses have to move, ties among them (a power of two
