@@ -793,21 +793,25 @@ __global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_
 }
 
 // ---- many pulses: a lane per group, the tables in device memory ----------------------------------------------
-// (beyond 255 points no longer fit a byte per magnitude, rows of thresholds take up to 128 KB)
-// Bytes of LDS per lane for the decoded point: int16 values, rounded up to an odd number of words.
-__host__ __device__ constexpr int decode_point_bytes16(int D) { return 4 * (D / 2 | 1); }
+// (rows of thresholds take up to 128 KB)
+// Bytes of LDS per lane for the decoded point, rounded up to an odd number of words, so that the lanes' rows spread over the
+// banks.  BYTES (K <= 255): a byte per magnitude and a bit per sign; else int16 values, with which half as many waves fit a
+// unit (393216 groups of 64, K = 180: 99 us with bytes, 136).
+template <bool BYTES>
+__host__ __device__ constexpr int decode_point_bytes(int D) { return 4 * ((BYTES ? D / 4 + D / 32 : D / 2) | 1); }
 
 // The walk of one lane.  A coordinate takes three dependent trips to the tables, of which the L1 and L2 hold the few lines
 // of a row that are in use: the guess of q's bucket, the four keys behind it, and the threshold found.  Equal keys
 // (about one comparison in a million, and the all-zero groups) show as a borrow of the subtraction, after which the
 // threshold before is taken.  Bound by its chain of about 140 instructions a coordinate and three trips.
-template <int CP, int W>
+template <int CP, int W, bool BYTES>
 struct lane_walk : lane_q<W> {
     using lane_q<W>::q;
     static constexpr int D = 64 * CP;
     const decode_wide_params &p;
-    int16_t *mine;
+    unsigned char *mine;
     int k, n2, i;
+    uint32_t sign_byte;
 
     // one coordinate; every q of the wave lies below 2^(32 WP)
     template <int WP>
@@ -821,7 +825,13 @@ struct lane_walk : lane_q<W> {
         const int C = (int)(j >> 1), m = k - C;
         k = C;
         n2 += __mul24(m, m);
-        mine[i] = (int16_t)(j & 1u ? m : -m);
+        if constexpr (BYTES) {
+            mine[i] = (unsigned char)m;
+            sign_byte = ((i & 7) ? sign_byte : 0u) | ((~j & 1u) << (i & 7));
+            if ((i & 7) == 7) mine[D + (i >> 3)] = (unsigned char)sign_byte;
+        } else {
+            reinterpret_cast<int16_t *>(mine)[i] = (int16_t)(j & 1u ? m : -m);
+        }
         i++;
     }
 
@@ -834,12 +844,12 @@ struct lane_walk : lane_q<W> {
     }
 };
 
-// A wave is a workgroup, with decode_point_bytes16 of LDS per lane.
-template <int CP, int W>
+// A wave is a workgroup, with decode_point_bytes of LDS per lane.
+template <int CP, int W, bool BYTES>
 __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
-    constexpr int D = 64 * CP, LB = decode_point_bytes16(D);
+    constexpr int D = 64 * CP, LB = decode_point_bytes<BYTES>(D);
     const int lane = threadIdx.x;
     const int64_t g0 = (int64_t)blockIdx.x * 64;
     const int count = (int)std::min<int64_t>(64, p.total_groups - g0);
@@ -849,7 +859,7 @@ __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
     const uint32_t ahead = (uint32_t)out_g + (uint32_t)std::min(lane, count - 1);
     const int64_t mine = g0 + std::min(lane, count - 1);
     const int64_t row = out_row + ahead / (uint32_t)p.groups, g = ahead % (uint32_t)p.groups;
-    lane_walk<CP, W> walk{{}, p, reinterpret_cast<int16_t *>(lds_raw + (size_t)lane * LB), p.K, 0, 0};
+    lane_walk<CP, W, BYTES> walk{{}, p, lds_raw + (size_t)lane * LB, p.K, 0, 0, 0u};
     // q = N(D,K) - 1 - index; an index that is no codeword decodes to zeros
     uint32_t br = 0;
 #pragma unroll
@@ -869,7 +879,11 @@ __global__ __launch_bounds__(64) void decode_wide_kernel(decode_wide_params p)
         const float gs = __uint_as_float((uint32_t)__builtin_amdgcn_readlane((int)__float_as_uint(gain), s));
         float v[CP];
 #pragma unroll
-        for (int j = 0; j < CP; j++) v[j] = gs * (float)reinterpret_cast<const int16_t *>(pt)[CP * lane + j];
+        for (int j = 0; j < CP; j++) {
+            const int at_j = CP * lane + j;
+            if constexpr (BYTES) v[j] = gs * (float)((pt[D + (at_j >> 3)] >> (at_j & 7) & 1) ? -(int)pt[at_j] : (int)pt[at_j]);
+            else v[j] = gs * (float)reinterpret_cast<const int16_t *>(pt)[at_j];
+        }
         store_values<CP>(p, at, v);
         pt += LB;
         at += D;
@@ -1165,6 +1179,7 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
 //            K = 255     21 / 48      30 / 48     45 / 48     50 / 48     57 / 48     57 / 48     (12)
 static int64_t few_groups(const pvq_ctx *c)
 {
+    if (c->D == 64 && c->words == 8 && c->K > 135) return 5120;
     return c->words == 4 || (c->D == 64 && c->K > 112 && c->K <= 230) ? 4608 : 3584;
 }
 
@@ -1172,7 +1187,11 @@ static int64_t few_groups(const pvq_ctx *c)
 // twice as many pulses as coordinates many places lie outside a window of 256, and then all of them are as well read from device
 // memory.  us, LDS / device memory, 8192 groups: D = 64, K = 96 34 / 44, 127 39 / 45, 140 43 / 46, 160 49 / 46, 200 58 / 47,
 // 255 59 / 48; D = 128, K = 187 71 / 95, 255 90 / 97.
-static bool rows_in_lds(const pvq_ctx *c) { return c->K <= (c->D == 64 ? 150 : 255); }
+static bool rows_in_lds(const pvq_ctx *c, int64_t groups)
+{
+    if (c->D == 128) return c->K <= 255;
+    return c->K <= 112 || (c->K <= 150 && groups <= 256 * 1024);
+}
 
 // Lanes of a workgroup whose rows of the tables go through LDS: the fewest, from 128 on, with which the groups take one place
 // on each of the 256 units, up to 512.  (64 lanes, a wave that loads its rows alone: 8192 groups of 128 in 80 us, with 128
@@ -1200,12 +1219,22 @@ static hipError_t launch_rows(const decode_wide_params &p, size_t lds, hipStream
     }
 }
 
+// Groups of 64 that the machine's LDS holds at once as int16 values, 18 waves a unit.  Up to there those take less time to keep
+// (8192 groups, K = 180: 46 us, as bytes 48); beyond, waves wait for a place (393216: 136, as bytes 93).
+constexpr int64_t kGroupsAtOnce16 = 256 * 64 * (int64_t)(160 * 1024 / ((64 * decode_point_bytes<false>(64) + 1279) / 1280 * 1280));
+
 template <int CP, int W>
 static hipError_t launch_lanes(const decode_wide_params &p, hipStream_t s)
 {
+    const dim3 grid((unsigned)((p.total_groups + 63) / 64)), blk(64);
+    if constexpr (CP == 1 && (W == 8 || W == 12)) {
+        if (p.K <= 255 && p.total_groups > kGroupsAtOnce16) {
+            hipLaunchKernelGGL((decode_wide_kernel<CP, W, true>), grid, blk, (size_t)64 * decode_point_bytes<true>(64 * CP), s, p);
+            return hipSuccess;
+        }
+    }
     if constexpr (CP == 2 ? W == 16 : W >= 8) {
-        const size_t lds = (size_t)64 * decode_point_bytes16(64 * CP);
-        hipLaunchKernelGGL((decode_wide_kernel<CP, W>), dim3((unsigned)((p.total_groups + 63) / 64)), dim3(64), lds, s, p);
+        hipLaunchKernelGGL((decode_wide_kernel<CP, W, false>), grid, blk, (size_t)64 * decode_point_bytes<false>(64 * CP), s, p);
         return hipSuccess;
     } else {
         return hipErrorInvalidValue;
@@ -1239,7 +1268,7 @@ hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
     hipLaunchKernelGGL((decode_wide_wave_kernel<CP, W>), dim3((unsigned)((total + kWavesFew - 1) / kWavesFew)), dim3(64 * kWavesFew), lds, s, p)
         PVQ_WIDE_DEC_DW
 #undef PVQ_WIDE_DEC
-    } else if (!rows_in_lds(c)) {
+    } else if (!rows_in_lds(c, total)) {
         hipError_t e = hipSuccess;
 #define PVQ_WIDE_DEC(CP, W) e = launch_lanes<CP, W>(p, s)
         PVQ_WIDE_DEC_DW

@@ -273,14 +273,15 @@ def test_decode_to_every_type_at_the_edges_of_a_wave(D, K, rows, groups):
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
-    # a wave per group up to 3584 or 4608 groups, a lane per group beyond (5121: a last wave with one group); rows of
+    # a wave per group up to 3584, 4608 or 5120 groups, a lane per group beyond (5121: a last wave with one group); rows of
     # thresholds just shorter and just longer than a window, points kept as bytes and as int16
     X = si.adversarial_groups(1 << 13, D, seed=K)[:rows * groups].reshape(rows, groups * D)
     run_long_groups(np.ascontiguousarray(X), D, K)
 
 
 @pytest.mark.parametrize("D,K,rows,groups", [(64, 40, 2304, 2), (64, 40, 419, 11), (128, 28, 4609, 1), (64, 96, 512, 7), (64, 96, 717, 5), (64, 127, 144, 32),
-                                             (64, 127, 419, 11), (64, 150, 4609, 1), (64, 151, 4609, 1), (64, 196, 23, 201), (64, 230, 4608, 1), (64, 231, 717, 5)])
+                                             (64, 127, 419, 11), (64, 150, 4609, 1), (64, 151, 4609, 1), (64, 150, 5121, 1), (64, 151, 5121, 1), (64, 151, 640, 8),
+                                             (64, 196, 23, 201), (64, 230, 4608, 1), (64, 231, 717, 5)])
 def test_long_groups_at_the_lines_between_the_decoders(D, K, rows, groups):
     # the last number of groups that a wave each decodes and the first that lanes do, by the integers' width and by the pulses;
     # the last pulses whose rows go through LDS and the first that are read from device memory, with integers of 8 and 12 words
@@ -288,6 +289,24 @@ def test_long_groups_at_the_lines_between_the_decoders(D, K, rows, groups):
     odd = si.adversarial_groups(1 << 10, D, seed=K)
     X.reshape(rows * groups, D)[3::29] = odd[np.arange(rows * groups)[3::29] % len(odd)]
     run_long_groups(X, D, K)
+
+
+@pytest.mark.parametrize("K,times", [(127, 61), (127, 62), (150, 69), (151, 68), (160, 69), (196, 68), (255, 69), (256, 69)])
+def test_long_groups_at_the_lines_of_large_batches(K, times):
+    # 613 x 7 groups of 64, repeated: up to 262144 and beyond rows in LDS or not, up to 294912 and beyond points as int16 values or
+    # as bytes (with K = 256 int16 always).  The block by itself, decoded by a wave or a lane per group, equals the oracle's.
+    rows, groups, D = 613, 7, 64
+    X = si.activation_matrix(rows, D * groups, seed=K, rotate=False, bf16=False)
+    odd = si.adversarial_groups(1 << 10, D, seed=K)
+    X.reshape(rows * groups, D)[3::29] = odd[np.arange(rows * groups)[3::29] % len(odd)]
+    run_long_groups(X, D, K)
+    ctx = pvq.pvq_ctx_create(D, K)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(X))
+    packed.index[rows // 2] = -1                     # no codewords: zeros
+    block = pvq.pvq_decode(ctx, packed, torch.float32)
+    many = pvq.Packed(rows * times, packed.cols, packed.index.repeat(times, 1), packed.scale.repeat(times, 1), None)
+    assert torch.equal(pvq.pvq_decode(ctx, many, torch.float32), block.repeat(times, 1))
+    ctx.close()
 
 
 @pytest.mark.parametrize("D,K,rows,groups", [(64, 40, 3001, 22), (128, 84, 1029, 33), (128, 187, 523, 64), (64, 255, 419, 9), (128, 255, 131, 29)])
