@@ -495,7 +495,7 @@ def main():
             t_ms = sorted(ms)[1]
             flop = float(cr) * cc * cc          # one multiply-add per element and earlier column: 2 x rows x cols^2 / 2
             ex[f"correct_{cr}x{cc}"] = {"ms": round(t_ms, 3), "TFLOPs": round(flop / t_ms / 1e9, 2),
-                                        "frac_of_fp32_alu_peak": round(flop / t_ms / 1e9 / 78.6, 3),
+                                        "frac_of_fp32_matrix_peak": round(flop / t_ms / 1e9 / 157.3, 3),
                                         "gpu_rows_per_s": round(cr / t_ms * 1e3, 1)}
             if cr == 8192:
                 w8, u8 = Wc0[:8].cpu().numpy(), Uc.cpu().numpy()
