@@ -21,14 +21,15 @@
 // panel p's, which is why there are two work buffers used in turn.  The panel workgroups come first in the grid
 // and raise their waves' priority, so they are placed before the flood of update tiles and run beside it: the
 // chain of panels (each needs the one before) stays off the critical path as long as a launch has enough update
-// tiles to outlast it; with few rows the chain is what remains.  Both roles need the same LDS (37 KB), four
-// workgroups per compute unit.
+// tiles to outlast it; with few rows the chain is what remains.  A workgroup has the LDS of the role that needs more: 36.9 KB
+// in groups of 8 (the update's), 39.9 in groups of 16 (the panel's), four workgroups to a compute unit; 53.2 in groups of
+// 32, three.
 // Both roles' 128 multiply-adds per element run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
 // element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
 // tied, subnormal and non-finite operands).
 // Before, with the update on the vector ALU (64 TFLOP/s) and 64 rows of a panel a lane each on four waves that took its
 // groups in turn (37 to 46 us a panel and 10 to 15 for a launch in front of it with its update): 8192 x 8192 9.5 ms, now
-// 6.8; 1024 x 4096 1.6 ms, now 0.92.
+// 6.7; 1024 x 4096 1.6 ms, now 0.92; 1024 x 8192 3.3, now 2.07; 28672 x 8192 29.5, now 21.2.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

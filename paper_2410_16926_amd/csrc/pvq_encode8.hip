@@ -10,17 +10,19 @@
 //     |sum - K| largest deviations are all positive, an adjusted coordinate drops below -1/2);
 //   * the index (App. B.2) is a sum of seven table entries, one per coordinate, from a table of per-coordinate offsets
 //     indexed by (coordinate, pulses left, signed value), whose addresses come out of one multiply-add each
-//     (index_address);
+//     (encode_group8);
 //   * four neighbouring lanes assemble their 24-bit indices into three dwords with DPP moves and write
 //     them straight to global memory; amplitude codes are OR-reduced across lanes the same way;
 //   * the row normaliser's pairwise sum is a wave butterfly followed by a small tree over wave sums
 //     (adding +0.0 for absent groups is exact, so padding a row to a power of two does not change
 //     the pair-level sum);
 //   * an amplitude code takes one 16-byte read for two of its bits (pvq_quantize_dev::count_edges).
-// Of the vector instructions float32 additions and multiplications issue in 2.4 cycles a wave, the others in 4 (v_rcp and
-// v_permlane*_swap 8): where there is a choice the forms are of the first kind.  28672 x 8192 bf16 weights, 2-bit codes: 248
-// vector instructions a group, 185 us; with integer addresses, a multiplication by the number of pulses for each, marks of
-// all rounds as masks and a bisection for the code 284 and 211.  14336 x 4096, 8-bit codes: 57 us, before 81.
+// Of the vector instructions additions (float32, 32-bit integers), multiplications, float32 multiply-adds and exclusive ors
+// issue in 2.6 cycles a wave (8 waves a SIMD), comparisons, shifts, minima and maxima, conversions, byte permutations and
+// lane moves in 4.3 to 4.8, v_rcp in 8.9: where there is a choice the forms are of the first kind.  28672 x 8192 bf16
+// weights, 2-bit codes: 242 vector instructions a group, 187 us (launches in a row; 188 to 196 in the benchmark's step); with
+// integer addresses, a multiplication by the number of pulses for each, marks of all rounds as masks and a bisection for
+// the code 284 and 211.  14336 x 4096, 8-bit codes: 57 us, before 81.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -329,10 +331,10 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             raw.get(v);
             // one exchange buffer (a barrier in front of every exchange, which also keeps a chunk's writes
             // behind the reads of the chunk before): two workgroups of 1024 lanes then fit a unit's LDS
-            // (which cross-lane stages go through the LDS permute unit: all of them for blocks of up to 512 values,
-            // where the encoder's arithmetic is what the kernel waits for and that unit is idle; only the one over
-            // 4 lanes for 1024 and 2048; none from 4096 on, where the exchanges through LDS need it: measured)
-            constexpr int kPermuted = LOG2N <= 9 ? 4 + 8 + 16 + 32 : LOG2N <= 11 ? 4 : 0;
+            // (the cross-lane stages from 4 lanes on go through the LDS permute unit for blocks of up to 512 values, where the
+            // encoder's arithmetic is what the kernel waits for and that unit is idle; none for larger blocks, whose
+            // exchanges through LDS need it)
+            constexpr int kPermuted = LOG2N <= 9 ? 4 + 8 + 16 + 32 : 0;
             int stages = log2n;
             if constexpr (LOG2N <= 9) asm volatile("" : "+s"(stages));   // (else the comparisons below stay in scalar registers over the loop)
             hadamard_stages<LOG2N, false, true, kPermuted>(v, tid, stages, hbuf, L);
@@ -363,9 +365,9 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
     }
 }
 
-// Blocks of 8192 values need workgroups of 1024 lanes; two of them share a unit only within 64 registers a
-// lane (the body needs 68: a few values go to scratch), which measured 0.60 against 0.73 ms on 28672 x 8192.
-// The smaller workgroups of the other block sizes keep all their registers.
+// Registers for eight waves a SIMD (64 a lane): with them two workgroups of 1024 lanes, which blocks of 8192 values need, share
+// a unit.  28672 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 264 / 306 / 317 / 388 us (pvq_hadamard to
+// float32 and pvq_encode: 494 / 503 / 515 / 495).
 template <typename TIn, bool CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)

@@ -633,7 +633,7 @@ static int check_correct_args(const pvq_ctx *c, const float *W, int64_t rows, in
     *nothing_to_do = false;
     int rc = check_shape(c, rows, cols);
     if (rc) return rc;
-    // (column tiles of 128 are the second grid dimension of the update kernel: at most 65535 of them)
+    // (a limit of the entry point: at most 2^15 panels of 128 columns, a launch each)
     if (c->wide || (c->D != 8 && c->D != 16 && c->D != 32) || cols % 64 || cols > (int64_t)1 << 22) return PVQ_E_UNSUPPORTED;
     if (rows == 0 || cols == 0) { *nothing_to_do = true; return PVQ_OK; }
     if (!W || !U || ldw < cols || ldu < cols) return PVQ_E_INVALID_ARG;
@@ -699,11 +699,13 @@ static int fill_decode_args(const pvq_ctx *c, pvq_decode_args &a, const uint32_t
 
 // The table decoder for groups of 8 copies 155 KB of tables into every unit's LDS before its first group; the
 // coordinate-by-coordinate decoder starts with 7 KB.  Launches in a row, K = 16, 2-bit codes, table / walk, us:
-//                512 x 512    1024 x 8192   2048 x 8192   3072 x 8192   4096 x 8192   28672 x 8192
-//   to bf16      25.2 /  3.7   18.5 / 10.6   20.1 / 16.2   20.4 / 20.2   20.8 / 24.7   125 / 151
-//   to float32   25.3 /  3.7   21.4 / 11.3   23.1 / 16.2   26.3 / 21.8   30.0 / 27.6   302 / 261
+//                512 x 512    1024 x 8192   2048 x 8192   3072 x 8192   4096 x 8192   8192 x 8192   28672 x 8192
+//   to bf16      23.8 /  3.2   19.7 / 10.2   20.9 / 14.9   20.7 / 18.7   21.3 / 22.7   34.0 / 38.9   126 / 143
+//   to float16   24.2 /  3.2   21.3 / 10.7   22.6 / 16.3   22.6 / 20.1   23.3 / 24.6   38.0 / 41.8   131 / 149
+//   to float32   26.1 /  3.3   21.9 / 11.3   22.2 / 16.9   23.5 / 22.5   29.2 / 28.4   62.9 / 64.7   247 / 263
 // The line (1.5 M groups, which a test states) was drawn with an earlier walk, from 1024 x 8192 and 2048 x 8192: by these
-// times it would lie at 3.1 M groups to 16 bits, and the walk would have every matrix to float32.
+// times it would lie at 4 M groups, whatever the type.  (K = 13 would be the walk's up to the largest matrix: 28672 x 8192 to
+// bf16 184 / 139, to float32 281 / 259.)
 static std::atomic<int64_t> g_table_decoder_min_groups{1572864};
 
 static bool table_decoder_pays(const pvq_ctx *c, const pvq_decode_args &a)

@@ -11,11 +11,11 @@
 //     multiply-add from the coordinate before and the coordinate an offset in the instruction.
 //   * A wave assembles its 64 indices, 2 b whole words, in words of its own in LDS with ds_or and writes them out.
 //   * The row's sum and the amplitude codes are the ones of the encoder for groups of 8 (pvq_quantize_dev.h).
-// Bound by vector instructions, 550 a group of 16 (16-bit weights, 2-bit codes).  8192 x 8192 of these, 48-bit indices: 67 us;
-// groups of 32, 96 bits: 88 us; 3001 x 11008 float32 weights, least-squares amplitudes in 4-bit codes, groups of 16, 52 bits:
-// 44 us; 7001 x 1000 in groups of 8: 13 us.  Before, with a workgroup per row that copied the size table, four reads of it
-// per coordinate, a bisection for the code and words assembled by a whole workgroup between barriers: 101, 148, 65, 26.
-// (A workgroup per set of rows instead of resident ones: 74, 140 and 49 us for the first three.)
+// Bound by vector instructions, 505 a group of 16 (16-bit weights, float32 amplitudes).  Launches in a row: 8192 x 8192 of
+// 16-bit weights, 2-bit codes, groups of 16, 48-bit indices: 61 us; groups of 32, 96 bits: 84 us; 3001 x 11008 float32
+// weights, least-squares amplitudes in 4-bit codes, groups of 16, 52 bits: 39 us (43 with the call's allocations); 7001 x 1000
+// in groups of 8: 13.5 us.  Before, with a workgroup per row that copied the size table, four reads of it per coordinate, a
+// bisection for the code and words assembled by a whole workgroup between barriers: 101, 148, 63, 26.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -68,8 +68,8 @@ __host__ __device__ inline encode_lds lds_of(int D, int W, const encode_launch &
 // encode
 // ---------------------------------------------------------------------------------------------
 
-// Waves that a SIMD's registers are divided among (groups of 16, 3001 x 11008: 44 us, with 4 46, with 6, which spill, 52;
-// groups of 32, 8192 x 8192: 104 us, with 3 141)
+// Waves that a SIMD's registers are divided among (groups of 16, 3001 x 11008: 39 us, with 4 43, with 6, which spill, 49;
+// groups of 32, 8192 x 8192, 2-bit codes: 84 us, with 3 118, with 5, which spill, 130)
 constexpr int waves_per_simd(int D) { return D == 8 ? 7 : D == 16 ? 5 : 4; }
 
 // A group as it comes from memory

@@ -730,7 +730,7 @@ __global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_
 #pragma unroll
     for (int i = 0; i < W; i++) walk.q[i] = q[i];
     walk.k2 = 2 * p.K; walk.n2 = 0; walk.i = 0; walk.sign = walk.mag = 0;
-    uint32_t mags[D / 4], signs[D / 32] = {};   // (registers, indexed by what is the same for all lanes)
+    uint32_t mags[D / 4], signs[D / 32] = {};   // (mags: D = 64 in registers, indexed by what is the same for all lanes, D = 128 in scratch)
     walk.start();
     walk.template walk<W>(mags, signs);
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");             // (the workgroup's LDS is not given back before the last loads into it)
@@ -795,8 +795,8 @@ __global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_
 // ---- many pulses: a lane per group, the tables in device memory ----------------------------------------------
 // (rows of thresholds take up to 128 KB)
 // Bytes of LDS per lane for the decoded point, rounded up to an odd number of words, so that the lanes' rows spread over the
-// banks.  BYTES (K <= 255): a byte per magnitude and a bit per sign; else int16 values, with which half as many waves fit a
-// unit (393216 groups of 64, K = 180: 99 us with bytes, 136).
+// banks.  BYTES (K <= 255): a byte per magnitude and a bit per sign; else int16 values, with which 18 waves and not 32 fit a
+// unit (393216 groups of 64, K = 180: 93 us with bytes, 136).
 template <bool BYTES>
 __host__ __device__ constexpr int decode_point_bytes(int D) { return 4 * ((BYTES ? D / 4 + D / 32 : D / 2) | 1); }
 
@@ -1175,6 +1175,7 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
 //   D = 64,  K = 40      13 / 30      16 / 30     23 / 30     24 / 30     27 / 30     32 / 30     (4)
 //            K = 96      13 / 33      17 / 34     31 / 34     38 / 34     41 / 34     41 / 34     (8)
 //            K = 127     13 / 39      17 / 39     31 / 39     38 / 39     41 / 39     41 / 39     (8)
+//            K = 160     5120 groups: 43 / 46                                                    (8)
 //            K = 220     17 / 47      24 / 48     40 / 48     43 / 48     50 / 47     51 / 48     (12)
 //            K = 255     21 / 48      30 / 48     45 / 48     50 / 48     57 / 48     57 / 48     (12)
 static int64_t few_groups(const pvq_ctx *c)
@@ -1185,8 +1186,16 @@ static int64_t few_groups(const pvq_ctx *c)
 
 // Beyond that, whether the rows of the tables go through LDS.  They do while a magnitude fits a byte; but with more than about
 // twice as many pulses as coordinates many places lie outside a window of 256, and then all of them are as well read from device
-// memory.  us, LDS / device memory, 8192 groups: D = 64, K = 96 34 / 44, 127 39 / 45, 140 43 / 46, 160 49 / 46, 200 58 / 47,
-// 255 59 / 48; D = 128, K = 187 71 / 95, 255 90 / 97.
+// memory: with many pulses always, with fewer once a unit has more groups than its two workgroups of 512 take at once.  us, LDS /
+// device memory:
+//                    8192 groups   131072     262144     393216     524288     1048576
+//   D = 64, K = 96     34 / 44     42 / 58    55 / 88    83 / 94    100 / 107   187 / 197   (device memory with an earlier kernel)
+//           K = 112    35 / 43     46 / 59    58 / 88    91 / 95    109 / 109   203 / 201   (the same)
+//           K = 127    39 / 45     52 / 59    66 / 88   105 / 89    123 / 104   233 / 194
+//           K = 150    46 / 46     60 / 59    75 / 81   120 / 91    142 / 106   271 / 198
+//           K = 160    49 / 46     63 / 52    78 / 81   126 / 91    147 / 108   282 / 200
+//           K = 200    58 / 47     75 / 57    96 / 91   157 / 105   182 / 122   351 / 226
+//   D = 128, K = 187 8192 groups 71 / 95, 262144 111 / 164, 524288 211 / 325; K = 255 90 / 97, 148 / 176, 285 / 346.
 static bool rows_in_lds(const pvq_ctx *c, int64_t groups)
 {
     if (c->D == 128) return c->K <= 255;
