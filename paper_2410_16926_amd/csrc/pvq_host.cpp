@@ -403,7 +403,7 @@ extern "C" int pvq_ctx_create(pvq_ctx **out, int D, int K, int scale_bits, const
         c->tab_guess = reinterpret_cast<const uint16_t *>(c->tab_u + guess_at);
     }
     if (e == hipSuccess && scale_bits) {
-        // the edge table is padded to 2^b entries with +inf so that kernels may read a full table
+        // 2^b entries, the last of which is no edge (+inf, which no kernel reads)
         e32.push_back(INFINITY);
         e = hipMalloc((void **)&c->edges, sizeof(float) * n);
         if (e == hipSuccess) e = hipMalloc((void **)&c->sqrtc, sizeof(float) * n);
