@@ -12,24 +12,25 @@
 // of 128, a launch per panel on the caller's stream (correct_step_kernel), whose workgroups have one of two roles:
 //     panel   (the first workgroups, 32 or 16 rows each) panel p - 1's 128 multiply-adds per element onto the panel's columns,
 //             which is all that panel p waits for, then the panel's groups one after the other, a row across 8 or 16
-//             lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  Bound by the latency of one chain:
-//             23 us for 16 groups of 8.
+//             lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  One wave a SIMD, which issues an instruction in four
+//             to five clocks whether it depends on the one before or not, so its time is the number of its instructions: 4.1 us
+//             in front (first reads 2, matrix instructions 1.7), 1.2 for the panel's part of U, 10.5 for 16 groups of 8.
 //     update  (all others) panel p - 1's 128 multiply-adds per element, in the same order, for the columns behind panel p:
-//             tiles of 128 rows x 128 columns, W read and written once per panel.  Bound: float32 matrix instructions
-//             (143 TFLOP/s in registers) and HBM together, 100 TFLOP/s at 63 x 64 tiles.
+//             tasks of 64 columns, W read and written once per panel.  Bound: float32 matrix instructions and memory together
+//             (8192 rows times 7936 columns: 167 us, the matrix instructions alone 125, memory alone 126; times 5888
+//             columns, whose W the last-level cache holds, 120 us, 96 and 64).
 // The two roles touch different columns, and the update reads panel p - 1's t values while the panel role writes
 // panel p's, which is why there are two work buffers used in turn.  The panel workgroups come first in the grid
-// and raise their waves' priority, so they are placed before the flood of update tiles and run beside it: the
+// and raise their waves' priority, so they are placed before the flood of update tasks and run beside it: the
 // chain of panels (each needs the one before) stays off the critical path as long as a launch has enough update
-// tiles to outlast it; with few rows the chain is what remains.  A workgroup has the LDS of the role that needs more: 36.9 KB
-// in groups of 8 (the update's), 39.9 in groups of 16 (the panel's), four workgroups to a compute unit; 53.2 in groups of
-// 32, three.
+// tasks to outlast it; with few rows the chain is what remains.  A workgroup has the LDS of the role that needs more: 36.9 KB
+// in groups of 8, 39.9 in groups of 16, four workgroups to a compute unit; 45.1 in groups of 32, three.
 // Both roles' 128 multiply-adds per element run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
 // element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
 // tied, subnormal and non-finite operands).
-// Before, with the update on the vector ALU (64 TFLOP/s) and 64 rows of a panel a lane each on four waves that took its
-// groups in turn (37 to 46 us a panel and 10 to 15 for a launch in front of it with its update): 8192 x 8192 9.5 ms, now
-// 6.7; 1024 x 4096 1.6 ms, now 0.92; 1024 x 8192 3.3, now 2.07; 28672 x 8192 29.5, now 21.2.
+// Before, with tiles of 128 x 128 whose workgroups waited for each stage of 32 rows of U and moved in step (loading, then
+// multiplying, then storing), and with the compiler's divisions and roots in the chain (27 us a panel): 8192 x 8192 6.6 ms, now 6.1; 1024 x 8192 2.06, now
+// 1.66; 1024 x 4096 0.90, now 0.71; 64 x 2048 0.41, now 0.28.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -44,11 +45,25 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kPanelCols = 128;   // columns per panel
 constexpr int kWaves = 4;         // waves of a workgroup
 constexpr int kThreads = 64 * kWaves;
-constexpr int kTile = 128;        // rows and columns of an update tile
-constexpr int kStage = 32;        // rows of U (and t values per row) that an update tile holds in LDS at a time
-// words from a row of t values, or of U, in LDS to the next: the 64 values of an operand lie on different banks
-constexpr int kTPitch = kStage + 4, kUPitch = kTile + 16;
-constexpr int kUpdateFloats = kTile * kTPitch + kStage * kUPitch;
+constexpr int kTileCols = 64;     // columns of an update's task
+constexpr int kItemRows = 16;     // rows that a wave of it takes at a time
+constexpr int kUpdateFloats = kPanelCols * kTileCols;
+
+// t values of a panel as the matrix instructions' operands: per 16 rows (fewer at the end) pieces of four values, of which a
+// lane takes one for four instructions in a row: piece (i, k4) of a row holds columns 16 i + 4 s + k4, s = 0 .. 3, and the rows'
+// pieces lie side by side, so that a read of 16 rows is 1 KiB in a row.
+struct t_rows {
+    int64_t at;      // piece (0, 0) of the row
+    int step;        // from a piece to the next one of the row
+    __device__ t_rows(int64_t row, int64_t rows)
+    {
+        const int64_t block = row & ~(int64_t)15;
+        step = 4 * (int)std::min<int64_t>(16, rows - block);
+        at = block * kPanelCols + 4 * (row - block);
+    }
+    __device__ const f32x4 *piece(const float *T, int i, int k4) const { return reinterpret_cast<const f32x4 *>(T + at + (4 * i + k4) * step); }
+    __device__ float *column(float *T, int k) const { return T + at + (4 * (k >> 4) + (k & 3)) * step + (k >> 2 & 3); }
+};
 
 struct correct_shape {
     int64_t ldw, rows, cols, ldu;
@@ -63,7 +78,11 @@ template <int D> struct split {
     // LDS of the panel role: D x D blocks of U on and above the panel's diagonal, before that t values and sums on their way
     // to and from the matrix cores' layout (kXPitch: an operand's values lie on different banks)
     static constexpr int kBlocks = kGroups * (kGroups + 1) / 2;
-    static constexpr int kFloats = (kBlocks + 3) * D * D;      // (a trailing update reads up to three blocks past the last)
+    // The first kNear groups behind a group are updated whether they are there or not (their instructions fill the waits of the
+    // substitution's chain), which reads up to kPast blocks behind the last; the divisors lie there, 4 words per column.
+    static constexpr int kNear = D == 8 ? 7 : D == 16 ? 3 : 0, kPast = kNear > 0 ? kNear : 1;
+    static constexpr int kDivisors = kBlocks * D * D;
+    static constexpr int kFloats = kDivisors + (4 * kPanelCols > kPast * D * D ? 4 * kPanelCols : kPast * D * D);
     static constexpr int kXPitch = kPanelCols + 4;
     static_assert(kRows * kXPitch <= kFloats, "the transposition fits");
 };
@@ -85,6 +104,33 @@ __device__ inline float lanes_sum(float v)
     return v;
 }
 
+// A divisor b with its reciprocal y = RN(1 / b) and what that is off by, yl = y (1 - b y): with them a / b, correctly rounded,
+// takes four instructions instead of the ten that serve every argument.  The first quotient a y + a yl is the exact one to a
+// few parts in 2^48, so rounded it is one of the two floats next to it; then a - q b is exact, and q + (a - q b) y rounds
+// to RN(a / b) (Markstein, Computation of elementary functions on the IBM RISC System/6000, 1990).  For b from 2^-20 to 2^20 and quotients from
+// 2^-70 to 2^70, where nothing over- or underflows; other b get y = NaN, which every quotient then is.
+struct divisor { float b, y, yl; };
+__device__ inline divisor make_divisor(float b)
+{
+    divisor d;
+    d.b = b;
+    const float r = 1.0f / b;
+    d.y = fabsf(b) >= 0x1p-20f && fabsf(b) <= 0x1p20f ? r : __builtin_nanf("");
+    d.yl = __builtin_fmaf(-b, r, 1.0f) * r;
+    return d;
+}
+__device__ inline float divide(float a, const divisor &d)
+{
+    const float q = __builtin_fmaf(a, d.y, a * d.yl);
+    return __builtin_fmaf(__builtin_fmaf(-q, d.b, a), d.y, q);
+}
+// lo <= |x| < hi
+__device__ inline bool magnitude_in(float x, float lo, float hi)
+{
+    const uint32_t l = 2u * __float_as_uint(lo), h = 2u * __float_as_uint(hi);
+    return 2u * __float_as_uint(x) - l < h - l;
+}
+
 // v of the lane j ^ X of the row
 template <int X>
 __device__ inline int lane_xor(int v)
@@ -102,16 +148,17 @@ __device__ inline int lane_xor(int v)
 template <int L, int N>
 __device__ inline float lane_broadcast(float v)
 {
-    const int i = __float_as_int(v);
-    if constexpr (L == 16) return __int_as_float(dpp<0x150 + N>(0, i));                        // row_newbcast
-    else return __int_as_float(dpp<0x150 + 8 + N, 0xC>(dpp<0x150 + N>(0, i), i));              // one for either half
+    const int i = __float_as_int(v), low = __builtin_amdgcn_mov_dpp(i, 0x150 + N, 0xF, 0xF, true);   // row_newbcast
+    return __int_as_float(L == 16 ? low : dpp<0x150 + (L == 16 ? 0 : 8) + N, 0xC>(low, i));          // (one for either half)
 }
 
-// How many coordinates of lanes j ^ X, X = 1 .. L - 1, come before coordinate c of this lane in the order of keys (largest
-// first, lower coordinate first on ties): key > mine, or >= where the other lane is the lower one (th: mine, less one
-// where bit b of j says so).
+// A bit of `behind` per coordinate of lanes j ^ X, X = 1 .. L - 1, set if it does not come before coordinate c of this lane in
+// the order of keys (largest first, lower coordinate first on ties): key < th, th being mine, and one more where bit b of j does
+// not say that the other lane is the lower one.  Keys are not negative, so the difference has the answer in its sign.  (The
+// other lane's key is the minuend: the reversed subtraction v_subrev_u32 with a DPP operand, which the compiler makes of the opposite,
+// permutes its other operand here.)
 template <int L, int C, int X>
-__device__ inline void count_before(const int (&key)[C], const int (&th)[C][4], int (&before)[C])
+__device__ inline void mark_behind(const int (&key)[C], const int (&th)[C][4], uint32_t (&behind)[C])
 {
     if constexpr (X < L) {
         constexpr int b = X < 2 ? 0 : X < 4 ? 1 : X < 8 ? 2 : 3;
@@ -119,78 +166,145 @@ __device__ inline void count_before(const int (&key)[C], const int (&th)[C][4], 
         for (int o = 0; o < C; o++) {
             const int other = lane_xor<X>(key[o]);
 #pragma unroll
-            for (int c = 0; c < C; c++) before[c] += other > th[c][b] ? 1 : 0;
+            for (int c = 0; c < C; c++) behind[c] = __builtin_amdgcn_alignbit(behind[c], (uint32_t)(other - th[c][b]), 31);
         }
-        count_before<L, C, X + 1>(key, th, before);
+        mark_behind<L, C, X + 1>(key, th, behind);
     }
 }
 
 // The quantiser of Sec. 2.5 (as in pvq_quantize_dev.h) with the group's coordinates C j .. C j + C - 1 in lane j of its row: the
-// same sums in the same order, the coordinates' places in the order of deviations counted by comparisons.  Returns the
-// sum of squares; y gets the signed point.
-template <int D>
-__device__ inline float quantize_lanes(const float (&w)[split<D>::C], int j, int K, int (&y)[split<D>::C])
+// same sums in the same order, the coordinates that hold the first places in the order of deviations found by comparing all
+// of them.  ss: the sum of squares, y: the signed point (zeros of either sign).
+//   PLAIN: for groups whose ss lies between 2^-90 and 2^90, which have a direction and whose norms are far from either end of the
+// type: K / l1 is the first quotient K RN'(1 / l1) and one correction, with v_rcp_f32's reciprocal, which is the correctly rounded
+// one for every K up to 255 and every significand of l1 (all of them compared with the division).
+template <int D, bool PLAIN>
+__device__ inline void quantize_lanes(const float (&w)[split<D>::C], int j, int K, float &ss, float (&y)[split<D>::C])
 {
     constexpr int L = split<D>::L, C = split<D>::C;
     float a1 = fabsf(w[0]), s2 = w[0] * w[0];
     if constexpr (C == 2) { a1 = a1 + fabsf(w[1]); s2 = s2 + w[1] * w[1]; }
-    const float l1 = lanes_sum<L>(a1), ss = lanes_sum<L>(s2);
-    const float g = (float)K / l1;
-    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+    const float l1 = lanes_sum<L>(a1), Kf = (float)K;
+    ss = lanes_sum<L>(s2);
+    float g;
+    bool degenerate = false;
+    if constexpr (PLAIN) {
+        const float r = __builtin_amdgcn_rcpf(l1), q = Kf * r;
+        g = __builtin_fmaf(__builtin_fmaf(-q, l1, Kf), r, q);
+    } else {
+        g = Kf / l1;
+        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+    }
     float t[C], yf[C];
-    float S = 0.0f;
 #pragma unroll
     for (int c = 0; c < C; c++) {
         t[c] = fabsf(w[c]) * g;
         yf[c] = rintf(t[c]);
-        S += yf[c];                           // small integers: exact in any order
     }
-    S = lanes_sum<L>(S);
-    const float m = (float)K - S;             // > 0: pulses to add, < 0: pulses to take away
+    // small integers: exact in any order;  > 0: pulses to add, < 0: pulses to take away
+    const float m = Kf - lanes_sum<L>(C == 2 ? yf[0] + yf[C - 1] : yf[0]);
     const float unit = m < 0.0f ? -1.0f : 1.0f;
-    // deviations as integers that order like them (zeros have one sign: t - yf is +0 there)
+    const int need = (int)fabsf(m);
+    // deviations; the `need` largest are positive, and positive floats order like their bits
     int key[C], th[C][4];
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        const float d = t[c] - yf[c];
-        const int b = __float_as_int(m < 0.0f ? -d : d);
-        key[c] = b ^ ((b >> 31) & 0x7FFFFFFF);
+        key[c] = std::max(__float_as_int((t[c] - yf[c]) * unit), 0);
 #pragma unroll
-        for (int v = 0; v < 4; v++) th[c][v] = key[c] - ((j >> v) & 1);
+        for (int v = 0; v < 4; v++) th[c][v] = key[c] + (~(j >> v) & 1);
     }
-    int before[C];
-#pragma unroll
-    for (int c = 0; c < C; c++) before[c] = 0;
-    if constexpr (C == 2) {
-        const int first = key[0] >= key[1] ? 1 : 0;
-        before[1] = first; before[0] = 1 - first;
-    }
-    count_before<L, C, 1>(key, th, before);
-    const int need = (int)fabsf(m);
+    uint32_t behind[C];
+    behind[0] = 0;
+    if constexpr (C == 2) { behind[0] = key[0] >= key[C - 1] ? 1u : 0u; behind[C - 1] = 1u - behind[0]; }
+    mark_behind<L, C, 1>(key, th, behind);
 #pragma unroll
     for (int c = 0; c < C; c++) {
-        int mag = (int)(yf[c] + (before[c] < need ? unit : 0.0f));
-        if (degenerate) mag = C * j + c == D - 1 ? K : 0;
-        y[c] = (w[c] < 0.0f && !degenerate) ? -mag : mag;
+        // unit where fewer than `need` are in front
+        const int moved = (D - 1 - need - (int)__builtin_popcount(behind[c])) >> 31 & __float_as_int(unit);
+        float mag = yf[c] + __int_as_float(moved);
+        // (a weight of -0 has the point's +0, which shows in the sign of its error; PLAIN refuses errors that stay zero)
+        if constexpr (PLAIN) {
+            y[c] = copysignf(mag, w[c]);
+        } else {
+            if (degenerate) mag = C * j + c == D - 1 ? Kf : 0.0f;
+            y[c] = w[c] < 0.0f && !degenerate ? -mag : mag;
+        }
     }
-    return ss;
 }
 
 // t U_GG = e, coordinate after coordinate: t_I is final once t_0 .. t_{I-1} have been taken off e_I.  e: the lane's
-// coordinates; u: rows of the block in the lane's columns, ud: its diagonal there.  tb gets all of t, mine the lane's own.
-template <int D, int I>
-__device__ inline void substitute(float (&e)[split<D>::C], const float (&u)[split<D>::C][D], const float (&ud)[split<D>::C],
-                                  int j, float (&tb)[D], float (&mine)[split<D>::C])
+// coordinates; u: rows of the block in the lane's columns, zero on and below the diagonal; d: its diagonal there.  tb gets all of
+// t, mine the lane's own.  PLAIN: a lane's e stays what it is behind its own place, since it loses products with zeros, so the
+// last quotients are the lane's own t; right if they all lie between 2^-70 and 2^70 (a zero would lose its sign).
+// next(I): work with t_0 .. t_I that the waits of the chain have time for.
+template <int D, bool PLAIN, int I, typename Next>
+__device__ inline void substitute(float (&e)[split<D>::C], const float (&u)[split<D>::C][D], const divisor (&d)[split<D>::C],
+                                  int j, float (&tb)[D], float (&mine)[split<D>::C], const Next &next)
 {
     constexpr int L = split<D>::L, C = split<D>::C;
     if constexpr (I < D) {
-        const float q = e[I % C] / ud[I % C];
-        mine[I % C] = j == I / C ? q : mine[I % C];
+        const float q = PLAIN ? divide(e[I % C], d[I % C]) : e[I % C] / d[I % C].b;
+        if constexpr (PLAIN) mine[I % C] = q;
+        else mine[I % C] = j == I / C ? q : mine[I % C];
+        if constexpr (I > 0) next(I - 1);
         tb[I] = lane_broadcast<L, I / C>(q);
 #pragma unroll
         for (int c = 0; c < C; c++) e[c] = __builtin_fmaf(-tb[I], u[c][I], e[c]);
-        substitute<D, I + 1>(e, u, ud, j, tb, mine);
+        substitute<D, PLAIN, I + 1>(e, u, d, j, tb, mine, next);
+        if constexpr (I + 1 == D) next(I);
     }
+}
+
+// A group from its values w: quantiser, amplitude, error, substitution; tb and mine as above.  Returns whether the result is
+// right, which PLAIN is not for every group.
+template <int D, bool LS, bool PLAIN, typename Next>
+__device__ inline bool solve_group(const float (&w)[split<D>::C], const float (&u)[split<D>::C][D], const divisor (&d)[split<D>::C],
+                                   int j, int K, float (&tb)[D], float (&mine)[split<D>::C], const Next &next)
+{
+    constexpr int L = split<D>::L, C = split<D>::C;
+    float y[C], ss;
+    quantize_lanes<D, PLAIN>(w, j, K, ss, y);
+    float sq = 0.0f, dot = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; c++) {
+        const float s = y[c] * y[c], p = y[c] * w[c];
+        sq = c == 0 ? s : sq + s;                               // integers
+        dot = c == 0 ? p : dot + p;
+    }
+    sq = lanes_sum<L>(sq);
+    float gain;
+    if constexpr (PLAIN) {
+        // Root of x: g = x y with v_rsq_f32's y and one step of Newton's, the correctly rounded one for every float from 2^-100 to
+        // 2^100 (all of them compared with sqrtf); the reciprocal of an integer's root from the same y and one step, correctly
+        // rounded for all integers up to 2^16 (likewise).
+        auto root_of = [](float x, float y0) {
+            const float g0 = x * y0, h = 0.5f * y0;
+            return __builtin_fmaf(__builtin_fmaf(-g0, g0, x), h, g0);
+        };
+        const float y0 = __builtin_amdgcn_rsqf(sq);
+        divisor r;
+        r.b = root_of(sq, y0);
+        r.y = __builtin_fmaf(__builtin_fmaf(-r.b, y0, 1.0f), y0, y0);
+        r.yl = __builtin_fmaf(-r.b, r.y, 1.0f) * r.y;
+        float s;
+        if constexpr (LS) s = divide(lanes_sum<L>(dot), r);
+        else s = root_of(ss, __builtin_amdgcn_rsqf(ss));
+        gain = divide(s, r);
+    } else {
+        const float root = sqrtf(sq);
+        gain = (LS ? lanes_sum<L>(dot) / root : sqrtf(ss)) / root;
+    }
+    float e[C];
+#pragma unroll
+    for (int c = 0; c < C; c++) { e[c] = w[c] - gain * y[c]; mine[c] = 0.0f; }
+    substitute<D, PLAIN, 0>(e, u, d, j, tb, mine, next);
+    bool right = true;
+    if constexpr (PLAIN) {
+        right = magnitude_in(ss, 0x1p-90f, 0x1p90f);
+#pragma unroll
+        for (int c = 0; c < C; c++) right = right && magnitude_in(mine[c], 0x1p-70f, 0x1p70f);
+    }
+    return right;
 }
 
 // Panel role.  A workgroup takes split<D>::kRows rows, a wave 8 (D = 8) or 4 of them: lane (row, j) holds coordinate(s) j of
@@ -200,7 +314,7 @@ __device__ inline void substitute(float (&e)[split<D>::C], const float (&u)[spli
 //   Then group after group: the quantiser across the lanes of a row, amplitude, error, substitution, and the t values,
 // which the substitution has brought to all lanes of the row, onto the groups behind (rows of U ascending).  The next group
 // is always w[0]: one body for all groups, which stays in the instruction cache.
-template <int D>
+template <int D, bool LS>
 __device__ inline void panel_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ Tprev,
                                   float *__restrict__ Tcur, const correct_shape &a, int64_t p0, int width, float *lds)
 {
@@ -217,57 +331,70 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     float *wrow = W + row * a.ldw + p0 + C * j;
     const int ngroups = width / D;
     const float *Up = U + p0 * a.ldu + p0;                      // row p0 + k, column p0 + c of the factor
+    const float diagonal = Up[std::min<int64_t>(threadIdx.x, width - 1) * (a.ldu + 1)];
 
+    // U on and above the panel's diagonal, on its way from the start: 64 columns of four rows make a piece, of which the panel's
+    // right half has 32 and its left half 16; a lane's four values lie side by side in LDS.
+    constexpr int kRight = kPanelCols / 4 / kWaves, kMyPieces = kRight + kPanelCols / 8 / kWaves;
+    const bool right_half = width > 64;
+    float up[kMyPieces][4];
+    auto first_row = [&](int x) { return 4 * (x < kRight ? wave + kWaves * x : wave + kWaves * (x - kRight)); };
+    auto fetch_panel = [&]() {
+#pragma unroll
+        for (int x = 0; x < kMyPieces; x++) {
+            // (of a panel that has no right half the left one's, which is not used)
+            const float *p = Up + (first_row(x) & (right_half ? 127 : 63)) * a.ldu + (x < kRight && right_half ? 64 : 0);
+#pragma unroll
+            for (int i = 0; i < 4; i++) up[x][i] = p[i * a.ldu + (uint32_t)lane];
+        }
+    };
     float w[NG][C];
     if (p0 > 0) {
-        // t values of the workgroup's rows
-#pragma unroll
-        for (int x = 0; x < S::kRows * kPanelCols / 4 / kThreads; x++) {
-            const int e = threadIdx.x + x * kThreads, rr = e / (kPanelCols / 4), c4 = (e % (kPanelCols / 4)) * 4;
-            *reinterpret_cast<float4 *>(lds + rr * S::kXPitch + c4) =
-                *reinterpret_cast<const float4 *>(Tprev + std::min<int64_t>(row0 + rr, a.rows - 1) * kPanelCols + c4);
-        }
         const int c16 = lane & 15, k4 = lane >> 4;              // an operand's row or column, and its place in k
         const bool cols_in = 32 * wave < width;
         f32x4 acc[RB][2];
-        constexpr int kAhead = 16;                              // operands of so many instructions on their way at a time
-        float uv[kAhead][2];
-        const float *ub = U + (p0 - kPanelCols + k4) * a.ldu + p0 + 32 * wave + c16;
-        auto fetch = [&]() {
+        constexpr int kAhead = 8;                               // operands of so many instructions are on their way while as many are used
+        float uv[2][kAhead][2];
+        // (a wave without columns reads the first ones)
+        const float *ub = U + (p0 - kPanelCols + k4) * a.ldu + p0 + (cols_in ? 32 * wave : 0) + c16;
+        auto fetch = [&](float (&v)[kAhead][2]) {
 #pragma unroll
-            for (int s = 0; s < kAhead; s++) { uv[s][0] = ub[0]; uv[s][1] = ub[16]; ub += 4 * a.ldu; }
+            for (int s = 0; s < kAhead; s++) { v[s][0] = ub[0]; v[s][1] = ub[16]; ub += 4 * a.ldu; }
         };
-        if (cols_in) {
+        f32x4 tq[2][RB][kAhead / 4];
+        auto fetch_t = [&](int h) {
 #pragma unroll
             for (int rb = 0; rb < RB; rb++) {
-                const float *p = W + std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1) * a.ldw + p0 + 32 * wave + 4 * k4;
-                acc[rb][0] = *reinterpret_cast<const f32x4 *>(p);
-                acc[rb][1] = *reinterpret_cast<const f32x4 *>(p + 16);
+                const t_rows t(std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1), a.rows);
+#pragma unroll
+                for (int i = 0; i < kAhead / 4; i++) tq[h & 1][rb][i] = *t.piece(Tprev, kAhead / 4 * h + i, k4);
             }
-            fetch();
+        };
+        fetch(uv[0]);
+        fetch_t(0);
+#pragma unroll
+        for (int rb = 0; rb < RB; rb++) {
+            const float *p = W + std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1) * a.ldw + p0 + (cols_in ? 32 * wave : 0) + 4 * k4;
+            acc[rb][0] = *reinterpret_cast<const f32x4 *>(p);
+            acc[rb][1] = *reinterpret_cast<const f32x4 *>(p + 16);
         }
-        __syncthreads();
-        if (cols_in) {
-#pragma unroll 1
-            for (int s0 = 0; s0 < kPanelCols / 4; s0 += kAhead) {
-                if (s0) fetch();
+        fetch_panel();
 #pragma unroll
-                for (int s = 0; s < kAhead; s++)
+        for (int h = 0; h < kPanelCols / 4 / kAhead; h++) {
+            if (h + 1 < kPanelCols / 4 / kAhead) { fetch(uv[(h + 1) & 1]); fetch_t(h + 1); }
 #pragma unroll
-                    for (int rb = 0; rb < RB; rb++) {
-                        const float tv = lds[(16 * rb + c16) * S::kXPitch + 4 * (s0 + s) + k4];
+            for (int s = 0; s < kAhead; s++)
 #pragma unroll
-                        for (int h = 0; h < 2; h++) acc[rb][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[s][h], tv, acc[rb][h], 0, 0, 0);
-                    }
-            }
+                for (int rb = 0; rb < RB; rb++)
+#pragma unroll
+                    for (int x = 0; x < 2; x++)
+                        acc[rb][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[h & 1][s][x], tq[h & 1][rb][s / 4][s % 4], acc[rb][x], 0, 0, 0);
         }
-        __syncthreads();
-        if (cols_in) {
 #pragma unroll
-            for (int rb = 0; rb < RB; rb++)
+        for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-                for (int h = 0; h < 2; h++) *reinterpret_cast<f32x4 *>(lds + (16 * rb + c16) * S::kXPitch + 32 * wave + 16 * h + 4 * k4) = acc[rb][h];
-        }
+            for (int h = 0; h < 2; h++)
+                if (cols_in) *reinterpret_cast<f32x4 *>(lds + (16 * rb + c16) * S::kXPitch + 32 * wave + 16 * h + 4 * k4) = acc[rb][h];
         __syncthreads();
 #pragma unroll
         for (int g = 0; g < NG; g++)
@@ -275,208 +402,230 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
             for (int c = 0; c < C; c++) w[g][c] = lds[rloc * S::kXPitch + (g < ngroups ? g : 0) * D + C * j + c];
         __syncthreads();
     } else {
+        fetch_panel();
 #pragma unroll
         for (int g = 0; g < NG; g++)
 #pragma unroll
             for (int c = 0; c < C; c++) w[g][c] = wrow[(g < ngroups ? g : 0) * D + c];
     }
 
-    // U on and above the panel's diagonal: block (G, G + rel) is number G NG - G (G - 1) / 2 + rel, its element (i, C j + c) at
-    // ((i / 4 C + c) L + j) 4 + i % 4, so that a lane reads four rows of its column at a time
-    constexpr int kQuads = kPanelCols * kPanelCols / 4;         // float4 of the panel's square
-    for (int e = threadIdx.x; e < kQuads; e += kThreads) {
-        const int k = e / (kPanelCols / 4), c4 = (e % (kPanelCols / 4)) * 4;
-        const int G = k / D, g = c4 / D, i = k % D, col = c4 % D;
-        if (g >= G && k < width && c4 < width) {
-            const float4 v = *reinterpret_cast<const float4 *>(Up + (int64_t)k * a.ldu + c4);
-            float *b = lds + (G * NG - G * (G - 1) / 2 + g - G) * D * D + i % 4;
-            const float vv[4] = {v.x, v.y, v.z, v.w};
+    // Block (G, G + rel) is number G NG - G (G - 1) / 2 + rel, its element (i, C j + c) at ((i / 4 C + c) L + j) 4 + i % 4, so that a
+    // lane reads four rows of its column at a time; the diagonal itself apart, as divisors, with zeros in its place and below.
+    const int col = lane % D, in_block = (lane / D) * D * D + (col % C * L + col / C) * 4;
 #pragma unroll
-            for (int q = 0; q < 4; q++) b[((i / 4 * C + (col + q) % C) * L + (col + q) / C) * 4] = vv[q];
+    for (int x = 0; x < kMyPieces; x++) {
+        if (x >= kRight || right_half) {
+            const int k = first_row(x), G = k / D, c = x < kRight ? 64 : 0;
+            float *to = lds + ((G * NG - G * (G - 1) / 2 - G + c / D) * D * D + (k % D) * (C * L)) + in_block;
+            float4 v = make_float4(up[x][0], up[x][1], up[x][2], up[x][3]);
+            if (4 * kWaves * (x < kRight ? x : x - kRight) < c) {
+                *reinterpret_cast<float4 *>(to) = v;            // (right of the diagonal as a whole)
+            } else if (c + lane >= G * D) {
+                const int below = c + lane - k;                 // rows of the piece above the diagonal
+                v.x = below > 0 ? v.x : 0.0f; v.y = below > 1 ? v.y : 0.0f; v.z = below > 2 ? v.z : 0.0f; v.w = below > 3 ? v.w : 0.0f;
+                *reinterpret_cast<float4 *>(to) = v;
+            }
         }
+    }
+    float *divisors = lds + S::kDivisors;
+    if ((int)threadIdx.x < width) {
+        const divisor d = make_divisor(diagonal);
+        *reinterpret_cast<float4 *>(divisors + 4 * threadIdx.x) = make_float4(d.b, d.y, d.yl, 0.0f);
     }
     __syncthreads();
 
-    float *trow = Tcur + row * kPanelCols + C * j;              // t values, negated
+    // What the next panel reads of U comes to this die's L2 meanwhile: its rows in the next panel's columns and the next panel's
+    // own, 2 x 128 rows of four 128-byte lines, a lane each (rows lie far apart, so that a first touch is a page's first touch
+    // too: 64 rows 17.7 us a panel, 18.6 without).
+    float touched[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    if (p0 + 2 * kPanelCols <= a.cols) {
+#pragma unroll
+        for (int x = 0; x < 4; x++) touched[x] = Up[(int64_t)(threadIdx.x / 4 + 64 * x) * a.ldu + kPanelCols + threadIdx.x % 4 * 32];
+    }
+    const t_rows trow(row, a.rows);                             // t values, negated
     const float *ublk = lds + j * 4;                            // block (G, G), the lane's column
-    const int own = C * j;
 #pragma unroll 1
     for (int G = 0; G < ngroups; G++) {
-        float (&wg)[C] = w[0];
-        // what is quantised, and stays in W
-        if (in) {
-#pragma unroll
-            for (int c = 0; c < C; c++) wrow[c] = wg[c];
-        }
-        float u[C][D], ud[C];
+        float wg[C], u[C][D], mine[C], tb[D];
+        divisor d[C];
 #pragma unroll
         for (int c = 0; c < C; c++) {
+            wg[c] = w[0][c];
 #pragma unroll
             for (int i = 0; i < D; i += 4) {
                 const float4 v = *reinterpret_cast<const float4 *>(ublk + (i / 4 * C + c) * L * 4);
                 u[c][i] = v.x; u[c][i + 1] = v.y; u[c][i + 2] = v.z; u[c][i + 3] = v.w;
             }
-            ud[c] = ublk[((own + c) / 4 * C + c) * L * 4 + (own + c) % 4];
+            const float4 v = *reinterpret_cast<const float4 *>(divisors + 4 * (G * D + C * j + c));
+            d[c].b = v.x; d[c].y = v.y; d[c].yl = v.z;
         }
-        int y[C];
-        const float ss = quantize_lanes<D>(wg, j, a.K, y);
-        float sq = 0.0f, dot = 0.0f;
+        // onto the groups behind: w[rel] less the products with the block's rows, ascending
+        auto behind = [&](int rel, int c) {
+            float v = w[rel][c];
 #pragma unroll
-        for (int c = 0; c < C; c++) {
-            const float yc = (float)y[c];
-            sq += yc * yc;                                      // integers
-            const float p = yc * wg[c];
-            dot = c == 0 ? p : dot + p;
-        }
-        const float root = sqrtf(lanes_sum<L>(sq));
-        const float s = a.ls ? lanes_sum<L>(dot) / root : sqrtf(ss);
-        const float gain = s / root;
-        float e[C], mine[C], tb[D];
+            for (int i = 0; i < D; i += 4) {
+                const float4 q = *reinterpret_cast<const float4 *>(ublk + rel * D * D + (i / 4 * C + c) * L * 4);
+                v = __builtin_fmaf(-tb[i], q.x, v); v = __builtin_fmaf(-tb[i + 1], q.y, v);
+                v = __builtin_fmaf(-tb[i + 2], q.z, v); v = __builtin_fmaf(-tb[i + 3], q.w, v);
+            }
+            return v;
+        };
+        // the first ones beside the substitution
+        float near[S::kPast][C];
+        f32x4 q[S::kPast][C][D / 4];
 #pragma unroll
-        for (int c = 0; c < C; c++) { e[c] = wg[c] - gain * (float)y[c]; mine[c] = 0.0f; }
-        substitute<D, 0>(e, u, ud, j, tb, mine);
+        for (int n = 0; n < S::kNear; n++)
+#pragma unroll
+            for (int c = 0; c < C; c++)
+#pragma unroll
+                for (int i = 0; i < D; i += 4) q[n][c][i / 4] = *reinterpret_cast<const f32x4 *>(ublk + (n + 1) * D * D + (i / 4 * C + c) * L * 4);
+        auto next = [&](int i) {
+#pragma unroll
+            for (int n = 0; n < S::kNear; n++)
+#pragma unroll
+                for (int c = 0; c < C; c++) near[n][c] = __builtin_fmaf(-tb[i], q[n][c][i / 4][i % 4], i == 0 ? w[n + 1][c] : near[n][c]);
+        };
+        const bool right = solve_group<D, LS, true>(wg, u, d, j, a.K, tb, mine, next);
+#pragma unroll
+        for (int n = 0; n < S::kNear; n++)
+#pragma unroll
+            for (int c = 0; c < C; c++) asm volatile("" : "+v"(near[n][c]));   // (here, not behind the branch)
+        // (a group without a direction, with zeros in its error, or with values near either end of the type: rare, and the wave
+        // takes its groups again with the operations that serve every argument)
+        if (!__all(right)) solve_group<D, LS, false>(wg, u, d, j, a.K, tb, mine, next);
+        // what was quantised stays in W
         if (in) {
 #pragma unroll
-            for (int c = 0; c < C; c++) trow[c] = -mine[c];
+            for (int c = 0; c < C; c++) { wrow[c] = wg[c]; *trow.column(Tcur, G * D + C * j + c) = -mine[c]; }
         }
-        // onto the groups behind, which move up by one; four at a time, as many of them as there are
+        // the groups behind move up by one; those that are further off four at a time, as many of them as there are
 #pragma unroll
-        for (int r4 = 0; r4 < NG; r4 += 4) {
-            if (G + r4 + (r4 == 0) < ngroups) {
+        for (int rel = 1; rel <= S::kNear; rel++)
 #pragma unroll
-                for (int rel = r4 == 0 ? 1 : r4; rel < r4 + 4 && rel < NG; rel++)
+            for (int c = 0; c < C; c++) w[rel - 1][c] = near[rel - 1][c];
 #pragma unroll
-                    for (int c = 0; c < C; c++) {
-                        float v = w[rel][c];
+        for (int r4 = S::kNear + 1; r4 < NG; r4 += 4) {
+            if (G + r4 < ngroups) {
 #pragma unroll
-                        for (int i = 0; i < D; i += 4) {
-                            const float4 q = *reinterpret_cast<const float4 *>(ublk + rel * D * D + (i / 4 * C + c) * L * 4);
-                            v = __builtin_fmaf(-tb[i], q.x, v); v = __builtin_fmaf(-tb[i + 1], q.y, v);
-                            v = __builtin_fmaf(-tb[i + 2], q.z, v); v = __builtin_fmaf(-tb[i + 3], q.w, v);
-                        }
-                        w[rel - 1][c] = v;
-                    }
+                for (int rel = r4; rel < r4 + 4 && rel < NG; rel++)
+#pragma unroll
+                    for (int c = 0; c < C; c++) w[rel - 1][c] = behind(rel, c);
             }
         }
         ublk += (NG - G) * D * D;
         wrow += D;
-        trow += D;
     }
+    asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
 }
 
-// Update role.  Tile (row tile, column tile) of the columns [c1, cols): W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ...
-// - t[r][127] U[c0 + 127][c], one multiply-add after the other, t = the t values of the panel at column c0, on the matrix
-// cores: v_mfma_f32_16x16x4_f32 adds its four products one by one, k ascending, each a fused multiply-add (bit for bit,
-// subnormals, infinities and NaN included).  A wave takes 64 x 64 of the tile, a stage = 32 rows of U and 32 t values per row
-// in LDS.  Neighbouring workgroups share the tile of U.
+// Update role.  Rows [row0, row1), columns [col0, col0 + 64): W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ... - t[r][127] U[c0 + 127][c], one
+// multiply-add after the other, t = the t values of the panel at column c0, on the matrix cores: v_mfma_f32_16x16x4_f32 adds its
+// four products one by one, k ascending, each a fused multiply-add (bit for bit, subnormals, infinities and NaN included).
+// The workgroup has its part of U in LDS, after which its waves do not wait for each other: a wave takes 16 rows at a time, whose W
+// and t values (as operands, t_rows) are requested when the rows before are begun, so that memory and matrix cores are busy at
+// the same time whatever the other waves do.
 __device__ inline void update_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ T,
-                                   const correct_shape &a, int64_t c0, int64_t c1, int row_tile, int col_tile, float *lds)
+                                   const correct_shape &a, int64_t c0, int64_t col0, int64_t row0, int64_t row1, float *lds)
 {
-    float *Ts = lds;                              // [row of the tile][k], kTPitch words a row
-    float *Us = lds + kTile * kTPitch;            // [k][column of the tile], kUPitch words a row
-    const int64_t row0 = (int64_t)row_tile * kTile, col0 = c1 + (int64_t)col_tile * kTile;
+    constexpr int kPieces = kPanelCols / 16;      // float4 of t values of a lane for a row, each for four instructions in a row
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wr = wave >> 1, wc = wave & 1;      // the wave's 64 rows and 64 columns
     const int c16 = lane & 15, k4 = lane >> 4;
-    const bool mine = row0 + 64 * wr < a.rows && col0 + 64 * wc < a.cols;   // (columns come in whole 64s)
-    // The instruction's rows are columns of the tile, so that a lane's four results are neighbours: row 16 rb + c16 of the
-    // wave's, columns 16 cb + 4 k4 .. + 3.
-    f32x4 acc[4][4];
-    float *wt = W + (row0 + 64 * wr + c16) * a.ldw + col0 + 64 * wc + 4 * k4;
-    const int rows_left = (int)std::min<int64_t>(64, a.rows - (row0 + 64 * wr)) - c16;   // row 16 rb of the lane is there if below this
-    if (mine) {
+    // U as operands: the four blocks of 16 columns side by side, so that an instruction's four are one read
+    {
+        float uq[kPanelCols * 16 / kThreads][4];
+        const float *up = U + (c0 + (tid >> 4)) * a.ldu + col0 + (tid & 15);
 #pragma unroll
-        for (int rb = 0; rb < 4; rb++) {
-            // (for a row that is not there the wave's last one, whose distance may be negative)
-            const float *p = wt + std::min(16 * rb, rows_left - 1) * a.ldw;
+        for (int x = 0; x < kPanelCols * 16 / kThreads; x++) {
 #pragma unroll
-            for (int cb = 0; cb < 4; cb++) acc[rb][cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
+            for (int q = 0; q < 4; q++) uq[x][q] = up[16 * q];
+            up += kThreads / 16 * a.ldu;
         }
+#pragma unroll
+        for (int x = 0; x < kPanelCols * 16 / kThreads; x++)
+            *reinterpret_cast<f32x4 *>(lds + (tid + x * kThreads) * 4) = f32x4{uq[x][0], uq[x][1], uq[x][2], uq[x][3]};
     }
-    // the lane's places in a stage's tiles: row tid / 8 and every 32nd one behind it of t, row tid / 32 and every eighth one
-    // behind it of U (one pointer that moves on: a pointer per load would take the registers of the sums)
-    const bool u_in = col0 + (tid & 31) * 4 < a.cols;
-    const float *up = U + (c0 + (tid >> 5)) * a.ldu + col0 + (tid & 31) * 4;
-    const float *tp = T + row0 * kPanelCols + (tid & 7) * 4;
-    const int t_last = (int)std::min<int64_t>(kTile, a.rows - row0) - 1;
-    uint32_t t_at[4];
+    __syncthreads();
+    int at = lane;                                                         // ([4 s + k4][c16])
+    // The instruction's rows are columns of W, so that a lane's four results are neighbours: row c16 of the wave's, columns
+    // 16 cb + 4 k4 .. + 3.  A row that is not there is the last one, and not stored.
+    f32x4 w[4], t[kPieces];
+    auto fetch = [&](int64_t r) {
+        const int64_t row = std::min<int64_t>(r + c16, row1 - 1);
+        const float *p = W + row * a.ldw + col0 + 4 * k4;
+        const t_rows tr(row, a.rows);
 #pragma unroll
-    for (int x = 0; x < 4; x++) t_at[x] = (uint32_t)std::min((tid >> 3) + 32 * x, t_last) * kPanelCols;
-#pragma unroll 1
-    for (int st = 0; st < kPanelCols / kStage; st++) {
-        f32x4 tq[4], uq[4];
+        for (int i = 0; i < kPieces; i++) t[i] = *tr.piece(T, i, k4);
 #pragma unroll
-        for (int x = 0; x < 4; x++) tq[x] = *reinterpret_cast<const f32x4 *>(tp + t_at[x]);
-        if (u_in) {
+        for (int cb = 0; cb < 4; cb++) w[cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
+    };
+    int64_t r = row0 + kItemRows * wave;
+    if (r < row1) fetch(r);
+    for (; r < row1; r += kItemRows * kWaves) {
+        asm volatile("" : "+v"(at));              // (the operands are the same for all rows, and more than there are registers)
+        const f32x4 *us = reinterpret_cast<const f32x4 *>(lds) + at;
+        f32x4 acc[4], tv[kPieces];
 #pragma unroll
-            for (int x = 0; x < 4; x++) { uq[x] = *reinterpret_cast<const f32x4 *>(up); up += 8 * a.ldu; }
-        } else {
+        for (int i = 0; i < kPieces; i++) tv[i] = t[i];
 #pragma unroll
-            for (int x = 0; x < 4; x++) uq[x] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int cb = 0; cb < 4; cb++) acc[cb] = w[cb];
+        if (r + kItemRows * kWaves < row1) fetch(r + kItemRows * kWaves);
+#pragma unroll
+        for (int s = 0; s < kPanelCols / 4; s++) {
+            const f32x4 uv = us[s * 64];
+#pragma unroll
+            for (int cb = 0; cb < 4; cb++) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[cb], tv[s / 4][s % 4], acc[cb], 0, 0, 0);
         }
-        tp += kStage;
-        if (st) __syncthreads();                  // the tiles of the stage before are no longer read
+        if (r + c16 < row1) {
+            float *p = W + (r + c16) * a.ldw + col0 + 4 * k4;
 #pragma unroll
-        for (int x = 0; x < 4; x++) {
-            *reinterpret_cast<f32x4 *>(Ts + ((tid >> 3) + 32 * x) * kTPitch + (tid & 7) * 4) = tq[x];
-            *reinterpret_cast<f32x4 *>(Us + ((tid >> 5) + 8 * x) * kUPitch + (tid & 31) * 4) = uq[x];
+            for (int cb = 0; cb < 4; cb++) *reinterpret_cast<f32x4 *>(p + 16 * cb) = acc[cb];
         }
-        __syncthreads();
-        if (mine) {
-#pragma unroll 2
-            for (int s = 0; s < kStage / 4; s++) {
-                float tv[4], uv[4];
-#pragma unroll
-                for (int x = 0; x < 4; x++) {
-                    tv[x] = Ts[(64 * wr + 16 * x + c16) * kTPitch + 4 * s + k4];
-                    uv[x] = Us[(4 * s + k4) * kUPitch + 64 * wc + 16 * x + c16];
-                }
-#pragma unroll
-                for (int rb = 0; rb < 4; rb++)
-#pragma unroll
-                    for (int cb = 0; cb < 4; cb++) acc[rb][cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[cb], tv[rb], acc[rb][cb], 0, 0, 0);
-            }
-        }
-    }
-    if (mine) {
-#pragma unroll
-        for (int rb = 0; rb < 4; rb++)
-            if (16 * rb < rows_left) {
-#pragma unroll
-                for (int cb = 0; cb < 4; cb++) *reinterpret_cast<f32x4 *>(wt + 16 * rb * a.ldw + 16 * cb) = acc[rb][cb];
-            }
     }
 }
 
 // The panel at column p0 (its own 128 or 64 columns, and in front of them the panel before's update of those), and the
 // panel before's update of the columns from p0 + 128 on.  Tprev: the t values of the panel before (unused for
-// p0 = 0), Tcur: where this panel's go.  The grid is panel_wgs + row_tiles * (column tiles behind the panel) workgroups,
-// the latter none for p0 = 0.
+// p0 = 0), Tcur: where this panel's go.  The grid is panel_wgs + chunks * (64s of columns behind the panel) workgroups, the latter none
+// for p0 = 0; a chunk is chunk_rows rows, and neighbouring workgroups, which are on different dies, take different ones of the
+// same columns: the t values of a chunk are read from one L2 if their number is a multiple of eight.
 // (at most 128 registers per lane, four workgroups per compute unit; three for groups of 32, whose blocks take more LDS)
-template <int D>
+template <int D, bool LS>
 __global__ __launch_bounds__(kThreads, D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
                                                                  const float *__restrict__ Tprev, float *__restrict__ Tcur,
-                                                                 correct_shape a, int64_t p0, int width, int panel_wgs, int row_tiles)
+                                                                 correct_shape a, int64_t p0, int width, int panel_wgs, int chunks, int chunk_rows, bool late)
 {
     __shared__ __align__(16) float lds[lds_floats<D>()];
     if ((int)blockIdx.x < panel_wgs) {
         // the chain's waves go first where they share a SIMD with update waves, which have plenty of others to fill in
         __builtin_amdgcn_s_setprio(2);
-        panel_role<D>(W, U, Tprev, Tcur, a, p0, width, lds);
+        panel_role<D, LS>(W, U, Tprev, Tcur, a, p0, width, lds);
     } else {
-        const int tile = (int)blockIdx.x - panel_wgs;
-        update_role(W, U, Tprev, a, p0 - kPanelCols, p0 + kPanelCols, tile % row_tiles, tile / row_tiles, lds);
+        // With few rows the chain is what a launch waits for, and its first reads stand in line with those of all tasks (1024 rows of
+        // 8192: its front 4 us alone, 12 to 15 beside them); the tasks, 15 to 27 us in all, let it go first by 3.4 us.
+        if (late) __builtin_amdgcn_s_sleep(127);
+        const int task = (int)blockIdx.x - panel_wgs;
+        const int64_t row0 = (int64_t)(task % chunks) * chunk_rows;
+        update_role(W, U, Tprev, a, p0 - kPanelCols, p0 + kPanelCols + (int64_t)(task / chunks) * kTileCols, row0,
+                    std::min<int64_t>(row0 + chunk_rows, a.rows), lds);
     }
 }
 
 template <int D>
 void launch_step(float *W, const float *U, const float *Tprev, float *Tcur, const correct_shape &a, int64_t p0, int width,
-                 int row_tiles, int col_tiles, hipStream_t s)
+                 int col_tiles, hipStream_t s)
 {
     const int panel_wgs = (int)((a.rows + split<D>::kRows - 1) / split<D>::kRows);
-    hipLaunchKernelGGL((correct_step_kernel<D>), dim3((unsigned)(panel_wgs + row_tiles * col_tiles)), dim3(kThreads), 0, s,
-                       W, U, Tprev, Tcur, a, p0, width, panel_wgs, row_tiles);
+    // rows of a task: enough tasks to fill the units evenly (tasks that end early leave their unit to the others), as few
+    // copies of U as that allows
+    constexpr int kLeast = kItemRows * kWaves, kTasks = 2048;
+    int64_t chunk_rows = 1024;
+    while (chunk_rows > kLeast && (a.rows + chunk_rows - 1) / chunk_rows * col_tiles < kTasks) chunk_rows /= 2;
+    const int chunks = (int)((a.rows + chunk_rows - 1) / chunk_rows);
+    const bool late = a.rows <= 2048;              // (1024 x 4096 756 to 714 us, 2048 x 4096 869 to 830; 4096 x 4096 1090 either way)
+    auto kernel = a.ls ? &correct_step_kernel<D, true> : &correct_step_kernel<D, false>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(panel_wgs + chunks * col_tiles)), dim3(kThreads), 0, s,
+                       W, U, Tprev, Tcur, a, p0, width, panel_wgs, chunks, (int)chunk_rows, late);
 }
 
 // W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: two buffers of rows x 128 floats.
@@ -485,17 +634,16 @@ hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols
 {
     correct_shape a;
     a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
-    const int row_tiles = (int)((rows + kTile - 1) / kTile);
     int p = 0;
     for (int64_t p0 = 0; p0 < cols; p0 += kPanelCols, p++) {
         const int width = (int)std::min<int64_t>(kPanelCols, cols - p0);   // 128, or 64 at the end
         const int64_t behind = cols - (p0 + kPanelCols);
-        const int col_tiles = p0 > 0 && behind > 0 ? (int)((behind + kTile - 1) / kTile) : 0;
+        const int col_tiles = p0 > 0 && behind > 0 ? (int)(behind / kTileCols) : 0;
         float *Tcur = work + (int64_t)(p & 1) * rows * kPanelCols, *Tprev = work + (int64_t)((p & 1) ^ 1) * rows * kPanelCols;
         switch (c->D) {
-        case 8: launch_step<8>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
-        case 16: launch_step<16>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
-        default: launch_step<32>(W, U, Tprev, Tcur, a, p0, width, row_tiles, col_tiles, s); break;
+        case 8: launch_step<8>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
+        case 16: launch_step<16>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
+        default: launch_step<32>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
         }
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

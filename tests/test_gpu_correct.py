@@ -111,6 +111,45 @@ def test_updates_of_tiny_weights_round_like_fused_multiply_adds():
     ctx.close()
 
 
+@pytest.mark.parametrize("D,K,amplitude", [(8, 16, "l2"), (8, 127, "ls"), (16, 33, "ls"), (16, 1, "l2"), (32, 60, "l2"), (32, 100, "ls")])
+def test_groups_that_the_short_arithmetic_refuses(D, K, amplitude):
+    # Divisions and roots of ordinary groups are short sequences that are right only between bounds; waves with other groups take
+    # the general ones.  Beside ordinary rows: zeros of either sign, groups and rows of zeros, single values (whose error is
+    # exactly zero in the norm's amplitude), values at and beyond the bounds' ends, and rows of U whose diagonal lies outside theirs.
+    rows, cols = 150, 320
+    rng = np.random.default_rng(si.BASE_SEED + 650 + D + K)
+    W0 = np.asarray(si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 651, rotate=False, bf16=False), dtype=np.float32)
+    W0[rng.random(W0.shape) < 0.02] = 0.0
+    W0[rng.random(W0.shape) < 0.02] = -0.0
+    W0[5] = 0.0
+    W0[6] = -0.0
+    W0[7, D:2 * D] = 0.0
+    W0[8, :D] = 0.0
+    W0[8, 3] = -0.75
+    for r, e in zip(range(20, 52), (-126, -100, -70, -52, -50, -48, -46, -45, -44, -43, -42, 30, 40, 43, 44, 45)):
+        W0[r] *= np.float32(2.0) ** e
+    _, U = si.calibration_hessian(cols, 2 * cols, si.BASE_SEED + 652)
+    for i, e in ((0, -22), (9, 22), (D + 1, -19), (130, 19), (200, -30), (319, 30)):
+        U[i] *= np.float32(2.0) ** e
+    ref, _ = oracle.correct(W0, U, D, K, amplitude=amplitude, nthreads=8)
+    ctx = pvq.pvq_ctx_create(D, K)
+    ctx.set_amplitude(amplitude if amplitude == "ls" else "norm")
+    Wd = gu.to_dev_f32(W0)
+    pvq.pvq_correct(ctx, Wd, gu.to_dev_f32(U))
+    got = Wd.cpu().numpy()
+    finite = np.isfinite(ref).all(axis=1)
+    assert finite.sum() > rows * 0.9
+    assert np.array_equal(got[finite].view(np.uint32), ref[finite].view(np.uint32))
+    ctx.close()
+
+
+@pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 2049, 320), (8, 16, 1025, 448), (16, 33, 127, 384), (32, 60, 2177, 320)])
+def test_rows_of_an_update_task(D, K, rows, cols):
+    # tasks of 128 to 1024 rows, 16 rows a wave at a time: one row more and fewer than whole tasks, and t values of a last
+    # block of fewer than 16 rows
+    run_correct(D, K, rows, cols, seed=si.BASE_SEED + 660 + rows)
+
+
 @pytest.mark.parametrize("rows,cols", [(200, 256), (1100, 640)])
 def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols):
     # kernels only, all on the capturing stream; every replay must reproduce the eager result for the weights
