@@ -14,7 +14,8 @@
 //             which is all that panel p waits for, then the panel's groups one after the other, a row across 8 or 16
 //             lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  One wave a SIMD, which issues an instruction in four
 //             to five clocks whether it depends on the one before or not, so its time is the number of its instructions: 4.1 us
-//             in front (first reads 2, matrix instructions 1.7), 1.2 for the panel's part of U, 10.5 for 16 groups of 8.
+//             in front (first reads 2, matrix instructions 1.7), 1.2 for the panel's part of U, 10.5 for 16 groups of 8
+//             (2.4, 0.5 and 10.5 with 16 rows).
 //     update  (all others) panel p - 1's 128 multiply-adds per element, in the same order, for the columns behind panel p:
 //             tasks of 64 columns, W read and written once per panel.  Bound: float32 matrix instructions and memory together
 //             (8192 rows times 7936 columns: 167 us, the matrix instructions alone 125, memory alone 126; times 5888
@@ -30,11 +31,12 @@
 // tied, subnormal and non-finite operands).
 // Before, with tiles of 128 x 128 whose workgroups waited for each stage of 32 rows of U and moved in step (loading, then
 // multiplying, then storing), and with the compiler's divisions and roots in the chain (27 us a panel): 8192 x 8192 6.6 ms, now 6.1; 1024 x 8192 2.06, now
-// 1.66; 1024 x 4096 0.90, now 0.71; 64 x 2048 0.41, now 0.28.
+// 1.61; 1024 x 4096 in groups of 16 0.72, now 0.53; 64 x 2048 0.41, now 0.27.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "pvq_internal.h"
 
@@ -73,7 +75,7 @@ struct correct_shape {
 // ---- a row's group across L neighbouring lanes, C = D / L coordinates a lane --------------------------------
 template <int D> struct split {
     static constexpr int L = D == 8 ? 8 : 16, C = D / L;
-    static constexpr int kRowsOfWave = 64 / L, kRows = kWaves * kRowsOfWave;   // of a workgroup
+    static constexpr int kRowsOfWave = 64 / L, kMostRows = kWaves * kRowsOfWave;   // of a workgroup
     static constexpr int kGroups = kPanelCols / D;
     // LDS of the panel role: D x D blocks of U on and above the panel's diagonal, before that t values and sums on their way
     // to and from the matrix cores' layout (kXPitch: an operand's values lie on different banks)
@@ -84,7 +86,7 @@ template <int D> struct split {
     static constexpr int kDivisors = kBlocks * D * D;
     static constexpr int kFloats = kDivisors + (4 * kPanelCols > kPast * D * D ? 4 * kPanelCols : kPast * D * D);
     static constexpr int kXPitch = kPanelCols + 4;
-    static_assert(kRows * kXPitch <= kFloats, "the transposition fits");
+    static_assert(kMostRows * kXPitch <= kFloats, "the transposition fits");
 };
 template <int D> constexpr int lds_floats() { return kUpdateFloats > split<D>::kFloats ? kUpdateFloats : split<D>::kFloats; }
 
@@ -307,25 +309,25 @@ __device__ inline bool solve_group(const float (&w)[split<D>::C], const float (&
     return right;
 }
 
-// Panel role.  A workgroup takes split<D>::kRows rows, a wave 8 (D = 8) or 4 of them: lane (row, j) holds coordinate(s) j of
+// Panel role.  A workgroup takes ROWS rows, a wave 8 (D = 8) or 4 of them: lane (row, j) holds coordinate(s) j of
 // every group of the panel, and the waves do not wait for each other once the panel's part of U is in LDS.
 //   First the panel before's 128 multiply-adds per element onto this panel's columns, on the matrix cores: a wave takes 32
 // columns, the results change hands through LDS.
 //   Then group after group: the quantiser across the lanes of a row, amplitude, error, substitution, and the t values,
 // which the substitution has brought to all lanes of the row, onto the groups behind (rows of U ascending).  The next group
 // is always w[0]: one body for all groups, which stays in the instruction cache.
-template <int D, bool LS>
+template <int D, bool LS, int ROWS>
 __device__ inline void panel_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ Tprev,
                                   float *__restrict__ Tcur, const correct_shape &a, int64_t p0, int width, float *lds)
 {
     using S = split<D>;
-    constexpr int L = S::L, C = S::C, NG = S::kGroups, RB = S::kRows / 16;
+    constexpr int L = S::L, C = S::C, NG = S::kGroups, RB = ROWS / 16;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int j = lane & (L - 1);
-    const int64_t row0 = (int64_t)blockIdx.x * S::kRows;
+    const int64_t row0 = (int64_t)blockIdx.x * ROWS;
     const int rloc = wave * S::kRowsOfWave + lane / L;
-    const bool in = row0 + rloc < a.rows;
+    const bool in = rloc < ROWS && row0 + rloc < a.rows;
     // lanes beyond the rows work on the last row again; they store nothing
     const int64_t row = std::min<int64_t>(row0 + rloc, a.rows - 1);
     float *wrow = W + row * a.ldw + p0 + C * j;
@@ -348,6 +350,39 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
             for (int i = 0; i < 4; i++) up[x][i] = p[i * a.ldu + (uint32_t)lane];
         }
     };
+    // Block (G, G + rel) is number G NG - G (G - 1) / 2 + rel, its element (i, C j + c) at ((i / 4 C + c) L + j) 4 + i % 4, so that a
+    // lane reads four rows of its column at a time; the diagonal itself apart, as divisors, with zeros in its place and below.
+    // EARLY: the pieces that lie behind what the sums need on their way from the matrix cores.
+    const int col = lane % D, in_block = (lane / D) * D * D + (col % C * L + col / C) * 4;
+    auto store_panel = [&](auto early) {
+#pragma unroll
+        for (int x = 0; x < kMyPieces; x++) {
+            const int least = 4 * kWaves * (x < kRight ? x : x - kRight) / D;   // the piece's group is not below it
+            const bool behind = (least * NG - least * (least - 1) / 2) * D * D >= ROWS * S::kXPitch;
+            if (behind == (decltype(early)::value) && (x >= kRight || right_half)) {
+                const int k = first_row(x), G = k / D, c = x < kRight ? 64 : 0;
+                float *to = lds + ((G * NG - G * (G - 1) / 2 - G + c / D) * D * D + (k % D) * (C * L)) + in_block;
+                float4 v = make_float4(up[x][0], up[x][1], up[x][2], up[x][3]);
+                if (4 * kWaves * (x < kRight ? x : x - kRight) < c) {
+                    *reinterpret_cast<float4 *>(to) = v;        // (right of the diagonal as a whole)
+                } else if (c + lane >= G * D) {
+                    const int below = c + lane - k;             // rows of the piece above the diagonal
+                    v.x = below > 0 ? v.x : 0.0f; v.y = below > 1 ? v.y : 0.0f; v.z = below > 2 ? v.z : 0.0f; v.w = below > 3 ? v.w : 0.0f;
+                    *reinterpret_cast<float4 *>(to) = v;
+                }
+            }
+        }
+    };
+    float *divisors = lds + S::kDivisors;
+    static_assert(ROWS * S::kXPitch <= S::kDivisors, "divisors lie behind the transposition");
+    auto store_divisors = [&]() {
+        if ((int)threadIdx.x < width) {
+            const divisor d = make_divisor(diagonal);
+            *reinterpret_cast<float4 *>(divisors + 4 * threadIdx.x) = make_float4(d.b, d.y, d.yl, 0.0f);
+        }
+    };
+    // (lanes beyond the rows of the workgroup have none)
+    const bool chain = wave * S::kRowsOfWave < ROWS;
     float w[NG][C];
     if (p0 > 0) {
         const int c16 = lane & 15, k4 = lane >> 4;              // an operand's row or column, and its place in k
@@ -382,6 +417,7 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
 #pragma unroll
         for (int h = 0; h < kPanelCols / 4 / kAhead; h++) {
             if (h + 1 < kPanelCols / 4 / kAhead) { fetch(uv[(h + 1) & 1]); fetch_t(h + 1); }
+            if (ROWS == 16 && h == 1) { store_panel(std::true_type{}); store_divisors(); }
 #pragma unroll
             for (int s = 0; s < kAhead; s++)
 #pragma unroll
@@ -399,39 +435,20 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
 #pragma unroll
         for (int g = 0; g < NG; g++)
 #pragma unroll
-            for (int c = 0; c < C; c++) w[g][c] = lds[rloc * S::kXPitch + (g < ngroups ? g : 0) * D + C * j + c];
+            for (int c = 0; c < C; c++) w[g][c] = chain ? lds[rloc * S::kXPitch + (g < ngroups ? g : 0) * D + C * j + c] : 0.0f;
         __syncthreads();
     } else {
         fetch_panel();
+        store_divisors();
+        store_panel(std::true_type{});
 #pragma unroll
         for (int g = 0; g < NG; g++)
 #pragma unroll
             for (int c = 0; c < C; c++) w[g][c] = wrow[(g < ngroups ? g : 0) * D + c];
     }
 
-    // Block (G, G + rel) is number G NG - G (G - 1) / 2 + rel, its element (i, C j + c) at ((i / 4 C + c) L + j) 4 + i % 4, so that a
-    // lane reads four rows of its column at a time; the diagonal itself apart, as divisors, with zeros in its place and below.
-    const int col = lane % D, in_block = (lane / D) * D * D + (col % C * L + col / C) * 4;
-#pragma unroll
-    for (int x = 0; x < kMyPieces; x++) {
-        if (x >= kRight || right_half) {
-            const int k = first_row(x), G = k / D, c = x < kRight ? 64 : 0;
-            float *to = lds + ((G * NG - G * (G - 1) / 2 - G + c / D) * D * D + (k % D) * (C * L)) + in_block;
-            float4 v = make_float4(up[x][0], up[x][1], up[x][2], up[x][3]);
-            if (4 * kWaves * (x < kRight ? x : x - kRight) < c) {
-                *reinterpret_cast<float4 *>(to) = v;            // (right of the diagonal as a whole)
-            } else if (c + lane >= G * D) {
-                const int below = c + lane - k;                 // rows of the piece above the diagonal
-                v.x = below > 0 ? v.x : 0.0f; v.y = below > 1 ? v.y : 0.0f; v.z = below > 2 ? v.z : 0.0f; v.w = below > 3 ? v.w : 0.0f;
-                *reinterpret_cast<float4 *>(to) = v;
-            }
-        }
-    }
-    float *divisors = lds + S::kDivisors;
-    if ((int)threadIdx.x < width) {
-        const divisor d = make_divisor(diagonal);
-        *reinterpret_cast<float4 *>(divisors + 4 * threadIdx.x) = make_float4(d.b, d.y, d.yl, 0.0f);
-    }
+    store_panel(std::false_type{});
+    if (ROWS > 16 && p0 > 0) { store_panel(std::true_type{}); store_divisors(); }   // (there are no registers for it in front)
     __syncthreads();
 
     // What the next panel reads of U comes to this die's L2 meanwhile: its rows in the next panel's columns and the next panel's
@@ -441,6 +458,10 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     if (p0 + 2 * kPanelCols <= a.cols) {
 #pragma unroll
         for (int x = 0; x < 4; x++) touched[x] = Up[(int64_t)(threadIdx.x / 4 + 64 * x) * a.ldu + kPanelCols + threadIdx.x % 4 * 32];
+    }
+    if (!chain) {
+        asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
+        return;
     }
     const t_rows trow(row, a.rows);                             // t values, negated
     const float *ublk = lds + j * 4;                            // block (G, G), the lane's column
@@ -531,6 +552,19 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, k4 = lane >> 4;
+    // The instruction's rows are columns of W, so that a lane's four results are neighbours: row c16 of the wave's, columns
+    // 16 cb + 4 k4 .. + 3.  A row that is not there is the last one, and not stored.
+    f32x4 w[4], t[kPieces];
+    auto fetch = [&](int64_t r) {
+        const int64_t row = std::min<int64_t>(r + c16, row1 - 1);
+        const float *p = W + row * a.ldw + col0 + 4 * k4;
+        const t_rows tr(row, a.rows);
+#pragma unroll
+        for (int i = 0; i < kPieces; i++) t[i] = *tr.piece(T, i, k4);
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) w[cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
+    };
+    int64_t r = row0 + kItemRows * wave;
     // U as operands: the four blocks of 16 columns side by side, so that an instruction's four are one read
     {
         float uq[kPanelCols * 16 / kThreads][4];
@@ -547,19 +581,6 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
     }
     __syncthreads();
     int at = lane;                                                         // ([4 s + k4][c16])
-    // The instruction's rows are columns of W, so that a lane's four results are neighbours: row c16 of the wave's, columns
-    // 16 cb + 4 k4 .. + 3.  A row that is not there is the last one, and not stored.
-    f32x4 w[4], t[kPieces];
-    auto fetch = [&](int64_t r) {
-        const int64_t row = std::min<int64_t>(r + c16, row1 - 1);
-        const float *p = W + row * a.ldw + col0 + 4 * k4;
-        const t_rows tr(row, a.rows);
-#pragma unroll
-        for (int i = 0; i < kPieces; i++) t[i] = *tr.piece(T, i, k4);
-#pragma unroll
-        for (int cb = 0; cb < 4; cb++) w[cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
-    };
-    int64_t r = row0 + kItemRows * wave;
     if (r < row1) fetch(r);
     for (; r < row1; r += kItemRows * kWaves) {
         asm volatile("" : "+v"(at));              // (the operands are the same for all rows, and more than there are registers)
@@ -590,7 +611,7 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
 // for p0 = 0; a chunk is chunk_rows rows, and neighbouring workgroups, which are on different dies, take different ones of the
 // same columns: the t values of a chunk are read from one L2 if their number is a multiple of eight.
 // (at most 128 registers per lane, four workgroups per compute unit; three for groups of 32, whose blocks take more LDS)
-template <int D, bool LS>
+template <int D, bool LS, int ROWS>
 __global__ __launch_bounds__(kThreads, D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
                                                                  const float *__restrict__ Tprev, float *__restrict__ Tcur,
                                                                  correct_shape a, int64_t p0, int width, int panel_wgs, int chunks, int chunk_rows, bool late)
@@ -599,7 +620,7 @@ __global__ __launch_bounds__(kThreads, D == 32 ? 3 : 4) void correct_step_kernel
     if ((int)blockIdx.x < panel_wgs) {
         // the chain's waves go first where they share a SIMD with update waves, which have plenty of others to fill in
         __builtin_amdgcn_s_setprio(2);
-        panel_role<D, LS>(W, U, Tprev, Tcur, a, p0, width, lds);
+        panel_role<D, LS, ROWS>(W, U, Tprev, Tcur, a, p0, width, lds);
     } else {
         // With few rows the chain is what a launch waits for, and its first reads stand in line with those of all tasks (1024 rows of
         // 8192: its front 4 us alone, 12 to 15 beside them); the tasks, 15 to 27 us in all, let it go first by 3.4 us.
@@ -615,7 +636,10 @@ template <int D>
 void launch_step(float *W, const float *U, const float *Tprev, float *Tcur, const correct_shape &a, int64_t p0, int width,
                  int col_tiles, hipStream_t s)
 {
-    const int panel_wgs = (int)((a.rows + split<D>::kRows - 1) / split<D>::kRows);
+    // With few rows, which do not fill the units either way, a panel workgroup takes 16: half the matrix instructions in front
+    // (64 x 2048 17.8 to 16.6 us a panel, 2048 x 4096 26.0 to 25.2; 4096 x 4096 34.1 to 35.0).
+    const int panel_rows = split<D>::kMostRows == 32 && a.rows > 2048 ? 32 : 16;
+    const int panel_wgs = (int)((a.rows + panel_rows - 1) / panel_rows);
     // rows of a task: enough tasks to fill the units evenly (tasks that end early leave their unit to the others), as few
     // copies of U as that allows
     constexpr int kLeast = kItemRows * kWaves, kTasks = 2048;
@@ -623,7 +647,9 @@ void launch_step(float *W, const float *U, const float *Tprev, float *Tcur, cons
     while (chunk_rows > kLeast && (a.rows + chunk_rows - 1) / chunk_rows * col_tiles < kTasks) chunk_rows /= 2;
     const int chunks = (int)((a.rows + chunk_rows - 1) / chunk_rows);
     const bool late = a.rows <= 2048;              // (1024 x 4096 756 to 714 us, 2048 x 4096 869 to 830; 4096 x 4096 1090 either way)
-    auto kernel = a.ls ? &correct_step_kernel<D, true> : &correct_step_kernel<D, false>;
+    constexpr int kMost = split<D>::kMostRows;
+    auto kernel = panel_rows == 16 ? (a.ls ? &correct_step_kernel<D, true, 16> : &correct_step_kernel<D, false, 16>)
+                                   : (a.ls ? &correct_step_kernel<D, true, kMost> : &correct_step_kernel<D, false, kMost>);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(panel_wgs + chunks * col_tiles)), dim3(kThreads), 0, s,
                        W, U, Tprev, Tcur, a, p0, width, panel_wgs, chunks, (int)chunk_rows, late);
 }
