@@ -19,7 +19,7 @@ SOURCES = ["pvq_host.cpp", "pvq_fast8_tables.cpp", "pvq_kernels.hip", "pvq_fast8
            "pvq_encode8.hip", "pvq_size_table.hip", "pvq_hadamard.hip", "pvq_wide.hip", "pvq_correct.hip", "pvq_walk.hip"]
 
 HEADERS = ["pvq_internal.h", "pvq_fast8.h", "pvq_hadamard_dev.h", "pvq_quantize_dev.h", "pvq_diagnostics.h", "pvq_small_table.h",
-           "pvq_walk.h"]
+           "pvq_walk.h", "pvq_exact_dev.h"]
 
 # -ffp-contract=off: the encoder's float32 results are part of the format (no fused multiply-adds
 # unless written as fmaf); correctly rounded float32 division and square root likewise.

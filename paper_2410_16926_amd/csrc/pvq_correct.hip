@@ -38,9 +38,12 @@
 #include <mutex>
 #include <type_traits>
 
+#include "pvq_exact_dev.h"
 #include "pvq_internal.h"
 
 namespace {
+
+using namespace pvq_exact_dev;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -106,31 +109,12 @@ __device__ inline float lanes_sum(float v)
     return v;
 }
 
-// A divisor b with its reciprocal y = RN(1 / b) and what that is off by, yl = y (1 - b y): with them a / b, correctly rounded,
-// takes four instructions instead of the ten that serve every argument.  The first quotient a y + a yl is the exact one to a
-// few parts in 2^48, so rounded it is one of the two floats next to it; then a - q b is exact, and q + (a - q b) y rounds
-// to RN(a / b) (Markstein, Computation of elementary functions on the IBM RISC System/6000, 1990).  For b from 2^-20 to 2^20 and quotients from
-// 2^-70 to 2^70, where nothing over- or underflows; other b get y = NaN, which every quotient then is.
-struct divisor { float b, y, yl; };
-__device__ inline divisor make_divisor(float b)
+// A column's divisor: for diagonals from 2^-20 to 2^20 and quotients from 2^-70 to 2^70; others get y = NaN, which every quotient then is.
+__device__ inline divisor column_divisor(float b)
 {
-    divisor d;
-    d.b = b;
-    const float r = 1.0f / b;
-    d.y = fabsf(b) >= 0x1p-20f && fabsf(b) <= 0x1p20f ? r : __builtin_nanf("");
-    d.yl = __builtin_fmaf(-b, r, 1.0f) * r;
+    divisor d = divisor_of(b, reciprocal(b));
+    if (!magnitude_in(b, 0x1p-20f, 0x1p20f)) d.y = __builtin_nanf("");
     return d;
-}
-__device__ inline float divide(float a, const divisor &d)
-{
-    const float q = __builtin_fmaf(a, d.y, a * d.yl);
-    return __builtin_fmaf(__builtin_fmaf(-q, d.b, a), d.y, q);
-}
-// lo <= |x| < hi
-__device__ inline bool magnitude_in(float x, float lo, float hi)
-{
-    const uint32_t l = 2u * __float_as_uint(lo), h = 2u * __float_as_uint(hi);
-    return 2u * __float_as_uint(x) - l < h - l;
 }
 
 // v of the lane j ^ X of the row
@@ -178,8 +162,7 @@ __device__ inline void mark_behind(const int (&key)[C], const int (&th)[C][4], u
 // same sums in the same order, the coordinates that hold the first places in the order of deviations found by comparing all
 // of them.  ss: the sum of squares, y: the signed point (zeros of either sign).
 //   PLAIN: for groups whose ss lies between 2^-90 and 2^90, which have a direction and whose norms are far from either end of the
-// type: K / l1 is the first quotient K RN'(1 / l1) and one correction, with v_rcp_f32's reciprocal, which is the correctly rounded
-// one for every K up to 255 and every significand of l1 (all of them compared with the division).
+// type.
 template <int D, bool PLAIN>
 __device__ inline void quantize_lanes(const float (&w)[split<D>::C], int j, int K, float &ss, float (&y)[split<D>::C])
 {
@@ -191,8 +174,7 @@ __device__ inline void quantize_lanes(const float (&w)[split<D>::C], int j, int 
     float g;
     bool degenerate = false;
     if constexpr (PLAIN) {
-        const float r = __builtin_amdgcn_rcpf(l1), q = Kf * r;
-        g = __builtin_fmaf(__builtin_fmaf(-q, l1, Kf), r, q);
+        g = small_over(Kf, l1);
     } else {
         g = Kf / l1;
         degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
@@ -276,22 +258,8 @@ __device__ inline bool solve_group(const float (&w)[split<D>::C], const float (&
     sq = lanes_sum<L>(sq);
     float gain;
     if constexpr (PLAIN) {
-        // Root of x: g = x y with v_rsq_f32's y and one step of Newton's, the correctly rounded one for every float from 2^-100 to
-        // 2^100 (all of them compared with sqrtf); the reciprocal of an integer's root from the same y and one step, correctly
-        // rounded for all integers up to 2^16 (likewise).
-        auto root_of = [](float x, float y0) {
-            const float g0 = x * y0, h = 0.5f * y0;
-            return __builtin_fmaf(__builtin_fmaf(-g0, g0, x), h, g0);
-        };
-        const float y0 = __builtin_amdgcn_rsqf(sq);
-        divisor r;
-        r.b = root_of(sq, y0);
-        r.y = __builtin_fmaf(__builtin_fmaf(-r.b, y0, 1.0f), y0, y0);
-        r.yl = __builtin_fmaf(-r.b, r.y, 1.0f) * r.y;
-        float s;
-        if constexpr (LS) s = divide(lanes_sum<L>(dot), r);
-        else s = root_of(ss, __builtin_amdgcn_rsqf(ss));
-        gain = divide(s, r);
+        const divisor root = root_divisor(sq);
+        gain = divide(LS ? divide(lanes_sum<L>(dot), root) : root_of(ss), root);
     } else {
         const float root = sqrtf(sq);
         gain = (LS ? lanes_sum<L>(dot) / root : sqrtf(ss)) / root;
@@ -377,7 +345,7 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     static_assert(ROWS * S::kXPitch <= S::kDivisors, "divisors lie behind the transposition");
     auto store_divisors = [&]() {
         if ((int)threadIdx.x < width) {
-            const divisor d = make_divisor(diagonal);
+            const divisor d = column_divisor(diagonal);
             *reinterpret_cast<float4 *>(divisors + 4 * threadIdx.x) = make_float4(d.b, d.y, d.yl, 0.0f);
         }
     };

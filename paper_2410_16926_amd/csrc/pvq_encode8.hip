@@ -5,8 +5,8 @@
 //   * one lane per group, workgroups of 256 lanes that take whole rows, 256 groups at a time, as many workgroups as
 //     the machine holds at once; the next tile's weights are on their way while one is worked on;
 //   * the pulse-count repair (Sec. 2.5) adjusts the coordinates that hold the |sum - K| first places in the
-//     order of deviations, found in one short round per place (adjust_first_places8).  This equals the
-//     one-at-a-time repair because no coordinate is ever adjusted twice (for finite input the
+//     order of deviations, which a network of three-operand minima, medians and maxima finds (adjust_first_places8).  This
+//     equals the one-at-a-time repair because no coordinate is ever adjusted twice (for finite input the
 //     |sum - K| largest deviations are all positive, an adjusted coordinate drops below -1/2);
 //   * the index (App. B.2) is a sum of seven table entries, one per coordinate, from a table of per-coordinate offsets
 //     indexed by (coordinate, pulses left, signed value), whose addresses come out of one multiply-add each
@@ -16,13 +16,13 @@
 //   * the row normaliser's pairwise sum is a wave butterfly followed by a small tree over wave sums
 //     (adding +0.0 for absent groups is exact, so padding a row to a power of two does not change
 //     the pair-level sum);
-//   * an amplitude code takes one 16-byte read for two of its bits (pvq_quantize_dev::count_edges).
-// Of the vector instructions additions (float32, 32-bit integers), multiplications, float32 multiply-adds and exclusive ors
-// issue in 2.6 cycles a wave (8 waves a SIMD), comparisons, shifts, minima and maxima, conversions, byte permutations and
-// lane moves in 4.3 to 4.8, v_rcp in 8.9: where there is a choice the forms are of the first kind.  28672 x 8192 bf16
-// weights, 2-bit codes: 242 vector instructions a group, 187 us (launches in a row; 188 to 196 in the benchmark's step); with
-// integer addresses, a multiplication by the number of pulses for each, marks of all rounds as masks and a bisection for
-// the code 284 and 211.  14336 x 4096, 8-bit codes: 57 us, before 81.
+//   * an amplitude code takes one 16-byte read for two of its bits, and a lane makes those of up to four groups (write_codes).
+// Bound by instructions, whichever unit they go to: 8 waves a SIMD issue one in about 2.7 clocks.  (Alone, with 8 waves a SIMD,
+// additions, multiplications, float32 multiply-adds and exclusive ors take 2.6 clocks a wave, comparisons, shifts, minima and
+// maxima, conversions, byte permutations and lane moves 4.3 to 4.8, v_rcp 8.9.)  28672 x 8192 bf16 weights, 2-bit codes: 234 vector,
+// 46 scalar and 10 LDS instructions a group, 152 us (launches in a row); with the places of the repair marked by masks on the
+// scalar unit, a code a lane and general quotients 242, 129 and 11, 185 us; with integer addresses, marks of all rounds as masks
+// and a bisection for the code 284 vector ones and 211 us.  14336 x 4096, 8-bit codes: 45 us, before 55 and 81.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -100,8 +100,9 @@ template <> struct raw8<uint16_t> {
 
 // One group: returns its 24-bit index, the sum of squares, and the signed point in y (float, zeros of either sign).
 // table: LDS address of offs[0][0][0].  POINT: y of a group without a direction is set too (else its y is unspecified).
+// ordinary: whether all groups of the wave have an ordinary norm.
 template <bool POINT>
-__device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t table, float &ss_out, bool &degenerate, float (&y)[D])
+__device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t table, float &ss_out, bool &ordinary, bool &degenerate, float (&y)[D])
 {
     float tmp[D];
 #pragma unroll
@@ -111,15 +112,12 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
     for (int i = 0; i < D; i++) tmp[i] = w[i] * w[i];
     ss_out = tree8(tmp);
 
-    float g = K / l1, pulses = K;
-    float t[D], mag[D];
+    const float g = over_norm(K, l1, ordinary, degenerate);
+    float t[D], mag[D], pulses = K;
 #pragma unroll
     for (int i = 0; i < D; i++) t[i] = w[i] * g;
-    // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite.  Zeros then, whose index comes out as
-    // that of (0, ..., 0, K): 0.  (Looked at closely only in waves with a norm that is not an ordinary one.)
-    degenerate = false;
-    if (__any(!ordinary_norm<kMaxK>(l1))) {
-        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+    // a group without a direction gets zeros, whose index comes out as that of (0, ..., 0, K): 0
+    if (!ordinary) {
         pulses = degenerate ? 0.0f : K;
 #pragma unroll
         for (int i = 0; i < D; i++) t[i] = degenerate ? 0.0f : t[i];
@@ -131,11 +129,11 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
     // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
     const float m = pulses - tree8(S);
     const float unit = m < 0.0f ? -1.0f : 1.0f;
-    // deviations, how far below its projected value (negated where pulses have to go), as integers: those that are looked for
-    // are positive, and positive floats order like their bits
-    int key[D];
+    // places in the order of deviations: how far a magnitude is below its projected value (above it where pulses have to go)
+    const float order = m < 0.0f ? -order_scale<3>() : order_scale<3>();
+    uint32_t key[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) key[i] = __float_as_int((fabsf(t[i]) - mag[i]) * unit);
+    for (int i = 0; i < D; i++) key[i] = order_of<3>(fabsf(t[i]) - mag[i], order, i);
     adjust_first_places8(key, fabsf(m), unit, mag);
     // (-0.0 never carries a pulse: a coordinate whose projection is zero is not among the ones raised)
 #pragma unroll
@@ -161,7 +159,7 @@ __device__ inline uint32_t encode_group8(const float (&w)[D], float K, uint32_t 
 
 // Least-squares amplitude (Sec. 3.3 Step 4) for the point in y: (y . w) / ||y||_2, products rounded one by one and summed over
 // adjacent pairs, level by level.
-__device__ inline float ls_amplitude8(const float (&w)[D], const float (&y)[D], bool degenerate)
+__device__ inline float ls_amplitude8(const float (&w)[D], const float (&y)[D], bool ordinary, bool degenerate)
 {
     float p[D], n[D];
 #pragma unroll
@@ -169,12 +167,12 @@ __device__ inline float ls_amplitude8(const float (&w)[D], const float (&y)[D], 
         p[i] = y[i] * w[i];
         n[i] = y[i] * y[i];                   // small integers
     }
-    if (__any(degenerate)) {
+    if (!ordinary) {
         // zeros of the point are positive (the sign of a sum of zeros is theirs)
 #pragma unroll
         for (int i = 0; i < D - 1; i++) p[i] = degenerate ? 0.0f * w[i] : p[i];
     }
-    return tree8(p) / sqrtf(tree8(n));
+    return over_root(tree8(p), tree8(n), ordinary);
 }
 
 // four neighbouring 24-bit indices -> three dwords: lane j of a quad (j < 3) builds dword j from its own index and the
@@ -193,13 +191,13 @@ __device__ inline float row_sum(const float *wsum, int lane)
 }
 
 // LDS of both kernels, from byte 0: the offset table, the edges' tree, two rows' wave sums (used in turn, so that one
-// barrier a row is enough), the row's sums of squares (CODES; every lane reads its own).
+// barrier a row is enough), the row's sums of squares (CODES; every wave reads its own).
 struct enc8_lds {
     float4 *tree;
     float *wsum, *ss_row;
     uint32_t table;
 };
-template <bool CODES>
+template <int CODES>
 __device__ inline enc8_lds fill_lds(uint32_t *smem, const enc8_launch &f, int lanes)
 {
     enc8_lds l;
@@ -220,8 +218,9 @@ constexpr int kHeadWords = kTableWords + 4 * kEdgeNodes + 2 * 64;
 constexpr int kBlock = 256;
 constexpr int kMaxGroups = 4096;   // groups per row this kernel takes (their sums of squares sit in LDS)
 
+// CODES: 0 for float32 amplitudes, else the groups that a lane takes when it writes amplitude codes (write_codes).
 // LS: least-squares amplitudes (Sec. 3.3 Step 4) instead of norms.
-template <typename TIn, bool CODES, bool LS>
+template <typename TIn, int CODES, bool LS>
 __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_encode_args a)
 {
     extern __shared__ __align__(16) uint32_t smem[];
@@ -252,11 +251,11 @@ __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_e
             // the tile behind, or the next row's first (of the last row once more)
             const bool more = tix + 1 < tiles;
             next.load(source(more ? row : min(row + (int64_t)gridDim.x, a.rows - 1), more ? tix + 1 : 0));
-            bool degenerate;
-            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, degenerate, y);
+            bool ordinary, degenerate;
+            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, ordinary, degenerate, y);
             float amp;
-            if constexpr (LS) { amp = ls_amplitude8(w, y, degenerate); ss = amp * amp; }
-            else amp = sqrtf(ss);
+            if constexpr (LS) { amp = ls_amplitude8(w, y, ordinary, degenerate); ss = amp * amp; }
+            else amp = root_of_squares(ss, ordinary);
             if (a.pulses_out && in) {
                 if (degenerate) y[D - 1] = K;
                 uint32_t lo = 0, hi = 0;
@@ -283,7 +282,7 @@ __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_e
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, threadIdx.x, kBlock, lane);
+            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, kBlock / kWave, lane);
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
@@ -297,7 +296,7 @@ __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_e
 // pair levels, the quads that assemble index words and the code words come out the same).  The rotated
 // values are float32 (scaled by float32(1 / sqrt(block))), exactly those of the rotation kernel with a
 // float32 result.  LOG2N as in pvq_hadamard.hip: 9 for blocks of up to 512 values, 10 .. 13 for that block.
-template <typename TIn, bool CODES, bool LS, int LOG2N>
+template <typename TIn, int CODES, bool LS, int LOG2N>
 __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encode_args &a, int log2n,
                                            const uint8_t *signs, float scale)
 {
@@ -312,7 +311,7 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
     __syncthreads();
 
     const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int quad_pos = lane & 3;
     const int chunks = G / L;                                    // whole chunks: every lane has a group
     const int from = load_lane<LOG2N>(tid);                      // the 8 values of a chunk that the lane loads
@@ -341,11 +340,11 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             float w[D], y[D], ss;
 #pragma unroll
             for (int j = 0; j < D; j++) w[j] = v[j] * scale;
-            bool degenerate;
-            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, degenerate, y);
+            bool ordinary, degenerate;
+            const uint32_t c = encode_group8<LS>(w, K, l.table, ss, ordinary, degenerate, y);
             float amp;
-            if constexpr (LS) { amp = ls_amplitude8(w, y, degenerate); ss = amp * amp; }
-            else amp = sqrtf(ss);
+            if constexpr (LS) { amp = ls_amplitude8(w, y, ordinary, degenerate); ss = amp * amp; }
+            else amp = root_of_squares(ss, ordinary);
             if constexpr (CODES) l.ss_row[g] = ss;
             else reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
             const uint32_t word = index_word(c, quad_pos);
@@ -359,23 +358,23 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, tid, L, lane);
+            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, waves, lane);
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
 }
 
 // Registers for eight waves a SIMD (64 a lane): with them two workgroups of 1024 lanes, which blocks of 8192 values need, share
-// a unit.  28672 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 264 / 306 / 317 / 388 us (pvq_hadamard to
-// float32 and pvq_encode: 494 / 503 / 515 / 495).
-template <typename TIn, bool CODES, bool LS, int LOG2N>
+// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 65 / 79 / 85 / 99 us (with the encoder before 73 / 84 /
+// 90 / 110).
+template <typename TIn, int CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)
 {
     rotate_encode8_body<TIn, CODES, LS, LOG2N>(f, a, log2n, signs, scale);
 }
 
-template <typename TIn, bool CODES, bool LS>
+template <typename TIn, int CODES, bool LS>
 __global__ __launch_bounds__(1024, 8) void rotate_encode8_kernel_8192(enc8_launch f, pvq_encode_args a, int log2n,
                                                                       const uint8_t *signs, float scale)
 {
@@ -432,13 +431,16 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     case 10: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 10>)); break;         \
     default: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 9>)); break;          \
     }
-    if (dtype == PVQ_F32) {
-        if (codes) { if (ls) PVQ_RE8_N(float, true, true) else PVQ_RE8_N(float, true, false) }
-        else { if (ls) PVQ_RE8_N(float, false, true) else PVQ_RE8_N(float, false, false) }
-    } else {
-        if (codes) { if (ls) PVQ_RE8_N(uint16_t, true, true) else PVQ_RE8_N(uint16_t, true, false) }
-        else { if (ls) PVQ_RE8_N(uint16_t, false, true) else PVQ_RE8_N(uint16_t, false, false) }
-    }
+    // (rows of one chunk have one run of 64 groups a wave)
+#define PVQ_RE8_C(T, LS_)                                                           \
+    do {                                                                            \
+        if (!codes) PVQ_RE8_N(T, 0, LS_)                                            \
+        else if (a.groups == L) PVQ_RE8_N(T, 1, LS_)                                \
+        else PVQ_RE8_N(T, 4, LS_)                                                   \
+    } while (0)
+    if (dtype == PVQ_F32) { if (ls) PVQ_RE8_C(float, true); else PVQ_RE8_C(float, false); }
+    else { if (ls) PVQ_RE8_C(uint16_t, true); else PVQ_RE8_C(uint16_t, false); }
+#undef PVQ_RE8_C
 #undef PVQ_RE8_N
 #undef PVQ_RE8_LAUNCH
     return hipGetLastError();
@@ -460,13 +462,17 @@ hipError_t pvq_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a, int dt
     const unsigned grid = resident_grid(a.rows, kBlock, lds);
 #define PVQ_ENC8_CASE(T, C, L) hipLaunchKernelGGL((encode8_kernel<T, C, L>), dim3(grid), dim3(block), lds, s, f, a)
     const bool ls = a.ls_amplitude != 0;
-    if (dtype == PVQ_F32) {
-        if (codes) { if (ls) PVQ_ENC8_CASE(float, true, true); else PVQ_ENC8_CASE(float, true, false); }
-        else { if (ls) PVQ_ENC8_CASE(float, false, true); else PVQ_ENC8_CASE(float, false, false); }
-    } else {
-        if (codes) { if (ls) PVQ_ENC8_CASE(uint16_t, true, true); else PVQ_ENC8_CASE(uint16_t, true, false); }
-        else { if (ls) PVQ_ENC8_CASE(uint16_t, false, true); else PVQ_ENC8_CASE(uint16_t, false, false); }
-    }
+    // (runs of 64 groups that a wave has in a row: one, two, or more)
+#define PVQ_ENC8_CODES(T, L)                                                        \
+    do {                                                                            \
+        if (!codes) PVQ_ENC8_CASE(T, 0, L);                                         \
+        else if (a.groups <= kBlock) PVQ_ENC8_CASE(T, 1, L);                        \
+        else if (a.groups <= 2 * kBlock) PVQ_ENC8_CASE(T, 2, L);                    \
+        else PVQ_ENC8_CASE(T, 4, L);                                                \
+    } while (0)
+    if (dtype == PVQ_F32) { if (ls) PVQ_ENC8_CODES(float, true); else PVQ_ENC8_CODES(float, false); }
+    else { if (ls) PVQ_ENC8_CODES(uint16_t, true); else PVQ_ENC8_CODES(uint16_t, false); }
+#undef PVQ_ENC8_CODES
 #undef PVQ_ENC8_CASE
     return hipGetLastError();
 }

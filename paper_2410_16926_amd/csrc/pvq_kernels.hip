@@ -11,10 +11,11 @@
 //     multiply-add from the coordinate before and the coordinate an offset in the instruction.
 //   * A wave assembles its 64 indices, 2 b whole words, in words of its own in LDS with ds_or and writes them out.
 //   * The row's sum and the amplitude codes are the ones of the encoder for groups of 8 (pvq_quantize_dev.h).
-// Bound by vector instructions, 505 a group of 16 (16-bit weights, float32 amplitudes).  Launches in a row: 8192 x 8192 of
-// 16-bit weights, 2-bit codes, groups of 16, 48-bit indices: 61 us; groups of 32, 96 bits: 84 us; 3001 x 11008 float32
-// weights, least-squares amplitudes in 4-bit codes, groups of 16, 52 bits: 39 us (43 with the call's allocations); 7001 x 1000
-// in groups of 8: 13.5 us.  Before, with a workgroup per row that copied the size table, four reads of it per coordinate, a
+// Bound by instructions, vector and scalar alike: 435 and 97 a group of 16 (16-bit weights, 48 bits, float32 amplitudes).
+// Launches in a row: 8192 x 8192 of 16-bit weights, 2-bit codes, groups of 16, 48-bit indices: 52 us; groups of 32, 96 bits: 70 us;
+// 3001 x 11008 float32 weights, least-squares amplitudes in 4-bit codes, groups of 16, 52 bits: 32 us; 7001 x 1000
+// in groups of 8: 11.7 us.  Before, with the places of the repair marked by masks on the scalar unit (513 and 189): 60, 82, 38, 12.5; with a
+// workgroup per row that copied the size table, four reads of it per coordinate, a
 // bisection for the code and words assembled by a whole workgroup between barriers: 101, 148, 63, 26.
 #include <hip/hip_runtime.h>
 
@@ -44,7 +45,7 @@ struct encode_launch {
 };
 
 // LDS, from byte 0: thresholds [2K+2][D-1] of W words, the edges' tree, each wave's words of an index tile, and per team
-// two rows' wave sums (used in turn, so that one barrier a row is enough) and the row's sums of squares (every lane reads its own)
+// two rows' wave sums (used in turn, so that one barrier a row is enough) and the row's sums of squares (every wave reads its own)
 struct encode_lds {
     uint32_t tree, stage, stage_words, sums, sum_words, rows, row_words, total;      // starts and total in bytes
 };
@@ -58,8 +59,8 @@ __host__ __device__ inline encode_lds lds_of(int D, int W, const encode_launch &
     l.stage_words = 2 * f.index_bits + W;
     l.sums = l.stage + (uint32_t)(lanes / kWave) * l.stage_words * 4;
     l.sum_words = codes ? (uint32_t)(G + kWave * kWave - 1) / (kWave * kWave) * kWave : 0;
-    l.rows = l.sums + 2 * teams * l.sum_words * 4;
-    l.row_words = codes ? (uint32_t)G : 0;
+    l.rows = (l.sums + 2 * teams * l.sum_words * 4 + 15) / 16 * 16;
+    l.row_words = codes ? (uint32_t)(G + 3) / 4 * 4 : 0;
     l.total = l.rows + teams * l.row_words * 4;
     return l;
 }
@@ -68,8 +69,8 @@ __host__ __device__ inline encode_lds lds_of(int D, int W, const encode_launch &
 // encode
 // ---------------------------------------------------------------------------------------------
 
-// Waves that a SIMD's registers are divided among (groups of 16, 3001 x 11008: 39 us, with 4 43, with 6, which spill, 49;
-// groups of 32, 8192 x 8192, 2-bit codes: 84 us, with 3 118, with 5, which spill, 130)
+// Waves that a SIMD's registers are divided among (with the repair before: groups of 16, 3001 x 11008: 39 us, with 4 43, with 6, which
+// spill, 49; groups of 32, 8192 x 8192, 2-bit codes: 84 us, with 3 118, with 5, which spill, 130)
 constexpr int waves_per_simd(int D) { return D == 8 ? 7 : D == 16 ? 5 : 4; }
 
 // A group as it comes from memory
@@ -102,7 +103,7 @@ template <int D, typename TIn> struct raw_group {
 // The point of Sec. 2.5: |w| K / ||w||_1, rounded, and pulses moved at the largest deviations.  Signed point in y (zeros of
 // either sign); a group without a direction gets zeros (its point is (0, ..., 0, K)).
 template <int D>
-__device__ inline void project_group(const float (&w)[D], float K, float &ss_out, bool &degenerate, float (&y)[D])
+__device__ inline void project_group(const float (&w)[D], float K, float &ss_out, bool &ordinary, bool &degenerate, float (&y)[D])
 {
     float tmp[D];
 #pragma unroll
@@ -116,10 +117,9 @@ __device__ inline void project_group(const float (&w)[D], float K, float &ss_out
     float t[D], pulses = K;
 #pragma unroll
     for (int i = 0; i < D; i++) t[i] = w[i] * g;
-    // no direction: all zeros, a norm whose reciprocal overflows, or anything not finite  (looked at closely only in waves
-    // with a norm that is not an ordinary one)
     degenerate = false;
-    if (__any(!ordinary_norm<kMaxK>(l1))) {
+    ordinary = __all(ordinary_norm(l1));
+    if (!ordinary) {
         degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
         pulses = degenerate ? 0.0f : K;
 #pragma unroll
@@ -130,11 +130,12 @@ __device__ inline void project_group(const float (&w)[D], float K, float &ss_out
     // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
     const float m = pulses - tree_sum<D>(tmp);
     const float unit = m < 0.0f ? -1.0f : 1.0f;
-    // deviations (negated where pulses have to go), as integers: those that are looked for are positive, and positive
-    // floats order like their bits
-    int key[D];
+    // places in the order of deviations (negated where pulses have to go)
+    constexpr int kLog2D = D == 8 ? 3 : D == 16 ? 4 : 5;
+    const float order = m < 0.0f ? -order_scale<kLog2D>() : order_scale<kLog2D>();
+    uint32_t key[D];
 #pragma unroll
-    for (int i = 0; i < D; i++) key[i] = __float_as_int((fabsf(t[i]) - fabsf(y[i])) * unit);
+    for (int i = 0; i < D; i++) key[i] = order_of<kLog2D>(fabsf(t[i]) - fabsf(y[i]), order, i);
     adjust_first_places<D>(key, fabsf(m), unit, y);
 }
 
@@ -161,7 +162,7 @@ __device__ inline typename wide<W>::type rank_point(const float (&y)[D], bool de
 // Least-squares amplitude (Sec. 3.3 Step 4) for the point y: (y . w) / ||y||_2, products rounded one by one and summed over
 // adjacent pairs, level by level.
 template <int D>
-__device__ inline float ls_amplitude(const float (&w)[D], const float (&y)[D], bool degenerate, float K)
+__device__ inline float ls_amplitude(const float (&w)[D], const float (&y)[D], bool ordinary, bool degenerate, float K)
 {
     float p[D], n[D];
 #pragma unroll
@@ -169,13 +170,13 @@ __device__ inline float ls_amplitude(const float (&w)[D], const float (&y)[D], b
         p[i] = y[i] * w[i];
         n[i] = y[i] * y[i];                   // small integers
     }
-    if (__any(degenerate)) {
+    if (!ordinary) {
         // zeros of the point are positive (the sign of a sum of zeros is theirs)
 #pragma unroll
         for (int i = 0; i < D; i++) p[i] = degenerate ? (i < D - 1 ? 0.0f : K) * w[i] : p[i];
         n[D - 1] = degenerate ? K * K : n[D - 1];
     }
-    return tree_sum<D>(p) / sqrtf(tree_sum<D>(n));
+    return over_root(tree_sum<D>(p), tree_sum<D>(n), ordinary);
 }
 
 // OR a `bits`-wide value into a wave's words at bit 32 * (word of `at`) + sh (one word behind it too, with nothing)
@@ -259,15 +260,15 @@ __global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(en
                 const bool more = t + waves < tiles;
                 next.load(group_at(more ? row : min(row + step, a.rows - 1), more ? t + waves : first));
             }
-            bool degenerate;
-            project_group<D>(w, K, ss, degenerate, y);
+            bool ordinary, degenerate;
+            project_group<D>(w, K, ss, ordinary, degenerate, y);
             const T c = rank_point<D, W>(y, degenerate, K, table, last);
             stage_field<W>(at, sh, in ? c : 0);
             // the amplitude: the norm, or the least-squares one, whose square then stands for
             // the sum of squares in the codes (Sec. 3.3 Steps 4 and 5)
             float amp;
-            if constexpr (LS) { amp = ls_amplitude<D>(w, y, degenerate, K); ss = amp * amp; }
-            else amp = sqrtf(ss);
+            if constexpr (LS) { amp = ls_amplitude<D>(w, y, ordinary, degenerate, K); ss = amp * amp; }
+            else amp = root_of_squares(ss, ordinary);
             if (in) {
                 if (sb > 0) ss_row[g] = ss;
                 else reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
@@ -315,8 +316,8 @@ __global__ __launch_bounds__(kMaxLanes, waves_per_simd(D)) void encode_kernel(en
                 }
                 const float rowss = (part[0] + part[1]) + (part[2] + part[3]);
                 if (first == 0 && lane == 0) a.rownorm_out[row] = rowss;
-                write_codes(sb, ss_row, rowss, tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G,
-                            first * kWave + lane, f.team, lane);
+                write_codes<1>(sb, ss_row, rowss, tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G,
+                            first, waves, lane);
             }
             turn = l.sum_words - turn;
         }

@@ -7,26 +7,36 @@
 
 #include <hip/hip_runtime.h>
 
+#include "pvq_exact_dev.h"
+
 namespace pvq_quantize_dev {
 
-// Whether a group's norm l1 is one that all groups but tiny and huge ones have: finite, not zero, and with K / l1 finite for
-// every K up to MAX_K.  What is not has to be looked at closely, and what is has a direction.  From a power of two 2^(f - 127)
-// on, f the exponent's field, K / l1 <= MAX_K 2^(127 - f), which is finite if MAX_K < 2^(f + 1).  (K / l1 overflows up to
-// l1 = K 2^-128, which is 2^-124 for K = 16: above the smallest normal float.)  Up to 2^127, so that infinities and NaN,
-// whose bits lie above, are not among them.
-__device__ constexpr uint32_t ordinary_norm_from(int max_k)
+using namespace pvq_exact_dev;
+
+// Whether a group's norm l1 is one that all groups but tiny and huge ones have: between 2^-36 and 2^46, so that K / l1 is finite and
+// the group has a direction, and the short quotients and roots are right for it: the sum of squares of up to 32 values lies between
+// 2^-77 and 2^92, and the square of (y . w) / ||y|| not below 2^-96 (the largest value holds a pulse, K <= 127).  What is not has to
+// be looked at closely.
+__device__ inline bool ordinary_norm(float l1) { return magnitude_in(l1, 0x1p-36f, 0x1p46f); }
+
+// K / l1; ordinary: whether all groups of the wave are.  degenerate: no direction, which are all zeros, norms whose reciprocal
+// overflows, and anything not finite.
+__device__ inline float over_norm(float K, float l1, bool &ordinary, bool &degenerate)
 {
-    uint32_t f = 1;
-    while (max_k >> (f + 1)) f++;
-    return f << 23;
+    float g = small_over(K, l1);
+    degenerate = false;
+    ordinary = __all(ordinary_norm(l1));
+    if (!ordinary) {
+        g = K / l1;
+        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(g < INFINITY);
+    }
+    return g;
 }
-template <int MAX_K>
-__device__ inline bool ordinary_norm(float l1)
-{
-    constexpr uint32_t from = ordinary_norm_from(MAX_K), to = 0x7F000000u;
-    static_assert(MAX_K / __builtin_bit_cast(float, from) <= __FLT_MAX__, "K over the smallest ordinary norm is finite");
-    return __float_as_uint(l1) - from < to - from;
-}
+
+// The amplitudes, ordinary being whether all groups of the wave are (ordinary_norm): the root of a sum of squares, and a sum of
+// products over the root of an integer.
+__device__ inline float root_of_squares(float ss, bool ordinary) { return ordinary ? root_of(ss) : sqrtf(ss); }
+__device__ inline float over_root(float dot, float n, bool ordinary) { return ordinary ? divide(dot, root_divisor(n)) : dot / sqrtf(n); }
 
 // Sum over adjacent pairs, level by level: ((v0+v1)+(v2+v3))+...  (fixed order, float32).
 template <int D>
@@ -39,68 +49,78 @@ __device__ inline float tree_sum(float (&v)[D])
     return v[0];
 }
 
-// The repair of Sec. 2.5 for groups of 8: mag[i] += unit for the coordinates that hold the `need` first places in the order
-// of keys (largest first, lower coordinate first on ties; the bits of floats, of which the first `need` are positive).  A
-// round takes the largest key left (three-operand maxima), marks the first coordinate that has it and takes its key out; a
-// wave runs as many rounds as its lane with the largest `need`, two or three for groups of 8 (counting every coordinate's
-// place with 28 comparisons takes a hundred instructions).  The first two rounds keep their marks as masks (scalar registers;
-// those of more rounds do not fit there).  Changes key.
-__device__ inline void adjust_first_places8(int (&key)[8], float need, float unit, float (&mag)[8])
+// Three-operand orders of unsigned integers.
+__device__ inline uint32_t max3(uint32_t a, uint32_t b, uint32_t c) { return max(max(a, b), c); }
+__device__ inline uint32_t min3(uint32_t a, uint32_t b, uint32_t c) { return min(min(a, b), c); }
+__device__ inline uint32_t med3(uint32_t a, uint32_t b, uint32_t c)
 {
-    bool adj[8];
-#pragma unroll
-    for (int i = 0; i < 8; i++) adj[i] = false;
-    auto mark = [&](bool open) {                  // (a lane that needs no more takes nothing)
-        const int best = max(max(max(max(key[0], key[1]), key[2]), max(max(key[3], key[4]), key[5])), max(key[6], key[7]));
-        bool taken = !open;
-#pragma unroll
-        for (int i = 0; i < 8; i++) {
-            const bool equal = key[i] == best;
-            adj[i] = adj[i] || (equal && !taken);
-            taken = taken || equal;
-        }
-    };
-    mark(need > 0.0f);
-    if (__any(need > 1.0f)) {
-#pragma unroll
-        for (int i = 0; i < 8; i++) key[i] = adj[i] ? INT32_MIN : key[i];
-        mark(need > 1.0f);
-    }
-#pragma unroll
-    for (int i = 0; i < 8; i++) mag[i] += adj[i] ? unit : 0.0f;
-    if (__any(need > 2.0f)) {
-#pragma unroll 1
-        for (float round = 2.0f; round < 8.0f && __any(need > round); round += 1.0f) {
-#pragma unroll
-            for (int i = 0; i < 8; i++) { key[i] = adj[i] ? INT32_MIN : key[i]; adj[i] = false; }
-            mark(need > round);
-#pragma unroll
-            for (int i = 0; i < 8; i++) mag[i] += adj[i] ? unit : 0.0f;
-        }
-    }
+    uint32_t r;
+    asm("v_med3_u32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+    return r;
 }
 
-// The same repair for any D and signed points (whose zeros have their sign too), in one loop for all rounds: a place that is taken gets the key -1 (below every positive float,
-// and the bits of no deviation), which shows at the end where a pulse moved.  A wave runs as many rounds as its lane with the
-// largest `need`, about three for D = 16 and five for D = 32.
-template <int D>
-__device__ inline void adjust_first_places(int (&key)[D], float need, float unit, float (&y)[D])
+// A coordinate's place in the order of deviations as one integer, larger for earlier places: the deviation's bits, scaled down so
+// that LOG2D bits are free behind them, and there the coordinate, lower ones first, so that no two places are the same.  The
+// scaled bits are the deviation's own from 2^-7 on, which is all that the first `need` places and the one behind them need:
+// deviations are at most 1/2 and add up to `need` (to a few parts in 2^20), so the D - need behind the first ones still add up to
+// need / 2, and the largest of them is above 1 / 64 for D <= 32.  Smaller ones may come out as equal, and negative ones are zero.
+// unit: the sign of the deviations looked for, times order_scale.
+template <int LOG2D> __device__ constexpr float order_scale() { return __builtin_bit_cast(float, 1u << (31 - LOG2D)); }
+template <int LOG2D>
+__device__ inline uint32_t order_of(float deviation, float unit, int i)
 {
-#pragma unroll 1
-    for (float round = 0.0f; round < (float)D && __any(need > round); round += 1.0f) {
-        int best = max(key[0], key[1]);
+    return (uint32_t)max(__float_as_int(deviation * unit), 0) << LOG2D | (uint32_t)((1 << LOG2D) - 1 - i);
+}
+
+// The repair of Sec. 2.5 for groups of 8: mag[i] += unit for the coordinates that hold the `need` first places (order_of), which
+// are those not behind the last of them.  The first three places come out of a network of 21 minima, medians and maxima; a fourth
+// (more there are not: eight deviations of at most 1/2 add up to `need`) is looked for in the waves that have such a group, one in seven.
+// A round per place, with equal deviations told apart by masks on the scalar unit, took a hundred vector and 75 scalar
+// instructions; this takes about 90 and six, and a scalar instruction's turn costs a SIMD as much as a vector one's.  28672 x 8192,
+// 2-bit codes: 242 vector and 129 scalar instructions a group, 184 us; now 234 and 46, 152 us.
+__device__ inline void adjust_first_places8(const uint32_t (&key)[8], float need, float unit, float (&mag)[8])
+{
+    const uint32_t a1 = max3(key[0], key[1], key[2]), b1 = med3(key[0], key[1], key[2]), c1 = min3(key[0], key[1], key[2]);
+    const uint32_t a2 = max3(key[3], key[4], key[5]), b2 = med3(key[3], key[4], key[5]), c2 = min3(key[3], key[4], key[5]);
+    const uint32_t a3 = max(key[6], key[7]), b3 = min(key[6], key[7]);
+    // the n-th of two ordered lists is the largest of the minima of places that add up to n
+    const uint32_t a = max(a1, a2), b = max3(min(a1, a2), b1, b2), c = max(max3(min(a1, b2), min(b1, a2), c1), c2);
+    uint32_t first = max(a, a3), second = max3(min(a, a3), b, b3), third = max3(min(a, b3), min(b, a3), c);
+    asm("" : "+v"(first), "+v"(second), "+v"(third));              // (all three at once: no branches)
+    uint32_t last = need > 0.0f ? first : ~0u;
+    last = need > 1.0f ? second : last;
+    last = need > 2.0f ? third : last;
+    if (__any(need > 3.0f)) {
+        uint32_t fourth = 0;
 #pragma unroll
-        for (int i = 2; i < D; i += 2) best = max(max(best, key[i]), key[i + 1]);
-        bool taken = !(need > round);             // (a lane that needs no more takes nothing)
-#pragma unroll
-        for (int i = 0; i < D; i++) {
-            const bool equal = key[i] == best;
-            key[i] = equal && !taken ? -1 : key[i];
-            taken = taken || equal;
-        }
+        for (int i = 0; i < 8; i++) fourth = max(fourth, key[i] < third ? key[i] : 0u);
+        last = need > 3.0f ? fourth : last;
     }
 #pragma unroll
-    for (int i = 0; i < D; i++) y[i] = copysignf(fabsf(y[i]) + (key[i] == -1 ? unit : 0.0f), y[i]);
+    for (int i = 0; i < 8; i++) mag[i] += key[i] >= last ? unit : 0.0f;
+}
+
+// The same repair for any D and signed points (whose zeros have their sign too).  The places come one after the other: with `last`
+// the place before, key - last as an unsigned number is largest for the first key behind it (keys not behind it stay below
+// 2^31), so a round is a subtraction for a coordinate and half a three-operand maximum, and needs no masks.  A wave runs as many
+// rounds as its lane with the largest `need`, about three for D = 16 and four for D = 32.  (Marks as masks, the key of a place that is
+// taken set to -1: 8192 x 8192, D = 16, 48 bits, float32 amplitudes 54.3 us, now 44.7; D = 32, 96 bits, 2-bit codes 82.4, now 69.8.)
+template <int D>
+__device__ inline void adjust_first_places(const uint32_t (&key)[D], float need, float unit, float (&y)[D])
+{
+    uint32_t last = max(key[0], key[1]);
+#pragma unroll
+    for (int i = 2; i < D; i += 2) last = max3(last, key[i], key[i + 1]);
+    last = need > 0.0f ? last : ~0u;
+#pragma unroll 1
+    for (float round = 1.0f; round < (float)D && __any(need > round); round += 1.0f) {
+        uint32_t behind = max(key[0] - last, key[1] - last);
+#pragma unroll
+        for (int i = 2; i < D; i += 2) behind = max3(behind, key[i] - last, key[i + 1] - last);
+        last = need > round ? last + behind : last;
+    }
+#pragma unroll
+    for (int i = 0; i < D; i++) y[i] = copysignf(fabsf(y[i]) + (key[i] >= last ? unit : 0.0f), y[i]);
 }
 
 // ---- sums and fields over the lanes of a wave ----------------------------------------------------------------------
@@ -128,7 +148,7 @@ __device__ inline float wave_pair_sum(float v)
     return v;
 }
 
-// OR of v over aligned runs of N lanes (N = 4, 8, 16, 32), in every lane of the run: the first four levels by lane
+// OR of v over aligned runs of N lanes (a power of two up to 32), in every lane of the run: the first four levels by lane
 // patterns inside a row of 16 lanes (within a quad; then, the quads being uniform, the mirror images inside 8 and 16
 // lanes bring the other half), the fifth across rows.
 template <int CTRL>
@@ -140,7 +160,7 @@ template <int N>
 __device__ inline uint32_t or_over_lanes(uint32_t v)
 {
     v = dpp_or<0xB1>(v);                              // quad_perm [1,0,3,2]
-    v = dpp_or<0x4E>(v);                              // quad_perm [2,3,0,1]
+    if constexpr (N > 2) v = dpp_or<0x4E>(v);         // quad_perm [2,3,0,1]
     if constexpr (N > 4) v = dpp_or<0x141>(v);        // row_half_mirror
     if constexpr (N > 8) v = dpp_or<0x140>(v);        // row_mirror
     if constexpr (N > 16) v |= __shfl_xor(v, 16, kWave);
@@ -177,26 +197,46 @@ __device__ inline uint32_t count_edges(const float4 *tree, float u)
     return v;
 }
 
-// The row's amplitude codes (Sec. 3.3 Step 5): code = number of quantile edges <= u, u = ss_g / rowss, packed 32/SB lanes to
-// a dword by an OR butterfly.  first, step: the lane's first group and the distance to its next.
-template <int SB>
-__device__ inline void write_codes(const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int step, int lane)
+// The row's amplitude codes (Sec. 3.3 Step 5): code = number of quantile edges <= u, u = ss_g / rowss.  The wave's groups are runs
+// of 64, number first, first + waves, ... of the row, and nobody else touches their sums of squares.  A lane takes N neighbouring
+// groups, of N runs at a time: the codes come together in the lane (with eight bits and N = 4 all of a word, else an OR over
+// 32 / (SB N) lanes), the waits fill each other, and the loop runs once for N of the wave's tiles.  N is chosen with the kernel: a
+// second form of this in the same kernel costs the loops around it registers.  (28672 x 8192 with 2-bit codes, four runs a wave: 163 us
+// with N = 1, 154 with 4, 160 with both forms.)
+template <int SB, int N>
+__device__ inline void write_codes(const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int waves, int lane)
 {
-    for (int g = first; g - lane < G; g += step) {
-        const float ss = g < G ? ss_row[g] : __builtin_nanf("");          // (no edge is reached: absent groups leave zeros)
-        const uint32_t code = count_edges<SB>(tree, ss / rowss);
-        const uint32_t word = or_over_lanes<32 / SB>(code << ((lane * SB) & 31));
-        if ((lane & (32 / SB - 1)) == 0 && g < G) srow[((uint32_t)g * SB) >> 5] = word;
+    constexpr int kLanes = 32 / (SB * N), kRunLanes = kWave / N;          // lanes of a word and of a run
+    for (int run = first; run * kWave < G; run += N * waves) {
+        const int g = (run + lane / kRunLanes * waves) * kWave + N * (lane % kRunLanes);
+        const float nan = __builtin_nanf("");                             // (no edge is reached: absent groups leave zeros)
+        float u[N];
+#pragma unroll
+        for (int i = 0; i < N; i++) u[i] = nan;
+        if (g < G) {
+            typedef float part __attribute__((ext_vector_type(N)));
+            const part v = *reinterpret_cast<const part *>(ss_row + g);
+#pragma unroll
+            for (int i = 0; i < N; i++) u[i] = g + i < G ? v[i] : nan;
+        }
+#pragma unroll
+        for (int i = 0; i < N; i++) u[i] = u[i] / rowss;
+        uint32_t word = 0;
+#pragma unroll
+        for (int i = 0; i < N; i++) word |= count_edges<SB>(tree, u[i]) << (SB * i);
+        if constexpr (kLanes > 1) word = or_over_lanes<kLanes>(word << (N * SB * (lane & (kLanes - 1))));
+        if ((lane & (kLanes - 1)) == 0 && g < G) srow[((uint32_t)g * SB) >> 5] = word;
     }
 }
 // (the width of a code is the same for all lanes; a branch per row, so that no loop keeps its conditions in registers)
-__device__ inline void write_codes(int sb, const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int step, int lane)
+template <int N>
+__device__ inline void write_codes(int sb, const float *ss_row, float rowss, const float4 *tree, uint32_t *srow, int G, int first, int waves, int lane)
 {
     switch (sb) {
-    case 1: write_codes<1>(ss_row, rowss, tree, srow, G, first, step, lane); break;
-    case 2: write_codes<2>(ss_row, rowss, tree, srow, G, first, step, lane); break;
-    case 4: write_codes<4>(ss_row, rowss, tree, srow, G, first, step, lane); break;
-    default: write_codes<8>(ss_row, rowss, tree, srow, G, first, step, lane); break;
+    case 1: write_codes<1, N>(ss_row, rowss, tree, srow, G, first, waves, lane); break;
+    case 2: write_codes<2, N>(ss_row, rowss, tree, srow, G, first, waves, lane); break;
+    case 4: write_codes<4, N>(ss_row, rowss, tree, srow, G, first, waves, lane); break;
+    default: write_codes<8, N>(ss_row, rowss, tree, srow, G, first, waves, lane); break;
     }
 }
 
