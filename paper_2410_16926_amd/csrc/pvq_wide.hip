@@ -25,6 +25,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "pvq_exact_dev.h"
 #include "pvq_hadamard_dev.h"
 #include "pvq_internal.h"
 
@@ -66,9 +67,10 @@ struct encode_wide_params {
 // CP*sub+CP-1, CP = D/16): the sums, the largest deviation, the prefix sum and the multi-word total need four cross-lane
 // levels, all of them permutations inside a row of 16 lanes after which every lane of the row holds the result, and a lane's
 // own coordinates (four or eight) are independent work in between.
-// Bound by vector instructions (1020 a wave at D = 128, K = 187, with the rotation in front) and the gathers of thresholds.
-// 2048 rows of 8192 rotated and encoded: 88 us, K = 84: 60 us; 2048 x 8192 encoded, D = 64, K = 96: 43 us.  With 90
-// instructions and not 30 per pulse that has to move, and a lane reading all of an entry's pieces: 101, 100, 64 us.  A wave
+// Bound by instructions (906 on the vector and 155 on the scalar unit a wave at D = 128, K = 187, with the rotation in front)
+// and the gathers of thresholds.  2048 rows of 8192 rotated and encoded: 83 us, K = 84: 58 us; 2048 x 8192 encoded, D = 64,
+// K = 96: 47 us.  With the places of the repair marked in every step, general division and root (1025 and 254 instructions):
+// 89, 64, 47 us; with 90 instructions a step besides, and a lane reading all of an entry's pieces: 101, 100, 64 us.  A wave
 // per group, the form of small batches before: 7.7 and 11 us for 32 and 4096 groups (D = 128, K = 187), this one 6.9 and 7.7.
 #define PVQ_ROW_STEPS(STEP) STEP(0xB1) STEP(0x4E) STEP(0x141) STEP(0x140)
 
@@ -96,8 +98,9 @@ __device__ inline float tree_sum(const float (&x)[CP])
 // One group of 16 * CP values held by 16 lanes (lane `sub` of the group: coordinates CP*sub .. CP*sub+CP-1):
 // the point, the amplitude, the index, and the index's words into the tile's bit stream in LDS at group
 // position gl.  `on` = false: the lanes go through the motions (every cross-lane step needs them) and
-// write nothing.  K and D = 16 * CP as in the context.
-template <int CP, int W>
+// write nothing.  K and D = 16 * CP as in the context.  DISTINCT: deviations are seldom equal (float32 values: bfloat16 ones
+// often have the same magnitude twice in a group).
+template <int CP, int W, bool DISTINCT>
 __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, int gl, int64_t row, int64_t g,
                                       const encode_wide_params &p, uint32_t *stream, int tile_words)
 {
@@ -111,10 +114,17 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
 #pragma unroll
     for (int j = 0; j < CP; j++) tmp[j] = w[j] * w[j];
     const float ss = row_sum_pairs(tree_sum<CP>(tmp));
-    const float gain = K / l1;
-    // no direction: the point is (0, ..., 0, +K), zeros here until the pulses have been moved
-    const bool degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(gain < INFINITY);
-    const bool any_degenerate = __any(degenerate);
+    // no direction: the point is (0, ..., 0, +K), zeros here until the pulses have been moved  (looked at, and the general
+    // division and root taken, only where a group's norm is not between 2^-40 and 2^46: between them its sum of squares lies
+    // between 2^-87 and 2^92.  bfloat16 sources: always, the two forms beside the steps below cost them 1 %)
+    const bool ordinary = DISTINCT && __all(pvq_exact_dev::magnitude_in(l1, 0x1p-40f, 0x1p46f));
+    float gain = pvq_exact_dev::integer_over(K, l1);
+    bool degenerate = false;
+    if (!ordinary) {
+        gain = K / l1;
+        degenerate = !(l1 > 0.0f) || !(l1 < INFINITY) || !(gain < INFINITY);
+    }
+    const bool any_degenerate = !ordinary && __any(degenerate);
 #pragma unroll
     for (int j = 0; j < CP; j++) t[j] = fabsf(w[j]) * gain;
     if (any_degenerate) {
@@ -127,41 +137,77 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
     // pulses to add (> 0) or to take away (< 0)   (small integers: exact in any order)
     const float miss = (degenerate ? 0.0f : K) - row_sum_pairs(tree_sum<CP>(tmp));
     const float unit = miss < 0.0f ? -1.0f : 1.0f, need = fabsf(miss);
-    // one pulse per step and group on the largest deviation (negated where pulses have to go), lowest coordinate on ties, as
-    // bits of floats: those that are looked for are positive, and none comes up twice (a place taken gets the key -1, the
-    // bits of no deviation).  The wave goes on while any of its four groups is off the pyramid, about five steps at D = 128.
+    // deviations (negated where pulses have to go), as bits of floats: the `need` largest are positive
     int key[CP];
 #pragma unroll
     for (int j = 0; j < CP; j++) key[j] = (int)__float_as_uint((t[j] - m[j]) * unit);
-#pragma unroll 1
-    for (float step = 0.0f; step < (float)D && __any(need > step); step += 1.0f) {
-        const bool open = need > step;      // the same in the 16 lanes of a group
-        int largest = max(key[0], key[1]);
+    bool repaired = false;
+    if constexpr (DISTINCT) {
+        // The largest, the largest below it, ...: with `last` the one before, key - last as an unsigned number is largest for the
+        // first key below it.  After as many steps as the group has pulses to move, the keys not below the last are moved,
+        // unless two of them were equal: then the sum tells, and the steps below are taken.  (The wave goes on while any of its
+        // four groups has a step left, about five at D = 128; a step's masks on the scalar unit cost as much as its vector
+        // instructions, and this has none.)
+        uint32_t place[CP];
 #pragma unroll
-        for (int j = 2; j < CP; j += 2) largest = max(max(largest, key[j]), key[j + 1]);
-        int best = largest;
-#define PVQ_STEP(CTRL) best = max(best, (int)dpp_move<CTRL>((uint32_t)best, 0x80000000u));
-        PVQ_ROW_STEPS(PVQ_STEP)
-#undef PVQ_STEP
-        bool taken = !(open && largest == best);
-        if (16 * __popcll(__ballot(!taken)) != __popcll(__ballot(open))) {      // a tie between lanes of a group
-            int first = taken ? 16 : sub;
-#define PVQ_STEP(CTRL) first = min(first, (int)dpp_move<CTRL>((uint32_t)first, 0x7FFFFFFFu));
+        for (int j = 0; j < CP; j++) place[j] = (uint32_t)max(key[j], 0);
+        uint32_t last = 0x80000000u;                // (above all of them)
+#pragma unroll 1
+        for (float step = 0.0f; step < (float)D && __any(need > step); step += 1.0f) {
+            uint32_t next = max(place[0] - last, place[1] - last);
+#pragma unroll
+            for (int j = 2; j < CP; j += 2) next = max(max(next, place[j] - last), place[j + 1] - last);
+#define PVQ_STEP(CTRL) next = max(next, dpp_move<CTRL>(next));
             PVQ_ROW_STEPS(PVQ_STEP)
 #undef PVQ_STEP
-            taken = taken || first != sub;
+            last = need > step ? last + next : last;
         }
+        float moved[CP];
 #pragma unroll
         for (int j = 0; j < CP; j++) {
-            const bool equal = key[j] == best;
-            key[j] = equal && !taken ? -1 : key[j];
-            taken = taken || equal;
+            moved[j] = m[j] + (place[j] >= last ? unit : 0.0f);
+            tmp[j] = moved[j];
         }
+        repaired = __all(row_sum_pairs(tree_sum<CP>(tmp)) == (degenerate ? 0.0f : K));
+        if (repaired) {
+#pragma unroll
+            for (int j = 0; j < CP; j++) m[j] = moved[j];
+        }
+    }
+    // One pulse per step and group on the largest deviation, lowest coordinate on ties; none comes up twice (a place taken gets
+    // the key -1, the bits of no deviation).
+    if (!repaired) {
+#pragma unroll 1
+        for (float step = 0.0f; step < (float)D && __any(need > step); step += 1.0f) {
+            const bool open = need > step;      // the same in the 16 lanes of a group
+            int largest = max(key[0], key[1]);
+#pragma unroll
+            for (int j = 2; j < CP; j += 2) largest = max(max(largest, key[j]), key[j + 1]);
+            int best = largest;
+#define PVQ_STEP(CTRL) best = max(best, (int)dpp_move<CTRL>((uint32_t)best, 0x80000000u));
+            PVQ_ROW_STEPS(PVQ_STEP)
+#undef PVQ_STEP
+            bool taken = !(open && largest == best);
+            if (16 * __popcll(__ballot(!taken)) != __popcll(__ballot(open))) {      // a tie between lanes of a group
+                int first = taken ? 16 : sub;
+#define PVQ_STEP(CTRL) first = min(first, (int)dpp_move<CTRL>((uint32_t)first, 0x7FFFFFFFu));
+                PVQ_ROW_STEPS(PVQ_STEP)
+#undef PVQ_STEP
+                taken = taken || first != sub;
+            }
+#pragma unroll
+            for (int j = 0; j < CP; j++) {
+                const bool equal = key[j] == best;
+                key[j] = equal && !taken ? -1 : key[j];
+                taken = taken || equal;
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < CP; j++) m[j] += key[j] == -1 ? unit : 0.0f;
     }
     float y[CP];
 #pragma unroll
     for (int j = 0; j < CP; j++) {
-        m[j] += key[j] == -1 ? unit : 0.0f;
         y[j] = copysignf(m[j], w[j]);
     }
     if (any_degenerate && degenerate && sub == 15) {
@@ -185,7 +231,7 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
         }
         amp = row_sum_pairs(tree_sum<CP>(pr)) / sqrtf(row_sum_pairs(tree_sum<CP>(tmp)));
     } else {
-        amp = sqrtf(ss);
+        amp = ordinary ? pvq_exact_dev::root_of(ss) : sqrtf(ss);
     }
     if (on && sub == 0) p.scale_out[row * p.groups + g] = amp;
     if (on && p.pulses_out) {
@@ -325,7 +371,7 @@ __global__ __launch_bounds__(512) void encode_wide16_kernel(encode_wide_params p
             }
         }
 
-        encode_group16<CP, W>(w, sub, on, gl, row, g, p, stream, tile_words);
+        encode_group16<CP, W, TIN == PVQ_F32>(w, sub, on, gl, row, g, p, stream, tile_words);
     }
     __syncthreads();
     uint32_t *dst = p.index_out + row * p.index_row_words + first_word;
@@ -395,7 +441,7 @@ __global__ __launch_bounds__(1024, 8) void rotate_encode16_kernel(rotate_encode_
     __syncthreads();
     const int sub = lane & 15, gl = lane >> 4;
     const bool on = gl < ng;
-    encode_group16<8, W>(v, sub, on, gl, row, g0 + (on ? gl : 0), p.e, stream, tile_words);
+    encode_group16<8, W, true>(v, sub, on, gl, row, g0 + (on ? gl : 0), p.e, stream, tile_words);
     __syncthreads();
     uint32_t *dst = p.e.index_out + row * p.e.index_row_words + first_word;
     for (int i = threadIdx.x; i < tile_words; i += blockDim.x) dst[i] = stream[i];
