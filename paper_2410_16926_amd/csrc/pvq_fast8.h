@@ -10,7 +10,7 @@
 //
 // Stages for D = 8:
 //   S0  (d=8, k=K)   pair (y0,y1)  -> residual in (6, k1)
-//   S1  (d=6, k1)    pair (y2,y3)  -> residual in (4, k2)
+//   S1  (d=6, k1)    pair (y2,y3)  -> residual in (4, k2), of 16 bits from here on
 //   S2  (d=4, k2)    single y4     -> residual in (3, k3)
 //   T3  (d=3, k3)    direct table over every (k3, r): y5, y6, y7
 // Finding a block: a bucket table indexed by (row k, r >> shift) names the block that holds the
@@ -18,11 +18,20 @@
 // its start relative to the bucket).  The block table entry carries the block's start and end; if
 // r lies beyond the end (a bucket with several small blocks) the lane steps on block by block.
 // Residuals are carried with a per-row bias that makes r >> shift the bucket's place in the stage's
-// whole bucket table (see the block entry).  All tables sit in one blob that a workgroup copies into
-// LDS; a second flavour keeps S0's block table outside for a kernel that reads it from device memory.
+// whole bucket table (see the block entries).  All tables sit in one blob that a workgroup copies into
+// LDS; a kernel may read some of S0's block entries from the blob itself.
 //
-// Values are emitted as packed bf16 pairs (exact for |y| <= 256) ready for v_dot2_f32_bf16, plus
-// 4 * sum(y^2) accumulated from the block entries' `meta` words.
+// The lookups in LDS, spread over all of it, and the instructions, those of the lanes that step on among them, are what
+// the kernels spend their time on.  So the block entries of S1 and S2 are 8 bytes (a gather of 16 bytes a lane takes the
+// LDS twice as long), which leaves room for finer buckets and S0's blocks beside them; a row's first bucket starts as far in
+// front of its first index as lets the fewest indices step on; and S1's entries name three blocks.  K = 16, chance that one of a
+// wave's 256 groups of normal weights steps on in S0, S1 and S2: 0.1, 0.5 and 0; with entries of 16 bytes, two blocks named and
+// rows that start with a bucket 0.1, 0.9 and 0.6 (S0's blocks in device memory; in LDS with coarser buckets 0.4).  Products of
+// 28672 x 8192 with 1, 4 and 16 vectors then 68, 83 and 102 us, now 56, 68 and 96; 8192 x 28672 with 16 94 and 89;
+// 10000 x 3000 decoded to bf16 42 and 29.
+//
+// Values are emitted as packed bf16 pairs (exact for |y| <= 256) ready for v_dot2_f32_bf16, which also forms
+// sum(y^2): exactly, on top of 2^22, so that the low bits of the float are 2 * sum(y^2).
 #pragma once
 
 #include <stdint.h>
@@ -46,83 +55,103 @@ typedef uint32_t pvq_u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t pvq_u32x2 __attribute__((ext_vector_type(2)));
 
 struct pvq_fast8_params {
-    uint32_t blob_bytes;  // whole blob
-    uint32_t tab_bytes;   // what a workgroup copies into LDS: all but an S0 block table kept outside
-    uint32_t lds_bytes;   // tab_bytes without its last table, 1/sqrt(n2) (a kernel with its own gain
+    uint32_t blob_bytes;  // whole blob: what a workgroup copies into LDS
+    uint32_t lds_bytes;   // blob_bytes without its last table, 1/sqrt(n2) (a kernel with its own gain
                           // table leaves that out)
-    uint32_t s0_outside;  // 1: S0's block table lies behind tab_bytes and is read from the blob in
-                          // device memory (and S0's bucket entries are two-candidate ones)
     uint32_t n_minus_1;   // N(8,K) - 1: stored indices are clamped to it
     uint32_t bk0, bk1, bk2, t3;   // byte offsets of the three bucket tables and of T3
     uint32_t bl0, bl1, bl2;       // ... and of the three block tables
-    uint32_t invs;        // float [K*K + 1]: 1 / sqrt(n2), indexed by n2 (entry 0 = 0)
+    uint32_t invs;        // 1 / sqrt(n2) as a float at invs + 2 * n2 (0 for n2 = 0); n2 is as odd or even as K
     uint32_t s0, s1, s2;  // bucket shifts of the three searched stages
     uint32_t k2max;       // n2 <= K*K
 };
 
-// Two bucket-entry forms.
-// "two-candidate" (S1, 32 bits): bits 0..12 start of candidate B inside the bucket, bits 13..16 index
-// distance from A to B (0 = no B), bits 17..31 index of A in the stage's block table.  B is the block
-// starting inside the bucket that covers most of it.
-// "next-block" (S0 32 bits, S2 16 bits): B is always the block after A, which lets one addition do
-// the whole selection: entry = ((index of A - bucket number) << shift) + (2^shift - start of B inside
-// the bucket), so that (entry + r) >> shift = index of A, plus one exactly when r has reached B (the
-// low parts carry).  In the 16-bit form the arithmetic is modulo 2^16.
-constexpr uint32_t kFast8ThrBits = 13;
+// Three bucket-entry forms.
+// "two-candidate" (S0, 32 bits): bits 0..11 index of A in the stage's block table, bits 12..15 index distance from A
+// to B, the top `shift` bits the start of B inside the bucket less one (all ones: no B), so that
+// r << (32 - shift) is above the whole entry exactly when r has reached B.  B is the block starting inside the
+// bucket that covers most of it.
+// "three-candidate" (S1, 32 bits): the block after A too, whose start less one is in the `shift` bits below those;
+// B (the distance from the block after A) is then the best of those that follow.
+// "next-block" (S2, 16 bits): B is always the block after A, which lets one addition do the whole selection:
+// entry = ((index of A - bucket number) << shift) + (2^shift - start of B inside the bucket), so that
+// (entry + r) >> shift = index of A, plus one exactly when r has reached B (the low parts carry), modulo 2^16.
+constexpr uint32_t kFast8IndexBits = 12;
 constexpr uint32_t kFast8DbBits = 4;
 constexpr uint32_t kFast8MaxShift = 13;   // all bucket shifts stay at or below this
+constexpr uint32_t kFast8MaxShift1 = 8;   // S1's: two starts in an entry
 // LDS left for the blob: the 160 KiB of a compute unit minus 5 KiB for the kernels' own buffers
 // (partial sums: 2 KiB; amplitude table: 1 KiB, or a fused gain table in place of 1/sqrt(n2))
 constexpr uint32_t kFast8MaxBytes = 160 * 1024 - 5120;
 
-// block entry (16 bytes, read as one uint4): x = start, y = end (0xFFFFFFFF for the last block of a
-// row), z = values as bf16 pair, w = meta = 4*(a^2+b^2).  start and end are biased: a residual is
-// carried as r + (its row's first bucket in the stage's bucket table) << shift, so that r >> shift
-// finds the bucket without a row offset; x = start + this row's bias - the next stage's row bias.
+// S0's block entry (16 bytes, read as one uint4): x = start, y = end (0xFFFFFFFF for the last block of the
+// row), z = values as bf16 pair, w = 2^22 + a^2 + b^2 as a float's bits.  start and end are biased: a residual is
+// carried as r + (its row's first bucket in the stage's bucket table) << shift + (the row's start in that
+// bucket), so that r >> shift finds the bucket without a row offset; x = start - the next stage's row bias.
 struct pvq_fast8_block {
-    uint32_t start, end, values, meta;
+    uint32_t start, end, values, squares;
 };
+// S1's and S2's (8 bytes): the low half of `range` is start + this row's bias - the next stage's row bias, modulo
+// 2^16 (the next stage's residuals have 16 bits), its high half the end of what that stage's row then holds:
+// a residual at or above it lies in a later block.  S2's values: the coordinate in the low half.
+struct pvq_fast8_small_block {
+    uint32_t range, values;
+};
+
+constexpr uint32_t kFast8Squares = 0x4A800000u;   // the bits of the float 2^22
+
+// acc + a^2 + b^2 for a bf16 pair (a, b), acc as the bits of a float
+PVQ_HD uint32_t pvq_fast8_add_squares(uint32_t acc, uint32_t pair)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    typedef __attribute__((ext_vector_type(2))) __bf16 pair_t;
+    const pair_t v = __builtin_bit_cast(pair_t, pair);
+    return __builtin_bit_cast(uint32_t, __builtin_amdgcn_fdot2_f32_bf16(v, v, __builtin_bit_cast(float, acc), false));
+#else
+    const float lo = __builtin_bit_cast(float, pair << 16), hi = __builtin_bit_cast(float, pair & 0xFFFF0000u);
+    return __builtin_bit_cast(uint32_t, __builtin_bit_cast(float, acc) + lo * lo + hi * hi);
+#endif
+}
 
 // A searched stage for NG independent groups at once, in two halves so that all bucket reads are
 // issued together and then all block reads (the latencies of the groups overlap instead of adding up).
 //
 // First half: the bucket lookups in the stage's bucket table at byte offset `bk` (r is biased with
 // its row, see the block entry); returns in addr[j] the byte offset of the block entry chosen for r[j].
-// MODE 0: two-candidate 32-bit entries; 1: next-block 32-bit entries; 2: next-block 16-bit entries.
-template <int NG, int MODE>
+// STAGE 0: two-candidate entries, block entries of 16 bytes; 1: three-candidate; 2: next-block.
+template <int NG, int STAGE>
 PVQ_HD void pvq_fast8_find(const unsigned char *lds, uint32_t bk, uint32_t shift, uint32_t bl,
                            const uint32_t (&r)[NG], uint32_t (&addr)[NG])
 {
+    constexpr uint32_t kEntryShift = STAGE == 0 ? 4 : 3;
     uint32_t e[NG];
 #pragma unroll
     for (int j = 0; j < NG; j++) {
-        if constexpr (MODE == 2) e[j] = *reinterpret_cast<const uint16_t *>(lds + bk + (r[j] >> shift) * 2u);
+        if constexpr (STAGE == 2) e[j] = *reinterpret_cast<const uint16_t *>(lds + bk + (r[j] >> shift) * 2u);
         else e[j] = *reinterpret_cast<const uint32_t *>(lds + bk + (r[j] >> shift) * 4u);
     }
 #pragma unroll
     for (int j = 0; j < NG; j++) {
         uint32_t idx;
-        if constexpr (MODE == 0) {
-            const uint32_t rlow = r[j] & ((1u << shift) - 1u);
-            const uint32_t thr = e[j] & ((1u << kFast8ThrBits) - 1u);
-            const uint32_t db = (e[j] >> kFast8ThrBits) & ((1u << kFast8DbBits) - 1u);
-            idx = (e[j] >> (kFast8ThrBits + kFast8DbBits)) + (rlow >= thr ? db : 0u);
-        } else if constexpr (MODE == 1) {
-            idx = (e[j] + r[j]) >> shift;
+        if constexpr (STAGE == 0) {
+            const uint32_t db = (e[j] >> kFast8IndexBits) & ((1u << kFast8DbBits) - 1u);
+            idx = (e[j] & ((1u << kFast8IndexBits) - 1u)) + (r[j] << (32u - shift) > e[j] ? db : 0u);
+        } else if constexpr (STAGE == 1) {
+            const uint32_t db = (e[j] >> kFast8IndexBits) & ((1u << kFast8DbBits) - 1u), x = r[j] << (32u - shift);
+            idx = (e[j] & ((1u << kFast8IndexBits) - 1u)) + (x > e[j] ? db : 0u) + (x > e[j] << shift ? 1u : 0u);
         } else {
             idx = (uint32_t)(uint16_t)(e[j] + r[j]) >> shift;
         }
-        addr[j] = bl + (idx << 4);
+        addr[j] = bl + (idx << kEntryShift);
     }
 }
 
-// Second half, after b[j] has been read from `mem + addr[j]`: a bucket with several small blocks
+// Second half for S0, after b[j] has been read from `lds + addr[j]`: a bucket with several small blocks
 // makes the few lanes concerned move on block by block; then r[j] becomes the residual inside the
-// block found.  `mem` is the memory that holds the block table (the LDS copy of the blob, or the
-// blob in device memory).  `addr_of(addr)` fills in the entries' addresses when they are needed: a
+// block found.  `addr_of(addr)` fills in the entries' addresses when they are needed: a
 // caller that did not keep them looks them up again, which only the rare groups that move on pay for.
 template <int NG, typename AddrOf>
-PVQ_HD void pvq_fast8_settle(const unsigned char *mem, uint32_t (&r)[NG], pvq_u32x4 (&b)[NG], AddrOf &&addr_of)
+PVQ_HD void pvq_fast8_settle(const unsigned char *lds, uint32_t (&r)[NG], pvq_u32x4 (&b)[NG], AddrOf &&addr_of)
 {
     bool miss = false, mj[NG];
 #pragma unroll
@@ -141,7 +170,7 @@ PVQ_HD void pvq_fast8_settle(const unsigned char *mem, uint32_t (&r)[NG], pvq_u3
             if (mj[j]) {
                 do {
                     addr[j] += 16;
-                    b[j] = *reinterpret_cast<const pvq_u32x4 *>(mem + addr[j]);
+                    b[j] = *reinterpret_cast<const pvq_u32x4 *>(lds + addr[j]);
                     PVQ_KEEP_TOGETHER(b[j]);
                 } while (r[j] >= b[j].y);
             }
@@ -151,92 +180,105 @@ PVQ_HD void pvq_fast8_settle(const unsigned char *mem, uint32_t (&r)[NG], pvq_u3
     for (int j = 0; j < NG; j++) r[j] -= b[j].x;
 }
 
-// both halves, block table in LDS
-template <int NG, int MODE>
+// both halves for S1 and S2: residuals of 16 bits from here on
+template <int NG, int STAGE>
 PVQ_HD void pvq_fast8_stage(const unsigned char *lds, uint32_t bk, uint32_t shift, uint32_t bl,
-                            uint32_t (&r)[NG], pvq_u32x4 (&b)[NG])
+                            uint32_t (&r)[NG], pvq_u32x2 (&b)[NG])
 {
-    uint32_t addr[NG];
-    pvq_fast8_find<NG, MODE>(lds, bk, shift, bl, r, addr);
+    uint32_t addr[NG], next[NG];
+    pvq_fast8_find<NG, STAGE>(lds, bk, shift, bl, r, addr);
 #pragma unroll
-    for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x4 *>(lds + addr[j]);
-    pvq_fast8_settle<NG>(lds, r, b, [&](uint32_t (&out)[NG]) {
+    for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x2 *>(lds + addr[j]);
+    bool miss = false, mj[NG];
 #pragma unroll
-        for (int j = 0; j < NG; j++) out[j] = addr[j];
-    });
+    for (int j = 0; j < NG; j++) {
+        PVQ_KEEP_TOGETHER(b[j]);
+        next[j] = (uint16_t)((uint16_t)r[j] - (uint16_t)b[j].x);
+        mj[j] = next[j] >= b[j].x >> 16;
+        miss = miss || mj[j];
+    }
+    if (miss) {
+#pragma unroll
+        for (int j = 0; j < NG; j++) {
+            if (mj[j]) {
+                do {
+                    addr[j] += 8;
+                    b[j] = *reinterpret_cast<const pvq_u32x2 *>(lds + addr[j]);
+                    PVQ_KEEP_TOGETHER(b[j]);
+                    next[j] = (uint16_t)((uint16_t)r[j] - (uint16_t)b[j].x);
+                } while (next[j] >= b[j].x >> 16);
+            }
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NG; j++) r[j] = next[j];
 }
 
-// S0 for NG stored indices, up to the addresses of the block entries (in `blob` when OUTSIDE, else in
-// `lds`): a caller that reads those entries from device memory can start S0 of its next indices
+// S0 for NG stored indices, up to the places of the block entries in the tables: a caller that reads those entries from device memory can start S0 of its next indices
 // while it still decodes the current ones.  r = the indices, clamped to the last valid one.
-template <int NG, bool OUTSIDE>
+template <int NG>
 PVQ_HD void pvq_fast8_s0_find(const unsigned char *lds, const pvq_fast8_params &p, const uint32_t (&c)[NG],
                               uint32_t (&r)[NG], uint32_t (&addr)[NG])
 {
 #pragma unroll
     for (int j = 0; j < NG; j++) r[j] = c[j] < p.n_minus_1 ? c[j] : p.n_minus_1;
-    pvq_fast8_find<NG, OUTSIDE ? 0 : 1>(lds, p.bk0, p.s0, p.bl0, r, addr);
+    pvq_fast8_find<NG, 0>(lds, p.bk0, p.s0, p.bl0, r, addr);
 }
 
 // The rest of the decoder, from S0's block entries b (as read from the addresses that
 // pvq_fast8_s0_find gave for the clamped indices r) on.  Per index:
-// four bf16 pairs (y0,y1) (y2,y3) (y4,y5) (y6,y7) and n2x4 = 4 * sum y^2.  Each pair is handed to
+// four bf16 pairs (y0,y1) (y2,y3) (y4,y5) (y6,y7) and the bits of the float 2^22 + sum y^2: kFast8Squares + 2 * sum y^2.  Each pair is handed to
 // `emit(j, pair number, word)` as soon as its stage has found it, so that a consumer that folds
 // pairs into sums (the fused product) keeps one accumulator per group alive instead of the block
 // entries.
-template <int NG, bool OUTSIDE, typename Emit>
-PVQ_HD void pvq_fast8_rest(const unsigned char *lds, const unsigned char *blob, const pvq_fast8_params &p,
-                           uint32_t (&r)[NG], pvq_u32x4 (&b)[NG], Emit &&emit, uint32_t (&n2x4)[NG])
+template <int NG, typename Emit>
+PVQ_HD void pvq_fast8_rest(const unsigned char *lds, const pvq_fast8_params &p,
+                           uint32_t (&r)[NG], pvq_u32x4 (&b)[NG], Emit &&emit, uint32_t (&squares)[NG])
 {
-    uint32_t acc[NG], y4[NG];
-    pvq_fast8_settle<NG>(OUTSIDE ? blob : lds, r, b, [&](uint32_t (&out)[NG]) {
+    uint32_t acc[NG];
+    pvq_u32x2 b1[NG], t[NG];
+    pvq_fast8_settle<NG>(lds, r, b, [&](uint32_t (&out)[NG]) {
         uint32_t same[NG];
-        pvq_fast8_s0_find<NG, OUTSIDE>(lds, p, r, same, out);
+        pvq_fast8_s0_find<NG>(lds, p, r, same, out);
     });
 #pragma unroll
     for (int j = 0; j < NG; j++) { emit(j, 0, b[j].z); acc[j] = b[j].w; }
-    pvq_fast8_stage<NG, 0>(lds, p.bk1, p.s1, p.bl1, r, b);
+    pvq_fast8_stage<NG, 1>(lds, p.bk1, p.s1, p.bl1, r, b1);
 #pragma unroll
-    for (int j = 0; j < NG; j++) { emit(j, 1, b[j].z); acc[j] += b[j].w; }
-    pvq_fast8_stage<NG, 2>(lds, p.bk2, p.s2, p.bl2, r, b);
-#pragma unroll
-    for (int j = 0; j < NG; j++) { y4[j] = b[j].z; acc[j] += b[j].w; }
-    pvq_u32x2 t[NG];
+    for (int j = 0; j < NG; j++) { emit(j, 1, b1[j].y); acc[j] = pvq_fast8_add_squares(acc[j], b1[j].y); }
+    pvq_fast8_stage<NG, 2>(lds, p.bk2, p.s2, p.bl2, r, b1);
 #pragma unroll
     for (int j = 0; j < NG; j++) t[j] = *reinterpret_cast<const pvq_u32x2 *>(lds + p.t3 + (r[j] << 3));
 #pragma unroll
     for (int j = 0; j < NG; j++) {
-        emit(j, 2, (t[j].x & 0xFFFF0000u) | y4[j]);
+        const uint32_t pair = t[j].x | b1[j].y;
+        emit(j, 2, pair);
         emit(j, 3, t[j].y);
-        n2x4[j] = (acc[j] + t[j].x) & 0x7FFu;
+        squares[j] = pvq_fast8_add_squares(pvq_fast8_add_squares(acc[j], pair), t[j].y);
     }
 }
 
-// Whole decoder, one index set after the other.  `lds` holds the first tab_bytes of the blob (on the
-// device: their copy in LDS), `blob` the whole blob (used for S0's block table when OUTSIDE).
-template <int NG, bool OUTSIDE, typename Emit>
-PVQ_HD void pvq_fast8_decode_emit(const unsigned char *lds, const unsigned char *blob, const pvq_fast8_params &p,
-                                  const uint32_t (&c)[NG], Emit &&emit, uint32_t (&n2x4)[NG])
+// Whole decoder, one index set after the other.  `lds`: the blob (on the device: its copy in LDS).
+template <int NG, typename Emit>
+PVQ_HD void pvq_fast8_decode_emit(const unsigned char *lds, const pvq_fast8_params &p,
+                                  const uint32_t (&c)[NG], Emit &&emit, uint32_t (&squares)[NG])
 {
     uint32_t r[NG], addr[NG];
     pvq_u32x4 b[NG];
-    const unsigned char *s0mem = OUTSIDE ? blob : lds;
-    pvq_fast8_s0_find<NG, OUTSIDE>(lds, p, c, r, addr);
+    pvq_fast8_s0_find<NG>(lds, p, c, r, addr);
 #pragma unroll
-    for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x4 *>(s0mem + addr[j]);
-    pvq_fast8_rest<NG, OUTSIDE>(lds, blob, p, r, b, emit, n2x4);
+    for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x4 *>(lds + addr[j]);
+    pvq_fast8_rest<NG>(lds, p, r, b, emit, squares);
 }
 
 // The same with the pairs stored.
-template <int NG, bool OUTSIDE>
-PVQ_HD void pvq_fast8_decode(const unsigned char *lds, const unsigned char *blob, const pvq_fast8_params &p,
-                             const uint32_t (&c)[NG], uint32_t (&pairs)[NG][4], uint32_t (&n2x4)[NG])
+template <int NG>
+PVQ_HD void pvq_fast8_decode(const unsigned char *lds, const pvq_fast8_params &p,
+                             const uint32_t (&c)[NG], uint32_t (&pairs)[NG][4], uint32_t (&squares)[NG])
 {
-    pvq_fast8_decode_emit<NG, OUTSIDE>(lds, blob, p, c, [&](int j, int pair, uint32_t w) { pairs[j][pair] = w; }, n2x4);
+    pvq_fast8_decode_emit<NG>(lds, p, c, [&](int j, int pair, uint32_t w) { pairs[j][pair] = w; }, squares);
 }
 
-// Host side: builds the blob for (8, K) if what goes to LDS fits `max_bytes`; returns false otherwise.
-// s0_outside: keep S0's block table behind the part copied to LDS.
+// Host side: builds the blob for (8, K) if it fits `max_bytes`; returns false otherwise.
 #include <vector>
-bool pvq_fast8_build(int K, uint32_t max_bytes, bool s0_outside, std::vector<unsigned char> &blob,
-                     pvq_fast8_params &p);
+bool pvq_fast8_build(int K, uint32_t max_bytes, std::vector<unsigned char> &blob, pvq_fast8_params &p);

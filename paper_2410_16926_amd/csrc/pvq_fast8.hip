@@ -34,15 +34,20 @@ struct fast8_launch {
     int index_bits, scale_bits;
 };
 
+// The fused gain table (see load_tables) in LDS: rows 0 or 1, 2 or 3, ... of n2; an odd n2's first row lies one group of
+// codes and a half further on, so that 2 * n2 * 2^scale_bits is a row's place from lds_bytes on.
+__host__ __device__ inline uint32_t fused_rows(const pvq_fast8_params &p) { return p.k2max / 2 + 1; }
+__host__ __device__ inline uint32_t fused_start(const fast8_launch &f) { return f.p.lds_bytes + ((2u * (f.p.k2max & 1u)) << f.scale_bits); }
+
 // Copies the blob into LDS.  With FUSED (amplitude codes of at most 2 bits) the blob's last table,
-// 1/sqrt(n2), is left out and its place taken by gain[n2][q] = (1/sqrt(n2)) * sqrt(center[q]),
-// 2^scale_bits floats per n2, so that one lookup gives a group's whole gain; otherwise the
+// 1/sqrt(n2), is left out and its place taken by gain[n2/2][q] = (1/sqrt(n2)) * sqrt(center[q]),
+// 2^scale_bits floats per n2 (which is as odd or even as K), so that one lookup gives a group's whole gain; otherwise the
 // 2^scale_bits values sqrt(center[q]) follow the blob.
 template <bool FUSED>
 __device__ inline void load_tables(unsigned char *lds, const fast8_launch &f, float *sqrtc_l)
 {
     const int nthreads = blockDim.x;
-    const uint32_t bytes = FUSED ? f.p.lds_bytes : f.p.tab_bytes;
+    const uint32_t bytes = FUSED ? f.p.lds_bytes : f.p.blob_bytes;
     // Every workgroup starts at another place of the blob (with all units asking for the same lines in the same
     // order, one L2 channel at a time serves the whole machine), two 16-byte pieces per lane and trip.  (All ten
     // pieces of a lane requested before the first LDS write measured 13 us slower per launch, one at a time and no
@@ -61,10 +66,11 @@ __device__ inline void load_tables(unsigned char *lds, const fast8_launch &f, fl
         *reinterpret_cast<uint4 *>(lds + s1 * 16u) = v1;
     }
     if constexpr (FUSED) {
-        const int n = (int)f.p.k2max + 1;
+        const int n = (int)fused_rows(f.p);
         for (int i = threadIdx.x; i < (n << f.scale_bits); i += nthreads) {
-            const int n2 = i >> f.scale_bits, q = i & ((1 << f.scale_bits) - 1);
-            sqrtc_l[i] = reinterpret_cast<const float *>(f.blob + f.p.invs)[n2] * f.sqrtc[q];
+            const uint32_t n2 = 2u * (uint32_t)(i >> f.scale_bits) + (f.p.k2max & 1u);
+            const int q = i & ((1 << f.scale_bits) - 1);
+            sqrtc_l[i] = *reinterpret_cast<const float *>(f.blob + f.p.invs + 2u * n2) * f.sqrtc[q];
         }
     } else if (f.scale_bits > 0) {
         for (int i = threadIdx.x; i < (1 << f.scale_bits); i += nthreads) sqrtc_l[i] = f.sqrtc[i];
@@ -168,37 +174,41 @@ __device__ inline quad_offsets make_quad_offsets(const fast8_launch &f, int g0, 
     return o;
 }
 
-// `row` must be uniform in the wave.  No arithmetic on loaded data here, so that fetches stay in
-// flight until the item is split.
+// The row's planes, addresses that are uniform in the wave.  No arithmetic on loaded data here, so that fetches stay in
+// flight until the item is split.  g: the quad's first group.
 template <bool CODES, bool B24>
-__device__ inline void fetch_quad(const fast8_launch &f, const pvq_decode_args &a, int64_t row, int g0, bool in_row,
-                                  const quad_offsets &o, quad_item_t<CODES> &it)
+__device__ inline void fetch_quad_at(const fast8_launch &f, const unsigned char *irow, const unsigned char *srow, int g,
+                                     const quad_offsets &o, quad_item_t<CODES> &it)
 {
-    const unsigned char *irow = reinterpret_cast<const unsigned char *>(a.index + row * a.index_row_words);
     if constexpr (B24) {
         const uint32_t *p = reinterpret_cast<const uint32_t *>(irow + o.index);
         it.w[0] = p[0]; it.w[1] = p[1]; it.w[2] = p[2];
     } else {
         const uint32_t b = (uint32_t)f.index_bits;
-        const uint32_t g = in_row ? (uint32_t)g0 : 0u;
 #pragma unroll
         for (int j = 0; j < kGroupsPerLane; j++) {
-            const uint32_t pos = (g + j) * b, w0 = pos >> 5, sh = pos & 31;
+            const uint32_t pos = (uint32_t)(g + j) * b, w0 = pos >> 5, sh = pos & 31;
             uint64_t v = reinterpret_cast<const uint32_t *>(irow)[w0];
             if (sh + b > 32) v |= (uint64_t)reinterpret_cast<const uint32_t *>(irow)[w0 + 1] << 32;
             it.c[j] = (uint32_t)(v >> sh) & (uint32_t)((1ull << b) - 1ull);
         }
     }
     if constexpr (CODES) {
-        const unsigned char *srow = reinterpret_cast<const unsigned char *>(
-            reinterpret_cast<const uint32_t *>(a.scale) + row * a.scale_row_words);
         it.codes = *reinterpret_cast<const uint32_t *>(srow + o.scale);
     } else {
-        const unsigned char *srow = reinterpret_cast<const unsigned char *>(
-            reinterpret_cast<const float *>(a.scale) + row * a.groups);
         const float4 v = *reinterpret_cast<const float4 *>(srow + o.scale);
         it.amp[0] = v.x; it.amp[1] = v.y; it.amp[2] = v.z; it.amp[3] = v.w;
     }
+}
+
+template <bool CODES, bool B24>
+__device__ inline void fetch_quad(const fast8_launch &f, const pvq_decode_args &a, int64_t row, int g0, bool in_row,
+                                  const quad_offsets &o, quad_item_t<CODES> &it)
+{
+    const uint32_t *scale = CODES ? reinterpret_cast<const uint32_t *>(a.scale) + row * a.scale_row_words
+                                  : reinterpret_cast<const uint32_t *>(a.scale) + row * a.groups;
+    fetch_quad_at<CODES, B24>(f, reinterpret_cast<const unsigned char *>(a.index + row * a.index_row_words),
+                              reinterpret_cast<const unsigned char *>(scale), in_row ? g0 : 0, o, it);
 }
 
 // What the decoder needs of an item, copied out so that the item's registers can take the next fetch.
@@ -267,6 +277,11 @@ __device__ inline float wave_sum_lane63(float v)
 // y = W_hat x
 // ---------------------------------------------------------------------------------------------
 
+// Of a lane's four groups, how many read S0's block entry from LDS when it is fetched a row ahead; the others read it through
+// the vector cache, which takes a cycle per lane of such a gather.  28672 x 8192 / 1024 x 8192, all four from the cache (33 M
+// accesses a launch, one in nearly every cycle): 55.2 / 9.3 us; one from LDS 55.0 / 9.1, two 55.7 / 9.0, four 57.4 / 9.1.
+constexpr int kS0FromLds = 2;
+
 // rows a wave decodes per batch of rows (= how far ahead it fetches), with and without S0 running
 // a row ahead (whose state takes the registers of two more fetched rows)
 constexpr int kGemvRowsPerWave = 4, kGemvRowsPerWaveAhead = 2;
@@ -277,19 +292,21 @@ constexpr size_t kPartBytes = 2 * 64 * 4 * sizeof(float);
 // every wave handles 4 rows of its slice; lanes keep their 32 activations per vector in registers.
 // Row sums: fixed-order sum inside the wave, then the slices' partial sums meet in LDS in slice order.
 // AMP: 0 = float32 amplitudes, 1 = amplitude codes, 2 = amplitude codes with the fused gain table.
-// AHEAD: S0 of a wave's next row is started before the current row is decoded, with S0's block
-// entries read from device memory (tables in the flavour that keeps that table outside LDS).
-template <int NB, int AMP, bool B24, bool AHEAD>
+// A single vector: S0 of a wave's next row is started before the current row is decoded (with more vectors the registers
+// go to the activations instead).
+template <int NB, int AMP, bool B24>
 __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq_decode_args a, int b0,
                                                              int nsl, int rl, int rows_per_block)
 {
-    constexpr bool CODES = AMP != 0;
+    constexpr bool CODES = AMP != 0, AHEAD = NB == 1;
     constexpr int RI = AHEAD ? kGemvRowsPerWaveAhead : kGemvRowsPerWave;
     // static, so that table offsets fold into the LDS instructions' immediate fields
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
     // the fused gain table replaces the 1/sqrt(n2) table at the end of the blob
-    float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? f.p.lds_bytes : f.p.tab_bytes));
-    float *part = sqrtc_l + (AMP == 2 ? ((f.p.k2max + 1) << f.scale_bits) : 256);
+    float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? fused_start(f) : f.p.blob_bytes));
+    // what the bits of 2^22 + n2 lack to the place of a group's gain (multiples of 16: a code is or-ed into them)
+    const uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits), invs_at = f.p.invs - kFast8Squares;
+    float *part = sqrtc_l + (AMP == 2 ? (fused_rows(f.p) << f.scale_bits) : 256);
 
     const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r_end = std::min<int64_t>(a.rows, r_begin + rows_per_block);
@@ -327,9 +344,8 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
         }
     }
 
-    // S0 runs one row ahead.  Its block entries come from the table's copy in device memory, through
-    // the vector cache: that takes one 16-byte lookup per group off the LDS, which is the busiest
-    // unit of this kernel, and the cache's latency passes while the row before is decoded.
+    // S0 runs one row ahead.  Some of its block entries come from the table in device memory, through the vector cache: see
+    // kS0FromLds.
     struct ahead_t {
         quad_split_t<CODES> q;
         uint32_t r[kGroupsPerLane];
@@ -340,9 +356,9 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
         split_quad<CODES, B24>(f, g0, item[slot], n.q);
         fetch_quad<CODES, B24>(f, a, std::min<int64_t>(refill_row, r_last), g0, in_row, qo, item[slot]);
         uint32_t addr[kGroupsPerLane];
-        pvq_fast8_s0_find<kGroupsPerLane, true>(lds, f.p, n.q.c, n.r, addr);
+        pvq_fast8_s0_find<kGroupsPerLane>(lds, f.p, n.q.c, n.r, addr);
 #pragma unroll
-        for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>(f.blob + addr[j]);
+        for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>((j < kS0FromLds ? (const unsigned char *)lds : f.blob) + addr[j]);
     };
     ahead_t nx;
     if constexpr (AHEAD) start_row(0, r_begin + RB + rowlane, nx);
@@ -365,7 +381,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
                 fetch_quad<CODES, B24>(f, a, std::min<int64_t>(batch + RB + i * rl + rowlane, r_last), g0, in_row, qo, item[i]);
             }
 
-            uint32_t n2x4[kGroupsPerLane];
+            uint32_t squares[kGroupsPerLane];
             float dot[kGroupsPerLane][NB];
             // every pair goes into the groups' dot products the moment its stage has found it
             auto emit = [&](int j, int pair, uint32_t w) {
@@ -373,8 +389,8 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
                 for (int b = 0; b < NB; b++)
                     dot[j][b] = dot2_bf16(w, xr[b][4 * j + pair], pair == 0 ? 0.0f : dot[j][b]);
             };
-            if constexpr (AHEAD) pvq_fast8_rest<kGroupsPerLane, true>(lds, f.blob, f.p, cu.r, cu.b, emit, n2x4);
-            else pvq_fast8_decode_emit<kGroupsPerLane, false>(lds, f.blob, f.p, cu.q.c, emit, n2x4);
+            if constexpr (AHEAD) pvq_fast8_rest<kGroupsPerLane>(lds, f.p, cu.r, cu.b, emit, squares);
+            else pvq_fast8_decode_emit<kGroupsPerLane>(lds, f.p, cu.q.c, emit, squares);
             float acc[NB];
 #pragma unroll
             for (int b = 0; b < NB; b++) acc[b] = 0.0f;
@@ -383,13 +399,11 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
             for (int j = 0; j < kGroupsPerLane; j++) {
                 float gain;
                 if constexpr (AMP == 2) {
-                    // byte offset of gain[n2][q]: 4 * (n2 * 2^bits + q), from 4*n2 and the code word
-                    // shifted left by two
-                    const uint32_t code4 = (codes4 >> (j * f.scale_bits)) & (((1u << f.scale_bits) - 1u) << 2);
-                    gain = *reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(sqrtc_l) +
-                                                            ((n2x4[j] << f.scale_bits) + code4));
+                    // gain[n2/2][q]: 4 * (n2/2 * 2^bits + q) bytes on, from 2*n2 and the code word shifted left by two
+                    const uint32_t code4 = ((codes4 >> (j * f.scale_bits)) & (((1u << f.scale_bits) - 1u) << 2)) | gains_at;
+                    gain = *reinterpret_cast<const float *>(lds + ((squares[j] << f.scale_bits) + code4));
                 } else {
-                    gain = *reinterpret_cast<const float *>(lds + f.p.invs + n2x4[j]) *
+                    gain = *reinterpret_cast<const float *>(lds + (squares[j] + invs_at)) *
                            amp_factor<CODES>(f, cu.q, j, sqrtc_l);
                 }
 #pragma unroll
@@ -425,9 +439,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
 // owns the row (its lane 63 adds each slice's sum, formed inside the wave, to a float of its own in LDS, in
 // slice order: deterministic), and after the table copy nothing makes the sixteen waves of a unit meet:
 // they drift apart, and their table lookups come spread out instead of in bursts after every barrier.
-// S0 runs one item ahead with its block entries through the vector cache, as in gemv8_kernel<1, ., ., true>
-// (tables in the flavour that keeps S0's block table outside LDS).  Rows of whole slices; AMP as in
-// gemv8_kernel.
+// S0 runs one item ahead, as in gemv8_kernel<1, ., .>.  Rows of whole slices; AMP as in gemv8_kernel.
 constexpr int kRowMaxRowsPerWave = 32;   // partial sums in LDS: 16 waves x 32 rows
 
 template <int AMP, bool B24>
@@ -437,8 +449,10 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
     constexpr bool CODES = AMP != 0;
     constexpr int kWaves = kGemvThreads / kWave;
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
-    float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? f.p.lds_bytes : f.p.tab_bytes));
-    float *part = sqrtc_l + (AMP == 2 ? ((f.p.k2max + 1) << f.scale_bits) : 256);
+    float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? fused_start(f) : f.p.blob_bytes));
+    // what the bits of 2^22 + n2 lack to the place of a group's gain (multiples of 16: a code is or-ed into them)
+    const uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits), invs_at = f.p.invs - kFast8Squares;
+    float *part = sqrtc_l + (AMP == 2 ? (fused_rows(f.p) << f.scale_bits) : 256);
 
     const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
     const int64_t r_end = std::min<int64_t>(a.rows, r_begin + rows_per_block);
@@ -452,51 +466,60 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
 
     // byte offsets of the lane's quad inside slice 0 of a row of the planes; a slice further on adds a constant
     const quad_offsets q0 = make_quad_offsets<CODES, B24>(f, gl, true);
-    const uint32_t index_step = B24 ? (uint32_t)(kTileGroups / 4) * 12u : 0u;
     const uint32_t scale_step = CODES ? (uint32_t)(kTileGroups / 32) * 4u * (uint32_t)f.scale_bits : (uint32_t)kTileGroups * 4u;
+    const int64_t index_bytes = a.index_row_words * 4, scale_bytes = CODES ? a.scale_row_words * 4 : a.groups * 4;
 
-    // the stream of fetches: item after item, (slice, row) kept as scalars; past the last item the last one is
-    // read again (nothing of it is kept)
-    int f_sl = 0, f_i = 0;
-    auto fetch_next = [&](quad_item_t<CODES> &it) {
-        quad_offsets o;
-        o.index = q0.index + (uint32_t)f_sl * index_step;
-        o.scale = q0.scale + (uint32_t)f_sl * scale_step;
-        fetch_quad<CODES, B24>(f, a, r_begin + wave + (int64_t)kWaves * f_i, f_sl * kTileGroups + gl, true, o, it);
-        if (f_i + 1 < nrows) f_i++;
-        else if (f_sl + 1 < nsl) { f_i = 0; f_sl++; }
+    // the stream of fetches: item after item, rows innermost, (slice, row) and the planes' addresses kept as scalars; past the
+    // last item the last one is read again (nothing of it is kept)
+    struct place_t { int sl, i; };
+    place_t f_at = {0, 0};
+    const unsigned char *index0 = reinterpret_cast<const unsigned char *>(a.index) + (r_begin + wave) * index_bytes;
+    const unsigned char *scale0 = reinterpret_cast<const unsigned char *>(a.scale) + (r_begin + wave) * scale_bytes;
+    const unsigned char *f_index = index0, *f_scale = scale0;
+    place_t raw_at[2];
+    auto fetch_next = [&](quad_item_t<CODES> &it, place_t &at) {
+        at = f_at;
+        fetch_quad_at<CODES, B24>(f, f_index, f_scale, f_at.sl * kTileGroups + gl, q0, it);
+        if (f_at.i + 1 < nrows) {
+            f_at.i++;
+            f_index += kWaves * index_bytes;
+            f_scale += kWaves * scale_bytes;
+        } else if (f_at.sl + 1 < nsl) {
+            f_at.i = 0;
+            f_at.sl++;
+            f_index = index0 + (B24 ? f_at.sl * (kTileGroups * 3) : 0);
+            f_scale = scale0 + f_at.sl * (int64_t)scale_step;
+        }
     };
 
     quad_item_t<CODES> raw[2];
-    if (nitems > 0) { fetch_next(raw[0]); fetch_next(raw[1]); }
+    if (nitems > 0) { fetch_next(raw[0], raw_at[0]); fetch_next(raw[1], raw_at[1]); }
     if (lane < kRowMaxRowsPerWave) mine[lane] = 0.0f;
     load_tables<AMP == 2>(lds, f, sqrtc_l);          // ends with the kernel's only barrier before the last one
 
     if (nitems > 0) {
         struct ahead_t {
+            place_t at;
             quad_split_t<CODES> q;
             uint32_t r[kGroupsPerLane];
             pvq_u32x4 b[kGroupsPerLane];
         };
-        // takes the raw item out of set `slot` (an item of slice `sl`), refills the set from the stream, and
-        // starts S0 for the item taken
-        auto start_item = [&](int slot, int sl, ahead_t &n) {
-            split_quad<CODES, B24>(f, sl * kTileGroups + gl, raw[slot], n.q);
-            fetch_next(raw[slot]);
+        // takes the raw item out of set `slot`, refills the set from the stream, and starts S0 for the item taken
+        auto start_item = [&](int slot, ahead_t &n) {
+            n.at = raw_at[slot];
+            split_quad<CODES, B24>(f, gl, raw[slot], n.q);      // (a slice's codes are whole words)
+            fetch_next(raw[slot], raw_at[slot]);
             uint32_t addr[kGroupsPerLane];
-            pvq_fast8_s0_find<kGroupsPerLane, true>(lds, f.p, n.q.c, n.r, addr);
+            pvq_fast8_s0_find<kGroupsPerLane>(lds, f.p, n.q.c, n.r, addr);
 #pragma unroll
-            for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>(f.blob + addr[j]);
-        };
-        // (slice, row) of the item being decoded and of the one after it
-        int c_sl = 0, c_i = 0, n_sl = 0, n_i = 0;
-        auto advance = [&](int &sl, int &i) {
-            if (i + 1 < nrows) i++;
-            else { i = 0; sl++; }
+            for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>((j < kS0FromLds ? (const unsigned char *)lds : f.blob) + addr[j]);
         };
         ahead_t nx;
-        start_item(0, 0, nx);
-        advance(n_sl, n_i);
+        start_item(0, nx);
+        // lane 63's place behind a row's sum, as a number that the compiler does not know to be 0 there: with one it knows to be
+        // the same in all lanes it adds up the lanes' values first, in a loop
+        int own = lane - (kWave - 1);
+        asm volatile("" : "+v"(own));
 
         uint32_t xr[16];
         int x_sl = -1;
@@ -508,44 +531,41 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
                     // (in front of the next item's requests: memory operations complete in order, so the wait for the
                     // activations, which the compiler places before their use whether or not this branch ran, would
                     // otherwise cover those requests too, in every item)
-                    if (c_sl != x_sl) {
+                    if (cu.at.sl != x_sl) {
                         const uint16_t *xp = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)b0 * a.ldx +
-                                             (int64_t)(c_sl * kTileGroups + gl) * 8;
+                                             (int64_t)(cu.at.sl * kTileGroups + gl) * 8;
 #pragma unroll
                         for (int j = 0; j < 4; j++) {
                             const uint4 v = *reinterpret_cast<const uint4 *>(xp + 8 * j);
                             xr[4 * j] = v.x; xr[4 * j + 1] = v.y; xr[4 * j + 2] = v.z; xr[4 * j + 3] = v.w;
                         }
-                        x_sl = c_sl;
+                        x_sl = cu.at.sl;
                     }
                     // item it + h + 1 sits in set (h + 1) % 2
-                    start_item((h + 1) % 2, std::min(n_sl, nsl - 1), nx);
-                    advance(n_sl, n_i);
-                    uint32_t n2x4[kGroupsPerLane];
+                    start_item((h + 1) % 2, nx);
+                    uint32_t squares[kGroupsPerLane];
                     float dot[kGroupsPerLane];
                     auto emit = [&](int j, int pair, uint32_t w) {
                         dot[j] = dot2_bf16(w, xr[4 * j + pair], pair == 0 ? 0.0f : dot[j]);
                     };
-                    pvq_fast8_rest<kGroupsPerLane, true>(lds, f.blob, f.p, cu.r, cu.b, emit, n2x4);
+                    pvq_fast8_rest<kGroupsPerLane>(lds, f.p, cu.r, cu.b, emit, squares);
                     float acc = 0.0f;
                     const uint32_t codes4 = cu.q.codes << 2;
 #pragma unroll
                     for (int j = 0; j < kGroupsPerLane; j++) {
                         float gain;
                         if constexpr (AMP == 2) {
-                            const uint32_t code4 = (codes4 >> (j * f.scale_bits)) & (((1u << f.scale_bits) - 1u) << 2);
-                            gain = *reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(sqrtc_l) +
-                                                                    ((n2x4[j] << f.scale_bits) + code4));
+                            const uint32_t code4 = ((codes4 >> (j * f.scale_bits)) & (((1u << f.scale_bits) - 1u) << 2)) | gains_at;
+                            gain = *reinterpret_cast<const float *>(lds + ((squares[j] << f.scale_bits) + code4));
                         } else {
-                            gain = *reinterpret_cast<const float *>(lds + f.p.invs + n2x4[j]) *
+                            gain = *reinterpret_cast<const float *>(lds + (squares[j] + invs_at)) *
                                    amp_factor<CODES>(f, cu.q, j, sqrtc_l);
                         }
                         acc = fmaf(gain, dot[j], acc);
                     }
                     const float v = wave_sum_lane63(acc);
                     // one lane, one address per row, slices in order: a plain sum in a fixed order
-                    if (lane == kWave - 1) atomicAdd(&mine[c_i], v);
-                    advance(c_sl, c_i);
+                    if (lane == kWave - 1) atomicAdd(&mine[cu.at.i + own], v);
                 }
             }
         }
@@ -610,7 +630,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_mfma_kernel(fast8_launch f
     constexpr bool CODES = AMP != 0;
     constexpr int kWaves = kGemvThreads / kWave;
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
-    float *sqrtc_l = reinterpret_cast<float *>(lds + f.p.tab_bytes);
+    float *sqrtc_l = reinterpret_cast<float *>(lds + f.p.blob_bytes);
     float *part = sqrtc_l + 256;
 
     const int64_t r_begin = (int64_t)blockIdx.x * tiles_per_block * kMfmaRows;
@@ -691,17 +711,17 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_mfma_kernel(fast8_launch f
 #pragma unroll
                 for (int j = 0; j < 4; j++)
                     bx[j] = *reinterpret_cast<const uint4 *>(xvec + (int64_t)(kSwap ? gq - 4 * kb + 4 * j + kb : gq + j) * 8);
-                uint32_t c[4], pr[4][4], n2x4[4];
+                uint32_t c[4], pr[4][4], squares[4];
                 c[0] = cur.w[0] & 0xFFFFFFu;
                 c[1] = __builtin_amdgcn_alignbit(cur.w[1], cur.w[0], 24) & 0xFFFFFFu;
                 c[2] = __builtin_amdgcn_alignbit(cur.w[2], cur.w[1], 16) & 0xFFFFFFu;
                 c[3] = cur.w[2] >> 8;
-                pvq_fast8_decode<4, false>(lds, f.blob, f.p, c, pr, n2x4);
+                pvq_fast8_decode<4>(lds, f.p, c, pr, squares);
                 const uint32_t codes = CODES ? cur.s[0] >> ((gq * sb) & 31u) : 0u;
                 float gains[4];
 #pragma unroll
                 for (int j = 0; j < 4; j++) {
-                    float gain = *reinterpret_cast<const float *>(lds + f.p.invs + n2x4[j]);
+                    float gain = *reinterpret_cast<const float *>(lds + (squares[j] + (f.p.invs - kFast8Squares)));
                     if constexpr (CODES) gain *= sqrtc_l[(codes >> (j * sb)) & ((1u << sb) - 1u)];
                     else gain *= __uint_as_float(cur.s[j]);
                     gains[j] = gain;
@@ -859,7 +879,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
 {
     // static, so that table offsets fold into the LDS instructions' immediate fields
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
-    float *sqrtc_l = reinterpret_cast<float *>(lds + f.p.tab_bytes);
+    float *sqrtc_l = reinterpret_cast<float *>(lds + f.p.blob_bytes);
     load_tables<false>(lds, f, sqrtc_l);
 
     const int G = (int)a.groups;
@@ -896,43 +916,43 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
 
         const int gbase = (int)tile * kTileGroups + place;
         const float srn = CODES ? sqrtf(cur_rn) : 1.0f;
-        uint32_t c[kGroupsPerLane], prs[kGroupsPerLane][4], n2x4s[kGroupsPerLane];
+        uint32_t c[kGroupsPerLane], prs[kGroupsPerLane][4], squares[kGroupsPerLane];
         item_indices<B24>(cur, gbase, c);
-        pvq_fast8_decode<kGroupsPerLane, false>(lds, f.blob, f.p, c, prs, n2x4s);
+        pvq_fast8_decode<kGroupsPerLane>(lds, f.p, c, prs, squares);
 #pragma unroll
         for (int j = 0; j < kGroupsPerLane; j++) {
             // amp / sqrt(n2): the amplitude first (sqrt(center) * sqrt(row normaliser), or the stored
             // float), then the tabulated 1/sqrt(n2)
             const float amp = CODES ? sqrtc_l[item_code(f, cur, gbase, j)] * srn : __uint_as_float(cur.a[j]);
-            const float gain = amp * *reinterpret_cast<const float *>(lds + f.p.invs + n2x4s[j]);
+            const float gain = amp * *reinterpret_cast<const float *>(lds + (squares[j] + (f.p.invs - kFast8Squares)));
             store_group<OUT>(reinterpret_cast<unsigned char *>(a.W_out) + row * a.ldw * (OUT == PVQ_F32 ? 4 : 2), gbase + kWave * j, G, lane, prs[j], gain);
         }
         cur = nxt; cur_rn = nxt_rn; row = nrow; tile = ntile; live = nlive; item += stride;
     }
 }
 
-fast8_launch make_launch(const pvq_ctx *c, bool gemv)
+fast8_launch make_launch(const pvq_ctx *c)
 {
     fast8_launch f;
-    f.p = gemv ? c->fast8g : c->fast8; f.blob = gemv ? c->fast8g_blob : c->fast8_blob; f.sqrtc = c->sqrtc;
+    f.p = c->fast8; f.blob = c->fast8_blob; f.sqrtc = c->sqrtc;
     f.index_bits = c->index_bits; f.scale_bits = c->scale_bits;
     return f;
 }
 
 int g_num_cus = 0;
 
-template <int NB, bool AHEAD>
+template <int NB>
 hipError_t launch_gemv_nb(const fast8_launch &f, const pvq_decode_args &a, int b0, int nsl, int rl,
                           int rows_per_block, dim3 grid, dim3 block, size_t lds, hipStream_t s)
 {
     const bool b24 = f.index_bits == 24;
     // the fused gain table must fit behind the blob together with the partial-sum buffer
-    const size_t fused_bytes = ((size_t)(f.p.k2max + 1) << f.scale_bits) * 4;
+    const size_t fused_bytes = (fused_start(f) - f.p.lds_bytes) + ((size_t)fused_rows(f.p) << f.scale_bits) * 4;
     const bool fused = f.scale_bits > 0 && f.scale_bits <= 2 &&
                        f.p.lds_bytes + fused_bytes + kPartBytes <= (size_t)kLdsBytes;
     const int amp = f.scale_bits == 0 ? 0 : (fused ? 2 : 1);
 #define PVQ_GEMV_CASE(AMP, B24) \
-    hipLaunchKernelGGL((gemv8_kernel<NB, AMP, B24, AHEAD>), grid, block, lds, s, f, a, b0, nsl, rl, rows_per_block)
+    hipLaunchKernelGGL((gemv8_kernel<NB, AMP, B24>), grid, block, lds, s, f, a, b0, nsl, rl, rows_per_block)
     if (amp == 2) { if (b24) PVQ_GEMV_CASE(2, true); else PVQ_GEMV_CASE(2, false); }
     else if (amp == 1) { if (b24) PVQ_GEMV_CASE(1, true); else PVQ_GEMV_CASE(1, false); }
     else { if (b24) PVQ_GEMV_CASE(0, true); else PVQ_GEMV_CASE(0, false); }
@@ -973,7 +993,7 @@ bool pvq_fast8_decode_usable(const pvq_ctx *c, const pvq_decode_args &a)
 
 hipError_t pvq_fast8_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, int out_dtype, hipStream_t s)
 {
-    const fast8_launch f = make_launch(c, false);
+    const fast8_launch f = make_launch(c);
     const size_t lds = 0;  // the kernels own the whole LDS statically
     const int64_t total = a.rows * ((a.groups + kTileGroups - 1) / kTileGroups);   // wave items
     // every block pays the table copy, so blocks get at least 64 wave items (16K groups) each
@@ -990,19 +1010,19 @@ hipError_t pvq_fast8_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, i
 namespace {
 
 // one launch of the fused product for vectors [b0, b0 + NB)
-template <int NB, bool AHEAD>
+template <int NB>
 hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, hipStream_t s)
 {
-    const fast8_launch f = make_launch(c, AHEAD);
+    const fast8_launch f = make_launch(c);
     const int nsl = (int)((a.groups + kTileGroups - 1) / kTileGroups);
     const int rl = std::max(1, (kGemvThreads / kWave) / nsl);
-    const int RB = (AHEAD ? kGemvRowsPerWaveAhead : kGemvRowsPerWave) * rl;
+    const int RB = (NB == 1 ? kGemvRowsPerWaveAhead : kGemvRowsPerWave) * rl;
     const size_t lds = 0;  // the kernels own the whole LDS statically
     const int64_t batches = (a.rows + RB - 1) / RB;
     const int64_t nblocks = std::max<int64_t>(1, std::min<int64_t>(g_num_cus > 0 ? g_num_cus : 256, batches));
     const int rows_per_block = (int)(((batches + nblocks - 1) / nblocks) * RB);
     const dim3 grid((unsigned)((a.rows + rows_per_block - 1) / rows_per_block)), block((unsigned)(kWave * nsl * rl));
-    return launch_gemv_nb<NB, AHEAD>(f, a, b0, nsl, rl, rows_per_block, grid, block, lds, s);
+    return launch_gemv_nb<NB>(f, a, b0, nsl, rl, rows_per_block, grid, block, lds, s);
 }
 
 constexpr size_t kRowPartBytes = (kGemvThreads / kWave) * kRowMaxRowsPerWave * sizeof(float);
@@ -1010,14 +1030,14 @@ constexpr size_t kRowPartBytes = (kGemvThreads / kWave) * kRowMaxRowsPerWave * s
 // the fused gain table (amplitude codes of at most 2 bits) must fit behind the tables with the partial sums
 bool row_fused(const fast8_launch &f)
 {
-    const size_t fused_bytes = ((size_t)(f.p.k2max + 1) << f.scale_bits) * 4;
+    const size_t fused_bytes = (fused_start(f) - f.p.lds_bytes) + ((size_t)fused_rows(f.p) << f.scale_bits) * 4;
     return f.scale_bits > 0 && f.scale_bits <= 2 && f.p.lds_bytes + fused_bytes + kRowPartBytes <= (size_t)kLdsBytes;
 }
 
 // one launch of the barrier-free single-vector kernel for vector b0
 hipError_t launch_gemv_row(const pvq_ctx *c, const pvq_decode_args &a, int b0, hipStream_t s)
 {
-    const fast8_launch f = make_launch(c, true);
+    const fast8_launch f = make_launch(c);
     constexpr int kWaves = kGemvThreads / kWave;
     const int64_t units = g_num_cus > 0 ? g_num_cus : 256;
     // whole rounds of sixteen rows per workgroup, at most 32 rounds (the partial sums' place in LDS)
@@ -1044,7 +1064,7 @@ namespace {
 // one launch of the matrix-core kernel for vectors [b0, b0 + nvec), nvec <= 16
 hipError_t launch_gemv_mfma(const pvq_ctx *c, const pvq_decode_args &a, int b0, int nvec, hipStream_t s)
 {
-    const fast8_launch f = make_launch(c, false);
+    const fast8_launch f = make_launch(c);
     const int nslabs = (int)(a.groups / kMfmaSlab);
     const int64_t tiles = (a.rows + kMfmaRows - 1) / kMfmaRows;
     const int64_t nblocks = std::max<int64_t>(1, std::min<int64_t>(g_num_cus > 0 ? g_num_cus : 256, tiles));
@@ -1068,7 +1088,7 @@ bool mfma_usable(const pvq_ctx *c, const pvq_decode_args &a)
 {
     return c->index_bits == 24 && a.groups % kMfmaSlab == 0 && a.groups >= 4 * kMfmaSlab && a.groups <= (1 << 20) &&
            a.rows <= ((int64_t)1 << 30) &&
-           (size_t)c->fast8.tab_bytes + 256 * sizeof(float) + kMfmaPartBytes <= (size_t)kLdsBytes;
+           (size_t)c->fast8.blob_bytes + 256 * sizeof(float) + kMfmaPartBytes <= (size_t)kLdsBytes;
 }
 
 // the barrier-free kernel takes rows of whole slices of 256 groups, and pays off when every wave of every
@@ -1077,7 +1097,7 @@ bool row_usable(const pvq_ctx *c, const pvq_decode_args &a)
 {
     const int64_t units = g_num_cus > 0 ? g_num_cus : 256;
     return a.groups % kTileGroups == 0 && a.groups / kTileGroups <= 4096 && a.rows >= units * 16 * 2 &&
-           (size_t)c->fast8g.tab_bytes + 256 * sizeof(float) + kRowPartBytes <= (size_t)kLdsBytes;
+           (size_t)c->fast8.blob_bytes + 256 * sizeof(float) + kRowPartBytes <= (size_t)kLdsBytes;
 }
 
 }  // namespace
@@ -1121,9 +1141,6 @@ bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
 // The passes that a product of a.batch vectors is made of, in order: which kernel takes how many vectors.
 int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pass *out)
 {
-    // a single vector runs S0 a row ahead (if the tables exist in that flavour); with more vectors
-    // the registers go to the activations instead
-    const bool ahead = c->fast8g_blob != nullptr;
     int n = 0, b0 = 0;
     while (b0 < a.batch) {
         const int left = a.batch - b0;
@@ -1134,7 +1151,7 @@ int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pas
         if (left >= 3 && mfma_usable(c, a)) p = {PVQ_PASS_MFMA, std::min(left, 16)};
         else if (left >= 4) p = {PVQ_PASS_VALU, 4};
         else if (left >= 2) p = {PVQ_PASS_VALU, 2};
-        else if (ahead && row_usable(c, a)) p = {PVQ_PASS_VALU_ROWS, 1};
+        else if (row_usable(c, a)) p = {PVQ_PASS_VALU_ROWS, 1};
         else p = {PVQ_PASS_VALU, 1};
         out[n++] = p;
         b0 += p.nvec;
@@ -1144,7 +1161,6 @@ int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pas
 
 hipError_t pvq_fast8_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hipStream_t s)
 {
-    const bool ahead = c->fast8g_blob != nullptr;
     pvq_gemv_pass plan[16];
     const int n = pvq_fast8_plan_gemv(c, a, plan);
     int b0 = 0;
@@ -1155,9 +1171,8 @@ hipError_t pvq_fast8_launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, hip
         case PVQ_PASS_MFMA: e = launch_gemv_mfma(c, a, b0, nvec, s); break;
         case PVQ_PASS_VALU_ROWS: e = launch_gemv_row(c, a, b0, s); break;
         default:
-            e = nvec == 4 ? launch_gemv_pass<4, false>(c, a, b0, s)
-                : nvec == 2 ? launch_gemv_pass<2, false>(c, a, b0, s)
-                : ahead ? launch_gemv_pass<1, true>(c, a, b0, s) : launch_gemv_pass<1, false>(c, a, b0, s);
+            e = nvec == 4 ? launch_gemv_pass<4>(c, a, b0, s)
+                : nvec == 2 ? launch_gemv_pass<2>(c, a, b0, s) : launch_gemv_pass<1>(c, a, b0, s);
         }
         if (e != hipSuccess) return e;
         b0 += nvec;

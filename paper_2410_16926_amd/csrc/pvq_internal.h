@@ -92,11 +92,9 @@ struct pvq_ctx {
     float *edges;   // 2^scale_bits - 1 float32 edges (or nullptr)
     float *sqrtc;   // 2^scale_bits float32 sqrt(centers) (or nullptr)
     // Table-driven decoder (D = 8, one-word indices, tables that fit LDS); fast8_blob == nullptr
-    // when the configuration has none.  Two flavours of the tables: all of them in one LDS copy (the
-    // decode kernel), and S0's block table kept in device memory (the fused product; nullptr if
-    // that flavour does not fit).
-    unsigned char *fast8_blob, *fast8g_blob;
-    pvq_fast8_params fast8, fast8g;
+    // when the configuration has none.
+    unsigned char *fast8_blob;
+    pvq_fast8_params fast8;
     // Coordinate-by-coordinate decoder's tables (every context with D <= 32); nullptr if they were not made.
     unsigned char *walk_blob = nullptr;
     pvq_walk_params walk;
