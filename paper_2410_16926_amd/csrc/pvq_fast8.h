@@ -60,9 +60,9 @@ struct pvq_fast8_params {
                           // table leaves that out)
     uint32_t n_minus_1;   // N(8,K) - 1: stored indices are clamped to it
     uint32_t bk0, bk1, bk2, t3;   // byte offsets of the three bucket tables and of T3
-    uint32_t bl0, bl1, bl2;       // ... and of the three block tables
+    uint32_t bl0, bl1;            // ... and of S0's and S1's block tables (S2's is at the blob's start)
     uint32_t invs;        // 1 / sqrt(n2) as a float at invs + 2 * n2 (0 for n2 = 0); n2 is as odd or even as K
-    uint32_t s0, s1, s2;  // bucket shifts of the three searched stages
+    uint32_t s0, s1, s2;  // bucket shifts of the three searched stages; of 24-bit indices pvq_fast8_shift24
     uint32_t k2max;       // n2 <= K*K
 };
 
@@ -80,6 +80,14 @@ constexpr uint32_t kFast8IndexBits = 12;
 constexpr uint32_t kFast8DbBits = 4;
 constexpr uint32_t kFast8MaxShift = 13;   // all bucket shifts stay at or below this
 constexpr uint32_t kFast8MaxShift1 = 8;   // S1's: two starts in an entry
+// The bucket shifts for 24-bit indices (K = 15 and 16), which the kernels know when they are compiled: the starts in S1's
+// entries are whole bytes then, compared without being moved, and S2's buckets so fine that no index steps on.
+constexpr uint32_t pvq_fast8_shift24(int stage) { return stage == 0 ? 11 : stage == 1 ? 8 : 3; }
+template <int STAGE, bool B24>
+PVQ_HD uint32_t pvq_fast8_shift(const pvq_fast8_params &p)
+{
+    return B24 ? pvq_fast8_shift24(STAGE) : STAGE == 0 ? p.s0 : STAGE == 1 ? p.s1 : p.s2;
+}
 // LDS left for the blob: the 160 KiB of a compute unit minus 5 KiB for the kernels' own buffers
 // (partial sums: 2 KiB; amplitude table: 1 KiB, or a fused gain table in place of 1/sqrt(n2))
 constexpr uint32_t kFast8MaxBytes = 160 * 1024 - 5120;
@@ -116,33 +124,32 @@ PVQ_HD uint32_t pvq_fast8_add_squares(uint32_t acc, uint32_t pair)
 // A searched stage for NG independent groups at once, in two halves so that all bucket reads are
 // issued together and then all block reads (the latencies of the groups overlap instead of adding up).
 //
-// First half: the bucket lookups in the stage's bucket table at byte offset `bk` (r is biased with
-// its row, see the block entry); returns in addr[j] the byte offset of the block entry chosen for r[j].
+// First half: the bucket lookups in the stage's bucket table (r is biased with its row, see the block entries); returns in
+// addr[j] the byte offset of the block entry chosen for r[j].
 // STAGE 0: two-candidate entries, block entries of 16 bytes; 1: three-candidate; 2: next-block.
-template <int NG, int STAGE>
-PVQ_HD void pvq_fast8_find(const unsigned char *lds, uint32_t bk, uint32_t shift, uint32_t bl,
-                           const uint32_t (&r)[NG], uint32_t (&addr)[NG])
+template <int NG, int STAGE, bool B24>
+PVQ_HD void pvq_fast8_find(const unsigned char *lds, const pvq_fast8_params &p, const uint32_t (&r)[NG], uint32_t (&addr)[NG])
 {
-    constexpr uint32_t kEntryShift = STAGE == 0 ? 4 : 3;
+    const uint32_t shift = pvq_fast8_shift<STAGE, B24>(p);
     uint32_t e[NG];
 #pragma unroll
     for (int j = 0; j < NG; j++) {
-        if constexpr (STAGE == 2) e[j] = *reinterpret_cast<const uint16_t *>(lds + bk + (r[j] >> shift) * 2u);
-        else e[j] = *reinterpret_cast<const uint32_t *>(lds + bk + (r[j] >> shift) * 4u);
+        if constexpr (STAGE == 2) e[j] = *reinterpret_cast<const uint16_t *>(lds + p.bk2 + (r[j] >> shift) * 2u);
+        else e[j] = *reinterpret_cast<const uint32_t *>(lds + (STAGE == 0 ? p.bk0 : p.bk1) + (r[j] >> shift) * 4u);
     }
 #pragma unroll
     for (int j = 0; j < NG; j++) {
-        uint32_t idx;
-        if constexpr (STAGE == 0) {
-            const uint32_t db = (e[j] >> kFast8IndexBits) & ((1u << kFast8DbBits) - 1u);
-            idx = (e[j] & ((1u << kFast8IndexBits) - 1u)) + (r[j] << (32u - shift) > e[j] ? db : 0u);
-        } else if constexpr (STAGE == 1) {
-            const uint32_t db = (e[j] >> kFast8IndexBits) & ((1u << kFast8DbBits) - 1u), x = r[j] << (32u - shift);
-            idx = (e[j] & ((1u << kFast8IndexBits) - 1u)) + (x > e[j] ? db : 0u) + (x > e[j] << shift ? 1u : 0u);
+        if constexpr (STAGE == 2) {
+            const uint32_t x = (uint16_t)(e[j] + r[j]);
+            addr[j] = B24 ? x & ~7u : (x >> shift) << 3;
         } else {
-            idx = (uint32_t)(uint16_t)(e[j] + r[j]) >> shift;
+            const uint32_t db = (e[j] >> kFast8IndexBits) & ((1u << kFast8DbBits) - 1u), x = r[j] << (32u - shift);
+            uint32_t idx = e[j] & ((1u << kFast8IndexBits) - 1u);
+            if constexpr (STAGE == 0) idx += x > e[j] ? db : 0u;
+            else if constexpr (B24) idx += ((r[j] & 0xFFu) > e[j] >> 24 ? db : 0u) + ((r[j] & 0xFFu) > ((e[j] >> 16) & 0xFFu) ? 1u : 0u);
+            else idx += (x > e[j] ? db : 0u) + (x > e[j] << shift ? 1u : 0u);
+            addr[j] = STAGE == 0 ? p.bl0 + (idx << 4) : p.bl1 + (idx << 3);
         }
-        addr[j] = bl + (idx << kEntryShift);
     }
 }
 
@@ -181,12 +188,11 @@ PVQ_HD void pvq_fast8_settle(const unsigned char *lds, uint32_t (&r)[NG], pvq_u3
 }
 
 // both halves for S1 and S2: residuals of 16 bits from here on
-template <int NG, int STAGE>
-PVQ_HD void pvq_fast8_stage(const unsigned char *lds, uint32_t bk, uint32_t shift, uint32_t bl,
-                            uint32_t (&r)[NG], pvq_u32x2 (&b)[NG])
+template <int NG, int STAGE, bool B24>
+PVQ_HD void pvq_fast8_stage(const unsigned char *lds, const pvq_fast8_params &p, uint32_t (&r)[NG], pvq_u32x2 (&b)[NG])
 {
     uint32_t addr[NG], next[NG];
-    pvq_fast8_find<NG, STAGE>(lds, bk, shift, bl, r, addr);
+    pvq_fast8_find<NG, STAGE, B24>(lds, p, r, addr);
 #pragma unroll
     for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x2 *>(lds + addr[j]);
     bool miss = false, mj[NG];
@@ -197,7 +203,8 @@ PVQ_HD void pvq_fast8_stage(const unsigned char *lds, uint32_t bk, uint32_t shif
         mj[j] = next[j] >= b[j].x >> 16;
         miss = miss || mj[j];
     }
-    if (miss) {
+    // (24-bit indices: S2's entries name every block of their buckets)
+    if (!(STAGE == 2 && B24) && miss) {
 #pragma unroll
         for (int j = 0; j < NG; j++) {
             if (mj[j]) {
@@ -216,13 +223,13 @@ PVQ_HD void pvq_fast8_stage(const unsigned char *lds, uint32_t bk, uint32_t shif
 
 // S0 for NG stored indices, up to the places of the block entries in the tables: a caller that reads those entries from device memory can start S0 of its next indices
 // while it still decodes the current ones.  r = the indices, clamped to the last valid one.
-template <int NG>
+template <int NG, bool B24>
 PVQ_HD void pvq_fast8_s0_find(const unsigned char *lds, const pvq_fast8_params &p, const uint32_t (&c)[NG],
                               uint32_t (&r)[NG], uint32_t (&addr)[NG])
 {
 #pragma unroll
     for (int j = 0; j < NG; j++) r[j] = c[j] < p.n_minus_1 ? c[j] : p.n_minus_1;
-    pvq_fast8_find<NG, 0>(lds, p.bk0, p.s0, p.bl0, r, addr);
+    pvq_fast8_find<NG, 0, B24>(lds, p, r, addr);
 }
 
 // The rest of the decoder, from S0's block entries b (as read from the addresses that
@@ -231,7 +238,7 @@ PVQ_HD void pvq_fast8_s0_find(const unsigned char *lds, const pvq_fast8_params &
 // `emit(j, pair number, word)` as soon as its stage has found it, so that a consumer that folds
 // pairs into sums (the fused product) keeps one accumulator per group alive instead of the block
 // entries.
-template <int NG, typename Emit>
+template <int NG, bool B24, typename Emit>
 PVQ_HD void pvq_fast8_rest(const unsigned char *lds, const pvq_fast8_params &p,
                            uint32_t (&r)[NG], pvq_u32x4 (&b)[NG], Emit &&emit, uint32_t (&squares)[NG])
 {
@@ -239,14 +246,14 @@ PVQ_HD void pvq_fast8_rest(const unsigned char *lds, const pvq_fast8_params &p,
     pvq_u32x2 b1[NG], t[NG];
     pvq_fast8_settle<NG>(lds, r, b, [&](uint32_t (&out)[NG]) {
         uint32_t same[NG];
-        pvq_fast8_s0_find<NG>(lds, p, r, same, out);
+        pvq_fast8_s0_find<NG, B24>(lds, p, r, same, out);
     });
 #pragma unroll
     for (int j = 0; j < NG; j++) { emit(j, 0, b[j].z); acc[j] = b[j].w; }
-    pvq_fast8_stage<NG, 1>(lds, p.bk1, p.s1, p.bl1, r, b1);
+    pvq_fast8_stage<NG, 1, B24>(lds, p, r, b1);
 #pragma unroll
     for (int j = 0; j < NG; j++) { emit(j, 1, b1[j].y); acc[j] = pvq_fast8_add_squares(acc[j], b1[j].y); }
-    pvq_fast8_stage<NG, 2>(lds, p.bk2, p.s2, p.bl2, r, b1);
+    pvq_fast8_stage<NG, 2, B24>(lds, p, r, b1);
 #pragma unroll
     for (int j = 0; j < NG; j++) t[j] = *reinterpret_cast<const pvq_u32x2 *>(lds + p.t3 + (r[j] << 3));
 #pragma unroll
@@ -259,24 +266,24 @@ PVQ_HD void pvq_fast8_rest(const unsigned char *lds, const pvq_fast8_params &p,
 }
 
 // Whole decoder, one index set after the other.  `lds`: the blob (on the device: its copy in LDS).
-template <int NG, typename Emit>
+template <int NG, bool B24, typename Emit>
 PVQ_HD void pvq_fast8_decode_emit(const unsigned char *lds, const pvq_fast8_params &p,
                                   const uint32_t (&c)[NG], Emit &&emit, uint32_t (&squares)[NG])
 {
     uint32_t r[NG], addr[NG];
     pvq_u32x4 b[NG];
-    pvq_fast8_s0_find<NG>(lds, p, c, r, addr);
+    pvq_fast8_s0_find<NG, B24>(lds, p, c, r, addr);
 #pragma unroll
     for (int j = 0; j < NG; j++) b[j] = *reinterpret_cast<const pvq_u32x4 *>(lds + addr[j]);
-    pvq_fast8_rest<NG>(lds, p, r, b, emit, squares);
+    pvq_fast8_rest<NG, B24>(lds, p, r, b, emit, squares);
 }
 
 // The same with the pairs stored.
-template <int NG>
+template <int NG, bool B24>
 PVQ_HD void pvq_fast8_decode(const unsigned char *lds, const pvq_fast8_params &p,
                              const uint32_t (&c)[NG], uint32_t (&pairs)[NG][4], uint32_t (&squares)[NG])
 {
-    pvq_fast8_decode_emit<NG>(lds, p, c, [&](int j, int pair, uint32_t w) { pairs[j][pair] = w; }, squares);
+    pvq_fast8_decode_emit<NG, B24>(lds, p, c, [&](int j, int pair, uint32_t w) { pairs[j][pair] = w; }, squares);
 }
 
 // Host side: builds the blob for (8, K) if it fits `max_bytes`; returns false otherwise.

@@ -305,7 +305,9 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
     // the fused gain table replaces the 1/sqrt(n2) table at the end of the blob
     float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? fused_start(f) : f.p.blob_bytes));
     // what the bits of 2^22 + n2 lack to the place of a group's gain (multiples of 16: a code is or-ed into them)
-    const uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits), invs_at = f.p.invs - kFast8Squares;
+    uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits);
+    const uint32_t invs_at = f.p.invs - kFast8Squares;
+    if constexpr (AMP == 2) asm volatile("" : "+v"(gains_at));     // (a vector register: one of an instruction's two constants may be scalar)
     float *part = sqrtc_l + (AMP == 2 ? (fused_rows(f.p) << f.scale_bits) : 256);
 
     const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
         split_quad<CODES, B24>(f, g0, item[slot], n.q);
         fetch_quad<CODES, B24>(f, a, std::min<int64_t>(refill_row, r_last), g0, in_row, qo, item[slot]);
         uint32_t addr[kGroupsPerLane];
-        pvq_fast8_s0_find<kGroupsPerLane>(lds, f.p, n.q.c, n.r, addr);
+        pvq_fast8_s0_find<kGroupsPerLane, B24>(lds, f.p, n.q.c, n.r, addr);
 #pragma unroll
         for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>((j < kS0FromLds ? (const unsigned char *)lds : f.blob) + addr[j]);
     };
@@ -389,8 +391,8 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
                 for (int b = 0; b < NB; b++)
                     dot[j][b] = dot2_bf16(w, xr[b][4 * j + pair], pair == 0 ? 0.0f : dot[j][b]);
             };
-            if constexpr (AHEAD) pvq_fast8_rest<kGroupsPerLane>(lds, f.p, cu.r, cu.b, emit, squares);
-            else pvq_fast8_decode_emit<kGroupsPerLane>(lds, f.p, cu.q.c, emit, squares);
+            if constexpr (AHEAD) pvq_fast8_rest<kGroupsPerLane, B24>(lds, f.p, cu.r, cu.b, emit, squares);
+            else pvq_fast8_decode_emit<kGroupsPerLane, B24>(lds, f.p, cu.q.c, emit, squares);
             float acc[NB];
 #pragma unroll
             for (int b = 0; b < NB; b++) acc[b] = 0.0f;
@@ -451,7 +453,9 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
     __shared__ __align__(16) unsigned char lds[kLdsBytes];
     float *sqrtc_l = reinterpret_cast<float *>(lds + (AMP == 2 ? fused_start(f) : f.p.blob_bytes));
     // what the bits of 2^22 + n2 lack to the place of a group's gain (multiples of 16: a code is or-ed into them)
-    const uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits), invs_at = f.p.invs - kFast8Squares;
+    uint32_t gains_at = f.p.lds_bytes - (kFast8Squares << f.scale_bits);
+    const uint32_t invs_at = f.p.invs - kFast8Squares;
+    if constexpr (AMP == 2) asm volatile("" : "+v"(gains_at));     // (a vector register: one of an instruction's two constants may be scalar)
     float *part = sqrtc_l + (AMP == 2 ? (fused_rows(f.p) << f.scale_bits) : 256);
 
     const int64_t r_begin = (int64_t)blockIdx.x * rows_per_block;
@@ -510,7 +514,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
             split_quad<CODES, B24>(f, gl, raw[slot], n.q);      // (a slice's codes are whole words)
             fetch_next(raw[slot], raw_at[slot]);
             uint32_t addr[kGroupsPerLane];
-            pvq_fast8_s0_find<kGroupsPerLane>(lds, f.p, n.q.c, n.r, addr);
+            pvq_fast8_s0_find<kGroupsPerLane, B24>(lds, f.p, n.q.c, n.r, addr);
 #pragma unroll
             for (int j = 0; j < kGroupsPerLane; j++) n.b[j] = *reinterpret_cast<const pvq_u32x4 *>((j < kS0FromLds ? (const unsigned char *)lds : f.blob) + addr[j]);
         };
@@ -548,7 +552,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_row_kernel(fast8_launch f,
                     auto emit = [&](int j, int pair, uint32_t w) {
                         dot[j] = dot2_bf16(w, xr[4 * j + pair], pair == 0 ? 0.0f : dot[j]);
                     };
-                    pvq_fast8_rest<kGroupsPerLane>(lds, f.p, cu.r, cu.b, emit, squares);
+                    pvq_fast8_rest<kGroupsPerLane, B24>(lds, f.p, cu.r, cu.b, emit, squares);
                     float acc = 0.0f;
                     const uint32_t codes4 = cu.q.codes << 2;
 #pragma unroll
@@ -716,7 +720,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_mfma_kernel(fast8_launch f
                 c[1] = __builtin_amdgcn_alignbit(cur.w[1], cur.w[0], 24) & 0xFFFFFFu;
                 c[2] = __builtin_amdgcn_alignbit(cur.w[2], cur.w[1], 16) & 0xFFFFFFu;
                 c[3] = cur.w[2] >> 8;
-                pvq_fast8_decode<4>(lds, f.p, c, pr, squares);
+                pvq_fast8_decode<4, true>(lds, f.p, c, pr, squares);
                 const uint32_t codes = CODES ? cur.s[0] >> ((gq * sb) & 31u) : 0u;
                 float gains[4];
 #pragma unroll
@@ -918,7 +922,7 @@ __global__ __launch_bounds__(kMaxThreads) void decode8_kernel(fast8_launch f, pv
         const float srn = CODES ? sqrtf(cur_rn) : 1.0f;
         uint32_t c[kGroupsPerLane], prs[kGroupsPerLane][4], squares[kGroupsPerLane];
         item_indices<B24>(cur, gbase, c);
-        pvq_fast8_decode<kGroupsPerLane>(lds, f.p, c, prs, squares);
+        pvq_fast8_decode<kGroupsPerLane, B24>(lds, f.p, c, prs, squares);
 #pragma unroll
         for (int j = 0; j < kGroupsPerLane; j++) {
             // amp / sqrt(n2): the amplitude first (sqrt(center) * sqrt(row normaliser), or the stored

@@ -108,7 +108,8 @@ uint32_t append(std::vector<unsigned char> &blob, const std::vector<T> &v)
     return off;
 }
 
-bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, uint32_t max_bytes,
+// known: the shifts are those that the kernels know
+bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, bool known, uint32_t max_bytes,
                        std::vector<unsigned char> &blob, pvq_fast8_params &p)
 {
     // ---- block lists --------------------------------------------------------------------
@@ -178,16 +179,18 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, uint3
     }
     if (first > (1u << kFast8IndexBits)) return false;   // S1's block numbers must fit the entries
     first = 0;
+    uint64_t missed2 = 0;
     for (int k = 0; k <= K; k++) {
         const uint64_t front = best_front(s2, [&](uint64_t f) {
             std::vector<uint16_t> row;
             return build_next_bucket_row<uint16_t>(rows2[k], 0, N.at(4, k), s2, f, row);
         });
         bias2[k] = ((uint32_t)bk2.size() << s2) + (uint32_t)front;
-        build_next_bucket_row<uint16_t>(rows2[k], first, N.at(4, k), s2, front, bk2);
+        missed2 += build_next_bucket_row<uint16_t>(rows2[k], first, N.at(4, k), s2, front, bk2);
         first += (uint32_t)rows2[k].size();
     }
     if (first >= (1u << (16 - s2))) return false;   // S2's block numbers must fit the 16-bit entries
+    if (known && missed2 > 0) return false;         // (the kernels do not look)
     // a residual of S2 has 16 bits, also before a step to the following block (at most a bucket of S1 too large)
     if (((uint64_t)bk2.size() << s2) + ((uint64_t)1 << s1) > 65536) return false;
 
@@ -195,17 +198,17 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, uint3
     // sizes are known now; offsets of the rows that `meta` words point to must be fixed before the
     // block tables are written
     auto up16 = [](size_t x) { return (x + 15) & ~(size_t)15; };
+    size_t nblk0 = rows0[0].size(), nblk1 = 0, nblk2 = 0;
+    for (auto &r : rows1) nblk1 += r.size();
+    for (auto &r : rows2) nblk2 += r.size();
     size_t off = 0;
+    const size_t o_bl2 = off; off = up16(off + nblk2 * 8);   // (at 0: the kernels add nothing)
     const size_t o_bk0 = off; off = up16(off + bk0.size() * 4);
     const size_t o_bk1 = off; off = up16(off + bk1.size() * 4);
     const size_t o_bk2 = off; off = up16(off + bk2.size() * 2);
     const size_t o_t3 = off;  off = up16(off + t3.size() * 4);
-    size_t nblk0 = rows0[0].size(), nblk1 = 0, nblk2 = 0;
-    for (auto &r : rows1) nblk1 += r.size();
-    for (auto &r : rows2) nblk2 += r.size();
     const size_t o_bl0 = off; off = up16(off + nblk0 * 16);
     const size_t o_bl1 = off; off = up16(off + nblk1 * 8);
-    const size_t o_bl2 = off; off = up16(off + nblk2 * 8);
     // 1/sqrt(n2) comes last of what goes to LDS: a kernel that builds its own gain table leaves it out
     const size_t lds_bytes = off;
     const size_t o_invs = off; off = up16(off + (size_t)(K * K / 2 + 1) * 4);
@@ -240,9 +243,9 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, uint3
     }
 
     blob.clear();
-    bool ok = append(blob, bk0) == o_bk0 && append(blob, bk1) == o_bk1 && append(blob, bk2) == o_bk2 &&
+    bool ok = append(blob, bl2) == o_bl2 && append(blob, bk0) == o_bk0 && append(blob, bk1) == o_bk1 && append(blob, bk2) == o_bk2 &&
               append(blob, t3) == o_t3;
-    ok = ok && append(blob, bl0) == o_bl0 && append(blob, bl1) == o_bl1 && append(blob, bl2) == o_bl2 && append(blob, invs) == o_invs;
+    ok = ok && append(blob, bl0) == o_bl0 && append(blob, bl1) == o_bl1 && append(blob, invs) == o_invs;
     align16(blob);
     if (!ok || blob.size() != off) return false;
 
@@ -250,7 +253,7 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, uint3
     p.lds_bytes = (uint32_t)lds_bytes;
     p.n_minus_1 = (uint32_t)(N.at(8, K) - 1);
     p.bk0 = (uint32_t)o_bk0; p.bk1 = (uint32_t)o_bk1; p.bk2 = (uint32_t)o_bk2; p.t3 = (uint32_t)o_t3;
-    p.bl0 = (uint32_t)o_bl0; p.bl1 = (uint32_t)o_bl1; p.bl2 = (uint32_t)o_bl2;
+    p.bl0 = (uint32_t)o_bl0; p.bl1 = (uint32_t)o_bl1;
     p.invs = (uint32_t)o_invs - 2u * (uint32_t)(K & 1);
     p.s0 = s0; p.s1 = s1; p.s2 = s2;
     p.k2max = (uint32_t)(K * K);
@@ -267,14 +270,16 @@ bool pvq_fast8_build(int K, uint32_t max_bytes, std::vector<unsigned char> &blob
     int bits = 0;
     while (((uint64_t)1 << bits) < N.at(8, K)) bits++;
     // Finer buckets mean fewer block-by-block steps; take the finest combination that fits.  The
-    // base shifts follow the index width (for 24 bits: 11 / 8 / 3); S2 is coarsened first (its
+    // base shifts follow the index width (for 24 bits they would be pvq_fast8_shift24's); S2 is coarsened first (its
     // blocks are the most regular), then S0, and S1 last.
     static const int steps[][3] = {{0, 0, 0}, {0, 0, 1}, {1, 0, 1}, {1, 0, 2}, {2, 0, 2}, {2, 1, 2}, {3, 1, 2}, {3, 2, 2}};
+    if (bits == 24)
+        return build_with_shifts(K, N, pvq_fast8_shift24(0), pvq_fast8_shift24(1), pvq_fast8_shift24(2), true, max_bytes, blob, p);
     for (const auto &st : steps) {
         const int s0 = std::min(std::max(1, bits - 13) + st[0], (int)kFast8MaxShift);
         const int s1 = std::min(std::max(1, bits - 16) + st[1], (int)kFast8MaxShift1);
         const int s2 = std::min(std::max(1, bits - 21) + st[2], 6);
-        if (build_with_shifts(K, N, s0, s1, s2, max_bytes, blob, p)) return true;
+        if (build_with_shifts(K, N, s0, s1, s2, false, max_bytes, blob, p)) return true;
     }
     return false;
 }
@@ -292,7 +297,8 @@ extern "C" int pvq_fast_tables_selftest(int K, uint64_t first, uint64_t count, u
     if (!pvq_fast8_build(K, kFast8MaxBytes, blob, p)) return PVQ_E_UNSUPPORTED;
     for (uint64_t c = first; c < first + count && c < total; c++) {
         uint32_t cc[1] = {(uint32_t)c}, pr[1][4], nn[1];
-        pvq_fast8_decode<1>(blob.data(), p, cc, pr, nn);
+        if (total > (1u << 23) && total <= (1u << 24)) pvq_fast8_decode<1, true>(blob.data(), p, cc, pr, nn);
+        else pvq_fast8_decode<1, false>(blob.data(), p, cc, pr, nn);
         const uint32_t *pairs = pr[0];
         const uint32_t n2x2 = nn[0] - kFast8Squares;
         int y[8];
