@@ -208,8 +208,8 @@ typedef unsigned __int128 u128;
 u128 low128(const U512 &v) { return ((u128)v.limb[1] << 64) | v.limb[0]; }
 
 // Lays the blob out (pvq_walk.h has the layout's formulas) and fills it.  Bucket (e, f) of a guess row with mb fraction
-// bits holds the q whose float, as the decoder forms it from q | 1, lies in [2^e (1 + f / 2^mb), 2^e (1 + (f+1) / 2^mb));
-// its guess is the last threshold that is not above any of them.
+// bits holds the q whose float, as the decoder forms it from q | 1, lies in [2^e (1 + f / 2^mb), 2^e (1 + (f+1) / 2^mb)), in
+// rows of doubles those whose q + 1/2 lies in half that range; its guess is the last threshold that is not above any of them.
 template <int D, int W, int DX, int DA, int DB>
 bool fill_walk_tables(const SizeTable &t, std::vector<unsigned char> &blob, pvq_walk_params &p)
 {
@@ -233,7 +233,13 @@ bool fill_walk_tables(const SizeTable &t, std::vector<unsigned char> &blob, pvq_
         }
         T[2 * K + 2] = ~(u128)0;
         blob.resize(at + row_bytes(p, words), 0);
-        for (int j = 0; j < entries; j++)
+        const bool doubles = double_row(dp, W, DX, DA);
+        if (doubles && t.at(dp + 1, K).bit_length() > 52) return false;
+        for (int j = 0; doubles && j < entries; j++) {
+            const double v = j < entries - 1 ? (double)(uint64_t)T[j] * kDoubleUnit : HUGE_VAL;
+            memcpy(&blob[at + 8 * j], &v, 8);
+        }
+        for (int j = 0; !doubles && j < entries; j++)
             for (int w = 0; w < words; w++) {
                 const uint32_t v = (uint32_t)(T[j] >> (32 * w));
                 memcpy(&blob[words == 3 ? (w < 2 ? at + 8 * j + 4 * w : at + p.part_bytes[1] + 4 * j) : at + 4 * (words * j + w)], &v, 4);
@@ -251,11 +257,16 @@ bool fill_walk_tables(const SizeTable &t, std::vector<unsigned char> &blob, pvq_
         };
         int j = 0, above = 0;                                      // thresholds: the last <= from, the last <= to
         for (uint32_t b = 0; b < n; b++) {
-            // q from .. to: exact below 2^23, with what the roundings may move beyond it
+            // q from .. to: as floats exact below 2^23, with what the roundings may move beyond it
             u128 from = edge(b), to = edge(b + 1);
-            if (from >> 23) from -= from >> 21;
-            if (to >> 23) to += std::min(to >> 21, ~(u128)0 - to);
-            from -= from & 1;                                      // (q | 1)
+            if (doubles) {                                         // (of 2 q + 1, exact)
+                from /= 2;
+                to /= 2;
+            } else {
+                if (from >> 23) from -= from >> 21;
+                if (to >> 23) to += std::min(to >> 21, ~(u128)0 - to);
+                from -= from & 1;                                  // (q | 1)
+            }
             to = std::min(to, limit);                              // (exclusive)
             if (from >= to) { guess[b] = (unsigned char)j; continue; }
             while (T[j + 1] <= from) j++;
@@ -273,14 +284,16 @@ bool build_walk_tables(const SizeTable &t, int D, int K, int words, std::vector<
 {
     if (D > 32 || K > 127) return false;
     memset(&p, 0, sizeof p);
-    int fit_3q = 0, fit_half = 0, fit_quarter = 0;
-    for (int d = 1; d < D; d++) {
+    int fit_3q = 0, fit_half = 0, fit_quarter = 0, fit_double = 0;
+    for (int d = 1; d <= D; d++) {
         const int bits = t.at(d, K).bit_length();
+        if (bits <= 52) fit_double = d;
+        if (d == D) break;
         if (words >= 4 && bits <= 24 * words) fit_3q = d;
         if (words >= 2 && bits <= 16 * words) fit_half = d;
         if (words >= 4 && bits <= 8 * words) fit_quarter = d;
     }
-    pvq_walk_schedule(D, words, fit_3q, fit_half, fit_quarter, &p.dX, &p.dA, &p.dB);
+    pvq_walk_schedule(D, words, fit_3q, fit_half, fit_quarter, fit_double, &p.dX, &p.dA, &p.dB);
     p.K = K;
     U512 last = t.at(D, K);
     last.decrement();

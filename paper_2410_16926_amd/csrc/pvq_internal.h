@@ -19,7 +19,7 @@
 struct pvq_walk_params {
     uint32_t bytes;         // of the blob, the amplitude table in front included (a multiple of 16)
     int K;
-    int dX, dA, dB;         // the width schedule: dimensions above dX in `words` words, above dA in three quarters of them, above dB in half, the rest in a quarter
+    int dX, dA, dB;         // the width schedule: dimensions above dX in `words` words, above dA in three quarters of them (of two: as doubles), above dB in half, the rest in a quarter
     uint32_t more;          // bit DP: some bucket of row DP holds more than one threshold besides its guess
     uint32_t part_bytes[3]; // bytes of a row with entries of 4, 8 and 16 bytes (a row of 12-byte entries: the first two)
     uint32_t last_index[4]; // N(D,K) - 1

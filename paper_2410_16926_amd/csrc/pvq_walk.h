@@ -43,8 +43,12 @@ template <> struct wide<4> { using type = unsigned __int128; };
 
 // ---- layout of the blob (shared with the host builder) ---------------------------------------------------
 // Words of row DP's integers under the schedule (D, W, DX, DA, DB): dimensions (DP + 1 are left) above DX in W words,
-// above DA in three quarters, above DB in half of them, the rest in a quarter.
-constexpr int words_of_row(int dp, int W, int DX, int DA, int DB) { return dp >= DX ? W : dp >= DA ? 3 * W / 4 : dp >= DB ? W / 2 : W / 4; }
+// above DA in three quarters (of two words: in both, as doubles), above DB in half of them, the rest in a quarter.
+constexpr int words_of_row(int dp, int W, int DX, int DA, int DB) { return dp >= DX ? W : dp >= DA ? (W == 2 ? 2 : 3 * W / 4) : dp >= DB ? W / 2 : W / 4; }
+// Whether row DP keeps q + 1/2 and the thresholds as doubles (exact: q < 2^52), scaled by kDoubleUnit.
+constexpr bool double_row(int dp, int W, int DX, int DA) { return W == 2 && dp < DX && dp >= DA; }
+// the scale: 1/2, the least q + 1/2, gets the exponent that 1 has as a float, and the buckets start where those of floats do
+constexpr double kDoubleUnit = 0x1p-895;
 // Fraction bits of guess row DP, chosen so that a bucket of q holds one threshold besides the one its guess stands for
 // (the rows of few dimensions grow slowly and get finer buckets).  Enough for every K of the schedules
 // that have no search behind the guess (searches); with the others pvq_walk_params::more says for which rows they are not.
@@ -123,6 +127,17 @@ PVQ_HD uint32_t subtract(uint32_t *d, const uint32_t *a, const uint32_t *b)
 #endif
     for (int x = 0; x < WP; x++) d[x] = __builtin_subc(a[x], b[x], borrow, &borrow);
     return borrow;
+}
+
+PVQ_HD uint32_t double_high(double v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__double2hiint(v);
+#else
+    uint64_t u;
+    memcpy(&u, &v, 8);
+    return (uint32_t)(u >> 32);
+#endif
 }
 
 // One of a row's entries, or a guess, at a byte of the tables: LDS address in a kernel, where they start at 0 (the launch
@@ -208,17 +223,47 @@ PVQ_HD uint32_t walk_step(const unsigned char *tables, const pvq_walk_params &p,
     }
 }
 
+// walk_step for a row of doubles: no conversion in front of the guess, whose bucket is in q's upper bits as they are, and one
+// instruction where integers of two words take two.  v: q + 1/2, never 0, so that a difference's sign tells which is larger.
+// 14336 x 4096, D = 16, K = 33, integers / doubles: one vector 27.9 / 27.0 us, 16 vectors 38.9 / 37.3, to bfloat16 35.3 / 34.3 (vector
+// instructions of the product 448 / 420).  Groups of 32 with integers of four words keep q in them: the five rows that could have
+// doubles (at most 52 bits, more than 32) would save three instructions in a hundred.  Squares by the dot instruction of bfloat16
+// pairs instead of a multiply-add each took longer (D = 32, K = 60, one vector 45.4 / 45.7).
+template <int DP, int D, int W, int DX, int DA, int DB, uint32_t NEXT>
+PVQ_HD uint32_t walk_step_double(const unsigned char *tables, uint32_t at, uint32_t ones, double &v)
+{
+    constexpr int MB = guess_bits(DP, D);
+    constexpr uint32_t guesses = guess_row(DP, D, W, DX, DA, DB) - (127u << MB);
+    const uint32_t j = table_at<uint8_t>(tables, guesses + (double_high(v) >> (20 - MB)));
+    const double d0 = v - table_at<double>(tables, at + 8u * j);
+    const double d1 = v - table_at<double>(tables, (at + 8u * (j + 1u - NEXT)) + 8u * NEXT);
+    const uint32_t borrow = !(d1 > 0.0);
+    uint32_t unused;
+    v = borrow ? d0 : d1;
+    return __builtin_subc(j, ones, borrow, &unused);               // j + 1 - borrow
+}
+
 // The state of a walk: the residual, pulses left, sum of squares.
 template <int D, int W, int DX, int DA, int DB, uint32_t NEXT>
 struct walk_state {
     uint32_t q[W];
     uint32_t k, at, more, ones;
     float n2;
+    double v;                                                      // in rows of doubles: (q + 1/2) * kDoubleUnit
 
     template <int I, typename Emit>
     PVQ_HD void coordinate(const unsigned char *tables, const pvq_walk_params &p, Emit &emit)
     {
-        const uint32_t j = walk_step<D - 1 - I, D, W, DX, DA, DB, NEXT>(tables, p, at, more, ones, q);
+        constexpr int DP = D - 1 - I;
+        uint32_t j;
+        if constexpr (double_row(DP, W, DX, DA)) {
+            if constexpr (I == 0 || !double_row(DP + 1, W, DX, DA))
+                v = fma((double)q[1], kDoubleUnit * 0x1p32, fma((double)q[0], kDoubleUnit, kDoubleUnit * 0.5));
+            j = walk_step_double<DP, D, W, DX, DA, DB, NEXT>(tables, at, ones, v);
+            if constexpr (!double_row(DP - 1, W, DX, DA)) q[0] = (uint32_t)(v * (1.0 / kDoubleUnit));
+        } else {
+            j = walk_step<DP, D, W, DX, DA, DB, NEXT>(tables, p, at, more, ones, q);
+        }
         at += row_bytes(p, words_of_row(D - 1 - I, W, DX, DA, DB));
         const uint32_t C = j >> 1;
         const float m = (float)(k - C);
@@ -264,13 +309,16 @@ PVQ_HD float unrank_walk(typename wide<W>::type c, const unsigned char *tables, 
 
 // Which width schedule a context gets: fit_3q / fit_half / fit_quarter = the largest number of dimensions d whose
 // N(d,K) fits three quarters / half / a quarter of the index's words.  Names only schedules listed in PVQ_WALK_DISPATCH.
-inline void pvq_walk_schedule(int D, int words, int fit_3q, int fit_half, int fit_quarter, int *dX, int *dA, int *dB)
+// fit_double = the largest one whose N(d,K) is at most 2^52.  Groups of 16 whose last 8 dimensions fit a word have doubles
+// above them, all or (K = 34 to 36) all but the first: N(15,36) < 2^52.
+inline void pvq_walk_schedule(int D, int words, int fit_3q, int fit_half, int fit_quarter, int fit_double, int *dX, int *dA, int *dB)
 {
     *dA = 0; *dB = 0;
     if (D == 16 && words == 2 && fit_half >= 8) *dA = 8;
     if (D == 32 && words == 2 && fit_half >= 12) *dA = 12;
     if (D == 32 && words == 4 && fit_half >= 15 && fit_quarter >= 6) { *dA = 15; *dB = 6; }
     *dX = *dA;
+    if (D == 16 && words == 2 && *dA == 8) *dX = fit_double >= 16 ? 16 : 15;
     if (D == 32 && words == 4 && *dA == 15 && fit_3q >= 28) *dX = 28;
 }
 
@@ -284,7 +332,7 @@ inline void pvq_walk_schedule(int D, int words, int fit_3q, int fit_half, int fi
         }                                                                                                    \
         if ((D_) == 16) {                                                                                    \
             if ((W_) == 1) return CALL(16, 1, 0, 0, 0);                                                      \
-            if ((W_) == 2) { if ((dA_) == 8) return CALL(16, 2, 8, 8, 0); return CALL(16, 2, 0, 0, 0); }     \
+            if ((W_) == 2) { if ((dX_) == 16) return CALL(16, 2, 16, 8, 0); if ((dX_) == 15) return CALL(16, 2, 15, 8, 0); return CALL(16, 2, 0, 0, 0); }     \
             return CALL(16, 4, 0, 0, 0);                                                                     \
         }                                                                                                    \
         if ((W_) == 1) return CALL(32, 1, 0, 0, 0);                                                          \

@@ -11,7 +11,7 @@
 //
 // Widths: the integers of a step with d dimensions left are below N(d,K), so the later coordinates run in
 // narrower arithmetic: dimensions above DX in W words, above DA in 3W/4, above DB in W/2, the rest in W/4 (for D = 16,
-// K = 33: 64 bits down to nine dimensions, 32 bits from eight on, N(8,33) < 2^32).  The last two coordinates
+// K = 33: doubles, which hold 52 bits, down to nine dimensions, 32 bits from eight on, N(8,33) < 2^32).  The last two coordinates
 // need no table: the thresholds of row 1 are 0, 1, 2, 4, 6, ..., and P(1,k) = {+k, -k}.
 #include <hip/hip_runtime.h>
 
@@ -321,9 +321,9 @@ struct gemv_teams {
     int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves
 };
 
-// Waves of a SIMD that a kernel's registers are to leave room for: eight in tiles of 16 rows of groups of 32 with up to two words,
-// which the schedule of the reads would pass by a few registers (next_from_product); else those of a workgroup of 1024 lanes.
-constexpr int gemv_waves(int D, int W, int R) { return D == 32 && W <= 2 && R == 16 ? 8 : 4; }
+// Waves of a SIMD that a kernel's registers are to leave room for: eight in tiles of 16 rows of groups of 16 and 32 with up to
+// two words, which the schedule of the reads would pass by a few registers (next_from_product); else those of a workgroup of 1024 lanes.
+constexpr int gemv_waves(int D, int W, int R) { return D >= 16 && W <= 2 && R == 16 ? 8 : 4; }
 
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
 __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)

@@ -163,3 +163,11 @@ def test_one_probe_per_coordinate_decoder_limits():
     with pytest.raises(pvq.PvqError) as e:
         pvq.pvq_walk_tables_selftest(32, 127)       # index beyond 128 bits
     assert e.value.status == -2
+
+
+@pytest.mark.parametrize("K", [13, 27, 33, 34, 36])
+def test_rows_of_doubles_replay_sampled_indices(K):
+    # groups of 16 whose q is kept as a double while more than eight dimensions are left: in all rows while N(16,K) has at most
+    # 52 bits (K <= 33), else in all but the first; the smallest and the largest K that have such rows
+    bad, sched, _ = pvq.pvq_walk_tables_selftest(16, K, seed=K, count=60000)
+    assert bad == 0 and sched == (8, 0)

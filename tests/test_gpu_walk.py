@@ -122,3 +122,24 @@ def test_products_with_several_teams_of_waves(D, K, bits, rows, groups):
         for tile_rows in (4, 16):
             gu.assert_gemv_close(pvq.pvq_decode_gemv_on(ctx, packed, x, "walk", tile_rows).cpu().numpy(), want, scale)
     ctx.close()
+
+
+@pytest.mark.parametrize("K", [13, 33, 34, 36])
+def test_rows_of_doubles(K):
+    # the first and last indices, and points on and beside the axes, in the kernels that keep q as a double
+    D, groups = 16, 33
+    W = si.gaussian_weights(70, D * groups, 0.02, seed=si.BASE_SEED + 660 + K, rotate=False)
+    for i in range(D):
+        W[i, :D], W[i, D:2 * D] = 0.0, 0.0
+        W[i, i], W[i, D + i] = 1.0, -1.0                    # +K and -K in one place
+        W[i, D + (i + 5) % D] = 0.9 / K                     # nearly
+    ctx = pvq.pvq_ctx_create(D, K)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, D, K))
+    gu.assert_decode_close(pvq.pvq_decode(ctx, packed, torch.float32).cpu().numpy(), ref)
+    for batch in (1, 16):
+        xf, xb = si.activations(batch, D * groups, seed=K + batch)
+        want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+        for _, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
+            gu.assert_gemv_close(y, want, scale)
+    ctx.close()
