@@ -373,7 +373,7 @@ def pvq_decode_gemv(ctx: PvqContext, packed: Packed, x, out=None):
 
 
 def pvq_decode_gemv_on(ctx: PvqContext, packed: Packed, x, decoder: str, tile_rows: int = 0, out=None):
-    """Diagnostics: pvq_decode_gemv on the decoder named ("table" or "walk", the latter with tiles of 4 or 16 rows, 0 = as
+    """Diagnostics: pvq_decode_gemv on the decoder named ("table" or "walk", the latter with tiles of 4, 8 (up to 8 vectors) or 16 rows, 0 = as
     its rule has it) instead of the one that the rule picks."""
     import torch
     batch = x.shape[0]

@@ -45,7 +45,7 @@ int pvq_decode_gemv_plan(const struct pvq_ctx *ctx, int64_t rows, int64_t cols, 
 /*
  * pvq_decode_gemv on the decoder named instead of the one that its rule picks: the table decoder (groups of 8;
  * PVQ_E_UNSUPPORTED where it cannot take the product), or the coordinate-by-coordinate one, there with tiles of
- * `tile_rows` rows (4 or 16; 0: as its rule has it; 0 for the table decoder).  Everything else as in pvq_decode_gemv.
+ * `tile_rows` rows (4, 8 with up to 8 vectors, or 16; 0: as its rule has it; 0 for the table decoder).  Everything else as in pvq_decode_gemv.
  */
 enum { PVQ_PRODUCT_BY_RULE = 0, PVQ_PRODUCT_TABLE = 1, PVQ_PRODUCT_WALK = 2 };
 int pvq_decode_gemv_on(const struct pvq_ctx *ctx, const uint32_t *index, const void *scale, const float *rownorm,

@@ -794,7 +794,7 @@ extern "C" int pvq_decode_gemv_on(const pvq_ctx *c, const uint32_t *index, const
                                   int decoder, int tile_rows)
 {
     if (decoder != PVQ_PRODUCT_TABLE && decoder != PVQ_PRODUCT_WALK) return PVQ_E_INVALID_ARG;
-    if (tile_rows != 0 && (decoder != PVQ_PRODUCT_WALK || (tile_rows != 4 && tile_rows != 16))) return PVQ_E_INVALID_ARG;
+    if (tile_rows != 0 && (decoder != PVQ_PRODUCT_WALK || (tile_rows != 4 && tile_rows != 16 && (tile_rows != 8 || batch > 8)))) return PVQ_E_INVALID_ARG;
     return decode_gemv(c, index, scale, rownorm, rows, cols, x, batch, ldx, y, ldy, stream, decoder, tile_rows);
 }
 

@@ -164,7 +164,7 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *ctx, const pvq_encode_ar
 // coordinate-by-coordinate decoder with one table probe per coordinate (pvq_walk.hip)
 bool pvq_walk_usable(const pvq_ctx *ctx);
 hipError_t pvq_walk_launch_decode(const pvq_ctx *ctx, const pvq_decode_args &a, int out_dtype, hipStream_t s);
-// tile_rows: 4 or 16 rows a tile, or 0 for the split that should take least
+// tile_rows: 4, 8 (up to 8 vectors) or 16 rows a tile, or 0 for the split that should take least
 hipError_t pvq_walk_launch_gemv(const pvq_ctx *ctx, const pvq_decode_args &a, int tile_rows, hipStream_t s);
 
 // D = 8 / 24-bit encoder (pvq_encode8.hip)

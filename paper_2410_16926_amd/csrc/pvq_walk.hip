@@ -43,18 +43,12 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 
-// the value of lane L of the lane's quad
-template <int L>
-__device__ inline float quad_lane(float v)
-{
-    return __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), L * 0x55, 0xF, 0xF, false));
-}
-
-// the sum over the lanes of the same place in their quads, in every lane: rotations by 4 and 8 inside the rows of 16, then
+// the sum over the lanes of the same place among R (4 or 8), in every lane: rotations by 4 and 8 inside the rows of 16, then
 // across the rows
-__device__ inline float sum_over_quads(float v)
+template <int R>
+__device__ inline float sum_over_columns(float v)
 {
-    v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x124, 0xF, 0xF, false));
+    if constexpr (R == 4) v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x124, 0xF, 0xF, false));
     v += __uint_as_float((uint32_t)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(v), 0x128, 0xF, 0xF, false));
     v += __shfl_xor(v, 16, kWave);
     return v + __shfl_xor(v, 32, kWave);
@@ -304,18 +298,21 @@ __global__ __launch_bounds__(kMaxThreads) void decode_walk_kernel(walk_launch wl
 }
 
 // Decode fused into y = W_hat x for up to 16 vectors in one pass.  A wave's 64 groups are R rows x 64/R neighbouring group
-// columns (lane = row + R column), so that a lane's own pulses, exact in bfloat16, are its part of the A operand of a
-// matrix instruction that computes 64/R blocks at once, each block a group column of R rows with activations of its own:
-// 16 x 16 x 4 with four blocks (R = 16, 16 vectors) or 4 x 4 x 4 with sixteen (R = 4, four vectors, NV of them for 4 NV).
+// columns (lane = row + R column), so that a lane's own pulses, exact in bfloat16, are its part of one operand of a
+// matrix instruction that computes several blocks at once, each of a group column's rows with the column's activations:
+// 16 x 16 x 4 with four blocks (R = 16, 16 vectors) or 4 x 4 x 4 with sixteen (R = 4, four vectors, NV of them for 4 NV).  R = 8 is
+// 4 x 4 x 4 too: a group column is two blocks, which hold four vectors each and by the instruction's broadcast both take those of one
+// of them.  A load of activations fetches R vectors of 64/R columns, 64 places that lie apart, so that with few rows a tile a
+// unit's loads take as long as its arithmetic (5 to 8 vectors, R = 4: two loads a column for four rows; R = 8: one for eight).
 // D/4 of these in a row give the dot products of whole groups, whose gains (one per row and block) are multiplied
 // afterwards: products exact in float32, as on the vector ALUs.  A workgroup takes R rows at a time, its waves take the
 // columns in turn, and their sums meet in LDS, so that a few rows fill the chip as well.  Where the tables leave room for one
 // workgroup to a unit, its waves are several teams, each with a tile of its own.
-// Bound by the vector instructions of the walk: 22 a coordinate in all for D = 16, K = 33 (32 us of issue in a launch of 34
-// on 14336 x 4096), 26 for D = 32, K = 60 (40 of 51), and 3 to 4 LDS reads (10 and 17 us).  14336 x 4096, D = 16, K = 33,
-// 4-bit codes, 1 / 4 / 5 / 16 vectors: 33 / 32 / 34 / 40 us, where passes of 4, 2 and 1 vectors on the vector ALUs, a wave
-// per row, took 48 / 64 / 110 / 254; D = 32, K = 60: 46 / 49 / 53 / 50 (109 / 203 / 317 / 809); 84 x 11776, D = 32, 11
-// vectors: 17 us (408); 139 x 864, D = 16, one vector: 4.7 us (5.9).
+// Bound by the vector instructions of the walk, 19 a coordinate in all for D = 16, K = 33 and 26 for D = 32, K = 60, and 3 to 4 LDS
+// reads (10 and 17 us on 14336 x 4096).  14336 x 4096, D = 16, K = 33,
+// float32 amplitudes, 1 / 4 / 5 / 8 / 16 vectors: 27 / 29 / 29 / 30 / 37 us (28 / 29 / 32 / 41 / 39 with tiles of 4 and 16 rows only and
+// integers for doubles); D = 32, K = 60: 40 / 41 / 42 / 43 / 50 (45 / 48 / 52 / 57 / 50); passes of 4, 2 and 1 vectors on the vector
+// ALUs, a wave per row, took 48 / 64 / 110 / - / 254 and 109 / 203 / 317 / - / 809.
 struct gemv_teams {
     int waves, teams;
     int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves
@@ -328,10 +325,10 @@ constexpr int gemv_waves(int D, int W, int R) { return D >= 16 && W <= 2 && R ==
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
 __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)
 {
-    static_assert(R == 16 ? NV == 4 : R == 4, "tiles");
+    static_assert(R == 16 ? NV == 4 : R == 8 ? NV <= 2 : R == 4, "tiles");
     using T = typename wide<W>::type;
     constexpr int CG = kWave / R;                  // group columns of a wave
-    constexpr int XV = R == 16 ? 1 : NV;           // vectors whose activations a lane holds
+    constexpr int XV = R == 4 ? NV : 1;            // vectors whose activations a lane holds
     constexpr int XW = D / 8;                      // 16-byte words of one group's activations
     constexpr int kSums = 4 * R * NV;              // of a tile: rows x vectors
     extern __shared__ __align__(16) unsigned char lds[];
@@ -359,7 +356,7 @@ __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_ke
     const uint16_t *x0[XV];
 #pragma unroll
     for (int v = 0; v < XV; v++)
-        x0[v] = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)(b0 + std::min(4 * v + lane % (R == 16 ? 16 : 4), vectors - 1)) * a.ldx;
+        x0[v] = reinterpret_cast<const uint16_t *>(a.x) + (int64_t)(b0 + std::min(R * v + lane % R, vectors - 1)) * a.ldx;
     const int stride = (int)gridDim.x * teams;
     // (a team without a tile of its own, in a workgroup's last turn, fetches the last one and leaves it)
     fetch(std::min((int)blockIdx.x * teams + team, row_tiles - 1), wave);   // (there are no more waves than chunks)
@@ -368,9 +365,10 @@ __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_ke
     for (int first = (int)blockIdx.x * teams; first < row_tiles; first += stride, turn++) {
         const int tile = first + team;
         const bool live = tile < row_tiles;
-        f32x4 acc[XV];                             // R = 16: rows 4 (lane / 16) + r, vector lane % 16; else row r, vector 4 v + lane % 4, own block
+        constexpr int AV = R == 16 ? 1 : NV;
+        f32x4 acc[AV];                             // R = 16: rows 4 (lane / 16) + r, vector lane % 16; else the lane's own row, vector 4 v + r
 #pragma unroll
-        for (int v = 0; v < XV; v++) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int v = 0; v < AV; v++) acc[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         for (int chunk = live ? wave : chunks; chunk < chunks; chunk += waves) {
             const T c = group_index<W>(nx, g_nx, wl.index_bits);
             const float amp = group_amp<W>(nx, g_nx, wl.scale_bits, sqrtc);
@@ -383,13 +381,13 @@ __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_ke
             const bool here = chunk + waves < chunks;
             fetch(here ? tile : std::min(tile + stride, row_tiles - 1), here ? chunk + waves : wave);
             f32x16 out16;
-            f32x4 out4[XV];
+            f32x4 out4[AV];
             if constexpr (R == 16) {
 #pragma unroll
                 for (int i = 0; i < 16; i++) out16[i] = 0.0f;
             } else {
 #pragma unroll
-                for (int v = 0; v < XV; v++) out4[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+                for (int v = 0; v < AV; v++) out4[v] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
             }
             uint32_t pair[2];
             float even = 0.0f;
@@ -398,12 +396,19 @@ __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_ke
                 pair[(i >> 1) & 1] = __builtin_amdgcn_perm(__float_as_uint(minus_y), __float_as_uint(even), 0x07060302u);
                 if ((i & 3) != 3) return;
                 const bf16x4 y4 = __builtin_bit_cast(bf16x4, make_uint2(pair[0], pair[1]));
-#pragma unroll
-                for (int v = 0; v < XV; v++) {
+                auto x4 = [&](int v) {
                     const uint4 q = x[v][i / 8];
-                    const bf16x4 x4 = __builtin_bit_cast(bf16x4, (i & 4) ? make_uint2(q.z, q.w) : make_uint2(q.x, q.y));
-                    if constexpr (R == 16) out16 = __builtin_amdgcn_mfma_f32_16x16x4bf16_1k(y4, x4, out16, 0, 0, 0);
-                    else out4[v] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(y4, x4, out4[v], 0, 0, 0);
+                    return __builtin_bit_cast(bf16x4, (i & 4) ? make_uint2(q.z, q.w) : make_uint2(q.x, q.y));
+                };
+                // (R = 8: the two blocks of a group column take the activations of its first or second block)
+                if constexpr (R == 16) {
+                    out16 = __builtin_amdgcn_mfma_f32_16x16x4bf16_1k(y4, x4(0), out16, 0, 0, 0);
+                } else if constexpr (R == 8) {
+                    out4[0] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(x4(0), y4, out4[0], 1, 0, 0);
+                    if constexpr (NV == 2) out4[1] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(x4(0), y4, out4[1], 1, 1, 0);
+                } else {
+#pragma unroll
+                    for (int v = 0; v < NV; v++) out4[v] = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(x4(v), y4, out4[v], 0, 0, 0);
                 }
             });
             float gain = norm_gain(-amp, n2);
@@ -420,36 +425,35 @@ __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_ke
                 if ((chunk + 1) * CG > G) {        // (both 0: the gain and the dot products of the last group may be infinite)
                     gain = chunk * CG + col_l < G ? gain : 0.0f;
 #pragma unroll
-                    for (int v = 0; v < XV; v++)
+                    for (int v = 0; v < AV; v++)
 #pragma unroll
                         for (int r = 0; r < 4; r++) out4[v][r] = chunk * CG + col_l < G ? out4[v][r] : 0.0f;
                 }
-                const float g4[4] = {quad_lane<0>(gain), quad_lane<1>(gain), quad_lane<2>(gain), quad_lane<3>(gain)};
 #pragma unroll
-                for (int v = 0; v < XV; v++)
+                for (int v = 0; v < AV; v++)
 #pragma unroll
-                    for (int r = 0; r < 4; r++) acc[v][r] = fmaf(g4[r], out4[v][r], acc[v][r]);
+                    for (int r = 0; r < 4; r++) acc[v][r] = fmaf(gain, out4[v][r], acc[v][r]);
             }
         }
         const int64_t row0 = (int64_t)tile * R;
         auto write = [&](const float *from, int t) {               // sum t of the tile, over the waves
-            const int vec = R == 16 ? (t >> 2) & 15 : t >> 2;
-            const int64_t row = row0 + (R == 16 ? 4 * (t >> 6) : 0) + (t & 3);
+            const int vec = R == 16 ? (t >> 2) & 15 : 4 * (t / (4 * R)) + (t & 3);
+            const int64_t row = row0 + (R == 16 ? 4 * (t >> 6) + (t & 3) : t / 4 % R);
             if (vec >= vectors || row >= a.rows) return;           // (no row of a team without a tile)
             const float norm = wl.scale_bits == 0 ? 1.0f : sqrtf(a.rownorm[row]);
             float v = from[t];
             for (int w = 1; w < waves; w++) v += from[w * kSums + t];
             a.y[(int64_t)(b0 + vec) * a.ldy + row] = v * norm;
         };
-        if constexpr (R == 4) {
-            // The sixteen blocks' sums, then the waves': two places in turn, so that the wave that writes this tile is done
+        if constexpr (R != 16) {
+            // The group columns' sums, then the waves': two places in turn, so that the wave that writes this tile is done
             // with its place when the others come to use it again, one barrier later.
             float *to = sums + (turn & 1) * (waves_all * kSums);
 #pragma unroll
-            for (int v = 0; v < XV; v++) {
+            for (int v = 0; v < AV; v++) {
 #pragma unroll
-                for (int r = 0; r < 4; r++) acc[v][r] = sum_over_quads(acc[v][r]);
-                if (lane < 4) *reinterpret_cast<f32x4 *>(to + wave * kSums + 16 * v + 4 * lane) = acc[v];
+                for (int r = 0; r < 4; r++) acc[v][r] = sum_over_columns<R>(acc[v][r]);
+                if (lane < R) *reinterpret_cast<f32x4 *>(to + wave * kSums + 4 * R * v + 4 * lane) = acc[v];
             }
             __syncthreads();
             if (wave == turn % waves && lane < kSums) write(to, lane);
@@ -582,26 +586,36 @@ size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
 
 // The split that should take least, from what a wave's 64 groups take in clocks: alone, as a chain of table reads; of
 // a SIMD's issue slots, when several waves share it; of the unit's loads of activations, which a tile of four rows
-// repeats four times as often (11 bytes a clock); and what a tile takes besides.  These are estimates (a line each through
-// products of D = 8, 16 and 32), not a bound: of 234 products (six contexts, 64 x 4096 to 8192 x 28672, 1 to 16 vectors)
-// the split picked is 6 % slower than the best one in the median, 18 % at the ninth decile, 47 % at the worst.  It picks
-// tiles of 16 rows for more than four vectors on large matrices (D = 32, 14336 x 4096, 16 vectors: 50 us, with four rows
-// 79), four rows while those would leave units idle (1289 x 16384, 11 vectors: 37 us, with sixteen 50).
-// How many workgroups a unit holds follows from their LDS and from the kernel's registers (simd4, simd16: waves of a
-// SIMD, for tiles of 4 and 16 rows); a workgroup more than that waits for a whole one (D = 16, K = 59, one vector on
+// repeats four times as often (11 bytes a clock) and one of eight once for every eight vectors; and what a tile takes besides.  These
+// are estimates (a line each through products of D = 8, 16 and 32), not a bound: of 234 products (six contexts, 64 x 4096 to
+// 8192 x 28672, 1 to 16 vectors) the split picked among tiles of 4 and 16 rows is 6 % slower than the best one in the median, 18 % at
+// the ninth decile, 47 % at the worst.  Tiles of 16 rows are for more than four vectors on large matrices (D = 32, 14336 x 4096, 16
+// vectors: 50 us, with four rows 79), of four rows where those would leave units idle (1289 x 16384, 11 vectors: 37 us, with sixteen 50),
+// of eight for up to eight vectors on large matrices (us, with eight rows / as it was with four or sixteen, 1 and 8 vectors):
+//   14336 x 4096, D = 32, K = 60: 40 / 45, 43 / 57;  D = 16, K = 33: 28.5 / 27.2 (fewer waves in flight: four rows), 30 / 41
+//   28672 x 8192, D = 16, K = 33: 92 / 108, 103 / 115;  14681 x 2560, D = 32, K = 60: 39 / 63, 42 / 33 (sixteen rows)
+// Tiles of sixteen rows, where the estimate picked those, are slower than of eight with groups of up to 16 and no search behind the guess
+// (above); with groups of 32 and with a search they are 6 % to 25 % faster or within 3 % (28672 x 8192, 8 vectors, D = 32, K = 60:
+// 150 us, with eight 163; D = 16, K = 45: 130, 138).
+// How many workgroups a unit holds follows from their LDS and from the kernel's registers (simd4, simd8, simd16: waves of a
+// SIMD, for tiles of 4, 8 and 16 rows); a workgroup more than that waits for a whole one (D = 16, K = 59, one vector on
 // 14336 x 4096: 114 us where three copies of the tables were thought to fit, with two 63).
-// tile_rows: only tiles of so many rows are looked at (0: both).
-gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows, int simd4, int simd16)
+// tile_rows: only tiles of so many rows are looked at (0: all).
+gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vectors, int tile_rows, int simd4, int simd8, int simd16)
 {
     gemv_split best = {0, 0, 0, 0};
     double least = 0;
     const double chain = 280.0 * c->D, issue = 4.0 * (80.0 + c->D * (c->words == 1 ? 14.0 : c->words == 2 ? 17.0 : 25.0));
-    for (int R = 4; R <= 16; R += 12) {
+    int in_flight = 0;                             // waves of a unit with the best split into tiles of 4 or 16 rows
+    for (const int R : {4, 16, 8}) {
         if (tile_rows ? R != tile_rows : R == 16 && vectors <= 4) continue;
-        const int nv = vectors <= 4 ? 1 : vectors <= 8 ? 2 : 4, sums = R == 16 ? 256 : 16 * nv;
-        const double loads = c->D * 128.0 / 11.0 * (R == 16 ? 1 : nv);
-        const int64_t tiles = (rows + R - 1) / R, chunks = (groups + kWave / R - 1) / (kWave / R);
-        const int64_t tiles_unit = (tiles + units() - 1) / units();
+        // (with one tile of four rows to a unit, eight would leave half of them idle)
+        if (R == 8 && !tile_rows && (rows <= 4 * units() || (best.rows == 16 && (c->D > 16 || c->walk.more != 0)))) continue;
+        const int nv = vectors <= 4 ? 1 : vectors <= 8 ? 2 : 4, sums = R == 16 ? 256 : 4 * R * nv;
+        if (R == 8 && nv > 2) continue;
+        const double loads = c->D * 128.0 / 11.0 * (R == 4 ? nv : R == 8 ? nv / 2.0 : 1.0);
+        const int64_t tiles = (rows + R - 1) / R;
+        const int chunks = ((int)groups + kWave / R - 1) / (kWave / R), tiles_unit = (int)((tiles + units() - 1) / units());
         bool most = true;                          // the most waves that have a chunk each
         for (int waves = 16; waves >= 1; waves -= waves > 8 ? 4 : waves > 4 ? 2 : 1) {
             if (waves > chunks) continue;
@@ -609,8 +623,8 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
             most = false;
             const size_t lds = gemv_lds(c, waves, R, sums);
             if (lds > 160 * 1024) continue;
-            const int resident = 4 * (R == 16 ? simd16 : simd4);                       // waves of a unit
-            int64_t blocks = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(resident / waves, (int64_t)unit_copies(lds)), tiles_unit));
+            const int resident = 4 * (R == 16 ? simd16 : R == 8 ? simd8 : simd4);            // waves of a unit
+            const int blocks = std::max(1, std::min(std::min(resident / waves, unit_copies(lds)), tiles_unit));
             // One workgroup to a unit, and a row too short for its waves: more teams.  D = 32, one vector on 14336 x 4096,
             // K = 68 / 80 / 105: two teams of eight 57 / 63 / 71 us (before the walk's search became shorter eight waves took
             // 145 / 170 / 171, two teams 91 / 108 / 108).
@@ -618,10 +632,17 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
             if (all && unit_copies(c->walk.bytes) == 1)
                 while (teams < tiles_unit && (teams + 1) * waves <= std::min(resident, 16) && gemv_lds(c, (teams + 1) * waves, R, sums) <= 160 * 1024) teams++;
             const double turns = (double)((tiles_unit + blocks * teams - 1) / (blocks * teams)), steps = (double)((chunks + waves - 1) / waves);
-            const double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
-                                         (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
+            double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
+                                   (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
+            // Fewer waves in flight than with tiles of 4 or 16 rows hide less (14336 x 4096, D = 16, K = 33, one vector: 28
+            // waves with eight rows 28.5 us, 32 with four 27.2; 8192 x 14336, D = 32, K = 80: 12 waves 122, 16 114), and groups
+            // of 32 gain nothing where the estimates are equal (8173 x 22528, K = 50, one vector: 111, with four rows 107).
+            const int here = blocks * teams * waves;
+            if (R == 8 && here < in_flight) cost *= 1.5 - 0.5 * here / in_flight;
+            if (R == 8 && c->D == 32) cost *= 1.01;
             if (best.rows == 0 || cost < least) {
                 least = cost;
+                if (R != 8) in_flight = here;
                 best = {R, waves, teams, (unsigned)std::min<int64_t>((tiles + teams - 1) / teams, (int64_t)units() * blocks)};
             }
         }
@@ -649,10 +670,14 @@ hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, int tile_rows
                                             vectors <= 4 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 1>>()
                                             : vectors <= 8 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 2>>()
                                                            : waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 4, 4>>(),
+                                            vectors <= 4 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 8, 1>>()
+                                                         : waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 8, 2>>(),
                                             waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 16, 4>>());
         if (split.rows == 0) return hipErrorInvalidValue;          // (no LDS left beside the tables: only where tile_rows asks for 16)
         hipError_t e;
-        if (split.rows == 16) e = launch_gemv_pass<D, W, DX, DA, DB, 16, 4>(c, a, b0, vectors, split, s);
+        if (split.rows == 8 && vectors <= 4) e = launch_gemv_pass<D, W, DX, DA, DB, 8, 1>(c, a, b0, vectors, split, s);
+        else if (split.rows == 8) e = launch_gemv_pass<D, W, DX, DA, DB, 8, 2>(c, a, b0, vectors, split, s);
+        else if (split.rows == 16) e = launch_gemv_pass<D, W, DX, DA, DB, 16, 4>(c, a, b0, vectors, split, s);
         else if (vectors <= 4) e = launch_gemv_pass<D, W, DX, DA, DB, 4, 1>(c, a, b0, vectors, split, s);
         else if (vectors <= 8) e = launch_gemv_pass<D, W, DX, DA, DB, 4, 2>(c, a, b0, vectors, split, s);
         else e = launch_gemv_pass<D, W, DX, DA, DB, 4, 4>(c, a, b0, vectors, split, s);

@@ -143,3 +143,22 @@ def test_rows_of_doubles(K):
         for _, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
             gu.assert_gemv_close(y, want, scale)
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K,bits", [(8, 16, 2), (8, 100, 0), (16, 33, 4), (16, 60, 0), (32, 8, 1), (32, 60, 0), (32, 80, 2)])
+@pytest.mark.parametrize("rows,groups", [(1, 2), (7, 7), (8, 8), (9, 9), (33, 131), (2061, 5)])
+def test_products_with_tiles_of_eight_rows(D, K, bits, rows, groups):
+    # two blocks of four rows share the activations of one of eight group columns: the ends of tiles, of the columns and of the
+    # vectors that a block loads
+    W = si.gaussian_weights(rows, D * groups, 0.02, seed=si.BASE_SEED + 670 + rows, rotate=False)
+    ctx, oe, oc = gu.make_ctx(D, K, bits, groups)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, D, K, bits, oe, nthreads=8), oc, nthreads=8)
+    for batch in (1, 3, 4, 5, 8):
+        xf, xb = si.activations(batch, D * groups, seed=rows + batch)
+        want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+        x = gu.to_dev_bf16(xb)
+        gu.assert_gemv_close(pvq.pvq_decode_gemv_on(ctx, packed, x, "walk", 8).cpu().numpy(), want, scale)
+    with pytest.raises(pvq.PvqError):
+        pvq.pvq_decode_gemv_on(ctx, packed, gu.to_dev_bf16(si.activations(9, D * groups, seed=1)[1]), "walk", 8)
+    ctx.close()
