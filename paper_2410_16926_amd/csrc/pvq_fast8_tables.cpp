@@ -24,10 +24,10 @@ struct Block {
 
 // Bucket row over one row of blocks: entry j describes indices [j << shift, (j+1) << shift), counted from `front` in
 // front of the row's first; NEXT: with the block after A (three candidates).  Returns how many indices are in none of their
-// bucket's blocks.
+// bucket's blocks; without `out` it only counts them, and passes over the buckets inside one block.
 template <bool NEXT>
 uint64_t build_bucket_row(const std::vector<Block> &blocks, uint32_t first_index, uint64_t total, int shift, uint64_t front,
-                          std::vector<uint32_t> &out)
+                          std::vector<uint32_t> *out)
 {
     const uint64_t width = (uint64_t)1 << shift;
     const uint64_t nb = (total + front + width - 1) / width;
@@ -36,6 +36,11 @@ uint64_t build_bucket_row(const std::vector<Block> &blocks, uint32_t first_index
     for (uint64_t j = 0; j < nb; j++) {
         const uint64_t lo = j * width < front ? 0 : j * width - front, hi = std::min((j + 1) * width - front, total);
         while (a + 1 < blocks.size() && blocks[a + 1].start <= lo) a++;
+        if (!out && a + 1 == blocks.size()) break;
+        if (!out && blocks[a + 1].start >= hi) {
+            j = ((blocks[a + 1].start + front) >> shift) - 1;
+            continue;
+        }
         auto cover = [&](size_t b) {           // of a block that starts inside the bucket, or of A from lo on
             return b < blocks.size() && blocks[b].start < hi ? std::min(hi, blocks[b].start + blocks[b].size) - std::max(lo, blocks[b].start) : 0;
         };
@@ -51,7 +56,7 @@ uint64_t build_bucket_row(const std::vector<Block> &blocks, uint32_t first_index
             missed -= cover(a + 1);
             e |= ((cover(a + 1) ? start(a + 1) : (uint32_t)width) - 1) << (32 - 2 * shift);
         }
-        out.push_back(e);
+        if (out) out->push_back(e);
     }
     return missed;
 }
@@ -61,9 +66,9 @@ uint64_t build_bucket_row(const std::vector<Block> &blocks, uint32_t first_index
 // number counts over all rows of the stage, as the biased residuals do (see write_blocks).
 template <typename E>
 uint64_t build_next_bucket_row(const std::vector<Block> &blocks, uint32_t first_index, uint64_t total, int shift, uint64_t front,
-                               std::vector<E> &out)
+                               std::vector<E> *out)
 {
-    const uint64_t row_bucket = out.size();   // the row's first bucket, counted over the whole stage
+    const uint64_t row_bucket = out ? out->size() : 0;   // the row's first bucket, counted over the whole stage
     const uint64_t width = (uint64_t)1 << shift;
     const uint64_t nb = (total + front + width - 1) / width;
     uint64_t missed = 0;
@@ -71,6 +76,11 @@ uint64_t build_next_bucket_row(const std::vector<Block> &blocks, uint32_t first_
     for (uint64_t j = 0; j < nb; j++) {
         const uint64_t lo = j * width < front ? 0 : j * width - front, hi = std::min((j + 1) * width - front, total);
         while (a + 1 < blocks.size() && blocks[a + 1].start <= lo) a++;
+        if (!out && a + 1 == blocks.size()) break;
+        if (!out && blocks[a + 1].start >= hi) {
+            j = ((blocks[a + 1].start + front) >> shift) - 1;
+            continue;
+        }
         uint64_t low = 0, covered = std::min(hi, blocks[a].start + blocks[a].size);
         if (a + 1 < blocks.size() && blocks[a + 1].start < hi) {
             low = width - (blocks[a + 1].start + front - j * width);
@@ -78,7 +88,7 @@ uint64_t build_next_bucket_row(const std::vector<Block> &blocks, uint32_t first_
         }
         missed += hi - covered;
         const uint64_t high = (uint64_t)first_index + a - (row_bucket + j);   // modulo the entry width
-        out.push_back((E)((high << shift) + low));
+        if (out) out->push_back((E)((high << shift) + low));
     }
     return missed;
 }
@@ -166,15 +176,14 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, bool 
     std::vector<uint32_t> bk0, bk1;
     std::vector<uint16_t> bk2;
     std::vector<uint32_t> bias1(K + 1), bias2(K + 1);   // what a row's residuals are carried with (see write_blocks)
-    build_bucket_row<false>(rows0[0], 0, N.at(8, K), s0, 0, bk0);
+    build_bucket_row<false>(rows0[0], 0, N.at(8, K), s0, 0, &bk0);
     uint32_t first = 0;
     for (int k = 0; k <= K; k++) {
         const uint64_t front = best_front(s1, [&](uint64_t f) {
-            std::vector<uint32_t> row;
-            return build_bucket_row<true>(rows1[k], 0, N.at(6, k), s1, f, row);
+            return build_bucket_row<true>(rows1[k], 0, N.at(6, k), s1, f, nullptr);
         });
         bias1[k] = ((uint32_t)bk1.size() << s1) + (uint32_t)front;
-        build_bucket_row<true>(rows1[k], first, N.at(6, k), s1, front, bk1);
+        build_bucket_row<true>(rows1[k], first, N.at(6, k), s1, front, &bk1);
         first += (uint32_t)rows1[k].size();
     }
     if (first > (1u << kFast8IndexBits)) return false;   // S1's block numbers must fit the entries
@@ -182,11 +191,10 @@ bool build_with_shifts(int K, const SmallTable &N, int s0, int s1, int s2, bool 
     uint64_t missed2 = 0;
     for (int k = 0; k <= K; k++) {
         const uint64_t front = best_front(s2, [&](uint64_t f) {
-            std::vector<uint16_t> row;
-            return build_next_bucket_row<uint16_t>(rows2[k], 0, N.at(4, k), s2, f, row);
+            return build_next_bucket_row<uint16_t>(rows2[k], 0, N.at(4, k), s2, f, nullptr);
         });
         bias2[k] = ((uint32_t)bk2.size() << s2) + (uint32_t)front;
-        missed2 += build_next_bucket_row<uint16_t>(rows2[k], first, N.at(4, k), s2, front, bk2);
+        missed2 += build_next_bucket_row<uint16_t>(rows2[k], first, N.at(4, k), s2, front, &bk2);
         first += (uint32_t)rows2[k].size();
     }
     if (first >= (1u << (16 - s2))) return false;   // S2's block numbers must fit the 16-bit entries
