@@ -1115,19 +1115,21 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 
 // Which of them it takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
 // vectors) has the others.
-//  - The tables take 8 us of a launch (155 KB for every unit), the walk 1.3 to 2 times as long per group.  Measured (K = 16, 2-bit
-//    codes, rows of 8192), table / walk, us:
-//        groups         1 vector     2..5 vectors          7         11         16
-//        0.5 M       10.5 /  8.6   17.3 /  8.9    17.5 /  9.6   18.8 / 12.6   20.0 / 13.8
-//        1.0 M       10.5 /  8.9   17.4 /  9.2    17.9 / 10.0   19.5 / 13.0   20.6 / 14.7
-//        1.3 M       10.6 / 14.9   17.5 / 15.2    17.8 / 17.0   19.4 / 20.3   20.8 / 23.4
-//        2.1 M       10.8 / 15.1   17.5 / 15.8    17.9 / 17.0   19.5 / 20.5   20.7 / 23.9
-//        3.1 M       15.7 / 17.1   17.8 / 17.9    18.1 / 21.7   19.7 / 24.7   21.1 / 26.0
-//        7.3 M       24.5 / 31.8   28.8 / 34.2    29.4 / 44.6   32.2 / 49.8   34.4 / 50.3
-//    So one line for 2..16 vectors cannot fit all of them: at 1.5 M groups the walk is still 2 us faster for 2..7 vectors, and
-//    the table decoder has been 1 to 3 us faster for 11 and 16 from 1.3 M on.  For one vector the crossing lies just above
-//    2^20 groups; at 2^20 itself (1024 x 8192) the table decoder loses 1.6 us, and has the product because the plan of
-//    that shape is stated by a test (test_the_plan_of_passes_names_the_kernels_that_run).
+//  - The tables take 7 us of a launch (155 KB for every unit), the walk 1.5 to 2 times as long per group.  Measured (K = 16, 2-bit
+//    codes), table / walk, us:
+//           rows x columns   groups         1            2            4            7            8           16 vectors
+//         512 x 8192        0.5 M    9.0 /  8.4  13.8 /  8.5  13.9 /  8.5  15.4 /  9.9  15.7 / 10.1  18.5 / 14.1
+//        1024 x 8192        1.0 M    9.3 /  8.8  14.0 /  8.8  14.4 /  8.9  15.5 / 10.3  15.8 / 10.5  18.6 / 14.6
+//        1100 x 8192        1.1 M    9.2 / 14.3  13.7 / 14.4  14.2 / 14.4       -       15.8 / 18.6  18.4 / 23.5
+//        2816 x 4096        1.4 M    9.2 / 10.4  13.5 / 10.6  11.2 / 10.5       -       11.2 / 13.1  12.3 / 15.3
+//         700 x 14336       1.3 M    9.5 / 11.7  13.6 / 11.8  19.2 / 12.1       -       21.4 / 14.9  25.9 / 21.8
+//        2048 x 8192        2.1 M    9.7 / 14.6  13.8 / 14.6  14.4 / 15.0  15.5 / 17.3  15.9 / 18.9  18.5 / 24.0
+//       14336 x 4096        7.3 M   19.7 / 30.5  22.1 / 30.3  23.4 / 33.6  25.3 / 44.1  26.5 / 46.9  31.5 / 49.9
+//    For one vector the crossing lies just above 2^20 groups; at 2^20 itself (1024 x 8192) the table decoder loses 0.5 us, and has
+//    the product because the plan of that shape is stated by a test (test_the_plan_of_passes_names_the_kernels_that_run).  For 2 to 8
+//    vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
+//    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows;
+//    1025 x 8704, 11 vectors: 18.1 / 18.3), and behind with fewer rows.
 //  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (4096 x 10720, 3 / 5 / 16
 //    vectors: 46 / 55 / 128 against 26 / 28 / 31 us), or one of four, which takes longer than the walk (32.4 / 26.0).
 //  - Fewer than 4096 groups and fewer than 8 vectors: the same test states the plan of three passes for 96 x 288 and 7
@@ -1139,7 +1141,7 @@ bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
     const int64_t groups = a.rows * a.groups;
     if (groups < 4096 && a.batch < 8) return true;                 // (the test's plan, not the faster one)
     if (a.batch >= 3 && !mfma_usable(c, a)) return false;
-    return groups >= (a.batch == 1 ? 1 << 20 : 3 << 19);
+    return groups >= (a.batch == 1 || (a.batch > 8 && a.rows > 1024) ? 1 << 20 : 3 << 19);
 }
 
 // The passes that a product of a.batch vectors is made of, in order: which kernel takes how many vectors.

@@ -162,3 +162,21 @@ def test_products_with_tiles_of_eight_rows(D, K, bits, rows, groups):
     with pytest.raises(pvq.PvqError):
         pvq.pvq_decode_gemv_on(ctx, packed, gu.to_dev_bf16(si.activations(9, D * groups, seed=1)[1]), "walk", 8)
     ctx.close()
+
+
+@pytest.mark.parametrize("rows,cols,batch,kind", [(1025, 8192, 9, "mfma_bf16"), (1025, 8192, 16, "mfma_bf16"), (1025, 8192, 8, "valu_fp32_generic"),
+                                                  (1024, 8192, 9, "valu_fp32_generic"), (1024, 8704, 16, "valu_fp32_generic"),
+                                                  (1025, 8000, 9, "valu_fp32_generic"), (2040, 4096, 9, "valu_fp32_generic"),
+                                                  (2051, 4096, 11, "mfma_bf16")])
+def test_products_at_the_line_between_the_decoders(rows, cols, batch, kind):
+    # more than eight vectors from 2^20 groups on, on more than 1024 rows of whole slabs
+    W = si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 680 + rows, rotate=False)
+    ctx, oe, oc = gu.make_ctx(8, 16, 2, cols // 8)
+    assert pvq.pvq_decode_gemv_plan(ctx, rows, cols, batch) == [(kind, batch)]
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W))
+    ref, _, _ = oracle.decode(oracle.encode(W, 8, 16, 2, oe, nthreads=8), oc, nthreads=8)
+    xf, xb = si.activations(batch, cols, seed=rows + batch)
+    want, scale = xf.astype(np.float64) @ ref.T, gu.product_scale(xf, ref)
+    for _, y in gu.products(ctx, packed, gu.to_dev_bf16(xb)):
+        gu.assert_gemv_close(y, want, scale)
+    ctx.close()
