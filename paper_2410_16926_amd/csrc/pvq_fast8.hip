@@ -1150,9 +1150,9 @@ int pvq_fast8_plan_gemv(const pvq_ctx *c, const pvq_decode_args &a, pvq_gemv_pas
     int n = 0, b0 = 0;
     while (b0 < a.batch) {
         const int left = a.batch - b0;
-        // 28672 x 8192: 1 vector 69 us on the barrier-free kernel (84 us with row batches and partial sums through LDS, which
-        // remains for short matrices and rows that are not whole slices), 2 vectors 84 us and 4 vectors 111..125 us on the
-        // vector-ALU kernels; the matrix-core pass takes 84 (3 or 4 vectors) to 103 us (16), so it takes three and more.
+        // 28672 x 8192: 1 vector 54 us on the barrier-free kernel (row batches and partial sums through LDS, 84 when it was 69, remain
+        // for short matrices and rows that are not whole slices), 2 vectors 64 us on the vector-ALU kernel; the matrix-core pass
+        // takes 67 (3 or 4 vectors) to 95 us (16), so it takes three and more.
         pvq_gemv_pass p;
         if (left >= 3 && mfma_usable(c, a)) p = {PVQ_PASS_MFMA, std::min(left, 16)};
         else if (left >= 4) p = {PVQ_PASS_VALU, 4};
