@@ -68,10 +68,11 @@ struct encode_wide_params {
 // levels, all of them permutations inside a row of 16 lanes after which every lane of the row holds the result, and a lane's
 // own coordinates (four or eight) are independent work in between.
 // Bound by instructions (906 on the vector and 155 on the scalar unit a wave at D = 128, K = 187, with the rotation in front)
-// and the gathers of thresholds.  2048 rows of 8192 rotated and encoded: 83 us, K = 84: 58 us; 2048 x 8192 encoded, D = 64,
-// K = 96: 47 us.  With the places of the repair marked in every step, general division and root (1025 and 254 instructions):
-// 89, 64, 47 us; with 90 instructions a step besides, and a lane reading all of an entry's pieces: 101, 100, 64 us.  A wave
-// per group, the form of small batches before: 7.7 and 11 us for 32 and 4096 groups (D = 128, K = 187), this one 6.9 and 7.7.
+// and the gathers of thresholds.  2048 rows of 8192 rotated and encoded: 79 us, K = 84: 54 us; 2048 x 8192 encoded, D = 64,
+// K = 96: 44 us from bfloat16, 45 from float32.  With the places of the repair marked in every step, general division and root
+// (1025 and 254 instructions): 84, 59, 44 and 47 us; with 90 instructions a step besides, and a lane reading all of an entry's
+// pieces: 101, 100, 64 (bfloat16).  A wave per group, the form of small batches before: 7.7 and 11 us for 32 and 4096 groups
+// (D = 128, K = 187), this one 6.9 and 7.7.
 #define PVQ_ROW_STEPS(STEP) STEP(0xB1) STEP(0x4E) STEP(0x141) STEP(0x140)
 
 __device__ inline float row_sum_pairs(float v)
@@ -141,13 +142,11 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
     int key[CP];
 #pragma unroll
     for (int j = 0; j < CP; j++) key[j] = (int)__float_as_uint((t[j] - m[j]) * unit);
-    bool repaired = false;
     if constexpr (DISTINCT) {
         // The largest, the largest below it, ...: with `last` the one before, key - last as an unsigned number is largest for the
         // first key below it.  After as many steps as the group has pulses to move, the keys not below the last are moved,
-        // unless two of them were equal: then the sum tells, and the steps below are taken.  (The wave goes on while any of its
-        // four groups has a step left, about five at D = 128; a step's masks on the scalar unit cost as much as its vector
-        // instructions, and this has none.)
+        // unless some of them were equal: then the sum tells.  (The wave goes on while any of its four groups has a step left,
+        // about five at D = 128; a step's masks on the scalar unit cost as much as its vector instructions, and this has none.)
         uint32_t place[CP];
 #pragma unroll
         for (int j = 0; j < CP; j++) place[j] = (uint32_t)max(key[j], 0);
@@ -168,15 +167,52 @@ __device__ inline void encode_group16(const float (&w)[CP], int sub, bool on, in
             moved[j] = m[j] + (place[j] >= last ? unit : 0.0f);
             tmp[j] = moved[j];
         }
-        repaired = __all(row_sum_pairs(tree_sum<CP>(tmp)) == (degenerate ? 0.0f : K));
-        if (repaired) {
+        if (!__all(row_sum_pairs(tree_sum<CP>(tmp)) == (degenerate ? 0.0f : K))) {
+            // Equal deviations, so that too many are not below `last`: it goes up again while those above it are enough.  (A
+            // group with fewer different deviations than pulses to move has come to its largest again, and starts at the lowest.)
+            // Taking every step again with masks instead, 2048 x 8192 float32 values that are bfloat16's, K = 84: 53.8 us, now
+            // 47.0; 64 x 8192 of which one in a thousand is not zero, rotated: 17.2, now 14.5.
+            auto count = [&](auto is) {
+                float n = 0.0f;
 #pragma unroll
-            for (int j = 0; j < CP; j++) m[j] = moved[j];
+                for (int j = 0; j < CP; j++) n += is(place[j]) ? 1.0f : 0.0f;
+                return n;
+            };
+            float above = row_sum_pairs(count([&](uint32_t v) { return v >= last; })), equal;
+            if (above < need) { last = 0; above = (float)D; }
+            for (bool up = true; __any(up);) {
+                equal = row_sum_pairs(count([&](uint32_t v) { return v == last; }));
+                uint32_t next = ~0u;
+#pragma unroll
+                for (int j = 0; j < CP; j++) next = min(next, place[j] > last ? place[j] : ~0u);
+#define PVQ_STEP(CTRL) next = min(next, dpp_move<CTRL>(next));
+                PVQ_ROW_STEPS(PVQ_STEP)
+#undef PVQ_STEP
+                up = above > need && above - equal >= need;
+                last = up ? next : last;
+                above -= up ? equal : 0.0f;
+            }
+            // of those equal to `last` the lowest coordinates, as many as are missing: the lane's share is what the lanes in front
+            // of it leave
+            float incl = count([&](uint32_t v) { return v == last; });
+            const float mine = incl;
+            incl += __uint_as_float(dpp_move<0x111>(__float_as_uint(incl)));        // row_shr:1
+            incl += __uint_as_float(dpp_move<0x112>(__float_as_uint(incl)));        // row_shr:2
+            incl += __uint_as_float(dpp_move<0x114>(__float_as_uint(incl)));        // row_shr:4
+            incl += __uint_as_float(dpp_move<0x118>(__float_as_uint(incl)));        // row_shr:8
+            float left = need - (above - equal) - (incl - mine);
+#pragma unroll
+            for (int j = 0; j < CP; j++) {
+                const bool is = place[j] == last;
+                moved[j] = m[j] + (place[j] > last || (is && left > 0.0f) ? unit : 0.0f);
+                left -= is ? 1.0f : 0.0f;
+            }
         }
-    }
-    // One pulse per step and group on the largest deviation, lowest coordinate on ties; none comes up twice (a place taken gets
-    // the key -1, the bits of no deviation).
-    if (!repaired) {
+#pragma unroll
+        for (int j = 0; j < CP; j++) m[j] = moved[j];
+    } else {
+        // One pulse per step and group on the largest deviation, lowest coordinate on ties; none comes up twice (a place taken
+        // gets the key -1, the bits of no deviation).
 #pragma unroll 1
         for (float step = 0.0f; step < (float)D && __any(need > step); step += 1.0f) {
             const bool open = need > step;      // the same in the 16 lanes of a group

@@ -66,3 +66,22 @@ def test_codes_of_rows_of_any_number_of_runs(D, K, bits, G):
     packed = pvq.pvq_encode(ctx, gu.to_dev_f32(W0), want_pulses=True)
     gu.assert_encode_equal(packed, oracle.encode(W0, D, K, bits, oe, nthreads=8))
     ctx.close()
+
+
+@pytest.mark.parametrize("D,K,levels,amplitude", [(64, 96, 2, "norm"), (64, 41, 5, "ls"), (64, 31, 30, "norm"), (128, 187, 3, "norm"),
+                                                  (128, 84, 9, "ls"), (128, 187, 60, "norm"), (64, 300, 4, "norm")])
+def test_equal_deviations_in_long_groups_of_float32_values(D, K, levels, amplitude):
+    # A running maximum passes over deviations that are equal, and the places are made up for afterwards: few magnitudes, so that
+    # whole runs of places are equal, at the last place, in front of it, and in more groups than have that many different ones;
+    # groups of distinct values between them, which share a wave with them.
+    rows, G = 24, 21
+    rng = np.random.default_rng(si.BASE_SEED + 860 + K + levels)
+    w = rng.choice(rng.uniform(0.2, 1.0, size=levels), size=(rows * G, D))
+    w[::5] = rng.standard_normal((len(w[::5]), D))
+    w[3::7] *= rng.random((len(w[3::7]), D)) < 0.1
+    w = (w * rng.choice([-1.0, 1.0], size=w.shape)).astype(np.float32).reshape(rows, G * D)
+    ctx = pvq.pvq_ctx_create(D, K)
+    ctx.set_amplitude(amplitude)
+    packed = pvq.pvq_encode(ctx, gu.to_dev_f32(w), want_pulses=K <= 127)
+    gu.assert_encode_equal(packed, oracle.encode(w, D, K, 0, None, nthreads=8, amplitude="ls" if amplitude == "ls" else "l2"))
+    ctx.close()
