@@ -143,6 +143,30 @@ def test_groups_that_the_short_arithmetic_refuses(D, K, amplitude):
     ctx.close()
 
 
+@pytest.mark.parametrize("D,K,amplitude", [(8, 16, "l2"), (16, 33, "ls"), (32, 60, "l2")])
+def test_groups_behind_groups_that_the_short_arithmetic_refuses(D, K, amplitude):
+    # A wave that has met a group for the general operations has them for the next one too, until they find an ordinary one: runs
+    # of such groups of every length from one on, at the start, the middle and the end of rows and panels, in some rows of a wave.
+    rows, cols = 100, 448
+    rng = np.random.default_rng(si.BASE_SEED + 655 + D)
+    W0 = np.asarray(si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + 656, rotate=False, bf16=False), dtype=np.float32)
+    groups = W0.reshape(rows, cols // D, D)
+    for r in range(0, rows, 3):
+        run = 1 + r // 3 % 5
+        for g in range(r % 7, cols // D, 2 * run):
+            groups[r, g:g + run] *= np.float32(0.0 if r % 2 else 2.0 ** -60)
+    W0[1] = 0.0
+    W0[40:75] = 0.0
+    _, U = si.calibration_hessian(cols, 2 * cols, si.BASE_SEED + 657)
+    ref, _ = oracle.correct(W0, U, D, K, amplitude=amplitude, nthreads=8)
+    ctx = pvq.pvq_ctx_create(D, K)
+    ctx.set_amplitude(amplitude if amplitude == "ls" else "norm")
+    Wd = gu.to_dev_f32(W0)
+    pvq.pvq_correct(ctx, Wd, gu.to_dev_f32(U))
+    assert np.array_equal(Wd.cpu().numpy().view(np.uint32), ref.view(np.uint32))
+    ctx.close()
+
+
 @pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 2049, 320), (8, 16, 1025, 448), (16, 33, 127, 384), (32, 60, 2177, 320)])
 def test_rows_of_an_update_task(D, K, rows, cols):
     # tasks of 128 to 1024 rows, 16 rows a wave at a time: one row more and fewer than whole tasks, and t values of a last
