@@ -580,7 +580,7 @@ struct gemv_split {
     unsigned grid;
 };
 
-// LDS of a pass: tables, a gain per lane, the waves' sums (rows x vectors; two places for tiles of four rows)
+// LDS of a pass: tables, a gain per lane, the waves' sums (rows x vectors; two places for tiles of four and eight rows)
 size_t gemv_lds(const pvq_ctx *c, int waves, int R, int sums)
 {
     return (size_t)c->walk.bytes + (size_t)waves * (R == 16 ? kWave + sums : 2 * sums) * sizeof(float);
@@ -607,8 +607,8 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
 {
     gemv_split best = {0, 0, 0, 0};
     double least = 0;
+    int in_flight = 0;                             // waves of a unit with the best split
     const double chain = 280.0 * c->D, issue = 4.0 * (80.0 + c->D * (c->words == 1 ? 14.0 : c->words == 2 ? 17.0 : 25.0));
-    int in_flight = 0;                             // waves of a unit with the best split into tiles of 4 or 16 rows
     for (const int R : {4, 16, 8}) {
         if (tile_rows ? R != tile_rows : R == 16 && vectors <= 4) continue;
         // (with one tile of four rows to a unit, eight would leave half of them idle)
@@ -618,6 +618,9 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
         const double loads = c->D * 128.0 / 11.0 * (R == 4 ? nv : R == 8 ? nv / 2.0 : 1.0);
         const int64_t tiles = (rows + R - 1) / R;
         const int chunks = ((int)groups + kWave / R - 1) / (kWave / R), tiles_unit = (int)((tiles + units() - 1) / units());
+        gemv_split mine = {0, 0, 0, 0};            // the best of these tiles
+        double cost_mine = 0;
+        int waves_mine = 0;
         bool most = true;                          // the most waves that have a chunk each
         for (int waves = 16; waves >= 1; waves -= waves > 8 ? 4 : waves > 4 ? 2 : 1) {
             if (waves > chunks) continue;
@@ -634,19 +637,28 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
             if (all && unit_copies(c->walk.bytes) == 1)
                 while (teams < tiles_unit && (teams + 1) * waves <= std::min(resident, 16) && gemv_lds(c, (teams + 1) * waves, R, sums) <= 160 * 1024) teams++;
             const double turns = (double)((tiles_unit + blocks * teams - 1) / (blocks * teams)), steps = (double)((chunks + waves - 1) / waves);
-            double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
-                                   (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
-            // Fewer waves in flight than with tiles of 4 or 16 rows hide less (14336 x 4096, D = 16, K = 33, one vector: 28
-            // waves with eight rows 28.5 us, 32 with four 27.2; 8192 x 14336, D = 32, K = 80: 12 waves 122, 16 114), and groups
-            // of 32 gain nothing where the estimates are equal (8173 x 22528, K = 50, one vector: 111, with four rows 107).
-            const int here = blocks * teams * waves;
-            if (R == 8 && here < in_flight) cost *= 1.5 - 0.5 * here / in_flight;
-            if (R == 8 && c->D == 32) cost *= 1.01;
-            if (best.rows == 0 || cost < least) {
-                least = cost;
-                if (R != 8) in_flight = here;
-                best = {R, waves, teams, (unsigned)std::min<int64_t>((tiles + teams - 1) / teams, (int64_t)units() * blocks)};
+            const double cost = std::max(std::max(turns * steps * chain, (double)tiles_unit * steps * waves / 4.0 * issue),
+                                         (double)tiles_unit * steps * waves * loads) + turns * (R == 16 ? 2500.0 : 1000.0);
+            if (mine.rows == 0 || cost < cost_mine) {
+                cost_mine = cost;
+                waves_mine = blocks * teams * waves;
+                mine = {R, waves, teams, (unsigned)std::min<int64_t>((tiles + teams - 1) / teams, (int64_t)units() * blocks)};
             }
+        }
+        if (mine.rows == 0) continue;
+        // Tiles of eight rows with fewer waves in flight than the best of the others hide less (14336 x 4096, D = 16, K = 33, one
+        // vector: 28 waves 28.5 us, with four rows 32 27.2; 8192 x 14336, D = 32, K = 80: 12 waves 122, 16 114), groups of 32 gain
+        // nothing where the estimates are equal (8173 x 22528, K = 50, one vector: 111, with four rows 107), and integers of one word,
+        // whose steps are short, only where it is well ahead (3001 x 11008, D = 32, K = 4, five vectors, the estimate 5 % ahead: 24.6,
+        // with four rows 20.6; 14336 x 4096, D = 16, K = 8, 12 % ahead: 25.7, with sixteen 31.5).
+        if (R == 8 && best.rows != 0) {
+            if (waves_mine < in_flight) cost_mine *= 1.5 - 0.5 * waves_mine / in_flight;
+            cost_mine *= c->words == 1 ? 1.1 : c->D == 32 ? 1.01 : 1.0;
+        }
+        if (best.rows == 0 || cost_mine < least) {
+            least = cost_mine;
+            in_flight = waves_mine;
+            best = mine;
         }
     }
     return best;
@@ -675,7 +687,7 @@ hipError_t launch_gemv(const pvq_ctx *c, const pvq_decode_args &a, int tile_rows
                                             vectors <= 4 ? waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 8, 1>>()
                                                          : waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 8, 2>>(),
                                             waves_per_simd<gemv_walk_kernel<D, W, DX, DA, DB, 16, 4>>());
-        if (split.rows == 0) return hipErrorInvalidValue;          // (no LDS left beside the tables: only where tile_rows asks for 16)
+        if (split.rows == 0) return hipErrorInvalidValue;          // (no LDS left beside the tables: only where tile_rows asks for 8 or 16)
         hipError_t e;
         if (split.rows == 8 && vectors <= 4) e = launch_gemv_pass<D, W, DX, DA, DB, 8, 1>(c, a, b0, vectors, split, s);
         else if (split.rows == 8) e = launch_gemv_pass<D, W, DX, DA, DB, 8, 2>(c, a, b0, vectors, split, s);
