@@ -190,6 +190,19 @@ __device__ inline float row_sum(const float *wsum, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(wave_pair_sum(wsum[lane])), kWave - 1));
 }
 
+// v as a number that the compiler does not know: what is computed from it is computed where it is used and not kept over the loops
+// in front.  The kernels have 64 registers for eight waves a SIMD, and what is only looked at once a row or a chunk (a lane's groups
+// when it writes codes, its pointers into weights and signs) had 2 to 10 values of the rotating kernels for 16-bit sources, and
+// 2 to 4 of the encoder for float32 sources, in scratch memory: 1500 x 6144 bf16 in blocks of 2048, 2-bit codes, 17.1 us, now 15.2;
+// 14336 x 4096 float32, 2-bit codes, 47.6, now 44.4.  (Kernels that have registers for it keep it: the encoder of bf16, 8-bit
+// codes, 47.0, with it 47.5.)
+template <typename T>
+__device__ inline T anew(T v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
+
 // LDS of both kernels, from byte 0: the offset table, the edges' tree, two rows' wave sums (used in turn, so that one
 // barrier a row is enough), the row's sums of squares (CODES; every wave reads its own).
 struct enc8_lds {
@@ -282,7 +295,8 @@ __global__ __launch_bounds__(kBlock, 8) void encode8_kernel(enc8_launch f, pvq_e
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, kBlock / kWave, lane);
+            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, kBlock / kWave,
+                               sizeof(TIn) == 4 ? anew(lane) : lane);
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
@@ -314,7 +328,7 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int quad_pos = lane & 3;
     const int chunks = G / L;                                    // whole chunks: every lane has a group
-    const int from = load_lane<LOG2N>(tid);                      // the 8 values of a chunk that the lane loads
+    const uint32_t from = (uint32_t)(load_lane<LOG2N>(tid) * D); // the 8 values of a chunk that the lane loads
     const int waves = L / kWave;
 
     float *wsum = l.wsum;
@@ -325,8 +339,9 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             const int g = ch * L + tid;
             float v[D];
             raw8<TIn> raw;
-            raw.load(xrow + (int64_t)(ch * L + from) * D);
-            if (signs) raw.flip(sign_bits(*reinterpret_cast<const uint2 *>(signs + (int64_t)(ch * L + from) * D)));
+            const uint32_t at = anew(from);                      // (an offset from a scalar address, not a pointer that moves with the chunks)
+            raw.load(xrow + (int64_t)(ch * L) * D + at);
+            if (signs) raw.flip(sign_bits(*reinterpret_cast<const uint2 *>(signs + (int64_t)(ch * L) * D + at)));
             raw.get(v);
             // one exchange buffer (a barrier in front of every exchange, which also keeps a chunk's writes
             // behind the reads of the chunk before): two workgroups of 1024 lanes then fit a unit's LDS
@@ -358,15 +373,15 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             __syncthreads();
             const float rowss = row_sum(wsum, lane);
             if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
-            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, waves, lane);
+            write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, waves, anew(lane));
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
     }
 }
 
 // Registers for eight waves a SIMD (64 a lane): with them two workgroups of 1024 lanes, which blocks of 8192 values need, share
-// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 65 / 79 / 85 / 99 us (with the encoder before 73 / 84 /
-// 90 / 110).
+// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 72 / 80 / 81 / 99 us, calls in a row (with the
+// encoder before its places came out of a network 78 / 85 / 90 / 110).
 template <typename TIn, int CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)

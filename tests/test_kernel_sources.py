@@ -103,3 +103,19 @@ def test_products_on_the_walk_keep_their_waves(tmp_path):
             most[D, W, DX, DA, DB, R, NV] = 72 if D <= 16 else 80
     assert len(most) > 10
     assert {k: found[k] for k in most if found[k] > most[k]} == {}
+
+
+def test_encoders_of_groups_of_eight_keep_their_values_in_registers(tmp_path):
+    """Eight waves a SIMD leave a lane 64 registers; what does not fit there goes to scratch memory and back."""
+    obj = os.path.join(os.path.dirname(CSRC), "_build", "pvq_encode8.hip.o")
+    if not os.path.exists(obj):
+        build.build()
+    llvm = "/opt/rocm/llvm/bin"
+    bundle, code = str(tmp_path / "bundle"), str(tmp_path / "code")
+    subprocess.run([f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={bundle}", obj, str(tmp_path / "copy.o")], check=True)
+    subprocess.run([f"{llvm}/clang-offload-bundler", "--type=o", "--targets=hipv4-amdgcn-amd-amdhsa--gfx950", f"--input={bundle}",
+                    f"--output={code}", "--unbundle"], check=True)
+    notes = subprocess.run([f"{llvm}/llvm-readelf", "--notes", code], check=True, capture_output=True, text=True).stdout
+    kernels = re.findall(r"\.name:\s*(\S*encode8_kernel\S*).*?\.vgpr_count:\s*(\d+).*?\.vgpr_spill_count:\s*(\d+)", notes, re.S)
+    assert len(kernels) > 50
+    assert [name for name, registers, spilled in kernels if int(registers) > 64 or int(spilled) > 0] == []
