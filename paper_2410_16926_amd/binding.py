@@ -21,9 +21,9 @@ EXPORTS = [
     "pvq_encode", "pvq_decode", "pvq_decode_gemv",
 ]
 
-# host-only diagnostics declared in csrc/pvq_diagnostics.h, exported for the tests
+# diagnostics declared in csrc/pvq_diagnostics.h, exported for the tests
 DIAGNOSTICS = ["pvq_fast_tables_selftest", "pvq_walk_tables_selftest", "pvq_decode_gemv_plan", "pvq_correct_set_front_tiles",
-               "pvq_decode_set_table_decoder_min_groups", "pvq_decode_gemv_on"]
+               "pvq_decode_set_table_decoder_min_groups", "pvq_decode_gemv_on", "pvq_exact_selftest"]
 
 
 class PvqError(RuntimeError):
@@ -59,6 +59,7 @@ def lib():
         L.pvq_beta_tables.argtypes = [i32, i64, i32, vp, vp]
         L.pvq_fast_tables_selftest.argtypes = [i32, C.c_uint64, C.c_uint64, vp]
         L.pvq_walk_tables_selftest.argtypes = [i32, i32, C.c_uint64, C.c_uint64, vp, vp, vp]
+        L.pvq_exact_selftest.argtypes = [i32, C.c_uint32, C.c_uint64, C.c_uint64, vp, vp]
         L.pvq_decode_gemv_plan.argtypes = [vp, i64, i64, i32, vp, vp, i32, vp]
         L.pvq_size_table_device.argtypes = [i32, i32, i32, vp, vp, vp]
         L.pvq_hadamard.argtypes = [vp, i32, i64, i64, i64, i32, vp, i32, vp, i32, i64, vp]
@@ -147,6 +148,19 @@ def pvq_walk_tables_selftest(D: int, K: int, seed: int = 1, count: int = 100000)
     _check(lib().pvq_walk_tables_selftest(D, K, seed, count, C.byref(bad), sched, C.byref(nbytes)),
            "pvq_walk_tables_selftest")
     return bad.value, (sched[0], sched[1]), nbytes.value
+
+
+EXACT = {"reciprocal": 0, "root": 1, "small_over": 2, "integer_over": 3, "root_divisor": 4, "divide": 5}
+
+
+def pvq_exact_selftest(what: str, first: int, count: int, ks=(0,)) -> int:
+    """How many of the short quotients and roots named differ from the general operations on the GPU, over [first, first + count)
+    for every k of ks (csrc/pvq_diagnostics.h says of what)."""
+    import torch
+    bad = torch.zeros(1, dtype=torch.int64, device="cuda")
+    for k in ks:
+        _check(lib().pvq_exact_selftest(EXACT[what], k, first, count, bad.data_ptr(), torch.cuda.current_stream().cuda_stream), "pvq_exact_selftest")
+    return int(bad.item())
 
 
 # (the walk's one pass forms its dot products on the matrix cores; its name is older than that)

@@ -16,7 +16,8 @@ LIB_PATH = os.path.join(_HERE, "libpvq.so")
 TORCH_PATH = os.path.join(_HERE, "_pvq_torch" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
 
 SOURCES = ["pvq_host.cpp", "pvq_fast8_tables.cpp", "pvq_kernels.hip", "pvq_fast8.hip",
-           "pvq_encode8.hip", "pvq_size_table.hip", "pvq_hadamard.hip", "pvq_wide.hip", "pvq_correct.hip", "pvq_walk.hip"]
+           "pvq_encode8.hip", "pvq_size_table.hip", "pvq_hadamard.hip", "pvq_wide.hip", "pvq_correct.hip", "pvq_walk.hip",
+           "pvq_exact_check.hip"]
 
 HEADERS = ["pvq_internal.h", "pvq_fast8.h", "pvq_hadamard_dev.h", "pvq_quantize_dev.h", "pvq_diagnostics.h", "pvq_small_table.h",
            "pvq_walk.h", "pvq_exact_dev.h"]

@@ -1,4 +1,4 @@
-/* Host-only diagnostics of libpvq.  Not part of the public interface (include/pvq.h): the symbols are
+/* Diagnostics of libpvq.  Not part of the public interface (include/pvq.h): the symbols are
  * exported so that the tests can call them through ctypes. */
 #ifndef PVQ_DIAGNOSTICS_H
 #define PVQ_DIAGNOSTICS_H
@@ -68,6 +68,19 @@ int pvq_correct_set_front_tiles(int64_t tiles, int64_t *previous);
  * amplitude and sqrt(sum y^2), the other multiplies by a tabulated reciprocal).  PVQ_E_INVALID_ARG for groups < 0.
  */
 int pvq_decode_set_table_decoder_min_groups(int64_t groups, int64_t *previous);
+
+/*
+ * The short quotients and roots that the encoders and the correction use for ordinary arguments (pvq_exact_dev.h), compared on
+ * the GPU with the division and the square root, whose bits they must have.  what / k / [first, first + count):
+ *   RECIPROCAL, ROOT             floats by their bits, within 2^-100 .. 2^100; k unused
+ *   SMALL_OVER, INTEGER_OVER     k / l: k from 1 to 255 and to 1023; l by its bits, as above
+ *   ROOT_DIVISOR                 integers n within 1 .. 65536: sqrt(n) and 1 / sqrt(n); k unused
+ *   DIVIDE                       samples of dividends and divisors (numbers below 2^40), k the seed
+ * Adds how many differ to *mismatches (device memory) on `stream`.  PVQ_E_INVALID_ARG for NULL and what is out of range.
+ */
+enum { PVQ_EXACT_RECIPROCAL = 0, PVQ_EXACT_ROOT = 1, PVQ_EXACT_SMALL_OVER = 2, PVQ_EXACT_INTEGER_OVER = 3, PVQ_EXACT_ROOT_DIVISOR = 4,
+       PVQ_EXACT_DIVIDE = 5 };
+int pvq_exact_selftest(int what, uint32_t k, uint64_t first, uint64_t count, uint64_t *mismatches, void *stream);
 
 #ifdef __cplusplus
 }
