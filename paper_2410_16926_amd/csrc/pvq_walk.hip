@@ -318,11 +318,9 @@ struct gemv_teams {
     int inverse;        // 256 / waves, rounded up: wave * inverse / 256 is the team of one of at most sixteen waves
 };
 
-// Waves of a SIMD that a kernel's registers are to leave room for: eight in tiles of 16 rows of groups of 16 with two words and of
-// groups of 32 with up to two, which the schedule of the reads would pass by a few registers (next_from_product); else those of a
-// workgroup of 1024 lanes.  (Groups of 16 with one word stay below 64 registers by themselves, and are slower when held to them: 3001 x
-// 11008, K = 8, 16 vectors 25.6 us, now 24.3.)
-constexpr int gemv_waves(int D, int W, int R) { return R == 16 && (W == 2 ? D >= 16 : W == 1 && D == 32) ? 8 : 4; }
+// Waves of a SIMD that a kernel's registers are to leave room for: eight in tiles of 16 rows of groups of 16 and 32 with up to
+// two words, which the schedule of the reads would pass by a few registers (next_from_product); else those of a workgroup of 1024 lanes.
+constexpr int gemv_waves(int D, int W, int R) { return D >= 16 && W <= 2 && R == 16 ? 8 : 4; }
 
 template <int D, int W, int DX, int DA, int DB, int R, int NV>
 __global__ __launch_bounds__(kMaxThreads, gemv_waves(D, W, R)) void gemv_walk_kernel(walk_launch wl, pvq_decode_args a, int b0, int vectors, int row_tiles, gemv_teams split)
