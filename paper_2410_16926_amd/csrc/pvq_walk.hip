@@ -645,13 +645,13 @@ gemv_split split_gemv(const pvq_ctx *c, int64_t rows, int64_t groups, int vector
         }
         if (mine.rows == 0) continue;
         // Tiles of eight rows with fewer waves in flight than the best of the others hide less (14336 x 4096, D = 16, K = 33, one
-        // vector: 28 waves 28.5 us, with four rows 32 27.2; 8192 x 14336, D = 32, K = 80: 12 waves 122, 16 114), groups of 32 gain
-        // nothing where the estimates are equal (8173 x 22528, K = 50, one vector: 111, with four rows 107), and integers of one word,
-        // whose steps are short, only where it is well ahead (3001 x 11008, D = 32, K = 4, five vectors, the estimate 5 % ahead: 24.6,
-        // with four rows 20.6; 14336 x 4096, D = 16, K = 8, 12 % ahead: 25.7, with sixteen 31.5).
+        // vector: 28 waves 28.5 us, with four rows 32 27.2; 8192 x 14336, D = 32, K = 80: 12 waves 122, 16 114), and groups of 32 gain
+        // nothing where the estimates are equal (8173 x 22528, K = 50, one vector: 111, with four rows 107), those with integers of
+        // one word only where it is well ahead (3001 x 11008, K = 4, five vectors, the estimate 5 % ahead: 24.6, with four rows 20.6;
+        // 2048 x 8192, 25 % ahead: 19.0 and 20.6).
         if (R == 8 && best.rows != 0) {
             if (waves_mine < in_flight) cost_mine *= 1.5 - 0.5 * waves_mine / in_flight;
-            cost_mine *= c->words == 1 ? 1.1 : c->D == 32 ? 1.01 : 1.0;
+            cost_mine *= c->D < 32 ? 1.0 : c->words == 1 ? 1.1 : 1.01;
         }
         if (best.rows == 0 || cost_mine < least) {
             least = cost_mine;
