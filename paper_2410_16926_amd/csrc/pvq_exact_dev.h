@@ -42,7 +42,7 @@ __device__ inline float divide(float a, const divisor &d)
 }
 
 // RN(k / l) for an integer 1 <= k <= 255 and l from 2^-100 to 2^100: the first quotient with v_rcp_f32 and one correction.  Every k
-// with every significand of l has been compared with the division (the first that differ have k above 320).
+// with every significand of l has been compared with the division (the first that differs is 367).
 __device__ inline float small_over(float k, float l)
 {
     const float y = __builtin_amdgcn_rcpf(l), q = k * y;

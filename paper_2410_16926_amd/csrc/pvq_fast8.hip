@@ -1128,7 +1128,7 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 //    For one vector the crossing lies just above 2^20 groups; at 2^20 itself (1024 x 8192) the table decoder loses 0.5 us, and has
 //    the product because the plan of that shape is stated by a test (test_the_plan_of_passes_names_the_kernels_that_run).  For 2 to 8
 //    vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
-//    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows;
+//    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows of 256;
 //    1025 x 8704, 11 vectors: 18.1 / 18.3), and behind with fewer rows.
 //  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (4096 x 10720, 3 / 5 / 16
 //    vectors: 46 / 55 / 128 against 26 / 28 / 31 us), or one of four, which takes longer than the walk (32.4 / 26.0).
@@ -1141,7 +1141,8 @@ bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
     const int64_t groups = a.rows * a.groups;
     if (groups < 4096 && a.batch < 8) return true;                 // (the test's plan, not the faster one)
     if (a.batch >= 3 && !mfma_usable(c, a)) return false;
-    return groups >= (a.batch == 1 || (a.batch > 8 && a.rows > 1024) ? 1 << 20 : 3 << 19);
+    const int64_t units = g_num_cus > 0 ? g_num_cus : 256;
+    return groups >= (a.batch == 1 || (a.batch > 8 && a.rows > 4 * units) ? 1 << 20 : 3 << 19);
 }
 
 // The passes that a product of a.batch vectors is made of, in order: which kernel takes how many vectors.

@@ -91,8 +91,8 @@ def test_narrow_update_inside_the_panel_workgroups(D, K, rows, cols, amplitude):
 @pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 15, 384), (8, 16, 33, 448), (8, 16, 257, 512), (16, 33, 17, 384), (16, 33, 143, 448),
                                            (32, 60, 16, 448), (32, 60, 129, 320)])
 def test_ragged_tiles_of_the_matrix_instructions(D, K, rows, cols):
-    # rows around the 16 of an instruction, the 16 or 32 of a panel workgroup and the 64 and 128 of an update tile; columns
-    # that end in half a panel and half a tile
+    # rows around the 16 of an instruction and of a wave's turn of an update task, the 16 or 32 of a panel workgroup and the 64 of a
+    # task's four waves; columns that end in half a panel and one task
     run_correct(D, K, rows, cols, seed=si.BASE_SEED + 630 + rows + cols, ld_extra=4)
 
 
