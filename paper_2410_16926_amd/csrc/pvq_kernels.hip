@@ -70,7 +70,8 @@ __host__ __device__ inline encode_lds lds_of(int D, int W, const encode_launch &
 // ---------------------------------------------------------------------------------------------
 
 // Waves that a SIMD's registers are divided among (with the repair before: groups of 16, 3001 x 11008: 39 us, with 4 43, with 6, which
-// spill, 49; groups of 32, 8192 x 8192, 2-bit codes: 84 us, with 3 118, with 5, which spill, 130)
+// spill, 49; groups of 32, 8192 x 8192, 2-bit codes: 84 us, with 3 118, with 5, which spill, 130).  With these a lane of groups of 16 from
+// float32 or with least-squares amplitudes has 2 to 7 values in scratch memory, of groups of 32 9 to 24.
 constexpr int waves_per_simd(int D) { return D == 8 ? 7 : D == 16 ? 5 : 4; }
 
 // A group as it comes from memory
