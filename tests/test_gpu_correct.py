@@ -53,14 +53,14 @@ def test_corrected_weights_with_amplitude_codes_and_leading_dimensions():
 
 
 def test_a_wider_matrix():
-    # 24 blocks of 64 columns, row tiles with a ragged end: the order of the updates across blocks
+    # 24 blocks of 64 columns, rows with a ragged end: the order of the updates across blocks
     run_correct(8, 16, 700, 1536, seed=si.BASE_SEED + 542)
 
 
 @pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 1100, 448), (16, 33, 300, 640), (32, 60, 150, 384), (8, 16, 2100, 320)])
 def test_wide_updates_beside_the_next_panel(D, K, rows, cols):
-    # from the third panel on a launch holds panel workgroups and update tiles of the panel before (several row
-    # tiles and column tiles, ragged ends), and the panels' t values alternate between two buffers; an odd number
+    # from the third panel on a launch holds panel workgroups and update tasks of the panel before (several in
+    # rows and columns, ragged ends), and the panels' t values alternate between two buffers; an odd number
     # of 64-column blocks ends in a half panel; the call is repeated on the same context
     W0, ref = run_correct(D, K, rows, cols, seed=si.BASE_SEED + 543 + rows)
     ctx = pvq.pvq_ctx_create(D, K)
