@@ -209,13 +209,14 @@ int pvq_encode(const pvq_ctx *ctx, const void *W, int dtype, int64_t rows, int64
  *   U      device, float32 [cols][ldu], 16-byte aligned, ldu >= cols, ldu a multiple of 4; only the upper
  *          triangle is used (what lies below the diagonal may be anything).  Not modified.
  *   work   device, 16-byte aligned scratch of at least pvq_correct_work_bytes(rows) bytes (two buffers of 128
- *          floats per row), owned by the caller, contents undefined afterwards.
+ *          floats per row), owned by the caller, contents undefined afterwards.  With twice as much (work_bytes says so)
+ *          a launch takes two panels of 128 columns instead of one wherever that is faster; the results are the same.
  *
  * float32 throughout; q = (s / sqrt(sum y^2)) * y; the substitution and the updates are fused multiply-adds
  * applied one at a time in the order of the rows of U, so the result does not depend on the launch shape.
  * Contexts with D = 8, 16 or 32 and cols a multiple of 64, else PVQ_E_UNSUPPORTED.  A zero on the
  * diagonal of U gives non-finite weights (then encoded as pvq_encode encodes them), never a fault.
- * Launches ceil(cols/128) kernels on `stream`, nothing else (no other stream, no event, no allocation), so
+ * Launches at most ceil(cols/128) kernels on `stream`, nothing else (no other stream, no event, no allocation), so
  * the call can be captured in a graph; asynchronous.
  */
 int pvq_correct_work_bytes(int64_t rows, size_t *bytes);

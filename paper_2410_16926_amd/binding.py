@@ -323,14 +323,15 @@ def pvq_rotate_encode(ctx: PvqContext, X, block: int, signs=None, out: Packed = 
 def pvq_correct(ctx: PvqContext, W, U, work=None):
     """Error correction group after group, in place.  W: float32 [rows][cols] device tensor (overwritten
     with the values to encode), U: float32 [cols][cols] upper triangular device tensor, U^T U = inverse
-    Hessian; work: optional uint8 device tensor of pvq_correct_work_bytes(rows) bytes.  Returns W."""
+    Hessian; work: optional uint8 device tensor of at least pvq_correct_work_bytes(rows) bytes, better of twice as many.
+    Returns W."""
     import torch
     rows, cols = W.shape
     assert W.dtype == torch.float32 and U.dtype == torch.float32 and tuple(U.shape) == (cols, cols)
     if work is None:
         nbytes = C.c_size_t(0)
         _check(lib().pvq_correct_work_bytes(rows, C.byref(nbytes)), "pvq_correct_work_bytes")
-        work = torch.empty((max(int(nbytes.value), 16),), dtype=torch.uint8, device=W.device)
+        work = torch.empty((max(2 * int(nbytes.value), 16),), dtype=torch.uint8, device=W.device)
     ldw = W.stride(0) if rows > 1 else max(cols, 1)
     ldu = U.stride(0) if cols > 1 else 1
     _check(lib().pvq_correct(ctx.handle, _ptr(W), rows, cols, ldw, _ptr(U), ldu, _ptr(work), work.numel(),

@@ -9,29 +9,31 @@
 // holds, for every group, the values that were quantised: encoding it gives the corrected code.
 //
 // Rows are independent, groups of a row strictly sequential, and U is the same for every row.  Columns are taken in panels
-// of 128, a launch per panel on the caller's stream (correct_step_kernel), whose workgroups have one of two roles:
-//     panel   (the first workgroups, 32 or 16 rows each) panel p - 1's 128 multiply-adds per element onto the panel's columns,
-//             which is all that panel p waits for, then the panel's groups one after the other, a row across 8 or 16
-//             lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  One wave a SIMD, which issues an instruction in four
-//             to five clocks whether it depends on the one before or not, so its time is the number of its instructions: 4.1 us
-//             in front (first reads 2, matrix instructions 1.7), 1.2 for the panel's part of U, 10.5 for 16 groups of 8
-//             (2.4, 0.5 and 10.5 with 16 rows).
-//     update  (all others) panel p - 1's 128 multiply-adds per element, in the same order, for the columns behind panel p:
-//             tasks of 64 columns, W read and written once per panel.  Bound: float32 matrix instructions and memory together
-//             (8192 rows times 7936 columns: 167 us, the matrix instructions alone 125, memory alone 126; times 5888
-//             columns, whose W the last-level cache holds, 120 us, 96 and 64).
-// The two roles touch different columns, and the update reads panel p - 1's t values while the panel role writes
-// panel p's, which is why there are two work buffers used in turn.  The panel workgroups come first in the grid
-// and raise their waves' priority, so they are placed before the flood of update tasks and run beside it: the
-// chain of panels (each needs the one before) stays off the critical path as long as a launch has enough update
-// tasks to outlast it; with few rows the chain is what remains.  A workgroup has the LDS of the role that needs more: 36.9 KB
-// in groups of 8, 39.9 in groups of 16, four workgroups to a compute unit; 45.1 in groups of 32, three.
-// Both roles' 128 multiply-adds per element run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
+// of 128, one or two panels a launch on the caller's stream (correct_step_kernel), whose workgroups have one of two roles:
+//     panel   (the first workgroups, 32 or 16 rows each) for each of the launch's panels, the multiply-adds of the launch before's
+//             panels onto its columns (and of the launch's own first panel onto its second), then its groups one after the
+//             other, a row across 8 or 16 lanes.  Leaves the panel's t values (rows x 128) in a work buffer.  One wave a SIMD,
+//             which issues an instruction in four to five clocks whether it depends on the one before or not, so its time is
+//             the number of its instructions: with one panel a launch 4.1 us in front (first reads 2, matrix instructions 1.7),
+//             1.2 for the panel's part of U, 10.5 for 16 groups of 8 (2.4, 0.5 and 10.5 with 16 rows); with two 44 us for both.
+//     update  (all others) the launch before's panels onto all columns behind the launch's own: 128 or 256 multiply-adds per
+//             element, in the same order, W read and written once a launch.
+// Bound: float32 matrix instructions (152 TFLOP/s in registers with any number of waves), and they keep other waves of their SIMD from
+// the vector unit while they run (a wave of them beside a wave of vector instructions takes the sum of both times, whatever
+// the priorities; beside bfloat16 ones it is the longer of both).  So the chain of panels costs the updates what it issues, and there is
+// little to gain from more waves.  What counts is that no wave waits for its own stores, that a launch's updates start and end
+// together, and fewer launches and passes over W.
+// The two roles touch different columns; the updates read the t values of the launch before's panels while the panel role writes
+// its own, so two panels a launch take four work buffers, one panel two.  Two panels a launch halve the passes over W and the launches'
+// starts; the chain pays for it with longer fronts, which shows where there are few rows (64 x 2048 268 / 281 us).  The panel
+// workgroups come first in the grid and raise their waves' priority.  A workgroup has the LDS of the role that needs more: 64 KB with two
+// panels, two workgroups to a unit; with one 36.9 KB in groups of 8, 39.9 in groups of 16, four to a unit; 45.1 in groups of 32, three.
+// Both roles' multiply-adds run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
 // element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
 // tied, subnormal and non-finite operands).
-// Before, with tiles of 128 x 128 whose workgroups waited for each stage of 32 rows of U and moved in step (loading, then
-// multiplying, then storing), and with the compiler's divisions and roots in the chain (27 us a panel): 8192 x 8192 6.6 ms, now 6.1; 1024 x 8192 2.06, now
-// 1.61; 1024 x 4096 in groups of 16 0.72, now 0.53; 64 x 2048 0.41, now 0.27.
+// 8192 x 8192 in groups of 8 5.02 ms, 28672 x 8192 17.7, 8192 x 4096 1.49, 4096 x 4096 1.06, 1024 x 8192 1.48 (one panel a
+// launch, for which the smallest work buffer has room, 5.6, 19.7, 1.59, 1.14, 1.66).  Before, with one panel a launch, tasks of 64 columns and 128 to 1024 rows and waves
+// that waited for their stores after every 16 rows, 6.12, 20.8, 1.75, 1.09, 1.61; with tiles of 128 x 128 whose workgroups moved in step 6.6 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -52,6 +54,7 @@ constexpr int kWaves = 4;         // waves of a workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kTileCols = 64;     // columns of an update's task
 constexpr int kItemRows = 16;     // rows that a wave of it takes at a time
+constexpr int kStepRows = kItemRows * kWaves;
 constexpr int kUpdateFloats = kPanelCols * kTileCols;
 
 // t values of a panel as the matrix instructions' operands: per 16 rows (fewer at the end) pieces of four values, of which a
@@ -75,10 +78,22 @@ struct correct_shape {
     int K, ls;
 };
 
+// How the updates are shared out: the rows' steps of kStepRows are in 2^log2_chunks chunks of `steps` each, the first `longer` of them one more;
+// a chunk's steps times the blocks of kTileCols columns go to its shares, `each` or, the first `rest` shares, one more (of a chunk that is
+// no longer, or is).
+struct update_split {
+    uint32_t log2_chunks, steps, longer, each[2], rest[2];
+};
+
+// The buffers of t values (rows x 128 floats each) that a launch uses: those of the launch before's panels, and its own behind them.
+template <int PANELS> struct t_buffers {
+    float *of[2 * PANELS];
+};
+
 // ---- a row's group across L neighbouring lanes, C = D / L coordinates a lane --------------------------------
 template <int D> struct split {
     static constexpr int L = D == 8 ? 8 : 16, C = D / L;
-    static constexpr int kRowsOfWave = 64 / L, kMostRows = kWaves * kRowsOfWave;   // of a workgroup
+    static constexpr int kRowsOfWave = 64 / L;
     static constexpr int kGroups = kPanelCols / D;
     // LDS of the panel role: D x D blocks of U on and above the panel's diagonal, before that t values and sums on their way
     // to and from the matrix cores' layout (kXPitch: an operand's values lie on different banks)
@@ -89,9 +104,8 @@ template <int D> struct split {
     static constexpr int kDivisors = kBlocks * D * D;
     static constexpr int kFloats = kDivisors + (4 * kPanelCols > kPast * D * D ? 4 * kPanelCols : kPast * D * D);
     static constexpr int kXPitch = kPanelCols + 4;
-    static_assert(kMostRows * kXPitch <= kFloats, "the transposition fits");
 };
-template <int D> constexpr int lds_floats() { return kUpdateFloats > split<D>::kFloats ? kUpdateFloats : split<D>::kFloats; }
+template <int D, int PANELS> constexpr int lds_floats() { return std::max(PANELS * kUpdateFloats, split<D>::kFloats); }
 
 template <int CTRL, int BANKS = 0xF>
 __device__ inline int dpp(int old, int v) { return __builtin_amdgcn_update_dpp(old, v, CTRL, 0xF, BANKS, false); }
@@ -276,20 +290,24 @@ __device__ inline bool solve_group(const float (&w)[split<D>::C], const float (&
 
 // Panel role.  A workgroup takes ROWS rows, a wave 8 (D = 8) or 4 of them: lane (row, j) holds coordinate(s) j of
 // every group of the panel, and the waves do not wait for each other once the panel's part of U is in LDS.
-//   First the panel before's 128 multiply-adds per element onto this panel's columns, on the matrix cores: a wave takes 32
-// columns, the results change hands through LDS.
+//   First the multiply-adds of the `before` panels in front whose updates have not reached this panel's columns, on the matrix cores:
+// a wave takes 32 columns, the results change hands through LDS.
 //   Then group after group: the quantiser across the lanes of a row, amplitude, error, substitution, and the t values,
 // which the substitution has brought to all lanes of the row, onto the groups behind (rows of U ascending).  The next group
 // is always w[0]: one body for all groups, which stays in the instruction cache.
-template <int D, bool LS, int ROWS>
-__device__ inline void panel_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ Tprev,
-                                  float *__restrict__ Tcur, const correct_shape &a, int64_t p0, int width, float *lds)
+template <int D, bool LS, int ROWS, int PANELS>
+__device__ inline void panel_role(float *__restrict__ W, const float *__restrict__ U, const t_buffers<PANELS> &T, const correct_shape &a,
+                                  int panel, int own, int width, float *lds)
 {
     using S = split<D>;
     constexpr int L = S::L, C = S::C, NG = S::kGroups, RB = ROWS / 16;
-    const int lane = threadIdx.x & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    int tid = threadIdx.x;
+    if constexpr (PANELS > 1) asm volatile("" : "+v"(tid));     // (else what follows from it is kept over both panels)
+    const int lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int j = lane & (L - 1);
+    const int64_t p0 = (int64_t)panel * kPanelCols;
+    const int before = PANELS == 1 ? (panel > 0 ? 1 : 0) : panel < PANELS ? panel : own;      // panels in front whose updates it lacks
     const int64_t row0 = (int64_t)blockIdx.x * ROWS;
     const int rloc = wave * S::kRowsOfWave + lane / L;
     const bool in = rloc < ROWS && row0 + rloc < a.rows;
@@ -298,14 +316,14 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     float *wrow = W + row * a.ldw + p0 + C * j;
     const int ngroups = width / D;
     const float *Up = U + p0 * a.ldu + p0;                      // row p0 + k, column p0 + c of the factor
-    const float diagonal = Up[std::min<int64_t>(threadIdx.x, width - 1) * (a.ldu + 1)];
+    const float diagonal = Up[std::min<int64_t>(tid, width - 1) * (a.ldu + 1)];
 
     // U on and above the panel's diagonal, on its way from the start: 64 columns of four rows make a piece, of which the panel's
     // right half has 32 and its left half 16; a lane's four values lie side by side in LDS.
     constexpr int kRight = kPanelCols / 4 / kWaves, kMyPieces = kRight + kPanelCols / 8 / kWaves;
     const bool right_half = width > 64;
     float up[kMyPieces][4];
-    auto first_row = [&](int x) { return 4 * (x < kRight ? wave + kWaves * x : wave + kWaves * (x - kRight)); };
+    auto first_row = [&](int x) { return 4 * (wave + kWaves * (x < kRight ? x : x - kRight)); };
     auto fetch_panel = [&]() {
 #pragma unroll
         for (int x = 0; x < kMyPieces; x++) {
@@ -341,55 +359,62 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     float *divisors = lds + S::kDivisors;
     static_assert(ROWS * S::kXPitch <= S::kDivisors, "divisors lie behind the transposition");
     auto store_divisors = [&]() {
-        if ((int)threadIdx.x < width) {
+        if (tid < width) {
             const divisor d = column_divisor(diagonal);
-            *reinterpret_cast<float4 *>(divisors + 4 * threadIdx.x) = make_float4(d.b, d.y, d.yl, 0.0f);
+            *reinterpret_cast<float4 *>(divisors + 4 * tid) = make_float4(d.b, d.y, d.yl, 0.0f);
         }
     };
     // (lanes beyond the rows of the workgroup have none)
     const bool chain = wave * S::kRowsOfWave < ROWS;
     float w[NG][C];
-    if (p0 > 0) {
+    if (before > 0) {
         const int c16 = lane & 15, k4 = lane >> 4;              // an operand's row or column, and its place in k
         const bool cols_in = 32 * wave < width;
         f32x4 acc[RB][2];
         constexpr int kAhead = 8;                               // operands of so many instructions are on their way while as many are used
         float uv[2][kAhead][2];
         // (a wave without columns reads the first ones)
-        const float *ub = U + (p0 - kPanelCols + k4) * a.ldu + p0 + (cols_in ? 32 * wave : 0) + c16;
+        const float *ub = U + (p0 - before * kPanelCols + k4) * a.ldu + p0 + (cols_in ? 32 * wave : 0) + c16;
         auto fetch = [&](float (&v)[kAhead][2]) {
 #pragma unroll
             for (int s = 0; s < kAhead; s++) { v[s][0] = ub[0]; v[s][1] = ub[16]; ub += 4 * a.ldu; }
         };
         f32x4 tq[2][RB][kAhead / 4];
-        auto fetch_t = [&](int h) {
+        auto fetch_t = [&](const float *Tb, int h) {
 #pragma unroll
             for (int rb = 0; rb < RB; rb++) {
                 const t_rows t(std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1), a.rows);
 #pragma unroll
-                for (int i = 0; i < kAhead / 4; i++) tq[h & 1][rb][i] = *t.piece(Tprev, kAhead / 4 * h + i, k4);
+                for (int i = 0; i < kAhead / 4; i++) tq[h & 1][rb][i] = *t.piece(Tb, kAhead / 4 * h + i, k4);
             }
         };
         fetch(uv[0]);
-        fetch_t(0);
+        fetch_t(T.of[PANELS == 1 ? 0 : own - before], 0);
 #pragma unroll
         for (int rb = 0; rb < RB; rb++) {
             const float *p = W + std::min<int64_t>(row0 + 16 * rb + c16, a.rows - 1) * a.ldw + p0 + (cols_in ? 32 * wave : 0) + 4 * k4;
             acc[rb][0] = *reinterpret_cast<const f32x4 *>(p);
             acc[rb][1] = *reinterpret_cast<const f32x4 *>(p + 16);
         }
+        constexpr int kSteps = kPanelCols / 4 / kAhead;
+        static_assert(kSteps % 2 == 0, "the next panel's first operands go where its own are");
         fetch_panel();
+#pragma unroll 1
+        for (int b = PANELS > 1 ? before : 1; b > 0; b--) {
+            const float *Tb = T.of[PANELS == 1 ? 0 : own - b];
 #pragma unroll
-        for (int h = 0; h < kPanelCols / 4 / kAhead; h++) {
-            if (h + 1 < kPanelCols / 4 / kAhead) { fetch(uv[(h + 1) & 1]); fetch_t(h + 1); }
-            if (ROWS == 16 && h == 1) { store_panel(std::true_type{}); store_divisors(); }
+            for (int h = 0; h < kSteps; h++) {
+                if (h + 1 < kSteps) { fetch(uv[(h + 1) & 1]); fetch_t(Tb, h + 1); }
+                else if (PANELS > 1 && b > 1) { fetch(uv[0]); fetch_t(T.of[own - b + 1], 0); }
+                if (ROWS == 16 && h == 1 && (PANELS == 1 || b == 1)) { store_panel(std::true_type{}); store_divisors(); }
 #pragma unroll
-            for (int s = 0; s < kAhead; s++)
+                for (int s = 0; s < kAhead; s++)
 #pragma unroll
-                for (int rb = 0; rb < RB; rb++)
+                    for (int rb = 0; rb < RB; rb++)
 #pragma unroll
-                    for (int x = 0; x < 2; x++)
-                        acc[rb][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[h & 1][s][x], tq[h & 1][rb][s / 4][s % 4], acc[rb][x], 0, 0, 0);
+                        for (int x = 0; x < 2; x++)
+                            acc[rb][x] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[h & 1][s][x], tq[h & 1][rb][s / 4][s % 4], acc[rb][x], 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int rb = 0; rb < RB; rb++)
@@ -413,24 +438,27 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
     }
 
     store_panel(std::false_type{});
-    if (ROWS > 16 && p0 > 0) { store_panel(std::true_type{}); store_divisors(); }   // (there are no registers for it in front)
+    if (ROWS > 16 && before > 0) { store_panel(std::true_type{}); store_divisors(); }   // (there are no registers for it in front)
     __syncthreads();
 
     // What the next panel reads of U comes to this die's L2 meanwhile: its rows in the next panel's columns and the next panel's
     // own, 2 x 128 rows of four 128-byte lines, a lane each (rows lie far apart, so that a first touch is a page's first touch
     // too: 64 rows 17.7 us a panel, 18.6 without).
-    float touched[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int kTouches = 16 / kWaves;
+    float touched[kTouches] = {};
     if (p0 + 2 * kPanelCols <= a.cols) {
 #pragma unroll
-        for (int x = 0; x < 4; x++) touched[x] = Up[(int64_t)(threadIdx.x / 4 + 64 * x) * a.ldu + kPanelCols + threadIdx.x % 4 * 32];
+        for (int x = 0; x < kTouches; x++) touched[x] = Up[(int64_t)(tid / 4 + 16 * kWaves * x) * a.ldu + kPanelCols + tid % 4 * 32];
     }
-    if (!chain) {
-        asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
-        return;
-    }
+    float *Tcur = T.of[PANELS == 1 ? 1 : own];
     const t_rows trow(row, a.rows);                             // t values, negated
     const float *ublk = lds + j * 4;                            // block (G, G), the lane's column
     bool plain = true;
+    auto arrived = [&]() {
+#pragma unroll
+        for (int x = 0; x < kTouches; x++) asm volatile("" : : "v"(touched[x]));
+    };
+    if (!chain) { arrived(); return; }
 #pragma unroll 1
     for (int G = 0; G < ngroups; G++) {
         float wg[C], u[C][D], mine[C], tb[D];
@@ -505,149 +533,213 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
         ublk += (NG - G) * D * D;
         wrow += D;
     }
-    asm volatile("" : : "v"(touched[0]), "v"(touched[1]), "v"(touched[2]), "v"(touched[3]));
+    arrived();
 }
 
-// Update role.  Rows [row0, row1), columns [col0, col0 + 64): W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ... - t[r][127] U[c0 + 127][c], one
-// multiply-add after the other, t = the t values of the panel at column c0, on the matrix cores: v_mfma_f32_16x16x4_f32 adds its
+// Update role.  Rows [row0, row1), columns [col0, col0 + 64): W[r][c] <- W[r][c] - t[r][0] U[c0][c] - ... (128 or 256 of them), one
+// multiply-add after the other, t = the t values of the panels from column c0 on, on the matrix cores: v_mfma_f32_16x16x4_f32 adds its
 // four products one by one, k ascending, each a fused multiply-add (bit for bit, subnormals, infinities and NaN included).
-// The workgroup has its part of U in LDS, after which its waves do not wait for each other: a wave takes 16 rows at a time, whose W
-// and t values (as operands, t_rows) are requested when the rows before are begun, so that memory and matrix cores are busy at
-// the same time whatever the other waves do.
-__device__ inline void update_role(float *__restrict__ W, const float *__restrict__ U, const float *__restrict__ T,
-                                   const correct_shape &a, int64_t c0, int64_t col0, int64_t row0, int64_t row1, float *lds)
+// The workgroup has its part of U in LDS, after which its waves do not wait for each other: a wave takes 16 rows at a time.  Their W is
+// requested an item ahead and t values (as operands, t_rows) eight pieces ahead, into the registers that have just been used, and no store is
+// under a condition: memory operations complete in order, so a wait for a load that may or may not have stores behind it would
+// wait for the stores too (update alone, 8192 rows x 3968 columns: 87 us so, now 76).  Items of 32 rows, an operand of U for eight
+// instructions, take longer (8192 x 8192 5.02 / 5.17 ms).
+template <int PANELS>
+__device__ inline void update_role(float *__restrict__ W, const float *__restrict__ U, const t_buffers<PANELS> &T, const correct_shape &a,
+                                   int panel, int64_t col0, int64_t row0, int64_t row1, float *lds)
 {
-    constexpr int kPieces = kPanelCols / 16;      // float4 of t values of a lane for a row, each for four instructions in a row
+    constexpr int kDeep = PANELS * kPanelCols;
+    constexpr int kPieces = kDeep / 16;           // float4 of t values of a lane for a row, each for four instructions in a row
+    constexpr int kRing = kPanelCols / 16;
+    const int64_t c0 = (int64_t)panel * kPanelCols;
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c16 = lane & 15, k4 = lane >> 4;
-    // The instruction's rows are columns of W, so that a lane's four results are neighbours: row c16 of the wave's, columns
-    // 16 cb + 4 k4 .. + 3.  A row that is not there is the last one, and not stored.
-    f32x4 w[4], t[kPieces];
-    auto fetch = [&](int64_t r) {
-        const int64_t row = std::min<int64_t>(r + c16, row1 - 1);
-        const float *p = W + row * a.ldw + col0 + 4 * k4;
-        const t_rows tr(row, a.rows);
-#pragma unroll
-        for (int i = 0; i < kPieces; i++) t[i] = *tr.piece(T, i, k4);
-#pragma unroll
-        for (int cb = 0; cb < 4; cb++) w[cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
-    };
-    int64_t r = row0 + kItemRows * wave;
     // U as operands: the four blocks of 16 columns side by side, so that an instruction's four are one read
+    float uq[kDeep * 16 / kThreads][4];
     {
-        float uq[kPanelCols * 16 / kThreads][4];
         const float *up = U + (c0 + (tid >> 4)) * a.ldu + col0 + (tid & 15);
 #pragma unroll
-        for (int x = 0; x < kPanelCols * 16 / kThreads; x++) {
+        for (int x = 0; x < kDeep * 16 / kThreads; x++) {
 #pragma unroll
             for (int q = 0; q < 4; q++) uq[x][q] = up[16 * q];
             up += kThreads / 16 * a.ldu;
         }
-#pragma unroll
-        for (int x = 0; x < kPanelCols * 16 / kThreads; x++)
-            *reinterpret_cast<f32x4 *>(lds + (tid + x * kThreads) * 4) = f32x4{uq[x][0], uq[x][1], uq[x][2], uq[x][3]};
     }
+    // The instruction's rows are columns of W, so that a lane's four results are neighbours: row c16 of the item's, columns
+    // 16 cb + 4 k4 .. + 3.  A row that is not there is the last one once more, which gets the same values.
+    f32x4 w[4], t[kRing];
+    auto place = [&](int64_t r) { return W + (r + std::min<int64_t>(c16, a.rows - 1 - r)) * a.ldw + col0 + 4 * k4; };
+    auto fetch_w = [&](int64_t r) {
+        const float *p = place(r);
+#pragma unroll
+        for (int cb = 0; cb < 4; cb++) w[cb] = *reinterpret_cast<const f32x4 *>(p + 16 * cb);
+    };
+    auto fetch_piece = [&](int64_t r, int i) {
+        const int n = (int)std::min<int64_t>(kItemRows, a.rows - r);      // (t_rows, whose block is the item)
+        t[i % kRing] = *reinterpret_cast<const f32x4 *>(T.of[i / kRing] + r * kPanelCols + 16 * n * (i % kRing) +
+                                                        (uint32_t)(4 * std::min(c16, n - 1) + 4 * n * k4));
+    };
+    int64_t r = row0 + kItemRows * wave;
+    int items = r < row1 ? (int)((row1 - r + kStepRows - 1) / (kStepRows)) : 0;
+    if (items > 0) {
+#pragma unroll
+        for (int i = 0; i < kRing; i++) fetch_piece(r, i);
+        fetch_w(r);
+    }
+#pragma unroll
+    for (int x = 0; x < kDeep * 16 / kThreads; x++)
+        *reinterpret_cast<f32x4 *>(lds + (tid + x * kThreads) * 4) = f32x4{uq[x][0], uq[x][1], uq[x][2], uq[x][3]};
     __syncthreads();
     int at = lane;                                                         // ([4 s + k4][c16])
-    if (r < row1) fetch(r);
-    for (; r < row1; r += kItemRows * kWaves) {
+    auto item = [&](auto more) {
+        constexpr bool kMore = decltype(more)::value;
         asm volatile("" : "+v"(at));              // (the operands are the same for all rows, and more than there are registers)
         const f32x4 *us = reinterpret_cast<const f32x4 *>(lds) + at;
-        f32x4 acc[4], tv[kPieces];
-#pragma unroll
-        for (int i = 0; i < kPieces; i++) tv[i] = t[i];
+        const int64_t next = r + kStepRows;
+        f32x4 acc[4];
 #pragma unroll
         for (int cb = 0; cb < 4; cb++) acc[cb] = w[cb];
-        if (r + kItemRows * kWaves < row1) fetch(r + kItemRows * kWaves);
+        if constexpr (kMore) fetch_w(next);
+        f32x4 uv[2];
+        uv[0] = us[0];
 #pragma unroll
-        for (int s = 0; s < kPanelCols / 4; s++) {
-            const f32x4 uv = us[s * 64];
+        for (int s = 0; s < kDeep / 4; s++) {
+            if (s + 1 < kDeep / 4) uv[(s + 1) & 1] = us[(s + 1) * 64];
 #pragma unroll
-            for (int cb = 0; cb < 4; cb++) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[cb], tv[s / 4][s % 4], acc[cb], 0, 0, 0);
+            for (int cb = 0; cb < 4; cb++) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x4f32(uv[s & 1][cb], t[s / 4 % kRing][s % 4], acc[cb], 0, 0, 0);
+            if (s % 4 == 3) {
+                const int i = s / 4 + kRing;
+                if (i < kPieces) fetch_piece(r, i);
+                else if constexpr (kMore) fetch_piece(next, i - kPieces);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
-        if (r + c16 < row1) {
-            float *p = W + (r + c16) * a.ldw + col0 + 4 * k4;
+        float *p = place(r);
 #pragma unroll
-            for (int cb = 0; cb < 4; cb++) *reinterpret_cast<f32x4 *>(p + 16 * cb) = acc[cb];
-        }
-    }
+        for (int cb = 0; cb < 4; cb++) *reinterpret_cast<f32x4 *>(p + 16 * cb) = acc[cb];
+        r = next;
+    };
+    for (; items > 1; items--) item(std::true_type{});
+    if (items > 0) item(std::false_type{});
 }
 
-// The panel at column p0 (its own 128 or 64 columns, and in front of them the panel before's update of those), and the
-// panel before's update of the columns from p0 + 128 on.  Tprev: the t values of the panel before (unused for
-// p0 = 0), Tcur: where this panel's go.  The grid is panel_wgs + chunks * (64s of columns behind the panel) workgroups, the latter none
-// for p0 = 0; a chunk is chunk_rows rows, and neighbouring workgroups, which are on different dies, take different ones of the
-// same columns: the t values of a chunk are read from one L2 if their number is a multiple of eight.
-// (at most 128 registers per lane, four workgroups per compute unit; three for groups of 32, whose blocks take more LDS)
-template <int D, bool LS, int ROWS>
-__global__ __launch_bounds__(kThreads, D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
-                                                                 const float *__restrict__ Tprev, float *__restrict__ Tcur,
-                                                                 correct_shape a, int64_t p0, int width, int panel_wgs, int chunks, int chunk_rows, bool late)
+// The PANELS panels from number `panel` on (128 columns each, 64 at the end), and the panels in front of them, as many, onto the columns
+// behind.  The grid is panel_wgs + chunks * shares workgroups, the latter none for panel 0: the updates' rows are in up to eight chunks, which
+// neighbouring workgroups, on different dies, take in turn, so that a chunk's t values are read from one L2; a chunk's steps of 64 rows
+// times 64 columns are shared out evenly.
+// (at most 128 registers per lane with one panel, four workgroups per compute unit, three for groups of 32, whose blocks take more LDS)
+template <int D, bool LS, int ROWS, int PANELS>
+__global__ __launch_bounds__(kThreads, PANELS > 1 ? 2 : D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
+                                                                 t_buffers<PANELS> T, correct_shape a, int panel, int panel_wgs, update_split parts, bool late)
 {
-    __shared__ __align__(16) float lds[lds_floats<D>()];
+    __shared__ __align__(16) float lds[lds_floats<D, PANELS>()];
     if ((int)blockIdx.x < panel_wgs) {
         // the chain's waves go first where they share a SIMD with update waves, which have plenty of others to fill in
         __builtin_amdgcn_s_setprio(2);
-        panel_role<D, LS, ROWS>(W, U, Tprev, Tcur, a, p0, width, lds);
+#pragma unroll 1
+        for (int x = 0; x < PANELS; x++) {
+            const int64_t left = a.cols - (int64_t)(panel + x) * kPanelCols;
+            if (left <= 0) break;
+            if (x > 0) {
+                // the panel before has left its t values, and nobody needs its LDS any more
+                __builtin_amdgcn_s_waitcnt(0x0F70);            // vmcnt(0)
+                __syncthreads();
+            }
+            panel_role<D, LS, ROWS, PANELS>(W, U, T, a, panel + x, PANELS + x, (int)std::min<int64_t>(kPanelCols, left), lds);
+        }
     } else {
         // With few rows the chain is what a launch waits for, and its first reads stand in line with those of all tasks (1024 rows of
         // 8192: its front 4 us alone, 12 to 15 beside them); the tasks, 15 to 27 us in all, let it go first by 3.4 us.
         if (late) __builtin_amdgcn_s_sleep(127);
-        const int task = (int)blockIdx.x - panel_wgs;
-        const int64_t row0 = (int64_t)(task % chunks) * chunk_rows;
-        update_role(W, U, Tprev, a, p0 - kPanelCols, p0 + kPanelCols + (int64_t)(task / chunks) * kTileCols, row0,
-                    std::min<int64_t>(row0 + chunk_rows, a.rows), lds);
+        const uint32_t wg = blockIdx.x - panel_wgs, share = wg >> parts.log2_chunks, chunk = wg - (share << parts.log2_chunks);
+        const bool more = chunk < parts.longer;
+        const uint32_t steps = parts.steps + (more ? 1u : 0u), first = chunk * parts.steps + std::min(chunk, parts.longer);
+        const uint32_t each = parts.each[more], rest = parts.rest[more];
+        uint32_t at = share * each + std::min(share, rest);
+        const uint32_t end = at + each + (share < rest ? 1u : 0u);
+        while (at < end) {
+            const uint32_t tile = at / steps, from = at - tile * steps, to = std::min(steps, from + end - at);
+            update_role<PANELS>(W, U, T, a, panel - PANELS, (int64_t)(panel + PANELS) * kPanelCols + (int64_t)tile * kTileCols,
+                                (int64_t)(first + from) * kStepRows, std::min<int64_t>((int64_t)(first + to) * kStepRows, a.rows), lds);
+            at += to - from;
+            if (at < end) __syncthreads();
+        }
     }
 }
 
-template <int D>
-void launch_step(float *W, const float *U, const float *Tprev, float *Tcur, const correct_shape &a, int64_t p0, int width,
-                 int col_tiles, hipStream_t s)
+template <int D, int ROWS, int PANELS>
+void launch_step(float *W, const float *U, float *work, const correct_shape &a, int panel, hipStream_t s)
 {
-    // With few rows, which do not fill the units either way, a panel workgroup takes 16: half the matrix instructions in front
-    // (64 x 2048 17.8 to 16.6 us a panel, 2048 x 4096 26.0 to 25.2; 4096 x 4096 34.1 to 35.0).
-    const int panel_rows = split<D>::kMostRows == 32 && a.rows > 2048 ? 32 : 16;
-    const int panel_wgs = (int)((a.rows + panel_rows - 1) / panel_rows);
-    // rows of a task: enough tasks to fill the units evenly (tasks that end early leave their unit to the others), as few
-    // copies of U as that allows
-    constexpr int kLeast = kItemRows * kWaves, kTasks = 2048;
-    int64_t chunk_rows = 1024;
-    while (chunk_rows > kLeast && (a.rows + chunk_rows - 1) / chunk_rows * col_tiles < kTasks) chunk_rows /= 2;
-    const int chunks = (int)((a.rows + chunk_rows - 1) / chunk_rows);
+    t_buffers<PANELS> T;                           // 2 PANELS buffers, used in turn
+    for (int x = 0; x < 2 * PANELS; x++) T.of[x] = work + (panel + PANELS + x) % (2 * PANELS) * a.rows * kPanelCols;
+    const int64_t behind = a.cols - (int64_t)(panel + PANELS) * kPanelCols;
+    const int col_tiles = panel > 0 && behind > 0 ? (int)(behind / kTileCols) : 0;
+    const int panel_wgs = (int)((a.rows + ROWS - 1) / ROWS);
+    // Update workgroups.  Where every unit has a panel workgroup, one beside it: they all start with the launch, and whatever the
+    // columns are they end together.  With fewer the units that have none are ahead, and smaller shares let them take more.  (Shares
+    // 256 / 512 / 1024 / 4096: 8192 x 8192 5020 / 5710 / 5370 / 5940 us, 8192 x 4096 1490 / 1500 / 1620 / 1810; 3000 x 8192 2750 / 2790 /
+    // 2650 / 2750; 1024 x 8192 1640 / 1650 / 1550 / 1480, 2048 x 4096 790 / 810 / 770 / 740.)
+    constexpr uint32_t kUnits = 256;
+    const uint32_t steps = (uint32_t)((a.rows + kStepRows - 1) / kStepRows);
+    const uint32_t most = panel_wgs >= (int)kUnits ? kUnits : a.rows > 2048 ? 4 * kUnits : 16 * kUnits;
+    update_split parts;
+    parts.log2_chunks = steps >= 8 ? 3 : steps >= 4 ? 2 : steps >= 2 ? 1 : 0;
+    const uint32_t chunks = 1u << parts.log2_chunks;
+    parts.steps = steps / chunks;
+    parts.longer = steps % chunks;
+    const uint32_t shares = (uint32_t)std::min<uint64_t>(most / chunks, (uint64_t)(parts.steps + (parts.longer ? 1 : 0)) * col_tiles);
+    for (uint32_t more = 0; more < 2; more++) {
+        const uint32_t all = (parts.steps + more) * (uint32_t)col_tiles;      // (fewer than 2^32: the matrix has 4096 values for each, 16 KiB)
+        parts.each[more] = shares ? all / shares : 0;
+        parts.rest[more] = shares ? all % shares : 0;
+    }
     const bool late = a.rows <= 2048;              // (1024 x 4096 756 to 714 us, 2048 x 4096 869 to 830; 4096 x 4096 1090 either way)
-    constexpr int kMost = split<D>::kMostRows;
-    auto kernel = panel_rows == 16 ? (a.ls ? &correct_step_kernel<D, true, 16> : &correct_step_kernel<D, false, 16>)
-                                   : (a.ls ? &correct_step_kernel<D, true, kMost> : &correct_step_kernel<D, false, kMost>);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(panel_wgs + chunks * col_tiles)), dim3(kThreads), 0, s,
-                       W, U, Tprev, Tcur, a, p0, width, panel_wgs, chunks, (int)chunk_rows, late);
+    auto kernel = a.ls ? &correct_step_kernel<D, true, ROWS, PANELS> : &correct_step_kernel<D, false, ROWS, PANELS>;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)panel_wgs + chunks * shares), dim3(kThreads), 0, s,
+                       W, U, T, a, panel, panel_wgs, parts, late);
 }
 
-// W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: two buffers of rows x 128 floats.
-hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
-                          int64_t ldu, float *work, hipStream_t s)
+template <int D, int PANELS>
+hipError_t launch_panels(float *W, const float *U, float *work, const correct_shape &a, hipStream_t s)
 {
-    correct_shape a;
-    a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
-    int p = 0;
-    for (int64_t p0 = 0; p0 < cols; p0 += kPanelCols, p++) {
-        const int width = (int)std::min<int64_t>(kPanelCols, cols - p0);   // 128, or 64 at the end
-        const int64_t behind = cols - (p0 + kPanelCols);
-        const int col_tiles = p0 > 0 && behind > 0 ? (int)(behind / kTileCols) : 0;
-        float *Tcur = work + (int64_t)(p & 1) * rows * kPanelCols, *Tprev = work + (int64_t)((p & 1) ^ 1) * rows * kPanelCols;
-        switch (c->D) {
-        case 8: launch_step<8>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
-        case 16: launch_step<16>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
-        default: launch_step<32>(W, U, Tprev, Tcur, a, p0, width, col_tiles, s); break;
-        }
+    const int panels = (int)((a.cols + kPanelCols - 1) / kPanelCols);
+    constexpr int kMost = kWaves * split<D>::kRowsOfWave;
+    for (int p = 0; p < panels; p += PANELS) {
+        // With few rows, which do not fill the units either way, a panel workgroup takes 16: half the matrix instructions in front
+        // (64 x 2048 17.8 to 16.6 us a panel, 2048 x 4096 26.0 to 25.2; 4096 x 4096 34.1 to 35.0).
+        if (a.rows <= 2048) launch_step<D, 16, PANELS>(W, U, work, a, p, s);
+        else launch_step<D, kMost, PANELS>(W, U, work, a, p, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
+template <int PANELS>
+hipError_t launch_panels(int D, float *W, const float *U, float *work, const correct_shape &a, hipStream_t s)
+{
+    switch (D) {
+    case 8: return launch_panels<8, PANELS>(W, U, work, a, s);
+    case 16: return launch_panels<16, PANELS>(W, U, work, a, s);
+    default: return launch_panels<32, PANELS>(W, U, work, a, s);
+    }
+}
+
+// W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: `buffers` (two or four) of rows x 128 floats.
+// Two panels a launch where the updates are what there is to wait for; with few rows, or up to 2048 of a narrow matrix, it is the chain,
+// whose fronts get longer (one / two panels, 256 x 4096 555 / 576 us, 512 x 4096 624 / 617, 512 x 8192 1419 / 1326, 1024 x 1024 135 / 142,
+// 768 x 2048 301 / 302, 8192 x 704 138 / 128).
+hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
+                          int64_t ldu, float *work, int buffers, hipStream_t s)
+{
+    correct_shape a;
+    a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
+    const bool two = buffers == 4 && (rows > 2048 || (rows >= 512 && cols >= 2048));
+    return two ? launch_panels<2>(c->D, W, U, work, a, s) : launch_panels<1>(c->D, W, U, work, a, s);
+}
 
 // Work buffers of the entry point that allocates nothing: the t values of two panels for up to kStaticRows rows
-// (twice 128 floats per row), 8 MiB on every GPU that loads the library, until the process ends.
+// (twice 128 floats per row), 8 MiB on every GPU that loads the library, until the process ends; of four for up to half the rows.
 constexpr int64_t kStaticRows = 8192;
 static __device__ __align__(256) float scratch[2 * kStaticRows * kPanelCols];
 
@@ -680,7 +772,13 @@ hipError_t scratch_on_current_device(float **ptr)
 hipError_t pvq_launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
                               int64_t ldu, float *work, hipStream_t s)
 {
-    return launch_correct(c, W, rows, cols, ldw, U, ldu, work, s);
+    return launch_correct(c, W, rows, cols, ldw, U, ldu, work, 2, s);
+}
+
+hipError_t pvq_launch_correct_two_panels(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
+                                         int64_t ldu, float *work, hipStream_t s)
+{
+    return launch_correct(c, W, rows, cols, ldw, U, ldu, work, 4, s);
 }
 
 int64_t pvq_correct_static_max_rows(void) { return kStaticRows; }
@@ -693,5 +791,5 @@ hipError_t pvq_launch_correct_static(const pvq_ctx *c, float *W, int64_t rows, i
     float *work = nullptr;
     const hipError_t e = scratch_on_current_device(&work);
     if (e != hipSuccess) return e;
-    return launch_correct(c, W, rows, cols, ldw, U, ldu, work, s);
+    return launch_correct(c, W, rows, cols, ldw, U, ldu, work, 2 * rows <= kStaticRows ? 4 : 2, s);
 }

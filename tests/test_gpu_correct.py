@@ -169,9 +169,35 @@ def test_groups_behind_groups_that_the_short_arithmetic_refuses(D, K, amplitude)
 
 @pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 2049, 320), (8, 16, 1025, 448), (16, 33, 127, 384), (32, 60, 2177, 320)])
 def test_rows_of_an_update_task(D, K, rows, cols):
-    # tasks of 128 to 1024 rows, 16 rows a wave at a time: one row more and fewer than whole tasks, and t values of a last
+    # steps of 64 rows, 16 rows a wave at a time: one row more and fewer than whole steps, and t values of a last
     # block of fewer than 16 rows
     run_correct(D, K, rows, cols, seed=si.BASE_SEED + 660 + rows)
+
+
+@pytest.mark.parametrize("D,K,rows,cols,ld_extra", [
+    (8, 16, 511, 2048, 0), (8, 16, 512, 2048, 0), (8, 16, 513, 2112, 4), (16, 33, 1041, 2240, 8), (32, 60, 600, 2176, 0), (8, 16, 2048, 1984, 0),
+    (8, 16, 2049, 64, 0), (8, 16, 2100, 192, 0), (32, 60, 2180, 576, 4), (8, 5, 4100, 448, 0), (16, 33, 4112, 320, 0), (8, 16, 8200, 384, 0)])
+def test_two_panels_a_launch(D, K, rows, cols, ld_extra):
+    # the smallest work buffer has room for one panel a launch, twice as much for two (the rule's lines are at 512 and 2048 rows and 2048
+    # columns): the same bits, odd and even numbers of panels, the last one of 64 columns or 128, workgroups and shares with a ragged end,
+    # and nothing written behind the buffer
+    g = torch.Generator(device="cuda")
+    g.manual_seed(si.BASE_SEED + 670 + rows)
+    W0 = torch.randn((rows, cols + ld_extra), generator=g, device="cuda") * 0.02
+    U = torch.triu(torch.randn((cols, cols), generator=g, device="cuda") * (0.3 / cols ** 0.5), diagonal=1)
+    U.diagonal().copy_(0.75 + 0.5 * torch.rand((cols,), generator=g, device="cuda"))
+    ctx = pvq.pvq_ctx_create(D, K)
+    results = []
+    for size in (1024, 2048):
+        whole = torch.full((rows * size + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+        W = W0.clone()
+        pvq.pvq_correct(ctx, W[:, :cols], U, work=whole[: rows * size])
+        assert bool((whole[rows * size:] == 0x5A).all())
+        assert torch.equal(W[:, cols:], W0[:, cols:])
+        results.append(W.view(torch.int32))
+    assert torch.equal(results[0], results[1])
+    assert not torch.equal(results[0], W0.view(torch.int32)) or cols <= D
+    ctx.close()
 
 
 @pytest.mark.parametrize("rows,cols", [(200, 256), (1100, 640)])
