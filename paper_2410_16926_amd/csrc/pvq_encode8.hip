@@ -22,7 +22,8 @@
 // maxima, conversions, byte permutations and lane moves 4.3 to 4.8, v_rcp 8.9.)  28672 x 8192 bf16 weights, 2-bit codes: 234 vector,
 // 46 scalar and 10 LDS instructions a group, 152 us (launches in a row); with the places of the repair marked by masks on the
 // scalar unit, a code a lane and general quotients 242, 129 and 11, 185 us; with integer addresses, marks of all rounds as masks
-// and a bisection for the code 284 vector ones and 211 us.  14336 x 4096, 8-bit codes: 45 us, before 55 and 81.
+// and a bisection for the code 284 vector ones and 211 us.  With clamped differences for comparisons in the repair and short quotients for
+// the codes, another 6 %: 160 / 151 us on one card, 14336 x 4096 with 8-bit codes 48.1 / 45.3 (before that 55 and 81).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -343,15 +344,13 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             raw.load(xrow + (int64_t)(ch * L) * D + at);
             if (signs) raw.flip(sign_bits(*reinterpret_cast<const uint2 *>(signs + (int64_t)(ch * L) * D + at)));
             raw.get(v);
-            // one exchange buffer (a barrier in front of every exchange, which also keeps a chunk's writes
-            // behind the reads of the chunk before): two workgroups of 1024 lanes then fit a unit's LDS
-            // (the cross-lane stages from 4 lanes on go through the LDS permute unit for blocks of up to 512 values, where the
+            // (two workgroups of 1024 lanes fit a unit's LDS; the cross-lane stages from 4 lanes on go through the LDS permute unit for blocks of up to 512 values, where the
             // encoder's arithmetic is what the kernel waits for and that unit is idle; none for larger blocks, whose
             // exchanges through LDS need it)
             constexpr int kPermuted = LOG2N <= 9 ? 4 + 8 + 16 + 32 : 0;
             int stages = log2n;
             if constexpr (LOG2N <= 9) asm volatile("" : "+s"(stages));   // (else the comparisons below stay in scalar registers over the loop)
-            hadamard_stages<LOG2N, false, true, kPermuted>(v, tid, stages, hbuf, L);
+            hadamard_stages<LOG2N, false, kPermuted>(v, tid, stages, hbuf);
             float w[D], y[D], ss;
 #pragma unroll
             for (int j = 0; j < D; j++) w[j] = v[j] * scale;
@@ -380,8 +379,11 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
 }
 
 // Registers for eight waves a SIMD (64 a lane): with them two workgroups of 1024 lanes, which blocks of 8192 values need, share
-// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 72 / 80 / 81 / 99 us, calls in a row (with the
-// encoder before its places came out of a network 78 / 85 / 90 / 110).
+// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 61 / 76 / 79 / 99 us, calls in a row (with two barriers
+// an exchange, selections in the stages across lanes and divisions for the codes 65 / 80 / 83 / 106).  With float32 amplitudes blocks of 8192 take 72:
+// a row's end costs 27, since its sum, its codes and the next row's first values follow one another while the only other workgroup of
+// the unit is as often at a barrier.  Tried for it: the next values requested before the row's sum (registers in scratch memory, 111), codes
+// behind the next row's first barrier (100), by four waves in turn (100).
 template <typename TIn, int CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)

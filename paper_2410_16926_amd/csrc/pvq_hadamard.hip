@@ -72,7 +72,7 @@ __global__ __launch_bounds__(1024) void hadamard_kernel(const void *X, int64_t l
     // runs 8^P apart, instead of going through LDS once more.
     constexpr bool kSplitStore = LOG2N == 10 || LOG2N == 13;
     constexpr int kSplitP = LOG2N == 13 ? 4 : 3;
-    hadamard_stages<LOG2N, true, false, LOG2N <= 9 ? 4 : 0>(v, lane, log2n, smem, L);
+    hadamard_stages<LOG2N, true, LOG2N <= 9 ? 4 : 0>(v, lane, log2n, smem);
 
     if constexpr (kSplitStore) {
         // register q holds column  own_base(lane) + (q >> 1) + (q & 1) * 8^P  of the chunk
@@ -134,8 +134,8 @@ hipError_t pvq_launch_hadamard(const void *X, int in_dtype, int64_t rows, int64_
     const int chunk = 8 * L;
     const int chunks_per_row = (int)((cols + chunk - 1) / chunk);
     const float scale = (float)(1.0 / std::sqrt((double)block));
-    // two buffers for the exchanges between waves (none for blocks that fit a wave's 512 values)
-    const size_t lds = log2n > 9 ? 2 * (size_t)(chunk + chunk / 32 + 1) * sizeof(float) : 0;
+    // for the exchanges between waves (none for blocks that fit a wave's 512 values)
+    const size_t lds = log2n > 9 ? (size_t)(chunk + chunk / 32 + 1) * sizeof(float) : 0;
     const dim3 grid((unsigned)(rows * chunks_per_row)), blk((unsigned)L);
 #define PVQ_HAD_LAUNCH(I, O, N) \
     hipLaunchKernelGGL((hadamard_kernel<I, O, N>), grid, blk, lds, s, X, ldx, Y, ldy, cols, log2n, signs, signs_after, scale, chunks_per_row)

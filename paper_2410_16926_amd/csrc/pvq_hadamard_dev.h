@@ -68,7 +68,8 @@ template <int MASK, bool PERMUTE = false, bool MIRRORED = false>
 __device__ inline void stage_across_lanes(float (&v)[8], int place)
 {
     static_assert(MASK <= 8 || PERMUTE, "16 and 32: stage_across_rows");
-    const float sign = place & MASK ? -1.0f : 1.0f;
+    float sign = place & MASK ? -1.0f : 1.0f;
+    asm("" : "+v"(sign));                          // (else the product becomes a selection, which issues at half the rate)
 #pragma unroll
     for (int j = 0; j < 8; j++) {
         const float own = v[j] * sign;
@@ -137,13 +138,12 @@ __device__ constexpr uint32_t own_offset(int q)
     return ((uint32_t)q >> R) + (((uint32_t)q & ((1u << R) - 1u)) << (3 * P));
 }
 
-// Through LDS from ownership (P0, R0) to (P1, R1); the caller alternates two buffers, so that one barrier
-// per exchange is enough (a buffer is written again only after a barrier that every wave reaches after
-// its reads of it).
-template <int P0, int R0, int P1, int R1, bool SYNC_BEFORE = false>
+// Through LDS from ownership (P0, R0) to (P1, R1).  Value i of the chunk always lies at place i of the buffer, so a lane writes where it
+// (in a chunk's first exchange: its wave, whose LDS instructions are carried out in order) has read before and nobody else has:
+// one buffer and one barrier per exchange are enough.
+template <int P0, int R0, int P1, int R1>
 __device__ inline void exchange(float (&v)[8], float *buf, uint32_t lane)
 {
-    if constexpr (SYNC_BEFORE) __syncthreads();   // a single buffer: its readers of the exchange before are done
     float *w = buf + pad(own_base<P0, R0>(lane));
 #pragma unroll
     for (int q = 0; q < 8; q++) w[pad(own_offset<P0, R0>(q))] = v[q];
@@ -156,10 +156,9 @@ __device__ inline void exchange(float (&v)[8], float *buf, uint32_t lane)
 // The same to ownership (P1, R1) from where the stages inside a wave leave the values of blocks of 1024 and more: lanes as
 // load_lane says, register bit 2 and lane bit 4, and register bit 1 and lane bit 5, with their roles changed.  (The lanes
 // of a wave then write 64 words two apart, which all banks share evenly.)
-template <int P1, int R1, bool SYNC_BEFORE = false>
+template <int P1, int R1>
 __device__ inline void exchange_from_rows(float (&v)[8], float *buf, uint32_t lane)
 {
-    if constexpr (SYNC_BEFORE) __syncthreads();
     const uint32_t place = (lane & 4 ? lane ^ 3 : lane) & 15;
     float *w = buf + pad((lane >> 4 & 2) | (lane >> 2 & 4) | place << 3 | (lane >> 6) << 9);
 #pragma unroll
@@ -171,15 +170,15 @@ __device__ inline void exchange_from_rows(float (&v)[8], float *buf, uint32_t la
 }
 
 // All stages of blocks of 2^log2n values (LOG2N = 9: any block of up to 512 values, log2n says which;
-// 10 .. 13: that block size).  smem: two buffers of pad(8 L) + 1 floats when LOG2N > 9.  v: the 8 values of load_lane<LOG2N>(lane).
+// 10 .. 13: that block size).  smem: pad(8 L) + 1 floats when LOG2N > 9.  v: the 8 values of load_lane<LOG2N>(lane).
 // STAY: blocks of 1024 and 8192 values end with a single stage, whose ownership (P, 1), P = 3 or 4, still
 // has runs of four consecutive values per lane; with STAY the values are left there (register q holds
 // column own_base<P,1>(lane) + (q >> 1) + (q & 1) * 8^P of the chunk) instead of going through LDS once
 // more.  Otherwise the lane ends with its 8 consecutive values.
-// ONEBUF: one buffer of pad(8 L) + 1 floats instead of two, with a barrier in front of every exchange as
-// well (for a kernel that would rather have the LDS than save the barriers).
-template <int LOG2N, bool STAY, bool ONEBUF = false, int PERMUTED = 0>
-__device__ inline void hadamard_stages(float (&v)[8], int lane, int log2n, float *smem, int L)
+// (With a barrier in front of every exchange too, 8192 x 8192 rotated in blocks of 8192 and encoded took 81.3 us with float32 amplitudes
+// and 105.5 with 2-bit codes, now 72.0 and 99.0.)
+template <int LOG2N, bool STAY, int PERMUTED = 0>
+__device__ inline void hadamard_stages(float (&v)[8], int lane, int log2n, float *smem)
 {
     if constexpr (LOG2N > 9) log2n = LOG2N;
     constexpr bool kMirrored = LOG2N > 9;
@@ -207,15 +206,14 @@ __device__ inline void hadamard_stages(float (&v)[8], int lane, int log2n, float
     if constexpr (LOG2N > 9) {
         constexpr int R3 = LOG2N - 9 < 3 ? LOG2N - 9 : 3;
         constexpr bool kSingleLast = LOG2N == 10 || LOG2N == 13;
-        float *buf0 = smem, *buf1 = ONEBUF ? smem : smem + pad(8u * (uint32_t)L) + 1u;
-        exchange_from_rows<3, R3, ONEBUF>(v, buf0, lane);
+        exchange_from_rows<3, R3>(v, smem, lane);
         stages_in_registers(v, R3);
         if constexpr (LOG2N > 12) {
-            exchange<3, R3, 4, LOG2N - 12, ONEBUF>(v, buf1, lane);
+            exchange<3, R3, 4, LOG2N - 12>(v, smem, lane);
             stages_in_registers(v, LOG2N - 12);
-            if constexpr (!(STAY && kSingleLast)) exchange<4, LOG2N - 12, 0, 3, ONEBUF>(v, buf0, lane);
+            if constexpr (!(STAY && kSingleLast)) exchange<4, LOG2N - 12, 0, 3>(v, smem, lane);
         } else if constexpr (!(STAY && kSingleLast)) {
-            exchange<3, R3, 0, 3, ONEBUF>(v, buf1, lane);
+            exchange<3, R3, 0, 3>(v, smem, lane);
         }
     }
 }

@@ -462,12 +462,12 @@ __global__ __launch_bounds__(1024, 8) void rotate_encode16_kernel(rotate_encode_
             for (int j = 0; j < 8; j++) v[j] = pvq_hadamard_dev::with_sign(v[j], bits, j);
         }
     }
-    pvq_hadamard_dev::hadamard_stages<LOG2N, false>(v, lane, p.log2n, smem, L);
+    pvq_hadamard_dev::hadamard_stages<LOG2N, false>(v, lane, p.log2n, smem);
 #pragma unroll
     for (int j = 0; j < 8; j++) v[j] = v[j] * p.scale;
 
     // the chunk's groups are a tile of the index plane (whole words: the host checks it)
-    uint32_t *stream = reinterpret_cast<uint32_t *>(smem) + (LOG2N > 9 ? 2 * (pvq_hadamard_dev::pad(8u * (uint32_t)L) + 1u) : 0u);
+    uint32_t *stream = reinterpret_cast<uint32_t *>(smem) + (LOG2N > 9 ? pvq_hadamard_dev::pad(8u * (uint32_t)L) + 1u : 0u);
     const int per_chunk = L / 16;
     const int64_t g0 = (int64_t)chunk * per_chunk;
     const int ng = (int)min((int64_t)per_chunk, p.e.groups - g0);
@@ -1223,7 +1223,7 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
     p.e.pulses_out = nullptr; p.e.cols = a.cols;
     if (a.rows * p.chunks_per_row > 0x7FFFFFFF) return hipErrorInvalidValue;
     size_t lds = (size_t)(L / 16) * c->index_bits / 8 + 16;
-    if (log2n > 9) lds += 2 * (size_t)(chunk + chunk / 32 + 1) * sizeof(float);
+    if (log2n > 9) lds += (size_t)(chunk + chunk / 32 + 1) * sizeof(float);
     const dim3 grid((unsigned)(a.rows * p.chunks_per_row)), blk((unsigned)L);
 #define PVQ_RE(T, W, N) hipLaunchKernelGGL((rotate_encode16_kernel<T, W, N>), grid, blk, lds, s, p)
 #define PVQ_RE_N(T, W)                             \
