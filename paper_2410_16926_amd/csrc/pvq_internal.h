@@ -63,7 +63,7 @@ inline double pvq_wide_double(const uint32_t *w, int words)
 // coordinates: an encoder adds them up, a decoder finds them one after the other.
 // Contexts with D = 64 or 128: rows are at least as long as the windows of 64 that a decoder reads, with all ones behind the thresholds.
 inline int pvq_wide_row(int K) { return K < 31 ? 64 : 2 * K + 2; }
-inline int pvq_wide_key_row(int K) { return 2 * K + 2 + 6; }
+inline int pvq_wide_key_row(int K) { return 2 * K + 2 + 6 + 3 & ~3; }   // (whole pieces of 16 bytes)
 // The other decoder's first guess: keys by bit length and the three bits behind the leading one (their bits 18 to 31, less 21).
 inline int pvq_wide_buckets(int words) { return (32 * words + 1) * 8; }
 

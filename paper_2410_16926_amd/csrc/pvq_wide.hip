@@ -535,9 +535,9 @@ template <int W>
 struct lane_q {
     uint32_t q[W];
 
-    // pvq_wide_key of q, which lies below 2^(32 WP): its leading word and the one below are nearly always among the upper four
+    // pvq_wide_key of q, which lies below 2^(32 WP); `lower`: its leading word is not among the upper four, and it has another key
     template <int WP>
-    __device__ inline uint32_t key_of_q() const
+    __device__ inline uint32_t key_of_q(bool &lower) const
     {
         constexpr int w1 = WP > 1 ? WP - 2 : 0, w2 = WP > 2 ? WP - 3 : 0, w3 = WP > 3 ? WP - 4 : 0;
         uint32_t a = q[WP - 1], b = WP > 1 ? q[w1] : 0u;
@@ -546,18 +546,24 @@ struct lane_q {
             const bool none = a == 0 && b == 0;                    // both upper words
             const uint32_t c = none ? (WP > 4 ? q[WP > 4 ? WP - 5 : 0] : 0u) : q[w2];
             a = none ? q[w2] : a; b = none ? (WP > 3 ? q[w3] : 0u) : b; length = none ? 32 * (WP - 2) : length;
-            const bool lower = a == 0;
-            a = lower ? b : a; b = lower ? c : b; length -= lower ? 32 : 0;
+            const bool second = a == 0;
+            a = second ? b : a; b = second ? c : b; length -= second ? 32 : 0;
         } else if (WP > 1) {
-            const bool lower = a == 0;
-            a = lower ? b : a; b = lower ? 0u : b; length -= lower ? 32 : 0;
+            const bool second = a == 0;
+            a = second ? b : a; b = second ? 0u : b; length -= second ? 32 : 0;
         }
         const int lead = __builtin_clz(a | 1u);
         const uint32_t from_one = (uint32_t)((((uint64_t)a << 32 | b) << lead) >> 32);   // the 32 bits from the leading one on
-        uint32_t key = __builtin_amdgcn_alignbit((uint32_t)(length - lead), from_one, 10);
-        if (WP > 4) { if (a == 0) key = pvq_wide_key(q, WP); }
-        else key = a == 0 ? 0u : key;
-        return key;
+        const uint32_t key = __builtin_amdgcn_alignbit((uint32_t)(length - lead), from_one, 10);
+        lower = WP > 4 && a == 0;
+        return WP > 4 || a != 0 ? key : 0u;
+    }
+    template <int WP>
+    __device__ inline uint32_t key_of_q() const
+    {
+        bool lower;
+        const uint32_t key = key_of_q<WP>(lower);
+        return lower ? pvq_wide_key(q, WP) : key;
     }
 
     // The coordinate's place in a row by the tables in device memory, two dependent trips: the guess of q's bucket, the four
@@ -611,147 +617,187 @@ struct lane_q {
 // ---- many groups: a lane per group, the rows of the tables in LDS ------------------------------------------
 // All lanes of a workgroup are at the same coordinate, so they need the same row, of it the places from their largest 2 k + 1
 // down (k pulses left; a coordinate of magnitude m is 2 m places below 2 k), and rows of fewer dimensions in fewer words.  The
-// rows go through LDS in turn, requested three coordinates ahead; the window is a matter of the workgroup's
-// largest and smallest k, looked at every eighth coordinate (k only falls, the margin below covers the rest).
+// rows go through LDS in turn, brought by a wave of their own, two rows for every barrier; the window is a matter of the
+// workgroup's largest and smallest k, looked at every eighth coordinate (k only falls, the margin below covers the rest).
 // A coordinate takes three keys (places 3, 7 and 11 below 2 k), the four keys of the block of places they point to, and the
 // threshold: three dependent reads of LDS.  A lane whose place is further down, or lies below the window (points that have
 // nearly all their pulses in a few coordinates), looks it up in device memory.
-// Bound by the walk's chain, about 150 instructions and the three reads a coordinate, 0.55 us of a wave alone; from two
-// waves a SIMD on by their issue (90 vector and 45 scalar instructions).  D = 128, K = 187, 8192-wide rows, 512 / 1024 / 2048 /
-// 4096 of them: 72 / 75 / 84 / 108 us; with guess, keys and thresholds in device memory 95 / 100 / 155 / 161.  D = 64, K = 96:
-// 37 / 41 / 53 / 97, before 55 / 57 / 86 / 104.  Four coordinates share a turn of the loop, so that slots and shifts are known
-// when it is compiled (one at a time: 104 / 104 / 117 us for the first three).
+// Bound by the walk's chain, about 100 instructions and the three reads a coordinate, 0.41 us of a wave alone; from two waves a
+// SIMD on by their issue as well.  D = 128, K = 187, 8192-wide rows, 512 / 1024 / 2048 / 4096 of them: 54 / 60 / 70 / 89 us; with
+// every wave requesting its share of every row (45 scalar instructions a coordinate), a barrier for every coordinate, comparisons and
+// carries that wait for one another, and three branches where one is now, 72 / 75 / 85 / 110; with guess, keys and thresholds in
+// device memory 95 / 100 / 155 / 161.  D = 64, K = 96: 31 / 35 / 46 / 97, before 37 / 41 / 53 / 99 and 55 / 57 / 86 / 104.  Four
+// coordinates share a turn of the loop, so that shifts are known when it is compiled.
 constexpr int kRowWindow = 256;       // places of a row in LDS
+constexpr int kRowMargin = 96;        // of them below the smallest 2 k when the window is set
 constexpr int kRowPad = 16;           // keys in front of them: zeros
 
-// A row in LDS: kT pieces of 16 bytes a lane for the thresholds, kK words a lane for the keys behind their padding.
-constexpr int rows_pieces(int W, int lanes) { return (kRowWindow * W / 4 + lanes - 1) / lanes; }
-constexpr int rows_keys(int lanes) { return (kRowWindow + lanes - 1) / lanes; }
+// A row in LDS: the keys behind their padding, the thresholds.  (The places that step looks for lie at most 17 below the
+// window: in the keys.)
 constexpr int kPointWords = 19;       // 64 coordinates on their way out: 16 words of magnitudes, 2 of signs, and one for the banks' sake
-constexpr int kRowSlots = 4;          // rows in LDS: the present coordinate's, the next two, and the one on its way
+constexpr uint32_t kRowKeys = 4 * kRowPad, kRowThresholds = kRowKeys + 4 * kRowWindow;
+constexpr uint32_t row_bytes(int W) { return kRowThresholds + 4 * kRowWindow * W; }
+static_assert(kRowThresholds >= 17 * 4 * 16, "a place below the window");
+// Rows in LDS: the present pair's, the next one's, and the pair on its way; with integers of 16 words without the last, so that
+// two workgroups fit a unit, with 8 words so that three do (D = 64, K = 96, 2048 / 3072 tokens 46 / 69 us; six rows in LDS 47 / 72).
+constexpr int row_slots(int W) { return W == 8 || W == 16 ? 4 : 6; }
+constexpr int rows_ahead(int W) { return row_slots(W) / 2 - 1; }   // pairs
 constexpr size_t decode_rows_lds(int W, int lanes)
 {
-    const size_t rows = (size_t)kRowSlots * (16 * rows_pieces(W, lanes) * lanes + 4 * (kRowPad + rows_keys(lanes) * lanes)) + (lanes / 64) * 8;
+    const size_t rows = (size_t)row_slots(W) * row_bytes(W) + (lanes / 64) * 8 + 4;
     return std::max(rows, (size_t)4 * kPointWords * lanes);
+}
+
+// The wave that brings the rows.  It has W + 1 loads on their way for a row (lanes past the window load its end once more) and
+// waits for them by that number, in order; the compiler does not see that they write LDS.
+template <int D, int W, int LANES>
+__device__ inline void bring_rows(const decode_wide_params &p, uint32_t slots, int *stat, int lane)
+{
+    constexpr int kSlots = row_slots(W), kAhead = rows_ahead(W);
+    int lo = 0;
+    uint32_t from[W], key_from = 0;                                // the lane's places of every load
+    auto set_window = [&](int most2, int least2) {
+        // (read behind one of the next barriers; the first place a multiple of four, as the keys come in fours)
+        lo = __builtin_amdgcn_readfirstlane(max(max(least2 - kRowMargin, most2 + 2 - kRowWindow), 0) + 3 & ~3);
+        stat[2 * (LANES / 64)] = lo;
+        const int count = __builtin_amdgcn_readfirstlane(most2 + 2) - lo;
+#pragma unroll
+        for (int x = 0; x < W; x++) from[x] = (uint32_t)min(1024 * x + 16 * lane, count * 4 * W - 16);
+        key_from = (uint32_t)min(16 * lane, (count + 3 & ~3) * 4 - 16);
+    };
+    int c = 0;
+    uint32_t slot = slots;
+    // row of coordinate c (past the last: row 0, not used) into the next slot
+    auto request = [&]() {
+        lo = __builtin_amdgcn_readfirstlane(lo); slot = __builtin_amdgcn_readfirstlane(slot); c = __builtin_amdgcn_readfirstlane(c);
+        const uint32_t row = (uint32_t)max(D - 1 - c, 0);
+        const unsigned char *t = reinterpret_cast<const unsigned char *>(p.tab_t) + (row * (uint32_t)p.row_len + (uint32_t)lo) * (4u * W);
+        const unsigned char *key = reinterpret_cast<const unsigned char *>(p.tab_key) + (row * (uint32_t)p.key_len + (uint32_t)lo) * 4u;
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                     : : "s"(slot + kRowKeys), "v"(key_from), "s"(key) : "memory", "m0");
+#pragma unroll
+        for (int x = 0; x < W; x++) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                         : : "s"(slot + kRowThresholds + 1024u * x), "v"(from[x]), "s"(t) : "memory", "m0");
+        }
+        c++;
+        slot = slot == slots + (kSlots - 1) * row_bytes(W) ? slots : slot + row_bytes(W);
+    };
+    set_window(2 * p.K, 2 * p.K);
+#pragma unroll 1
+    for (int x = 0; x < 2 * kAhead; x++) request();
+#pragma unroll 1
+    for (int pair = 0; pair < D / 2; pair++) {
+        // the pair's rows are in LDS once only the later ones' loads are on their way; behind the barrier the pair before has been used
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((kAhead - 1) * 2 * (W + 1)) : "memory");
+        if ((pair & 3) == 0 && pair > 0) {
+            int most2 = 0, least2 = 2 * p.K;
+#pragma unroll
+            for (int w = 0; w < LANES / 64; w++) { most2 = max(most2, stat[2 * w]); least2 = min(least2, stat[2 * w + 1]); }
+            set_window(most2, min(least2, most2));
+        }
+        request();
+        request();
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");             // (LDS is used otherwise behind this)
 }
 
 template <int CP, int W, int LANES>
 struct rows_walk : lane_q<W> {
     using lane_q<W>::q;
     static constexpr int D = 64 * CP;
-    static constexpr int kT = rows_pieces(W, LANES), kK = rows_keys(LANES);
-    static constexpr uint32_t kTBytes = 16 * kT * LANES, kKBytes = 4 * (kRowPad + kK * LANES);   // of a slot
     const decode_wide_params &p;
-    const uint32_t ts, ks;            // LDS addresses of the slots' thresholds, keys
-    int *const stat;                  // LDS: every wave's largest and smallest 2 k
+    const uint32_t slots;             // LDS address of the rows
+    int *const stat;                  // LDS: every wave's largest and smallest 2 k, the window's first place
     const int tid, wave;
     const bool walks;                 // the wave has a group to walk for
     int k2, n2, i;                    // 2 k, 4 sum m^2
     uint32_t sign, mag;               // the last coordinates' places' lowest bits, the latest on top; their magnitudes, a byte each
-    int lo[kRowSlots];                // first place of a slot's window
-    int latest_lo, latest_count;      // the window of the rows requested from now on
+    uint32_t slot;                    // the coordinate's row
+    int first;                        // the first place of its window
 
     template <typename T>
     __device__ __forceinline__ static T from_lds(uint32_t at) { return *reinterpret_cast<const __attribute__((address_space(3))) T *>(at); }
-
-    __device__ inline void set_window(int most2, int least2)
-    {
-        latest_lo = __builtin_amdgcn_readfirstlane(max(max(least2 - 64, most2 + 2 - kRowWindow), 0));
-        latest_count = __builtin_amdgcn_readfirstlane(most2 + 2) - latest_lo;
-    }
-    // The window's places of coordinate c's row (past the last: row 0, not used) straight into slot S.  The compiler does not
-    // see that these loads write LDS; a wave has kT + kK of them on their way for a row (lanes past the window load its end
-    // once more, or what lies behind it in the tables, into the slot's rest) and step waits for them by that number, in order.
-    template <int S>
-    __device__ inline void request(int c)
-    {
-        // (the same for the workgroup)
-        latest_lo = __builtin_amdgcn_readfirstlane(latest_lo); latest_count = __builtin_amdgcn_readfirstlane(latest_count);
-        lo[S] = latest_lo;
-        const uint32_t row = (uint32_t)max(D - 1 - c, 0);
-        const unsigned char *t = reinterpret_cast<const unsigned char *>(p.tab_t) + (row * (uint32_t)p.row_len + (uint32_t)latest_lo) * (4u * W);
-        const unsigned char *key = reinterpret_cast<const unsigned char *>(p.tab_key) + (row * (uint32_t)p.key_len + (uint32_t)latest_lo) * 4u;
-        const int last = latest_count * (4 * W) - 16;
-#pragma unroll
-        for (int x = 0; x < kT; x++) {
-            const uint32_t from = (uint32_t)min(16 * tid, max(last - x * LANES * 16, 0));
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-                         : : "s"(ts + (S * kTBytes + (uint32_t)(x * LANES * 16)) + (uint32_t)(wave * 1024)), "v"(from), "s"(t + x * LANES * 16) : "memory", "m0");
-        }
-#pragma unroll
-        for (int x = 0; x < kK; x++) {
-            const uint32_t from = (uint32_t)min(4 * tid, max(4 * latest_count - 4 - x * LANES * 4, 0));
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2"
-                         : : "s"(ks + (S * kKBytes + (uint32_t)(4 * kRowPad + x * LANES * 4)) + (uint32_t)(wave * 256)), "v"(from), "s"(key + x * LANES * 4) : "memory", "m0");
-        }
-    }
-    // before the first coordinate: all of a lane's pulses are left
-    __device__ inline void start()
-    {
-        set_window(2 * p.K, 2 * p.K);
-        request<0>(0);
-        request<1>(1);
-        request<2>(2);
-    }
 
     // coordinate i + S, i a multiple of four; every q of the wave lies below 2^(32 WP)
     template <int WP, int S>
     __device__ inline void step()
     {
-        // the row is in LDS once only the next two rows' loads are on their way, and the row before it has been used
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"(2 * (kT + kK)) : "memory");
-        if (S == 0 && (i & 4) == 0 && i > 0) {
-            int most2 = 0, least2 = 2 * p.K;
-#pragma unroll
-            for (int w = 0; w < LANES / 64; w++) { most2 = max(most2, stat[2 * w]); least2 = min(least2, stat[2 * w + 1]); }
-            set_window(most2, min(least2, most2));
-        }
-        request<(S + 3) % kRowSlots>(i + S + 3);
-        if (!walks) return;
-        const uint32_t row = (uint32_t)(D - 1 - S - i);
-        const uint32_t kq = this->template key_of_q<WP>();
+        slot = __builtin_amdgcn_readfirstlane(slot);               // (the same for the workgroup)
+        bool unknown;
+        const uint32_t kq = this->template key_of_q<WP>(unknown);
         // places below 2 k whose threshold is above q: three keys, then the four of the block of places they point to
-        const int first = __builtin_amdgcn_readfirstlane(lo[S]);
         const int top = max(k2 - first, -1);
-        uint32_t keys = ks + (S * kKBytes + 4 * (kRowPad - 11));
+        uint32_t keys = slot + (kRowKeys - 4 * 11);
         asm volatile("" : "+s"(keys));                             // (one address for the reads' small offsets)
         const uint32_t at = keys + 4u * (uint32_t)top;
-        int down = (from_lds<uint32_t>(at + 32) > kq ? -4 : 0) + (from_lds<uint32_t>(at + 16) > kq ? -4 : 0) + (from_lds<uint32_t>(at) > kq ? -4 : 0);
+        // (differences of keys, which lie below 2^31, by their signs (the integers have at most 438 bits): a comparison's result may be used
+        // two instructions later only
+        auto above = [&](uint32_t place) { return (int)(kq - from_lds<uint32_t>(place)) >> 31; };
+        int down = 4 * (above(at + 32) + above(at + 16) + above(at));
         const uint32_t block = keys + 4u * (uint32_t)(top + down);
-        down -= from_lds<uint32_t>(block + 44) > kq ? 1 : 0; down -= from_lds<uint32_t>(block + 40) > kq ? 1 : 0;
-        down -= from_lds<uint32_t>(block + 36) > kq ? 1 : 0; down -= from_lds<uint32_t>(block + 32) > kq ? 1 : 0;
+        down += (above(block + 44) + above(block + 40)) + (above(block + 36) + above(block + 32));
         const int in_window = top + down;
         uint32_t j = (uint32_t)(first + in_window);
-        const uint32_t entry = ts + (uint32_t)__mul24(max(in_window, 0), 4 * W);
+        const uint32_t entry = slot + (uint32_t)__mul24(in_window, 4 * W);
         uint32_t t[(WP + 3) / 4 * 4];
 #pragma unroll
         for (int x = 0; x < (WP + 3) / 4; x++) {
-            const u32x4 v = from_lds<u32x4>(entry + (S * kTBytes + 16 * x));
+            const u32x4 v = from_lds<u32x4>(entry + (kRowThresholds + 16 * x));
             t[4 * x] = v[0]; t[4 * x + 1] = v[1]; t[4 * x + 2] = v[2]; t[4 * x + 3] = v[3];
         }
-        // below the window, or further down than the keys that were looked at
-        const bool elsewhere = in_window < 0 || down == -16;
-        if (elsewhere) {
-            j = lane_q<W>::place_by_guess(p, row, kq, k2 >> 1);
-            lane_q<W>::template read_threshold<WP>(p, row, j, t);
-            // used here, so that the compiler's wait for it stands here: behind the branch it would be one for the rows just
-            // requested as well
+        // q - t in three parts side by side, and what a part owes the next
+        constexpr int kParts = WP >= 6 ? 3 : 1, kPart = (WP + kParts - 1) / kParts;
+        uint32_t owes[kParts] = {};
 #pragma unroll
-            for (int x = 0; x < (WP + 3) / 4 * 4; x++) asm volatile("" : "+v"(t[x]));
+        for (int y = 0; y < kPart; y++)
+#pragma unroll
+            for (int part = 0; part < kParts; part++)
+                if (const int x = part * kPart + y; x < WP) q[x] = __builtin_subc(q[x], t[x], owes[part], &owes[part]);
+        uint32_t br = owes[kParts - 1];
+#pragma unroll
+        for (int part = 1; part < kParts; part++) {
+            uint32_t far;                                          // owed further than a word
+            q[part * kPart] = __builtin_subc(q[part * kPart], 0u, owes[part - 1], &far);
+            br |= far;
         }
-        this->template subtract<WP>(p, row, j, t);
+        // below the window, or further down than the keys that were looked at; another key; equal keys: by the tables in device memory
+        if (min(in_window, down + 15) < 0 || unknown || br) {
+#pragma unroll
+            for (int part = 0; part < kParts; part++) {
+                q[part * kPart] += part > 0 ? owes[part > 0 ? part - 1 : 0] : 0u;
+                uint32_t c = 0;
+#pragma unroll
+                for (int x = part * kPart; x < WP && x < (part + 1) * kPart; x++) q[x] = __builtin_addc(q[x], t[x], c, &c);
+            }
+            const uint32_t row = (uint32_t)(D - 1 - S - i);
+            j = lane_q<W>::place_by_guess(p, row, this->template key_of_q<WP>(), k2 >> 1);
+            lane_q<W>::template read_threshold<WP>(p, row, j, t);
+            this->template subtract<WP>(p, row, j, t);
+        }
         const int left2 = (int)(j & ~1u), d = k2 - left2;
         k2 = left2;
         n2 = (int)__umul24((uint32_t)d, (uint32_t)d) + n2;
         mag = S == 0 ? (uint32_t)d >> 1 : (uint32_t)d << (8 * S - 1) | mag;
         sign = __builtin_amdgcn_alignbit(j, sign, 1);
+        slot = slot == slots + (row_slots(W) - 1) * row_bytes(W) ? slots : slot + row_bytes(W);
+    }
+    template <int WP, int S>
+    __device__ __forceinline__ void two_steps()
+    {
+        asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" : : : "memory");
+        // the rows from this pair on have another window than those before
+        constexpr int kAhead = rows_ahead(W);
+        if ((S == 0 && i == 0) || (S == (kAhead == 1 ? 2 : 0) && (i & 4) == (kAhead == 1 ? 0 : 4)))
+            first = __builtin_amdgcn_readfirstlane(stat[2 * (LANES / 64)]);
+        if (walks) { step<WP, S>(); step<WP, S + 1>(); }
     }
 
     // mags, signs: the point
     template <int WP>
     __device__ __forceinline__ void four_steps(uint32_t (&mags)[D / 4], uint32_t (&signs)[D / 32])
     {
-        step<WP, 0>(); step<WP, 1>(); step<WP, 2>(); step<WP, 3>();
+        two_steps<WP, 0>(); two_steps<WP, 2>();
         const int at = __builtin_amdgcn_readfirstlane(i) >> 2;
         mags[at] = mag;
 #pragma unroll
@@ -776,15 +822,19 @@ struct rows_walk : lane_q<W> {
 };
 
 template <int CP, int W, int LANES>
-__global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_kernel(decode_wide_params p)
+__global__ __launch_bounds__(LANES + 64, LANES == 512 ? (W <= 8 ? 7 : 5) : 1) void decode_wide_rows_kernel(decode_wide_params p)
 {
     extern __shared__ __align__(16) uint32_t lds_words[];
     constexpr int D = 64 * CP;
-    using walk_t = rows_walk<CP, W, LANES>;
-    uint32_t *keys = lds_words + kRowSlots * walk_t::kTBytes / 4;
-    int *stat = reinterpret_cast<int *>(keys + kRowSlots * walk_t::kKBytes / 4);
+    int *stat = reinterpret_cast<int *>(lds_words + row_slots(W) * row_bytes(W) / 4);
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const uint32_t slots = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)lds_words;
+    if (wave == LANES / 64) {
+        bring_rows<D, W, LANES>(p, slots, stat, lane);
+        __syncthreads();
+        return;
+    }
     const int64_t g0 = (int64_t)blockIdx.x * LANES;
     // the lane's group (lanes behind the last group take that one, and write nothing)
     const int64_t gid = std::min<int64_t>(g0 + tid, p.total_groups - 1);
@@ -806,16 +856,13 @@ __global__ __launch_bounds__(LANES, LANES == 512 ? 4 : 1) void decode_wide_rows_
 #pragma unroll
     for (int i = 0; i < W; i++) q[i] = walkers ? (uint32_t)__shfl((int)q[i], source, 64) : 0u;
 
-    if (tid < kRowSlots * kRowPad) keys[tid / kRowPad * (walk_t::kKBytes / 4) + tid % kRowPad] = 0;
-    auto lds_address = [](void *at) { return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) unsigned char *)at; };
-    walk_t walk{{}, p, lds_address(lds_words), lds_address(keys), stat, tid, wave, walkers != 0};
+    if (tid < row_slots(W) * kRowPad) lds_words[tid / kRowPad * (row_bytes(W) / 4) + tid % kRowPad] = 0;
+    rows_walk<CP, W, LANES> walk{{}, p, slots, stat, tid, wave, walkers != 0};
 #pragma unroll
     for (int i = 0; i < W; i++) walk.q[i] = q[i];
-    walk.k2 = 2 * p.K; walk.n2 = 0; walk.i = 0; walk.sign = walk.mag = 0;
+    walk.k2 = 2 * p.K; walk.n2 = 0; walk.i = 0; walk.sign = walk.mag = 0; walk.slot = slots; walk.first = 0;
     uint32_t mags[D / 4], signs[D / 32] = {};   // (mags: D = 64 in registers, indexed by what is the same for all lanes, D = 128 in scratch)
-    walk.start();
     walk.template walk<W>(mags, signs);
-    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");             // (the workgroup's LDS is not given back before the last loads into it)
 
     int n2 = walk.n2 >> 2;
     if (valid && one_hot) {
@@ -1249,27 +1296,33 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
 
 // Up to this many groups a wave per group decodes.  Its time grows with the groups once the SIMDs' issue slots are full, in
 // steps, by the width of the integers (and for many pulses by the windows a coordinate is looked for in); a lane per group
-// takes the one walk of a wave whatever their number, until there are several waves per SIMD.  us, wave / lane, to bfloat16:
-//                        128 groups   2048        3520        4096        4608        4736
-//   D = 128, K = 28      23 / 57      30 / 58     44 / 58     44 / 58     52 / 58     61 / 58     (integers of 4 words)
-//            K = 84      23 / 65      30 / 66     58 / 66     71 / 66     78 / 66     79 / 66     (8)
-//            K = 187     24 / 70      34 / 72     73 / 72     76 / 72     87 / 72     92 / 72     (12)
-//   D = 64,  K = 40      13 / 30      16 / 30     23 / 30     24 / 30     27 / 30     32 / 30     (4)
-//            K = 96      13 / 33      17 / 34     31 / 34     38 / 34     41 / 34     41 / 34     (8)
-//            K = 127     13 / 39      17 / 39     31 / 39     38 / 39     41 / 39     41 / 39     (8)
-//            K = 160     5120 groups: 43 / 46                                                    (8)
-//            K = 220     17 / 47      24 / 48     40 / 48     43 / 48     50 / 47     51 / 48     (12)
-//            K = 255     21 / 48      30 / 48     45 / 48     50 / 48     57 / 48     57 / 48     (12)
+// takes the one walk of a wave whatever their number, until there are several waves per SIMD.  us, a wave per group, and lanes
+// (the last column):
+//                        2048   2176   2560   2816   3072   3200   3584   3840   4096   4352   4608    lanes
+//   D = 128, K = 28      29     36     36     44     44     44     44     44     44     51     51      45      (integers of 4 words)
+//            K = 84      30     37     37     46     46     56     58                                  50      (8)
+//            K = 120     33     51     56     63     66     67     73                                  50      (12)
+//            K = 187     33     51     56     63     66     67     73                                  52      (12)
+//            K = 255     56     60     67     68     71     82     85                                  67      (16)
+//   D = 64,  K = 40      16     19     19     23     23     23     23     23     23     27     27      23      (4)
+//            K = 96      16     20     20     25     25     30     31                                  26      (8)
+//            K = 127     16     20     20     25     25     30     31     35     37     39     40      31      (8)
+//            K = 150     16     20     20     25     25     30     31     35     37     39     40      41      (8)
+//            K = 160     5120 groups: 43 / 46                                                                  (8; lanes: device memory)
+//            K = 220     2048 24, 3520 40, 4096 43, 4608 50 / lanes 47 to 48                                   (12; the same)
+//            K = 255     2048 30, 3520 45, 4096 50, 4608 57 / 48                                               (12; the same)
 static int64_t few_groups(const pvq_ctx *c)
 {
-    if (c->D == 64 && c->words == 8 && c->K > 135) return 5120;
-    return c->words == 4 || (c->D == 64 && c->K > 112 && c->K <= 230) ? 4608 : 3584;
+    if (c->words == 4) return 4096;
+    if (c->D == 128) return c->words == 8 ? 3072 : c->K > 255 ? 3584 : c->words == 12 ? 2048 : 2560;
+    if (c->words == 8) return c->K <= 112 ? 3072 : c->K <= 135 ? 3584 : c->K <= 150 ? 4352 : 5120;
+    return c->K <= 230 ? 4608 : 3584;
 }
 
 // Beyond that, whether the rows of the tables go through LDS.  They do while a magnitude fits a byte; but with more than about
 // twice as many pulses as coordinates many places lie outside a window of 256, and then all of them are as well read from device
-// memory: with many pulses always, with fewer once a unit has more groups than its two workgroups of 512 take at once.  us, LDS /
-// device memory:
+// memory: with many pulses always, with fewer once a unit has more groups than its two workgroups of 512 take at once.  us, LDS
+// (every wave requesting its share of the rows; the present form takes 10 to 25 % less up to K = 127) / device memory:
 //                    8192 groups   131072     262144     393216     524288     1048576
 //   D = 64, K = 96     34 / 44     42 / 58    55 / 88    83 / 94    100 / 107   187 / 197   (device memory with an earlier kernel)
 //           K = 112    35 / 43     46 / 59    58 / 88    91 / 95    109 / 109   203 / 201   (the same)
@@ -1303,7 +1356,7 @@ static hipError_t launch_rows(const decode_wide_params &p, size_t lds, hipStream
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES), lds, s, p);
+        hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES + 64), lds, s, p);
         return hipSuccess;
     } else {
         return hipErrorInvalidValue;
