@@ -337,7 +337,7 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
         const TIn *xrow = reinterpret_cast<const TIn *>(a.W) + row * a.ldw;
         uint32_t *irow = a.index_out + row * a.index_row_words;
         for (int ch = 0; ch < chunks; ch++) {
-            const int g = ch * L + tid;
+            const int g = ch * L + (CODES ? anew(tid) : tid);
             float v[D];
             raw8<TIn> raw;
             const uint32_t at = anew(from);                      // (an offset from a scalar address, not a pointer that moves with the chunks)
@@ -365,13 +365,13 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
             if (quad_pos < 3) irow[3 * (g >> 2) + quad_pos] = word;
             if constexpr (CODES) {
                 const float s64 = wave_pair_sum(ss);
-                if (lane == kWave - 1) wsum[ch * waves + wave] = s64;
+                if (anew(lane) == kWave - 1) wsum[ch * waves + wave] = s64;
             }
         }
         if constexpr (CODES) {
             __syncthreads();
-            const float rowss = row_sum(wsum, lane);
-            if (threadIdx.x == 0) a.rownorm_out[row] = rowss;
+            const float rowss = row_sum(wsum, anew(lane));
+            if (anew(tid) == 0) a.rownorm_out[row] = rowss;
             write_codes<CODES>(sb, l.ss_row, rowss, l.tree, reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, G, wave, waves, anew(lane));
             wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
         }
