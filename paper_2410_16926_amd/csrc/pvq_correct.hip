@@ -684,7 +684,12 @@ void launch_step(float *W, const float *U, float *work, const correct_shape &a, 
     const uint32_t steps = (uint32_t)((a.rows + kStepRows - 1) / kStepRows);
     const uint32_t most = panel_wgs >= (int)kUnits ? kUnits : a.rows > 2048 ? 4 * kUnits : 16 * kUnits;
     update_split parts;
-    parts.log2_chunks = steps >= 8 ? 3 : steps >= 4 ? 2 : steps >= 2 ? 1 : 0;
+    // As many chunks as take about the same number of steps: a die whose chunks have one step in two more than the others' keeps
+    // the launch waiting (768 rows, 12 steps, of 8192: in eight chunks 1507 us, in four 1451; 1280 rows in eight 1756, in four 1638; 320 rows
+    // in four 1317, in one 1290).
+    parts.log2_chunks = 3;
+    auto rows_of_chunks = [&]() { return (int64_t)(steps + (1u << parts.log2_chunks) - 1 >> parts.log2_chunks << parts.log2_chunks) * kStepRows; };
+    while (parts.log2_chunks > 0 && 16 * (rows_of_chunks() - a.rows) > a.rows) parts.log2_chunks--;
     const uint32_t chunks = 1u << parts.log2_chunks;
     parts.steps = steps / chunks;
     parts.longer = steps % chunks;
@@ -727,14 +732,15 @@ hipError_t launch_panels(int D, float *W, const float *U, float *work, const cor
 
 // W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: `buffers` (two or four) of rows x 128 floats.
 // Two panels a launch where the updates are what there is to wait for; with few rows, or up to 2048 of a narrow matrix, it is the chain,
-// whose fronts get longer (one / two panels, 256 x 4096 555 / 576 us, 512 x 4096 624 / 617, 512 x 8192 1419 / 1326, 1024 x 1024 135 / 142,
-// 768 x 2048 301 / 302, 8192 x 704 138 / 128).
+// whose fronts get longer (one / two panels in groups of 8, 512 x 8192 1343 / 1378 us, 768 x 6144 1020 / 1039, 768 x 8192 1451 / 1451,
+// 1024 x 2048 294 / 311, 1024 x 4096 670 / 667, 1280 x 2560 397 / 406, 1280 x 3072 497 / 497, 1536 x 2048 318 / 321, 2048 x 2048 338 / 330,
+// 8192 x 704 138 / 128; in groups of 16 1024 x 4096 531 / 522, 768 x 8192 1218 / 1163, in groups of 32 547 / 540, 1273 / 1196).
 hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
                           int64_t ldu, float *work, int buffers, hipStream_t s)
 {
     correct_shape a;
     a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
-    const bool two = buffers == 4 && (rows > 2048 || (rows >= 512 && cols >= 2048));
+    const bool two = buffers == 4 && (rows > 2048 || (rows > 512 && (rows - 512) * cols >= 1 << 21));
     return two ? launch_panels<2>(c->D, W, U, work, a, s) : launch_panels<1>(c->D, W, U, work, a, s);
 }
 

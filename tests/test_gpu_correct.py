@@ -174,12 +174,19 @@ def test_rows_of_an_update_task(D, K, rows, cols):
     run_correct(D, K, rows, cols, seed=si.BASE_SEED + 660 + rows)
 
 
+@pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 200, 384), (8, 16, 321, 448), (8, 16, 577, 448), (16, 33, 768, 384), (8, 16, 1281, 320)])
+def test_rows_in_eight_chunks_or_fewer(D, K, rows, cols):
+    # 4, 6, 10, 12 and 21 steps of 64 rows: in one chunk, 12 in four
+    run_correct(D, K, rows, cols, seed=si.BASE_SEED + 680 + rows)
+
+
 @pytest.mark.parametrize("D,K,rows,cols,ld_extra", [
     (8, 16, 511, 2048, 0), (8, 16, 512, 2048, 0), (8, 16, 513, 2112, 4), (16, 33, 1041, 2240, 8), (32, 60, 600, 2176, 0), (8, 16, 2048, 1984, 0),
+    (8, 16, 1024, 4096, 0), (8, 16, 1023, 4096, 0), (8, 16, 1500, 2176, 4), (16, 33, 2041, 1408, 8), (32, 60, 1290, 2752, 0),
     (8, 16, 2049, 64, 0), (8, 16, 2100, 192, 0), (32, 60, 2180, 576, 4), (8, 5, 4100, 448, 0), (16, 33, 4112, 320, 0), (8, 16, 8200, 384, 0)])
 def test_two_panels_a_launch(D, K, rows, cols, ld_extra):
-    # the smallest work buffer has room for one panel a launch, twice as much for two (the rule's lines are at 512 and 2048 rows and 2048
-    # columns): the same bits, odd and even numbers of panels, the last one of 64 columns or 128, workgroups and shares with a ragged end,
+    # the smallest work buffer has room for one panel a launch, twice as much for two (the rule's lines are at 2048 rows and at
+    # 2^21 values behind the first 512 rows): the same bits, odd and even numbers of panels, the last one of 64 columns or 128, workgroups and shares with a ragged end,
     # and nothing written behind the buffer
     g = torch.Generator(device="cuda")
     g.manual_seed(si.BASE_SEED + 670 + rows)
