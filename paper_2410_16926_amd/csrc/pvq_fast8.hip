@@ -370,6 +370,7 @@ __global__ __launch_bounds__(kGemvThreads) void gemv8_kernel(fast8_launch f, pvq
         float *pbuf = part + parity * (64 * NB);
 #pragma unroll
         for (int i = 0; i < RI; i++) {
+            if (batch + i * rl + rowlane > r_last) break;          // (the same for the wave, whose rows end here)
             ahead_t cu;
             if constexpr (AHEAD) {
                 cu = nx;
@@ -1013,18 +1014,27 @@ hipError_t pvq_fast8_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, i
 
 namespace {
 
+// rows that a workgroup of gemv8_kernel has at a time, one for each of its waves that share a slice
+int row_lanes(const pvq_decode_args &a)
+{
+    const int nsl = (int)((a.groups + kTileGroups - 1) / kTileGroups);
+    return std::max(1, (kGemvThreads / kWave) / nsl);
+}
+
 // one launch of the fused product for vectors [b0, b0 + NB)
 template <int NB>
 hipError_t launch_gemv_pass(const pvq_ctx *c, const pvq_decode_args &a, int b0, hipStream_t s)
 {
     const fast8_launch f = make_launch(c);
     const int nsl = (int)((a.groups + kTileGroups - 1) / kTileGroups);
-    const int rl = std::max(1, (kGemvThreads / kWave) / nsl);
-    const int RB = (NB == 1 ? kGemvRowsPerWaveAhead : kGemvRowsPerWave) * rl;
+    const int rl = row_lanes(a);
     const size_t lds = 0;  // the kernels own the whole LDS statically
-    const int64_t batches = (a.rows + RB - 1) / RB;
-    const int64_t nblocks = std::max<int64_t>(1, std::min<int64_t>(g_num_cus > 0 ? g_num_cus : 256, batches));
-    const int rows_per_block = (int)(((batches + nblocks - 1) / nblocks) * RB);
+    // Rows in rounds of one for each of a workgroup's row lanes, as many workgroups as there are units: a row of a wave (256 groups) takes
+    // 2 us, so a unit without rows costs more than the copy of the tables (whole batches of rows, two or
+    // four times as many: 1024 x 8192, 1 / 2 vectors, 8.8 / 13.4 us, now 7.3 / 7.9; 6000 x 5984 15.7 / 21.1, now 14.9 / 15.7).
+    const int64_t rounds = (a.rows + rl - 1) / rl;
+    const int64_t nblocks = std::max<int64_t>(1, std::min<int64_t>(g_num_cus > 0 ? g_num_cus : 256, rounds));
+    const int rows_per_block = (int)(((rounds + nblocks - 1) / nblocks) * rl);
     const dim3 grid((unsigned)((a.rows + rows_per_block - 1) / rows_per_block)), block((unsigned)(kWave * nsl * rl));
     return launch_gemv_nb<NB>(f, a, b0, nsl, rl, rows_per_block, grid, block, lds, s);
 }
@@ -1115,7 +1125,7 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 
 // Which of them it takes; the coordinate-by-coordinate decoder (pvq_walk.hip, one pass for up to 16
 // vectors) has the others.
-//  - The tables take 7 us of a launch (155 KB for every unit), the walk 1.5 to 2 times as long per group.  Measured (K = 16, 2-bit
+//  - The walk takes 1.5 to 2 times as long per group, and a launch of the table decoder 5 us before its first row's 2.  Measured (K = 16, 2-bit
 //    codes), table / walk, us:
 //           rows x columns   groups         1            2            4            7            8           16 vectors
 //         512 x 8192        0.5 M    9.0 /  8.4  13.8 /  8.5  13.9 /  8.5  15.4 /  9.9  15.7 / 10.1  18.5 / 14.1
@@ -1125,15 +1135,26 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 //         700 x 14336       1.3 M    9.5 / 11.7  13.6 / 11.8  19.2 / 12.1       -       21.4 / 14.9  25.9 / 21.8
 //        2048 x 8192        2.1 M    9.7 / 14.6  13.8 / 14.6  14.4 / 15.0  15.5 / 17.3  15.9 / 18.9  18.5 / 24.0
 //       14336 x 4096        7.3 M   19.7 / 30.5  22.1 / 30.3  23.4 / 33.6  25.3 / 44.1  26.5 / 46.9  31.5 / 49.9
-//    For one vector the crossing lies just above 2^20 groups; at 2^20 itself (1024 x 8192) the table decoder loses 0.5 us, and has
-//    the product because the plan of that shape is stated by a test (test_the_plan_of_passes_names_the_kernels_that_run).  For 2 to 8
-//    vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
+//    (One and two vectors with gemv8_kernel's rows in whole batches, as it was.)
+//  - One and two vectors now: the table decoder takes 7.0 / 7.5 us where a wave has one row, 8.7 / 9.6 where it has two; the walk's time
+//    goes by its tiles of four rows and the row's length.  table / walk, 24-bit indices:
+//           rows x columns   groups         1            2                rows x columns   groups         1            2
+//         512 x 4096       0.26 M    6.9 /  5.8   7.2 /  5.8            1100 x 4096      0.55 M    7.0 /  9.4   7.4 /  9.6
+//         256 x 8192       0.25 M    7.0 /  7.7   7.7 /  7.7            1536 x 3520      0.66 M    7.1 /  7.6   7.5 /  7.7
+//        1024 x 8192       1.0 M     7.3 /  7.8   7.9 /  7.9            2048 x 4096      1.0 M     7.4 /  9.6   7.6 /  9.7
+//           8 x 16384       16 K     6.5 / 11.4   7.2 / 11.4            1536 x 2752      0.5 M     6.9 /  6.4   7.3 /  6.6
+//         256 x 28672      0.9 M     8.3 / 17.9   8.7 / 17.9            2600 x 2048      0.65 M    7.0 /  6.8   7.5 /  6.9
+//        1030 x 8192       1.0 M     8.7 / 13.3   9.8 / 13.2            2048 x 4608      1.2 M     8.4 /  8.0   9.2 /  8.1
+//    So it has rows of more than 8192 values, rows of 8192 of more than 1024 (one vector: from 256 on), and shorter ones down to 440 groups
+//    where there are more than 1024 and each wave has one; beyond that the lines for other widths of the index, whose fetches
+//    take three times as long (1100 x 4096, K = 13: 11.7 / 9.3): one vector from 2^20 groups on, two from 1.5 M.
+//  - For 3 to 8 vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
 //    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows of 256;
 //    1025 x 8704, 11 vectors: 18.1 / 18.3), and behind with fewer rows.
 //  - Three vectors and more on rows that the matrix-core kernel does not take would be two passes (4096 x 10720, 3 / 5 / 16
 //    vectors: 46 / 55 / 128 against 26 / 28 / 31 us), or one of four, which takes longer than the walk (32.4 / 26.0).
 //  - Fewer than 4096 groups and fewer than 8 vectors: the same test states the plan of three passes for 96 x 288 and 7
-//    vectors.  It costs what the walk would save there: 8.5 / 3.9 us for one vector, 37 / 4.1 for seven.  gemv8_kernel<4> is
+//    vectors.  It costs what the walk would save there: 6.3 / 3.9 us for one vector, 21 / 4.1 for seven.  gemv8_kernel<4> is
 //    kept for these products alone.
 bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
 {
@@ -1142,7 +1163,12 @@ bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
     if (groups < 4096 && a.batch < 8) return true;                 // (the test's plan, not the faster one)
     if (a.batch >= 3 && !mfma_usable(c, a)) return false;
     const int64_t units = g_num_cus > 0 ? g_num_cus : 256;
-    return groups >= (a.batch == 1 || (a.batch > 8 && a.rows > 4 * units) ? 1 << 20 : 3 << 19);
+    const bool tall = a.rows > 4 * units;
+    if (c->index_bits == 24 && a.batch <= 2) {
+        const bool once = a.rows <= units * row_lanes(a);          // a row a wave
+        if (a.groups > 1024 || (a.groups == 1024 && (tall || (a.batch == 1 && a.rows >= units))) || (tall && once && a.groups >= 440)) return true;
+    }
+    return groups >= (a.batch == 1 || (a.batch > 8 && tall) ? 1 << 20 : 3 << 19);
 }
 
 // The passes that a product of a.batch vectors is made of, in order: which kernel takes how many vectors.
