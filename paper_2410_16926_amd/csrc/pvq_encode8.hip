@@ -378,12 +378,8 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
     }
 }
 
-// Registers for eight waves a SIMD (64 a lane): with them two workgroups of 1024 lanes, which blocks of 8192 values need, share
-// a unit.  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096 / 8192: 61 / 76 / 79 / 99 us, calls in a row (with two barriers
-// an exchange, selections in the stages across lanes and divisions for the codes 65 / 80 / 83 / 106).  With float32 amplitudes blocks of 8192 take 72:
-// a row's end costs 27, since its sum, its codes and the next row's first values follow one another while the only other workgroup of
-// the unit is as often at a barrier.  Tried for it: the next values requested before the row's sum (registers in scratch memory, 111), codes
-// behind the next row's first barrier (100), by four waves in turn (100).
+// Registers for eight waves a SIMD (64 a lane).  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096: 61 / 76 / 79 us, calls in a
+// row (with two barriers an exchange, selections in the stages across lanes and divisions for the codes 65 / 80 / 83).
 template <typename TIn, int CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)
@@ -391,11 +387,157 @@ __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, p
     rotate_encode8_body<TIn, CODES, LS, LOG2N>(f, a, log2n, signs, scale);
 }
 
-template <typename TIn, int CODES, bool LS>
+// (float32 rows of several blocks: the others have the kernel below)
+template <int CODES, bool LS>
 __global__ __launch_bounds__(1024, 8) void rotate_encode8_kernel_8192(enc8_launch f, pvq_encode_args a, int log2n,
                                                                       const uint8_t *signs, float scale)
 {
-    rotate_encode8_body<TIn, CODES, LS, 13>(f, a, log2n, signs, scale);
+    rotate_encode8_body<float, CODES, LS, 13>(f, a, log2n, signs, scale);
+}
+
+// The same with sixteen values a lane, for blocks of 1024, 2048 and 8192 in rows of whole chunks of 8192 values: 512 lanes take a chunk, two
+// runs of 8 values each.  A wave then holds 1024 values in a row, ten stages stay inside it, and the last one to three are one
+// ownership: two trips through LDS where eight values a lane need three for blocks of 8192, and none of them between waves for blocks
+// of 1024.  The last one ends in the wave's own 1024 values, which are 128 groups that it takes in two halves, from LDS.
+// What bounded blocks of 8192 were the barriers: the tables and the values leave room for two workgroups of 1024 lanes on a unit, so that
+// either waits for the other, and a row's end (its sum, its codes, the next row's first values) cost 27 of 99 us.  Now there are three
+// workgroups, one barrier fewer a chunk, and 80 registers a lane (six waves a SIMD), in which the next values are on their way while
+// groups are encoded.  8192 x 8192 bf16: 2-bit codes 98.6 -> 80.4 us, float32 amplitudes 81.1 -> 70.8.
+// CODED: 0 for float32 amplitudes, else the chunks that a row may have.  Their sums of squares stay in registers until the row's end and
+// then take the place of values that the wave has read (with LDS of their own a third workgroup would not fit).
+constexpr int kHalfBlockLanes = 512;
+constexpr int kWaveWords = 1024 + 1024 / 32;                         // of the exchange buffer, padded
+template <typename TIn, int CODED, bool LS, int LOG2N>
+__global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kernel(enc8_launch f, pvq_encode_args a, const uint8_t *signs, float scale)
+{
+    using namespace pvq_hadamard_dev;
+    extern __shared__ __align__(16) uint32_t smem[];
+    const float K = (float)f.K;
+    const enc8_lds l = fill_lds<CODED>(smem, f, kHalfBlockLanes);
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int G = (int)a.groups, chunks = CODED == 1 ? 1 : G / 1024;
+    const TIn *W = reinterpret_cast<const TIn *>(a.W);
+
+    float *const own = l.ss_row + kWaveWords * wave;                 // the wave's values
+    float *const across = l.ss_row + pad((uint32_t)tid);             // values 1024 apart, for the last three stages
+    const float *const group = own + pad((uint32_t)(D * lane));
+
+    raw8<TIn> raw[2];
+    uint2 s8[2];
+    constexpr bool kSignsAhead = sizeof(TIn) == 2 || CODED < 4;      // (else they have no registers)
+    auto request_signs = [&](int ch) {
+        if (!signs) return;
+        const uint32_t from = (uint32_t)(1024 * wave + D * load_lane<13>(anew(lane)));
+#pragma unroll
+        for (int h = 0; h < 2; h++) s8[h] = *reinterpret_cast<const uint2 *>(signs + (int64_t)ch * 8192 + 512 * h + from);
+    };
+    auto request = [&](int64_t row, int ch) {
+        const uint32_t from = (uint32_t)(1024 * wave + D * load_lane<13>(anew(lane)));
+#pragma unroll
+        for (int h = 0; h < 2; h++) raw[h].load(W + row * a.ldw + (int64_t)ch * 8192 + 512 * h + from);
+        if constexpr (kSignsAhead) request_signs(ch);
+    };
+    request(blockIdx.x, 0);
+    __syncthreads();
+    float *wsum = l.wsum;
+    float kept[CODED ? CODED : 1][2] = {};                                // sums of squares of the row's blocks
+    for (int64_t row = blockIdx.x; row < a.rows; row += gridDim.x) {
+        uint32_t *irow = a.index_out + row * a.index_row_words;
+        for (int ch = 0; ch < chunks; ch++) {
+            float v[2][D];
+            const int at_lane = anew(lane), place = load_lane<13>(at_lane);
+            if constexpr (!kSignsAhead) request_signs(ch);
+#pragma unroll
+            for (int h = 0; h < 2; h++) {
+                if (signs) raw[h].flip(sign_bits(s8[h]));
+                raw[h].get(v[h]);
+                stages_in_registers(v[h], 3);
+                stage_across_lanes<1>(v[h], place);
+                stage_across_lanes<2>(v[h], place);
+                stage_across_lanes<4, false, true>(v[h], place);
+                stage_across_lanes<8>(v[h], place);
+                stage_across_rows<16, 4, true>(v[h]);
+                stage_across_rows<32, 2, true>(v[h]);
+            }
+            __builtin_amdgcn_wave_barrier();                         // (the wave has read what lay here)
+            // (roles of register and lane bits as exchange_from_rows has them)
+            float *const put = own + pad((uint32_t)((at_lane >> 4 & 2) | (at_lane >> 2 & 4) | (place & 15) << 3));
+#pragma unroll
+            for (int q = 0; q < D; q++) {
+                const float x = v[0][q], y = v[1][q];
+                const uint32_t at = pad((uint32_t)((q & 1) | (q & 4) << 5 | (q & 2) << 7));
+                put[at] = x + y;
+                put[at + pad(512)] = x - y;
+            }
+            if constexpr (LOG2N > 10) {
+                __syncthreads();
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+#pragma unroll
+                    for (int q = 0; q < D; q++) v[h][q] = across[pad(512) * h + kWaveWords * q];
+                }
+#pragma unroll
+                for (int h = 0; h < 2; h++) {
+                    stages_in_registers(v[h], LOG2N - 10);
+#pragma unroll
+                    for (int q = 0; q < D; q++) across[pad(512) * h + kWaveWords * q] = v[h][q];
+                }
+                __syncthreads();
+            } else {
+                __builtin_amdgcn_wave_barrier();
+            }
+            // the block behind, or the next row's first (of the last row once more)
+            const bool more = ch + 1 < chunks;
+            request(more ? row : min(row + (int64_t)gridDim.x, a.rows - 1), more ? ch + 1 : 0);
+            float ss_first = 0.0f, ss = 0.0f;
+#pragma unroll 1
+            for (int h = 0; h < 2; h++) {
+                const int run = 16 * ch + 2 * wave + h, g = run * kWave + lane;
+                float w[D], y[D];
+#pragma unroll
+                for (int j = 0; j < D; j++) w[j] = group[pad(512) * h + j] * scale;
+                bool ordinary, degenerate;
+                ss_first = ss;
+                const uint32_t c = encode_group8<LS>(w, K, l.table, ss, ordinary, degenerate, y);
+                float amp;
+                if constexpr (LS) { amp = ls_amplitude8(w, y, ordinary, degenerate); ss = amp * amp; }
+                else amp = root_of_squares(ss, ordinary);
+                if constexpr (!CODED) reinterpret_cast<float *>(a.scale_out)[row * G + g] = amp;
+                const uint32_t word = index_word(c, lane & 3);
+                if ((lane & 3) < 3) irow[3 * (g >> 2) + (lane & 3)] = word;
+                if constexpr (CODED) {
+                    const float s64 = wave_pair_sum(ss);
+                    if (lane == kWave - 1) wsum[run] = s64;
+                }
+            }
+            if constexpr (CODED) {
+#pragma unroll
+                for (int b = 0; b < CODED; b++) {
+                    kept[b][0] = CODED == 1 || b == ch ? ss_first : kept[b][0];
+                    kept[b][1] = CODED == 1 || b == ch ? ss : kept[b][1];
+                }
+            }
+        }
+        if constexpr (CODED) {
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int b = 0; b < CODED; b++) {
+                own[2 * kWave * b + lane] = kept[b][0];
+                own[2 * kWave * b + kWave + lane] = kept[b][1];
+            }
+            __syncthreads();
+            const float rowss = row_sum(wsum, anew(lane));
+            if (anew(tid) == 0) a.rownorm_out[row] = rowss;
+#pragma unroll 1
+            for (int ch = 0; ch < chunks; ch++) {
+                const int run = 16 * ch + 2 * wave;                  // two runs of 64 groups
+                write_codes<2>(f.scale_bits, own + 2 * kWave * ch - kWave * run, rowss, l.tree,
+                               reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, kWave * (run + 2), run, 1, anew(lane));
+            }
+            wsum = wsum == l.wsum ? l.wsum + 64 : l.wsum;
+        }
+    }
 }
 
 }  // namespace
@@ -428,8 +570,41 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     const int L = rotate8_lanes(block);
     const bool codes = c->scale_bits > 0, ls = a.ls_amplitude != 0;
     const float scale = (float)(1.0 / std::sqrt((double)block));
+    // Sixteen values a lane (us, eight / sixteen, 2-bit codes, bf16 unless said):
+    //  - blocks of 8192: 64 x 8192 6.7 / 6.0, 1024 x 8192 15.0 / 11.9, 8192 x 8192 98.6 / 80.4, float32 106.9 / 87.8; 3000 x 24576 102.5 / 89.6.
+    //    Not float32 rows of several blocks with codes while every workgroup has one: their signs are not on their way early
+    //    (768 x 16384 19.4 / 20.4, 1024 x 16384 26.5 / 24.4);
+    //  - blocks of 1024, which then need no barrier: 64 x 8192 9.1 / 6.1, 8192 x 8192 83.2 / 74.1, 3000 x 16384 67.8 / 58.0;
+    //  - blocks of 2048: 64 x 8192 9.2 / 6.1, 8192 x 8192 84.4 / 79.8, 3000 x 16384 67.7 / 61.2, 1536 x 16384 float32 34.9 / 35.6;
+    //  - not blocks of 4096, of which four workgroups of eight values a lane fit a unit: 8192 x 8192 80.6 / 79.8, 1536 x 16384 float32 33.8 / 36.0.
+    const bool few = a.rows <= 768;
+    const bool halves = a.groups % 1024 == 0 && (log2n == 13 ? !(dtype == PVQ_F32 && codes && a.groups > 1024 && few) : log2n == 10 || log2n == 11);
     const size_t hbuf = log2n > 9 ? (size_t)(8 * L + 8 * L / 32 + 1) : 0;
     const size_t lds = (kHeadWords + (codes ? (size_t)((a.groups + 3) & ~3) : 0) + hbuf) * 4;
+    if (halves) {
+        const size_t lds_halves = (kHeadWords + 8 * kWaveWords) * 4;
+        const unsigned places = resident_grid(a.rows, kHalfBlockLanes, lds_halves);
+#define PVQ_RE8_HALVES_N(T, C, LS_, N) \
+    hipLaunchKernelGGL((rotate_encode8_halves_kernel<T, C, LS_, N>), dim3(places), dim3(kHalfBlockLanes), lds_halves, s, f, a, signs, scale)
+#define PVQ_RE8_HALVES(T, C, LS_)                                                   \
+    switch (log2n) {                                                                \
+    case 13: PVQ_RE8_HALVES_N(T, C, LS_, 13); break;                                \
+    case 11: PVQ_RE8_HALVES_N(T, C, LS_, 11); break;                                \
+    default: PVQ_RE8_HALVES_N(T, C, LS_, 10); break;                                \
+    }
+#define PVQ_RE8_HALVES_C(T, LS_)                                                    \
+    do {                                                                            \
+        if (!codes) PVQ_RE8_HALVES(T, 0, LS_)                                       \
+        else if (a.groups == 1024) PVQ_RE8_HALVES(T, 1, LS_)                        \
+        else PVQ_RE8_HALVES(T, 4, LS_)                                              \
+    } while (0)
+        if (dtype == PVQ_F32) { if (ls) PVQ_RE8_HALVES_C(float, true); else PVQ_RE8_HALVES_C(float, false); }
+        else { if (ls) PVQ_RE8_HALVES_C(uint16_t, true); else PVQ_RE8_HALVES_C(uint16_t, false); }
+#undef PVQ_RE8_HALVES_C
+#undef PVQ_RE8_HALVES
+#undef PVQ_RE8_HALVES_N
+        return hipGetLastError();
+    }
     const unsigned grid = resident_grid(a.rows, L, lds);
 #define PVQ_RE8_LAUNCH(KERNEL)                                                                                   \
     do {                                                                                                        \
@@ -442,11 +617,16 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     } while (0)
 #define PVQ_RE8_N(T, C, LS_)                                                        \
     switch (log2n) {                                                                \
-    case 13: PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<T, C, LS_>)); break;        \
     case 12: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 12>)); break;         \
     case 11: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 11>)); break;         \
     case 10: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 10>)); break;         \
     default: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 9>)); break;          \
+    }
+    if (log2n == 13) {
+        if (a.groups == 2 * L) { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<2, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<2, false>)); }
+        else if (a.groups == 3 * L) { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<1, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<1, false>)); }
+        else { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<4, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<4, false>)); }
+        return hipGetLastError();
     }
     // (a wave has as many runs of 64 groups as a row has chunks; 11754 x 16384 in blocks of 8192: 301 us with four groups a lane, half the
     // waves without a code to write)

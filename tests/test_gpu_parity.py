@@ -571,6 +571,40 @@ def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
     ctx.close()
 
 
+@pytest.mark.parametrize("rows,cols,block,bits,bf16,amplitude",
+                         [(1, 8192, 8192, 4, False, "l2"), (769, 8192, 8192, 1, True, "ls"), (1600, 8192, 8192, 8, False, "ls"),
+                          (5, 8192, 1024, 2, False, "l2"), (770, 8192, 1024, 0, True, "l2"), (6, 8192, 2048, 8, True, "ls"),
+                          (3, 16384, 8192, 2, True, "l2"), (768, 16384, 8192, 4, False, "l2"), (769, 16384, 8192, 4, False, "ls"),
+                          (780, 24576, 8192, 2, False, "l2"), (2, 24576, 8192, 0, False, "ls"), (3, 32768, 8192, 8, True, "l2"),
+                          (4, 32768, 1024, 1, False, "l2"), (3, 24576, 2048, 4, True, "l2"), (3, 24576, 8192, 2, False, "ls"),
+                          (2, 32768, 8192, 8, False, "l2")])
+def test_rotation_and_encoding_with_sixteen_values_a_lane(rows, cols, block, bits, bf16, amplitude):
+    # one to four chunks of 8192 values a row, every width of a code, a workgroup with one row and with two or three, strided rows,
+    # zeros among them (groups without a direction, amplitudes of zero): the bits of rotation and encoding in two calls, and the
+    # oracle's for a row of each kind
+    D, K = 8, 16
+    rng = np.random.default_rng(rows + cols + block + bits)
+    W = torch.zeros((rows, cols + 64), dtype=torch.bfloat16 if bf16 else torch.float32, device="cuda")
+    X = W[:, :cols]
+    X.copy_(torch.from_numpy(rng.standard_normal((rows, cols)).astype(np.float32) * 0.02))
+    X[0, :block] = 0.0
+    sg = rng.integers(0, 2, size=cols).astype(np.uint8)
+    sgd = torch.from_numpy(sg).cuda()
+    ctx, oe, oc = gu.make_ctx(D, K, bits, cols // D)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    for given in (sgd, None):
+        packed = pvq.pvq_rotate_encode(ctx, X, block, given)
+        two = pvq.pvq_encode(ctx, pvq.pvq_hadamard(X, block, given, out_dtype=torch.float32))
+        assert torch.equal(two.index, packed.index) and torch.equal(two.scale, packed.scale)
+        if bits:
+            assert torch.equal(two.rownorm, packed.rownorm)
+    some = [0, rows - 1]
+    packed = pvq.pvq_rotate_encode(ctx, X[some].contiguous(), block, sgd)
+    rotated = oracle.hadamard_rows(X[some].float().cpu().numpy(), block, sg)
+    gu.assert_encode_equal(packed, oracle.encode(rotated, D, K, bits, oe, nthreads=8, amplitude=amplitude), check_pulses=False)
+    ctx.close()
+
+
 def test_rotation_and_encoding_for_groups_of_8_limits():
     X = torch.zeros((2, 1024), dtype=torch.float32, device="cuda")
     ctx = pvq.pvq_ctx_create(8, 16)

@@ -119,3 +119,7 @@ def test_encoders_of_groups_of_eight_keep_their_values_in_registers(tmp_path):
     kernels = re.findall(r"\.name:\s*(\S*encode8_kernel\S*).*?\.vgpr_count:\s*(\d+).*?\.vgpr_spill_count:\s*(\d+)", notes, re.S)
     assert len(kernels) > 50
     assert [name for name, registers, spilled in kernels if int(registers) > 64 or int(spilled) > 0] == []
+    # 80 for the six waves that three workgroups of 512 lanes make
+    halves = re.findall(r"\.name:\s*(\S*encode8_halves_kernel\S*).*?\.vgpr_count:\s*(\d+).*?\.vgpr_spill_count:\s*(\d+)", notes, re.S)
+    assert len(halves) > 30
+    assert [name for name, registers, spilled in halves if int(registers) > 80 or int(spilled) > 0] == []
