@@ -395,14 +395,16 @@ __global__ __launch_bounds__(1024, 8) void rotate_encode8_kernel_8192(enc8_launc
     rotate_encode8_body<float, CODES, LS, 13>(f, a, log2n, signs, scale);
 }
 
-// The same with sixteen values a lane, for blocks of 1024, 2048 and 8192 in rows of whole chunks of 8192 values: 512 lanes take a chunk, two
-// runs of 8 values each.  A wave then holds 1024 values in a row, ten stages stay inside it, and the last one to three are one
-// ownership: two trips through LDS where eight values a lane need three for blocks of 8192, and none of them between waves for blocks
-// of 1024.  The last one ends in the wave's own 1024 values, which are 128 groups that it takes in two halves, from LDS.
+// The same with sixteen values a lane, for blocks of 64 to 2048 and 8192: a wave holds 1024 values in a row, in two runs of 8 a lane, ten
+// stages stay inside it, and what is left for larger blocks is one ownership: two trips through LDS where eight values a lane
+// need three for blocks of 8192, and no barriers between waves for blocks of up to 1024.  The last trip ends in the wave's own 1024 values,
+// which are 128 groups that it takes in two halves, from LDS.  A chunk is what the workgroup's waves hold (eight of them for blocks of more
+// than 1024).
 // What bounded blocks of 8192 were the barriers: the tables and the values leave room for two workgroups of 1024 lanes on a unit, so that
 // either waits for the other, and a row's end (its sum, its codes, the next row's first values) cost 27 of 99 us.  Now there are three
 // workgroups, one barrier fewer a chunk, and 80 registers a lane (six waves a SIMD), in which the next values are on their way while
-// groups are encoded.  8192 x 8192 bf16: 2-bit codes 98.6 -> 80.4 us, float32 amplitudes 81.1 -> 70.8.
+// groups are encoded.  8192 x 8192 bf16: 2-bit codes 98.6 -> 80.4 us, float32 amplitudes 81.1 -> 70.8.  With few rows it is the
+// chunks of a row that a workgroup takes one after the other, of 256 groups before and of up to 1024 now, and their memory's latency.
 // CODED: 0 for float32 amplitudes, else the chunks that a row may have.  Their sums of squares stay in registers until the row's end and
 // then take the place of values that the wave has read (with LDS of their own a third workgroup would not fit).
 constexpr int kHalfBlockLanes = 512;
@@ -413,10 +415,11 @@ __global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kern
     using namespace pvq_hadamard_dev;
     extern __shared__ __align__(16) uint32_t smem[];
     const float K = (float)f.K;
-    const enc8_lds l = fill_lds<CODED>(smem, f, kHalfBlockLanes);
+    const int waves = LOG2N > 10 ? kHalfBlockLanes / kWave : blockDim.x / kWave;
+    const enc8_lds l = fill_lds<CODED>(smem, f, waves * kWave);
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int G = (int)a.groups, chunks = CODED == 1 ? 1 : G / 1024;
+    const int G = (int)a.groups, chunks = CODED == 1 ? 1 : G / (2 * kWave * waves);
     const TIn *W = reinterpret_cast<const TIn *>(a.W);
 
     float *const own = l.ss_row + kWaveWords * wave;                 // the wave's values
@@ -430,12 +433,12 @@ __global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kern
         if (!signs) return;
         const uint32_t from = (uint32_t)(1024 * wave + D * load_lane<13>(anew(lane)));
 #pragma unroll
-        for (int h = 0; h < 2; h++) s8[h] = *reinterpret_cast<const uint2 *>(signs + (int64_t)ch * 8192 + 512 * h + from);
+        for (int h = 0; h < 2; h++) s8[h] = *reinterpret_cast<const uint2 *>(signs + (int64_t)ch * (1024 * waves) + 512 * h + from);
     };
     auto request = [&](int64_t row, int ch) {
         const uint32_t from = (uint32_t)(1024 * wave + D * load_lane<13>(anew(lane)));
 #pragma unroll
-        for (int h = 0; h < 2; h++) raw[h].load(W + row * a.ldw + (int64_t)ch * 8192 + 512 * h + from);
+        for (int h = 0; h < 2; h++) raw[h].load(W + row * a.ldw + (int64_t)ch * (1024 * waves) + 512 * h + from);
         if constexpr (kSignsAhead) request_signs(ch);
     };
     request(blockIdx.x, 0);
@@ -456,19 +459,20 @@ __global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kern
                 stage_across_lanes<1>(v[h], place);
                 stage_across_lanes<2>(v[h], place);
                 stage_across_lanes<4, false, true>(v[h], place);
-                stage_across_lanes<8>(v[h], place);
-                stage_across_rows<16, 4, true>(v[h]);
-                stage_across_rows<32, 2, true>(v[h]);
+                if constexpr (LOG2N > 6) stage_across_lanes<8>(v[h], place);
+                if constexpr (LOG2N > 7) stage_across_rows<16, 4, true>(v[h]);
+                if constexpr (LOG2N > 8) stage_across_rows<32, 2, true>(v[h]);
             }
             __builtin_amdgcn_wave_barrier();                         // (the wave has read what lay here)
             // (roles of register and lane bits as exchange_from_rows has them)
-            float *const put = own + pad((uint32_t)((at_lane >> 4 & 2) | (at_lane >> 2 & 4) | (place & 15) << 3));
+            constexpr bool k16 = LOG2N > 7, k32 = LOG2N > 8;
+            float *const put = own + pad((uint32_t)((k32 ? at_lane >> 4 & 2 : at_lane << 3 & 256) | (k16 ? at_lane >> 2 & 4 : at_lane << 3 & 128) | (place & 15) << 3));
 #pragma unroll
             for (int q = 0; q < D; q++) {
                 const float x = v[0][q], y = v[1][q];
-                const uint32_t at = pad((uint32_t)((q & 1) | (q & 4) << 5 | (q & 2) << 7));
-                put[at] = x + y;
-                put[at + pad(512)] = x - y;
+                const uint32_t at = pad((uint32_t)((q & 1) | (q & 4) << (k16 ? 5 : 0) | (q & 2) << (k32 ? 7 : 0)));
+                put[at] = LOG2N > 9 ? x + y : x;
+                put[at + pad(512)] = LOG2N > 9 ? x - y : y;
             }
             if constexpr (LOG2N > 10) {
                 __syncthreads();
@@ -493,7 +497,7 @@ __global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kern
             float ss_first = 0.0f, ss = 0.0f;
 #pragma unroll 1
             for (int h = 0; h < 2; h++) {
-                const int run = 16 * ch + 2 * wave + h, g = run * kWave + lane;
+                const int run = 2 * (waves * ch + wave) + h, g = run * kWave + lane;
                 float w[D], y[D];
 #pragma unroll
                 for (int j = 0; j < D; j++) w[j] = group[pad(512) * h + j] * scale;
@@ -531,7 +535,7 @@ __global__ __launch_bounds__(kHalfBlockLanes, 6) void rotate_encode8_halves_kern
             if (anew(tid) == 0) a.rownorm_out[row] = rowss;
 #pragma unroll 1
             for (int ch = 0; ch < chunks; ch++) {
-                const int run = 16 * ch + 2 * wave;                  // two runs of 64 groups
+                const int run = 2 * (waves * ch + wave);                  // two runs of 64 groups
                 write_codes<2>(f.scale_bits, own + 2 * kWave * ch - kWave * run, rowss, l.tree,
                                reinterpret_cast<uint32_t *>(a.scale_out) + row * a.scale_row_words, kWave * (run + 2), run, 1, anew(lane));
             }
@@ -570,32 +574,51 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     const int L = rotate8_lanes(block);
     const bool codes = c->scale_bits > 0, ls = a.ls_amplitude != 0;
     const float scale = (float)(1.0 / std::sqrt((double)block));
-    // Sixteen values a lane (us, eight / sixteen, 2-bit codes, bf16 unless said):
-    //  - blocks of 8192: 64 x 8192 6.7 / 6.0, 1024 x 8192 15.0 / 11.9, 8192 x 8192 98.6 / 80.4, float32 106.9 / 87.8; 3000 x 24576 102.5 / 89.6.
-    //    Not float32 rows of several blocks with codes while every workgroup has one: their signs are not on their way early
-    //    (768 x 16384 19.4 / 20.4, 1024 x 16384 26.5 / 24.4);
-    //  - blocks of 1024, which then need no barrier: 64 x 8192 9.1 / 6.1, 8192 x 8192 83.2 / 74.1, 3000 x 16384 67.8 / 58.0;
-    //  - blocks of 2048: 64 x 8192 9.2 / 6.1, 8192 x 8192 84.4 / 79.8, 3000 x 16384 67.7 / 61.2, 1536 x 16384 float32 34.9 / 35.6;
-    //  - not blocks of 4096, of which four workgroups of eight values a lane fit a unit: 8192 x 8192 80.6 / 79.8, 1536 x 16384 float32 33.8 / 36.0.
-    const bool few = a.rows <= 768;
-    const bool halves = a.groups % 1024 == 0 && (log2n == 13 ? !(dtype == PVQ_F32 && codes && a.groups > 1024 && few) : log2n == 10 || log2n == 11);
+    // Sixteen values a lane (us, eight / sixteen, bf16 and 2-bit codes unless said).  A workgroup has as many waves, up to eight, as
+    // divide the row's 1024s.
+    //  - Where no workgroup has more than a row or two, for all blocks but of 4096: 64 x 8192 in blocks of 64 8.4 / 6.3, 64 x 28672 20.5 / 13.1,
+    //    700 x 4096 in blocks of 256 8.0 / 7.0, 700 x 14336 float32 in blocks of 64 17.6 / 17.2, 768 x 16384 in blocks of 1024 21.1 / 17.4.
+    //    (One or two waves, and rows of more than four chunks with codes, have the others.)  Not float32 rows of several blocks of 8192 with codes, whose
+    //    signs are not on their way early: 768 x 16384 19.4 / 20.4, 1024 x 16384 26.5 / 24.4.
+    //  - With more rows in whole chunks of 8192 values, of which three workgroups fit a unit (fewer waves: 4000 x 6144 in blocks of 64 28.6 / 33.2):
+    //    blocks of 8192: 1024 x 8192 15.0 / 11.9, 8192 x 8192 98.6 / 80.4, float32 106.9 / 87.8; 3000 x 24576 102.5 / 89.6;
+    //    blocks of 2048: 8192 x 8192 84.4 / 79.8, 3000 x 16384 67.7 / 61.2; of 1024: 83.2 / 74.1, 67.8 / 58.0; of 512: 79.4 / 74.1, 62.1 / 57.4;
+    //    blocks of 256 and 128, only in rows of one chunk: 8192 x 8192 73.3 / 70.8, 69.6 / 69.0 (4000 x 16384 70.6 / 71.9, 66.1 / 68.6);
+    //    blocks of 64, the same: 8192 x 8192 65.7 / 65.4, float32 76.5 / 73.6, 2048 x 8192 19.7 / 18.7 but float32 20.2 / 20.6.
+    //  - Not blocks of 4096, of which four workgroups of eight values a lane fit a unit: 8192 x 8192 80.6 / 79.8, 1536 x 16384 float32 33.8 / 36.0.
+    const int units = (int)(a.groups / 128);                         // of 1024 values, a wave's
+    int waves = 8;
+    while (log2n <= 10 && waves > 1 && units % waves != 0) waves--;
+    const bool few = a.rows <= 768, whole = a.groups % 1024 == 0, one = a.groups == 1024;
+    bool halves = false;
+    if (a.groups % 128 == 0 && waves > 2 && (!codes || units <= 4 * waves)) {
+        if (log2n == 13) halves = !(dtype == PVQ_F32 && codes && !one && few);
+        else if (log2n == 11) halves = whole;
+        else if (log2n == 9 || log2n == 10) halves = few || whole;
+        else if (log2n == 7 || log2n == 8) halves = few || one;
+        else if (log2n == 6) halves = few || (one && (dtype != PVQ_F32 || a.rows > 4096));
+    }
     const size_t hbuf = log2n > 9 ? (size_t)(8 * L + 8 * L / 32 + 1) : 0;
     const size_t lds = (kHeadWords + (codes ? (size_t)((a.groups + 3) & ~3) : 0) + hbuf) * 4;
     if (halves) {
-        const size_t lds_halves = (kHeadWords + 8 * kWaveWords) * 4;
-        const unsigned places = resident_grid(a.rows, kHalfBlockLanes, lds_halves);
+        const size_t lds_halves = (kHeadWords + waves * kWaveWords) * 4;
+        const unsigned places = resident_grid(a.rows, waves * kWave, lds_halves);
 #define PVQ_RE8_HALVES_N(T, C, LS_, N) \
-    hipLaunchKernelGGL((rotate_encode8_halves_kernel<T, C, LS_, N>), dim3(places), dim3(kHalfBlockLanes), lds_halves, s, f, a, signs, scale)
+    hipLaunchKernelGGL((rotate_encode8_halves_kernel<T, C, LS_, N>), dim3(places), dim3(waves * kWave), lds_halves, s, f, a, signs, scale)
 #define PVQ_RE8_HALVES(T, C, LS_)                                                   \
     switch (log2n) {                                                                \
     case 13: PVQ_RE8_HALVES_N(T, C, LS_, 13); break;                                \
     case 11: PVQ_RE8_HALVES_N(T, C, LS_, 11); break;                                \
-    default: PVQ_RE8_HALVES_N(T, C, LS_, 10); break;                                \
+    case 10: PVQ_RE8_HALVES_N(T, C, LS_, 10); break;                                \
+    case 9: PVQ_RE8_HALVES_N(T, C, LS_, 9); break;                                  \
+    case 8: PVQ_RE8_HALVES_N(T, C, LS_, 8); break;                                  \
+    case 7: PVQ_RE8_HALVES_N(T, C, LS_, 7); break;                                  \
+    default: PVQ_RE8_HALVES_N(T, C, LS_, 6); break;                                 \
     }
 #define PVQ_RE8_HALVES_C(T, LS_)                                                    \
     do {                                                                            \
         if (!codes) PVQ_RE8_HALVES(T, 0, LS_)                                       \
-        else if (a.groups == 1024) PVQ_RE8_HALVES(T, 1, LS_)                        \
+        else if (units == waves) PVQ_RE8_HALVES(T, 1, LS_)                          \
         else PVQ_RE8_HALVES(T, 4, LS_)                                              \
     } while (0)
         if (dtype == PVQ_F32) { if (ls) PVQ_RE8_HALVES_C(float, true); else PVQ_RE8_HALVES_C(float, false); }

@@ -577,9 +577,16 @@ def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
                           (3, 16384, 8192, 2, True, "l2"), (768, 16384, 8192, 4, False, "l2"), (769, 16384, 8192, 4, False, "ls"),
                           (780, 24576, 8192, 2, False, "l2"), (2, 24576, 8192, 0, False, "ls"), (3, 32768, 8192, 8, True, "l2"),
                           (4, 32768, 1024, 1, False, "l2"), (3, 24576, 2048, 4, True, "l2"), (3, 24576, 8192, 2, False, "ls"),
-                          (2, 32768, 8192, 8, False, "l2")])
+                          (2, 32768, 8192, 8, False, "l2"),
+                          (3, 4096, 64, 2, True, "l2"), (1100, 8192, 64, 2, True, "l2"), (4200, 8192, 64, 0, False, "l2"), (2, 28672, 64, 8, False, "ls"),
+                          (5, 14336, 128, 1, True, "l2"), (768, 6144, 128, 4, False, "l2"), (780, 8192, 128, 2, False, "ls"),
+                          (3, 10240, 256, 0, True, "ls"), (770, 8192, 256, 8, True, "l2"), (2, 32768, 256, 2, False, "l2"),
+                          (767, 4096, 512, 2, False, "l2"), (780, 16384, 512, 1, True, "ls"), (3, 22528, 512, 2, True, "l2"),
+                          (4, 14336, 1024, 2, True, "l2"), (3, 20480, 1024, 4, False, "l2"), (769, 6144, 1024, 2, True, "l2"),
+                          (2, 30720, 1024, 0, True, "l2"), (3, 2048, 256, 2, True, "l2")])
 def test_rotation_and_encoding_with_sixteen_values_a_lane(rows, cols, block, bits, bf16, amplitude):
-    # one to four chunks of 8192 values a row, every width of a code, a workgroup with one row and with two or three, strided rows,
+    # one to four chunks a row, chunks of three to eight waves, every width of a code, a workgroup with one row and with several, both sides of
+    # the lines between this kernel and the one with eight values a lane, strided rows,
     # zeros among them (groups without a direction, amplitudes of zero): the bits of rotation and encoding in two calls, and the
     # oracle's for a row of each kind
     D, K = 8, 16
