@@ -378,8 +378,8 @@ __device__ inline void rotate_encode8_body(const enc8_launch &f, const pvq_encod
     }
 }
 
-// Registers for eight waves a SIMD (64 a lane).  8192 x 8192 bf16, 2-bit codes, blocks of 64 / 512 / 4096: 61 / 76 / 79 us, calls in a
-// row (with two barriers an exchange, selections in the stages across lanes and divisions for the codes 65 / 80 / 83).
+// Registers for eight waves a SIMD (64 a lane).  8192 x 8192 bf16, 2-bit codes, blocks of 4096: 79 us, calls in a row (with two barriers an
+// exchange, selections in the stages across lanes and divisions for the codes 83); 4000 x 6144 in blocks of 64 28.6.
 template <typename TIn, int CODES, bool LS, int LOG2N>
 __global__ __launch_bounds__(512, 8) void rotate_encode8_kernel(enc8_launch f, pvq_encode_args a, int log2n,
                                                             const uint8_t *signs, float scale)
