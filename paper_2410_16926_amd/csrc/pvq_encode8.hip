@@ -580,23 +580,37 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     //    700 x 4096 in blocks of 256 8.0 / 7.0, 700 x 14336 float32 in blocks of 64 17.6 / 17.2, 768 x 16384 in blocks of 1024 21.1 / 17.4.
     //    (One or two waves, and rows of more than four chunks with codes, have the others.)  Not float32 rows of several blocks of 8192 with codes, whose
     //    signs are not on their way early: 768 x 16384 19.4 / 20.4, 1024 x 16384 26.5 / 24.4.
-    //  - With more rows in whole chunks of 8192 values, of which three workgroups fit a unit (fewer waves: 4000 x 6144 in blocks of 64 28.6 / 33.2):
-    //    blocks of 8192: 1024 x 8192 15.0 / 11.9, 8192 x 8192 98.6 / 80.4, float32 106.9 / 87.8; 3000 x 24576 102.5 / 89.6;
-    //    blocks of 2048: 8192 x 8192 84.4 / 79.8, 3000 x 16384 67.7 / 61.2; of 1024: 83.2 / 74.1, 67.8 / 58.0; of 512: 79.4 / 74.1, 62.1 / 57.4;
-    //    blocks of 256 and 128, only in rows of one chunk: 8192 x 8192 73.3 / 70.8, 69.6 / 69.0 (4000 x 16384 70.6 / 71.9, 66.1 / 68.6);
-    //    blocks of 64, the same: 8192 x 8192 65.7 / 65.4, float32 76.5 / 73.6, 2048 x 8192 19.7 / 18.7 but float32 20.2 / 20.6.
+    //  - With more rows in whole chunks of 8192 values, of which three workgroups fit a unit (fewer waves: 4000 x 6144 in blocks of 64 28.6 / 33.2),
+    //    768 rows at a time; with eight values a lane eight workgroups fit, 2048 rows.  Rows of one chunk, by their number:
+    //                                        769         1100        1300        1536        2048        2304        3000        3500        4500        8192
+    //      block 64, float32             11.6 / 10.8 14.9 / 13.8 16.3 / 17.6 17.1 / 17.9 19.8 / 21.2 21.4 / 23.8 26.5 / 29.4 32.3 / 32.3             75.7 / 80.9
+    //            64                      10.7 / 10.1 13.0 / 11.9 14.6 / 15.0 15.5 / 15.4 19.0 / 19.2 20.5 / 22.2 24.8 / 27.8 30.5 / 30.7             63.6 / 66.9
+    //            128, float32            12.3 / 11.3 15.7 / 14.4 17.3 / 18.2 17.5 / 18.7 21.5 / 22.1 22.9 / 24.9 28.3 / 31.0 33.8 / 34.1             77.4 / 76.2
+    //            128                     11.4 / 10.5 13.7 / 12.8 15.5 / 16.0 16.5 / 16.5 20.0 / 20.1 22.0 / 23.4 27.0 / 29.9 32.3 / 33.0             68.3 / 71.8
+    //            256, float32            13.3 / 11.8 16.7 / 15.0 18.3 / 18.8 18.6 / 19.1 22.3 / 22.7 24.5 / 25.4 30.2 / 31.7 35.9 / 34.9             85.0 / 81.8
+    //            256                     12.3 / 10.7 14.7 / 12.7 16.4 / 16.1 17.2 / 16.6 20.8 / 20.7 22.7 / 23.7 28.6 / 30.0 33.9 / 33.1             71.7 / 71.8
+    //            512                     13.0 / 11.0             17.8 / 16.9 18.5 / 17.3 23.0 / 21.5 25.2 / 24.7 31.2 / 31.7 38.5 / 34.7 44.2 / 44.8 78.5 / 75.6
+    //            1024, float32           13.0 / 11.4             18.1 / 19.3 18.4 / 19.7 23.3 / 23.4 26.1 / 26.6 32.4 / 33.4 36.1 / 36.4 46.5 / 46.8 89.6 / 84.6
+    //            1024                    12.7 / 11.2             16.7 / 17.1 17.6 / 17.5 22.1 / 21.7 25.1 / 24.9 31.8 / 31.9 35.4 / 34.9 44.9 / 45.1 80.2 / 76.4
+    //            2048, float32           12.9 / 11.6             18.3 / 19.7 18.7 / 19.8 23.2 / 23.9 26.1 / 27.6 32.8 / 34.9 37.4 / 38.6 46.6 / 50.6 92.2 / 90.5
+    //            2048                    12.9 / 11.0             16.8 / 17.4 17.7 / 17.8 22.2 / 22.0 25.4 / 26.0 32.3 / 33.4 35.7 / 36.9 45.6 / 48.0 81.0 / 82.4
+    //    blocks of 8192: 1024 x 8192 15.0 / 11.9, 8192 x 8192 98.6 / 80.4, float32 106.9 / 87.8; 3000 x 24576 102.5 / 89.6.  Rows of several chunks: blocks
+    //    of 512 8192 x 16384 168 / 153; of 1024 179 / 156, float32 184 / 162; of 2048 181 / 161, 3000 x 16384 65.8 / 63.1, float32 67.5 / 67.1, but with
+    //    float32 amplitudes 3000 x 16384 55.5 / 55.5, 8192 x 16384 146 / 148, float32 163 / 171; of 128 and 256 4000 x 16384 66.1 / 68.6, 70.6 / 71.9.
     //  - Not blocks of 4096, of which four workgroups of eight values a lane fit a unit: 8192 x 8192 80.6 / 79.8, 1536 x 16384 float32 33.8 / 36.0.
     const int units = (int)(a.groups / 128);                         // of 1024 values, a wave's
     int waves = 8;
     while (log2n <= 10 && waves > 1 && units % waves != 0) waves--;
-    const bool few = a.rows <= 768, whole = a.groups % 1024 == 0, one = a.groups == 1024;
+    const bool few = a.rows <= 768, whole = a.groups % 1024 == 0, one = a.groups == 1024, f32 = dtype == PVQ_F32;
+    const bool some = a.rows <= 1152;                                // (between 1100 and 1300, see the table)
     bool halves = false;
     if (a.groups % 128 == 0 && waves > 2 && (!codes || units <= 4 * waves)) {
-        if (log2n == 13) halves = !(dtype == PVQ_F32 && codes && !one && few);
-        else if (log2n == 11) halves = whole;
-        else if (log2n == 9 || log2n == 10) halves = few || whole;
-        else if (log2n == 7 || log2n == 8) halves = few || one;
-        else if (log2n == 6) halves = few || (one && (dtype != PVQ_F32 || a.rows > 4096));
+        if (log2n == 13) halves = !(f32 && codes && !one && few);
+        else if (log2n == 11) halves = whole && (some || (codes && !one));
+        else if (log2n == 10) halves = few || (whole && (some || !one || !f32 || a.rows > 2560));
+        else if (log2n == 9) halves = few || whole;
+        else if (log2n == 8) halves = few || (one && (some || (!f32 && a.rows <= 2048) || a.rows > 3072));
+        else if (log2n == 6 || log2n == 7) halves = few || (one && some);
     }
     const size_t hbuf = log2n > 9 ? (size_t)(8 * L + 8 * L / 32 + 1) : 0;
     const size_t lds = (kHeadWords + (codes ? (size_t)((a.groups + 3) & ~3) : 0) + hbuf) * 4;
@@ -645,7 +659,9 @@ hipError_t pvq_rotate_encode8_launch(const pvq_ctx *c, const pvq_encode_args &a,
     case 10: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 10>)); break;         \
     default: PVQ_RE8_LAUNCH((rotate_encode8_kernel<T, C, LS_, 9>)); break;          \
     }
-    if (log2n == 13) {
+    if (log2n == 13) {                                               // float32, codes, at most 768 rows of two to four blocks
+        static_assert(kMaxGroups <= 4 * 8192 / D, "no row is too long for the kernel above");
+        if (dtype != PVQ_F32 || !codes) return hipErrorInvalidValue;
         if (a.groups == 2 * L) { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<2, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<2, false>)); }
         else if (a.groups == 3 * L) { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<1, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<1, false>)); }
         else { if (ls) PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<4, true>)); else PVQ_RE8_LAUNCH((rotate_encode8_kernel_8192<4, false>)); }

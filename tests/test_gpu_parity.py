@@ -583,7 +583,11 @@ def test_rotated_rows_that_workgroups_take_in_turn(rows, cols, block):
                           (3, 10240, 256, 0, True, "ls"), (770, 8192, 256, 8, True, "l2"), (2, 32768, 256, 2, False, "l2"),
                           (767, 4096, 512, 2, False, "l2"), (780, 16384, 512, 1, True, "ls"), (3, 22528, 512, 2, True, "l2"),
                           (4, 14336, 1024, 2, True, "l2"), (3, 20480, 1024, 4, False, "l2"), (769, 6144, 1024, 2, True, "l2"),
-                          (2, 30720, 1024, 0, True, "l2"), (3, 2048, 256, 2, True, "l2")])
+                          (2, 30720, 1024, 0, True, "l2"), (3, 2048, 256, 2, True, "l2"),
+                          (1152, 8192, 64, 8, False, "l2"), (1153, 8192, 64, 2, True, "l2"), (1152, 8192, 128, 1, True, "ls"), (1153, 8192, 128, 4, False, "l2"),
+                          (1153, 8192, 256, 2, False, "l2"), (2048, 8192, 256, 4, True, "l2"), (2049, 8192, 256, 4, True, "ls"), (3073, 8192, 256, 1, False, "l2"),
+                          (1153, 8192, 1024, 2, False, "l2"), (2561, 8192, 1024, 0, False, "ls"), (1152, 8192, 2048, 2, False, "l2"), (1153, 8192, 2048, 8, True, "l2"),
+                          (1160, 16384, 2048, 2, False, "l2"), (1160, 16384, 2048, 0, True, "l2")])
 def test_rotation_and_encoding_with_sixteen_values_a_lane(rows, cols, block, bits, bf16, amplitude):
     # one to four chunks a row, chunks of three to eight waves, every width of a code, a workgroup with one row and with several, both sides of
     # the lines between this kernel and the one with eight values a lane, strided rows,
