@@ -93,7 +93,7 @@ template <int PANELS> struct t_buffers {
 // ---- a row's group across L neighbouring lanes, C = D / L coordinates a lane --------------------------------
 template <int D> struct split {
     static constexpr int L = D == 8 ? 8 : 16, C = D / L;
-    static constexpr int kRowsOfWave = 64 / L;
+    static constexpr int kRowsOfWave = 64 / L, kMost = kWaves * kRowsOfWave;         // rows of a panel workgroup, at most
     static constexpr int kGroups = kPanelCols / D;
     // LDS of the panel role: D x D blocks of U on and above the panel's diagonal, before that t values and sums on their way
     // to and from the matrix cores' layout (kXPitch: an operand's values lie on different banks)
@@ -626,8 +626,8 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
 
 // The PANELS panels from number `panel` on (128 columns each, 64 at the end), and the panels in front of them, as many, onto the columns
 // behind.  The grid is panel_wgs + chunks * shares workgroups, the latter none for panel 0: the updates' rows are in up to eight chunks, which
-// neighbouring workgroups, on different dies, take in turn, so that a chunk's t values are read from one L2; a chunk's steps of 64 rows
-// times 64 columns are shared out evenly.
+// neighbouring workgroups, on different dies, take in turn, so that with eight a chunk's t values are read from one L2 (with fewer, from one of
+// two or more); a chunk's steps of 64 rows times 64 columns are shared out evenly.
 // (at most 128 registers per lane with one panel, four workgroups per compute unit, three for groups of 32, whose blocks take more LDS)
 template <int D, bool LS, int ROWS, int PANELS>
 __global__ __launch_bounds__(kThreads, PANELS > 1 ? 2 : D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
@@ -676,13 +676,19 @@ void launch_step(float *W, const float *U, float *work, const correct_shape &a, 
     const int64_t behind = a.cols - (int64_t)(panel + PANELS) * kPanelCols;
     const int col_tiles = panel > 0 && behind > 0 ? (int)(behind / kTileCols) : 0;
     const int panel_wgs = (int)((a.rows + ROWS - 1) / ROWS);
-    // Update workgroups.  Where every unit has a panel workgroup, one beside it: they all start with the launch, and whatever the
-    // columns are they end together.  With fewer the units that have none are ahead, and smaller shares let them take more.  (Shares
-    // 256 / 512 / 1024 / 4096: 8192 x 8192 5020 / 5710 / 5370 / 5940 us, 8192 x 4096 1490 / 1500 / 1620 / 1810; 3000 x 8192 2750 / 2790 /
-    // 2650 / 2750; 1024 x 8192 1640 / 1650 / 1550 / 1480, 2048 x 4096 790 / 810 / 770 / 740.)
-    constexpr uint32_t kUnits = 256;
-    const uint32_t steps = (uint32_t)((a.rows + kStepRows - 1) / kStepRows);
-    const uint32_t most = panel_wgs >= (int)kUnits ? kUnits : a.rows > 2048 ? 4 * kUnits : 16 * kUnits;
+    // Update workgroups.  Where every unit has as many panel workgroups as the others, one beside them: they all start with the launch,
+    // and whatever the columns are they end together; with one panel a launch also where all panel workgroups have a place at once.
+    // Elsewhere some units are ahead, and smaller shares let them take more.  (Shares 256 / 1024 / 2048 / 4096, us.  Two panels a launch:
+    // 8192 x 8192 5020 / 5370 / - / 5940, 16384 x 4096 2850 / 2820 / 2900 / 2990, 32768 x 4096 5590 / 5660 / 5710 / 5810, but 8200 x 8192 5980 / 5600 / 5490 / 5690,
+    // 20000 x 4096 5200 / 3660 / 3630 / 3690, in groups of 16 10000 x 4096 2740 / 2000 / 2010 / -; 3000 x 8192 2750 / 2650 / - / 2750, 1024 x 8192 1640 / 1550 / - /
+    // 1480.  One panel: 8200 x 8192 5870 / 6000 / 5830 / 5870, 16384 x 4096 3020 / 3150 / 3020 / 3070, in groups of 32 7168 x 4096 1490 / 1540 / 1500 / -.
+    // Where a unit does not hold them all the last panel workgroups have update
+    // workgroups in front of them: one panel 40000 x 4096 10900 / 7650 / 7460 / 7650, in groups of 32 14336 x 4096 4130 / 2810 / 2740 / -.)
+    constexpr uint32_t kUnits = 256, kPlaces = (D == 32 ? 3 : 4) * kUnits;
+    const uint32_t steps = (uint32_t)((a.rows + kStepRows - 1) / kStepRows), chain = (uint32_t)panel_wgs;
+    const bool even = 16 * ((chain + kUnits - 1) / kUnits * kUnits - chain) <= chain;
+    const bool beside = chain >= kUnits && (PANELS > 1 ? even : chain <= kPlaces || (even && chain <= 4 * kUnits));
+    const uint32_t most = beside ? kUnits : chain > kUnits ? 8 * kUnits : a.rows > 2048 ? 4 * kUnits : 16 * kUnits;
     update_split parts;
     // As many chunks as take about the same number of steps: a die whose chunks have one step in two more than the others' keeps
     // the launch waiting (768 rows, 12 steps, of 8192: in eight chunks 1507 us, in four 1451; 1280 rows in eight 1756, in four 1638; 320 rows
@@ -709,12 +715,11 @@ template <int D, int PANELS>
 hipError_t launch_panels(float *W, const float *U, float *work, const correct_shape &a, hipStream_t s)
 {
     const int panels = (int)((a.cols + kPanelCols - 1) / kPanelCols);
-    constexpr int kMost = kWaves * split<D>::kRowsOfWave;
     for (int p = 0; p < panels; p += PANELS) {
         // With few rows, which do not fill the units either way, a panel workgroup takes 16: half the matrix instructions in front
         // (64 x 2048 17.8 to 16.6 us a panel, 2048 x 4096 26.0 to 25.2; 4096 x 4096 34.1 to 35.0).
         if (a.rows <= 2048) launch_step<D, 16, PANELS>(W, U, work, a, p, s);
-        else launch_step<D, kMost, PANELS>(W, U, work, a, p, s);
+        else launch_step<D, split<D>::kMost, PANELS>(W, U, work, a, p, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -732,15 +737,21 @@ hipError_t launch_panels(int D, float *W, const float *U, float *work, const cor
 
 // W: rows x cols float32 (cols a multiple of 64), U: cols x cols, work: `buffers` (two or four) of rows x 128 floats.
 // Two panels a launch where the updates are what there is to wait for; with few rows, or up to 2048 of a narrow matrix, it is the chain,
-// whose fronts get longer (one / two panels in groups of 8, 512 x 8192 1343 / 1378 us, 768 x 6144 1020 / 1039, 768 x 8192 1451 / 1451,
+// whose fronts get longer, and so it is where the panel workgroups are more than the two for every unit that have a place at once, and the
+// columns few (one / two panels in groups of 8, 512 x 8192 1343 / 1378 us, 768 x 6144 1020 / 1039, 768 x 8192 1451 / 1451,
 // 1024 x 2048 294 / 311, 1024 x 4096 670 / 667, 1280 x 2560 397 / 406, 1280 x 3072 497 / 497, 1536 x 2048 318 / 321, 2048 x 2048 338 / 330,
-// 8192 x 704 138 / 128; in groups of 16 1024 x 4096 531 / 522, 768 x 8192 1218 / 1163, in groups of 32 547 / 540, 1273 / 1196).
+// 8192 x 704 138 / 128; in groups of 16 1024 x 4096 531 / 522, 768 x 8192 1218 / 1163, in groups of 32 547 / 540, 1273 / 1196;
+// 16384 x 1024 318 / 306, 16400 x 1024 324 / 402, 16400 x 3072 1812 / 1900, 20000 x 3072 2164 / 2247, 16400 x 4096 3056 / 3031, 20000 x 4096 3708 / 3629; 32768 x 1536
+// 997 / 1071, 32768 x 2048 1724 / 1667, 40000 x 2048 2104 / 2061, 65536 x 3072 7176 / 6620; in groups of 16, 16 rows a workgroup, 8192 x 1024 203 / 188, 8200 x 2048
+// 560 / 592, 10000 x 4096 2011 / 2009, 20000 x 2048 1129 / 1177, 20000 x 4096 3801 / 3717).
 hipError_t launch_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
                           int64_t ldu, float *work, int buffers, hipStream_t s)
 {
     correct_shape a;
     a.ldw = ldw; a.rows = rows; a.cols = cols; a.ldu = ldu; a.K = c->K; a.ls = c->amplitude == PVQ_AMP_LS ? 1 : 0;
-    const bool two = buffers == 4 && (rows > 2048 || (rows > 512 && (rows - 512) * cols >= 1 << 21));
+    const int64_t most_rows = c->D == 8 ? split<8>::kMost : split<16>::kMost, chain = (rows + most_rows - 1) / most_rows;
+    const bool at_once = chain <= 512 || cols >= (chain > 960 && c->D == 8 ? 2048 : 4096);
+    const bool two = buffers == 4 && (rows > 2048 ? at_once : rows > 512 && (rows - 512) * cols >= 1 << 21);
     return two ? launch_panels<2>(c->D, W, U, work, a, s) : launch_panels<1>(c->D, W, U, work, a, s);
 }
 

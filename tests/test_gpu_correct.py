@@ -207,6 +207,32 @@ def test_two_panels_a_launch(D, K, rows, cols, ld_extra):
     ctx.close()
 
 
+@pytest.mark.parametrize("D,K,rows,cols,two", [
+    (8, 16, 8192, 320, True), (8, 16, 8193, 320, True), (8, 16, 16384, 320, True), (8, 16, 16385, 320, False), (8, 16, 16400, 4096, True),
+    (8, 16, 30720, 2048, False), (8, 16, 30721, 2048, True), (8, 16, 40000, 384, False), (16, 33, 8192, 320, True), (16, 33, 8193, 320, False),
+    (16, 33, 8200, 4096, True), (32, 60, 12300, 320, False), (32, 60, 16390, 448, False)])
+def test_more_panel_workgroups_than_have_a_place(D, K, rows, cols, two):
+    # 32 rows a panel workgroup in groups of 8, else 16: 256, 512 and 960 of them and one more, few columns and many.  With the smallest work buffer
+    # one panel a launch; with twice as much its second half is touched where a launch has two.  The same bits, and the oracle's for some rows
+    g = torch.Generator(device="cuda")
+    g.manual_seed(si.BASE_SEED + 690 + rows)
+    W0 = torch.randn((rows, cols), generator=g, device="cuda") * 0.02
+    U = torch.triu(torch.randn((cols, cols), generator=g, device="cuda") * (0.3 / cols ** 0.5), diagonal=1)
+    U.diagonal().copy_(0.75 + 0.5 * torch.rand((cols,), generator=g, device="cuda"))
+    ctx = pvq.pvq_ctx_create(D, K)
+    one = W0.clone()
+    pvq.pvq_correct(ctx, one, U, work=torch.empty((rows * 1024,), dtype=torch.uint8, device="cuda"))
+    work = torch.full((rows * 2048,), 0x5A, dtype=torch.uint8, device="cuda")
+    W = W0.clone()
+    pvq.pvq_correct(ctx, W, U, work=work)
+    assert torch.equal(one.view(torch.int32), W.view(torch.int32))
+    assert bool((work[rows * 1024:] == 0x5A).all()) == (not two)
+    some = [0, 31, rows // 2, rows - 17, rows - 1]
+    ref, _ = oracle.correct(W0[some].cpu().numpy(), U.cpu().numpy(), D, K, nthreads=5)
+    assert np.array_equal(W[some].cpu().numpy().view(np.uint32), ref.view(np.uint32))
+    ctx.close()
+
+
 @pytest.mark.parametrize("rows,cols", [(200, 256), (1100, 640)])
 def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols):
     # kernels only, all on the capturing stream; every replay must reproduce the eager result for the weights
