@@ -31,9 +31,10 @@
 // Both roles' multiply-adds run on the matrix cores: v_mfma_f32_16x16x4_f32 adds its four products to an
 // element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
 // tied, subnormal and non-finite operands).
-// 8192 x 8192 in groups of 8 5.02 ms, 28672 x 8192 17.7, 8192 x 4096 1.49, 4096 x 4096 1.06, 1024 x 8192 1.48 (one panel a
-// launch, for which the smallest work buffer has room, 5.6, 19.7, 1.59, 1.14, 1.66).  Before, with one panel a launch, tasks of 64 columns and 128 to 1024 rows and waves
-// that waited for their stores after every 16 rows, 6.12, 20.8, 1.75, 1.09, 1.61; with tiles of 128 x 128 whose workgroups moved in step 6.6 ms.
+// 8192 x 8192 in groups of 8 5.07 ms, 28672 x 8192 17.8, 8192 x 4096 1.52, 4096 x 4096 1.05, 1024 x 8192 1.51; one panel a launch, for which the smallest
+// work buffer has room, 5.56, 19.7, 1.61, 1.10, 1.58.  Before, with one panel a launch, tasks of 64 columns and 128 to 1024 rows and waves
+// that waited for their stores after every 16 rows, 6.10, 21.2, 1.74, 1.10, 1.55 (so with that work buffer 7 to 10 million values in groups of 8 take
+// up to 2.5 % longer now); with tiles of 128 x 128 whose workgroups moved in step 6.6 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -631,7 +632,7 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
 // (at most 128 registers per lane with one panel, four workgroups per compute unit, three for groups of 32, whose blocks take more LDS)
 template <int D, bool LS, int ROWS, int PANELS>
 __global__ __launch_bounds__(kThreads, PANELS > 1 ? 2 : D == 32 ? 3 : 4) void correct_step_kernel(float *__restrict__ W, const float *__restrict__ U,
-                                                                 t_buffers<PANELS> T, correct_shape a, int panel, int panel_wgs, update_split parts, bool late)
+                                                                 t_buffers<PANELS> T, correct_shape a, int panel, int panel_wgs, update_split parts, int late)
 {
     __shared__ __align__(16) float lds[lds_floats<D, PANELS>()];
     if ((int)blockIdx.x < panel_wgs) {
@@ -650,8 +651,8 @@ __global__ __launch_bounds__(kThreads, PANELS > 1 ? 2 : D == 32 ? 3 : 4) void co
         }
     } else {
         // With few rows the chain is what a launch waits for, and its first reads stand in line with those of all tasks (1024 rows of
-        // 8192: its front 4 us alone, 12 to 15 beside them); the tasks, 15 to 27 us in all, let it go first by 3.4 us.
-        if (late) __builtin_amdgcn_s_sleep(127);
+        // 8192: its front 4 us alone, 12 to 15 beside them); the tasks, 15 to 27 us in all, let it go first by `late` times 0.43 us.
+        for (int x = 0; x < late; x++) __builtin_amdgcn_s_sleep(16);
         const uint32_t wg = blockIdx.x - panel_wgs, share = wg >> parts.log2_chunks, chunk = wg - (share << parts.log2_chunks);
         const bool more = chunk < parts.longer;
         const uint32_t steps = parts.steps + (more ? 1u : 0u), first = chunk * parts.steps + std::min(chunk, parts.longer);
@@ -681,14 +682,14 @@ void launch_step(float *W, const float *U, float *work, const correct_shape &a, 
     // Elsewhere some units are ahead, and smaller shares let them take more.  (Shares 256 / 1024 / 2048 / 4096, us.  Two panels a launch:
     // 8192 x 8192 5020 / 5370 / - / 5940, 16384 x 4096 2850 / 2820 / 2900 / 2990, 32768 x 4096 5590 / 5660 / 5710 / 5810, but 8200 x 8192 5980 / 5600 / 5490 / 5690,
     // 20000 x 4096 5200 / 3660 / 3630 / 3690, in groups of 16 10000 x 4096 2740 / 2000 / 2010 / -; 3000 x 8192 2750 / 2650 / - / 2750, 1024 x 8192 1640 / 1550 / - /
-    // 1480.  One panel: 8200 x 8192 5870 / 6000 / 5830 / 5870, 16384 x 4096 3020 / 3150 / 3020 / 3070, in groups of 32 7168 x 4096 1490 / 1540 / 1500 / -.
-    // Where a unit does not hold them all the last panel workgroups have update
+    // 1480.  One panel: 8200 x 8192 5870 / 6000 / 5830 / 5870, 16384 x 4096 3020 / 3150 / 3020 / 3070, in groups of 32 7168 x 4096 1490 / 1540 / 1500 / -; 2048 x 8192
+    // - / 2170 / 2080 / 2140, in groups of 16 - / 2000 / 1910 / 1980.  Where a unit does not hold them all the last panel workgroups have update
     // workgroups in front of them: one panel 40000 x 4096 10900 / 7650 / 7460 / 7650, in groups of 32 14336 x 4096 4130 / 2810 / 2740 / -.)
     constexpr uint32_t kUnits = 256, kPlaces = (D == 32 ? 3 : 4) * kUnits;
     const uint32_t steps = (uint32_t)((a.rows + kStepRows - 1) / kStepRows), chain = (uint32_t)panel_wgs;
     const bool even = 16 * ((chain + kUnits - 1) / kUnits * kUnits - chain) <= chain;
     const bool beside = chain >= kUnits && (PANELS > 1 ? even : chain <= kPlaces || (even && chain <= 4 * kUnits));
-    const uint32_t most = beside ? kUnits : chain > kUnits ? 8 * kUnits : a.rows > 2048 ? 4 * kUnits : 16 * kUnits;
+    const uint32_t most = beside ? kUnits : chain > kUnits ? 8 * kUnits : a.rows > 2048 ? 4 * kUnits : (PANELS > 1 ? 16 : 8) * kUnits;
     update_split parts;
     // As many chunks as take about the same number of steps: a die whose chunks have one step in two more than the others' keeps
     // the launch waiting (768 rows, 12 steps, of 8192: in eight chunks 1507 us, in four 1451; 1280 rows in eight 1756, in four 1638; 320 rows
@@ -705,7 +706,18 @@ void launch_step(float *W, const float *U, float *work, const correct_shape &a, 
         parts.each[more] = shares ? all / shares : 0;
         parts.rest[more] = shares ? all % shares : 0;
     }
-    const bool late = a.rows <= 2048;              // (1024 x 4096 756 to 714 us, 2048 x 4096 869 to 830; 4096 x 4096 1090 either way)
+    // How long the updates wait, in 0.43 us: with one panel a launch until the rest of its chain is about what they take, so less with more
+    // of them.  (0 / 4 / 7 / 10 / 12, us, in groups of 8: 256 x 8192 1200 / 1160 / 1160 / 1170 / 1150, 512 x 4096 613 / 608 / - / 599 / 591, 768 x 4096 675 / 662 /
+    // 655 / 646 / 643, 1024 x 8192 1600 / 1590 / 1580 / 1580 / -, 1280 x 8192 1720 / 1710 / 1710 / 1730 / -, 2048 x 8192 2100 / 2080 / 2100 / 2160 / -; of 16 768 x 4096 530 /
+    // 513 / 504 / 497 / -, 1024 x 6144 906 / 890 / 899 / 919 / -, 2048 x 6144 1210 / 1240 / 1270 / 1320 / -.  Two panels: 1024 x 4096 756 to 714, 2048 x 4096 869 to 830.
+    // More than 2048 rows: none, 4096 x 4096 1090 either way.)
+    int late = 0;
+    if (a.rows <= 2048) {
+        const int64_t n = a.rows * a.cols;
+        if (PANELS > 1) late = 8;
+        else if (D == 8) late = n <= 5 << 20 ? 12 : n <= 8 << 20 ? 10 : 4;
+        else late = n < 4 << 20 ? 10 : n < 6 << 20 ? 8 : n <= 8 << 20 ? 4 : 0;
+    }
     auto kernel = a.ls ? &correct_step_kernel<D, true, ROWS, PANELS> : &correct_step_kernel<D, false, ROWS, PANELS>;
     hipLaunchKernelGGL(kernel, dim3((unsigned)panel_wgs + chunks * shares), dim3(kThreads), 0, s,
                        W, U, T, a, panel, panel_wgs, parts, late);
