@@ -493,6 +493,7 @@ struct decode_wide_params {
     const double *tab_near;
     uint32_t last_index[16];
     void *W_out;
+    int64_t first_group;       // of the launch (decode_wide_rows_kernel)
 };
 
 // word i of the W-word index of group g of a row (zero beyond the index)
@@ -626,7 +627,7 @@ struct lane_q {
 // SIMD on by their issue as well.  D = 128, K = 187, 8192-wide rows, 512 / 1024 / 2048 / 4096 of them: 54 / 60 / 70 / 89 us; with
 // every wave requesting its share of every row (45 scalar instructions a coordinate), a barrier for every coordinate, comparisons and
 // carries that wait for one another, and three branches where one is now, 72 / 75 / 85 / 110; with guess, keys and thresholds in
-// device memory 95 / 100 / 155 / 161.  D = 64, K = 96: 31 / 35 / 46 / 97, before 37 / 41 / 53 / 99 and 55 / 57 / 86 / 104.  Four
+// device memory 95 / 100 / 155 / 161.  D = 64, K = 96: 31 / 35 / 46 / 89, before 37 / 41 / 53 / 99 and 55 / 57 / 86 / 104.  Four
 // coordinates share a turn of the loop, so that shifts are known when it is compiled.
 constexpr int kRowWindow = 256;       // places of a row in LDS
 constexpr int kRowMargin = 96;        // of them below the smallest 2 k when the window is set
@@ -822,7 +823,7 @@ struct rows_walk : lane_q<W> {
 };
 
 template <int CP, int W, int LANES>
-__global__ __launch_bounds__(LANES + 64, LANES == 512 ? (W <= 8 ? 7 : 5) : 1) void decode_wide_rows_kernel(decode_wide_params p)
+__global__ __launch_bounds__(LANES + 64, LANES >= 448 ? (W <= 8 ? 7 : 5) : 1) void decode_wide_rows_kernel(decode_wide_params p)
 {
     extern __shared__ __align__(16) uint32_t lds_words[];
     constexpr int D = 64 * CP;
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(LANES + 64, LANES == 512 ? (W <= 8 ? 7 : 5) : 1) vo
         __syncthreads();
         return;
     }
-    const int64_t g0 = (int64_t)blockIdx.x * LANES;
+    const int64_t g0 = p.first_group + (int64_t)blockIdx.x * LANES;
     // the lane's group (lanes behind the last group take that one, and write nothing)
     const int64_t gid = std::min<int64_t>(g0 + tid, p.total_groups - 1);
     const int64_t row = gid / p.groups, g = gid - row * p.groups;
@@ -1321,27 +1322,39 @@ static int64_t few_groups(const pvq_ctx *c)
 
 // Beyond that, whether the rows of the tables go through LDS.  They do while a magnitude fits a byte; but with more than about
 // twice as many pulses as coordinates many places lie outside a window of 256, and then all of them are as well read from device
-// memory: with many pulses always, with fewer once a unit has more groups than its two workgroups of 512 take at once.  us, LDS
-// (every wave requesting its share of the rows; the present form takes 10 to 25 % less up to K = 127) / device memory:
-//                    8192 groups   131072     262144     393216     524288     1048576
-//   D = 64, K = 96     34 / 44     42 / 58    55 / 88    83 / 94    100 / 107   187 / 197   (device memory with an earlier kernel)
-//           K = 112    35 / 43     46 / 59    58 / 88    91 / 95    109 / 109   203 / 201   (the same)
-//           K = 127    39 / 45     52 / 59    66 / 88   105 / 89    123 / 104   233 / 194
-//           K = 150    46 / 46     60 / 59    75 / 81   120 / 91    142 / 106   271 / 198
-//           K = 160    49 / 46     63 / 52    78 / 81   126 / 91    147 / 108   282 / 200
-//           K = 200    58 / 47     75 / 57    96 / 91   157 / 105   182 / 122   351 / 226
-//   D = 128, K = 187 8192 groups 71 / 95, 262144 111 / 164, 524288 211 / 325; K = 255 90 / 97, 148 / 176, 285 / 346.
+// memory: with many pulses always, with fewer once a unit has more groups than its two workgroups of 512 take at once (where device memory
+// has its next step in turn).  us, LDS / device memory:
+//                    8192 groups   65536      131072     163840     196608     262144     294912     393216     524288     1048576
+//   D = 64, K = 96     27 / 45    31 / 48    36 / 50    46 / 52    46 / 53    48 / 80    70 / 82    71 / 88    89 / 102  162 / 190
+//           K = 112    28 / 46    34 / 49    40 / 51    50 / 53    52 / 54    52 / 80    78 / 83    81 / 89    95 / 104  173 / 194
+//           K = 120    30 / 46    37 / 49    43 / 51    54 / 53    55 / 54    56 / 80    85 / 83    88 / 90   102 / 105  184 / 195
+//           K = 127    33 / 46    40 / 48    46 / 51    57 / 53    59 / 54    60 / 80    91 / 82    93 / 90   108 / 106  195 / 197
+//           K = 135    35 / 46    43 / 48    51 / 51    61 / 53    63 / 54    64 / 81   100 / 83   103 / 91   117 / 107  213 / 198
+//           K = 150    41 / 46    50 / 49    57 / 51    69 / 53    70 / 55    71 / 81   113 / 84   115 / 91   132 / 107  244 / 203
+//           K = 160    49 / 46                63 / 52                          78 / 81              126 / 91   147 / 108  282 / 200   (LDS: every wave
+//           K = 200    58 / 47                75 / 57                          96 / 91              157 / 105  182 / 122  351 / 226    requesting rows)
+//   D = 128, K = 187 8192 groups 53 / 95, 262144 91 / 164, 524288 209 / 325; K = 255 70 / 97, 132 / 279, 267 / 528.
 static bool rows_in_lds(const pvq_ctx *c, int64_t groups)
 {
     if (c->D == 128) return c->K <= 255;
-    return c->K <= 112 || (c->K <= 150 && groups <= 256 * 1024);
+    return c->K <= 120 || (c->K <= 150 && groups <= 256 * 1024);
 }
 
 // Lanes of a workgroup whose rows of the tables go through LDS: the fewest, from 128 on, with which the groups take one place
 // on each of the 256 units, up to 512.  (64 lanes, a wave that loads its rows alone: 8192 groups of 128 in 80 us, with 128
 // lanes 70; 256 at most: 262144 groups in 151 us, with 512 lanes, two workgroups to a unit, 109.)
-static int rows_lanes(int64_t groups)
+// With integers of up to 8 words three workgroups of 512 and the wave that brings their rows fit a unit, 27 waves where it has room for 28 or
+// 32; what comes in the place of one that is done does not always find room for nine waves (or leaves five waves' room unused).  Workgroups of 448 lanes have
+// eight waves, of which three or four fit any time.  From where workgroups follow one another, us, 512 / 448 lanes:
+//                      393216     458752     524288     655360     786432     1048576    1572864 groups
+//   D = 64, K = 40     63 / 69    76 / 69    77 / 81    93 / 94   117 / 106  154 / 145  234 / 199
+//           K = 96     72 / 75    86 / 76   101 / 89   112 / 104  144 / 119  181 / 162  274 / 224
+//           K = 112    80 / 82   104 / 85   119 / 97   125 / 112  164 / 129  208 / 175  303 / 243
+//   D = 128, K = 28    99 / 115  129 / 116  131 / 141  159 / 166  185 / 189  260 / 257  374 / 349      (integers of 4 words)
+//            K = 84   115 / 131  151 / 132  153 / 163  209 / 190  252 / 221  324 / 299  459 / 411      (8)
+static int rows_lanes(const pvq_ctx *c, int64_t groups)
 {
+    if (c->words == 8 ? groups > (c->D == 64 ? 768 : 1024) * 512 : c->words == 4 && c->D == 64 && groups > 1280 * 512) return 448;
     int lanes = 128;
     while (lanes < 512 && groups > (int64_t)256 * lanes) lanes *= 2;
     return lanes;
@@ -1350,13 +1363,24 @@ static int rows_lanes(int64_t groups)
 template <int CP, int W, int LANES>
 static hipError_t launch_rows(const decode_wide_params &p, size_t lds, hipStream_t s)
 {
-    if constexpr (CP == 2 || W <= 8) {              // (as wide as the integers of rows_in_lds are)
+    if constexpr (LANES == 448 ? W == 8 || (CP == 1 && W == 4) : CP == 2 || W <= 8) {  // (as wide as the integers of rows_in_lds are)
         if (lds > 64 * 1024) {
             const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(decode_wide_rows_kernel<CP, W, LANES>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)((p.total_groups + LANES - 1) / LANES)), dim3(LANES + 64), lds, s, p);
+        // With integers of 16 words a workgroup reads 17 KB a coordinate, from L2 as long as the workgroups of a die are at about the same one.
+        // Those that come in the place of others are not, so the 512 that have a place at once are a launch, unless the last would have
+        // few (D = 128, K = 255, us, in one / in launches of 512: 458752 groups 310 / 263, 524288 312 / 267, 786432 460 / 403, 1048576 579 / 538,
+        // but 393216 222 / 239, 655360 349 / 368, 917504 478 / 511; with 12 words 524288 209 / 184, but 917504 327 / 360, and in one no slower than any
+        // form before).
+        const int64_t workgroups = (p.total_groups + LANES - 1) / LANES;
+        const int64_t of_launch = W == 16 && (workgroups - 1) % 512 >= 256 ? 512 : workgroups;
+        for (int64_t at = 0; at < workgroups; at += of_launch) {
+            decode_wide_params q = p;
+            q.first_group = at * LANES;
+            hipLaunchKernelGGL((decode_wide_rows_kernel<CP, W, LANES>), dim3((unsigned)std::min(of_launch, workgroups - at)), dim3(LANES + 64), lds, s, q);
+        }
         return hipSuccess;
     } else {
         return hipErrorInvalidValue;
@@ -1402,7 +1426,7 @@ hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
     p.K = c->K; p.bits = c->index_bits; p.out_dtype = out_dtype;
     p.row_len = pvq_wide_row(c->K); p.key_len = pvq_wide_key_row(c->K); p.buckets = pvq_wide_buckets(c->words);
     p.tab_t = c->tab_u; p.tab_key = c->tab_key; p.tab_near = c->tab_near; p.tab_guess = c->tab_guess;
-    p.W_out = a.W_out;
+    p.W_out = a.W_out; p.first_group = 0;
     for (int i = 0; i < 16; i++) p.last_index[i] = c->last_index[i];
     if ((p.total_groups + 63) / 64 > 0x7FFFFFFF) return hipErrorInvalidValue;
     const int64_t total = p.total_groups;
@@ -1419,13 +1443,14 @@ hipError_t pvq_wide_launch_decode(const pvq_ctx *c, const pvq_decode_args &a, in
 #undef PVQ_WIDE_DEC
         if (e != hipSuccess) return e;
     } else {
-        const int lanes = rows_lanes(total);
+        const int lanes = rows_lanes(c, total);
         const size_t lds = decode_rows_lds(c->words, lanes);
         hipError_t e = hipSuccess;
 #define PVQ_WIDE_DEC(CP, W)                                                        \
     switch (lanes) {                                                               \
     case 128: e = launch_rows<CP, W, 128>(p, lds, s); break;                       \
     case 256: e = launch_rows<CP, W, 256>(p, lds, s); break;                       \
+    case 448: e = launch_rows<CP, W, 448>(p, lds, s); break;                       \
     default: e = launch_rows<CP, W, 512>(p, lds, s); break;                        \
     }
         PVQ_WIDE_DEC_DW
