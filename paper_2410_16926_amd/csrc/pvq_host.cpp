@@ -660,7 +660,7 @@ extern "C" int pvq_correct(const pvq_ctx *c, float *W, int64_t rows, int64_t col
     if (!aligned(work, 16)) return PVQ_E_ALIGNMENT;
     if ((rc = check_device(c))) return rc;
     const bool twice = work_bytes / 2 >= (size_t)rows * 256 * sizeof(float);
-    const auto launch = twice && pvq_launch_correct_two_panels ? pvq_launch_correct_two_panels : pvq_launch_correct;
+    const auto launch = twice ? pvq_launch_correct_two_panels : pvq_launch_correct;
     const hipError_t e = launch(c, W, rows, cols, ldw, U, ldu, (float *)work, (hipStream_t)stream);
     return e == hipSuccess ? PVQ_OK : hip_fail(e);
 }

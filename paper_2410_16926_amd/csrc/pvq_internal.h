@@ -141,10 +141,9 @@ hipError_t pvq_launch_fill_zero(float *p, int64_t n, hipStream_t s);   // p[0..n
 // of 64, U cols x cols upper triangular, work 2 x rows x 128 floats (the t values of two panels, used in turn)
 hipError_t pvq_launch_correct(const pvq_ctx *ctx, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
                               int64_t ldu, float *work, hipStream_t s);
-// the same with work of 4 x rows x 128 floats: two panels a launch where that is faster  (weak: a program of the library's host
-// sources alone, with stand-ins for the launches, need not have it)
-__attribute__((weak)) hipError_t pvq_launch_correct_two_panels(const pvq_ctx *ctx, float *W, int64_t rows, int64_t cols, int64_t ldw,
-                                                               const float *U, int64_t ldu, float *work, hipStream_t s);
+// the same with work of 4 x rows x 128 floats: two panels a launch where that is faster
+hipError_t pvq_launch_correct_two_panels(const pvq_ctx *ctx, float *W, int64_t rows, int64_t cols, int64_t ldw, const float *U,
+                                         int64_t ldu, float *work, hipStream_t s);
 // the same with the library's static work buffer (at most pvq_correct_static_max_rows() rows), on `s` alone
 int64_t pvq_correct_static_max_rows(void);
 hipError_t pvq_launch_correct_static(const pvq_ctx *ctx, float *W, int64_t rows, int64_t cols, int64_t ldw,

@@ -15,6 +15,7 @@ bool pvq_encode_fits(const pvq_ctx *, const pvq_encode_args &) { return true; }
 hipError_t pvq_launch_encode(const pvq_ctx *, const pvq_encode_args &, int, hipStream_t) { return reached("pvq_launch_encode"); }
 hipError_t pvq_launch_fill_zero(float *, int64_t, hipStream_t) { return reached("pvq_launch_fill_zero"); }
 hipError_t pvq_launch_correct(const pvq_ctx *, float *, int64_t, int64_t, int64_t, const float *, int64_t, float *, hipStream_t) { return reached("pvq_launch_correct"); }
+hipError_t pvq_launch_correct_two_panels(const pvq_ctx *, float *, int64_t, int64_t, int64_t, const float *, int64_t, float *, hipStream_t) { return reached("pvq_launch_correct_two_panels"); }
 int64_t pvq_correct_static_max_rows(void) { return 8192; }
 hipError_t pvq_launch_correct_static(const pvq_ctx *, float *, int64_t, int64_t, int64_t, const float *, int64_t, hipStream_t) { return reached("pvq_launch_correct_static"); }
 hipError_t pvq_launch_size_table(int, int, int, uint32_t *, uint32_t *, hipStream_t) { return reached("pvq_launch_size_table"); }

@@ -3,11 +3,13 @@
 import ctypes as C
 import os
 import re
+import subprocess
 
 import numpy as np
 import pytest
 
 import paper_2410_16926_amd as pvq
+from paper_2410_16926_amd import build
 from tests import pins
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -171,3 +173,11 @@ def test_rows_of_doubles_replay_sampled_indices(K):
     # 52 bits (K <= 33), else in all but the first; the smallest and the largest K that have such rows
     bad, sched, _ = pvq.pvq_walk_tables_selftest(16, K, seed=K, count=60000)
     assert bad == 0 and sched == (8, 0)
+
+
+def test_every_function_of_the_library_is_linked_for_certain():
+    # a weak symbol would let a build that has lost its definition link, and the call that needs it take another path
+    names = subprocess.run(["nm", "-D", "--defined-only", build.LIB_PATH], check=True, capture_output=True, text=True).stdout
+    defined = [line.split()[-2:] for line in names.splitlines() if "pvq_" in line]
+    assert len(defined) > 30
+    assert [name for kind, name in defined if kind in "WwVv" and re.search(r"^(pvq_|_Z\d+pvq_)", name)] == []
