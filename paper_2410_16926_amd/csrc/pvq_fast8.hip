@@ -1136,17 +1136,24 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 //        2048 x 8192        2.1 M    9.7 / 14.6  13.8 / 14.6  14.4 / 15.0  15.5 / 17.3  15.9 / 18.9  18.5 / 24.0
 //       14336 x 4096        7.3 M   19.7 / 30.5  22.1 / 30.3  23.4 / 33.6  25.3 / 44.1  26.5 / 46.9  31.5 / 49.9
 //    (One and two vectors with gemv8_kernel's rows in whole batches, as it was.)
-//  - One and two vectors now: the table decoder takes 7.0 / 7.5 us where a wave has one row, 8.7 / 9.6 where it has two; the walk's time
-//    goes by its tiles of four rows and the row's length.  table / walk, 24-bit indices:
-//           rows x columns   groups         1            2                rows x columns   groups         1            2
-//         512 x 4096       0.26 M    6.9 /  5.8   7.2 /  5.8            1100 x 4096      0.55 M    7.0 /  9.4   7.4 /  9.6
-//         256 x 8192       0.25 M    7.0 /  7.7   7.7 /  7.7            1536 x 3520      0.66 M    7.1 /  7.6   7.5 /  7.7
-//        1024 x 8192       1.0 M     7.3 /  7.8   7.9 /  7.9            2048 x 4096      1.0 M     7.4 /  9.6   7.6 /  9.7
-//           8 x 16384       16 K     6.5 / 11.4   7.2 / 11.4            1536 x 2752      0.5 M     6.9 /  6.4   7.3 /  6.6
-//         256 x 28672      0.9 M     8.3 / 17.9   8.7 / 17.9            2600 x 2048      0.65 M    7.0 /  6.8   7.5 /  6.9
-//        1030 x 8192       1.0 M     8.7 / 13.3   9.8 / 13.2            2048 x 4608      1.2 M     8.4 /  8.0   9.2 /  8.1
-//    So it has rows of more than 8192 values, rows of 8192 of more than 1024 (one vector: from 256 on), and shorter ones down to 440 groups
-//    where there are more than 1024 and each wave has one; beyond that the lines for other widths of the index, whose fetches
+//  - One and two vectors now: a launch of the table decoder takes 7.0 / 7.5 us where a wave has one row, 1.6 / 2 more for every further one;
+//    the walk's time goes by the tiles of four rows that a unit has and by the row's length.  24-bit indices, 2-bit codes, by groups of a row, table / walk:
+//        rows              352        440        520        600        640        680        800        896        960        1024       1028       1100       1200       1280       1284       1400
+//         512, 1 vector             (1 tile, 1 row a wave)                                          7.0 / 6.9  7.0 / 7.5  7.0 / 7.7  7.1 / 7.5  7.1 / 8.3  7.0 / 7.9  7.2 / 8.8  7.3 / 9.1  7.1 / 8.9
+//              2                                                                                    7.6 / 6.9  7.8 / 7.5  7.8 / 7.9  7.7 / 7.7  7.6 / 8.3  7.7 / 8.0  7.8 / 8.9  7.7 / 9.1  7.3 / 8.9
+//        1024, 1 vector   (1 tile, 2 rows from 1025 groups on)                                      7.4 / 7.0  7.4 / 7.6  7.4 / 7.8  8.5 / 7.8  8.6 / 8.5  8.6 / 8.3  8.8 / 9.1  8.2 / 9.2  8.3 / 9.1
+//              2                                                                                    7.8 / 7.0  7.8 / 7.6  7.9 / 7.9  9.4 / 7.9  9.7 / 8.5  9.7 / 8.3  9.8 / 9.1  8.9 / 9.4  9.1 / 9.2
+//        1100, 1 vector  6.9 / 6.3  7.0 / 7.6  7.0 / 7.5  7.1 / 8.5  7.0 / 8.5  7.3 / 10.0 8.5 / 11.8       (2 tiles, 1 row up to 768 groups)
+//        1700            7.3 / 6.4  7.2 / 7.7  8.4 / 7.7  8.4 / 8.7  8.8 / 8.7  8.6 / 10.2 8.6 / 11.9       (2 tiles, 1 row up to 512)
+//              2         7.5 / 6.5  7.5 / 7.7  9.1 / 7.9  9.1 / 8.8  9.3 / 8.9  9.2 / 10.3 9.5 / 12.0
+//        2300, 1 vector  8.3 / 7.9  8.4 / 9.4  8.6 / 10.2 8.6 / 10.7 8.7 / 11.0 8.7 / 12.9 10.7 / 14.7      (3 tiles, 2 rows up to 768)
+//              2         9.0 / 8.0  9.2 / 9.6  9.2 / 10.3 9.2 / 10.8 9.2 / 11.1 9.3 / 12.8 11.5 / 14.7
+//        2700, 1 vector  8.7 / 7.9  8.6 / 9.5  10.3 / 10.4 10.3 / 10.9 10.4 / 11.2 10.6 / 13.1 10.7 / 14.8  (3 tiles, 2 rows up to 512)
+//              2         9.3 / 8.0  9.3 / 9.6  10.8 / 10.6 11.1 / 11.0 11.1 / 11.2 11.2 / 13.1 11.6 / 14.8
+//    With float32 amplitudes the walk takes 0.2 to 0.4 us less (440 groups: 2049 rows, two vectors 9.1 / 8.9; 1028: 512 rows 7.6 / 7.4).
+//    So the table decoder has rows from 440 groups on where a wave has fewer rows than a unit has tiles (two vectors and more than one row: from 480 on),
+//    from 660 on where they are as many and more than one, from 960 (two vectors: 1088) where it is one row and one tile, and from 1280 (1284) where
+//    there are more rows than tiles; beyond that the lines for other widths of the index, whose fetches
 //    take three times as long (1100 x 4096, K = 13: 11.7 / 9.3): one vector from 2^20 groups on, two from 1.5 M.
 //  - For 3 to 8 vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
 //    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows of 256;
@@ -1165,8 +1172,9 @@ bool pvq_fast8_gemv_pays(const pvq_ctx *c, const pvq_decode_args &a)
     const int64_t units = g_num_cus > 0 ? g_num_cus : 256;
     const bool tall = a.rows > 4 * units;
     if (c->index_bits == 24 && a.batch <= 2) {
-        const bool once = a.rows <= units * row_lanes(a);          // a row a wave
-        if (a.groups > 1024 || (a.groups == 1024 && (tall || (a.batch == 1 && a.rows >= units))) || (tall && once && a.groups >= 440)) return true;
+        const int64_t tiles = (a.rows + 4 * units - 1) / (4 * units), rounds = (a.rows + units * row_lanes(a) - 1) / (units * row_lanes(a));
+        const bool one = a.batch == 1;
+        if (a.groups >= (rounds < tiles ? (one || rounds == 1 ? 440 : 480) : rounds > tiles ? (one ? 1280 : 1284) : tiles > 1 ? 660 : one ? 960 : 1088)) return true;
     }
     return groups >= (a.batch == 1 || (a.batch > 8 && tall) ? 1 << 20 : 3 << 19);
 }
