@@ -180,14 +180,16 @@ def test_rows_in_eight_chunks_or_fewer(D, K, rows, cols):
     run_correct(D, K, rows, cols, seed=si.BASE_SEED + 680 + rows)
 
 
-@pytest.mark.parametrize("D,K,rows,cols,ld_extra", [
-    (8, 16, 511, 2048, 0), (8, 16, 512, 2048, 0), (8, 16, 513, 2112, 4), (16, 33, 1041, 2240, 8), (32, 60, 600, 2176, 0), (8, 16, 2048, 1984, 0),
-    (8, 16, 1024, 4096, 0), (8, 16, 1023, 4096, 0), (8, 16, 1500, 2176, 4), (16, 33, 2041, 1408, 8), (32, 60, 1290, 2752, 0),
-    (8, 16, 2049, 64, 0), (8, 16, 2100, 192, 0), (32, 60, 2180, 576, 4), (8, 5, 4100, 448, 0), (16, 33, 4112, 320, 0), (8, 16, 8200, 384, 0)])
-def test_two_panels_a_launch(D, K, rows, cols, ld_extra):
+@pytest.mark.parametrize("D,K,rows,cols,ld_extra,two", [
+    (8, 16, 511, 2048, 0, False), (8, 16, 512, 2048, 0, False), (8, 16, 513, 2112, 4, False), (16, 33, 1041, 2240, 8, False), (32, 60, 600, 2176, 0, False),
+    (8, 16, 2048, 1984, 0, True), (8, 16, 1024, 4096, 0, True), (8, 16, 1023, 4096, 0, False), (8, 16, 1500, 2176, 4, True), (16, 33, 2041, 1408, 8, True),
+    (32, 60, 1290, 2752, 0, True), (8, 16, 2049, 64, 0, None), (8, 16, 2100, 192, 0, None), (32, 60, 2180, 576, 4, True), (8, 5, 4100, 448, 0, True),
+    (16, 33, 4112, 320, 0, True), (8, 16, 8200, 384, 0, True)])
+def test_two_panels_a_launch(D, K, rows, cols, ld_extra, two):
     # the smallest work buffer has room for one panel a launch, twice as much for two (the rule's lines are at 2048 rows and at
     # 2^21 values behind the first 512 rows): the same bits, odd and even numbers of panels, the last one of 64 columns or 128, workgroups and shares with a ragged end,
-    # and nothing written behind the buffer
+    # and nothing written behind the buffer.  two: whether the larger buffer's second half, which a second launch of two panels has its t values in, is
+    # touched (None: there is no second launch)
     g = torch.Generator(device="cuda")
     g.manual_seed(si.BASE_SEED + 670 + rows)
     W0 = torch.randn((rows, cols + ld_extra), generator=g, device="cuda") * 0.02
@@ -202,8 +204,74 @@ def test_two_panels_a_launch(D, K, rows, cols, ld_extra):
         assert bool((whole[rows * size:] == 0x5A).all())
         assert torch.equal(W[:, cols:], W0[:, cols:])
         results.append(W.view(torch.int32))
+    if two is not None:
+        assert bool((whole[rows * 1024: rows * 2048] == 0x5A).all()) == (not two)
     assert torch.equal(results[0], results[1])
     assert not torch.equal(results[0], W0.view(torch.int32)) or cols <= D
+    ctx.close()
+
+
+@pytest.mark.parametrize("rows,cols", [(2100, 320), (1570, 2048)])
+@pytest.mark.parametrize("D,K,amplitude", [(8, 16, "l2"), (8, 127, "ls"), (16, 33, "ls"), (16, 58, "l2"), (32, 60, "l2"), (32, 100, "ls")])
+def test_two_panels_a_launch_with_groups_that_the_short_arithmetic_refuses(D, K, amplitude, rows, cols):
+    # both amplitudes in workgroups of 16 and of 32 rows; beside ordinary rows zeros of either sign, groups, runs of groups and rows of zeros, tiny
+    # and huge values, in the first panel of a launch, in the second and across the two, and rows of U outside the bounds.  All such rows are compared
+    # with the oracle, and ordinary ones of their workgroups
+    rng = np.random.default_rng(si.BASE_SEED + 665 + D + K)
+    W0 = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)
+    odd = np.arange(7, rows, 33)
+    for n, r in enumerate(odd):
+        g = W0[r].reshape(cols // D, D)
+        kind, at = n % 8, (n // 8 * 5) % (cols // D)
+        if kind == 0: W0[r] = 0.0
+        elif kind == 1: W0[r] = -0.0
+        elif kind == 2: g[at:] = 0.0
+        elif kind == 3: g[at: at + 1 + n % 9] *= np.float32(2.0) ** -60
+        elif kind == 4: W0[r] *= np.float32(2.0) ** (-126, -70, -52, -48, -45, -43)[n % 6]
+        elif kind == 5: W0[r] *= np.float32(2.0) ** (30, 40, 43, 44)[n % 4]
+        elif kind == 6: g[at] = 0.0; g[at, D - 1] = -0.75
+        else: W0[r, rng.random(cols) < 0.3] = -0.0
+    U = np.triu(rng.standard_normal((cols, cols)) * (0.3 / cols ** 0.5), 1).astype(np.float32)
+    U[np.diag_indices(cols)] = (0.75 + 0.5 * rng.random(cols)).astype(np.float32)
+    for i, e in ((0, -22), (9, 22), (127, -19), (130, 19), (200, -30), (255, 30)):
+        U[i] *= np.float32(2.0) ** e
+    some = np.unique(np.concatenate([odd, odd - 7, np.minimum(odd + 1, rows - 1), [rows - 1]]))
+    ref, _ = oracle.correct(W0[some], U, D, K, amplitude=amplitude, nthreads=8)
+    ctx = pvq.pvq_ctx_create(D, K)
+    ctx.set_amplitude(amplitude if amplitude == "ls" else "norm")
+    Wd, Ud = gu.to_dev_f32(W0), gu.to_dev_f32(U)
+    work = torch.full((rows * 2048,), 0x5A, dtype=torch.uint8, device="cuda")
+    pvq.pvq_correct(ctx, Wd, Ud, work=work)
+    assert not bool((work[rows * 1024:] == 0x5A).all())          # two panels a launch
+    got = Wd.cpu().numpy()[some]
+    finite = np.isfinite(ref).all(axis=1)
+    assert finite.sum() > len(some) * 0.9
+    assert np.array_equal(got[finite].view(np.uint32), ref[finite].view(np.uint32))
+    one = gu.to_dev_f32(W0)
+    pvq.pvq_correct(ctx, one, Ud, work=work[: rows * 1024])
+    fine = torch.isfinite(one).all(dim=1)
+    assert torch.equal(one[fine].view(torch.int32), Wd[fine].view(torch.int32))
+    ctx.close()
+
+
+@pytest.mark.parametrize("D,K,rows,cols", [(8, 16, 4096, 320), (8, 16, 4097, 320), (16, 33, 2049, 448), (32, 60, 4096, 384), (8, 16, 1600, 1984)])
+def test_the_library_s_own_work_buffer_with_two_panels_a_launch(D, K, rows, cols):
+    # room for four buffers up to 4096 rows: the bits of a caller's work buffer of either size
+    g = torch.Generator(device="cuda")
+    g.manual_seed(si.BASE_SEED + 675 + rows)
+    W0 = torch.randn((rows, cols), generator=g, device="cuda") * 0.02
+    U = torch.triu(torch.randn((cols, cols), generator=g, device="cuda") * (0.3 / cols ** 0.5), diagonal=1)
+    U.diagonal().copy_(0.75 + 0.5 * torch.rand((cols,), generator=g, device="cuda"))
+    ctx = pvq.pvq_ctx_create(D, K)
+    results = []
+    for size in (None, 1024, 2048):
+        W = W0.clone()
+        if size is None:
+            pvq.pvq_correct_static(ctx, W, U)
+        else:
+            pvq.pvq_correct(ctx, W, U, work=torch.empty((rows * size,), dtype=torch.uint8, device="cuda"))
+        results.append(W.view(torch.int32))
+    assert torch.equal(results[0], results[1]) and torch.equal(results[0], results[2])
     ctx.close()
 
 
@@ -233,8 +301,8 @@ def test_more_panel_workgroups_than_have_a_place(D, K, rows, cols, two):
     ctx.close()
 
 
-@pytest.mark.parametrize("rows,cols", [(200, 256), (1100, 640)])
-def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols):
+@pytest.mark.parametrize("rows,cols,size", [(200, 256, 1024), (1100, 640, 1024), (2100, 640, 2048)])
+def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols, size):
     # kernels only, all on the capturing stream; every replay must reproduce the eager result for the weights
     # then in the buffer
     D, K = 8, 16
@@ -242,7 +310,7 @@ def test_the_call_can_be_captured_in_a_graph_and_replayed(rows, cols):
     _, U = si.calibration_hessian(cols, 2 * cols, si.BASE_SEED + 561)
     Ud = gu.to_dev_f32(U)
     W = torch.empty((rows, cols), dtype=torch.float32, device="cuda")
-    work = torch.empty((rows * 1024,), dtype=torch.uint8, device="cuda")
+    work = torch.empty((rows * size,), dtype=torch.uint8, device="cuda")
 
     def fill(seed):
         W.copy_(gu.to_dev_f32(si.gaussian_weights(rows, cols, 0.02, seed=si.BASE_SEED + seed, rotate=False, bf16=False)))

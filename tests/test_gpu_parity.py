@@ -273,8 +273,8 @@ def test_decode_to_every_type_at_the_edges_of_a_wave(D, K, rows, groups):
 @pytest.mark.parametrize("D,K", [(64, 2), (64, 30), (64, 31), (64, 255), (128, 1), (128, 256), (128, 382)])
 @pytest.mark.parametrize("rows,groups", [(1, 1), (7, 9), (1024, 5), (569, 9)])
 def test_long_groups_both_decoders(D, K, rows, groups):
-    # a wave per group up to 3584, 4608 or 5120 groups, a lane per group beyond (5121: a last wave with one group); rows of
-    # thresholds just shorter and just longer than a window, points kept as bytes and as int16
+    # a wave per group up to 2048 to 5120 groups, by the integers' width and the pulses, a lane per group beyond (5121: a last wave with
+    # one group; the lines themselves are in test_gpu_long_rows.py); rows of thresholds just shorter and just longer than a window, points kept as bytes and as int16
     X = si.adversarial_groups(1 << 13, D, seed=K)[:rows * groups].reshape(rows, groups * D)
     run_long_groups(np.ascontiguousarray(X), D, K)
 
@@ -283,7 +283,7 @@ def test_long_groups_both_decoders(D, K, rows, groups):
                                              (64, 127, 419, 11), (64, 150, 4609, 1), (64, 151, 4609, 1), (64, 150, 5121, 1), (64, 151, 5121, 1), (64, 151, 640, 8),
                                              (64, 196, 23, 201), (64, 230, 4608, 1), (64, 231, 717, 5)])
 def test_long_groups_at_the_lines_between_the_decoders(D, K, rows, groups):
-    # the last number of groups that a wave each decodes and the first that lanes do, by the integers' width and by the pulses;
+    # around the lines of an earlier form of the decoder with lanes (the present ones are in test_gpu_long_rows.py), with several groups a row;
     # the last pulses whose rows go through LDS and the first that are read from device memory, with integers of 8 and 12 words
     X = si.activation_matrix(rows, D * groups, seed=D + K + rows, rotate=False, bf16=False)
     odd = si.adversarial_groups(1 << 10, D, seed=K)
@@ -293,7 +293,7 @@ def test_long_groups_at_the_lines_between_the_decoders(D, K, rows, groups):
 
 @pytest.mark.parametrize("K,times", [(127, 61), (127, 62), (150, 69), (151, 68), (160, 69), (196, 68), (255, 69), (256, 69)])
 def test_long_groups_at_the_lines_of_large_batches(K, times):
-    # 613 x 7 groups of 64, repeated: up to 262144 and beyond rows in LDS or not, up to 294912 and beyond points as int16 values or
+    # 613 x 7 groups of 64, repeated: up to 262144 and beyond rows in LDS or not (from K = 121 on; beyond 393216 in test_gpu_long_rows.py), up to 294912 and beyond points as int16 values or
     # as bytes (with K = 256 int16 always).  The block by itself, decoded by a wave or a lane per group, equals the oracle's.
     rows, groups, D = 613, 7, 64
     X = si.activation_matrix(rows, D * groups, seed=K, rotate=False, bf16=False)
@@ -613,6 +613,42 @@ def test_rotation_and_encoding_with_sixteen_values_a_lane(rows, cols, block, bit
     packed = pvq.pvq_rotate_encode(ctx, X[some].contiguous(), block, sgd)
     rotated = oracle.hadamard_rows(X[some].float().cpu().numpy(), block, sg)
     gu.assert_encode_equal(packed, oracle.encode(rotated, D, K, bits, oe, nthreads=8, amplitude=amplitude), check_pulses=False)
+    ctx.close()
+
+
+@pytest.mark.parametrize("bits,bf16,amplitude", [(0, False, "l2"), (2, False, "l2"), (8, True, "l2"), (0, True, "ls"), (4, False, "ls")])
+@pytest.mark.parametrize("rows,cols,block", [(40, 4096, 64), (40, 8192, 128), (40, 6144, 256), (800, 8192, 512), (40, 16384, 1024), (800, 8192, 2048), (40, 8192, 8192)])
+def test_rotation_and_encoding_with_sixteen_values_a_lane_of_values_at_the_ends_of_the_type(rows, cols, block, bits, bf16, amplitude):
+    # infinities, NaN, rows whose sums of squares overflow, vanish or are subnormal, single values, zeros of either sign: rotation and encoding in
+    # two calls give the same, NaN for NaN; and the oracle's codes of the rows without infinities and NaN
+    D, K = 8, 16
+    rng = np.random.default_rng(rows + cols + block + bits)
+    X0 = (rng.standard_normal((rows, cols)) * 0.02).astype(np.float32)
+    X0[1, 5], X0[2, block - 1], X0[3, cols - 1] = np.inf, -np.inf, np.nan
+    X0[4] *= np.float32(2.0) ** 125                                # rotated and squared beyond the type
+    X0[5] *= np.float32(2.0) ** 64
+    for r, e in zip(range(6, 20), (-142, -130, -120, -90, -72, -66, -60, -45, -36, -33, -30, -27, -24, 40)):
+        X0[r] *= np.float32(2.0) ** e
+    X0[20], X0[21] = 0.0, -0.0
+    X0[22, 1:] = 0.0
+    X0[23, block:] = 0.0
+    X0[24, : cols // 2] *= np.float32(2.0) ** -30
+    X = torch.from_numpy(X0).cuda().to(torch.bfloat16 if bf16 else torch.float32)
+    sg = rng.integers(0, 2, size=cols).astype(np.uint8)
+    sgd = torch.from_numpy(sg).cuda()
+    ctx, oe, _ = gu.make_ctx(D, K, bits, cols // D)
+    ctx.set_amplitude({"l2": "norm", "ls": "ls"}[amplitude])
+    packed = pvq.pvq_rotate_encode(ctx, X, block, sgd)
+    two = pvq.pvq_encode(ctx, pvq.pvq_hadamard(X, block, sgd, out_dtype=torch.float32))
+    assert torch.equal(two.index, packed.index)
+
+    def same(a, b):
+        return torch.equal(a, b) if a.dtype != torch.float32 else bool(((a == b) | (a.isnan() & b.isnan())).all())
+    assert same(two.scale, packed.scale) and (not bits or same(two.rownorm, packed.rownorm))
+    some = [0] + list(range(6, 26)) + [rows - 1]
+    part = pvq.pvq_rotate_encode(ctx, X[some].contiguous(), block, sgd)
+    rotated = oracle.hadamard_rows(X[some].float().cpu().numpy(), block, sg)
+    gu.assert_encode_equal(part, oracle.encode(rotated, D, K, bits, oe, nthreads=8, amplitude=amplitude), check_pulses=False)
     ctx.close()
 
 
