@@ -483,25 +483,29 @@ def main():
         ctxc = pvq.pvq_ctx_create(8, K)
         for cr, cc in ((1024, COLS), (8192, COLS), (ROWS, COLS)):
             Wc0 = torch.randn((cr, cc), generator=gcor, device=dev) * 0.02
-            work = torch.empty((cr * 1024,), dtype=torch.uint8, device=dev)
+            # the work buffer that the binding makes (four panels' t values: two panels a launch), and the smallest that the call takes
+            work = torch.empty((cr * 2048,), dtype=torch.uint8, device=dev)
             Wc = Wc0.clone()
-            pvq.pvq_correct(ctxc, Wc, Uc, work=work); torch.cuda.synchronize()
-            ms = []
-            for _ in range(3):
-                Wc.copy_(Wc0); torch.cuda.synchronize()
-                e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-                e0.record(); pvq.pvq_correct(ctxc, Wc, Uc, work=work); e1.record(); torch.cuda.synchronize()
-                ms.append(e0.elapsed_time(e1))
-            t_ms = sorted(ms)[1]
+            t_small, t_ms = (0.0, 0.0)
+            for size in (1024, 2048):
+                part = work[: cr * size]
+                pvq.pvq_correct(ctxc, Wc, Uc, work=part); torch.cuda.synchronize()
+                ms = []
+                for _ in range(3):
+                    Wc.copy_(Wc0); torch.cuda.synchronize()
+                    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                    e0.record(); pvq.pvq_correct(ctxc, Wc, Uc, work=part); e1.record(); torch.cuda.synchronize()
+                    ms.append(e0.elapsed_time(e1))
+                t_small, t_ms = t_ms, sorted(ms)[1]
             flop = float(cr) * cc * cc          # one multiply-add per element and earlier column: 2 x rows x cols^2 / 2
-            ex[f"correct_{cr}x{cc}"] = {"ms": round(t_ms, 3), "TFLOPs": round(flop / t_ms / 1e9, 2),
+            ex[f"correct_{cr}x{cc}"] = {"ms": round(t_ms, 3), "smallest_work_buffer_ms": round(t_small, 3), "TFLOPs": round(flop / t_ms / 1e9, 2),
                                         "frac_of_fp32_matrix_peak": round(flop / t_ms / 1e9 / 157.3, 3),
                                         "gpu_rows_per_s": round(cr / t_ms * 1e3, 1)}
             if cr == 8192:
                 w8, u8 = Wc0[:8].cpu().numpy(), Uc.cpu().numpy()
                 t0 = time.perf_counter(); oracle.correct(w8, u8, 8, K); t_cpu = time.perf_counter() - t0
                 ex[f"correct_{cr}x{cc}"]["oracle_one_core_rows_per_s"] = round(8 / t_cpu, 3)
-            del Wc0, Wc, work
+            del Wc0, Wc, work, part
         ctxc.close()
         del Uc
         result["extras"] = ex

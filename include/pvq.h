@@ -209,8 +209,9 @@ int pvq_encode(const pvq_ctx *ctx, const void *W, int dtype, int64_t rows, int64
  *   U      device, float32 [cols][ldu], 16-byte aligned, ldu >= cols, ldu a multiple of 4; only the upper
  *          triangle is used (what lies below the diagonal may be anything).  Not modified.
  *   work   device, 16-byte aligned scratch of at least pvq_correct_work_bytes(rows) bytes (two buffers of 128
- *          floats per row), owned by the caller, contents undefined afterwards.  With twice as much (work_bytes says so)
- *          a launch takes two panels of 128 columns instead of one wherever that is faster; the results are the same.
+ *          floats per row), owned by the caller, contents undefined afterwards.  Where work_bytes is at least twice that,
+ *          a launch takes two panels of 128 columns instead of one wherever that is faster (1.51 against 1.58 ms for 1024 x 8192, 5.07
+ *          against 5.56 for 8192 x 8192); the results are the same.
  *
  * float32 throughout; q = (s / sqrt(sum y^2)) * y; the substitution and the updates are fused multiply-adds
  * applied one at a time in the order of the rows of U, so the result does not depend on the launch shape.

@@ -89,8 +89,8 @@ def test_prefill_batch_of_activations_long_groups():
 
 def test_error_correction_of_a_square_projection():
     # Sec. 3.3 Step 6 on 8192 x 8192 (the attention projections' shape), in the configuration that the
-    # benchmark's extras time: 64 panels, each launch with 256 panel workgroups in front of the update
-    # tasks.  Rows are independent, so the oracle corrects a sample of rows (first and last rows of panel
+    # benchmark's extras time: 64 panels in 32 launches, each with 256 panel workgroups in front of as many for the
+    # updates.  Rows are independent, so the oracle corrects a sample of rows (first and last rows of panel
     # workgroups and of update tasks, and rows in between) and those must match bit for bit.  The factor is a seeded well-conditioned upper triangular matrix (any such matrix is the
     # factor of some inverse Hessian); the arithmetic, not the statistics, is what is compared here.
     rows = cols = 8192
