@@ -1308,7 +1308,8 @@ hipError_t pvq_wide_launch_rotate_encode(const pvq_ctx *c, const pvq_encode_args
 //   D = 64,  K = 40      16     19     19     23     23     23     23     23     23     27     27      23      (4)
 //            K = 96      16     20     20     25     25     30     31                                  26      (8)
 //            K = 127     16     20     20     25     25     30     31     35     37     39     40      31      (8)
-//            K = 150     16     20     20     25     25     30     31     35     37     39     40      41      (8)
+//            K = 143     16     20     20     25     25     30     31     35     37     39     40      39      (8)
+//            K = 150     16     20     20     25     25     30     31     35     37     39     40      42      (8; 4800 groups 42 / 42)
 //            K = 160     5120 groups: 43 / 46                                                                  (8; lanes: device memory)
 //            K = 220     2048 24, 3520 40, 4096 43, 4608 50 / lanes 47 to 48                                   (12; the same)
 //            K = 255     2048 30, 3520 45, 4096 50, 4608 57 / 48                                               (12; the same)
@@ -1316,7 +1317,7 @@ static int64_t few_groups(const pvq_ctx *c)
 {
     if (c->words == 4) return 4096;
     if (c->D == 128) return c->words == 8 ? 3072 : c->K > 255 ? 3584 : c->words == 12 ? 2048 : 2560;
-    if (c->words == 8) return c->K <= 112 ? 3072 : c->K <= 135 ? 3584 : c->K <= 150 ? 4352 : 5120;
+    if (c->words == 8) return c->K <= 112 ? 3072 : c->K <= 135 ? 3584 : c->K <= 143 ? 4352 : c->K <= 150 ? 4800 : 5120;
     return c->K <= 230 ? 4608 : 3584;
 }
 

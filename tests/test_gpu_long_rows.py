@@ -16,7 +16,7 @@ torch = pytest.importorskip("torch")
 # windows; half of the groups with nearly all pulses in a few coordinates, so that places lie outside the window
 @pytest.mark.parametrize("D,K,groups", [(128, 3, 4096), (128, 28, 4097), (128, 84, 3072), (128, 84, 3073), (128, 187, 2048), (128, 187, 2049),
                                         (128, 188, 2561), (128, 255, 2560), (128, 255, 2561), (64, 43, 4097), (64, 44, 3072), (64, 112, 3073),
-                                        (64, 113, 3585), (64, 136, 4352), (64, 136, 4353), (64, 150, 4353)])
+                                        (64, 113, 3585), (64, 136, 4352), (64, 136, 4353), (64, 143, 4353), (64, 144, 4353), (64, 150, 4353), (64, 150, 4800), (64, 150, 4801)])
 def test_long_groups_where_lanes_take_over(D, K, groups):
     X = si.activation_matrix(groups, D, seed=D + K + groups, rotate=False, bf16=False)
     odd = si.adversarial_groups(1 << 10, D, seed=K)
