@@ -18,7 +18,7 @@
 //             1.2 for the panel's part of U, 10.5 for 16 groups of 8 (2.4, 0.5 and 10.5 with 16 rows); with two 44 us for both.
 //     update  (all others) the launch before's panels onto all columns behind the launch's own: 128 or 256 multiply-adds per
 //             element, in the same order, W read and written once a launch.
-// Bound: float32 matrix instructions (152 TFLOP/s in registers with any number of waves), and they keep other waves of their SIMD from
+// Bound: float32 matrix instructions (155 TFLOP/s in registers with any number of waves), and they keep other waves of their SIMD from
 // the vector unit while they run (a wave of them beside a wave of vector instructions takes the sum of both times, whatever
 // the priorities; beside bfloat16 ones it is the longer of both).  So the chain of panels costs the updates what it issues, and there is
 // little to gain from more waves.  What counts is that no wave waits for its own stores, that a launch's updates start and end

@@ -1153,7 +1153,7 @@ bool pvq_fast8_gemv_usable(const pvq_ctx *c, const pvq_decode_args &a)
 //    With float32 amplitudes the walk takes 0.2 to 0.4 us less (440 groups: 2049 rows, two vectors 9.1 / 8.9; 1028: 512 rows 7.6 / 7.4).
 //    So the table decoder has rows from 440 groups on where a wave has fewer rows than a unit has tiles (two vectors and more than one row: from 480 on),
 //    from 660 on where they are as many and more than one, from 960 (two vectors: 1088) where it is one row and one tile, and from 1280 (1284) where
-//    there are more rows than tiles; beyond that the lines for other widths of the index, whose fetches
+//    there are more rows than tiles; beyond that (1024 x 8224, one vector, 8.6 / 7.8, but 3073 x 2816 8.4 / 9.5) the lines for other widths of the index, whose fetches
 //    take three times as long (1100 x 4096, K = 13: 11.7 / 9.3): one vector from 2^20 groups on, two from 1.5 M.
 //  - For 3 to 8 vectors one decoder or the other is ahead by up to 3 us up to 1.5 M groups (1025 x 8704, 8 vectors: 15.7 / 13.6); for 9 and more the
 //    table decoder is by 0.2 to 5 us from 2^20 groups on, where the walk has more than one tile of four rows for a unit (1024 rows of 256;
