@@ -210,7 +210,7 @@ int pvq_encode(const pvq_ctx *ctx, const void *W, int dtype, int64_t rows, int64
  *          triangle is used (what lies below the diagonal may be anything).  Not modified.
  *   work   device, 16-byte aligned scratch of at least pvq_correct_work_bytes(rows) bytes (two buffers of 128
  *          floats per row), owned by the caller, contents undefined afterwards.  Where work_bytes is at least twice that,
- *          a launch takes two panels of 128 columns instead of one wherever that is faster (1.51 against 1.58 ms for 1024 x 8192, 5.07
+ *          a launch takes two panels of 128 columns instead of one wherever that is faster (1.51 against 1.57 ms for 1024 x 8192, 5.07
  *          against 5.56 for 8192 x 8192); the results are the same.
  *
  * float32 throughout; q = (s / sqrt(sum y^2)) * y; the substitution and the updates are fused multiply-adds

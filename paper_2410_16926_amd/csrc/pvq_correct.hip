@@ -32,9 +32,9 @@
 // element one by one, k ascending, each a fused multiply-add (measured bit for bit against fmaf over random, cancelling,
 // tied, subnormal and non-finite operands).
 // 8192 x 8192 in groups of 8 5.07 ms, 28672 x 8192 17.8, 8192 x 4096 1.52, 4096 x 4096 1.05, 1024 x 8192 1.51; one panel a launch, for which the smallest
-// work buffer has room, 5.56, 19.7, 1.61, 1.10, 1.58.  Before, with one panel a launch, tasks of 64 columns and 128 to 1024 rows and waves
+// work buffer has room, 5.56, 19.7, 1.61, 1.10, 1.57.  Before, with one panel a launch, tasks of 64 columns and 128 to 1024 rows and waves
 // that waited for their stores after every 16 rows, 6.10, 21.2, 1.74, 1.10, 1.55 (so with that work buffer 7 to 10 million values in groups of 8 take
-// up to 2.5 % longer now); with tiles of 128 x 128 whose workgroups moved in step 6.6 ms.
+// up to 1.5 % longer now); with tiles of 128 x 128 whose workgroups moved in step 6.6 ms.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -545,7 +545,9 @@ __device__ inline void panel_role(float *__restrict__ W, const float *__restrict
 // under a condition: memory operations complete in order, so a wait for a load that may or may not have stores behind it would
 // wait for the stores too (update alone, 8192 rows x 3968 columns: 87 us so, now 76).  Items of 32 rows, an operand of U for eight
 // instructions, take longer (8192 x 8192 5.02 / 5.17 ms).
-template <int PANELS>
+// IN_ORDER: the instructions stay as they are written.  Not where a wave mostly has one item, with one panel a launch of up to 2048 rows in
+// groups of 8 (1024 x 8192 1582 / 1568 us, 1280 x 8192 1719 / 1697; 3000 x 4096 1009 / 1040).
+template <int PANELS, bool IN_ORDER>
 __device__ inline void update_role(float *__restrict__ W, const float *__restrict__ U, const t_buffers<PANELS> &T, const correct_shape &a,
                                    int panel, int64_t col0, int64_t row0, int64_t row1, float *lds)
 {
@@ -614,7 +616,7 @@ __device__ inline void update_role(float *__restrict__ W, const float *__restric
                 if (i < kPieces) fetch_piece(r, i);
                 else if constexpr (kMore) fetch_piece(next, i - kPieces);
             }
-            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (IN_ORDER) __builtin_amdgcn_sched_barrier(0);
         }
         float *p = place(r);
 #pragma unroll
@@ -661,7 +663,7 @@ __global__ __launch_bounds__(kThreads, PANELS > 1 ? 2 : D == 32 ? 3 : 4) void co
         const uint32_t end = at + each + (share < rest ? 1u : 0u);
         while (at < end) {
             const uint32_t tile = at / steps, from = at - tile * steps, to = std::min(steps, from + end - at);
-            update_role<PANELS>(W, U, T, a, panel - PANELS, (int64_t)(panel + PANELS) * kPanelCols + (int64_t)tile * kTileCols,
+            update_role<PANELS, PANELS != 1 || D != 8 || ROWS != 16>(W, U, T, a, panel - PANELS, (int64_t)(panel + PANELS) * kPanelCols + (int64_t)tile * kTileCols,
                                 (int64_t)(first + from) * kStepRows, std::min<int64_t>((int64_t)(first + to) * kStepRows, a.rows), lds);
             at += to - from;
             if (at < end) __syncthreads();
